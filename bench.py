@@ -248,8 +248,8 @@ def radices_of(cfg, P, override=""):
 
 def kernel_name(stage, gran, exact, max_block_bytes=None):
     et = "true" if exact else "false"
-    if stage == "hop" and max_block_bytes is not None and 0 < max_block_bytes <= 64:
-        return "tuna::k_hop_small<%d>" % (4 if gran >= 4 else 1)      # one thread per block when all blocks fit into 64 bytes
+    if stage == "hop" and max_block_bytes is not None and 0 < max_block_bytes <= 256:      # short blocks
+        return "tuna::k_hop_direct<%d, %s, false>" % (1 if max_block_bytes <= 16 else 4 if max_block_bytes <= 64 else 16, et)
     return {"pack": "tuna::k_copy<0, %d, %s>" % (gran, et), "exchange": "tuna::k_copy<1, 16, false>",
             "unpack": "tuna::k_copy<2, %d, %s>" % (min(gran, 16), et), "hop": "tuna::k_copy<3, %d, %s>" % (gran, et),
             "tiled_hop": "tuna::k_copy_tiled<%d, 4>" % (16 if gran >= 16 else 4),

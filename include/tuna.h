@@ -386,8 +386,9 @@ int tuna_debug_phase_sizes(const void* sendbuf, const int32_t* sendcounts, const
  * block (the share of rank distances whose digit is non-zero, summed over the digit positions), moving
  * blocks = the same count in blocks; one set of constants for three-stage phases and one for one-kernel
  * hops; T in the paper's slots adds to the byte term by how empty the slots are (mean block / M).  When no
- * block exceeds 64 bytes the one-kernel hops run a kernel of their own (one thread per block), whose
- * blocks and bytes are priced by constants of their own, c5 and c6, in place of c4 and c3.
+ * block exceeds 64 bytes the one-kernel hops run a kernel of their own (1 or 4 lanes per block), whose
+ * blocks and bytes are priced by constants of their own, c5 and c6, in place of c4 and c3; such a block counts
+ * four times in a schedule of several phases, where its size has to be exchanged and its place in T scanned.
  *   tuna_calibrate   times about sixty immediate calls of dense synthetic problems on the current
  *                    device (a few hundred milliseconds; allocates up to about 8 GiB and frees it;
  *                    synchronises) and fits the constants to them.  Without it the constants are the

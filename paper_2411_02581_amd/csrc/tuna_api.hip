@@ -716,6 +716,10 @@ bool too_large(int P, const Status& hs) {
     return std::min(by_m, by_all) >= (1ull << 31);
 }
 
+// One-kernel phases of problems whose blocks are all short run k_hop_direct (one lane resolves a block, 1, 4 or 16
+// lanes move it) instead of the byte-balanced engine.
+bool small_blocks(const Prepared& pr) { return pr.max_count > 0 && pr.max_count <= kDirectMaxBytes; }
+
 constexpr int kTiledMinMeanBytes = 700;    // see prepare_sizes
 constexpr int kTiledMinMeanBytesIntoT = 512;
 
@@ -749,7 +753,7 @@ int prepare_sizes(Prepared& pr, int dense_option, hipStream_t s, Status& hs, boo
     // The destination-tiled hop: one-kernel phases over all rounds at once, receive regions dense (validation
     // flag), word- or chunk-granular data (whole-line data is as fast in the copy engine, byte-granular data
     // would need the pieces at block edges put together byte by byte), blocks that are not all tiny (those
-    // have k_hop_small).
+    // have k_hop_direct).
     // Into R it pays when the blocks are mostly pieces inside blocks, not edges: measured, 1 KiB blocks gain 8 %
     // per call at r = P and 512-byte blocks lose 2 %; Zipf sizes with four blocks in five under 256 bytes lose 11 %
     // in their last phase.  Hence, for a schedule's last phase (all its blocks are final), a mean block of at least
@@ -758,7 +762,7 @@ int prepare_sizes(Prepared& pr, int dense_option, hipStream_t s, Status& hs, boo
     // mean block of 256 bytes, and lose 2 to 8 % below that: a mean block of kTiledMinMeanBytesIntoT.
     const unsigned long long P2 = (unsigned long long)P * (unsigned long long)P;
     pr.tiled = pr.fused && !pr.staggered && pr.block_count == 0 && !(hs.flags & 8u) && (pr.gran == 4 || pr.gran == 16) &&
-               hs.max_count > kSmallBlockBytes && !pr.dp->host.phases.empty() &&
+               !small_blocks(pr) && !pr.dp->host.phases.empty() &&
                hs.total_bytes >= (unsigned long long)kTiledMinMeanBytesIntoT * P2;
     pr.tiled_final = pr.tiled && hs.total_bytes >= (unsigned long long)kTiledMinMeanBytes * P2 && hs.short_blocks * 4 <= P2;
     pr.ds = data_sizes_for(pr.dp->host, hs.max_count, hs.total_chunks, pr.fused, pr.staggered, pr.exact_t, pr.t_chunks,
@@ -799,10 +803,6 @@ int prepare_call(Ctx& c, const Options& opt, const void* sendbuf, const int32_t*
     pr.block_count = opt.block_count;
     return prepare_sizes(pr, opt.t_layout, s, hs, empty);
 }
-
-// One-kernel phases of problems whose blocks all fit into 64 bytes run k_hop_small (one thread per block)
-// instead of the byte-balanced engine.
-bool small_blocks(const Prepared& pr) { return pr.max_count > 0 && pr.max_count <= kSmallBlockBytes; }
 
 // Phases that run as the destination-tiled hop: the last one (all its blocks are final) when the blocks are
 // mostly interior, and with T in exact size the ones before it -- the blocks a rank stores into T lie back to
@@ -847,7 +847,7 @@ int launch_tiled_metadata(const Prepared& pr, size_t i, const int32_t* cur, int3
         PhaseLayoutArgs m{};
         m.cur = cur; m.nxt = nxt; m.zt = pr.dp->d_zt[i]; m.seg = pr.dp->d_seg[i]; m.nseg = ph.nseg;
         m.P = P; m.Q = pr.Q; m.N = pr.N; m.dim = ph.dim; m.rx = (int)ph.rx;
-        m.Ls = Ls; m.Lr = Lr; m.want_send = 0; m.want_tbound = 1; m.x = exact_t_of(pr, i);
+        m.Ls = Ls; m.Lr = Lr; m.want_chunks = 1; m.want_send = 0; m.want_tbound = 1; m.x = exact_t_of(pr, i);
         m.rank_bytes = pr.rank_bytes;
         m.phase_bytes = &pr.sb.d_status->phase_bytes[i]; m.phase_chunks = &pr.sb.d_status->phase_chunks[i];
         m.phase_units = pr.sb.d_status->phase_units[i];
@@ -882,7 +882,7 @@ int launch_phase_metadata(const Prepared& pr, size_t i, const int32_t* cur, int3
     PhaseLayoutArgs m{};
     m.cur = cur; m.nxt = nxt; m.zt = pr.dp->d_zt[i]; m.seg = pr.dp->d_seg[i]; m.nseg = ph.nseg;
     m.P = pr.P; m.Q = pr.Q; m.N = pr.N; m.dim = ph.dim; m.rx = (int)ph.rx;
-    m.Ls = Ls; m.Lr = Lr; m.want_send = one_kernel ? 0 : 1;
+    m.Ls = Ls; m.Lr = Lr; m.want_chunks = 1; m.want_send = one_kernel ? 0 : 1;
     if (pr.exact_t) { m.want_tbound = 1; m.x = exact_t_of(pr, i); }
     m.rank_bytes = pr.rank_bytes;
     m.phase_bytes = &pr.sb.d_status->phase_bytes[i]; m.phase_chunks = &pr.sb.d_status->phase_chunks[i];
@@ -898,8 +898,8 @@ int launch_phase_metadata(const Prepared& pr, size_t i, const int32_t* cur, int3
     return launch_resolve(pr, i, nxt, hop, s);
 }
 
-// one-kernel phase: where every block comes from and goes to, once per phase instead of once per wave
-int launch_resolve(const Prepared& pr, size_t i, const int32_t* nxt, const HopDev& hop, hipStream_t s) {
+// what a phase's blocks are resolved from
+ResolveArgs resolve_args(const Prepared& pr, size_t i, const int32_t* nxt, const HopDev& hop) {
     const PhaseHost& ph = pr.dp->host.phases[i];
     ResolveArgs ra{};
     ra.nxt = nxt; ra.seg = pr.dp->d_seg[i]; ra.nseg = ph.nseg;
@@ -910,6 +910,64 @@ int launch_resolve(const Prepared& pr, size_t i, const int32_t* nxt, const HopDe
     ra.x = exact_t_of(pr, i);
     ra.hop = hop;
     ra.exact_sizes = small_blocks(pr) ? 1 : 0;
+    return ra;
+}
+
+template <int LPB, bool TALL, int STREAM>
+void launch_direct_as(const DirectArgs& a, dim3 grid, bool exact, hipStream_t s) {
+    if (!a.part) hipLaunchKernelGGL((k_hop_direct<LPB, TALL, STREAM, false, true>), grid, dim3(256), 0, s, a);
+    else if (exact) hipLaunchKernelGGL((k_hop_direct<LPB, TALL, STREAM, true, false>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((k_hop_direct<LPB, TALL, STREAM, false, false>), grid, dim3(256), 0, s, a);
+}
+template <bool TALL>
+void launch_direct_shape(int lpb, int gran, const DirectArgs& a, dim3 grid, bool exact, hipStream_t s) {
+    if (lpb == 1) launch_direct_as<1, TALL, 0>(a, grid, exact, s);
+    else if (lpb == 4) {
+        if (gran >= 16) launch_direct_as<4, TALL, 1>(a, grid, exact, s);
+        else launch_direct_as<4, TALL, 0>(a, grid, exact, s);
+    } else if (gran == 128) launch_direct_as<16, TALL, 2>(a, grid, exact, s);
+    else if (gran == 16) launch_direct_as<16, TALL, 1>(a, grid, exact, s);
+    else launch_direct_as<16, TALL, 0>(a, grid, exact, s);
+}
+
+int direct_lpb(const Prepared& pr) { return pr.max_count <= 16 ? 1 : (pr.max_count <= 64 ? 4 : 16); }
+bool direct_tall(const PhaseHost& ph) { return (long long)ph.nz * 16 > ph.nseg; }
+// Workgroup columns and steps per workgroup over `nseg` segments of a phase: one step each while that gives no more than 8192 workgroups (four
+// per resident slot of the device), then up to 8 steps; and the rows of partial sums that such a launch stores.
+unsigned direct_columns(const Prepared& pr, const PhaseHost& ph, int nseg, int* iters) {
+    const DirectShape sh = direct_shape(direct_lpb(pr), direct_tall(ph));
+    const int segs = direct_segs(sh);
+    const long long steps = (nseg + segs - 1) / segs, rows = (pr.P + direct_ranks(sh) - 1) / direct_ranks(sh);
+    *iters = (int)std::max(1LL, std::min(8LL, steps * rows / 8192));
+    return (unsigned)((steps + *iters - 1) / *iters);
+}
+unsigned direct_rows(const Prepared& pr, const PhaseHost& ph) {
+    int iters = 0;
+    return direct_columns(pr, ph, ph.nseg, &iters) * (unsigned)(4 / direct_shape(direct_lpb(pr), direct_tall(ph)).waves_r);
+}
+
+// The payload of a phase of short blocks: from the hop arrays (nxt and part null), or resolved in the same kernel from
+// the block sizes after the phase (nxt) or the receive counts (by_source), with partial sums into `part`.
+int launch_direct(const Prepared& pr, size_t i, const int32_t* nxt, const HopDev& hop, int seg_lo, int seg_hi,
+                  const int32_t* by_source, uint2* part, hipStream_t s) {
+    if (seg_hi <= seg_lo) return TUNA_OK;
+    const PhaseHost& ph = pr.dp->host.phases[i];
+    DirectArgs a{};
+    a.r = resolve_args(pr, i, nxt, hop);
+    a.by_source = by_source; a.T = pr.T; a.seg_lo = seg_lo; a.seg_hi = seg_hi; a.part = part;
+    const unsigned cols = direct_columns(pr, ph, seg_hi - seg_lo, &a.iters);
+    const int lpb = direct_lpb(pr), ranks = direct_ranks(direct_shape(lpb, direct_tall(ph)));
+    const dim3 grid(cols, (unsigned)((pr.P + ranks - 1) / ranks));
+    if (direct_tall(ph)) launch_direct_shape<true>(lpb, pr.gran, a, grid, pr.exact_kernels, s);
+    else launch_direct_shape<false>(lpb, pr.gran, a, grid, pr.exact_kernels, s);
+    HIPCHK(hipGetLastError());
+    return TUNA_OK;
+}
+
+// one-kernel phase: where every block comes from and goes to, once per phase instead of once per wave
+int launch_resolve(const Prepared& pr, size_t i, const int32_t* nxt, const HopDev& hop, hipStream_t s) {
+    const PhaseHost& ph = pr.dp->host.phases[i];
+    const ResolveArgs ra = resolve_args(pr, i, nxt, hop);
     if (ph.nz >= kResolveTile) {     // many rounds: neighbouring segments come from neighbouring senders
         constexpr int per = 256 / kResolveTile;
         const dim3 grid((unsigned)((ph.nseg + per - 1) / per), (unsigned)((pr.P + kResolveTile - 1) / kResolveTile));
@@ -1053,10 +1111,8 @@ int launch_phase_data(const Prepared& pr, size_t i, const LayoutDev& Ls, const L
         }
         int rc;
         if (phase_is_one_kernel(pr, ph) && small_blocks(pr)) {
-            const dim3 grid((unsigned)((a.seg_hi - a.seg_lo + 255) / 256), (unsigned)pr.P);
-            if (pr.gran >= 4) hipLaunchKernelGGL(k_hop_small<4>, grid, dim3(256), 0, s, hop, pr.T, a.seg_lo, a.seg_hi);
-            else hipLaunchKernelGGL(k_hop_small<1>, grid, dim3(256), 0, s, hop, pr.T, a.seg_lo, a.seg_hi);
-            HIPCHK(hipGetLastError());
+            rc = launch_direct(pr, i, nullptr, hop, a.seg_lo, a.seg_hi, nullptr, nullptr, s);
+            if (rc != TUNA_OK) return rc;
             mark(pr.ctx, s, kCatPack, (int)i);
             continue;
         }
@@ -1134,6 +1190,39 @@ size_t one_pass_meta_bytes(const Prepared& pr) {
            (hld ? hop_bytes_for(pr.P, hld) : 0) + self_meta_bytes(pr);
 }
 
+// An immediate call whose phases are all one-kernel hops of short blocks, all rounds of a phase at once: done in one
+// pass whatever its payload, with k_hop_direct resolving the blocks (tested for room: the partial sums of all phases
+// take the place of the hop arrays).
+bool runs_direct(const Prepared& pr) {
+    if (!pr.fused || pr.staggered || pr.block_count > 0 || !small_blocks(pr) || pr.dp->host.phases.empty()) return false;
+    size_t rows = 0;
+    for (const auto& ph : pr.dp->host.phases) rows += direct_rows(pr, ph);
+    return rows <= (size_t)max_hop_ld(pr);
+}
+
+// The metadata of a phase that runs as k_hop_direct: the size exchange, and with exact-size T the places of the
+// blocks the phase stores there.
+int launch_direct_metadata(const Prepared& pr, size_t i, const int32_t* cur, int32_t* nxt, hipStream_t s) {
+    if (pr.sizes_direct) return TUNA_OK;
+    const PhaseHost& ph = pr.dp->host.phases[i];
+    const int P = pr.P;
+    hipLaunchKernelGGL(k_size_exchange, dim3((unsigned)((P + 255) / 256), (unsigned)((P + kExchangeRanks - 1) / kExchangeRanks)),
+                       dim3(256), 0, s, cur, nxt, pr.dp->d_zt[i], P, pr.Q, pr.N, ph.dim, (int)ph.rx);
+    HIPCHK(hipGetLastError());
+    PhaseLayoutArgs m{};
+    m.x = exact_t_of(pr, i);
+    if (!pr.exact_t || m.x.ncls == 0) return TUNA_OK;
+    m.cur = cur; m.nxt = nxt; m.zt = pr.dp->d_zt[i]; m.seg = pr.dp->d_seg[i]; m.nseg = ph.nseg;
+    m.P = P; m.Q = pr.Q; m.N = pr.N; m.dim = ph.dim; m.rx = (int)ph.rx;
+    m.want_tbound = 1;
+    hipLaunchKernelGGL(k_phase_layout, dim3(P), dim3(kScanThreads), 0, s, m);
+    HIPCHK(hipGetLastError());
+    hipLaunchKernelGGL(k_layout_base, dim3(m.x.ncls), dim3(kScanThreads), 0, s, P, LayoutDev{}, LayoutDev{}, 0, (unsigned long long*)nullptr, -1,
+                       m.x, (const unsigned long long*)nullptr, (unsigned long long*)nullptr, (unsigned int*)nullptr);
+    HIPCHK(hipGetLastError());
+    return TUNA_OK;
+}
+
 // A call in one pass: rotation, the own blocks, then per digit phase its metadata kernels followed at
 // once by its payload kernels, launched for an upper bound of work.  `mbase` holds one_pass_meta_bytes,
 // `dbase` pr.ds.total bytes.
@@ -1162,12 +1251,14 @@ int run_one_pass(Prepared& pr, void* mbase, size_t mbytes, void* dbase, hipStrea
 
     // ---- initial rotation (index only) and the own block ----------------------------------------
     const dim3 grot((unsigned)((P + 255) / 256), (unsigned)((P + kExchangeRanks - 1) / kExchangeRanks));
+    const bool direct = runs_direct(pr);
     // A schedule of one phase whose block sizes nobody asked to see: every block arrives in its only hop, so what
     // the phase's metadata exchange would leave in the receivers' size arrays is recvcounts, rotated (validation
-    // has checked that it is the transpose of sendcounts): one kernel instead of the rotation and the exchange.
+    // has checked that it is the transpose of sendcounts): one kernel instead of the rotation and the exchange,
+    // and none when the blocks are short (k_hop_direct reads recvcounts itself).
     pr.sizes_direct = pl.phases.size() == 1 && pr.fused && !pr.debug_sizes;
-    if (pr.sizes_direct) hipLaunchKernelGGL(k_rotate_init, grot, dim3(256), 0, s, pr.recvcounts, mb.nxt, P, pr.Q, pr.N, 1);
-    else hipLaunchKernelGGL(k_rotate_init, grot, dim3(256), 0, s, pr.sendcounts, mb.cur, P, pr.Q, pr.N, 0);
+    if (pr.sizes_direct && !direct) hipLaunchKernelGGL(k_rotate_init, grot, dim3(256), 0, s, pr.recvcounts, mb.nxt, P, pr.Q, pr.N, 1);
+    else if (!pr.sizes_direct) hipLaunchKernelGGL(k_rotate_init, grot, dim3(256), 0, s, pr.sendcounts, mb.cur, P, pr.Q, pr.N, 0);
     HIPCHK(hipGetLastError());
     mark(pr.ctx, s, kCatPrepare, -1);
     rc = launch_self_metadata(pr, s);
@@ -1179,6 +1270,28 @@ int run_one_pass(Prepared& pr, void* mbase, size_t mbytes, void* dbase, hipStrea
     // ---- digit phases -----------------------------------------------------------------------------
     int32_t* cur = mb.cur;
     int32_t* nxt = mb.nxt;
+    if (direct) {
+        // short blocks: per phase the size exchange, the places of the blocks it stores into exact-size T, and one
+        // kernel that resolves and moves its blocks.  The partial sums lie where the hop arrays would.
+        PhaseRows rows{};
+        uint2* part = reinterpret_cast<uint2*>(pr.hop.src);
+        for (size_t i = 0; i < pl.phases.size(); ++i) {
+            rc = launch_direct_metadata(pr, i, cur, nxt, s);
+            if (rc != TUNA_OK) return rc;
+            mark(pr.ctx, s, kCatMeta, (int)i);
+            const int nseg = pl.phases[i].nseg;
+            rc = launch_direct(pr, i, nxt, HopDev{}, 0, nseg, pr.sizes_direct ? pr.recvcounts : nullptr,
+                               part + (size_t)rows.row[i] * P, s);
+            if (rc != TUNA_OK) return rc;
+            rows.row[i + 1] = rows.row[i] + (int)direct_rows(pr, pl.phases[i]);
+            mark(pr.ctx, s, kCatPack, (int)i);
+            std::swap(cur, nxt);
+        }
+        hipLaunchKernelGGL(k_phase_sums, dim3((unsigned)((P + kWave - 1) / kWave), (unsigned)pl.phases.size()), dim3(256), 0, s, part, rows, P,
+                           pr.sb.d_status);
+        HIPCHK(hipGetLastError());
+        return TUNA_OK;
+    }
     for (size_t i = 0; i < pl.phases.size(); ++i) {
         rc = launch_phase_metadata(pr, i, cur, nxt, mb.Ls, mb.Lr, pr.hop, s);
         if (rc != TUNA_OK) return rc;
@@ -1308,9 +1421,10 @@ int run_once(Ctx& c, const Options& opt, const void* sendbuf, const int32_t* sen
     fill_stats_header(pr, hs, st);
     if (empty) { c.have_stats = true; return TUNA_OK; }
     const PlanHost& pl = pr.dp->host;
-    if (use_two_pass(pl, hs) && pr.fused && !c.profile && !pr.debug_sizes) {
+    const bool direct = runs_direct(pr);
+    if (use_two_pass(pl, hs) && pr.fused && !c.profile && !pr.debug_sizes && !direct) {
         rc = run_pipelined(c, pr, s);
-    } else if (use_two_pass(pl, hs)) {
+    } else if (use_two_pass(pl, hs) && !direct) {
         rc = run_two_pass(c, pr, s);
     } else {
         // ---- workspace ---------------------------------------------------------------------------
@@ -1783,7 +1897,7 @@ int run_static(const void* sendbuf, const int32_t* sendcounts, const int64_t* sd
 //     ms = c0 + c1 * phases + c2 * (phases + 1) * P^2 / 1e6 + c3 * hop bytes / 1e9 + c4 * moving blocks / 1e6
 // with hop bytes = sum over phases of the payload bytes that move, moving blocks likewise.  One set of
 // constants per mode (three-stage, one-kernel).  One-kernel phases of problems whose blocks all fit into
-// 64 bytes run another kernel (k_hop_small, one thread per block), whose blocks and bytes are priced by
+// 64 bytes run another kernel (k_hop_direct, 1 or 4 lanes per block), whose blocks and bytes are priced by
 // constants of their own, c5 and c6, in place of c4 and c3.  The built-in constants were fitted to
 // immediate calls on MI355X by tuna_calibrate; calling it replaces them by a fit to calls timed on the
 // device at hand.
@@ -1793,18 +1907,20 @@ struct Model {
     double c[kModelTerms];
 };
 struct ModelSet {
-    Model m[2] = {{{0.0393, 0.0360, 0.0071, 1.0192, 0.0412, 0.0, 0.0}},            // [0] three stages
-                  {{0.0368, 0.0312, 0.0061, 0.3481, 0.0398, 0.0150, 1.4108}}};    // [1] one-kernel hops
+    Model m[2] = {{{0.0426, 0.0385, 0.0069, 1.0098, 0.0413, 0.0, 0.0}},            // [0] three stages
+                  // [1] one-kernel hops; a gigabyte of short blocks is not priced under one of long blocks, though
+                  // the fit, whose short-block problems are mostly cache resident, says 0.17
+                  {{0.0345, 0.0329, 0.0000, 0.3548, 0.0482, 0.0059, 0.3600}}};
     // T in the paper's slots of M bytes: the bytes that pass through T cost more the emptier the slots are
     // (sparse writes and reads): their share of the byte term is scaled by 1 + k * (1 - mean / M)
     double slot_penalty[2] = {0.25, 0.45};
     // byte-granular problems (some count, displacement or buffer address is not a multiple of 4) run the
     // kernel variants that load and store single bytes at block edges: their byte term is scaled by this
-    double byte_granular[2] = {1.15, 1.38};
+    double byte_granular[2] = {1.15, 1.37};
     // line-granular problems (every count, displacement and buffer address is a multiple of 128) run the kernel
     // variants that read their sources with streaming loads, and no block shares a line with its neighbour:
     // their byte and block terms are scaled by this
-    double line_granular[2] = {0.90, 0.79};
+    double line_granular[2] = {0.90, 0.72};
     bool calibrated = false;
 };
 ModelSet g_model;
@@ -1813,7 +1929,7 @@ struct Features {
     double phases, p2, hop_gb, mblocks, msmall, small_gb, t_share;    // t_share: share of the hop bytes that is written to or read from T
 };
 
-// small: the problem's one-kernel phases run k_hop_small (one-kernel mode and no block above 64 bytes)
+// small: the problem's one-kernel phases run k_hop_direct (one-kernel mode and no block above 64 bytes)
 Features features_of(const PlanHost& pl, double payload_bytes, bool small) {
     Features f{};
     const double P = (double)pl.P;
@@ -1822,6 +1938,10 @@ Features features_of(const PlanHost& pl, double payload_bytes, bool small) {
     double moving = 0.0;
     for (const auto& ph : pl.phases) moving += (double)ph.nseg * P;
     (small ? f.msmall : f.mblocks) = moving / 1e6;
+    // A short block of a schedule of one phase is looked up in the receive counts and the displacements; with several
+    // phases its size is rotated and exchanged, its place in T scanned and looked up.  Uniform [0, 16] B at P = 2048
+    // takes 4 ns per block at r = P and 15 to 16 ns per block and phase at r = 2, 8 and 46.
+    if (small && f.phases > 1.0) f.msmall *= 4.0;
     // sizes are taken to be independent of the rank distance: every slot index carries payload / P^2
     (small ? f.small_gb : f.hop_gb) = P > 0 ? payload_bytes * (moving / (P * P)) / 1e9 : 0.0;
     // a block of h hops passes through T h - 1 times: it is written there h - 1 times and read h - 1 times,
@@ -1843,7 +1963,8 @@ double bytes_ms(const Model& m, const Features& f) { return m.c[3] * f.hop_gb + 
 // the model's byte and block terms: what depends on the payload
 double data_ms(const Model& m, const Features& f) { return bytes_ms(m, f) + m.c[4] * f.mblocks + m.c[5] * f.msmall; }
 
-bool small_block_path(bool fused, int64_t max_block) { return fused && max_block > 0 && max_block <= kSmallBlockBytes; }
+constexpr int kModelSmallBytes = 64;
+bool small_block_path(bool fused, int64_t max_block) { return fused && max_block > 0 && max_block <= kModelSmallBytes; }
 
 double predict_ms(int P, int Q, int rl, int rg, bool fused, int t_layout, int64_t payload_bytes, int64_t max_block,
                   int granularity) {
@@ -1939,7 +2060,7 @@ int calibrate(hipStream_t s) {
     const Problem lines = {2048, 256, {8, 2048, 0}};
     // tiny (fixed costs), many tiny blocks (per-block and per-entry costs), large blocks beyond the caches
     // (bytes), and a mix; S is 4 bytes off a multiple of 16, the usual alignment of float payloads
-    const Problem problems[] = {{32, 68, {2, 6, 32}}, {256, 516, {2, 16, 256}}, {1024, 20, {2, 32, 1024}}, {2048, 36, {8, 2048, 0}},
+    const Problem problems[] = {{32, 300, {2, 6, 32}}, {256, 516, {2, 16, 256}}, {1024, 20, {2, 32, 1024}}, {2048, 36, {8, 2048, 0}},
                                 {2048, 4, {2, 2048, 0}}, {1024, 60, {4, 1024, 0}},
                                 {512, 4100, {2, 23, 512}}, {2048, 260, {8, 2048, 0}}};
     size_t max_entries = 0, max_bytes = 0;

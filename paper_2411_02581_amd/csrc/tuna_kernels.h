@@ -426,6 +426,8 @@ __global__ void __launch_bounds__(256) k_validate_finish(const unsigned long lon
         st->t_chunks = tc;
         st->short_blocks = sb;
     }
+    // the totals that k_phase_sums adds to; the other paths write them whole
+    if (threadIdx.x < 64) st->phase_bytes[threadIdx.x] = st->phase_chunks[threadIdx.x] = 0;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -564,6 +566,7 @@ struct PhaseLayoutArgs {
     int nseg;
     int P, Q, N, dim, rx;
     LayoutDev Ls, Lr;
+    int want_chunks;                // 0: no chunk layouts at all, only the T-bound blocks (phases of short blocks)
     int want_send;                  // 0: only the receive-side layout (one-kernel phases)
     int want_tbound;                // 1: also lay out the blocks this phase stores into exact-size T (see ExactT)
     ExactT x;
@@ -699,7 +702,7 @@ __global__ void __launch_bounds__(kScanThreads) k_phase_layout(const PhaseLayout
     int* pre_s = a.Ls.pre + (size_t)p * a.Ls.ld;
     int carry_r = 0, carry_s = 0;
     unsigned long long bytes = 0;
-    for (int base = 0; base < a.nseg; base += kScanThreads * kScanItems) {
+    for (int base = 0; base < a.nseg && (a.want_chunks || a.inline_exchange); base += kScanThreads * kScanItems) {
         int cr[kScanItems], cs[kScanItems];
 #pragma unroll
         for (int k = 0; k < kScanItems; ++k) {
@@ -715,7 +718,7 @@ __global__ void __launch_bounds__(kScanThreads) k_phase_layout(const PhaseLayout
                     szr = nrow[e];
                 }
                 if (a.want_send) szs = crow[e];
-                if (a.head_displs && szr > 0 && a.seg.dst[s] < 0) {
+                if (a.want_chunks && a.head_displs && szr > 0 && a.seg.dst[s] < 0) {
                     int j, l;
                     split_slot_index(e, a.Q, a.N, j, l);
                     int sn = pn + j; if (sn >= a.N) sn -= a.N;
@@ -727,6 +730,7 @@ __global__ void __launch_bounds__(kScanThreads) k_phase_layout(const PhaseLayout
             cr[k] = (head + szr + 15) >> 4;
             cs[k] = (szs + 15) >> 4;
         }
+        if (!a.want_chunks) continue;
         int run[kScanItems];
         block_scan_batch(cr, run, carry_r, wsum);
 #pragma unroll
@@ -775,6 +779,7 @@ __global__ void __launch_bounds__(kScanThreads) k_phase_layout(const PhaseLayout
             if (tid == 0) a.x.csub[(size_t)cid * P + p] = carry_t;
         }
     }
+    if (!a.want_chunks) return;
 #pragma unroll
     for (int d = kWave / 2; d > 0; d >>= 1) bytes += __shfl_xor(bytes, d, kWave);
     // one sum per rank, added up by k_layout_base: thousands of atomics on one address would take
@@ -1023,7 +1028,7 @@ struct ResolveArgs {
     long long slot_bytes;
     ExactT x;                           // T in exact size
     HopDev hop;
-    int exact_sizes;                    // 1: every size is the block's byte count (k_hop_small copies exactly that), also into T
+    int exact_sizes;                    // 1: every size is the block's byte count (k_hop_direct copies exactly that), also into T
 };
 
 constexpr int kResolveTile = 16;
@@ -1083,42 +1088,250 @@ __global__ void __launch_bounds__(256) k_resolve_hop(const ResolveArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------
-// k_hop_small: a one-kernel phase whose blocks all fit into 64 bytes (Section "Performance analysis of
-// TuNA": the small-message regime, S of a few bytes).  The byte-balanced engine above cuts work into
-// 4 KiB units and searches a window of block boundaries per unit; with blocks of a few bytes that
-// search is most of the work.  Here one thread moves one block: it reads the block's resolved source,
-// destination and size (k_resolve_hop) and copies its at most 16 words (or 64 bytes).  Neighbouring
-// threads hold neighbouring blocks of one receiver, whose destinations are neighbours in R or T, so a
-// wave's stores fall into a few lines.  grid (ceil(segments / 256), P); a batch of rounds covers the
-// segments [seg_lo, seg_hi).
+// k_hop_direct: a one-kernel phase whose blocks are all short (Section "Performance analysis of TuNA": the
+// small-message regime).  The byte-balanced engine cuts work into 4 KiB units and searches a window of block
+// boundaries per unit; with short blocks the prefix scans, unit lists and searches are most of a phase.  Here a
+// workgroup takes the blocks of 16 neighbouring receivers x SEGS neighbouring segments, one lane resolves one
+// block -- where its sender holds it, where its receiver keeps it, how long it is -- and LPB lanes move it, 16
+// bytes each, so LPB x 16 bytes is the longest block the kernel takes.  No scan, no unit list and, except for a
+// plan's (RESOLVED), no hop arrays: 40 bytes per block that would be written and read back.
+//   Bound by memory: the entries of the matrices it looks up and the payload, both in whole lines.  Blocks that
+// never moved are looked up down a column of sdispls and lie, for neighbouring receivers, side by side in a
+// sender's S: the 16 receivers of a tile share those lines; the SEGS blocks of one receiver lie side by side in R.
+//   A block of 16 bytes and more is moved in 16-byte accesses at its own alignment, the last one ending with the
+// block and overlapping the one before it (the same bytes are stored twice); a shorter one by the lane that
+// resolved it in two overlapping accesses of 8 or 4 bytes, or byte by byte.  Only bytes of the block are read.
+//   Measured per call against one thread per block (up to 64 bytes) and the engine (above), both from hop arrays:
+// 33 M blocks of 64 bytes and as many empty ones (P = 8192, linear) 6.91 -> 1.57 ms; uniform [0, 16] B, P = 2048, two
+// phases 0.44 -> 0.27 ms; all blocks 256 bytes, P = 2048 as 64 x 32, four phases 1.73 -> 1.40 ms; uniform [0, 248] B,
+// P = 4096, linear 1.64 -> 1.24 ms.
+//   TALL tiles (16 receivers x few segments, LPB = 1 and 4) share the lines of S and sdispls between receivers: that pays
+// when a round has few blocks, as in the linear schedule (64-byte blocks: 1.57 against 2.0 ms).  With many blocks per
+// round neighbouring receivers read other rows, and long rows of one receiver are better (uniform [0, 16] B, two phases:
+// 0.26 against 0.33 ms).
+//   STREAM: 1 = streaming stores (chunk-granular data; -4 %, but +5 % and more where blocks share 16-byte chunks),
+// 2 = streaming loads too (whole lines; another -4 %).
+//   Payload bytes and 16-byte chunks are summed per receiver and stored as one partial result per tile column
+// (a.part); k_phase_sums adds them up.
 // ------------------------------------------------------------------------------------------
-constexpr int kSmallBlockBytes = 64;
-template <int GRAN>
-__global__ void __launch_bounds__(256) k_hop_small(HopDev hop, unsigned char* T, int seg_lo, int seg_hi) {
-    const int s = seg_lo + blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= seg_hi) return;
-    const size_t o = (size_t)blockIdx.y * hop.ld + s;
-    const int size = hop.size[o];
-    if (size <= 0) return;
-    const unsigned long long hs = hop.src[o], hd = hop.dst[o];
-    const unsigned long long tb = (unsigned long long)T;
-    const unsigned char* src = reinterpret_cast<const unsigned char*>((hs & ~(kHopInT | kHopFill)) + ((hs & kHopInT) ? tb : 0ull));
-    unsigned char* dst = reinterpret_cast<unsigned char*>((hd & ~(kHopInT | kHopFill)) + ((hd & kHopInT) ? tb : 0ull));
-    if (GRAN >= 4) {
-        // all loads first, then all stores; `size` is the block's exact byte count (ResolveArgs.exact_sizes)
-        const uint32_t* s4 = reinterpret_cast<const uint32_t*>(src);
-        uint32_t* d4 = reinterpret_cast<uint32_t*>(dst);
-        const int n = min(size, kSmallBlockBytes) >> 2;
-        uint32_t w[kSmallBlockBytes / 4];
-#pragma unroll
-        for (int i = 0; i < kSmallBlockBytes / 4; ++i) w[i] = i < n ? s4[i] : 0u;
-#pragma unroll
-        for (int i = 0; i < kSmallBlockBytes / 4; ++i)
-            if (i < n) d4[i] = w[i];
-    } else {
-        const int n = min(size, kSmallBlockBytes);
-        for (int i = 0; i < n; ++i) dst[i] = src[i];
+constexpr int kDirectMaxBytes = 256;        // longest block of the LPB = 16 kernel
+// the tile of one workgroup and step: receivers per wave, blocks per lane (of neighbouring receivers), waves side by
+// side along the receivers (the others along the segments)
+struct DirectShape { int wave_ranks, sets, waves_r; };
+constexpr DirectShape direct_shape(int lpb, bool tall) {
+    return tall ? (lpb == 1 ? DirectShape{1, 4, 4} : lpb == 4 ? DirectShape{4, 1, 4} : DirectShape{1, 1, 4})
+                : (lpb == 1 ? DirectShape{1, 4, 1} : DirectShape{2, 1, 4});
+}
+constexpr int direct_segs(DirectShape s) { return kWave / s.wave_ranks * (4 / s.waves_r); }
+constexpr int direct_ranks(DirectShape s) { return s.wave_ranks * s.sets * s.waves_r; }
+struct DirectArgs {
+    ResolveArgs r;                      // hop: only when RESOLVED
+    const int32_t* by_source;           // schedule of one phase: recvcounts, read at the source's place instead of r.nxt
+    unsigned char* T;
+    int seg_lo, seg_hi;
+    int iters;                          // steps of direct_segs(LPB) segments per workgroup
+    uint2* part;                        // [grid.x][P]: payload bytes and chunks of the tile column, per receiver (not when RESOLVED)
+};
+
+typedef v4u v4u_any __attribute__((aligned(1)));
+typedef unsigned long long u64_any __attribute__((aligned(1)));
+typedef unsigned int u32_any __attribute__((aligned(1)));
+#define TUNA_GLOBAL __attribute__((address_space(1)))
+template <class T> __device__ __forceinline__ T load_global(unsigned long long a) { return *(const TUNA_GLOBAL T*)a; }
+template <class T, class V> __device__ __forceinline__ void store_global(unsigned long long a, V v) { *(TUNA_GLOBAL T*)a = v; }
+
+// A block of fewer than 16 bytes (up to 16 in the LPB = 1 kernel), by one lane.  The loads are made without a
+// branch, from `dummy` where the block is of another kind: a load under a branch is waited for at the branch's end,
+// so the loads of several blocks would go out one after the other.  Blocks of 1 to 3 bytes are left to short_store.
+struct ShortBlock { unsigned long long w0, w1; unsigned int x0, x1; };
+__device__ __forceinline__ ShortBlock short_load(unsigned long long src, int n, unsigned long long dummy) {
+    const bool one = n >= 4 && n < 8;
+    ShortBlock b;
+    b.w0 = load_global<u64_any>(n >= 8 ? src : dummy);
+    b.w1 = load_global<u64_any>(n > 8 ? src + n - 8 : dummy);
+    b.x0 = load_global<u32_any>(one ? src : dummy);
+    b.x1 = load_global<u32_any>(one && n > 4 ? src + n - 4 : dummy);
+    return b;
+}
+__device__ __forceinline__ void short_store(unsigned long long dst, unsigned long long src, int n, const ShortBlock& b) {
+    if (n >= 8) {
+        store_global<u64_any>(dst, b.w0);
+        if (n > 8) store_global<u64_any>(dst + n - 8, b.w1);
+    } else if (n >= 4) {
+        store_global<u32_any>(dst, b.x0);
+        if (n > 4) store_global<u32_any>(dst + n - 4, b.x1);
+    } else if (n > 0) {
+        const unsigned char c0 = load_global<unsigned char>(src), c1 = load_global<unsigned char>(src + (n >> 1)), c2 = load_global<unsigned char>(src + n - 1);
+        store_global<unsigned char>(dst, c0); store_global<unsigned char>(dst + (n >> 1), c1); store_global<unsigned char>(dst + n - 1, c2);
     }
+}
+
+template <int LPB, bool TALL, int STREAM, bool DENSE, bool RESOLVED>
+__global__ void __launch_bounds__(256) k_hop_direct(const DirectArgs a) {
+    constexpr DirectShape SH = direct_shape(LPB, TALL);
+    constexpr int SEGS = kWave / SH.wave_ranks;          // segments per wave and step
+    constexpr int SETS = SH.sets;                        // blocks a lane resolves per step
+    constexpr int WS = 4 / SH.waves_r;                   // waves side by side along the segments
+    constexpr int BPS = kWave / LPB;                     // blocks a wave moves per step of its copy loop
+    constexpr int FLIGHT = LPB < 8 ? LPB : 8;            // steps whose loads are in flight together
+    __shared__ unsigned long long s_src[LPB > 1 ? 4 : 1][LPB > 1 ? kWave : 1], s_dst[LPB > 1 ? 4 : 1][LPB > 1 ? kWave : 1];
+    __shared__ int s_n[LPB > 1 ? 4 : 1][LPB > 1 ? kWave : 1];
+    const ResolveArgs& r = a.r;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int P = r.P, Q = r.Q, N = r.N;
+    const int p0 = blockIdx.y * direct_ranks(SH) + (wv / WS) * SH.wave_ranks * SETS + lane / SEGS;
+    const int sub = lane & (SEGS - 1);
+    const unsigned long long tb = (unsigned long long)a.T;
+    unsigned int sum_b[SETS], sum_c[SETS];
+#pragma unroll
+    for (int u = 0; u < SETS; ++u) sum_b[u] = sum_c[u] = 0;
+    for (int it = 0; it < a.iters; ++it) {
+        const int s0 = a.seg_lo + ((blockIdx.x * a.iters + it) * WS + wv % WS) * SEGS;
+        if (s0 >= a.seg_hi) break;
+        const int s = min(s0 + sub, a.seg_hi - 1);
+        const bool in = s0 + sub < a.seg_hi;
+        unsigned long long src[SETS], dst[SETS];
+        int n[SETS];
+        // ---- where every block is and goes: loads from valid addresses without branches, so that they go out together
+        if (RESOLVED) {
+#pragma unroll
+            for (int u = 0; u < SETS; ++u) {
+                const size_t o = (size_t)min(p0 + u, P - 1) * r.hop.ld + s;
+                n[u] = r.hop.size[o]; src[u] = r.hop.src[o]; dst[u] = r.hop.dst[o];
+            }
+#pragma unroll
+            for (int u = 0; u < SETS; ++u) {
+                src[u] = (src[u] & ~(kHopInT | kHopFill)) + ((src[u] & kHopInT) ? tb : 0ull);
+                dst[u] = (dst[u] & ~(kHopInT | kHopFill)) + ((dst[u] & kHopInT) ? tb : 0ull);
+            }
+        } else {
+            const int e = r.seg.e[s], dist = r.seg.z[s] * r.rx, ssrc = r.seg.src[s], sdst = r.seg.dst[s];
+            const int sph = DENSE ? r.seg.srcph[s] : 0, scl = DENSE ? r.seg.scls[s] : 0, dcl = DENSE ? r.seg.dcls[s] : 0;
+            const bool in_s = ssrc < 0, in_r = sdst < 0;  // read from S (never moved), stored into R (final)
+            int j, l;
+            split_slot_index(e, Q, N, j, l);
+            long long va[SETS], vc[SETS];
+            int vb[SETS], vd[SETS], q[SETS];
+#pragma unroll
+            for (int u = 0; u < SETS; ++u) {
+                const int p = min(p0 + u, P - 1);
+                int pn, pg;
+                split_slot_index(p, Q, N, pn, pg);
+                q[u] = partner_up(pn, pg, Q, N, r.dim, dist);
+                int qn, qg;
+                split_slot_index(q[u], Q, N, qn, qg);
+                int dn = qn - j; if (dn < 0) dn += N;
+                int dg = qg - l; if (dg < 0) dg += Q;
+                int sn = pn + j; if (sn >= N) sn -= N;
+                int sg = pg + l; if (sg >= Q) sg -= Q;
+                const size_t row = (size_t)p * P, at_s = (size_t)q[u] * P + dn * Q + dg, at_r = row + sn * Q + sg;
+                n[u] = *(a.by_source ? a.by_source + at_r : r.nxt + row + e);
+                const int64_t* tbase = reinterpret_cast<const int64_t*>(r.x.tbase);
+                va[u] = *(in_s ? r.sdispls + at_s : (DENSE ? tbase + (size_t)scl * P + q[u] : r.sdispls));
+                vc[u] = *(in_r ? r.rdispls + at_r : (DENSE ? tbase + (size_t)dcl * P + p : r.rdispls));
+                if (DENSE) {
+                    vb[u] = *(in_s ? r.seg.e : r.x.tpos + ((size_t)sph * P + q[u]) * P + e);
+                    vd[u] = *(in_r ? r.seg.e : r.x.tpre + (size_t)p * r.x.ld + s);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < SETS; ++u) {
+                const int p = min(p0 + u, P - 1);
+                if (DENSE) {
+                    src[u] = in_s ? (unsigned long long)r.S + va[u] : tb + ((unsigned long long)(va[u] + vb[u]) << 4);
+                    dst[u] = in_r ? (unsigned long long)r.R + vc[u] : tb + ((unsigned long long)(vc[u] + vd[u]) << 4);
+                } else {
+                    src[u] = in_s ? (unsigned long long)r.S + va[u] : tb + (unsigned long long)(((long long)q[u] * r.slots + ssrc) * r.slot_bytes);
+                    dst[u] = in_r ? (unsigned long long)r.R + vc[u] : tb + (unsigned long long)(((long long)p * r.slots + sdst) * r.slot_bytes);
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < SETS; ++u) {
+            if (!in || p0 + u >= P) n[u] = 0;
+            n[u] = min(n[u], 16 * LPB);                  // validation has bounded it: nothing is cut here
+            sum_b[u] += (unsigned int)n[u];
+            // chunks as the staging layouts count them: cut at the 16-byte boundaries of R
+            if (!RESOLVED) sum_c[u] += n[u] > 0 ? ((r.seg.dst[s] < 0 ? (unsigned int)(dst[u] & 15ull) : 0u) + (unsigned int)n[u] + 15u) >> 4 : 0u;
+        }
+        const unsigned long long dummy = (unsigned long long)r.seg.e;       // any 16 bytes that can be read
+        if constexpr (LPB == 1) {
+            ShortBlock b[SETS];
+#pragma unroll
+            for (int u = 0; u < SETS; ++u) b[u] = short_load(src[u], n[u], dummy);
+#pragma unroll
+            for (int u = 0; u < SETS; ++u) short_store(dst[u], src[u], n[u], b[u]);
+        } else {
+            // the wave's 64 blocks go to its own part of the LDS; no workgroup barrier
+            s_src[wv][lane] = src[0]; s_dst[wv][lane] = dst[0]; s_n[wv][lane] = n[0];
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            const int c = (lane & (LPB - 1)) * 16;
+#pragma unroll
+            for (int k0 = 0; k0 < LPB; k0 += FLIGHT) {
+                v4u v[FLIGHT];
+                unsigned long long d[FLIGHT];
+                bool act[FLIGHT];
+#pragma unroll
+                for (int k = 0; k < FLIGHT; ++k) {
+                    const int b = (k0 + k) * BPS + lane / LPB;
+                    const int nb = s_n[wv][b];
+                    act[k] = nb >= 16 && c < nb;
+                    const unsigned int o = (unsigned int)min(c, nb - 16);
+                    const unsigned long long sa = s_src[wv][b] + o;
+                    d[k] = s_dst[wv][b] + o;
+                    const TUNA_GLOBAL v4u_any* from = (const TUNA_GLOBAL v4u_any*)(act[k] ? sa : dummy);
+                    v[k] = STREAM == 2 ? __builtin_nontemporal_load(from) : *from;
+                }
+#pragma unroll
+                for (int k = 0; k < FLIGHT; ++k)
+                    if (act[k]) {
+                        if (STREAM) __builtin_nontemporal_store(v[k], (TUNA_GLOBAL v4u_any*)d[k]);
+                        else store_global<v4u_any>(d[k], v[k]);
+                    }
+            }
+            // blocks of fewer than 16 bytes: the lane that resolved them
+            const int ns = n[0] < 16 ? n[0] : 0;
+            if (__ballot(ns > 0)) short_store(dst[0], src[0], ns, short_load(src[0], ns, dummy));
+            __builtin_amdgcn_wave_barrier();             // the next step overwrites the wave's LDS
+        }
+    }
+    if (!RESOLVED) {
+#pragma unroll
+        for (int u = 0; u < SETS; ++u) {
+#pragma unroll
+            for (int d = SEGS / 2; d > 0; d >>= 1) { sum_b[u] += __shfl_xor(sum_b[u], d, kWave); sum_c[u] += __shfl_xor(sum_c[u], d, kWave); }
+            if (sub == 0 && p0 + u < P) a.part[((size_t)blockIdx.x * WS + wv % WS) * P + p0 + u] = make_uint2(sum_b[u], sum_c[u]);
+        }
+    }
+}
+
+// k_phase_sums: the partial sums of the phases that ran as k_hop_direct, rows [row[x], row[x + 1]) of `part` for
+// phase x, into the status block: payload bytes, and staged chunks with every receiver's share rounded up to a line
+// as the staging layouts round it.  Four threads per receiver, grid (ceil(P / 64), phases); k_validate_finish cleared
+// the totals.
+struct PhaseRows { int row[64 + 1]; };
+__global__ void __launch_bounds__(256) k_phase_sums(const uint2* __restrict__ part, PhaseRows rows, int P, Status* __restrict__ st) {
+    __shared__ unsigned long long s_b[4][kWave], s_c[4][kWave];
+    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+    const int p = blockIdx.x * kWave + lane, x = blockIdx.y;
+    const int r1 = rows.row[x + 1];
+    unsigned long long b = 0, c = 0;
+    if (p < P) {
+#pragma unroll 8
+        for (int i = rows.row[x] + wv; i < r1; i += 4) { const uint2 v = part[(size_t)i * P + p]; b += v.x; c += v.y; }
+    }
+    s_b[wv][lane] = b; s_c[wv][lane] = c;
+    __syncthreads();
+    if (wv) return;
+    b += s_b[1][lane] + s_b[2][lane] + s_b[3][lane];
+    c += s_c[1][lane] + s_c[2][lane] + s_c[3][lane];
+    c = (c + kRankAlignChunks - 1) / kRankAlignChunks * kRankAlignChunks;
+#pragma unroll
+    for (int d = kWave / 2; d > 0; d >>= 1) { b += __shfl_xor(b, d, kWave); c += __shfl_xor(c, d, kWave); }
+    if (lane == 0 && b) { atomicAdd(&st->phase_bytes[x], b); atomicAdd(&st->phase_chunks[x], c); }
 }
 
 // Compiled for 8 waves per SIMD (a workgroup is one wave per SIMD).  The host lowers the number of

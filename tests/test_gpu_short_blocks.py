@@ -1,0 +1,85 @@
+"""Phases whose blocks are all short (k_hop_direct): byte parity with the CPU oracle at the edges of its lanes
+(16, 64 and 256 bytes, one byte and one word on either side), of its tiles (15 to 17, 63 to 65, 257 ranks) and of
+its two tile shapes (few and many blocks per round), for byte-, word-, chunk- and line-granular sizes, dense and
+gapped receive regions, immediate calls, plans and the call that allocates nothing; the totals per phase equal those
+of a plan, which scans them."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+CANARY = 0xB7
+
+
+@pytest.fixture(scope="module")
+def tuna():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2411_02581_amd as t
+    t.load()
+    return t
+
+
+def _counts(P, longest, quantum, seed):
+    rng = np.random.default_rng(seed)
+    c = rng.integers(0, longest // quantum + 1, (P, P)) * quantum
+    c[rng.random((P, P)) < 0.2] = 0
+    c[rng.integers(P), rng.integers(P)] = longest          # the longest block there is
+    return np.ascontiguousarray(c, dtype=np.int32)
+
+
+CASES = [(15, 15, 1, 3), (17, 16, 4, 2), (64, 16, 8, 64), (65, 17, 1, 4), (130, 63, 1, 130), (257, 64, 8, 16), (128, 64, 64, 12),
+         (129, 65, 1, 2), (63, 255, 1, 8), (200, 256, 4, 200), (144, 240, 16, 12), (96, 256, 128, 4), (66, 257, 1, 66)]
+
+
+@pytest.mark.parametrize("t_layout", ["exact", "slots"])
+@pytest.mark.parametrize("P,longest,quantum,radix", CASES)
+def test_short_blocks(tuna, P, longest, quantum, radix, t_layout):
+    counts = _counts(P, longest, quantum, P * 1000 + longest)
+    if quantum >= 64:
+        counts[counts > 0] = longest                        # whole blocks: displacements keep the granularity
+    for Q in (0, 12 if P == 144 else 0):
+        lay = wl.make_layout(counts, gap=8 * (quantum == 4), permute_seed=5 if quantum == 1 else None)
+        host = wl.payload_position_hash(longest, lay.send_bytes)
+        want = np.full(lay.recv_bytes, CANARY, dtype=np.uint8)
+        assert oracle.alltoallv(host, lay.sendcounts, lay.sdispls, want, lay.recvcounts, lay.rdispls) == 0
+        dev = "cuda:0"
+        send = torch.from_numpy(host).to(dev)
+        recv = torch.full((lay.recv_bytes,), CANARY, dtype=torch.uint8, device=dev)
+        sc, sd, rc_, rd = [torch.from_numpy(a).to(dev) for a in (lay.sendcounts, lay.sdispls, lay.recvcounts, lay.rdispls)]
+        o = tuna.tuna_opts_init()
+        o.mode = tuna.TUNA_MODE_FUSED                       # small problems too take the general path
+        o.t_layout = tuna.TUNA_T_EXACT if t_layout == "exact" else tuna.TUNA_T_SLOTS
+        totals = []
+
+        def check(what):
+            torch.cuda.synchronize()
+            bad = np.flatnonzero(recv.cpu().numpy() != want)
+            assert bad.size == 0, "%s: %d bytes differ, first at %d" % (what, bad.size, bad[0])
+            recv.fill_(CANARY)
+            st = tuna.tuna_get_stats()
+            totals.append([(st.phase[x].payload_bytes, st.phase[x].staged_bytes) for x in range(st.n_phases)])
+
+        print("short blocks", P, longest, quantum, radix, Q, t_layout, flush=True)
+        for _ in range(2):
+            rc = tuna.tuna_alltoallv_ex(None, send, sc, sd, recv, rc_, rd, P, Q, radix, radix, o)
+            assert rc == 0, tuna.tuna_strerror(rc)
+            check("call")
+        rc, plan = tuna.tuna_alltoallv_init_ex(None, send, sc, sd, recv, rc_, rd, P, Q, radix, radix, o)
+        assert rc == 0, tuna.tuna_strerror(rc)
+        try:
+            assert tuna.tuna_start(plan) == 0
+            check("plan")
+        finally:
+            tuna.tuna_plan_free(plan)
+        assert totals[0] == totals[1] == totals[2]
+        if radix == P and Q == 0:
+            assert totals[0][0][0] == int(counts.sum()) - int(np.trace(counts))
+        rc = tuna.tuna_alltoallv_noalloc(send, sc, sd, recv, rc_, rd, P, Q, radix, radix)
+        assert rc == 0, tuna.tuna_strerror(rc)
+        torch.cuda.synchronize()
+        assert np.array_equal(recv.cpu().numpy(), want), "noalloc"
