@@ -150,7 +150,8 @@ class Resident:
                 ph = st.phase[x]
                 meta_ms += ph.ms_metadata
                 # the tiled hop of a schedule's last phase is a kernel variant of its own when the data is word-granular
-                last_tiled = bool(st.fused) and x + 1 == st.n_phases and st.granularity < 16
+                # and the blocks are longer than k_hop_rows takes
+                last_tiled = bool(st.fused) and x + 1 == st.n_phases and st.granularity < 16 and st.max_block_bytes > 65536
                 for name, ms in (("pack", ph.ms_pack), ("exchange", ph.ms_exchange),
                                  ("unpack_last" if last_tiled else "unpack", ph.ms_unpack)):
                     if ms > 0:
@@ -178,7 +179,7 @@ class Resident:
                "one_kernel_phases": st.fused, "profiled_ms_per_step": prof_total / self.steps,
                "metadata_ms_per_step": meta_ms / self.steps, "prepare_ms_per_step": prep_ms / self.steps,
                "own_blocks_ms_per_step": self_ms / self.steps, "kernels": kernels, "granularity": st.granularity,
-               "max_block_bytes": int(st.max_block_bytes)}
+               "max_block_bytes": int(st.max_block_bytes), "mean_block_bytes": Btot / float(st.P) ** 2}
         print("[bench] %s: %.3f ms/step, %.1f GB/s effective; " % (label, ms_per_step, row["effective_GBs"]) +
               ", ".join("%s %.0f GB/s" % (k, v["achieved_GBs"]) for k, v in kernels.items()) +
               (" [one-kernel phases]" if st.fused else " [three stages]"), file=sys.stderr, flush=True)
@@ -246,10 +247,13 @@ def radices_of(cfg, P, override=""):
     return [("r=%d" % min(r, P), min(r, P), min(r, P)) for r in rs]
 
 
-def kernel_name(stage, gran, exact, max_block_bytes=None):
+def kernel_name(stage, gran, exact, max_block_bytes=None, mean_block_bytes=None):
     et = "true" if exact else "false"
-    if stage == "hop" and max_block_bytes is not None and 0 < max_block_bytes <= 256:      # short blocks
-        return "tuna::k_hop_direct<%d, %s, false>" % (1 if max_block_bytes <= 16 else 4 if max_block_bytes <= 64 else 16, et)
+    if "hop" in stage and max_block_bytes:
+        if max_block_bytes <= 256:      # short blocks; the tall tiles are those of the schedules of one phase
+            return "tuna::k_hop_direct<%d, ...>" % (1 if max_block_bytes <= 16 else 4 if max_block_bytes <= 64 else 16)
+        if max_block_bytes <= 65536 and (stage == "hop" or (mean_block_bytes or 0) <= 4096):
+            return "tuna::k_hop_rows<%s, %s, false>" % ("true" if gran == 128 else "false", et)
     return {"pack": "tuna::k_copy<0, %d, %s>" % (gran, et), "exchange": "tuna::k_copy<1, 16, false>",
             "unpack": "tuna::k_copy<2, %d, %s>" % (min(gran, 16), et), "hop": "tuna::k_copy<3, %d, %s>" % (gran, et),
             "tiled_hop": "tuna::k_copy_tiled<%d, 4>" % (16 if gran >= 16 else 4),
@@ -271,7 +275,8 @@ def roofline_of(rows, steps, traffic, copy_ceiling):
     if not tot:
         return None
     name, (ms, n, alg) = max(tot.items(), key=lambda kv: kv[1][0])
-    kname = kernel_name(name, rows[0]["granularity"], bool(rows[0]["exact_size_t"]), rows[0].get("max_block_bytes"))
+    kname = kernel_name(name, rows[0]["granularity"], bool(rows[0]["exact_size_t"]), rows[0].get("max_block_bytes"),
+                        rows[0].get("mean_block_bytes"))
     achieved = alg / (ms * 1e-3) / 1e9
     tr = traffic.get("bytes_per_launch", {}).get(kname) if traffic else None
     return {"bound": "hbm", "kernel": kname, "stage": name, "achieved": achieved, "peak": HBM_PEAK_GBS,

@@ -463,7 +463,7 @@ int launch_copy(int gran, size_t unit_cap, const CopyArgs& a, hipStream_t s, boo
 }
 
 // Metadata of one digit phase: sizes exchanged, both staging layouts scanned, wave units cut.
-int phase_metadata(const PhaseLayoutArgs& a, hipStream_t s, const ExactT& x, bool sizes_ready = false) {
+int phase_metadata(const PhaseLayoutArgs& a, hipStream_t s, const ExactT& x, bool sizes_ready = false, bool want_units = true) {
     if (!a.inline_exchange && !sizes_ready) {
         hipLaunchKernelGGL(k_size_exchange, dim3((unsigned)((a.P + 255) / 256), (unsigned)((a.P + kExchangeRanks - 1) / kExchangeRanks)),
                            dim3(256), 0, s, a.cur, a.nxt, a.zt, a.P, a.Q, a.N, a.dim, a.rx);
@@ -476,6 +476,7 @@ int phase_metadata(const PhaseLayoutArgs& a, hipStream_t s, const ExactT& x, boo
     hipLaunchKernelGGL(k_layout_base, dim3(nl + (a.want_tbound ? x.ncls : 0)), dim3(kScanThreads), 0, s, a.P, a.Lr, a.Ls, nl,
                        a.phase_chunks, a.want_send ? 1 : 0, x, a.rank_bytes, a.phase_bytes, a.phase_units);
     HIPCHK(hipGetLastError());
+    if (!want_units) return TUNA_OK;
     const int lds_ints = a.nseg + 1 <= kUnitsLdsMaxInts ? a.nseg + 1 : 0;
     hipLaunchKernelGGL(k_layout_units, dim3(a.P, a.want_send ? 2 : 1), dim3(256), (size_t)lds_ints * 4, s, a.nseg, a.Lr,
                        a.Ls, lds_ints);
@@ -720,6 +721,16 @@ bool too_large(int P, const Status& hs) {
 // lanes move it) instead of the byte-balanced engine.
 bool small_blocks(const Prepared& pr) { return pr.max_count > 0 && pr.max_count <= kDirectMaxBytes; }
 
+// The other calls and plans whose phases are all one-kernel hops over all rounds at once run k_hop_rows, unless a block
+// can be so long that waves of whole blocks would not balance, or the destination-tiled hop can run and blocks are long
+// on average: there its metadata costs little and its units are all full (normal sizes, per call, tiled against rows:
+// mean 3 KB 0.942 / 0.932 ms linear and 1.794 / 1.780 at r = 30, 6 KB 0.844 / 0.848 and 1.575 / 1.595, 10 KB at r = 2
+// 4.05 / 4.43).
+constexpr double kRowsMaxMeanBytes = 4096.0;
+bool row_blocks(const Prepared& pr) {
+    if (pr.max_count <= kDirectMaxBytes || pr.max_count > kRowsMaxBytes || !pr.fused || pr.staggered || pr.block_count > 0) return false;
+    return !pr.tiled || (double)pr.total_bytes <= kRowsMaxMeanBytes * (double)pr.P * (double)pr.P;
+}
 constexpr int kTiledMinMeanBytes = 700;    // see prepare_sizes
 constexpr int kTiledMinMeanBytesIntoT = 512;
 
@@ -804,18 +815,20 @@ int prepare_call(Ctx& c, const Options& opt, const void* sendbuf, const int32_t*
     return prepare_sizes(pr, opt.t_layout, s, hs, empty);
 }
 
-// Phases that run as the destination-tiled hop: the last one (all its blocks are final) when the blocks are
-// mostly interior, and with T in exact size the ones before it -- the blocks a rank stores into T lie back to
-// back inside their class, so their destinations form runs just like those in R, and they are whole chunks.
-// (T in slots keeps the copy engine: its slot tails are filled up to the line by a path of their own.)
-bool phase_is_tiled(const Prepared& pr, size_t i) {
+// Phases whose stores are mostly whole lines, reported as destination-tiled: the last one (all its blocks are final)
+// when the blocks are mostly interior, and with T in exact size the ones before it -- the blocks a rank stores into T
+// lie back to back inside their class, so their destinations form runs just like those in R, and they are whole chunks.
+bool phase_stores_lines(const Prepared& pr, size_t i) {
     return i + 1 == pr.dp->host.phases.size() ? pr.tiled_final : (pr.tiled && pr.exact_t);
 }
+// Of them, those with blocks longer than k_hop_rows takes run k_copy_tiled.  (T in slots keeps the copy engine there:
+// its slot tails are filled up to the line by a path of their own.)
+bool phase_is_tiled(const Prepared& pr, size_t i) { return phase_stores_lines(pr, i) && !row_blocks(pr); }
 
 // The last phase of a word-granular schedule as a tiled hop takes units of twice the size (k_copy_tiled<4, 8>):
 // every block it writes has an edge piece, and what a wave spends on its edge pieces does not grow with the unit.
 bool phase_has_wide_units(const Prepared& pr, size_t i) {
-    return i + 1 == pr.dp->host.phases.size() && pr.tiled_final && pr.gran < 16;
+    return i + 1 == pr.dp->host.phases.size() && phase_is_tiled(pr, i) && pr.gran < 16;
 }
 
 // the receive-side layout of phase i with the unit size its payload kernel takes
@@ -893,7 +906,7 @@ int launch_phase_metadata(const Prepared& pr, size_t i, const int32_t* cur, int3
     // P = 256, while at P = 4096 the separate kernel saves 44 us per phase): the scan kernel then
     // exchanges the sizes itself
     m.inline_exchange = (pr.P <= 128 && !pr.sizes_direct) ? 1 : 0;
-    int rc = phase_metadata(m, s, exact_t_of(pr, i), pr.sizes_direct);
+    int rc = phase_metadata(m, s, exact_t_of(pr, i), pr.sizes_direct, !(one_kernel && (small_blocks(pr) || row_blocks(pr))));
     if (rc != TUNA_OK || !one_kernel) return rc;
     return launch_resolve(pr, i, nxt, hop, s);
 }
@@ -930,6 +943,12 @@ void launch_direct_shape(int lpb, int gran, const DirectArgs& a, dim3 grid, bool
     else launch_direct_as<16, TALL, 0>(a, grid, exact, s);
 }
 
+// segments a wave of k_hop_rows takes: about kRowsBytes of payload by the mean block
+int rows_segs(const Prepared& pr) {
+    const double mean = std::max(1.0, (double)pr.total_bytes / ((double)pr.P * (double)pr.P));
+    return (int)std::max(1.0, std::min(64.0, kRowsBytes / mean));
+}
+
 int direct_lpb(const Prepared& pr) { return pr.max_count <= 16 ? 1 : (pr.max_count <= 64 ? 4 : 16); }
 bool direct_tall(const PhaseHost& ph) { return (long long)ph.nz * 16 > ph.nseg; }
 // Workgroup columns and steps per workgroup over `nseg` segments of a phase: one step each while that gives no more than 8192 workgroups (four
@@ -942,8 +961,30 @@ unsigned direct_columns(const Prepared& pr, const PhaseHost& ph, int nseg, int* 
     return (unsigned)((steps + *iters - 1) / *iters);
 }
 unsigned direct_rows(const Prepared& pr, const PhaseHost& ph) {
+    if (row_blocks(pr)) { const int segs = rows_segs(pr); return (unsigned)((ph.nseg + segs - 1) / segs); }
     int iters = 0;
     return direct_columns(pr, ph, ph.nseg, &iters) * (unsigned)(4 / direct_shape(direct_lpb(pr), direct_tall(ph)).waves_r);
+}
+
+template <bool LINES>
+void launch_rows_as(const DirectArgs& a, dim3 grid, bool exact, hipStream_t s) {
+    if (!a.part) hipLaunchKernelGGL((k_hop_rows<LINES, false, true>), grid, dim3(256), 0, s, a);
+    else if (exact) hipLaunchKernelGGL((k_hop_rows<LINES, true, false>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((k_hop_rows<LINES, false, false>), grid, dim3(256), 0, s, a);
+}
+
+// The payload of a phase of blocks of up to kRowsMaxBytes; arguments as launch_direct's.
+int launch_rows(const Prepared& pr, size_t i, const int32_t* nxt, const HopDev& hop, const int32_t* by_source, uint2* part, hipStream_t s) {
+    const PhaseHost& ph = pr.dp->host.phases[i];
+    DirectArgs a{};
+    a.r = resolve_args(pr, i, nxt, hop);
+    a.by_source = by_source; a.T = pr.T; a.seg_lo = 0; a.seg_hi = ph.nseg; a.part = part;
+    a.segs = rows_segs(pr); a.user_limit = pr.user_limit;
+    const dim3 grid((unsigned)((ph.nseg + 4 * a.segs - 1) / (4 * a.segs)), (unsigned)pr.P);
+    if (pr.gran == 128) launch_rows_as<true>(a, grid, pr.exact_kernels, s);
+    else launch_rows_as<false>(a, grid, pr.exact_kernels, s);
+    HIPCHK(hipGetLastError());
+    return TUNA_OK;
 }
 
 // The payload of a phase of short blocks: from the hop arrays (nxt and part null), or resolved in the same kernel from
@@ -1116,6 +1157,12 @@ int launch_phase_data(const Prepared& pr, size_t i, const LayoutDev& Ls, const L
             mark(pr.ctx, s, kCatPack, (int)i);
             continue;
         }
+        if (phase_is_one_kernel(pr, ph) && row_blocks(pr)) {
+            rc = launch_rows(pr, i, nullptr, hop, nullptr, nullptr, s);
+            if (rc != TUNA_OK) return rc;
+            mark(pr.ctx, s, phase_stores_lines(pr, i) ? kCatUnpack : kCatPack, (int)i);
+            continue;
+        }
         if (phase_is_tiled(pr, i)) {
             // tiled over the 16-byte pieces of the destinations (k_copy_tiled); its time is reported as the
             // phase's unpack time, so that it can be told from the copy engine's one-kernel hops
@@ -1190,17 +1237,15 @@ size_t one_pass_meta_bytes(const Prepared& pr) {
            (hld ? hop_bytes_for(pr.P, hld) : 0) + self_meta_bytes(pr);
 }
 
-// An immediate call whose phases are all one-kernel hops of short blocks, all rounds of a phase at once: done in one
-// pass whatever its payload, with k_hop_direct resolving the blocks (tested for room: the partial sums of all phases
-// take the place of the hop arrays).
+// An immediate call whose phases are all one-kernel hops of blocks of up to kRowsMaxBytes, all rounds of a phase at once:
+// done in one pass whatever its payload, k_hop_direct or k_hop_rows finding the blocks themselves.  (What is left of the
+// metadata, a size exchange and the scans of T, is not worth a second stream: 2 to 7 % slower with phases of 64 MiB to
+// 2 GiB, the same at 14 GiB.)
 bool runs_direct(const Prepared& pr) {
-    if (!pr.fused || pr.staggered || pr.block_count > 0 || !small_blocks(pr) || pr.dp->host.phases.empty()) return false;
-    size_t rows = 0;
-    for (const auto& ph : pr.dp->host.phases) rows += direct_rows(pr, ph);
-    return rows <= (size_t)max_hop_ld(pr);
+    return pr.fused && !pr.staggered && pr.block_count == 0 && (small_blocks(pr) || row_blocks(pr)) && !pr.dp->host.phases.empty();
 }
 
-// The metadata of a phase that runs as k_hop_direct: the size exchange, and with exact-size T the places of the
+// The metadata of such a phase: the size exchange, and with exact-size T the places of the
 // blocks the phase stores there.
 int launch_direct_metadata(const Prepared& pr, size_t i, const int32_t* cur, int32_t* nxt, hipStream_t s) {
     if (pr.sizes_direct) return TUNA_OK;
@@ -1221,6 +1266,15 @@ int launch_direct_metadata(const Prepared& pr, size_t i, const int32_t* cur, int
                        m.x, (const unsigned long long*)nullptr, (unsigned long long*)nullptr, (unsigned int*)nullptr);
     HIPCHK(hipGetLastError());
     return TUNA_OK;
+}
+
+// The payload of such a phase, found and moved in one kernel; partial sums into `part` (direct_rows rows of P entries).
+int launch_direct_payload(const Prepared& pr, size_t i, const int32_t* nxt, uint2* part, hipStream_t s) {
+    const int32_t* by_source = pr.sizes_direct ? pr.recvcounts : nullptr;
+    const int rc = row_blocks(pr) ? launch_rows(pr, i, nxt, HopDev{}, by_source, part, s)
+                                  : launch_direct(pr, i, nxt, HopDev{}, 0, pr.dp->host.phases[i].nseg, by_source, part, s);
+    if (rc == TUNA_OK) mark(pr.ctx, s, phase_stores_lines(pr, i) ? kCatUnpack : kCatPack, (int)i);
+    return rc;
 }
 
 // A call in one pass: rotation, the own blocks, then per digit phase its metadata kernels followed at
@@ -1271,24 +1325,32 @@ int run_one_pass(Prepared& pr, void* mbase, size_t mbytes, void* dbase, hipStrea
     int32_t* cur = mb.cur;
     int32_t* nxt = mb.nxt;
     if (direct) {
-        // short blocks: per phase the size exchange, the places of the blocks it stores into exact-size T, and one
-        // kernel that resolves and moves its blocks.  The partial sums lie where the hop arrays would.
-        PhaseRows rows{};
-        uint2* part = reinterpret_cast<uint2*>(pr.hop.src);
+        // per phase the size exchange, the places of the blocks it stores into exact-size T, and one kernel that finds
+        // and moves its blocks.  The partial sums lie where the hop arrays would (a phase has at most one row per
+        // segment) and are added up when there is no room for the next phase's, at the latest at the end.
+        const size_t room = (size_t)pr.hop.ld;
+        size_t used = 0;
+        PhaseParts parts{};
+        auto add_up = [&]() {
+            hipLaunchKernelGGL(k_phase_sums, dim3((unsigned)((P + kWave - 1) / kWave), (unsigned)pl.phases.size()), dim3(256), 0, s, parts, P,
+                               pr.sb.d_status);
+            parts = PhaseParts{};
+            used = 0;
+        };
         for (size_t i = 0; i < pl.phases.size(); ++i) {
             rc = launch_direct_metadata(pr, i, cur, nxt, s);
             if (rc != TUNA_OK) return rc;
             mark(pr.ctx, s, kCatMeta, (int)i);
-            const int nseg = pl.phases[i].nseg;
-            rc = launch_direct(pr, i, nxt, HopDev{}, 0, nseg, pr.sizes_direct ? pr.recvcounts : nullptr,
-                               part + (size_t)rows.row[i] * P, s);
+            const size_t rows = direct_rows(pr, pl.phases[i]);
+            if (used + rows > room) add_up();
+            parts.part[i] = reinterpret_cast<uint2*>(pr.hop.src) + used * P;
+            parts.rows[i] = (int)rows;
+            used += rows;
+            rc = launch_direct_payload(pr, i, nxt, const_cast<uint2*>(parts.part[i]), s);
             if (rc != TUNA_OK) return rc;
-            rows.row[i + 1] = rows.row[i] + (int)direct_rows(pr, pl.phases[i]);
-            mark(pr.ctx, s, kCatPack, (int)i);
             std::swap(cur, nxt);
         }
-        hipLaunchKernelGGL(k_phase_sums, dim3((unsigned)((P + kWave - 1) / kWave), (unsigned)pl.phases.size()), dim3(256), 0, s, part, rows, P,
-                           pr.sb.d_status);
+        add_up();
         HIPCHK(hipGetLastError());
         return TUNA_OK;
     }
@@ -1907,20 +1969,20 @@ struct Model {
     double c[kModelTerms];
 };
 struct ModelSet {
-    Model m[2] = {{{0.0426, 0.0385, 0.0069, 1.0098, 0.0413, 0.0, 0.0}},            // [0] three stages
+    Model m[2] = {{{0.0411, 0.0380, 0.0072, 1.0033, 0.0407, 0.0, 0.0}},            // [0] three stages
                   // [1] one-kernel hops; a gigabyte of short blocks is not priced under one of long blocks, though
-                  // the fit, whose short-block problems are mostly cache resident, says 0.17
-                  {{0.0345, 0.0329, 0.0000, 0.3548, 0.0482, 0.0059, 0.3600}}};
+                  // the fit, whose short-block problems are mostly cache resident, says 0.31
+                  {{0.0221, 0.0265, 0.0012, 0.3680, 0.0247, 0.0061, 0.3700}}};
     // T in the paper's slots of M bytes: the bytes that pass through T cost more the emptier the slots are
     // (sparse writes and reads): their share of the byte term is scaled by 1 + k * (1 - mean / M)
     double slot_penalty[2] = {0.25, 0.45};
     // byte-granular problems (some count, displacement or buffer address is not a multiple of 4) run the
     // kernel variants that load and store single bytes at block edges: their byte term is scaled by this
-    double byte_granular[2] = {1.15, 1.37};
+    double byte_granular[2] = {1.16, 1.07};
     // line-granular problems (every count, displacement and buffer address is a multiple of 128) run the kernel
     // variants that read their sources with streaming loads, and no block shares a line with its neighbour:
     // their byte and block terms are scaled by this
-    double line_granular[2] = {0.90, 0.72};
+    double line_granular[2] = {0.90, 0.84};
     bool calibrated = false;
 };
 ModelSet g_model;

@@ -1129,7 +1129,9 @@ struct DirectArgs {
     const int32_t* by_source;           // schedule of one phase: recvcounts, read at the source's place instead of r.nxt
     unsigned char* T;
     int seg_lo, seg_hi;
-    int iters;                          // steps of direct_segs(LPB) segments per workgroup
+    int iters;                          // steps of segments per workgroup (k_hop_direct)
+    int segs;                           // segments per wave, at most 64 (k_hop_rows)
+    unsigned long long user_limit;      // address one past the last byte of S that holds a block
     uint2* part;                        // [grid.x][P]: payload bytes and chunks of the tile column, per receiver (not when RESOLVED)
 };
 
@@ -1308,20 +1310,201 @@ __global__ void __launch_bounds__(256) k_hop_direct(const DirectArgs a) {
     }
 }
 
-// k_phase_sums: the partial sums of the phases that ran as k_hop_direct, rows [row[x], row[x + 1]) of `part` for
+// pieces segment s owns, and the dead pieces in front of them
+__device__ __forceinline__ int tiled_pieces(unsigned long long a, int n, bool has_prev, unsigned long long e_prev,
+                                            int* dead) {
+    const unsigned long long e = a + (unsigned long long)n;
+    const bool new_run = !has_prev || e_prev != a;
+    const unsigned long long last = (e + 15) >> 4;
+    const unsigned long long first = new_run ? (a >> 7) << 3 : (a + 15) >> 4;
+    *dead = (new_run && has_prev) ? (int)((((e_prev + 127) >> 7) << 3) - ((e_prev + 15) >> 4)) : 0;
+    return last > first ? (int)(last - first) : 0;
+}
+
+// ------------------------------------------------------------------------------------------
+// k_hop_rows: a one-kernel phase of blocks of up to 64 KiB, any sizes, alignment and granularity.  One wave takes
+// `segs` neighbouring segments of one receiver, about 7 KB of payload: lane i finds block s0 + i (source, destination,
+// bytes), a wave scan lays the blocks out as rows of aligned 16-byte pieces of the destination (tiled_pieces), and the
+// wave moves 8 pieces per lane at a time.  What the destination-tiled hop needs a resolve pass, a layout pass and unit
+// lists for -- 40 bytes of hop arrays per block written and read, and four kernels per phase -- lies in one wave's
+// registers and LDS here; the blocks a receiver gets side by side are consecutive segments, so the wave's pieces are one
+// run of R or of a class of T.
+//   Bound by memory (both sides at 5.3 to 5.7 TB/s at 16 GiB, 6.5 TB/s for a plain copy).  A piece inside its block is one
+// 16-byte load at the source's alignment and one aligned streaming store.  The first and the last bytes of a block that
+// are no whole piece are stored by 16-byte accesses that begin or end with the block and overlap the whole pieces beside
+// them (the same bytes twice), so no piece is put together from two blocks and no store is ever narrower; blocks under
+// 16 bytes are stored by the lane that found them.  Byte-granular problems run the same code: accesses at odd addresses
+// are as fast as aligned ones (16-byte loads 1 byte off: 5.6 TB/s in a copy, like aligned ones).
+//   Measured against the destination-tiled hop and the engine's with their metadata kernels: per call, 16 GiB of 1 KiB
+// blocks 6.75 -> 6.35 ms linear and 22.9 -> 22.1 ms at r = 8; 512-byte blocks on average, byte-granular, P = 1000, per
+// start 333 -> 214 us; uniform [0, 512] B, P = 2048, r = 46 1.24 -> 0.99 ms; 512-byte blocks, P = 2048, r = 16
+// 2.57 -> 2.05 ms.  8 pieces per lane against 4: -4 to -9 %.  7000 bytes and not 8192: a wave whose pieces do not fit
+// into one step takes a second, nearly empty one.  Streaming stores against cached ones: -8 to -15 %; streaming loads
+// only where blocks are whole lines (512 bytes: -5 %; 1 KiB blocks at 4-byte alignment: up to +6 %).  Four receivers x
+// the same segments per workgroup instead of one receiver: 1 KiB blocks +3 %; rows of workgroups cut so that one XCD sees
+// the same senders for all receivers: +1 to +13 %.
+// ------------------------------------------------------------------------------------------
+constexpr int kRowsPieces = 8;              // pieces per lane and step
+constexpr int kRowsBytes = 7000;            // payload of one wave, by the mean block
+constexpr int kRowsMaxBytes = 1 << 16;      // a wave moves whole blocks: longer ones would leave the others waiting
+
+// Where block (segment s, receiver p) is read from and stored to, and its bytes: from the hop arrays, or from the
+// tables, matrices and T positions, all loads from valid addresses and without branches so that they go out together.
+// Into T a block takes whole chunks.
+template <bool DENSE, bool RESOLVED>
+__device__ __forceinline__ void find_block(const DirectArgs& a, int p, int s, unsigned long long& src, unsigned long long& dst, int& n,
+                                           int& exact, bool& final) {
+    const ResolveArgs& r = a.r;
+    const unsigned long long tb = (unsigned long long)a.T;
+    bool in_s;
+    if (RESOLVED) {
+        const size_t o = (size_t)p * r.hop.ld + s;
+        const unsigned long long hs = r.hop.src[o], hd = r.hop.dst[o];
+        n = r.hop.size[o];
+        in_s = !(hs & kHopInT);
+        final = !(hd & kHopInT);
+        src = (hs & ~(kHopInT | kHopFill)) + (in_s ? 0ull : tb);
+        dst = (hd & ~(kHopInT | kHopFill)) + (final ? 0ull : tb);
+        exact = n;
+    } else {
+        const int P = r.P, Q = r.Q, N = r.N;
+        const int e = r.seg.e[s], dist = r.seg.z[s] * r.rx, ssrc = r.seg.src[s], sdst = r.seg.dst[s];
+        const int sph = DENSE ? r.seg.srcph[s] : 0, scl = DENSE ? r.seg.scls[s] : 0, dcl = DENSE ? r.seg.dcls[s] : 0;
+        in_s = ssrc < 0;
+        final = sdst < 0;
+        int j, l, pn, pg, qn, qg;
+        split_slot_index(e, Q, N, j, l);
+        split_slot_index(p, Q, N, pn, pg);
+        const int q = partner_up(pn, pg, Q, N, r.dim, dist);
+        split_slot_index(q, Q, N, qn, qg);
+        int dn = qn - j; if (dn < 0) dn += N;
+        int dg = qg - l; if (dg < 0) dg += Q;
+        int sn = pn + j; if (sn >= N) sn -= N;
+        int sg = pg + l; if (sg >= Q) sg -= Q;
+        const size_t row = (size_t)p * P, at_s = (size_t)q * P + dn * Q + dg, at_r = row + sn * Q + sg;
+        n = *(a.by_source ? a.by_source + at_r : r.nxt + row + e);
+        exact = n;
+        if (!final) n = (n + 15) & ~15;
+        if (DENSE) {
+            const int64_t* tbase = reinterpret_cast<const int64_t*>(r.x.tbase);
+            const long long va = *(in_s ? r.sdispls + at_s : tbase + (size_t)scl * P + q);
+            const long long vc = *(final ? r.rdispls + at_r : tbase + (size_t)dcl * P + p);
+            const int vb = *(in_s ? r.seg.e : r.x.tpos + ((size_t)sph * P + q) * P + e);
+            const int vd = *(final ? r.seg.e : r.x.tpre + (size_t)p * r.x.ld + s);
+            src = in_s ? (unsigned long long)r.S + va : tb + ((unsigned long long)(va + vb) << 4);
+            dst = final ? (unsigned long long)r.R + vc : tb + ((unsigned long long)(vc + vd) << 4);
+        } else {
+            const long long va = *(in_s ? r.sdispls + at_s : r.sdispls);
+            const long long vc = *(final ? r.rdispls + at_r : r.rdispls);
+            src = in_s ? (unsigned long long)r.S + va : tb + (unsigned long long)(((long long)q * r.slots + ssrc) * r.slot_bytes);
+            dst = final ? (unsigned long long)r.R + vc : tb + (unsigned long long)(((long long)p * r.slots + sdst) * r.slot_bytes);
+        }
+    }
+    // whole chunks are read past the block's end, but never past the part of S that holds blocks
+    if (in_s && n > 0 && src + (unsigned long long)n > a.user_limit) n = (int)(a.user_limit - src);
+}
+
+// LINES: every block is whole 128-byte lines (streaming loads)
+template <bool LINES, bool DENSE, bool RESOLVED>
+__global__ void __launch_bounds__(256) k_hop_rows(const DirectArgs a) {
+    constexpr int CPL = kRowsPieces;
+    __shared__ int s_pre[4][kWave], s_off0[4][kWave], s_n[4][kWave];
+    __shared__ unsigned long long s_src[4][kWave], s_dst[4][kWave];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int P = a.r.P;
+    const int p = blockIdx.y;
+    const int grp = blockIdx.x * 4 + wv;
+    const int s0 = a.seg_lo + grp * a.segs;
+    if (s0 >= a.seg_hi) return;                          // no barrier below: a wave may leave alone
+    const bool in = lane < a.segs && s0 + lane < a.seg_hi;
+    unsigned long long src, dst;
+    int n, exact;
+    bool final;
+    find_block<DENSE, RESOLVED>(a, p, min(s0 + min(lane, a.segs - 1), a.seg_hi - 1), src, dst, n, exact, final);
+    if (!in || n < 0) n = exact = 0;
+    if (!RESOLVED) {
+        unsigned int b = (unsigned int)exact, c = n > 0 ? ((final ? (unsigned int)(dst & 15ull) : 0u) + (unsigned int)exact + 15u) >> 4 : 0u;
+#pragma unroll
+        for (int d = kWave / 2; d > 0; d >>= 1) { b += __shfl_xor(b, d, kWave); c += __shfl_xor(c, d, kWave); }
+        if (lane == 0) a.part[(size_t)grp * P + p] = make_uint2(b, c);
+    }
+    // ---- the wave's blocks as rows of aligned 16-byte pieces of the destination (tiled_pieces); the part of a block
+    // in front of its first whole piece is its head
+    unsigned long long e_prev = __shfl_up(dst + (unsigned long long)n, 1, kWave);
+    int dead;
+    const int own = tiled_pieces(dst, n, lane > 0, e_prev, &dead);
+    const bool new_run = lane == 0 || e_prev != dst;
+    const int cnt = in ? dead + own : 0;
+    const int incl = wave_incl_scan(cnt);
+    const int total = __builtin_amdgcn_readlane(incl, kWave - 1);
+    s_pre[wv][lane] = incl - cnt;
+    s_off0[wv][lane] = (new_run ? -(int)((unsigned int)dst & 127u) : (int)((0u - (unsigned int)dst) & 15u)) - (dead << 4);
+    s_n[wv][lane] = n; s_src[wv][lane] = src; s_dst[wv][lane] = dst;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const unsigned long long dummy = (unsigned long long)a.r.seg.e;
+    // ---- heads, and blocks of fewer than 16 bytes, by the lane that found the block
+    const bool head = n >= 16 && (dst & 15ull);
+    const v4u hv = load_global<v4u_any>(head ? src : dummy);
+    const int ns = n < 16 ? n : 0;
+    const bool any_short = __ballot(ns > 0) != 0;
+    if (any_short) short_store(dst, src, ns, short_load(src, ns, dummy));
+    bool stored = false;
+    int top = 1;
+    while (2 * top < a.segs) top *= 2;
+    for (int base = 0; base < total; base += kWave * CPL) {
+        int lo[CPL];
+#pragma unroll
+        for (int k = 0; k < CPL; ++k) lo[k] = 0;
+        for (int step = top; step > 0; step >>= 1) {
+#pragma unroll
+            for (int k = 0; k < CPL; ++k) {
+                const int c = base + k * kWave + lane;
+                if (s_pre[wv][lo[k] + step] <= c) lo[k] += step;      // entries behind the last block hold the total
+            }
+        }
+        v4u v[CPL];
+        unsigned long long d[CPL];
+        bool act[CPL];
+#pragma unroll
+        for (int k = 0; k < CPL; ++k) {
+            const int c = base + k * kWave + lane;
+            const int nb = s_n[wv][lo[k]];
+            const int off = s_off0[wv][lo[k]] + ((c - s_pre[wv][lo[k]]) << 4);
+            act[k] = off >= 0 && off < nb && nb >= 16;
+            const int o = min(off, nb - 16);             // the last piece ends with the block
+            const unsigned long long sa = s_src[wv][lo[k]] + (unsigned long long)(long long)o;
+            d[k] = s_dst[wv][lo[k]] + (unsigned long long)(long long)o;
+            const TUNA_GLOBAL v4u_any* from = (const TUNA_GLOBAL v4u_any*)(act[k] ? sa : dummy);
+            v[k] = LINES ? __builtin_nontemporal_load(from) : *from;
+        }
+        if (!stored) {
+            stored = true;
+            if (head) store_global<v4u_any>(dst, hv);
+        }
+#pragma unroll
+        for (int k = 0; k < CPL; ++k)
+            if (act[k]) __builtin_nontemporal_store(v[k], (TUNA_GLOBAL v4u_any*)d[k]);
+    }
+}
+
+// k_phase_sums: the partial sums of the phases that ran as k_hop_direct or k_hop_rows, rows[x] rows of P entries for
 // phase x, into the status block: payload bytes, and staged chunks with every receiver's share rounded up to a line
 // as the staging layouts round it.  Four threads per receiver, grid (ceil(P / 64), phases); k_validate_finish cleared
 // the totals.
-struct PhaseRows { int row[64 + 1]; };
-__global__ void __launch_bounds__(256) k_phase_sums(const uint2* __restrict__ part, PhaseRows rows, int P, Status* __restrict__ st) {
+struct PhaseParts { const uint2* part[64]; int rows[64]; };
+__global__ void __launch_bounds__(256) k_phase_sums(PhaseParts parts, int P, Status* __restrict__ st) {
     __shared__ unsigned long long s_b[4][kWave], s_c[4][kWave];
     const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
     const int p = blockIdx.x * kWave + lane, x = blockIdx.y;
-    const int r1 = rows.row[x + 1];
+    const uint2* part = parts.part[x];
+    const int rows = parts.rows[x];
     unsigned long long b = 0, c = 0;
     if (p < P) {
 #pragma unroll 8
-        for (int i = rows.row[x] + wv; i < r1; i += 4) { const uint2 v = part[(size_t)i * P + p]; b += v.x; c += v.y; }
+        for (int i = wv; i < rows; i += 4) { const uint2 v = part[(size_t)i * P + p]; b += v.x; c += v.y; }
     }
     s_b[wv][lane] = b; s_c[wv][lane] = c;
     __syncthreads();
@@ -1645,17 +1828,6 @@ struct TiledLayoutArgs {
     LayoutDev Lr;
     unsigned long long* rank_bytes;     // [P]: payload bytes every rank receives in the phase; nullptr: already known
 };
-
-// pieces segment s owns, and the dead pieces in front of them
-__device__ __forceinline__ int tiled_pieces(unsigned long long a, int n, bool has_prev, unsigned long long e_prev,
-                                            int* dead) {
-    const unsigned long long e = a + (unsigned long long)n;
-    const bool new_run = !has_prev || e_prev != a;
-    const unsigned long long last = (e + 15) >> 4;
-    const unsigned long long first = new_run ? (a >> 7) << 3 : (a + 15) >> 4;
-    *dead = (new_run && has_prev) ? (int)((((e_prev + 127) >> 7) << 3) - ((e_prev + 15) >> 4)) : 0;
-    return last > first ? (int)(last - first) : 0;
-}
 
 __global__ void __launch_bounds__(kScanThreads) k_tiled_layout(const TiledLayoutArgs a) {
     __shared__ int wsum[kScanThreads / kWave];
