@@ -556,6 +556,7 @@ struct Prepared {
     long long* d_cbase = nullptr;       // [classes]: where the host placed every class in T
     std::vector<long long> cbase;       // the same on the host
     unsigned long long t_chunks = 0;    // chunks of exact-size T as laid out
+    uint2* pairs = nullptr;             // first phase's T-bound blocks by segment (launch_t_places)
     HopDev hop{};                       // one-kernel phases of a one-pass call: the resolved addresses of the phase being run
     // the ranks' own blocks: moved by the copy engine when blocks can be large (see launch_self_copy)
     bool self_engine = false;
@@ -860,7 +861,7 @@ int launch_tiled_metadata(const Prepared& pr, size_t i, const int32_t* cur, int3
         PhaseLayoutArgs m{};
         m.cur = cur; m.nxt = nxt; m.zt = pr.dp->d_zt[i]; m.seg = pr.dp->d_seg[i]; m.nseg = ph.nseg;
         m.P = P; m.Q = pr.Q; m.N = pr.N; m.dim = ph.dim; m.rx = (int)ph.rx;
-        m.Ls = Ls; m.Lr = Lr; m.want_chunks = 1; m.want_send = 0; m.want_tbound = 1; m.x = exact_t_of(pr, i);
+        m.Ls = Ls; m.Lr = Lr; m.want_send = 0; m.want_tbound = 1; m.x = exact_t_of(pr, i);
         m.rank_bytes = pr.rank_bytes;
         m.phase_bytes = &pr.sb.d_status->phase_bytes[i]; m.phase_chunks = &pr.sb.d_status->phase_chunks[i];
         m.phase_units = pr.sb.d_status->phase_units[i];
@@ -895,7 +896,7 @@ int launch_phase_metadata(const Prepared& pr, size_t i, const int32_t* cur, int3
     PhaseLayoutArgs m{};
     m.cur = cur; m.nxt = nxt; m.zt = pr.dp->d_zt[i]; m.seg = pr.dp->d_seg[i]; m.nseg = ph.nseg;
     m.P = pr.P; m.Q = pr.Q; m.N = pr.N; m.dim = ph.dim; m.rx = (int)ph.rx;
-    m.Ls = Ls; m.Lr = Lr; m.want_chunks = 1; m.want_send = one_kernel ? 0 : 1;
+    m.Ls = Ls; m.Lr = Lr; m.want_send = one_kernel ? 0 : 1;
     if (pr.exact_t) { m.want_tbound = 1; m.x = exact_t_of(pr, i); }
     m.rank_bytes = pr.rank_bytes;
     m.phase_bytes = &pr.sb.d_status->phase_bytes[i]; m.phase_chunks = &pr.sb.d_status->phase_chunks[i];
@@ -916,13 +917,16 @@ ResolveArgs resolve_args(const Prepared& pr, size_t i, const int32_t* nxt, const
     const PhaseHost& ph = pr.dp->host.phases[i];
     ResolveArgs ra{};
     ra.nxt = nxt; ra.seg = pr.dp->d_seg[i]; ra.nseg = ph.nseg;
+    ra.sendcounts = pr.sendcounts; ra.recvcounts = pr.recvcounts;
     ra.P = pr.P; ra.Q = pr.Q; ra.N = pr.N; ra.dim = ph.dim; ra.rx = (int)ph.rx;
+    ra.rx1 = (int)std::min<int64_t>(ph.rx * ph.r, INT_MAX);
     ra.S = (const unsigned char*)pr.sendbuf; ra.sdispls = pr.sdispls;
     ra.R = (unsigned char*)pr.recvbuf; ra.rdispls = pr.rdispls;
     ra.slots = pr.ds.slots; ra.slot_bytes = pr.ds.slot_bytes;
     ra.x = exact_t_of(pr, i);
     ra.hop = hop;
     ra.exact_sizes = small_blocks(pr) ? 1 : 0;
+    if (i == 0 && pr.pairs) { ra.pairs = pr.pairs; ra.pairs_ld = pr.hop.ld; }
     return ra;
 }
 
@@ -974,11 +978,11 @@ void launch_rows_as(const DirectArgs& a, dim3 grid, bool exact, hipStream_t s) {
 }
 
 // The payload of a phase of blocks of up to kRowsMaxBytes; arguments as launch_direct's.
-int launch_rows(const Prepared& pr, size_t i, const int32_t* nxt, const HopDev& hop, const int32_t* by_source, uint2* part, hipStream_t s) {
+int launch_rows(const Prepared& pr, size_t i, const HopDev& hop, uint2* part, hipStream_t s) {
     const PhaseHost& ph = pr.dp->host.phases[i];
     DirectArgs a{};
-    a.r = resolve_args(pr, i, nxt, hop);
-    a.by_source = by_source; a.T = pr.T; a.seg_lo = 0; a.seg_hi = ph.nseg; a.part = part;
+    a.r = resolve_args(pr, i, nullptr, hop);
+    a.T = pr.T; a.seg_lo = 0; a.seg_hi = ph.nseg; a.part = part;
     a.segs = rows_segs(pr); a.user_limit = pr.user_limit;
     const dim3 grid((unsigned)((ph.nseg + 4 * a.segs - 1) / (4 * a.segs)), (unsigned)pr.P);
     if (pr.gran == 128) launch_rows_as<true>(a, grid, pr.exact_kernels, s);
@@ -987,15 +991,14 @@ int launch_rows(const Prepared& pr, size_t i, const int32_t* nxt, const HopDev& 
     return TUNA_OK;
 }
 
-// The payload of a phase of short blocks: from the hop arrays (nxt and part null), or resolved in the same kernel from
-// the block sizes after the phase (nxt) or the receive counts (by_source), with partial sums into `part`.
-int launch_direct(const Prepared& pr, size_t i, const int32_t* nxt, const HopDev& hop, int seg_lo, int seg_hi,
-                  const int32_t* by_source, uint2* part, hipStream_t s) {
+// The payload of a phase of short blocks: from the hop arrays (part null), or found in the same kernel, with partial
+// sums into `part`.
+int launch_direct(const Prepared& pr, size_t i, const HopDev& hop, int seg_lo, int seg_hi, uint2* part, hipStream_t s) {
     if (seg_hi <= seg_lo) return TUNA_OK;
     const PhaseHost& ph = pr.dp->host.phases[i];
     DirectArgs a{};
-    a.r = resolve_args(pr, i, nxt, hop);
-    a.by_source = by_source; a.T = pr.T; a.seg_lo = seg_lo; a.seg_hi = seg_hi; a.part = part;
+    a.r = resolve_args(pr, i, nullptr, hop);
+    a.T = pr.T; a.seg_lo = seg_lo; a.seg_hi = seg_hi; a.part = part;
     const unsigned cols = direct_columns(pr, ph, seg_hi - seg_lo, &a.iters);
     const int lpb = direct_lpb(pr), ranks = direct_ranks(direct_shape(lpb, direct_tall(ph)));
     const dim3 grid(cols, (unsigned)((pr.P + ranks - 1) / ranks));
@@ -1152,13 +1155,13 @@ int launch_phase_data(const Prepared& pr, size_t i, const LayoutDev& Ls, const L
         }
         int rc;
         if (phase_is_one_kernel(pr, ph) && small_blocks(pr)) {
-            rc = launch_direct(pr, i, nullptr, hop, a.seg_lo, a.seg_hi, nullptr, nullptr, s);
+            rc = launch_direct(pr, i, hop, a.seg_lo, a.seg_hi, nullptr, s);
             if (rc != TUNA_OK) return rc;
             mark(pr.ctx, s, kCatPack, (int)i);
             continue;
         }
         if (phase_is_one_kernel(pr, ph) && row_blocks(pr)) {
-            rc = launch_rows(pr, i, nullptr, hop, nullptr, nullptr, s);
+            rc = launch_rows(pr, i, hop, nullptr, s);
             if (rc != TUNA_OK) return rc;
             mark(pr.ctx, s, phase_stores_lines(pr, i) ? kCatUnpack : kCatPack, (int)i);
             continue;
@@ -1239,40 +1242,43 @@ size_t one_pass_meta_bytes(const Prepared& pr) {
 
 // An immediate call whose phases are all one-kernel hops of blocks of up to kRowsMaxBytes, all rounds of a phase at once:
 // done in one pass whatever its payload, k_hop_direct or k_hop_rows finding the blocks themselves.  (What is left of the
-// metadata, a size exchange and the scans of T, is not worth a second stream: 2 to 7 % slower with phases of 64 MiB to
-// 2 GiB, the same at 14 GiB.)
+// metadata is not worth a second stream: with a size exchange and the scans of T per phase on one, calls were 2 to 7 %
+// slower with phases of 64 MiB to 2 GiB and the same at 14 GiB.)
 bool runs_direct(const Prepared& pr) {
-    return pr.fused && !pr.staggered && pr.block_count == 0 && (small_blocks(pr) || row_blocks(pr)) && !pr.dp->host.phases.empty();
+    return pr.fused && !pr.staggered && pr.block_count == 0 && (small_blocks(pr) || row_blocks(pr)) && !pr.dp->host.phases.empty() &&
+           pr.dp->host.phases.size() <= kPlaceMaxPhases;
 }
 
-// The metadata of such a phase: the size exchange, and with exact-size T the places of the
-// blocks the phase stores there.
-int launch_direct_metadata(const Prepared& pr, size_t i, const int32_t* cur, int32_t* nxt, hipStream_t s) {
-    if (pr.sizes_direct) return TUNA_OK;
-    const PhaseHost& ph = pr.dp->host.phases[i];
-    const int P = pr.P;
-    hipLaunchKernelGGL(k_size_exchange, dim3((unsigned)((P + 255) / 256), (unsigned)((P + kExchangeRanks - 1) / kExchangeRanks)),
-                       dim3(256), 0, s, cur, nxt, pr.dp->d_zt[i], P, pr.Q, pr.N, ph.dim, (int)ph.rx);
+// All the metadata of such a call: with exact-size T the places of the blocks that its phases store there.
+// The pairs lie in the hop arrays' destinations, which such a call does not use.
+constexpr int kPairsMinRadix = 16;          // neighbours 64 bytes apart and more
+int launch_t_places(Prepared& pr, hipStream_t s) {
+    if (!pr.exact_t) return TUNA_OK;
+    if (pr.dp->host.phases[0].r >= kPairsMinRadix) pr.pairs = reinterpret_cast<uint2*>(pr.hop.dst);
+    const PlanHost& pl = pr.dp->host;
+    PlaceArgs a{};
+    a.P = pr.P; a.Q = pr.Q; a.N = pr.N; a.sendcounts = pr.sendcounts; a.recvcounts = pr.recvcounts; a.x = exact_t_of(pr, 0);
+    a.pairs = pr.pairs; a.pairs_ld = pr.hop.ld;
+    int rows = 0;
+    for (size_t i = 0; i < pl.phases.size(); ++i) {
+        const int ncls = (int)(pr.dp->tcls[i].size() / 3);
+        if (!ncls) continue;
+        a.ph[a.nph++] = PlacePhase{pr.dp->d_seg[i].e, pr.dp->d_seg[i].src, pr.dp->d_tord[i], pr.dp->d_tcls[i], (int)i, rows, pl.phases[i].dim,
+                                   (int)std::min<int64_t>(pl.phases[i].rx * pl.phases[i].r, INT_MAX)};
+        rows += ncls;
+    }
+    if (!rows) return TUNA_OK;
+    hipLaunchKernelGGL(k_t_places, dim3((unsigned)pr.P, (unsigned)rows), dim3(kScanThreads), 0, s, a);
     HIPCHK(hipGetLastError());
-    PhaseLayoutArgs m{};
-    m.x = exact_t_of(pr, i);
-    if (!pr.exact_t || m.x.ncls == 0) return TUNA_OK;
-    m.cur = cur; m.nxt = nxt; m.zt = pr.dp->d_zt[i]; m.seg = pr.dp->d_seg[i]; m.nseg = ph.nseg;
-    m.P = P; m.Q = pr.Q; m.N = pr.N; m.dim = ph.dim; m.rx = (int)ph.rx;
-    m.want_tbound = 1;
-    hipLaunchKernelGGL(k_phase_layout, dim3(P), dim3(kScanThreads), 0, s, m);
-    HIPCHK(hipGetLastError());
-    hipLaunchKernelGGL(k_layout_base, dim3(m.x.ncls), dim3(kScanThreads), 0, s, P, LayoutDev{}, LayoutDev{}, 0, (unsigned long long*)nullptr, -1,
-                       m.x, (const unsigned long long*)nullptr, (unsigned long long*)nullptr, (unsigned int*)nullptr);
+    hipLaunchKernelGGL(k_t_bases, dim3((unsigned)rows), dim3(kScanThreads), 0, s, a);
     HIPCHK(hipGetLastError());
     return TUNA_OK;
 }
 
 // The payload of such a phase, found and moved in one kernel; partial sums into `part` (direct_rows rows of P entries).
-int launch_direct_payload(const Prepared& pr, size_t i, const int32_t* nxt, uint2* part, hipStream_t s) {
-    const int32_t* by_source = pr.sizes_direct ? pr.recvcounts : nullptr;
-    const int rc = row_blocks(pr) ? launch_rows(pr, i, nxt, HopDev{}, by_source, part, s)
-                                  : launch_direct(pr, i, nxt, HopDev{}, 0, pr.dp->host.phases[i].nseg, by_source, part, s);
+int launch_direct_payload(const Prepared& pr, size_t i, uint2* part, hipStream_t s) {
+    const int rc = row_blocks(pr) ? launch_rows(pr, i, HopDev{}, part, s)
+                                  : launch_direct(pr, i, HopDev{}, 0, pr.dp->host.phases[i].nseg, part, s);
     if (rc == TUNA_OK) mark(pr.ctx, s, phase_stores_lines(pr, i) ? kCatUnpack : kCatPack, (int)i);
     return rc;
 }
@@ -1308,11 +1314,12 @@ int run_one_pass(Prepared& pr, void* mbase, size_t mbytes, void* dbase, hipStrea
     const bool direct = runs_direct(pr);
     // A schedule of one phase whose block sizes nobody asked to see: every block arrives in its only hop, so what
     // the phase's metadata exchange would leave in the receivers' size arrays is recvcounts, rotated (validation
-    // has checked that it is the transpose of sendcounts): one kernel instead of the rotation and the exchange,
-    // and none when the blocks are short (k_hop_direct reads recvcounts itself).
+    // has checked that it is the transpose of sendcounts): one kernel instead of the rotation and the exchange.
+    // Phases that find their blocks themselves need neither.
     pr.sizes_direct = pl.phases.size() == 1 && pr.fused && !pr.debug_sizes;
-    if (pr.sizes_direct && !direct) hipLaunchKernelGGL(k_rotate_init, grot, dim3(256), 0, s, pr.recvcounts, mb.nxt, P, pr.Q, pr.N, 1);
-    else if (!pr.sizes_direct) hipLaunchKernelGGL(k_rotate_init, grot, dim3(256), 0, s, pr.sendcounts, mb.cur, P, pr.Q, pr.N, 0);
+    if (direct) (void)0;
+    else if (pr.sizes_direct) hipLaunchKernelGGL(k_rotate_init, grot, dim3(256), 0, s, pr.recvcounts, mb.nxt, P, pr.Q, pr.N, 1);
+    else hipLaunchKernelGGL(k_rotate_init, grot, dim3(256), 0, s, pr.sendcounts, mb.cur, P, pr.Q, pr.N, 0);
     HIPCHK(hipGetLastError());
     mark(pr.ctx, s, kCatPrepare, -1);
     rc = launch_self_metadata(pr, s);
@@ -1325,9 +1332,11 @@ int run_one_pass(Prepared& pr, void* mbase, size_t mbytes, void* dbase, hipStrea
     int32_t* cur = mb.cur;
     int32_t* nxt = mb.nxt;
     if (direct) {
-        // per phase the size exchange, the places of the blocks it stores into exact-size T, and one kernel that finds
-        // and moves its blocks.  The partial sums lie where the hop arrays would (a phase has at most one row per
+        // the places in exact-size T, then one kernel per phase that finds and moves its blocks.  The partial sums lie where the hop arrays would (a phase has at most one row per
         // segment) and are added up when there is no room for the next phase's, at the latest at the end.
+        rc = launch_t_places(pr, s);
+        if (rc != TUNA_OK) return rc;
+        mark(pr.ctx, s, kCatMeta, 0);
         const size_t room = (size_t)pr.hop.ld;
         size_t used = 0;
         PhaseParts parts{};
@@ -1338,17 +1347,14 @@ int run_one_pass(Prepared& pr, void* mbase, size_t mbytes, void* dbase, hipStrea
             used = 0;
         };
         for (size_t i = 0; i < pl.phases.size(); ++i) {
-            rc = launch_direct_metadata(pr, i, cur, nxt, s);
-            if (rc != TUNA_OK) return rc;
-            mark(pr.ctx, s, kCatMeta, (int)i);
             const size_t rows = direct_rows(pr, pl.phases[i]);
             if (used + rows > room) add_up();
+            if (i) mark(pr.ctx, s, kCatMeta, (int)i);        // all phases' places were found before the first: next to nothing
             parts.part[i] = reinterpret_cast<uint2*>(pr.hop.src) + used * P;
             parts.rows[i] = (int)rows;
             used += rows;
-            rc = launch_direct_payload(pr, i, nxt, const_cast<uint2*>(parts.part[i]), s);
+            rc = launch_direct_payload(pr, i, const_cast<uint2*>(parts.part[i]), s);
             if (rc != TUNA_OK) return rc;
-            std::swap(cur, nxt);
         }
         add_up();
         HIPCHK(hipGetLastError());
@@ -1969,20 +1975,20 @@ struct Model {
     double c[kModelTerms];
 };
 struct ModelSet {
-    Model m[2] = {{{0.0411, 0.0380, 0.0072, 1.0033, 0.0407, 0.0, 0.0}},            // [0] three stages
+    Model m[2] = {{{0.0405, 0.0378, 0.0068, 1.0048, 0.0414, 0.0, 0.0}},            // [0] three stages
                   // [1] one-kernel hops; a gigabyte of short blocks is not priced under one of long blocks, though
-                  // the fit, whose short-block problems are mostly cache resident, says 0.31
-                  {{0.0221, 0.0265, 0.0012, 0.3680, 0.0247, 0.0061, 0.3700}}};
+                  // the fit, whose short-block problems are mostly cache resident, says 0.30
+                  {{0.0366, 0.0133, 0.0016, 0.3783, 0.0193, 0.0053, 0.3800}}};
     // T in the paper's slots of M bytes: the bytes that pass through T cost more the emptier the slots are
     // (sparse writes and reads): their share of the byte term is scaled by 1 + k * (1 - mean / M)
     double slot_penalty[2] = {0.25, 0.45};
     // byte-granular problems (some count, displacement or buffer address is not a multiple of 4) run the
     // kernel variants that load and store single bytes at block edges: their byte term is scaled by this
-    double byte_granular[2] = {1.16, 1.07};
+    double byte_granular[2] = {1.15, 1.05};
     // line-granular problems (every count, displacement and buffer address is a multiple of 128) run the kernel
     // variants that read their sources with streaming loads, and no block shares a line with its neighbour:
     // their byte and block terms are scaled by this
-    double line_granular[2] = {0.90, 0.84};
+    double line_granular[2] = {0.90, 0.83};
     bool calibrated = false;
 };
 ModelSet g_model;
@@ -2001,8 +2007,8 @@ Features features_of(const PlanHost& pl, double payload_bytes, bool small) {
     for (const auto& ph : pl.phases) moving += (double)ph.nseg * P;
     (small ? f.msmall : f.mblocks) = moving / 1e6;
     // A short block of a schedule of one phase is looked up in the receive counts and the displacements; with several
-    // phases its size is rotated and exchanged, its place in T scanned and looked up.  Uniform [0, 16] B at P = 2048
-    // takes 4 ns per block at r = P and 15 to 16 ns per block and phase at r = 2, 8 and 46.
+    // phases its place in T is scanned, stored and looked up twice, and most lookups leave the rows of one rank.  Four
+    // times the constant fits uniform [0, 16] B at P = 2048 within 10 % at r = 2, 8, 46 and P.
     if (small && f.phases > 1.0) f.msmall *= 4.0;
     // sizes are taken to be independent of the rank distance: every slot index carries payload / P^2
     (small ? f.small_gb : f.hop_gb) = P > 0 ? payload_bytes * (moving / (P * P)) / 1e9 : 0.0;

@@ -566,7 +566,6 @@ struct PhaseLayoutArgs {
     int nseg;
     int P, Q, N, dim, rx;
     LayoutDev Ls, Lr;
-    int want_chunks;                // 0: no chunk layouts at all, only the T-bound blocks (phases of short blocks)
     int want_send;                  // 0: only the receive-side layout (one-kernel phases)
     int want_tbound;                // 1: also lay out the blocks this phase stores into exact-size T (see ExactT)
     ExactT x;
@@ -702,7 +701,7 @@ __global__ void __launch_bounds__(kScanThreads) k_phase_layout(const PhaseLayout
     int* pre_s = a.Ls.pre + (size_t)p * a.Ls.ld;
     int carry_r = 0, carry_s = 0;
     unsigned long long bytes = 0;
-    for (int base = 0; base < a.nseg && (a.want_chunks || a.inline_exchange); base += kScanThreads * kScanItems) {
+    for (int base = 0; base < a.nseg; base += kScanThreads * kScanItems) {
         int cr[kScanItems], cs[kScanItems];
 #pragma unroll
         for (int k = 0; k < kScanItems; ++k) {
@@ -718,7 +717,7 @@ __global__ void __launch_bounds__(kScanThreads) k_phase_layout(const PhaseLayout
                     szr = nrow[e];
                 }
                 if (a.want_send) szs = crow[e];
-                if (a.want_chunks && a.head_displs && szr > 0 && a.seg.dst[s] < 0) {
+                if (a.head_displs && szr > 0 && a.seg.dst[s] < 0) {
                     int j, l;
                     split_slot_index(e, a.Q, a.N, j, l);
                     int sn = pn + j; if (sn >= a.N) sn -= a.N;
@@ -730,7 +729,6 @@ __global__ void __launch_bounds__(kScanThreads) k_phase_layout(const PhaseLayout
             cr[k] = (head + szr + 15) >> 4;
             cs[k] = (szs + 15) >> 4;
         }
-        if (!a.want_chunks) continue;
         int run[kScanItems];
         block_scan_batch(cr, run, carry_r, wsum);
 #pragma unroll
@@ -779,7 +777,6 @@ __global__ void __launch_bounds__(kScanThreads) k_phase_layout(const PhaseLayout
             if (tid == 0) a.x.csub[(size_t)cid * P + p] = carry_t;
         }
     }
-    if (!a.want_chunks) return;
 #pragma unroll
     for (int d = kWave / 2; d > 0; d >>= 1) bytes += __shfl_xor(bytes, d, kWave);
     // one sum per rank, added up by k_layout_base: thousands of atomics on one address would take
@@ -796,6 +793,35 @@ __global__ void __launch_bounds__(kScanThreads) k_phase_layout(const PhaseLayout
     if (tid == 0) {
         pre_r[a.nseg] = carry_r; a.Lr.tot[p] = carry_r;
         if (a.want_send) { pre_s[a.nseg] = carry_s; a.Ls.tot[p] = carry_s; }
+    }
+}
+
+// A class of exact-size T: rank p's part starts at the class's first chunk plus the parts of the ranks before it, each
+// rounded up to a 128-byte line.  One workgroup of kScanThreads.
+__device__ __forceinline__ void class_base(const ExactT& x, int cid, int P, long long* wc) {
+    const int* sub = x.csub + (size_t)cid * P;
+    long long* base = x.tbase + (size_t)cid * P;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    const int per = (P + kScanThreads - 1) / kScanThreads;
+    const int p0 = min(P, tid * per), p1 = min(P, p0 + per);
+    long long sc = 0;
+    for (int p = p0; p < p1; ++p) sc += (sub[p] + kRankAlignChunks - 1) / kRankAlignChunks * kRankAlignChunks;
+    long long ic = sc;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const long long uc = __shfl_up(ic, d, kWave);
+        if (lane >= d) ic += uc;
+    }
+    if (lane == kWave - 1) wc[wv] = ic;
+    __syncthreads();
+    long long oc = 0;
+#pragma unroll
+    for (int k = 0; k < kScanThreads / kWave; ++k)
+        if (k < wv) oc += wc[k];
+    long long run = x.cbase[cid] + oc + ic - sc;
+    for (int p = p0; p < p1; ++p) {
+        base[p] = run;
+        run += (sub[p] + kRankAlignChunks - 1) / kRankAlignChunks * kRankAlignChunks;
     }
 }
 
@@ -822,33 +848,7 @@ __global__ void __launch_bounds__(kScanThreads) k_layout_base(int P, LayoutDev L
                         phase_units + which);             // layout 0 is the receive side, 1 the send side
         return;
     }
-    // a class of exact-size T: rank p's part starts at the class's first chunk plus the parts of the
-    // ranks before it, each rounded up to a 128-byte line
-    const int cid = x.tcls[3 * (which - n_layouts)];
-    const int* sub = x.csub + (size_t)cid * P;
-    long long* base = x.tbase + (size_t)cid * P;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
-    const int per = (P + kScanThreads - 1) / kScanThreads;
-    const int p0 = min(P, tid * per), p1 = min(P, p0 + per);
-    long long sc = 0;
-    for (int p = p0; p < p1; ++p) sc += (sub[p] + kRankAlignChunks - 1) / kRankAlignChunks * kRankAlignChunks;
-    long long ic = sc;
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const long long uc = __shfl_up(ic, d, kWave);
-        if (lane >= d) ic += uc;
-    }
-    if (lane == kWave - 1) wc[wv] = ic;
-    __syncthreads();
-    long long oc = 0;
-#pragma unroll
-    for (int k = 0; k < kScanThreads / kWave; ++k)
-        if (k < wv) oc += wc[k];
-    long long run = x.cbase[cid] + oc + ic - sc;
-    for (int p = p0; p < p1; ++p) {
-        base[p] = run;
-        run += (sub[p] + kRankAlignChunks - 1) / kRankAlignChunks * kRankAlignChunks;
-    }
+    class_base(x, x.tcls[3 * (which - n_layouts)], P, wc);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1016,7 +1016,12 @@ __device__ __forceinline__ unsigned long long exact_t_src(unsigned char* T, cons
 // persistent plan resolves them before its T is allocated.
 // ------------------------------------------------------------------------------------------
 struct ResolveArgs {
-    const int32_t* nxt;                 // [P][P] block sizes after the phase's size exchange (the receiver's view)
+    const int32_t* nxt;                 // [P][P] block sizes after the phase's size exchange (the receiver's view); k_resolve_hop only
+    const int32_t* sendcounts;          // block sizes for the kernels that find their blocks themselves (block_bytes)
+    const int32_t* recvcounts;
+    int rx1;                            // r^(x+1) of the phase
+    const uint2* pairs;                 // first phase of a schedule with exact-size T: [P][pairs_ld] by segment, the T-bound blocks' chunk offset and bytes
+    int pairs_ld;
     SegDev seg;
     int nseg;
     int P, Q, N, dim, rx;
@@ -1126,7 +1131,6 @@ constexpr int direct_segs(DirectShape s) { return kWave / s.wave_ranks * (4 / s.
 constexpr int direct_ranks(DirectShape s) { return s.wave_ranks * s.sets * s.waves_r; }
 struct DirectArgs {
     ResolveArgs r;                      // hop: only when RESOLVED
-    const int32_t* by_source;           // schedule of one phase: recvcounts, read at the source's place instead of r.nxt
     unsigned char* T;
     int seg_lo, seg_hi;
     int iters;                          // steps of segments per workgroup (k_hop_direct)
@@ -1166,6 +1170,100 @@ __device__ __forceinline__ void short_store(unsigned long long dst, unsigned lon
         const unsigned char c0 = load_global<unsigned char>(src), c1 = load_global<unsigned char>(src + (n >> 1)), c2 = load_global<unsigned char>(src + n - 1);
         store_global<unsigned char>(dst, c0); store_global<unsigned char>(dst + (n >> 1), c1); store_global<unsigned char>(dst + n - 1, c2);
     }
+}
+
+// Where the bytes of a block are written down.  Block (j, l) of rank (n, g) in phase (dim, x), after its hop: it has
+// covered the digits up to x of its distance, so it comes from O = (n, g) + that part and is bound for D = O - (j, l)
+// (Algorithm "TuNA", line 14, without the exchange: in one memory every size can be looked up where the caller wrote
+// it).  The entry of recvcounts is the nearer one where neighbouring blocks have one destination (final blocks, and
+// all later phases: runs of r^(x+1) blocks), that of sendcounts where they have one origin (never moved before).
+__device__ __forceinline__ const int32_t* block_bytes(const int32_t* sendcounts, const int32_t* recvcounts, bool in_s, int n, int g, int j,
+                                                      int l, int P, int Q, int N, int dim, int rx1) {
+    int on = n, og = g + l;
+    if (dim == 0) og = g + (int)((unsigned int)l % (unsigned int)rx1);
+    else on = n + (int)((unsigned int)j % (unsigned int)rx1);
+    if (og >= Q) og -= Q;
+    if (on >= N) on -= N;
+    int dn = on - j; if (dn < 0) dn += N;
+    int dg = og - l; if (dg < 0) dg += Q;
+    const int o = on * Q + og, d = dn * Q + dg;
+    return in_s ? sendcounts + (size_t)o * P + d : recvcounts + (size_t)d * P + o;
+}
+
+// ------------------------------------------------------------------------------------------
+// k_t_places, k_t_bases: exact-size T for phases that find their blocks themselves: the places of the blocks that every
+// phase stores into T, of all phases at once -- block sizes come from the caller's matrices (block_bytes), so no phase
+// waits for another's size exchange.  k_t_places: one workgroup per receiver and class scans the chunks of the class's
+// blocks in message order; the offsets inside the receiver's part go to tpos by slot index, the part's size to csub.
+// The neighbours of the first phase's message order are r apart in tpos and in the caller's rows: its offsets and sizes
+// are kept by segment too (pairs) when r is 16 or more: uniform [0, 64] B, P = 4096, r = 64 2.17 -> 1.74 ms per call; at
+// r = 4 and 8 they cost 1 %.
+// k_t_bases: one workgroup per class.  Two launches per call in place of four per phase (rotation and size exchange
+// included): P = 256, r = 4, four phases 174 -> 138 us per call, uniform [0, 100] B, P = 1500, r = 4 682 -> 598 us.
+// ------------------------------------------------------------------------------------------
+constexpr int kPlaceMaxPhases = 24;         // P <= 32768 has at most 16
+struct PlacePhase {
+    const int32_t* e;       // the phase's table (SegDev)
+    const int32_t* src;
+    const int32_t* tord;    // its T-bound segments by class (ExactT)
+    const int32_t* tcls;
+    int phase;              // its index in the schedule
+    int first;              // workgroup row of its first class
+    int dim, rx1;
+};
+struct PlaceArgs {
+    PlacePhase ph[kPlaceMaxPhases];
+    int nph;                // the phases that store into T
+    int P, Q, N;
+    const int32_t* sendcounts;
+    const int32_t* recvcounts;
+    ExactT x;
+    uint2* pairs;           // of the first phase (ResolveArgs)
+    int pairs_ld;
+};
+__device__ __forceinline__ int place_phase(const PlaceArgs& a, int row) {
+    int f = 0;
+    while (f + 1 < a.nph && a.ph[f + 1].first <= row) ++f;
+    return f;
+}
+__global__ void __launch_bounds__(kScanThreads) k_t_places(const PlaceArgs a) {
+    __shared__ int wsum[kScanThreads / kWave];
+    const int p = blockIdx.x, P = a.P;
+    const int f = place_phase(a, blockIdx.y);
+    const PlacePhase& ph = a.ph[f];
+    const int32_t* cls = ph.tcls + 3 * (blockIdx.y - ph.first);
+    const int cid = cls[0], c0 = cls[1], cn = cls[2];
+    int pn, pg;
+    split_slot_index(p, a.Q, a.N, pn, pg);
+    int* pos_t = a.x.tpos + ((size_t)ph.phase * P + p) * P;
+    int carry = 0;
+    for (int base = 0; base < cn; base += kScanThreads * kScanItems) {
+        int ct[kScanItems], se[kScanItems], sg[kScanItems], sz[kScanItems];
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) {
+            const int i = base + scan_item_index(k);
+            sg[k] = ph.tord[c0 + min(i, cn - 1)];
+            se[k] = ph.e[sg[k]];
+            int j, l;
+            split_slot_index(se[k], a.Q, a.N, j, l);
+            sz[k] = *block_bytes(a.sendcounts, a.recvcounts, ph.src[sg[k]] < 0, pn, pg, j, l, P, a.Q, a.N, ph.dim, ph.rx1);
+            ct[k] = i < cn ? (sz[k] + 15) >> 4 : 0;
+        }
+        int run[kScanItems];
+        block_scan_batch(ct, run, carry, wsum);
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k)
+            if (base + scan_item_index(k) < cn) {
+                pos_t[se[k]] = run[k];
+                if (ph.phase == 0 && a.pairs) a.pairs[(size_t)p * a.pairs_ld + sg[k]] = make_uint2((unsigned int)run[k], (unsigned int)sz[k]);
+            }
+    }
+    if (threadIdx.x == 0) a.x.csub[(size_t)cid * P + p] = carry;
+}
+__global__ void __launch_bounds__(kScanThreads) k_t_bases(const PlaceArgs a) {
+    __shared__ long long wc[kScanThreads / kWave];
+    const PlacePhase& ph = a.ph[place_phase(a, blockIdx.x)];
+    class_base(a.x, ph.tcls[3 * (blockIdx.x - ph.first)], a.P, wc);
 }
 
 template <int LPB, bool TALL, int STREAM, bool DENSE, bool RESOLVED>
@@ -1227,14 +1325,15 @@ __global__ void __launch_bounds__(256) k_hop_direct(const DirectArgs a) {
                 int dg = qg - l; if (dg < 0) dg += Q;
                 int sn = pn + j; if (sn >= N) sn -= N;
                 int sg = pg + l; if (sg >= Q) sg -= Q;
-                const size_t row = (size_t)p * P, at_s = (size_t)q[u] * P + dn * Q + dg, at_r = row + sn * Q + sg;
-                n[u] = *(a.by_source ? a.by_source + at_r : r.nxt + row + e);
+                const size_t at_s = (size_t)q[u] * P + dn * Q + dg, at_r = (size_t)p * P + sn * Q + sg;
+                const int32_t* pair = reinterpret_cast<const int32_t*>(r.pairs + (size_t)p * r.pairs_ld + s);
+                n[u] = *(in_r ? r.recvcounts + at_r : r.pairs ? pair + 1 : block_bytes(r.sendcounts, r.recvcounts, in_s, pn, pg, j, l, P, Q, N, r.dim, r.rx1));
                 const int64_t* tbase = reinterpret_cast<const int64_t*>(r.x.tbase);
                 va[u] = *(in_s ? r.sdispls + at_s : (DENSE ? tbase + (size_t)scl * P + q[u] : r.sdispls));
                 vc[u] = *(in_r ? r.rdispls + at_r : (DENSE ? tbase + (size_t)dcl * P + p : r.rdispls));
                 if (DENSE) {
                     vb[u] = *(in_s ? r.seg.e : r.x.tpos + ((size_t)sph * P + q[u]) * P + e);
-                    vd[u] = *(in_r ? r.seg.e : r.x.tpre + (size_t)p * r.x.ld + s);
+                    vd[u] = *(in_r ? r.seg.e : r.pairs ? pair : r.x.tpos + ((size_t)r.x.phase * P + p) * P + e);
                 }
             }
 #pragma unroll
@@ -1381,8 +1480,9 @@ __device__ __forceinline__ void find_block(const DirectArgs& a, int p, int s, un
         int dg = qg - l; if (dg < 0) dg += Q;
         int sn = pn + j; if (sn >= N) sn -= N;
         int sg = pg + l; if (sg >= Q) sg -= Q;
-        const size_t row = (size_t)p * P, at_s = (size_t)q * P + dn * Q + dg, at_r = row + sn * Q + sg;
-        n = *(a.by_source ? a.by_source + at_r : r.nxt + row + e);
+        const size_t at_s = (size_t)q * P + dn * Q + dg, at_r = (size_t)p * P + sn * Q + sg;
+        const int32_t* pair = reinterpret_cast<const int32_t*>(r.pairs + (size_t)p * r.pairs_ld + s);
+        n = *(final ? r.recvcounts + at_r : r.pairs ? pair + 1 : block_bytes(r.sendcounts, r.recvcounts, in_s, pn, pg, j, l, P, Q, N, r.dim, r.rx1));
         exact = n;
         if (!final) n = (n + 15) & ~15;
         if (DENSE) {
@@ -1390,7 +1490,7 @@ __device__ __forceinline__ void find_block(const DirectArgs& a, int p, int s, un
             const long long va = *(in_s ? r.sdispls + at_s : tbase + (size_t)scl * P + q);
             const long long vc = *(final ? r.rdispls + at_r : tbase + (size_t)dcl * P + p);
             const int vb = *(in_s ? r.seg.e : r.x.tpos + ((size_t)sph * P + q) * P + e);
-            const int vd = *(final ? r.seg.e : r.x.tpre + (size_t)p * r.x.ld + s);
+            const int vd = *(final ? r.seg.e : r.pairs ? pair : r.x.tpos + ((size_t)r.x.phase * P + p) * P + e);
             src = in_s ? (unsigned long long)r.S + va : tb + ((unsigned long long)(va + vb) << 4);
             dst = final ? (unsigned long long)r.R + vc : tb + ((unsigned long long)(vc + vd) << 4);
         } else {
