@@ -7,6 +7,7 @@
 #include <algorithm>
 #include <chrono>
 #include <cmath>
+#include <cstddef>
 #include <cstdio>
 #include <cstring>
 #include <map>
@@ -80,6 +81,8 @@ struct StatusBufs {
     Status* h_status = nullptr;              // host mirror (pinned for the library's own)
     Status* h_status_dev = nullptr;          // the device's address of the pinned mirror (nullptr: not mapped)
     unsigned long long* d_vpart = nullptr;   // partial results of the validation pass, one row per workgroup
+    unsigned long long* h_part = nullptr;      // the partial results in pinned memory, where few workgroups write them for
+    unsigned long long* h_part_dev = nullptr;  // the host to fold (nullptr: none, k_validate_finish folds them)
     int num_cus = 256;
 };
 
@@ -181,6 +184,11 @@ int ensure_ctx(Ctx& c) {
         c.sb.h_status_dev = nullptr;
     }
     HIPCHK(hipMalloc((void**)&c.sb.d_vpart, align_up(vpart_words(c.sb.num_cus) * 8)));
+    HIPCHK(hipHostMalloc((void**)&c.sb.h_part, (size_t)kValFoldRows * (kValPartial + kValFoldClasses) * 8, hipHostMallocDefault));
+    if (hipHostGetDevicePointer((void**)&c.sb.h_part_dev, c.sb.h_part, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        c.sb.h_part_dev = nullptr;
+    }
     HIPCHK(hipEventCreate(&c.ev_end));
     std::memset(&c.stats, 0, sizeof(c.stats));
     c.ready = true;
@@ -191,6 +199,7 @@ void free_ctx(Ctx& c) {
     if (c.sb.d_status) (void)hipFree(c.sb.d_status);
     if (c.sb.h_status) (void)hipHostFree(c.sb.h_status);
     if (c.sb.d_vpart) (void)hipFree(c.sb.d_vpart);
+    if (c.sb.h_part) (void)hipHostFree(c.sb.h_part);
     if (c.meta) (void)hipFree(c.meta);
     if (c.data) (void)hipFree(c.data);
     if (c.tiny_t) (void)hipFree(c.tiny_t);
@@ -502,20 +511,40 @@ int run_validate(const StatusBufs& sb, const int32_t* sendcounts, const int32_t*
     // with a schedule that has T: also the size of every class of exact-size T (summed into the status block)
     const int nph = exact_t_for ? (int)exact_t_for->host.phases.size() : 0;
     const int ncls = class_count(nph);
-    if (ncls > 0) {
+    // Few workgroups: their rows go straight to pinned memory and the host adds them up.  More rows would take longer to
+    // cross the bus and to add up than the two kernels and the copy they save (about 20 us).
+    const bool fold = sb.h_part_dev && vgrid <= (unsigned)kValFoldRows && ncls <= kValFoldClasses;
+    if (ncls > 0 && !fold) {
         hipLaunchKernelGGL(k_zero64, dim3((unsigned)((ncls + 255) / 256)), dim3(256), 0, s, sb.d_status->cls_chunks, ncls);
         HIPCHK(hipGetLastError());
     }
-    hipLaunchKernelGGL(k_validate, dim3(vgrid), dim3(kValTile, 4), (size_t)ncls * 8, s, sendcounts, recvcounts, sdispls,
-                       rdispls, P, sb.d_vpart, exact_t_for ? exact_t_for->d_hm1 : nullptr,
+    const unsigned ny = t * t < (size_t)sb.num_cus * 2 ? 16 : 4;
+    const int copies = ncls <= 160 ? kValCopies : 1;         // 40 KiB of LDS; no schedule has more than 136
+    hipLaunchKernelGGL(k_validate, dim3(vgrid), dim3(kValTile, ny), (size_t)ncls * copies * 8, s, sendcounts, recvcounts, sdispls,
+                       rdispls, P, fold ? sb.h_part_dev : sb.d_vpart, exact_t_for ? exact_t_for->d_hm1 : nullptr,
                        exact_t_for ? exact_t_for->host.Q : 1, exact_t_for ? exact_t_for->host.N : 1,
-                       exact_t_for ? exact_t_for->d_mask : nullptr, nph, sb.d_status->cls_chunks);
+                       exact_t_for ? exact_t_for->d_mask : nullptr, nph, sb.d_status, fold ? 1 : 0, copies);
     HIPCHK(hipGetLastError());
+    if (fold) {
+        HIPCHK(hipStreamSynchronize(s));
+        Status& h = *sb.h_status;
+        unsigned long long fa = 0, m = 0;
+        h.total_bytes = h.total_chunks = h.send_extent = h.t_chunks = h.short_blocks = 0;
+        for (int i = 0; i < ncls; ++i) h.cls_chunks[i] = 0;
+        for (unsigned r = 0; r < vgrid; ++r) {
+            const unsigned long long* o = sb.h_part + (size_t)r * (kValPartial + kValFoldClasses);
+            fa |= o[0]; m = std::max(m, o[1]);
+            h.total_bytes += o[2]; h.total_chunks += o[3]; h.send_extent = std::max(h.send_extent, o[4]);
+            h.t_chunks += o[5]; h.short_blocks += o[6];
+            for (int i = 0; i < ncls; ++i) h.cls_chunks[i] += o[kValPartial + i];
+        }
+        h.flags = (unsigned int)(fa >> 32); h.align_bits = (unsigned int)(fa & 127u); h.max_count = (int)m;
+        return TUNA_OK;
+    }
     hipLaunchKernelGGL(k_validate_finish, dim3(1), dim3(256), 0, s, sb.d_vpart, (int)vgrid, sb.d_status);
     HIPCHK(hipGetLastError());
-    HIPCHK(hipMemcpyAsync(sb.h_status, sb.d_status, 64, hipMemcpyDeviceToHost, s));
-    if (ncls > 0)
-        HIPCHK(hipMemcpyAsync(sb.h_status->cls_chunks, sb.d_status->cls_chunks, (size_t)ncls * 8, hipMemcpyDeviceToHost, s));
+    // the head and the class sums behind it in one copy
+    HIPCHK(hipMemcpyAsync(sb.h_status, sb.d_status, offsetof(Status, cls_chunks) + (size_t)ncls * 8, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     return TUNA_OK;
 }
@@ -1259,6 +1288,9 @@ int launch_t_places(Prepared& pr, hipStream_t s) {
     PlaceArgs a{};
     a.P = pr.P; a.Q = pr.Q; a.N = pr.N; a.sendcounts = pr.sendcounts; a.recvcounts = pr.recvcounts; a.x = exact_t_of(pr, 0);
     a.pairs = pr.pairs; a.pairs_ld = pr.hop.ld;
+    a.by_value = pr.cbase.size() <= kPlaceClasses ? 1 : 0;
+    if (a.by_value) std::copy(pr.cbase.begin(), pr.cbase.end(), a.cbase);
+    else if (const int rc = upload_cbase(pr, s)) return rc;
     int rows = 0;
     for (size_t i = 0; i < pl.phases.size(); ++i) {
         const int ncls = (int)(pr.dp->tcls[i].size() / 3);
@@ -1303,7 +1335,8 @@ int run_one_pass(Prepared& pr, void* mbase, size_t mbytes, void* dbase, hipStrea
     pr.stage_r = cd.take<v4u>(pr.fused ? 0 : ds.stage_chunks);
     pr.T = cd.take<unsigned char>(ds.t_bytes + kTailSlack);
     if (!cm.ok || !cd.ok) return TUNA_ERR_WORKSPACE_TOO_SMALL;
-    int rc = upload_cbase(pr, s);
+    const bool direct = runs_direct(pr);
+    int rc = direct ? TUNA_OK : upload_cbase(pr, s);         // launch_t_places passes them on
     if (rc != TUNA_OK) return rc;
     st.temp_bytes = (int64_t)ds.t_bytes;
     st.staging_bytes = pr.fused ? 0 : (int64_t)(2 * ds.stage_chunks * 16);
@@ -1311,7 +1344,6 @@ int run_one_pass(Prepared& pr, void* mbase, size_t mbytes, void* dbase, hipStrea
 
     // ---- initial rotation (index only) and the own block ----------------------------------------
     const dim3 grot((unsigned)((P + 255) / 256), (unsigned)((P + kExchangeRanks - 1) / kExchangeRanks));
-    const bool direct = runs_direct(pr);
     // A schedule of one phase whose block sizes nobody asked to see: every block arrives in its only hop, so what
     // the phase's metadata exchange would leave in the receivers' size arrays is recvcounts, rotated (validation
     // has checked that it is the transpose of sendcounts): one kernel instead of the rotation and the exchange.

@@ -36,8 +36,8 @@ constexpr int kFlagSrcT = 32;    // source is a T slot: reading past the block's
 
 constexpr int kMaxClasses = 64 * 63 / 2;     // class_count(TUNA_MAX_PHASES)
 
-// Device-side status block: the validation pass writes the head, every phase its own entries of the
-// three arrays; the head is read back once after validation.
+// Device-side status block: the validation pass writes the head and the class sums, every phase its own entries of the
+// other arrays; head and class sums are read back after validation, in one copy.
 struct Status {
     unsigned int flags;            // bit 0: negative count, bit 1: recvcounts != transpose(sendcounts), (bit 3: receive regions not dense)
                                    // bit 2: negative displacement of a non-empty block
@@ -49,12 +49,12 @@ struct Status {
     unsigned long long send_extent;    // max over non-empty blocks of sdispls + count: bytes of sendbuf that hold blocks
     unsigned long long t_chunks;       // exact-size T: chunks stored into T over all phases
     unsigned long long short_blocks;   // blocks of fewer than kShortBlockBytes bytes, empty ones included
+    unsigned long long cls_chunks[kMaxClasses];   // exact-size T: chunks of every class (f, y), summed by the validation pass
     unsigned long long phase_bytes[64];   // payload bytes moved per phase
     unsigned long long phase_chunks[64];  // staged chunks per phase
     unsigned int phase_units[64][2];      // wave units per phase: [0] receive-side layout, [1] send-side layout
     unsigned int self_units;              // wave units of the ranks' own blocks when the copy engine moves them
     unsigned int reserved2;
-    unsigned long long cls_chunks[kMaxClasses];   // exact-size T: chunks of every class (f, y), summed by the validation pass
 };
 
 // The per-phase table of moving blocks on the device, one array per field (message order).
@@ -218,24 +218,33 @@ __global__ void __launch_bounds__(256) k_build_hops(const PlanScalars pl, int32_
 // ceil(count / 16) * hm1[slot index of the block] chunks over all blocks.
 // A non-empty block with a negative displacement is flagged too.  Workgroups of (64, 4) threads
 // stride over the tiles and write one row of partial results each.
+// Bound by its reads (24 bytes per pair) at P = 4096 and by the chain of loads per tile below P = 1024: there workgroups
+// have 16 waves, so that a tile is one step of four rows per thread for either matrix instead of four steps (P = 256:
+// 19 -> 14 us, P = 1024 23 -> 19 us).  The class sums are LDS atomics on one of kValCopies copies per lane: neighbouring blocks mostly belong
+// to one class, and on one copy a wave's additions queued up behind each other (P = 4096, r = 8: 159 -> 124 us).
+// With `cls_rows` (few workgroups) the partial rows, class sums included, lie in pinned host memory and the host adds
+// them up: no kernel to clear the sums, none to fold the rows, no copy of the result (see run_validate; P = 256, r = 4
+// 138 -> 117 us per call with the above).
 // ------------------------------------------------------------------------------------------
 constexpr int kValTile = 64;
 constexpr int kValPartial = 8;              // 64-bit words per workgroup in the partial-result array
+constexpr int kValCopies = 32;
+constexpr int kValFoldRows = 64, kValFoldClasses = 24;      // most workgroups and classes that the host folds
 constexpr int kShortBlockBytes = 256;       // below this a block is mostly edges to the destination-tiled hop
-__global__ void __launch_bounds__(256) k_validate(const int32_t* __restrict__ sendcounts,
-                                                  const int32_t* __restrict__ recvcounts,
-                                                  const int64_t* __restrict__ sdispls,
-                                                  const int64_t* __restrict__ rdispls,
-                                                  int P, unsigned long long* __restrict__ partial,
-                                                  const int32_t* __restrict__ hm1, int Q, int N,
-                                                  const unsigned long long* __restrict__ mask, int nph,
-                                                  unsigned long long* __restrict__ cls_chunks) {
+__global__ void __launch_bounds__(1024) k_validate(const int32_t* __restrict__ sendcounts,
+                                                   const int32_t* __restrict__ recvcounts,
+                                                   const int64_t* __restrict__ sdispls,
+                                                   const int64_t* __restrict__ rdispls,
+                                                   int P, unsigned long long* __restrict__ partial,
+                                                   const int32_t* __restrict__ hm1, int Q, int N,
+                                                   const unsigned long long* __restrict__ mask, int nph,
+                                                   Status* __restrict__ st, int cls_rows, int copies) {
     __shared__ int tile[kValTile][kValTile + 1];
-    __shared__ unsigned long long red[4][7];
-    extern __shared__ unsigned long long lcls[];          // class_count(nph) sums of this workgroup (with `mask`)
-    const int tx = threadIdx.x, ty = threadIdx.y;
+    __shared__ unsigned long long red[16][7];
+    extern __shared__ unsigned long long lcls[];          // class_count(nph) sums of this workgroup, `copies` of each (with `mask`)
+    const int tx = threadIdx.x, ty = threadIdx.y, ny = blockDim.y;
     const int ncls = mask ? class_count(nph) : 0;
-    for (int i = ty * kValTile + tx; i < ncls; i += 4 * kValTile) lcls[i] = 0;
+    for (int i = ty * kValTile + tx; i < ncls * copies; i += ny * kValTile) lcls[i] = 0;
     __syncthreads();
     const int tpr = (P + kValTile - 1) / kValTile;       // tiles per row
     const int ntile = tpr * tpr;
@@ -248,13 +257,13 @@ __global__ void __launch_bounds__(256) k_validate(const int32_t* __restrict__ se
         const int jn = hm1 ? j / Q : 0, jg = hm1 ? j - jn * Q : 0;   // the destination's node and local id
         // four rows per step, their loads issued together from clamped indices: with one row per step the pass
         // was a chain of 32 dependent memory round trips per tile (48 us for 1024 ranks)
-        for (int a0 = ty; a0 < kValTile; a0 += 16) {
+        for (int a0 = ty; a0 < kValTile; a0 += 4 * ny) {
             int cv[4];
             long long dv[4];
             bool ok[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const int i = bi + a0 + 4 * u;
+                const int i = bi + a0 + ny * u;
                 ok[u] = i < P && j < P;
                 const size_t idx = ok[u] ? (size_t)i * P + j : 0;
                 cv[u] = sendcounts[idx];
@@ -262,7 +271,7 @@ __global__ void __launch_bounds__(256) k_validate(const int32_t* __restrict__ se
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const int a = a0 + 4 * u;
+                const int a = a0 + ny * u;
                 const int i = bi + a;
                 int c = 0;
                 if (ok[u]) {
@@ -295,7 +304,7 @@ __global__ void __launch_bounds__(256) k_validate(const int32_t* __restrict__ se
                             while (m) {
                                 const int y = __ffsll((long long)m) - 1;
                                 m &= m - 1;
-                                atomicAdd(&lcls[class_id(f, y, nph)], ch);
+                                atomicAdd(&lcls[class_id(f, y, nph) * copies + (tx & (copies - 1))], ch);
                                 f = y;
                             }
                         }
@@ -306,13 +315,13 @@ __global__ void __launch_bounds__(256) k_validate(const int32_t* __restrict__ se
         }
         __syncthreads();
         if (recvcounts) {
-            for (int a0 = ty; a0 < kValTile; a0 += 16) {
+            for (int a0 = ty; a0 < kValTile; a0 += 4 * ny) {
                 int rv[4];
                 long long dv[4], dx[4];
                 bool in[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    const int jr = bj + a0 + 4 * u, i = bi + tx;     // recvcounts[jr][i] must equal sendcounts[i][jr]
+                    const int jr = bj + a0 + ny * u, i = bi + tx;     // recvcounts[jr][i] must equal sendcounts[i][jr]
                     in[u] = i < P && jr < P;
                     const size_t idx = in[u] ? (size_t)jr * P + i : 0;
                     rv[u] = recvcounts[idx];
@@ -322,7 +331,7 @@ __global__ void __launch_bounds__(256) k_validate(const int32_t* __restrict__ se
                 }
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    const int a = a0 + 4 * u;
+                    const int a = a0 + ny * u;
                     const int i = bi + tx;
                     int rc = 0;
                     long long d = 0;
@@ -367,20 +376,26 @@ __global__ void __launch_bounds__(256) k_validate(const int32_t* __restrict__ se
         r[1] = (unsigned long long)mx; r[2] = bytes; r[3] = chunks; r[4] = extent; r[5] = tchunks; r[6] = shortb;
     }
     __syncthreads();
+    unsigned long long* o = partial + (size_t)blockIdx.x * (cls_rows ? kValPartial + kValFoldClasses : kValPartial);
     if (tx == 0 && ty == 0) {
         unsigned long long fa = 0, m = 0, by = 0, ch = 0, ex = 0, tc = 0, sb = 0;
-        for (int w = 0; w < 4; ++w) {
+        for (int w = 0; w < ny; ++w) {
             fa |= red[w][0]; m = max(m, red[w][1]); by += red[w][2]; ch += red[w][3]; ex = max(ex, red[w][4]);
             tc += red[w][5]; sb += red[w][6];
         }
-        // one row of partial results per workgroup, folded by k_validate_finish: thousands of atomics
+        // one row of partial results per workgroup, folded by k_validate_finish or the host: thousands of atomics
         // on the same few addresses would take longer than reading the matrices
-        unsigned long long* o = partial + (size_t)blockIdx.x * kValPartial;
         o[0] = fa; o[1] = m; o[2] = by; o[3] = ch; o[4] = ex; o[5] = tc; o[6] = sb;
     }
-    // the class sums: one atomic per class and workgroup that holds any of it (cls_chunks starts at zero)
-    for (int i = ty * kValTile + tx; i < ncls; i += 4 * kValTile)
-        if (lcls[i]) atomicAdd(&cls_chunks[i], lcls[i]);
+    // the class sums: in the row, or one atomic per class and workgroup that holds any of it (cls_chunks starts at zero)
+    for (int i = ty * kValTile + tx; i < ncls; i += ny * kValTile) {
+        unsigned long long v = 0;
+        for (int k = 0; k < copies; ++k) v += lcls[i * copies + ((i + k) & (copies - 1))];
+        if (cls_rows) o[kValPartial + i] = v;
+        else if (v) atomicAdd(&st->cls_chunks[i], v);
+    }
+    // the totals that k_phase_sums adds to (without cls_rows k_validate_finish clears them)
+    if (cls_rows && blockIdx.x == 0 && ty == 0) st->phase_bytes[tx] = st->phase_chunks[tx] = 0;
 }
 
 // k_zero64: n 64-bit words to zero (the class sums before a validation pass).
@@ -798,7 +813,7 @@ __global__ void __launch_bounds__(kScanThreads) k_phase_layout(const PhaseLayout
 
 // A class of exact-size T: rank p's part starts at the class's first chunk plus the parts of the ranks before it, each
 // rounded up to a 128-byte line.  One workgroup of kScanThreads.
-__device__ __forceinline__ void class_base(const ExactT& x, int cid, int P, long long* wc) {
+__device__ __forceinline__ void class_base(const ExactT& x, int cid, long long first, int P, long long* wc) {
     const int* sub = x.csub + (size_t)cid * P;
     long long* base = x.tbase + (size_t)cid * P;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
@@ -818,7 +833,7 @@ __device__ __forceinline__ void class_base(const ExactT& x, int cid, int P, long
 #pragma unroll
     for (int k = 0; k < kScanThreads / kWave; ++k)
         if (k < wv) oc += wc[k];
-    long long run = x.cbase[cid] + oc + ic - sc;
+    long long run = first + oc + ic - sc;
     for (int p = p0; p < p1; ++p) {
         base[p] = run;
         run += (sub[p] + kRankAlignChunks - 1) / kRankAlignChunks * kRankAlignChunks;
@@ -848,7 +863,8 @@ __global__ void __launch_bounds__(kScanThreads) k_layout_base(int P, LayoutDev L
                         phase_units + which);             // layout 0 is the receive side, 1 the send side
         return;
     }
-    class_base(x, x.tcls[3 * (which - n_layouts)], P, wc);
+    const int cid = x.tcls[3 * (which - n_layouts)];
+    class_base(x, cid, x.cbase[cid], P, wc);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1201,6 +1217,7 @@ __device__ __forceinline__ const int32_t* block_bytes(const int32_t* sendcounts,
 // k_t_bases: one workgroup per class.  Two launches per call in place of four per phase (rotation and size exchange
 // included): P = 256, r = 4, four phases 174 -> 138 us per call, uniform [0, 100] B, P = 1500, r = 4 682 -> 598 us.
 // ------------------------------------------------------------------------------------------
+constexpr int kPlaceClasses = 28;           // 8 phases
 constexpr int kPlaceMaxPhases = 24;         // P <= 32768 has at most 16
 struct PlacePhase {
     const int32_t* e;       // the phase's table (SegDev)
@@ -1220,6 +1237,8 @@ struct PlaceArgs {
     ExactT x;
     uint2* pairs;           // of the first phase (ResolveArgs)
     int pairs_ld;
+    int by_value;           // the classes' first chunks are here, not in x.cbase: no copy to the device before the kernels
+    long long cbase[kPlaceClasses];
 };
 __device__ __forceinline__ int place_phase(const PlaceArgs& a, int row) {
     int f = 0;
@@ -1263,7 +1282,8 @@ __global__ void __launch_bounds__(kScanThreads) k_t_places(const PlaceArgs a) {
 __global__ void __launch_bounds__(kScanThreads) k_t_bases(const PlaceArgs a) {
     __shared__ long long wc[kScanThreads / kWave];
     const PlacePhase& ph = a.ph[place_phase(a, blockIdx.x)];
-    class_base(a.x, ph.tcls[3 * (blockIdx.x - ph.first)], a.P, wc);
+    const int cid = ph.tcls[3 * (blockIdx.x - ph.first)];
+    class_base(a.x, cid, a.by_value ? a.cbase[cid] : a.x.cbase[cid], a.P, wc);
 }
 
 template <int LPB, bool TALL, int STREAM, bool DENSE, bool RESOLVED>
