@@ -131,7 +131,8 @@ typedef struct tuna_plan_info {
  *                   with local radix min(radix, Q) and global radix min(radix, N), N = P / Q.
  * The call validates the counts on the device, reads a few integers back (one stream
  * synchronisation), sizes or grows the workspace, then enqueues all phases on `stream` and
- * returns without waiting for them.  Payloads of 64 MiB and more with at least two digit phases:
+ * returns without waiting for them.  Payloads of 64 MiB and more with at least two digit phases and
+ * blocks of more than 64 KiB (or more than 4 KiB on average, where the destination-tiled hop runs):
  * with one-kernel hops (the default) the block-size exchanges and scans of all phases run on a
  * second stream owned by the context while `stream` moves the payload, each phase's payload kernel
  * behind an event of its metadata; work enqueued on `stream` after the call is ordered behind all
@@ -139,10 +140,10 @@ typedef struct tuna_plan_info {
  * passes instead -- the metadata of every phase first, a second read-back of the phases' exact
  * work-list lengths, then the payload kernels -- which costs one more synchronisation and saves
  * launching every copy kernel for an upper bound of work.
- * Problems of at most 64 ranks, 1 MiB of payload and 8 digit phases are done by one kernel launch
- * (validation, all phases and the own blocks in one workgroup; options at their defaults, no
- * profiling): there the launches, not the bytes, are what a call costs.  It returns after that
- * kernel has finished.
+ * Problems of at most 64 ranks, 1 MiB of payload, 8 digit phases and 1200 blocks moved (200 more per
+ * phase; all ranks and phases together) are done by one kernel launch (validation, all phases and the
+ * own blocks in one workgroup; options at their defaults, no profiling): there the launches, not the
+ * bytes, are what a call costs.  It returns after that kernel has finished.
  */
 int tuna_alltoallv(const void* sendbuf, const int32_t* sendcounts, const int64_t* sdispls,
                    void* recvbuf, const int32_t* recvcounts, const int64_t* rdispls,

@@ -1407,16 +1407,17 @@ int run_once(Ctx& c, const Options& opt, const void* sendbuf, const int32_t* sen
              void* recvbuf, const int32_t* recvcounts, const int64_t* rdispls, int P, int ranks_per_node, int rl, int rg,
              void* stream);
 
-// A whole call in one kernel launch (k_tiny_call) for problems of at most 64 ranks and 1 MiB of payload,
+// A whole call in one kernel launch (k_tiny_call) for problems of at most 64 ranks, few blocks and 1 MiB of payload,
 // where a call costs what its launches cost: about thirty launches and a synchronisation become one
 // launch and a synchronisation.  Only when everything was left to the library (mode, no batches, no
 // staggering, no profiling).  *done = false: the kernel declined (invalid counts, or not that small) and
 // nothing has moved; the caller goes on with the general path.
 constexpr size_t kTinyTBytes = 4u << 20;
+constexpr long long kTinyMaxMoving = 1200, kTinyMovingPerPhase = 200;       // blocks moved, over all ranks and phases
 int run_tiny(Ctx& c, const void* sendbuf, const int32_t* sendcounts, const int64_t* sdispls, void* recvbuf,
              const int32_t* recvcounts, const int64_t* rdispls, int P, int ranks_per_node, int rl, int rg,
-             hipStream_t s, bool* done) {
-    *done = false;
+             hipStream_t s, bool* done, bool* asked) {
+    *done = *asked = false;
     int Q = 0;
     if (resolve_hierarchy(P, ranks_per_node, &Q) != TUNA_OK || rl < 2 || rg < 2) return TUNA_OK;   // the general path reports it
     if (!sendbuf || !recvbuf || !sendcounts || !recvcounts || !sdispls || !rdispls) return TUNA_OK;
@@ -1427,6 +1428,13 @@ int run_tiny(Ctx& c, const void* sendbuf, const int32_t* sendcounts, const int64
     if (rc != TUNA_OK) return rc;
     const PlanHost& pl = dp->host;
     if ((int)pl.phases.size() > kTinyMaxPhases) return TUNA_OK;
+    // One workgroup moves 128 blocks at a time, about 20 ns a block; the general path costs a launch or two per phase but
+    // has the whole device.  Per call, one launch against the general path: 16 ranks r = 2 34 / 60 us, linear 16 26 / 46,
+    // 24 33 / 46, 32 42 / 46, 48 66 / 46, 64 118 / 49; r = 2 24 ranks 49 / 64, 32 ranks 73 / 66, 64 ranks 277 / 93.
+    long long moving = 0;
+    for (const auto& ph : pl.phases) moving += (long long)ph.nseg * P;
+    if (moving > kTinyMaxMoving + kTinyMovingPerPhase * (long long)pl.phases.size()) return TUNA_OK;
+    *asked = true;
     if (!c.tiny_t) {
         const hipError_t e = hipMalloc((void**)&c.tiny_t, kTinyTBytes);
         if (e != hipSuccess) { (void)hipGetLastError(); c.tiny_t = nullptr; return TUNA_OK; }
@@ -1438,7 +1446,8 @@ int run_tiny(Ctx& c, const void* sendbuf, const int32_t* sendcounts, const int64
     a.P = P; a.Q = Q; a.N = P / Q; a.nph = (int)pl.phases.size();
     for (int i = 0; i < a.nph; ++i) {
         const SegDev& sd = dp->d_seg[i];
-        a.ph[i] = TinyPhase{sd.e, sd.z, sd.src, sd.dst, pl.phases[i].nseg, pl.phases[i].dim, (int)pl.phases[i].rx};
+        a.ph[i] = TinyPhase{sd.e, sd.z, sd.src, sd.dst, pl.phases[i].nseg, pl.phases[i].dim, (int)pl.phases[i].rx,
+                            (int)(pl.phases[i].rx * pl.phases[i].r)};
     }
     // the kernel writes its 64 bytes of status straight into the pinned host mirror: a copy command after it
     // would cost a fifth of the whole call
@@ -1483,11 +1492,11 @@ int run(Ctx& c, const Options& opt, const void* sendbuf, const int32_t* sendcoun
         void* stream) {
     if (P <= kTinyMaxRanks && opt.mode == TUNA_MODE_AUTO && opt.t_layout == TUNA_T_AUTO && !opt.staggered &&
         !opt.block_count && !opt.profile && !c.user_ws && c.tiny_declined != (const void*)sendcounts) {
-        bool done = false;
+        bool done = false, asked = false;
         const int trc = run_tiny(c, sendbuf, sendcounts, sdispls, recvbuf, recvcounts, rdispls, P, ranks_per_node, rl, rg,
-                                 (hipStream_t)stream, &done);
+                                 (hipStream_t)stream, &done, &asked);
         if (trc != TUNA_OK || done) return trc;
-        c.tiny_declined = sendcounts;
+        if (asked) c.tiny_declined = sendcounts;
     }
     int rc = run_once(c, opt, sendbuf, sendcounts, sdispls, recvbuf, recvcounts, rdispls, P, ranks_per_node, rl, rg, stream);
     if (rc == TUNA_ERR_NOMEM && opt.t_layout == TUNA_T_AUTO && c.stats.dense_t) {

@@ -2266,13 +2266,17 @@ __global__ void __launch_bounds__(kCopyThreads) k_copy_tiled(const TiledCopyArgs
 // schedule), so no slot is read and written in one phase.  Sixteen lanes move one block at a time;
 // workgroup barriers separate the phases.
 // What a phase needs besides the payload is read from global memory once, at the start, all loads in
-// flight together, and kept in LDS: both size matrices, the low 32 bits of both displacement
-// matrices and the tables of every phase.  A phase then costs one round trip to memory -- the
+// flight together, and kept in LDS: the rotated sizes, the low 32 bits of both displacement
+// matrices and the tables of every phase.  A block's size is looked up where the rotation left it (no
+// exchange between the phases).  A phase then costs one round trip to memory -- the
 // payload's -- instead of four dependent ones (tables, sizes, displacements, payload).
 // The kernel declines -- writes tiny_done = 0 and moves nothing -- when the counts are invalid, when
 // the problem is not tiny after all (payload above kTinyMaxPayload, T above its capacity) or when a
 // displacement of a non-empty block does not fit into 32 bits; the host then takes the general path,
 // which reports the error or does the work.
+// Bound by latency: one workgroup, and per phase a round trip of the payload and a barrier behind its stores.  Without the
+// exchange and with 16 bytes per lane in place of 4 or 1: 16 ranks, r = 2 38 -> 34 us per call, 24 ranks byte-granular
+// 163 -> 61 us, 64 ranks linear byte-granular 250 -> 118 us.
 // Dynamic LDS: tiny_lds_bytes(P, total table entries).
 // ------------------------------------------------------------------------------------------
 constexpr int kTinyMaxRanks = 64;
@@ -2284,7 +2288,7 @@ struct TinyPhase {
     const int32_t* z;
     const int32_t* src;
     const int32_t* dst;
-    int nseg, dim, rx;
+    int nseg, dim, rx, rx1;
 };
 struct TinyArgs {
     const unsigned char* S;
@@ -2302,9 +2306,9 @@ struct TinyArgs {
                                     // them after the stream's synchronisation without a copy of its own
 };
 
-// four P x P arrays of 4 bytes (two size matrices, two displacement matrices) and four ints per table entry
+// three P x P arrays of 4 bytes (the sizes and two displacement matrices) and four ints per table entry
 inline size_t tiny_lds_bytes(int P, int table_entries) {
-    return ((size_t)4 * P * P + (size_t)4 * table_entries) * 4;
+    return ((size_t)3 * P * P + (size_t)4 * table_entries) * 4;
 }
 
 // one wave copies `n` bytes; dword granular when everything is 4-byte aligned, else byte by byte
@@ -2324,8 +2328,7 @@ __global__ void __launch_bounds__(kTinyThreads) k_tiny_call(const TinyArgs a) {
     __shared__ int verdict;
     const int P = a.P, Q = a.Q, N = a.N, P2 = P * P;
     int* cur = tiny_lds;                                            // [P][P] sizes by slot index (the rotation's result)
-    int* nxt = cur + P2;
-    unsigned int* sd32 = reinterpret_cast<unsigned int*>(nxt + P2); // [P][P] sdispls, low 32 bits
+    unsigned int* sd32 = reinterpret_cast<unsigned int*>(cur + P2); // [P][P] sdispls, low 32 bits
     unsigned int* rd32 = sd32 + P2;                                 // [P][P] rdispls, low 32 bits
     int* tab = reinterpret_cast<int*>(rd32 + P2);                   // per phase: e[nseg], z[nseg], src[nseg], dst[nseg]
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
@@ -2412,27 +2415,15 @@ __global__ void __launch_bounds__(kTinyThreads) k_tiny_call(const TinyArgs a) {
         if (n > 0) tiny_copy(a.R + rd32[p * P + p], a.S + sd32[p * P + p], n, lane);
     }
     // ---- digit phases ----------------------------------------------------------------------------------------
-    int* c0 = cur;
-    int* c1 = nxt;
     int off = 0;
+    const unsigned long long dummy = (unsigned long long)a.T;       // any 16 bytes that can be read
     for (int x = 0; x < a.nph; ++x) {
-        const int nseg = a.ph[x].nseg, dim = a.ph[x].dim, rx = a.ph[x].rx;
+        const int nseg = a.ph[x].nseg, dim = a.ph[x].dim, rx = a.ph[x].rx, rx1 = a.ph[x].rx1;
         const int* te = tab + off;
         const int* tz = te + nseg;
         const int* ts = tz + nseg;
         const int* td = ts + nseg;
         off += 4 * nseg;
-        // metadata exchange: sizes that do not move are carried over, the others arrive from the sender
-        for (int k = tid; k < P2; k += kTinyThreads) c1[k] = c0[k];
-        __syncthreads();
-        for (int k = tid; k < P * nseg; k += kTinyThreads) {
-            const int q = k / nseg, s = k - q * nseg;
-            const int e = te[s];
-            const int qn = q / Q, qg = q - qn * Q;
-            const int sender = partner_up(qn, qg, Q, N, dim, tz[s] * rx);
-            c1[q * P + e] = c0[sender * P + e];
-        }
-        __syncthreads();
         // the hops.  Sixteen lanes move one block; the 64 groups of the workgroup take the blocks 64 apart, two
         // per step, so that the whole workgroup has loads in flight at once (with one thread per block and the
         // copies done wave by wave, a phase of 128 blocks kept two waves busy and fourteen idle).  Every lane of
@@ -2443,14 +2434,23 @@ __global__ void __launch_bounds__(kTinyThreads) k_tiny_call(const TinyArgs a) {
             if (k >= nb) return 0;
             const int q = k / nseg, s = k - q * nseg;
             const int e = te[s];
-            const int size = c1[q * P + e];
+            int qn, qg, j, l;
+            split_slot_index(q, Q, N, qn, qg);
+            split_slot_index(e, Q, N, j, l);
+            // the block's size: in the rotated sizes of the rank it comes from, the digits up to this phase's away (see
+            // block_bytes); no exchange from phase to phase
+            int on0 = qn, og0 = qg + l;
+            if (dim == 0) og0 = qg + l % rx1;
+            else on0 = qn + j % rx1;
+            if (og0 >= Q) og0 -= Q;
+            if (on0 >= N) on0 -= N;
+            const int size = cur[(on0 * Q + og0) * P + e];
             if (size <= 0) return 0;
-            const int qn = q / Q, qg = q - qn * Q;
             const int sender = partner_up(qn, qg, Q, N, dim, tz[s] * rx);
-            const int j = e / Q, l = e - j * Q;
             const int ssrc = ts[s], sdst = td[s];
             if (ssrc < 0) {
-                const int sn = sender / Q, sg = sender - sn * Q;
+                int sn, sg;
+                split_slot_index(sender, Q, N, sn, sg);
                 int dn = sn - j; if (dn < 0) dn += N;
                 int dg = sg - l; if (dg < 0) dg += Q;
                 src = (unsigned long long)(a.S + sd32[sender * P + dn * Q + dg]);
@@ -2470,36 +2470,24 @@ __global__ void __launch_bounds__(kTinyThreads) k_tiny_call(const TinyArgs a) {
             unsigned long long sa = 0, da = 0, sb = 0, db = 0;
             const int na = resolve(b0 + grp, sa, da);
             const int nbb = resolve(b0 + kTinyThreads / 16 + grp, sb, db);
-            const bool wa = ((sa | da | (unsigned long long)na) & 3ull) == 0;
-            const bool wb = ((sb | db | (unsigned long long)nbb) & 3ull) == 0;
-            const uint32_t* a4 = reinterpret_cast<const uint32_t*>(sa);
-            const uint32_t* b4 = reinterpret_cast<const uint32_t*>(sb);
-            uint32_t* ad4 = reinterpret_cast<uint32_t*>(da);
-            uint32_t* bd4 = reinterpret_cast<uint32_t*>(db);
-            const int nwa = wa ? na >> 2 : 0, nwb = wb ? nbb >> 2 : 0;
-            for (int i = sub; i < max(nwa, nwb); i += 32) {     // four independent words per step
-                const uint32_t a0 = i < nwa ? a4[i] : 0u;
-                const uint32_t a1 = i + 16 < nwa ? a4[i + 16] : 0u;
-                const uint32_t c0_ = i < nwb ? b4[i] : 0u;
-                const uint32_t c1_ = i + 16 < nwb ? b4[i + 16] : 0u;
-                if (i < nwa) ad4[i] = a0;
-                if (i + 16 < nwa) ad4[i + 16] = a1;
-                if (i < nwb) bd4[i] = c0_;
-                if (i + 16 < nwb) bd4[i + 16] = c1_;
+            // 16 bytes per lane at the blocks' own alignment, the last ones ending with the block (as in k_hop_direct): a
+            // block of up to 256 bytes is one round trip
+            for (int o = sub * 16; o < max(na, nbb); o += 256) {
+                const bool wa = na >= 16 && o < na, wb = nbb >= 16 && o < nbb;
+                const int oa = min(o, na - 16), ob = min(o, nbb - 16);
+                const v4u va = load_global<v4u_any>(wa ? sa + oa : dummy);
+                const v4u vb = load_global<v4u_any>(wb ? sb + ob : dummy);
+                if (wa) store_global<v4u_any>(da + oa, va);
+                if (wb) store_global<v4u_any>(db + ob, vb);
             }
-            if (!wa) {
-                const unsigned char* sp = reinterpret_cast<const unsigned char*>(sa);
-                unsigned char* dp = reinterpret_cast<unsigned char*>(da);
-                for (int i = sub; i < na; i += 16) dp[i] = sp[i];
-            }
-            if (!wb) {
-                const unsigned char* sp = reinterpret_cast<const unsigned char*>(sb);
-                unsigned char* dp = reinterpret_cast<unsigned char*>(db);
-                for (int i = sub; i < nbb; i += 16) dp[i] = sp[i];
+            if (sub == 0) {
+                const int sha = na < 16 ? na : 0, shb = nbb < 16 ? nbb : 0;
+                const ShortBlock ba = short_load(sa, sha, dummy), bb = short_load(sb, shb, dummy);
+                short_store(da, sa, sha, ba);
+                short_store(db, sb, shb, bb);
             }
         }
         __syncthreads();                                  // the blocks stored into T are read in a later phase
-        int* t = c0; c0 = c1; c1 = t;
     }
 }
 
