@@ -175,6 +175,9 @@ int tuna_alltoallv_hier(const void* sendbuf, const int32_t* sendcounts, const in
  *                before it (which store whole 16-byte chunks into T) when T is kept in exact size and
  *                the mean block is 512 bytes or more; otherwise (and always for T in slots, batches of
  *                rounds and the staggered schedule) over the blocks.  Which of the two ran changes no byte.
+ *                Phases whose blocks are all at most 64 KiB (and at most 4 KiB on average, where the rule above
+ *                picks the tiling) are tiled over their destinations whatever they are, by kernels that find the
+ *                blocks themselves; the rule then only says under which of the two times they are reported.
  *                TUNA_MODE_STAGED: pack -> exchange -> unpack, the paper's three steps as three kernels.
  *                TUNA_MODE_FUSED: the one-kernel hops.
  *   staggered, t_layout, block_count, profile: as TUNA_OPT_STAGGERED, TUNA_OPT_DENSE_T,

@@ -579,6 +579,7 @@ struct Prepared {
     bool exact_kernels = false;         // T in exact size was asked for
     bool tiled = false;                 // one-kernel phases before the last run as the destination-tiled hop (k_copy_tiled) where they can
     bool tiled_final = false;           // and so does the last phase
+    bool for_plan = false;              // a persistent plan, whose starts only run the payload kernels
     bool sizes_direct = false;          // one phase: the receivers' sizes were taken from recvcounts (run_one_pass), no size exchange
     std::vector<int*> tpre;             // per phase: the blocks' offsets in message order (one array shared, or one each)
     ExactT x{};
@@ -851,9 +852,14 @@ int prepare_call(Ctx& c, const Options& opt, const void* sendbuf, const int32_t*
 bool phase_stores_lines(const Prepared& pr, size_t i) {
     return i + 1 == pr.dp->host.phases.size() ? pr.tiled_final : (pr.tiled && pr.exact_t);
 }
-// Of them, those with blocks longer than k_hop_rows takes run k_copy_tiled.  (T in slots keeps the copy engine there:
-// its slot tails are filled up to the line by a path of their own.)
-bool phase_is_tiled(const Prepared& pr, size_t i) { return phase_stores_lines(pr, i) && !row_blocks(pr); }
+// Phases that run k_hop_rows.  A plan has paid for its metadata when it is made: there the phases above keep the
+// destination-tiled hop, whose units are all full (1 KiB, per start, tiled against rows: P = 2048
+// r = 8 5.06 / 5.42 ms, linear 1.59 / 1.63, P = 1024 r = 2 1.97 / 2.04); a call is faster without the metadata (P = 2048
+// r = 2 9.57 / 9.24, P = 1024 r = 4 1.70 / 1.61).
+bool phase_is_rows(const Prepared& pr, size_t i) { return row_blocks(pr) && !(pr.for_plan && phase_stores_lines(pr, i)); }
+// The other phases whose stores are mostly whole lines run k_copy_tiled.  (T in slots keeps the copy engine: its slot
+// tails are filled up to the line by a path of their own.)
+bool phase_is_tiled(const Prepared& pr, size_t i) { return phase_stores_lines(pr, i) && !phase_is_rows(pr, i); }
 
 // The last phase of a word-granular schedule as a tiled hop takes units of twice the size (k_copy_tiled<4, 8>):
 // every block it writes has an edge piece, and what a wave spends on its edge pieces does not grow with the unit.
@@ -936,7 +942,7 @@ int launch_phase_metadata(const Prepared& pr, size_t i, const int32_t* cur, int3
     // P = 256, while at P = 4096 the separate kernel saves 44 us per phase): the scan kernel then
     // exchanges the sizes itself
     m.inline_exchange = (pr.P <= 128 && !pr.sizes_direct) ? 1 : 0;
-    int rc = phase_metadata(m, s, exact_t_of(pr, i), pr.sizes_direct, !(one_kernel && (small_blocks(pr) || row_blocks(pr))));
+    int rc = phase_metadata(m, s, exact_t_of(pr, i), pr.sizes_direct, !(one_kernel && (small_blocks(pr) || phase_is_rows(pr, i))));
     if (rc != TUNA_OK || !one_kernel) return rc;
     return launch_resolve(pr, i, nxt, hop, s);
 }
@@ -1189,7 +1195,7 @@ int launch_phase_data(const Prepared& pr, size_t i, const LayoutDev& Ls, const L
             mark(pr.ctx, s, kCatPack, (int)i);
             continue;
         }
-        if (phase_is_one_kernel(pr, ph) && row_blocks(pr)) {
+        if (phase_is_one_kernel(pr, ph) && phase_is_rows(pr, i)) {
             rc = launch_rows(pr, i, hop, nullptr, s);
             if (rc != TUNA_OK) return rc;
             mark(pr.ctx, s, phase_stores_lines(pr, i) ? kCatUnpack : kCatPack, (int)i);
@@ -1709,6 +1715,7 @@ int plan_create(Ctx& c, const Options& opt, const void* sendbuf, const int32_t* 
     plan->ctx = &c;
     Prepared& pr = plan->pr;
     pr.debug_sizes = debug_sizes;
+    pr.for_plan = true;
     Status hs{};
     c.profile = false;
     int rc = prepare_call(c, opt, sendbuf, sendcounts, sdispls, recvbuf, recvcounts, rdispls, P, ranks_per_node, rl, rg, s,
