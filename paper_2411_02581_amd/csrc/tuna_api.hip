@@ -503,8 +503,10 @@ int resolve_hierarchy(int P, int ranks_per_node, int* Q) {
 }
 
 // Validation + sizing pass shared by tuna_alltoallv* and tuna_workspace_bytes: fills *sb.h_status.
+// clear_totals: the per-phase totals in *sb.d_status start at zero (an immediate call, whose kernels may add to them).  A
+// sizing query and a plan leave them alone: until the next call they are the last one's statistics, or still being summed.
 int run_validate(const StatusBufs& sb, const int32_t* sendcounts, const int32_t* recvcounts, const int64_t* sdispls,
-                 const int64_t* rdispls, int P, hipStream_t s, const DevicePlan* exact_t_for = nullptr) {
+                 const int64_t* rdispls, int P, hipStream_t s, const DevicePlan* exact_t_for, bool clear_totals) {
     // every field of the status block a call reads is written by the call's own kernels: no clearing
     const size_t t = (size_t)((P + kValTile - 1) / kValTile);
     const unsigned vgrid = (unsigned)(t * t < (size_t)sb.num_cus * 8 ? t * t : (size_t)sb.num_cus * 8);
@@ -523,7 +525,7 @@ int run_validate(const StatusBufs& sb, const int32_t* sendcounts, const int32_t*
     hipLaunchKernelGGL(k_validate, dim3(vgrid), dim3(kValTile, ny), (size_t)ncls * copies * 8, s, sendcounts, recvcounts, sdispls,
                        rdispls, P, fold ? sb.h_part_dev : sb.d_vpart, exact_t_for ? exact_t_for->d_hm1 : nullptr,
                        exact_t_for ? exact_t_for->host.Q : 1, exact_t_for ? exact_t_for->host.N : 1,
-                       exact_t_for ? exact_t_for->d_mask : nullptr, nph, sb.d_status, fold ? 1 : 0, copies);
+                       exact_t_for ? exact_t_for->d_mask : nullptr, nph, sb.d_status, fold ? 1 : 0, copies, clear_totals ? 1 : 0);
     HIPCHK(hipGetLastError());
     if (fold) {
         HIPCHK(hipStreamSynchronize(s));
@@ -541,7 +543,8 @@ int run_validate(const StatusBufs& sb, const int32_t* sendcounts, const int32_t*
         h.flags = (unsigned int)(fa >> 32); h.align_bits = (unsigned int)(fa & 127u); h.max_count = (int)m;
         return TUNA_OK;
     }
-    hipLaunchKernelGGL(k_validate_finish, dim3(1), dim3(256), 0, s, sb.d_vpart, (int)vgrid, sb.d_status);
+    hipLaunchKernelGGL(k_validate_finish, dim3(1), dim3(256), 0, s, sb.d_vpart, (int)vgrid, sb.d_status,
+                       clear_totals ? 1 : 0);
     HIPCHK(hipGetLastError());
     // the head and the class sums behind it in one copy
     HIPCHK(hipMemcpyAsync(sb.h_status, sb.d_status, offsetof(Status, cls_chunks) + (size_t)ncls * 8, hipMemcpyDeviceToHost, s));
@@ -771,7 +774,7 @@ int prepare_sizes(Prepared& pr, int dense_option, hipStream_t s, Status& hs, boo
     const int P = pr.P;
     const bool has_t = pr.dp->host.slots > 0;              // a schedule without T (r >= P - 1) has nothing to size
     int rc = run_validate(pr.sb, pr.sendcounts, pr.recvcounts, pr.sdispls, pr.rdispls, P, s,
-                          (dense_option != 0 && has_t) ? pr.dp : nullptr);
+                          (dense_option != 0 && has_t) ? pr.dp : nullptr, !pr.for_plan);
     if (rc != TUNA_OK) return rc;
     hs = *pr.sb.h_status;
     if (pr.dp->built_on == s) pr.dp->complete = true;      // run_validate synchronised this stream
@@ -2446,7 +2449,8 @@ int tuna_workspace_bytes(const int32_t* sendcounts, int P, int ranks_per_node, i
     rc = get_plan(P, Q, local_radix, staggered ? N : global_radix, fused, nullptr, &dp);
     if (rc != TUNA_OK) return rc;
     const PlanHost& pl = dp->host;
-    rc = run_validate(g.sb, sendcounts, nullptr, nullptr, nullptr, P, nullptr, (o.t_layout != 0 && pl.slots > 0) ? dp : nullptr);
+    rc = run_validate(g.sb, sendcounts, nullptr, nullptr, nullptr, P, nullptr, (o.t_layout != 0 && pl.slots > 0) ? dp : nullptr,
+                      /*clear_totals=*/false);
     if (rc != TUNA_OK) return rc;
     const Status* h_status = g.sb.h_status;
     std::vector<long long> cbase;

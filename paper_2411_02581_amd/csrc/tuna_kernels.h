@@ -238,7 +238,7 @@ __global__ void __launch_bounds__(1024) k_validate(const int32_t* __restrict__ s
                                                    int P, unsigned long long* __restrict__ partial,
                                                    const int32_t* __restrict__ hm1, int Q, int N,
                                                    const unsigned long long* __restrict__ mask, int nph,
-                                                   Status* __restrict__ st, int cls_rows, int copies) {
+                                                   Status* __restrict__ st, int cls_rows, int copies, int clear_totals) {
     __shared__ int tile[kValTile][kValTile + 1];
     __shared__ unsigned long long red[16][7];
     extern __shared__ unsigned long long lcls[];          // class_count(nph) sums of this workgroup, `copies` of each (with `mask`)
@@ -394,8 +394,9 @@ __global__ void __launch_bounds__(1024) k_validate(const int32_t* __restrict__ s
         if (cls_rows) o[kValPartial + i] = v;
         else if (v) atomicAdd(&st->cls_chunks[i], v);
     }
-    // the totals that k_phase_sums adds to (without cls_rows k_validate_finish clears them)
-    if (cls_rows && blockIdx.x == 0 && ty == 0) st->phase_bytes[tx] = st->phase_chunks[tx] = 0;
+    // the totals that k_phase_sums adds to (without cls_rows k_validate_finish clears them), not for a sizing query: the
+    // totals there belong to the context's last call
+    if (cls_rows && clear_totals && blockIdx.x == 0 && ty == 0) st->phase_bytes[tx] = st->phase_chunks[tx] = 0;
 }
 
 // k_zero64: n 64-bit words to zero (the class sums before a validation pass).
@@ -406,7 +407,7 @@ __global__ void __launch_bounds__(256) k_zero64(unsigned long long* __restrict__
 
 // k_validate_finish: folds the workgroups' partial results into the status block (one workgroup).
 __global__ void __launch_bounds__(256) k_validate_finish(const unsigned long long* __restrict__ partial, int n,
-                                                         Status* __restrict__ st) {
+                                                         Status* __restrict__ st, int clear_totals) {
     __shared__ unsigned long long red[4][7];
     unsigned long long fa = 0, m = 0, by = 0, ch = 0, ex = 0, tc = 0, sb = 0;
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
@@ -442,7 +443,7 @@ __global__ void __launch_bounds__(256) k_validate_finish(const unsigned long lon
         st->short_blocks = sb;
     }
     // the totals that k_phase_sums adds to; the other paths write them whole
-    if (threadIdx.x < 64) st->phase_bytes[threadIdx.x] = st->phase_chunks[threadIdx.x] = 0;
+    if (clear_totals && threadIdx.x < 64) st->phase_bytes[threadIdx.x] = st->phase_chunks[threadIdx.x] = 0;
 }
 
 // ------------------------------------------------------------------------------------------
