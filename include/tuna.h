@@ -74,7 +74,8 @@ typedef struct tuna_phase_stats {
     int32_t rounds;         /* number of point-to-point rounds (valid z) in this phase */
     int64_t blocks;         /* blocks moved, all ranks, empty ones included */
     int64_t payload_bytes;  /* b_x: payload bytes of those blocks */
-    int64_t staged_bytes;   /* bytes they occupy in a staging buffer (every block padded to 16 B) */
+    int64_t staged_bytes;   /* bytes they occupy in a staging buffer: 16 per chunk a block touches (one-kernel phases: between
+                             * the 16-byte boundaries of its destination), every rank's share rounded up to 128 */
     float ms_metadata;      /* metadata exchange + scans (profiling mode only, else 0) */
     float ms_pack;          /* one-kernel phases have one payload kernel: the copy engine's hop is reported here, */
     float ms_exchange;

@@ -915,9 +915,12 @@ int launch_tiled_metadata(const Prepared& pr, size_t i, const int32_t* cur, int3
     if (rc != TUNA_OK) return rc;
     TiledLayoutArgs fa{};
     fa.hop = hop; fa.nseg = ph.nseg; fa.P = P; fa.Lr = Lr; fa.rank_bytes = last ? pr.rank_bytes : nullptr;
+    // the pieces are not the staged chunks of the statistics (neighbours share edge pieces, runs have dead ones): those
+    // are counted into the send-side layout, which a one-kernel phase has no other use for
+    fa.rank_chunks = Ls.tot;
     hipLaunchKernelGGL(k_tiled_layout, dim3(P), dim3(kScanThreads), 0, s, fa);
     HIPCHK(hipGetLastError());
-    hipLaunchKernelGGL(k_layout_base, dim3(1), dim3(kScanThreads), 0, s, P, Lr, Ls, 1, &pr.sb.d_status->phase_chunks[i], 0,
+    hipLaunchKernelGGL(k_layout_base, dim3(2), dim3(kScanThreads), 0, s, P, Lr, Ls, 2, &pr.sb.d_status->phase_chunks[i], 1,
                        ExactT{}, pr.rank_bytes, &pr.sb.d_status->phase_bytes[i], pr.sb.d_status->phase_units[i]);
     HIPCHK(hipGetLastError());
     const int lds_ints = ph.nseg + 1 <= kUnitsLdsMaxInts ? ph.nseg + 1 : 0;

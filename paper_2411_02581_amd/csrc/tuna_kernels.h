@@ -1941,23 +1941,26 @@ k_copy(const CopyArgs a) {
 // predecessor.  A segment that starts a run owns the pieces from the start of a's 128-byte line, and
 // in front of them come the dead pieces that complete the previous run's last line, so that every run
 // starts at a multiple of 8 pieces.  The prefix row has the same form as a chunk prefix row:
-// k_layout_base and k_layout_units cut it into wave units of 256 pieces.
+// k_layout_base and k_layout_units cut it into wave units of 256 pieces.  The staged chunks of the statistics
+// are summed beside it: pieces are not chunks.
 // ------------------------------------------------------------------------------------------
 struct TiledLayoutArgs {
     HopDev hop;
     int nseg, P;
     LayoutDev Lr;
+    int* rank_chunks;                   // [P]: staged chunks of every rank, counted as the chunk scan and k_phase_sums count them
     unsigned long long* rank_bytes;     // [P]: payload bytes every rank receives in the phase; nullptr: already known
 };
 
 __global__ void __launch_bounds__(kScanThreads) k_tiled_layout(const TiledLayoutArgs a) {
     __shared__ int wsum[kScanThreads / kWave];
     __shared__ unsigned long long wbytes[kScanThreads / kWave];
+    __shared__ int wchunks[kScanThreads / kWave];
     const int p = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const size_t o = (size_t)p * a.hop.ld;
     int* pre_r = a.Lr.pre + (size_t)p * a.Lr.ld;
-    int carry = 0;
+    int carry = 0, chunks = 0;
     unsigned long long bytes = 0;
     for (int base = 0; base < a.nseg; base += kScanThreads * kScanItems) {
         int cr[kScanItems];
@@ -1976,6 +1979,7 @@ __global__ void __launch_bounds__(kScanThreads) k_tiled_layout(const TiledLayout
                 const int own = tiled_pieces(d, n, s > 0, e_prev, &dead);
                 cr[k] = dead + own;
                 bytes += (unsigned long long)n;
+                chunks += n > 0 ? ((int)(d & 15ull) + n + 15) >> 4 : 0;
             }
         }
         int run[kScanItems];
@@ -1987,15 +1991,17 @@ __global__ void __launch_bounds__(kScanThreads) k_tiled_layout(const TiledLayout
         }
     }
 #pragma unroll
-    for (int d = kWave / 2; d > 0; d >>= 1) bytes += __shfl_xor(bytes, d, kWave);
+    for (int d = kWave / 2; d > 0; d >>= 1) { bytes += __shfl_xor(bytes, d, kWave); chunks += __shfl_xor(chunks, d, kWave); }
     __syncthreads();
-    if (lane == 0) wbytes[tid / kWave] = bytes;
+    if (lane == 0) { wbytes[tid / kWave] = bytes; wchunks[tid / kWave] = chunks; }
     __syncthreads();
     if (tid == 0) {
         unsigned long long t = 0;
+        int c = 0;
 #pragma unroll
-        for (int k = 0; k < kScanThreads / kWave; ++k) t += wbytes[k];
+        for (int k = 0; k < kScanThreads / kWave; ++k) { t += wbytes[k]; c += wchunks[k]; }
         if (a.rank_bytes) a.rank_bytes[p] = t;
+        a.rank_chunks[p] = c;
         pre_r[a.nseg] = carry; a.Lr.tot[p] = carry;
     }
 }

@@ -91,3 +91,48 @@ def test_short_and_row_blocks(tuna, P, longest, quantum, radix, t_layout):
         assert rc == 0, tuna.tuna_strerror(rc)
         torch.cuda.synchronize()
         assert np.array_equal(recv.cpu().numpy(), want), "noalloc"
+
+
+def _staged(lay):
+    """Staged bytes of the linear schedule's only phase: every received block's chunks between the 16-byte boundaries
+    of R, every rank's share rounded up to a line."""
+    n, d = lay.recvcounts.astype(np.int64), lay.rdispls
+    chunks = np.where(n > 0, (d % 16 + n + 15) // 16, 0)
+    np.fill_diagonal(chunks, 0)
+    return int(((chunks.sum(axis=1) + 7) // 8 * 8).sum()) * 16
+
+
+@pytest.mark.parametrize("radix", [4, 96])
+@pytest.mark.parametrize("name", ["normal 1 KiB", "normal 1 KiB chunks", "normal 6 KiB", "Zipf"])
+def test_totals_of_call_and_plan_agree(tuna, name, radix):
+    """Dense receive regions, where a plan keeps the destination-tiled hop and counts pieces of runs for its units: the
+    staged bytes that it reports are the call's all the same."""
+    P, dev = 96, "cuda:0"
+    counts = {"normal 1 KiB": lambda: wl.counts_normal(P, 3, 1024.0, 256.0, 4),
+              "normal 1 KiB chunks": lambda: wl.counts_normal(P, 3, 1024.0, 256.0, 16),
+              "normal 6 KiB": lambda: wl.counts_normal(P, 4, 6144.0, 1536.0, 4),
+              "Zipf": lambda: wl.counts_zipf(P, 12, 1.2, 16384, 4)}[name]()
+    lay = wl.make_layout(np.ascontiguousarray(counts, dtype=np.int32))
+    sc, sd, rc_, rd = [torch.from_numpy(a).to(dev) for a in (lay.sendcounts, lay.sdispls, lay.recvcounts, lay.rdispls)]
+    send = torch.zeros(lay.send_bytes, dtype=torch.uint8, device=dev)
+    recv = torch.zeros(lay.recv_bytes, dtype=torch.uint8, device=dev)
+    o = tuna.tuna_opts_init()
+    o.t_layout = tuna.TUNA_T_EXACT
+
+    def totals():
+        st = tuna.tuna_get_stats()
+        return [(st.phase[x].payload_bytes, st.phase[x].staged_bytes) for x in range(st.n_phases)]
+
+    print("totals of call and plan", name, radix, flush=True)
+    assert tuna.tuna_alltoallv_ex(None, send, sc, sd, recv, rc_, rd, P, 0, radix, radix, o) == 0
+    call = totals()
+    rc, plan = tuna.tuna_alltoallv_init_ex(None, send, sc, sd, recv, rc_, rd, P, 0, radix, radix, o)
+    assert rc == 0
+    try:
+        assert tuna.tuna_start(plan) == 0
+        torch.cuda.synchronize()
+        assert totals() == call
+    finally:
+        tuna.tuna_plan_free(plan)
+    if radix == P:
+        assert call[0][1] == _staged(lay)
