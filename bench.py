@@ -138,7 +138,7 @@ class Resident:
         torch.cuda.synchronize()
         ms_per_step = (time.perf_counter() - t_start) * 1e3 / self.steps
         o.profile = 1
-        kern = {"pack": [0.0, 0, 0], "exchange": [0.0, 0, 0], "unpack": [0.0, 0, 0], "unpack_last": [0.0, 0, 0]}   # ms, launches, payload bytes
+        kern = {}                                            # stage: [ms, launches, payload bytes]
         meta_ms = prep_ms = self_ms = prof_total = 0.0
         for _ in range(self.steps):
             self.call(rl, rg, o)
@@ -149,23 +149,15 @@ class Resident:
             for x in range(st.n_phases):
                 ph = st.phase[x]
                 meta_ms += ph.ms_metadata
-                # the tiled hop of a schedule's last phase is a kernel variant of its own when the data is word-granular
-                # and the blocks are longer than k_hop_rows takes
-                last_tiled = bool(st.fused) and x + 1 == st.n_phases and st.granularity < 16 and st.max_block_bytes > 65536
-                for name, ms in (("pack", ph.ms_pack), ("exchange", ph.ms_exchange),
-                                 ("unpack_last" if last_tiled else "unpack", ph.ms_unpack)):
+                for name, ms in zip(self.stages(st, x), (ph.ms_pack, ph.ms_exchange, ph.ms_unpack)):
                     if ms > 0:
-                        kern[name][0] += ms
-                        kern[name][1] += 1
-                        kern[name][2] += ph.payload_bytes
+                        k = kern.setdefault(name, [0.0, 0, 0])
+                        k[0] += ms
+                        k[1] += 1
+                        k[2] += ph.payload_bytes
         o.profile = 0
         st = tuna.tuna_get_stats()
         hop_bytes = sum(st.phase[x].payload_bytes for x in range(st.n_phases))
-        if st.fused:        # one kernel per phase: the copy engine's hop is reported in the pack column, the
-            kern = {"hop": kern["pack"], "tiled_hop": kern["unpack"],     # destination-tiled hop in the unpack column
-                    "tiled_hop_last": kern["unpack_last"]}
-        else:
-            kern.pop("unpack_last")
         kernels = {}
         for name, (ms, n, pbytes) in kern.items():
             if n and ms > 0:
@@ -184,6 +176,16 @@ class Resident:
               ", ".join("%s %.0f GB/s" % (k, v["achieved_GBs"]) for k, v in kernels.items()) +
               (" [one-kernel phases]" if st.fused else " [three stages]"), file=sys.stderr, flush=True)
         return row
+
+    def stages(self, st, x):
+        """Names of what phase x reports as its pack, exchange and unpack time."""
+        t = self.tuna
+        if not st.fused and not (st.hop_kernels and st.phase[x].dim == 1):      # (the staggered schedule's global phases are one kernel)
+            return "pack", "exchange", "unpack"
+        # one kernel per phase: the destination-tiled hop in the unpack column, every other in the pack column; the tiled hop
+        # of a schedule's last phase is a kernel variant of its own when the data is word-granular
+        hop = "direct_hop" if st.hop_kernels & t.TUNA_HOP_DIRECT else "row_hop" if st.hop_kernels & t.TUNA_HOP_ROWS else "hop"
+        return hop, "exchange", "tiled_hop_last" if x + 1 == st.n_phases and st.granularity < 16 else "tiled_hop"
 
     def sweep(self, radices, **opt):
         return [self.time_calls(rl, rg, self.opts(**opt), label) for label, rl, rg in radices]
@@ -247,17 +249,14 @@ def radices_of(cfg, P, override=""):
     return [("r=%d" % min(r, P), min(r, P), min(r, P)) for r in rs]
 
 
-def kernel_name(stage, gran, exact, max_block_bytes=None, mean_block_bytes=None):
+def kernel_name(stage, gran, exact, max_block_bytes):
     et = "true" if exact else "false"
-    if "hop" in stage and max_block_bytes:
-        if max_block_bytes <= 256:      # short blocks; the tall tiles are those of the schedules of one phase
-            return "tuna::k_hop_direct<%d, ...>" % (1 if max_block_bytes <= 16 else 4 if max_block_bytes <= 64 else 16)
-        if max_block_bytes <= 65536 and (stage == "hop" or (mean_block_bytes or 0) <= 4096):
-            return "tuna::k_hop_rows<%s, %s, false>" % ("true" if gran == 128 else "false", et)
+    lpb = 1 if max_block_bytes <= 16 else 4 if max_block_bytes <= 64 else 16
     return {"pack": "tuna::k_copy<0, %d, %s>" % (gran, et), "exchange": "tuna::k_copy<1, 16, false>",
             "unpack": "tuna::k_copy<2, %d, %s>" % (min(gran, 16), et), "hop": "tuna::k_copy<3, %d, %s>" % (gran, et),
-            "tiled_hop": "tuna::k_copy_tiled<%d, 4>" % (16 if gran >= 16 else 4),
-            "tiled_hop_last": "tuna::k_copy_tiled<4, 8>"}[stage]
+            "tiled_hop": "tuna::k_copy_tiled<%d, 4>" % (16 if gran >= 16 else 4), "tiled_hop_last": "tuna::k_copy_tiled<4, 8>",
+            "direct_hop": "tuna::k_hop_direct<%d, ...>" % lpb,
+            "row_hop": "tuna::k_hop_rows<%s, %s, false>" % ("true" if gran == 128 else "false", et)}[stage]
 
 
 def roofline_of(rows, steps, traffic, copy_ceiling):
@@ -275,8 +274,7 @@ def roofline_of(rows, steps, traffic, copy_ceiling):
     if not tot:
         return None
     name, (ms, n, alg) = max(tot.items(), key=lambda kv: kv[1][0])
-    kname = kernel_name(name, rows[0]["granularity"], bool(rows[0]["exact_size_t"]), rows[0].get("max_block_bytes"),
-                        rows[0].get("mean_block_bytes"))
+    kname = kernel_name(name, rows[0]["granularity"], bool(rows[0]["exact_size_t"]), rows[0]["max_block_bytes"])
     achieved = alg / (ms * 1e-3) / 1e9
     tr = traffic.get("bytes_per_launch", {}).get(kname) if traffic else None
     return {"bound": "hbm", "kernel": kname, "stage": name, "achieved": achieved, "peak": HBM_PEAK_GBS,

@@ -77,10 +77,17 @@ typedef struct tuna_phase_stats {
     int64_t staged_bytes;   /* bytes they occupy in a staging buffer: 16 per chunk a block touches (one-kernel phases: between
                              * the 16-byte boundaries of its destination), every rank's share rounded up to 128 */
     float ms_metadata;      /* metadata exchange + scans (profiling mode only, else 0) */
-    float ms_pack;          /* one-kernel phases have one payload kernel: the copy engine's hop is reported here, */
+    float ms_pack;          /* one-kernel phases have one payload kernel: the destination-tiled hop is reported as ms_unpack, */
     float ms_exchange;
-    float ms_unpack;        /* the destination-tiled hop here */
+    float ms_unpack;        /* every other one as ms_pack (tuna_stats_t.hop_kernels says which they were) */
 } tuna_phase_stats_t;
+
+/* Payload kernels of one-kernel phases.  One call or plan runs the destination-tiled hop in some of its phases and one
+ * of the other three in the rest. */
+#define TUNA_HOP_ENGINE 1   /* the copy engine's hop */
+#define TUNA_HOP_TILED 2    /* the destination-tiled hop */
+#define TUNA_HOP_DIRECT 4   /* blocks of up to 256 bytes, found by the kernel that moves them */
+#define TUNA_HOP_ROWS 8     /* blocks of up to 64 KiB, found by the kernel that moves them */
 
 typedef struct tuna_stats {
     int32_t P, Q, N;                 /* ranks, ranks per node, nodes (flat: Q = P, N = 1) */
@@ -102,7 +109,7 @@ typedef struct tuna_stats {
     float ms_prepare;                /* validation, sizing, initial rotation (profiling mode only) */
     float ms_self;                   /* own-block copy */
     float ms_total;                  /* first to last kernel of the call */
-    float reserved_f;
+    int32_t hop_kernels;             /* TUNA_HOP_* of the one-kernel phases, or-ed (0: none, or the single-launch call) */
     tuna_phase_stats_t phase[TUNA_MAX_PHASES];
 } tuna_stats_t;
 
@@ -177,8 +184,8 @@ int tuna_alltoallv_hier(const void* sendbuf, const int32_t* sendcounts, const in
  *                the mean block is 512 bytes or more; otherwise (and always for T in slots, batches of
  *                rounds and the staggered schedule) over the blocks.  Which of the two ran changes no byte.
  *                Phases whose blocks are all at most 64 KiB (and at most 4 KiB on average, where the rule above
- *                picks the tiling) are tiled over their destinations whatever they are, by kernels that find the
- *                blocks themselves; the rule then only says under which of the two times they are reported.
+ *                picks the tiling) run kernels that find the blocks themselves instead; a plan, which has paid for
+ *                its metadata, keeps the tiling where the rule picks it.
  *                TUNA_MODE_STAGED: pack -> exchange -> unpack, the paper's three steps as three kernels.
  *                TUNA_MODE_FUSED: the one-kernel hops.
  *   staggered, t_layout, block_count, profile: as TUNA_OPT_STAGGERED, TUNA_OPT_DENSE_T,

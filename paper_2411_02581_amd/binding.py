@@ -32,6 +32,7 @@ TUNA_MAX_PHASES = 64
 TUNA_RADIX_AUTO = 0
 TUNA_MODE_AUTO, TUNA_MODE_STAGED, TUNA_MODE_FUSED = 0, 1, 2
 TUNA_T_SLOTS, TUNA_T_EXACT, TUNA_T_AUTO = 0, 1, 2
+TUNA_HOP_ENGINE, TUNA_HOP_TILED, TUNA_HOP_DIRECT, TUNA_HOP_ROWS = 1, 2, 4, 8
 
 EXPORTS = ("tuna_alltoallv", "tuna_alltoallv_hier", "tuna_alltoallv_noalloc", "tuna_alltoallv_ex", "tuna_alltoallv_init_ex",
            "tuna_opts_init", "tuna_ctx_create", "tuna_ctx_destroy", "tuna_ctx_get_stats", "tuna_build_id", "tuna_debug_phase_sizes", "tuna_workspace_bytes", "tuna_set_workspace",
@@ -61,7 +62,7 @@ class tuna_stats_t(ctypes.Structure):
                 ("temp_slots_per_rank", ctypes.c_int64), ("temp_bytes", ctypes.c_int64),
                 ("staging_bytes", ctypes.c_int64), ("workspace_bytes", ctypes.c_int64),
                 ("ms_prepare", ctypes.c_float), ("ms_self", ctypes.c_float),
-                ("ms_total", ctypes.c_float), ("reserved_f", ctypes.c_float),
+                ("ms_total", ctypes.c_float), ("hop_kernels", ctypes.c_int32),
                 ("phase", tuna_phase_stats_t * TUNA_MAX_PHASES)]
 
 

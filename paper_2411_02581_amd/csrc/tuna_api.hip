@@ -849,9 +849,9 @@ int prepare_call(Ctx& c, const Options& opt, const void* sendbuf, const int32_t*
     return prepare_sizes(pr, opt.t_layout, s, hs, empty);
 }
 
-// Phases whose stores are mostly whole lines, reported as destination-tiled: the last one (all its blocks are final)
-// when the blocks are mostly interior, and with T in exact size the ones before it -- the blocks a rank stores into T
-// lie back to back inside their class, so their destinations form runs just like those in R, and they are whole chunks.
+// Phases whose stores are mostly whole lines: the last one (all its blocks are final) when the blocks are mostly
+// interior, and with T in exact size the ones before it -- the blocks a rank stores into T lie back to back inside
+// their class, so their destinations form runs just like those in R, and they are whole chunks.
 bool phase_stores_lines(const Prepared& pr, size_t i) {
     return i + 1 == pr.dp->host.phases.size() ? pr.tiled_final : (pr.tiled && pr.exact_t);
 }
@@ -863,6 +863,19 @@ bool phase_is_rows(const Prepared& pr, size_t i) { return row_blocks(pr) && !(pr
 // The other phases whose stores are mostly whole lines run k_copy_tiled.  (T in slots keeps the copy engine: its slot
 // tails are filled up to the line by a path of their own.)
 bool phase_is_tiled(const Prepared& pr, size_t i) { return phase_stores_lines(pr, i) && !phase_is_rows(pr, i); }
+
+// The payload kernel of phase i (TUNA_HOP_*; 0: three stages), and those of all phases.
+int phase_kernel(const Prepared& pr, size_t i) {
+    if (!phase_is_one_kernel(pr, pr.dp->host.phases[i])) return 0;
+    if (small_blocks(pr)) return TUNA_HOP_DIRECT;
+    if (phase_is_rows(pr, i)) return TUNA_HOP_ROWS;
+    return phase_is_tiled(pr, i) ? TUNA_HOP_TILED : TUNA_HOP_ENGINE;
+}
+int hop_kernels_of(const Prepared& pr) {
+    int all = 0;
+    for (size_t i = 0; i < pr.dp->host.phases.size(); ++i) all |= phase_kernel(pr, i);
+    return all;
+}
 
 // The last phase of a word-granular schedule as a tiled hop takes units of twice the size (k_copy_tiled<4, 8>):
 // every block it writes has an edge piece, and what a wave spends on its edge pieces does not grow with the unit.
@@ -948,7 +961,7 @@ int launch_phase_metadata(const Prepared& pr, size_t i, const int32_t* cur, int3
     // P = 256, while at P = 4096 the separate kernel saves 44 us per phase): the scan kernel then
     // exchanges the sizes itself
     m.inline_exchange = (pr.P <= 128 && !pr.sizes_direct) ? 1 : 0;
-    int rc = phase_metadata(m, s, exact_t_of(pr, i), pr.sizes_direct, !(one_kernel && (small_blocks(pr) || phase_is_rows(pr, i))));
+    int rc = phase_metadata(m, s, exact_t_of(pr, i), pr.sizes_direct, !(phase_kernel(pr, i) & (TUNA_HOP_DIRECT | TUNA_HOP_ROWS)));
     if (rc != TUNA_OK || !one_kernel) return rc;
     return launch_resolve(pr, i, nxt, hop, s);
 }
@@ -1195,21 +1208,22 @@ int launch_phase_data(const Prepared& pr, size_t i, const LayoutDev& Ls, const L
             if (row_units * (size_t)pr.P < unit_cap) { launch_units = row_units; a.batch_rows = 1; }
         }
         int rc;
-        if (phase_is_one_kernel(pr, ph) && small_blocks(pr)) {
+        const int kernel = phase_kernel(pr, i);
+        if (kernel == TUNA_HOP_DIRECT) {
             rc = launch_direct(pr, i, hop, a.seg_lo, a.seg_hi, nullptr, s);
             if (rc != TUNA_OK) return rc;
             mark(pr.ctx, s, kCatPack, (int)i);
             continue;
         }
-        if (phase_is_one_kernel(pr, ph) && phase_is_rows(pr, i)) {
+        if (kernel == TUNA_HOP_ROWS) {
             rc = launch_rows(pr, i, hop, nullptr, s);
             if (rc != TUNA_OK) return rc;
-            mark(pr.ctx, s, phase_stores_lines(pr, i) ? kCatUnpack : kCatPack, (int)i);
+            mark(pr.ctx, s, kCatPack, (int)i);
             continue;
         }
-        if (phase_is_tiled(pr, i)) {
+        if (kernel == TUNA_HOP_TILED) {
             // tiled over the 16-byte pieces of the destinations (k_copy_tiled); its time is reported as the
-            // phase's unpack time, so that it can be told from the copy engine's one-kernel hops
+            // phase's unpack time, so that it can be told from the other one-kernel hops
             TiledCopyArgs fa{};
             fa.L = layout_of_phase(pr, i, Lr); fa.hop = hop; fa.nseg = ph.nseg; fa.T = pr.T; fa.user_limit = pr.user_limit;
             const dim3 grid((unsigned)((launch_units + kCopyThreads / kWave - 1) / (kCopyThreads / kWave)));
@@ -1230,7 +1244,7 @@ int launch_phase_data(const Prepared& pr, size_t i, const LayoutDev& Ls, const L
             mark(pr.ctx, s, kCatUnpack, (int)i);
             continue;
         }
-        if (phase_is_one_kernel(pr, ph)) {
+        if (kernel == TUNA_HOP_ENGINE) {
             // one hop in one kernel: S / T of the sender -> R / the other copy of T at the receiver
             a.stage = nullptr; a.L = Lr; a.hop = hop;
             // measured on the 16 GiB workload: a phase of many rounds gathers short pieces from many senders
@@ -1323,7 +1337,7 @@ int launch_t_places(Prepared& pr, hipStream_t s) {
 int launch_direct_payload(const Prepared& pr, size_t i, uint2* part, hipStream_t s) {
     const int rc = row_blocks(pr) ? launch_rows(pr, i, HopDev{}, part, s)
                                   : launch_direct(pr, i, HopDev{}, 0, pr.dp->host.phases[i].nseg, part, s);
-    if (rc == TUNA_OK) mark(pr.ctx, s, phase_stores_lines(pr, i) ? kCatUnpack : kCatPack, (int)i);
+    if (rc == TUNA_OK) mark(pr.ctx, s, kCatPack, (int)i);
     return rc;
 }
 
@@ -1541,6 +1555,7 @@ int run_once(Ctx& c, const Options& opt, const void* sendbuf, const int32_t* sen
     tuna_stats_t& st = c.stats;
     fill_stats_header(pr, hs, st);
     if (empty) { c.have_stats = true; return TUNA_OK; }
+    st.hop_kernels = hop_kernels_of(pr);
     const PlanHost& pl = pr.dp->host;
     const bool direct = runs_direct(pr);
     if (use_two_pass(pl, hs) && pr.fused && !c.profile && !pr.debug_sizes && !direct) {
@@ -1729,6 +1744,7 @@ int plan_create(Ctx& c, const Options& opt, const void* sendbuf, const int32_t* 
     if (rc != TUNA_OK) { delete plan; return rc; }
     fill_stats_header(pr, hs, plan->stats);
     if (plan->empty) { ++sh.live_plans; *out = plan; return TUNA_OK; }
+    plan->stats.hop_kernels = hop_kernels_of(pr);
     const size_t mbytes = plan_meta_bytes(pr);
     hipError_t e = hipMalloc(&plan->mem_meta, mbytes ? mbytes : kAlign);
     if (e != hipSuccess) { (void)hipGetLastError(); sh.last_hip_error = (int)e; delete plan; return TUNA_ERR_NOMEM; }
@@ -2004,6 +2020,7 @@ int run_static(const void* sendbuf, const int32_t* sendcounts, const int64_t* sd
     fill_stats_header(pr, hs, g.stats);
     g.have_stats = true;
     if (empty) return TUNA_OK;
+    g.stats.hop_kernels = hop_kernels_of(pr);
     const size_t mbytes = one_pass_meta_bytes(pr);
     if (cv.off + mbytes + pr.ds.total > cv.cap) return TUNA_ERR_NOALLOC_LIMIT;
     char* mbase = cv.base + cv.off;

@@ -157,7 +157,8 @@ def test_large_calls_with_metadata_on_a_second_stream(tuna):
     assert big.call(tuna, None, 0, 4, 4, o) == 0
     torch.cuda.synchronize()
     st = tuna.tuna_get_stats()
-    assert big.ok() and all(st.phase[x].ms_metadata > 0 and st.phase[x].ms_unpack > 0 for x in range(st.n_phases))
+    assert big.ok() and st.hop_kernels == tuna.TUNA_HOP_ROWS
+    assert all(st.phase[x].ms_metadata > 0 and st.phase[x].ms_pack > 0 for x in range(st.n_phases))
     rc, ctx = tuna.tuna_ctx_create()
     assert rc == 0
     try:

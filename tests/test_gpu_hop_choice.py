@@ -1,10 +1,12 @@
-"""Which kernel a one-kernel phase runs (Algorithm "TuNA", lines 15-20 as one hop): the destination-tiled hop
-where the library's rule says it pays -- dense receive regions, data at least word-granular, all rounds of a
-phase at once; for a schedule's last phase, whose blocks all go into R, blocks that are mostly interior (mean of
-700 bytes or more, at most a quarter of them under 256 bytes); for the phases before it, which store whole
-chunks into T, a mean block of 512 bytes or more -- and the copy engine's hop everywhere else.  With profiling
-on, a phase's tiled hop is timed as its unpack time and the engine's hop as its pack time, which is how the test
-tells them apart; every case is also compared with the CPU oracle byte for byte."""
+"""Which kernel a one-kernel phase runs (Algorithm "TuNA", lines 15-20 as one hop).  Blocks of up to 256 bytes: the
+direct hop, which finds them itself.  Blocks of up to 64 KiB, all rounds of a phase at once: the row hop, which does
+so too -- except where the destination-tiled hop can run and is the faster one.  That one needs dense receive
+regions and data at least word-granular; for a schedule's last phase, whose blocks all go into R, blocks that are
+mostly interior (mean of 700 bytes or more, at most a quarter of them under 256 bytes); for the phases before it,
+which store whole chunks into T, a mean block of 512 bytes or more.  A plan, which has paid for its metadata, keeps
+it there; a call does for mean blocks above 4 KiB.  The copy engine's hop does everything else.  The statistics say
+which of the four ran, and under profiling a phase's tiled hop is timed as its unpack time and every other one as
+its pack time; every case is also compared with the CPU oracle byte for byte."""
 import numpy as np
 import pytest
 
@@ -27,8 +29,8 @@ def tuna():
     return t
 
 
-def _normal(seed=11):
-    return wl.counts_normal(P, seed, 1024.0, 256.0, 4)
+def _normal(seed=11, mean=1024.0):
+    return wl.counts_normal(P, seed, mean, mean / 4, 4)
 
 
 def _mostly_short():
@@ -39,25 +41,66 @@ def _mostly_short():
     return c
 
 
+def _zipf(longest):
+    c = wl.counts_zipf(P, 12, 1.2, min(longest, 65536), 4).copy()
+    c[5, 17] = longest
+    return c
+
+
+def _equal(n):
+    return np.full((P, P), n, dtype=np.int32)
+
+
+E, T, D, R = "engine", "tiled", "direct", "rows"
 CASES = {
-    # name: (counts, layout arguments, options, (tiled expected in the phases before the last, in the last)); None: three stages
-    "normal 1 KiB, dense": (_normal, {}, {}, (True, True)),
-    "normal 1 KiB, chunk-granular": (lambda: _normal() // 16 * 16, {"align": 16}, {}, (True, True)),
-    "gaps between the blocks of R": (_normal, {"gap": 8}, {}, (False, False)),
-    "byte-granular sizes": (lambda: _normal() + 1, {}, {}, (False, False)),
-    "Zipf sizes (most blocks tiny, mean 800 bytes)": (lambda: wl.counts_zipf(P, 12, 1.2, 16384, 4), {}, {}, (True, False)),
-    "mean block of 516 bytes": (lambda: np.full((P, P), 516, dtype=np.int32), {}, {}, (True, False)),
-    "mean block of 260 bytes": (lambda: np.full((P, P), 260, dtype=np.int32), {}, {}, (False, False)),
-    "two blocks in five short": (_mostly_short, {}, {}, (True, False)),
-    "rounds in batches": (_normal, {}, {"block_count": 3}, (False, False)),
-    "three-stage phases": (_normal, {}, {"mode": "staged"}, None),
+    # name: (counts, layout arguments, options, call: (kernel of the phases before the last, of the last), plan: likewise);
+    # None: three stages
+    "normal 1 KiB, dense": (_normal, {}, {}, (R, R), (T, T)),
+    "normal 1 KiB, chunk-granular": (lambda: _normal() // 16 * 16, {"align": 16}, {}, (R, R), (T, T)),
+    "normal 3.9 KiB, dense": (lambda: _normal(14, 3900.0), {}, {}, (R, R), (T, T)),
+    "normal 4.3 KiB, dense": (lambda: _normal(14, 4300.0), {}, {}, (T, T), (T, T)),
+    "gaps between the blocks of R": (_normal, {"gap": 8}, {}, (R, R), (R, R)),
+    "gaps, normal 4.3 KiB": (lambda: _normal(14, 4300.0), {"gap": 8}, {}, (R, R), (R, R)),
+    "byte-granular sizes": (lambda: _normal() + 1, {}, {}, (R, R), (R, R)),
+    "Zipf sizes (most blocks tiny, mean 800 bytes)": (lambda: _zipf(16384), {}, {}, (R, R), (T, R)),
+    "Zipf sizes, longest block 65536 bytes, gaps": (lambda: _zipf(65536), {"gap": 8}, {}, (R, R), (R, R)),
+    "Zipf sizes, longest block 65540 bytes, gaps": (lambda: _zipf(65540), {"gap": 8}, {}, (E, E), (E, E)),
+    "Zipf sizes, longest block 65540 bytes": (lambda: _zipf(65540), {}, {}, (T, E), (T, E)),
+    "mean block of 700 bytes": (lambda: _equal(700), {}, {}, (R, R), (T, T)),
+    "mean block of 696 bytes": (lambda: _equal(696), {}, {}, (R, R), (T, R)),
+    "mean block of 516 bytes": (lambda: _equal(516), {}, {}, (R, R), (T, R)),
+    "mean block of 508 bytes": (lambda: _equal(508), {}, {}, (R, R), (R, R)),
+    "mean block of 260 bytes": (lambda: _equal(260), {}, {}, (R, R), (R, R)),
+    "longest block 257 bytes": (lambda: _equal(257), {}, {}, (R, R), (R, R)),
+    "longest block 256 bytes": (lambda: _equal(256), {}, {}, (D, D), (D, D)),
+    "longest block 256 bytes, gaps": (lambda: _equal(256), {"gap": 3}, {}, (D, D), (D, D)),
+    "two blocks in five short": (_mostly_short, {}, {}, (R, R), (T, R)),
+    "rounds in batches": (_normal, {}, {"block_count": 3}, (E, E), (E, E)),
+    "rounds in batches, short blocks": (lambda: _equal(64), {}, {"block_count": 3}, (D, D), (D, D)),
+    "three-stage phases": (_normal, {}, {"mode": "staged"}, None, None),
 }
+
+
+def _check(tuna, name, want, n_phases):
+    st = tuna.tuna_get_stats()
+    assert st.n_phases == n_phases
+    bit = {E: tuna.TUNA_HOP_ENGINE, T: tuna.TUNA_HOP_TILED, D: tuna.TUNA_HOP_DIRECT, R: tuna.TUNA_HOP_ROWS}
+    kernels = [] if want is None else [want[1 if x + 1 == n_phases else 0] for x in range(n_phases)]
+    assert st.hop_kernels == sum(bit[k] for k in set(kernels)), (name, st.hop_kernels)
+    for x in range(n_phases):
+        ph = st.phase[x]
+        if want is None:                                    # pack, exchange and unpack all ran
+            assert ph.ms_pack > 0 and ph.ms_exchange > 0 and ph.ms_unpack > 0, (name, x)
+        elif kernels[x] == T:
+            assert ph.ms_unpack > 0 and ph.ms_pack == 0 and ph.ms_exchange == 0, (name, x)
+        else:
+            assert ph.ms_pack > 0 and ph.ms_unpack == 0 and ph.ms_exchange == 0, (name, x)
 
 
 @pytest.mark.parametrize("name", sorted(CASES))
 @pytest.mark.parametrize("radix", [4, P])
 def test_which_hop_runs(tuna, name, radix):
-    make, lay_args, opts, tiled = CASES[name]
+    make, lay_args, opts, call, plan_kernels = CASES[name]
     counts = np.ascontiguousarray(make(), dtype=np.int32)
     lay = wl.make_layout(counts, **lay_args)
     host = wl.payload_position_hash(21, lay.send_bytes)
@@ -72,18 +115,20 @@ def test_which_hop_runs(tuna, name, radix):
     o.t_layout = tuna.TUNA_T_EXACT
     o.mode = tuna.TUNA_MODE_STAGED if opts.get("mode") == "staged" else tuna.TUNA_MODE_FUSED
     o.block_count = opts.get("block_count", 0)
+    n_phases = 1 if radix == P else 4
     print("case %s, radix %d" % (name, radix), flush=True)
     rc = tuna.tuna_alltoallv_ex(None, send, meta[0], meta[1], recv, meta[2], meta[3], P, 0, radix, radix, o)
     assert rc == 0, tuna.tuna_strerror(rc)
     torch.cuda.synchronize()
     assert np.array_equal(recv.cpu().numpy(), want), name
-    st = tuna.tuna_get_stats()
-    assert st.n_phases == (1 if radix == P else 4)
-    for x in range(st.n_phases):
-        ph = st.phase[x]
-        if tiled is None:                                   # pack, exchange and unpack all ran
-            assert ph.ms_pack > 0 and ph.ms_exchange > 0 and ph.ms_unpack > 0, (name, x)
-        elif tiled[1 if x + 1 == st.n_phases else 0]:
-            assert ph.ms_unpack > 0 and ph.ms_pack == 0 and ph.ms_exchange == 0, (name, x)
-        else:
-            assert ph.ms_pack > 0 and ph.ms_unpack == 0 and ph.ms_exchange == 0, (name, x)
+    _check(tuna, name, call, n_phases)
+    rc, plan = tuna.tuna_alltoallv_init_ex(None, send, meta[0], meta[1], recv, meta[2], meta[3], P, 0, radix, radix, o)
+    assert rc == 0, tuna.tuna_strerror(rc)
+    try:
+        recv.fill_(CANARY)
+        assert tuna.tuna_start(plan) == 0
+        torch.cuda.synchronize()
+        assert np.array_equal(recv.cpu().numpy(), want), name + " (plan)"
+        _check(tuna, name + " (plan)", plan_kernels, n_phases)
+    finally:
+        assert tuna.tuna_plan_free(plan) == 0
