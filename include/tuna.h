@@ -139,9 +139,8 @@ typedef struct tuna_plan_info {
  *                   with local radix min(radix, Q) and global radix min(radix, N), N = P / Q.
  * The call validates the counts on the device, reads a few integers back (one stream
  * synchronisation), sizes or grows the workspace, then enqueues all phases on `stream` and
- * returns without waiting for them.  Payloads of 64 MiB and more with at least two digit phases and
- * blocks of more than 64 KiB (or more than 4 KiB on average, where the destination-tiled hop runs):
- * with one-kernel hops (the default) the block-size exchanges and scans of all phases run on a
+ * returns without waiting for them.  Payloads of 64 MiB and more with at least two digit phases whose
+ * blocks are not found by the kernels that move them (TUNA_HOP_ENGINE, TUNA_HOP_TILED): with one-kernel hops (the default) the block-size exchanges and scans of all phases run on a
  * second stream owned by the context while `stream` moves the payload, each phase's payload kernel
  * behind an event of its metadata; work enqueued on `stream` after the call is ordered behind all
  * of it as usual.  With three-stage phases, or when the call is profiled, such a call is done in two
@@ -184,8 +183,10 @@ int tuna_alltoallv_hier(const void* sendbuf, const int32_t* sendcounts, const in
  *                the mean block is 512 bytes or more; otherwise (and always for T in slots, batches of
  *                rounds and the staggered schedule) over the blocks.  Which of the two ran changes no byte.
  *                Phases whose blocks are all at most 64 KiB (and at most 4 KiB on average, where the rule above
- *                picks the tiling) run kernels that find the blocks themselves instead; a plan, which has paid for
- *                its metadata, keeps the tiling where the rule picks it.
+ *                picks the tiling) run kernels that find the blocks themselves instead, unless long blocks lie so
+ *                close together -- a receiver that gets most of the payload, a band of neighbours -- that work by
+ *                blocks would not balance; a plan, which has paid for its metadata, keeps the tiling where the rule
+ *                picks it.
  *                TUNA_MODE_STAGED: pack -> exchange -> unpack, the paper's three steps as three kernels.
  *                TUNA_MODE_FUSED: the one-kernel hops.
  *   staggered, t_layout, block_count, profile: as TUNA_OPT_STAGGERED, TUNA_OPT_DENSE_T,

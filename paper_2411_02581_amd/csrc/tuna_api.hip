@@ -531,13 +531,13 @@ int run_validate(const StatusBufs& sb, const int32_t* sendcounts, const int32_t*
         HIPCHK(hipStreamSynchronize(s));
         Status& h = *sb.h_status;
         unsigned long long fa = 0, m = 0;
-        h.total_bytes = h.total_chunks = h.send_extent = h.t_chunks = h.short_blocks = 0;
+        h.total_bytes = h.total_chunks = h.send_extent = h.t_chunks = h.short_blocks = h.windows = 0;
         for (int i = 0; i < ncls; ++i) h.cls_chunks[i] = 0;
         for (unsigned r = 0; r < vgrid; ++r) {
             const unsigned long long* o = sb.h_part + (size_t)r * (kValPartial + kValFoldClasses);
             fa |= o[0]; m = std::max(m, o[1]);
             h.total_bytes += o[2]; h.total_chunks += o[3]; h.send_extent = std::max(h.send_extent, o[4]);
-            h.t_chunks += o[5]; h.short_blocks += o[6];
+            h.t_chunks += o[5]; h.short_blocks += o[6]; h.windows = max_windows(h.windows, o[7]);
             for (int i = 0; i < ncls; ++i) h.cls_chunks[i] += o[kValPartial + i];
         }
         h.flags = (unsigned int)(fa >> 32); h.align_bits = (unsigned int)(fa & 127u); h.max_count = (int)m;
@@ -571,6 +571,7 @@ struct Prepared {
     unsigned long long user_limit = 0;
     int max_count = 0;
     unsigned long long total_bytes = 0;
+    unsigned long long windows = 0;     // Status.windows
     DataSizes ds{};
     v4u* stage_s = nullptr;
     v4u* stage_r = nullptr;
@@ -761,8 +762,35 @@ bool small_blocks(const Prepared& pr) { return pr.max_count > 0 && pr.max_count 
 // mean 3 KB 0.942 / 0.932 ms linear and 1.794 / 1.780 at r = 30, 6 KB 0.844 / 0.848 and 1.575 / 1.595, 10 KB at r = 2
 // 4.05 / 4.43).
 constexpr double kRowsMaxMeanBytes = 4096.0;
+int rows_segs(const Prepared& pr);
+// A wave of k_hop_rows takes a number of blocks that the mean gives: where long blocks lie side by side -- a receiver
+// that gets far more than the others, a band of neighbours -- a few waves move most of the payload, 8 KiB at a time
+// (64 KiB from each of 1024 ranks to one, per call and per start: 182 and 46 us with the engine's hop, 1185 and 1105 with
+// rows; 16 KiB to one 124 / 337; 16 KiB to 64 of them 505 / 603; 64 KiB to each of 16 neighbours 527 / 590, radix 4 and
+// 4 neighbours 0.73 / 2.09 ms).  What can lie side by side in a phase: a receiver's blocks from neighbouring senders,
+// and in a phase before the last also a sender's blocks for others.  Windows of 64 of them hold 1.3 times their mean with
+// uniform sizes, 2 to 3.6 times with Zipf sizes, and 4 times where rows were still as fast (256 ranks, 4 neighbours,
+// 104 / 100 us); everything above was 8 times and more.  (Long blocks of one sender that are as far apart as the radix
+// meet in the first phase without showing in a window: 16 KiB at every 32nd distance, r = 32, 587 / 833 us.)
+// The longest wave alone takes about 1.5 us per 8 KiB, and it can start late.  A call has 40 us and more to spare, what the
+// engine's metadata kernels take: 1 KiB from each of 1024 ranks to one 109 / 74 us, 64 KiB from one to each 109 / 91, Zipf
+// sizes up to 16 KiB among 96 ranks (103 KiB in one wave) 78 / 53, up to 64 KiB among 256 129 / 109.  A plan has those
+// behind it: 64 KiB to one rank 21.1 / 24.8 us, Zipf sizes up to 16 KiB among 96 ranks 10.0 / 13.3, up to 64 KiB among 256
+// (150 MB) 60 / 67 and among 512 (630 MB) 258 / 265, up to 16 KiB among 1024 (870 MB) 359 / 344; byte-granular ones, which
+// cost the engine more, up to 64 KiB among 512 (460 MB) 239 / 212, up to 16 KiB among 256 (39 MB, r = 8) 60 / 70.
+constexpr double kRowsMaxWindow = 6.0;
+bool rows_balanced(const Prepared& pr) {
+    const double total = (double)pr.total_bytes, mean = total / ((double)pr.P * (double)pr.P);
+    double window = (double)(pr.windows >> 32);
+    if (pr.dp->host.phases.size() > 1) window = std::max(window, (double)(pr.windows & 0xffffffffull));
+    const double longest = std::min(window, (double)rows_segs(pr) * (double)pr.max_count);
+    const bool even = window <= kRowsMaxWindow * mean * (double)std::min(pr.P, kValTile);
+    if (pr.for_plan) return longest <= 24576.0 + (even ? total / (pr.gran < 4 ? 1600.0 : 6144.0) : 0.0);
+    return longest <= (even ? 196608.0 + total / 512.0 : 81920.0);
+}
 bool row_blocks(const Prepared& pr) {
     if (pr.max_count <= kDirectMaxBytes || pr.max_count > kRowsMaxBytes || !pr.fused || pr.staggered || pr.block_count > 0) return false;
+    if (!rows_balanced(pr)) return false;
     return !pr.tiled || (double)pr.total_bytes <= kRowsMaxMeanBytes * (double)pr.P * (double)pr.P;
 }
 constexpr int kTiledMinMeanBytes = 700;    // see prepare_sizes
@@ -794,6 +822,7 @@ int prepare_sizes(Prepared& pr, int dense_option, hipStream_t s, Status& hs, boo
     pr.gran = (abits & 127u) == 0 ? 128 : ((abits & 15u) == 0 ? 16 : ((abits & 3u) == 0 ? 4 : 1));
     pr.max_count = hs.max_count;
     pr.total_bytes = hs.total_bytes;
+    pr.windows = hs.windows;
     pr.user_limit = (unsigned long long)(uintptr_t)pr.sendbuf + hs.send_extent;
     // The destination-tiled hop: one-kernel phases over all rounds at once, receive regions dense (validation
     // flag), word- or chunk-granular data (whole-line data is as fast in the copy engine, byte-granular data

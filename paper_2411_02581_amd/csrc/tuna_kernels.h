@@ -49,6 +49,8 @@ struct Status {
     unsigned long long send_extent;    // max over non-empty blocks of sdispls + count: bytes of sendbuf that hold blocks
     unsigned long long t_chunks;       // exact-size T: chunks stored into T over all phases
     unsigned long long short_blocks;   // blocks of fewer than kShortBlockBytes bytes, empty ones included
+    unsigned long long windows;        // most bytes that one receiver gets from kValTile aligned neighbouring senders (high half)
+                                       // and one sender sends to as many receivers (low half); blocks count up to kWindowBlock
     unsigned long long cls_chunks[kMaxClasses];   // exact-size T: chunks of every class (f, y), summed by the validation pass
     unsigned long long phase_bytes[64];   // payload bytes moved per phase
     unsigned long long phase_chunks[64];  // staged chunks per phase
@@ -225,12 +227,20 @@ __global__ void __launch_bounds__(256) k_build_hops(const PlanScalars pl, int32_
 // With `cls_rows` (few workgroups) the partial rows, class sums included, lie in pinned host memory and the host adds
 // them up: no kernel to clear the sums, none to fold the rows, no copy of the result (see run_validate; P = 256, r = 4
 // 138 -> 117 us per call with the above).
+// The first two waves also sum the tile's columns and rows; the largest sums say whether long blocks lie side by side
+// (rows_balanced).
 // ------------------------------------------------------------------------------------------
 constexpr int kValTile = 64;
 constexpr int kValPartial = 8;              // 64-bit words per workgroup in the partial-result array
 constexpr int kValCopies = 32;
 constexpr int kValFoldRows = 64, kValFoldClasses = 24;      // most workgroups and classes that the host folds
 constexpr int kShortBlockBytes = 256;       // below this a block is mostly edges to the destination-tiled hop
+constexpr int kWindowBlock = 1 << 25;       // kValTile of them fit 32 bits
+// the larger ones of two pairs of sums (Status.windows)
+__host__ __device__ inline unsigned long long max_windows(unsigned long long a, unsigned long long b) {
+    const unsigned long long low = 0xffffffffull, ar = a >> 32, br = b >> 32, as = a & low, bs = b & low;
+    return (ar > br ? ar : br) << 32 | (as > bs ? as : bs);
+}
 __global__ void __launch_bounds__(1024) k_validate(const int32_t* __restrict__ sendcounts,
                                                    const int32_t* __restrict__ recvcounts,
                                                    const int64_t* __restrict__ sdispls,
@@ -240,12 +250,13 @@ __global__ void __launch_bounds__(1024) k_validate(const int32_t* __restrict__ s
                                                    const unsigned long long* __restrict__ mask, int nph,
                                                    Status* __restrict__ st, int cls_rows, int copies, int clear_totals) {
     __shared__ int tile[kValTile][kValTile + 1];
-    __shared__ unsigned long long red[16][7];
+    __shared__ unsigned long long red[16][8];
     extern __shared__ unsigned long long lcls[];          // class_count(nph) sums of this workgroup, `copies` of each (with `mask`)
     const int tx = threadIdx.x, ty = threadIdx.y, ny = blockDim.y;
     const int ncls = mask ? class_count(nph) : 0;
     for (int i = ty * kValTile + tx; i < ncls * copies; i += ny * kValTile) lcls[i] = 0;
     __syncthreads();
+    unsigned int window = 0;                              // largest sum of a column (first wave) or row (second wave)
     const int tpr = (P + kValTile - 1) / kValTile;       // tiles per row
     const int ntile = tpr * tpr;
     unsigned int flags = 0, abits = 0;
@@ -329,6 +340,14 @@ __global__ void __launch_bounds__(1024) k_validate(const int32_t* __restrict__ s
                     // the last lane of a row reads its successor's displacement itself (below)
                     dx[u] = (rdispls && tx == kValTile - 1 && in[u] && i + 1 < P) ? rdispls[idx + 1] : 0;
                 }
+                if (a0 == ty && ty < 2) {                 // under the first loads: bytes of receiver j from the tile's senders, of sender bi + tx
+                    const int* entry = ty == 0 ? &tile[0][tx] : &tile[tx][0];
+                    const int step = ty == 0 ? kValTile + 1 : 1;
+                    unsigned int sum = 0;
+#pragma unroll 16
+                    for (int a = 0; a < kValTile; ++a) sum += (unsigned int)min(entry[a * step], kWindowBlock);
+                    window = max(window, sum);
+                }
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const int a = a0 + ny * u;
@@ -369,23 +388,34 @@ __global__ void __launch_bounds__(1024) k_validate(const int32_t* __restrict__ s
         tchunks += __shfl_xor(tchunks, d, kWave);
         shortb += __shfl_xor(shortb, d, kWave);
         extent = max(extent, (unsigned long long)__shfl_xor(extent, d, kWave));
+        window = max(window, __shfl_xor(window, d, kWave));
     }
     if (tx == 0) {                                       // one wave per value of ty
         unsigned long long* r = red[ty];
         r[0] = ((unsigned long long)flags << 32) | (abits & 127u);
-        r[1] = (unsigned long long)mx; r[2] = bytes; r[3] = chunks; r[4] = extent; r[5] = tchunks; r[6] = shortb;
+        r[1] = (unsigned long long)mx; r[2] = bytes; r[3] = chunks; r[4] = extent; r[5] = tchunks; r[6] = shortb; r[7] = window;
     }
     __syncthreads();
     unsigned long long* o = partial + (size_t)blockIdx.x * (cls_rows ? kValPartial + kValFoldClasses : kValPartial);
-    if (tx == 0 && ty == 0) {
-        unsigned long long fa = 0, m = 0, by = 0, ch = 0, ex = 0, tc = 0, sb = 0;
-        for (int w = 0; w < ny; ++w) {
-            fa |= red[w][0]; m = max(m, red[w][1]); by += red[w][2]; ch += red[w][3]; ex = max(ex, red[w][4]);
-            tc += red[w][5]; sb += red[w][6];
+    if (ty == 0) {                                        // one lane per wave's row: sixteen rows one after the other took 1 us more
+        const unsigned long long* r = red[min(tx, ny - 1)];
+        const bool in = tx < ny;
+        unsigned long long fa = in ? r[0] : 0, m = in ? r[1] : 0, by = in ? r[2] : 0, ch = in ? r[3] : 0, ex = in ? r[4] : 0;
+        unsigned long long tc = in ? r[5] : 0, sb = in ? r[6] : 0;
+        const unsigned long long wi = red[0][7] << 32 | red[1][7];
+#pragma unroll
+        for (int d = 8; d > 0; d >>= 1) {
+            fa |= __shfl_xor(fa, d, kWave);
+            m = max(m, (unsigned long long)__shfl_xor(m, d, kWave));
+            by += __shfl_xor(by, d, kWave);
+            ch += __shfl_xor(ch, d, kWave);
+            ex = max(ex, (unsigned long long)__shfl_xor(ex, d, kWave));
+            tc += __shfl_xor(tc, d, kWave);
+            sb += __shfl_xor(sb, d, kWave);
         }
         // one row of partial results per workgroup, folded by k_validate_finish or the host: thousands of atomics
         // on the same few addresses would take longer than reading the matrices
-        o[0] = fa; o[1] = m; o[2] = by; o[3] = ch; o[4] = ex; o[5] = tc; o[6] = sb;
+        if (tx == 0) { o[0] = fa; o[1] = m; o[2] = by; o[3] = ch; o[4] = ex; o[5] = tc; o[6] = sb; o[7] = wi; }
     }
     // the class sums: in the row, or one atomic per class and workgroup that holds any of it (cls_chunks starts at zero)
     for (int i = ty * kValTile + tx; i < ncls; i += ny * kValTile) {
@@ -408,11 +438,12 @@ __global__ void __launch_bounds__(256) k_zero64(unsigned long long* __restrict__
 // k_validate_finish: folds the workgroups' partial results into the status block (one workgroup).
 __global__ void __launch_bounds__(256) k_validate_finish(const unsigned long long* __restrict__ partial, int n,
                                                          Status* __restrict__ st, int clear_totals) {
-    __shared__ unsigned long long red[4][7];
-    unsigned long long fa = 0, m = 0, by = 0, ch = 0, ex = 0, tc = 0, sb = 0;
+    __shared__ unsigned long long red[4][8];
+    unsigned long long fa = 0, m = 0, by = 0, ch = 0, ex = 0, tc = 0, sb = 0, wi = 0;
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
         const unsigned long long* o = partial + (size_t)i * kValPartial;
         fa |= o[0]; m = max(m, o[1]); by += o[2]; ch += o[3]; ex = max(ex, o[4]); tc += o[5]; sb += o[6];
+        wi = max_windows(wi, o[7]);
     }
 #pragma unroll
     for (int d = kWave / 2; d > 0; d >>= 1) {
@@ -423,15 +454,16 @@ __global__ void __launch_bounds__(256) k_validate_finish(const unsigned long lon
         ex = max(ex, (unsigned long long)__shfl_xor(ex, d, kWave));
         tc += __shfl_xor(tc, d, kWave);
         sb += __shfl_xor(sb, d, kWave);
+        wi = max_windows(wi, __shfl_xor(wi, d, kWave));
     }
     const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-    if (lane == 0) { red[wv][0] = fa; red[wv][1] = m; red[wv][2] = by; red[wv][3] = ch; red[wv][4] = ex; red[wv][5] = tc; red[wv][6] = sb; }
+    if (lane == 0) { red[wv][0] = fa; red[wv][1] = m; red[wv][2] = by; red[wv][3] = ch; red[wv][4] = ex; red[wv][5] = tc; red[wv][6] = sb; red[wv][7] = wi; }
     __syncthreads();
     if (threadIdx.x == 0) {
-        fa = m = by = ch = ex = tc = sb = 0;
+        fa = m = by = ch = ex = tc = sb = wi = 0;
         for (int w = 0; w < 4; ++w) {
             fa |= red[w][0]; m = max(m, red[w][1]); by += red[w][2]; ch += red[w][3]; ex = max(ex, red[w][4]);
-            tc += red[w][5]; sb += red[w][6];
+            tc += red[w][5]; sb += red[w][6]; wi = max_windows(wi, red[w][7]);
         }
         st->flags = (unsigned int)(fa >> 32);
         st->align_bits = (unsigned int)(fa & 127u);
@@ -441,6 +473,7 @@ __global__ void __launch_bounds__(256) k_validate_finish(const unsigned long lon
         st->send_extent = ex;
         st->t_chunks = tc;
         st->short_blocks = sb;
+        st->windows = wi;
     }
     // the totals that k_phase_sums adds to; the other paths write them whole
     if (clear_totals && threadIdx.x < 64) st->phase_bytes[threadIdx.x] = st->phase_chunks[threadIdx.x] = 0;

@@ -4,7 +4,8 @@ so too -- except where the destination-tiled hop can run and is the faster one. 
 regions and data at least word-granular; for a schedule's last phase, whose blocks all go into R, blocks that are
 mostly interior (mean of 700 bytes or more, at most a quarter of them under 256 bytes); for the phases before it,
 which store whole chunks into T, a mean block of 512 bytes or more.  A plan, which has paid for its metadata, keeps
-it there; a call does for mean blocks above 4 KiB.  The copy engine's hop does everything else.  The statistics say
+it there; a call does for mean blocks above 4 KiB.  The copy engine's hop does everything else, also where long
+blocks lie side by side, so that a few waves of the row hop would move most of the payload.  The statistics say
 which of the four ran, and under profiling a phase's tiled hop is timed as its unpack time and every other one as
 its pack time; every case is also compared with the CPU oracle byte for byte."""
 import numpy as np
@@ -51,10 +52,18 @@ def _equal(n):
     return np.full((P, P), n, dtype=np.int32)
 
 
+def _except(n, rest):
+    """Blocks of `rest` bytes, and of n where the sender and the receiver say so."""
+    def make(where):
+        i = np.arange(P)
+        return np.where(np.broadcast_to(where(i[:, None], i[None, :]), (P, P)), n, rest).astype(np.int32)
+    return make
+
+
 E, T, D, R = "engine", "tiled", "direct", "rows"
 CASES = {
-    # name: (counts, layout arguments, options, call: (kernel of the phases before the last, of the last), plan: likewise);
-    # None: three stages
+    # name: (counts, layout arguments, options, call: (kernel of the phases before the last, of the last[, of the only
+    # phase of a linear schedule, where it is another one]), plan: likewise); None: three stages
     "normal 1 KiB, dense": (_normal, {}, {}, (R, R), (T, T)),
     "normal 1 KiB, chunk-granular": (lambda: _normal() // 16 * 16, {"align": 16}, {}, (R, R), (T, T)),
     "normal 3.9 KiB, dense": (lambda: _normal(14, 3900.0), {}, {}, (R, R), (T, T)),
@@ -62,8 +71,8 @@ CASES = {
     "gaps between the blocks of R": (_normal, {"gap": 8}, {}, (R, R), (R, R)),
     "gaps, normal 4.3 KiB": (lambda: _normal(14, 4300.0), {"gap": 8}, {}, (R, R), (R, R)),
     "byte-granular sizes": (lambda: _normal() + 1, {}, {}, (R, R), (R, R)),
-    "Zipf sizes (most blocks tiny, mean 800 bytes)": (lambda: _zipf(16384), {}, {}, (R, R), (T, R)),
-    "Zipf sizes, longest block 65536 bytes, gaps": (lambda: _zipf(65536), {"gap": 8}, {}, (R, R), (R, R)),
+    "Zipf sizes (most blocks tiny, mean 800 bytes)": (lambda: _zipf(16384), {}, {}, (R, R), (T, E)),
+    "Zipf sizes, longest block 65536 bytes, gaps": (lambda: _zipf(65536), {"gap": 8}, {}, (R, R), (E, E)),
     "Zipf sizes, longest block 65540 bytes, gaps": (lambda: _zipf(65540), {"gap": 8}, {}, (E, E), (E, E)),
     "Zipf sizes, longest block 65540 bytes": (lambda: _zipf(65540), {}, {}, (T, E), (T, E)),
     "mean block of 700 bytes": (lambda: _equal(700), {}, {}, (R, R), (T, T)),
@@ -75,6 +84,13 @@ CASES = {
     "longest block 256 bytes": (lambda: _equal(256), {}, {}, (D, D), (D, D)),
     "longest block 256 bytes, gaps": (lambda: _equal(256), {"gap": 3}, {}, (D, D), (D, D)),
     "two blocks in five short": (_mostly_short, {}, {}, (R, R), (T, R)),
+    "64 KiB to one rank, gaps": (lambda: _except(65536, 40)(lambda s, r: r == 7), {"gap": 8}, {}, (E, E), (E, E)),
+    "64 KiB to one rank": (lambda: _except(65536, 40)(lambda s, r: r == 7), {}, {}, (T, E), (T, E)),
+    "1 KiB to one rank": (lambda: _except(1024, 40)(lambda s, r: r == 7), {}, {}, (R, R), (E, E)),
+    "300 bytes to one rank": (lambda: _except(300, 40)(lambda s, r: r == 7), {}, {}, (R, R), (R, R)),
+    "64 KiB from one rank": (lambda: _except(65536, 40)(lambda s, r: s == 7), {"gap": 8}, {}, (E, E, R), (E, E)),
+    "16 KiB among eight ranks": (lambda: _except(16384, 40)(lambda s, r: (s < 8) & (r < 8)), {}, {}, (E, E), (E, E)),
+    "one block of 64 KiB among tiny ones": (lambda: _except(65536, 40)(lambda s, r: (s == 7) & (r == 9)), {}, {}, (R, R), (E, E)),
     "rounds in batches": (_normal, {}, {"block_count": 3}, (E, E), (E, E)),
     "rounds in batches, short blocks": (lambda: _equal(64), {}, {"block_count": 3}, (D, D), (D, D)),
     "three-stage phases": (_normal, {}, {"mode": "staged"}, None, None),
@@ -85,7 +101,7 @@ def _check(tuna, name, want, n_phases):
     st = tuna.tuna_get_stats()
     assert st.n_phases == n_phases
     bit = {E: tuna.TUNA_HOP_ENGINE, T: tuna.TUNA_HOP_TILED, D: tuna.TUNA_HOP_DIRECT, R: tuna.TUNA_HOP_ROWS}
-    kernels = [] if want is None else [want[1 if x + 1 == n_phases else 0] for x in range(n_phases)]
+    kernels = [] if want is None else [want[-1]] if n_phases == 1 else [want[0]] * (n_phases - 1) + [want[1]]
     assert st.hop_kernels == sum(bit[k] for k in set(kernels)), (name, st.hop_kernels)
     for x in range(n_phases):
         ph = st.phase[x]
