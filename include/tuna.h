@@ -182,8 +182,8 @@ int tuna_alltoallv_hier(const void* sendbuf, const int32_t* sendcounts, const in
  *                before it (which store whole 16-byte chunks into T) when T is kept in exact size and
  *                the mean block is 512 bytes or more; otherwise (and always for T in slots, batches of
  *                rounds and the staggered schedule) over the blocks.  Which of the two ran changes no byte.
- *                Phases whose blocks are all at most 64 KiB (and at most 4 KiB on average, where the rule above
- *                picks the tiling) run kernels that find the blocks themselves instead, unless long blocks lie so
+ *                Phases whose blocks are all at most 64 KiB (and, where the rule above picks the tiling, at most 1.5 KiB
+ *                on average, 4 KiB with payloads of up to 256 MiB) run kernels that find the blocks themselves instead, unless long blocks lie so
  *                close together -- a receiver that gets most of the payload, a band of neighbours -- that work by
  *                blocks would not balance; a plan, which has paid for its metadata, keeps the tiling where the rule
  *                picks it.

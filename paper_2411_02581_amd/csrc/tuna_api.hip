@@ -756,13 +756,28 @@ bool too_large(int P, const Status& hs) {
 // lanes move it) instead of the byte-balanced engine.
 bool small_blocks(const Prepared& pr) { return pr.max_count > 0 && pr.max_count <= kDirectMaxBytes; }
 
-// The other calls and plans whose phases are all one-kernel hops over all rounds at once run k_hop_rows, unless a block
-// can be so long that waves of whole blocks would not balance, or the destination-tiled hop can run and blocks are long
-// on average: there its metadata costs little and its units are all full (normal sizes, per call, tiled against rows:
-// mean 3 KB 0.942 / 0.932 ms linear and 1.794 / 1.780 at r = 30, 6 KB 0.844 / 0.848 and 1.575 / 1.595, 10 KB at r = 2
-// 4.05 / 4.43).
-constexpr double kRowsMaxMeanBytes = 4096.0;
 int rows_segs(const Prepared& pr);
+constexpr double kRowsEvenBytes = 24576.0;      // a wave of k_hop_rows with no more is done in three steps
+
+// The other calls and plans whose phases are all one-kernel hops over all rounds at once run k_hop_rows, unless a block
+// can be so long that waves of whole blocks would not balance, long blocks lie side by side (rows_balanced), or the
+// destination-tiled hop can run and its metadata costs less than what its full units gain (rows_mean_limit).
+// That metadata goes with the blocks and the launches: it is worth saving for short blocks, and up to longer ones where
+// the payload is small.  Normal sizes, per call, tiled against rows: 1 KiB, P = 2048, r = 8 5.39 / 5.23 ms, 1.5 KiB 7.69 /
+// 7.84, 1.8 KiB 9.08 / 9.56; P = 1024 (2.5 to 4 GB), r = 8, 2.4 KiB 2.99 / 3.08, 3.6 KiB 4.31 / 4.62, r = 2 6.99 / 7.39;
+// P = 512 (630 to 940 MB), r = 8, 2.4 KiB 0.74 / 0.68, 3.2 KiB 0.92 / 0.87, r = 2, 3.6 KiB 1.76 / 1.83; P = 256 (240 MB),
+// r = 4, 3.6 KiB 0.40 / 0.34.  Above half of kRowsBytes a wave has one block and half-empty lanes.
+// Where some phases could not be tiled (many short blocks in the last one, T in slots) rows are the faster ones throughout
+// up to 4 KiB, in plans too, while waves are even (every other block empty, the others 4092 bytes, P = 1024: per call 936 /
+// 855 us, r = 16 2.27 / 2.15 ms, per start 841 / 786 us), not where a wave can meet several long blocks (Zipf sizes up to
+// 64 KiB, P = 1024: per call 1.07 / 1.09 ms, r = 32 1.95 / 2.04, per start 0.98 / 1.00).
+double rows_mean_limit(const Prepared& pr) {
+    if (!pr.tiled) return HUGE_VAL;
+    const bool all_tiled = pr.tiled_final && (pr.exact_t || pr.dp->host.phases.size() == 1);
+    if (!all_tiled && (double)rows_segs(pr) * (double)pr.max_count <= kRowsEvenBytes) return 4096.0;
+    if (pr.for_plan || pr.total_bytes > (1ull << 30)) return 1536.0;
+    return pr.total_bytes > (256ull << 20) ? kRowsBytes / 2 : 4096.0;
+}
 // A wave of k_hop_rows takes a number of blocks that the mean gives: where long blocks lie side by side -- a receiver
 // that gets far more than the others, a band of neighbours -- a few waves move most of the payload, 8 KiB at a time
 // (64 KiB from each of 1024 ranks to one, per call and per start: 182 and 46 us with the engine's hop, 1185 and 1105 with
@@ -785,13 +800,13 @@ bool rows_balanced(const Prepared& pr) {
     if (pr.dp->host.phases.size() > 1) window = std::max(window, (double)(pr.windows & 0xffffffffull));
     const double longest = std::min(window, (double)rows_segs(pr) * (double)pr.max_count);
     const bool even = window <= kRowsMaxWindow * mean * (double)std::min(pr.P, kValTile);
-    if (pr.for_plan) return longest <= 24576.0 + (even ? total / (pr.gran < 4 ? 1600.0 : 6144.0) : 0.0);
+    if (pr.for_plan) return longest <= kRowsEvenBytes + (even ? total / (pr.gran < 4 ? 1600.0 : 6144.0) : 0.0);
     return longest <= (even ? 196608.0 + total / 512.0 : 81920.0);
 }
 bool row_blocks(const Prepared& pr) {
     if (pr.max_count <= kDirectMaxBytes || pr.max_count > kRowsMaxBytes || !pr.fused || pr.staggered || pr.block_count > 0) return false;
     if (!rows_balanced(pr)) return false;
-    return !pr.tiled || (double)pr.total_bytes <= kRowsMaxMeanBytes * (double)pr.P * (double)pr.P;
+    return (double)pr.total_bytes <= rows_mean_limit(pr) * (double)pr.P * (double)pr.P;
 }
 constexpr int kTiledMinMeanBytes = 700;    // see prepare_sizes
 constexpr int kTiledMinMeanBytesIntoT = 512;

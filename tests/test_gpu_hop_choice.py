@@ -4,7 +4,8 @@ so too -- except where the destination-tiled hop can run and is the faster one. 
 regions and data at least word-granular; for a schedule's last phase, whose blocks all go into R, blocks that are
 mostly interior (mean of 700 bytes or more, at most a quarter of them under 256 bytes); for the phases before it,
 which store whole chunks into T, a mean block of 512 bytes or more.  A plan, which has paid for its metadata, keeps
-it there; a call does for mean blocks above 4 KiB.  The copy engine's hop does everything else, also where long
+it there; a call does for mean blocks above 4 KiB, 3.5 KiB or 1.5 KiB, by its payload (256 MiB, 1 GiB), where it can
+run in every phase.  The copy engine's hop does everything else, also where long
 blocks lie side by side, so that a few waves of the row hop would move most of the payload.  The statistics say
 which of the four ran, and under profiling a phase's tiled hop is timed as its unpack time and every other one as
 its pack time; every case is also compared with the CPU oracle byte for byte."""
@@ -68,6 +69,7 @@ CASES = {
     "normal 1 KiB, chunk-granular": (lambda: _normal() // 16 * 16, {"align": 16}, {}, (R, R), (T, T)),
     "normal 3.9 KiB, dense": (lambda: _normal(14, 3900.0), {}, {}, (R, R), (T, T)),
     "normal 4.3 KiB, dense": (lambda: _normal(14, 4300.0), {}, {}, (T, T), (T, T)),
+    "every other block empty, the others 4 KiB": (lambda: _except(4092, 0)(lambda s, r: (s + r) % 2 == 0), {}, {}, (R, R), (T, R)),
     "gaps between the blocks of R": (_normal, {"gap": 8}, {}, (R, R), (R, R)),
     "gaps, normal 4.3 KiB": (lambda: _normal(14, 4300.0), {"gap": 8}, {}, (R, R), (R, R)),
     "byte-granular sizes": (lambda: _normal() + 1, {}, {}, (R, R), (R, R)),
@@ -148,3 +150,45 @@ def test_which_hop_runs(tuna, name, radix):
         _check(tuna, name + " (plan)", plan_kernels, n_phases)
     finally:
         assert tuna.tuna_plan_free(plan) == 0
+
+
+def _device_problem(P, counts, gap=0):
+    """A problem too large for the oracle's test time: its payload is made on the device, its reference is the call with
+    three-stage phases (another set of kernels)."""
+    dev = "cuda:0"
+    lay = wl.make_layout(np.ascontiguousarray(counts, dtype=np.int32), gap=gap)
+    meta = [torch.from_numpy(a).to(dev) for a in (lay.sendcounts, lay.sdispls, lay.recvcounts, lay.rdispls)]
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(P)
+    send = torch.empty((lay.send_bytes + 7) // 8, dtype=torch.int64, device=dev).random_(generator=gen)
+    recv = torch.zeros((lay.recv_bytes + 7) // 8, dtype=torch.int64, device=dev)
+    return lay, send, meta, recv
+
+
+def _half(P, n):
+    i = np.arange(P)
+    return np.where((i[:, None] + i[None, :]) % 2 == 0, n, 0).astype(np.int32)
+
+
+# (a negative radix: every other block is empty, so that the last phase cannot be tiled)
+@pytest.mark.parametrize("P,mean,radix,want", [(320, 3300, 8, R), (320, 3700, 8, T), (640, 2400, 8, R), (640, 2800, 640, T),
+                                               (1024, 1400, 16, R), (1024, 1650, 16, T), (1024, 1700, -16, R)])
+def test_hop_of_a_call_by_payload(tuna, P, mean, radix, want):
+    counts = wl.counts_normal(P, P + mean, float(mean), mean / 4.0, 4) if radix > 0 else _half(P, 2 * mean)
+    radix = abs(radix)
+    lay, send, meta, recv = _device_problem(P, counts)
+    print("hop by payload", P, mean, radix, lay.payload_bytes, flush=True)
+    results = []
+    for mode in (tuna.TUNA_MODE_STAGED, tuna.TUNA_MODE_FUSED):
+        o = tuna.tuna_opts_init()
+        o.mode, o.t_layout = mode, tuna.TUNA_T_EXACT
+        recv.zero_()
+        rc = tuna.tuna_alltoallv_ex(None, send, meta[0], meta[1], recv, meta[2], meta[3], P, 0, radix, radix, o)
+        assert rc == 0, tuna.tuna_strerror(rc)
+        torch.cuda.synchronize()
+        results.append(recv.clone())
+        st = tuna.tuna_get_stats()
+    assert torch.equal(*results)
+    assert st.hop_kernels == {R: tuna.TUNA_HOP_ROWS, T: tuna.TUNA_HOP_TILED}[want], st.hop_kernels
+    del results
+    tuna.tuna_release()
