@@ -182,11 +182,13 @@ int tuna_alltoallv_hier(const void* sendbuf, const int32_t* sendcounts, const in
  *                before it (which store whole 16-byte chunks into T) when T is kept in exact size and
  *                the mean block is 512 bytes or more; otherwise (and always for T in slots, batches of
  *                rounds and the staggered schedule) over the blocks.  Which of the two ran changes no byte.
- *                Phases whose blocks are all at most 64 KiB (and, where the rule above picks the tiling, at most 1.5 KiB
- *                on average, 4 KiB with payloads of up to 256 MiB) run kernels that find the blocks themselves instead, unless long blocks lie so
- *                close together -- a receiver that gets most of the payload, a band of neighbours -- that work by
- *                blocks would not balance; a plan, which has paid for its metadata, keeps the tiling where the rule
- *                picks it.
+ *                Phases whose blocks are all at most 64 KiB run kernels that find the blocks themselves instead,
+ *                except where the tiling runs and the blocks are long on average (1.5 KiB and more with payloads
+ *                above 1 GiB, 3.5 KiB above 256 MiB, else 4 KiB; a plan, which has paid for its metadata, keeps the
+ *                tiling throughout), where all are whole 128-byte lines and long (16 KiB on average; in a plan one
+ *                above 12 KiB), and where long blocks lie so close together -- a receiver that gets most of the
+ *                payload, a band of neighbours -- that work by blocks would not balance.
+ *                tuna_stats_t.hop_kernels says which kernels ran.
  *                TUNA_MODE_STAGED: pack -> exchange -> unpack, the paper's three steps as three kernels.
  *                TUNA_MODE_FUSED: the one-kernel hops.
  *   staggered, t_layout, block_count, profile: as TUNA_OPT_STAGGERED, TUNA_OPT_DENSE_T,

@@ -761,7 +761,8 @@ constexpr double kRowsEvenBytes = 24576.0;      // a wave of k_hop_rows with no 
 
 // The other calls and plans whose phases are all one-kernel hops over all rounds at once run k_hop_rows, unless a block
 // can be so long that waves of whole blocks would not balance, long blocks lie side by side (rows_balanced), or the
-// destination-tiled hop can run and its metadata costs less than what its full units gain (rows_mean_limit).
+// destination-tiled hop can run, or the engine's on whole lines, and its metadata costs less than what its full units
+// gain (rows_mean_limit).
 // That metadata goes with the blocks and the launches: it is worth saving for short blocks, and up to longer ones where
 // the payload is small.  Normal sizes, per call, tiled against rows: 1 KiB, P = 2048, r = 8 5.39 / 5.23 ms, 1.5 KiB 7.69 /
 // 7.84, 1.8 KiB 9.08 / 9.56; P = 1024 (2.5 to 4 GB), r = 8, 2.4 KiB 2.99 / 3.08, 3.6 KiB 4.31 / 4.62, r = 2 6.99 / 7.39;
@@ -771,9 +772,17 @@ constexpr double kRowsEvenBytes = 24576.0;      // a wave of k_hop_rows with no 
 // up to 4 KiB, in plans too, while waves are even (every other block empty, the others 4092 bytes, P = 1024: per call 936 /
 // 855 us, r = 16 2.27 / 2.15 ms, per start 841 / 786 us), not where a wave can meet several long blocks (Zipf sizes up to
 // 64 KiB, P = 1024: per call 1.07 / 1.09 ms, r = 32 1.95 / 2.04, per start 0.98 / 1.00).
+// Whole lines: no block has edge pieces, so the engine's hop loses nothing at them, and long blocks are its full units
+// (engine / rows, per call: equal blocks of 12 KiB, P = 512 1.29 / 1.21 ms, 16 KiB 1.60 / 1.60, 32 KiB 3.22 / 3.34, normal 14 KB
+// 1.41 / 1.41, 20 KB 1.99 / 2.05, uniform up to 64 KiB, P = 256 0.85 / 0.90; per start: 12 KiB 1.20 / 1.16, 16 KiB 1.53 / 1.58,
+// normal 10 KB 0.935 / 0.942, 14 KB 1.33 / 1.37, 20 KB 1.91 / 2.00, every other block empty, the others 16 KiB 0.78 / 0.81).
+// A plan's line lies at the longest block, a call's, whose metadata evens the two out longer, at the mean.  T in slots costs the
+// engine more than that (equal blocks of 32 KiB, P = 256, r = 16: per call 1.67 / 1.58 ms, per start 1.56 / 1.53).
 double rows_mean_limit(const Prepared& pr) {
+    const bool one_layout = pr.exact_t || pr.dp->host.phases.size() == 1;       // no phase stores into slots
+    if (pr.gran == 128) return !one_layout ? HUGE_VAL : !pr.for_plan ? 16384.0 : pr.max_count <= 12288 ? HUGE_VAL : 0.0;
     if (!pr.tiled) return HUGE_VAL;
-    const bool all_tiled = pr.tiled_final && (pr.exact_t || pr.dp->host.phases.size() == 1);
+    const bool all_tiled = pr.tiled_final && one_layout;
     if (!all_tiled && (double)rows_segs(pr) * (double)pr.max_count <= kRowsEvenBytes) return 4096.0;
     if (pr.for_plan || pr.total_bytes > (1ull << 30)) return 1536.0;
     return pr.total_bytes > (256ull << 20) ? kRowsBytes / 2 : 4096.0;

@@ -5,10 +5,11 @@ regions and data at least word-granular; for a schedule's last phase, whose bloc
 mostly interior (mean of 700 bytes or more, at most a quarter of them under 256 bytes); for the phases before it,
 which store whole chunks into T, a mean block of 512 bytes or more.  A plan, which has paid for its metadata, keeps
 it there; a call does for mean blocks above 4 KiB, 3.5 KiB or 1.5 KiB, by its payload (256 MiB, 1 GiB), where it can
-run in every phase.  The copy engine's hop does everything else, also where long
-blocks lie side by side, so that a few waves of the row hop would move most of the payload.  The statistics say
-which of the four ran, and under profiling a phase's tiled hop is timed as its unpack time and every other one as
-its pack time; every case is also compared with the CPU oracle byte for byte."""
+run in every phase.  On whole lines the copy engine's hop is the better one from a mean block of 16 KiB (a plan: from
+a longest block of 12 KiB), unless T is in slots.  The copy engine's hop does everything else, also where long blocks
+lie side by side, so that a few waves of the row hop would move most of the payload.  The statistics say which of the
+four ran, and under profiling a phase's tiled hop is timed as its unpack time and every other one as its pack time;
+every case is also compared with the CPU oracle byte for byte."""
 import numpy as np
 import pytest
 
@@ -70,6 +71,11 @@ CASES = {
     "normal 3.9 KiB, dense": (lambda: _normal(14, 3900.0), {}, {}, (R, R), (T, T)),
     "normal 4.3 KiB, dense": (lambda: _normal(14, 4300.0), {}, {}, (T, T), (T, T)),
     "every other block empty, the others 4 KiB": (lambda: _except(4092, 0)(lambda s, r: (s + r) % 2 == 0), {}, {}, (R, R), (T, R)),
+    "whole lines, 12 KiB": (lambda: _equal(12288), {"align": 128}, {}, (R, R), (R, R)),
+    "whole lines, 12.1 KiB": (lambda: _equal(12288 + 128), {"align": 128}, {}, (R, R), (E, E)),
+    "whole lines, 16 KiB": (lambda: _equal(16384), {"align": 128}, {}, (R, R), (E, E)),
+    "whole lines, 16.1 KiB": (lambda: _equal(16384 + 128), {"align": 128}, {}, (E, E), (E, E)),
+    "whole lines, 16.1 KiB, T in slots": (lambda: _equal(16384 + 128), {"align": 128}, {"t_layout": 0}, (R, R, E), (R, R, E)),
     "gaps between the blocks of R": (_normal, {"gap": 8}, {}, (R, R), (R, R)),
     "gaps, normal 4.3 KiB": (lambda: _normal(14, 4300.0), {"gap": 8}, {}, (R, R), (R, R)),
     "byte-granular sizes": (lambda: _normal() + 1, {}, {}, (R, R), (R, R)),
@@ -130,7 +136,7 @@ def test_which_hop_runs(tuna, name, radix):
     meta = [torch.from_numpy(a).to(dev) for a in (lay.sendcounts, lay.sdispls, lay.recvcounts, lay.rdispls)]
     o = tuna.tuna_opts_init()
     o.profile = 1
-    o.t_layout = tuna.TUNA_T_EXACT
+    o.t_layout = opts.get("t_layout", tuna.TUNA_T_EXACT)
     o.mode = tuna.TUNA_MODE_STAGED if opts.get("mode") == "staged" else tuna.TUNA_MODE_FUSED
     o.block_count = opts.get("block_count", 0)
     n_phases = 1 if radix == P else 4
