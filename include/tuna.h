@@ -147,7 +147,7 @@ typedef struct tuna_plan_info {
  * passes instead -- the metadata of every phase first, a second read-back of the phases' exact
  * work-list lengths, then the payload kernels -- which costs one more synchronisation and saves
  * launching every copy kernel for an upper bound of work.
- * Problems of at most 64 ranks, 1 MiB of payload, 8 digit phases and 1200 blocks moved (200 more per
+ * Problems of at most 40 ranks, 1 MiB of payload, 8 digit phases and 1200 blocks moved (200 more per
  * phase; all ranks and phases together) are done by one kernel launch (validation, all phases and the
  * own blocks in one workgroup; options at their defaults, no profiling): there the launches, not the
  * bytes, are what a call costs.  It returns after that kernel has finished.

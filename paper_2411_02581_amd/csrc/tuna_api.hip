@@ -1486,7 +1486,7 @@ int run_once(Ctx& c, const Options& opt, const void* sendbuf, const int32_t* sen
              void* recvbuf, const int32_t* recvcounts, const int64_t* rdispls, int P, int ranks_per_node, int rl, int rg,
              void* stream);
 
-// A whole call in one kernel launch (k_tiny_call) for problems of at most 64 ranks, few blocks and 1 MiB of payload,
+// A whole call in one kernel launch (k_tiny_call) for problems of at most 40 ranks, few blocks and 1 MiB of payload,
 // where a call costs what its launches cost: about thirty launches and a synchronisation become one
 // launch and a synchronisation.  Only when everything was left to the library (mode, no batches, no
 // staggering, no profiling).  *done = false: the kernel declined (invalid counts, or not that small) and
@@ -1532,14 +1532,11 @@ int run_tiny(Ctx& c, const void* sendbuf, const int32_t* sendcounts, const int64
     // would cost a fifth of the whole call
     a.T = c.tiny_t; a.slots = pl.slots; a.t_capacity = kTinyTBytes; a.st = c.sb.h_status_dev ? c.sb.h_status_dev : c.sb.d_status;
     c.sb.h_status->tiny_done = 0;
-    // the kernel keeps the size and displacement matrices and every phase's tables in LDS: more than the
-    // 64 KiB a kernel may use without asking
+    // the kernel keeps the size and displacement matrices and every phase's tables in LDS
     int table_entries = 0;
     for (int i = 0; i < a.nph; ++i) table_entries += pl.phases[i].nseg;
     const size_t lds = tiny_lds_bytes(P, table_entries);
-    static const hipError_t lds_allowed = hipFuncSetAttribute(reinterpret_cast<const void*>(k_tiny_call),
-        hipFuncAttributeMaxDynamicSharedMemorySize, (int)tiny_lds_bytes(kTinyMaxRanks, kTinyMaxPhases * kTinyMaxRanks));
-    if (lds_allowed != hipSuccess) { (void)hipGetLastError(); return TUNA_OK; }     // the general path does the call
+    static_assert(tiny_lds_bytes(kTinyMaxRanks, kTinyMaxPhases * kTinyMaxRanks) <= 48 * 1024, "what a kernel may use without asking");
     hipLaunchKernelGGL(k_tiny_call, dim3(1), dim3(kTinyThreads), lds, s, a);
     HIPCHK(hipGetLastError());
     if (!c.sb.h_status_dev) HIPCHK(hipMemcpyAsync(c.sb.h_status, c.sb.d_status, 64, hipMemcpyDeviceToHost, s));

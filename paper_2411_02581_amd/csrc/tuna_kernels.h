@@ -2319,7 +2319,7 @@ __global__ void __launch_bounds__(kCopyThreads) k_copy_tiled(const TiledCopyArgs
 // 163 -> 61 us, 64 ranks linear byte-granular 250 -> 118 us.
 // Dynamic LDS: tiny_lds_bytes(P, total table entries).
 // ------------------------------------------------------------------------------------------
-constexpr int kTinyMaxRanks = 64;
+constexpr int kTinyMaxRanks = 40;           // above it every schedule moves more blocks than run_tiny sends here
 constexpr int kTinyMaxPhases = 8;
 constexpr int kTinyThreads = 1024;
 constexpr unsigned long long kTinyMaxPayload = 1ull << 20;      // bytes
@@ -2347,7 +2347,7 @@ struct TinyArgs {
 };
 
 // three P x P arrays of 4 bytes (the sizes and two displacement matrices) and four ints per table entry
-inline size_t tiny_lds_bytes(int P, int table_entries) {
+constexpr size_t tiny_lds_bytes(int P, int table_entries) {
     return ((size_t)3 * P * P + (size_t)4 * table_entries) * 4;
 }
 

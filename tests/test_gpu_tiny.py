@@ -1,5 +1,5 @@
-"""Problems of at most 64 ranks and 1 MiB of payload, called with everything left to the library, are done
-by one kernel launch (k_tiny_call: validation, rotation, own blocks and every digit phase in one workgroup).
+"""Problems of at most 40 ranks, 1 MiB of payload and few moving blocks, called with everything left to the library, are
+done by one kernel launch (k_tiny_call: validation, rotation, own blocks and every digit phase in one workgroup).
 Same bar as everywhere: the whole receive allocation equals the CPU oracle's byte for byte, for every radix
 and hierarchy; invalid counts and problems that are not tiny after all fall through to the general path,
 which reports the error or does the work."""
@@ -22,7 +22,28 @@ def tuna():
     import paper_2411_02581_amd as t
     t.load()
     assert t.tuna_opts_init().mode == t.TUNA_MODE_AUTO        # the defaults: the one-kernel call is eligible
-    return t
+    # a declined problem is not asked again: the counts declined last lie at an address that nothing here reuses
+    keep = Prob(wl.counts_uniform_bytes(16, 1, 12000), 1)
+    keep.run(t, 0, 2, 2, "declined")
+    assert not single_launch(t)
+    yield t
+    del keep
+
+
+TINY_T = 4 << 20
+
+
+def single_launch(tuna):
+    st = tuna.tuna_get_stats()
+    assert (st.hop_kernels == 0) == (st.workspace_bytes == TINY_T)
+    return st.workspace_bytes == TINY_T                       # the one-kernel call's own small T, nothing else
+
+
+def few_blocks(tuna, P, Q, rl, rg):
+    """The library's rule: at most 1200 blocks moved and 200 more per phase, over all ranks and phases."""
+    rc, info = tuna.tuna_plan_info(P, Q, rl, rg)
+    assert rc == 0
+    return P <= 40 and info.blocks_sent_per_rank * P <= 1200 + 200 * info.n_phases
 
 
 class Prob:
@@ -56,7 +77,7 @@ def test_config1_in_one_launch(tuna):
         st = tuna.tuna_get_stats()
         assert (st.P, st.local_radix, st.fused, st.granularity) == (16, r, 1, 4)
         assert st.total_payload_bytes == prob.lay.payload_bytes and st.max_block_bytes == prob.lay.sendcounts.max()
-        assert st.workspace_bytes == 4 << 20                  # the one-kernel call's own small T, nothing else
+        assert single_launch(tuna)
     assert (st.w_local, st.K_local) == (1, 15)
 
 
@@ -68,24 +89,64 @@ def test_every_radix(tuna, P):
     prob = Prob(counts, P, gap=5, permute_seed=9)
     for r in sorted(set(list(range(2, min(P, 9) + 1)) + [max(P, 2), P + 3])):
         prob.run(tuna, 0, r, r, "P=%d r=%d" % (P, r))
+        assert single_launch(tuna) == few_blocks(tuna, P, 0, r, r), r
 
 
-@pytest.mark.parametrize("P,Q,rl,rg", [(12, 3, 2, 2), (24, 4, 2, 3), (36, 6, 6, 6), (64, 8, 2, 2), (64, 16, 4, 2), (60, 5, 3, 4)])
+# one block per pair and its single hop: 37 ranks move 1332 of at most 1400 blocks, 38 move 1406; with radix P - 1 there is a
+# second phase: 40 ranks move 1560 of at most 1600, 41 1640
+@pytest.mark.parametrize("P,radix,tiny", [(37, 37, True), (38, 38, False), (38, 37, True), (40, 39, True), (40, 40, False), (41, 40, False),
+                                          (24, 2, True), (32, 2, False)])
+def test_both_sides_of_the_limit(tuna, P, radix, tiny):
+    prob = Prob(wl.counts_uniform_bytes(P, 300 + P, 300), P)
+    prob.run(tuna, 0, radix, radix, "P=%d r=%d" % (P, radix))
+    assert single_launch(tuna) == tiny == few_blocks(tuna, P, 0, radix, radix)
+
+
+@pytest.mark.parametrize("P,Q,rl,rg", [(12, 3, 2, 2), (24, 4, 2, 3), (36, 6, 6, 6), (64, 8, 2, 2), (64, 16, 4, 2), (60, 5, 3, 4),
+                                         (20, 5, 2, 2), (30, 5, 5, 6), (16, 4, 2, 2)])
 def test_hierarchies(tuna, P, Q, rl, rg):
     counts = wl.counts_uniform_elements(P, 500 + P, 40, 4)
     prob = Prob(counts, P + 1, gap=4)
     prob.run(tuna, Q, rl, rg, "P=%d Q=%d rl=%d rg=%d" % (P, Q, rl, rg))
     st = tuna.tuna_get_stats()
     assert (st.Q, st.N, st.fused) == (Q, P // Q, 1)
+    assert single_launch(tuna) == few_blocks(tuna, P, Q, rl, rg)
 
 
 def test_not_tiny_after_all_and_errors(tuna):
-    """More than 1 MiB of payload among few ranks, a T that would not fit the small buffer, and invalid
-    counts: the kernel declines and the general path takes over."""
+    """More than 1 MiB of payload among few ranks, a T that would not fit the small buffer, displacements beyond 32 bits
+    and invalid counts: the kernel declines and the general path takes over; so it does from the start where there are
+    many blocks."""
+    for P, longest in ((16, 12000), (8, 50000)):
+        big = Prob(wl.counts_uniform_bytes(P, 5, longest), 3)
+        assert big.lay.payload_bytes > 1 << 20 and few_blocks(tuna, P, 0, 2, 2)
+        for _ in range(2):                                               # declined, then not asked again
+            big.run(tuna, 0, 2, 2, "%d bytes among %d ranks" % (big.lay.payload_bytes, P))
+            assert not single_launch(tuna)
+    just = Prob(np.full((16, 16), 4096, dtype=np.int32), 3)              # 1 MiB and not a byte more; T of 22 slots per rank fits
+    just.run(tuna, 0, 2, 2, "1 MiB among 16 ranks")
+    assert just.lay.payload_bytes == 1 << 20 and single_launch(tuna)
+    counts = np.zeros((16, 16), dtype=np.int32)
+    counts[3, 10] = 500 << 10
+    counts[5, 6] = 100
+    wide = Prob(counts, 4)
+    wide.run(tuna, 0, 2, 2, "one 500 KiB block among 16 ranks")
+    assert not single_launch(tuna)
+    far = Prob(wl.counts_uniform_bytes(12, 6, 200), 7)
+    far.run(tuna, 0, 3, 3, "near")
+    assert single_launch(tuna)
+    _, sd, rc_, rd = far.meta
+    far_send = torch.cat([torch.zeros(1 << 32, dtype=torch.uint8, device="cuda:0"), far.send])
+    counts = far.meta[0].clone()
+    far.recv.fill_(CANARY)
+    assert tuna.tuna_alltoallv_hier(far_send, counts, sd + (1 << 32), far.recv, rc_, rd, 12, 0, 3, 3) == 0
+    torch.cuda.synchronize()
+    assert np.array_equal(far.recv.cpu().numpy()[:far.lay.recv_bytes], far.want) and not single_launch(tuna)
+    del far_send
     big = Prob(wl.counts_uniform_bytes(32, 5, 4000), 3)                  # about 2 MiB
     assert big.lay.payload_bytes > 1 << 20
     big.run(tuna, 0, 2, 2, "2 MiB among 32 ranks")
-    assert tuna.tuna_get_stats().workspace_bytes != 4 << 20
+    assert not single_launch(tuna)
     counts = np.zeros((64, 64), dtype=np.int32)
     counts[3, 40] = 900 << 10                                            # under 1 MiB, but 64 x 2 x 57 slots of it are not
     counts[5, 6] = 100
@@ -103,3 +164,4 @@ def test_not_tiny_after_all_and_errors(tuna):
     torch.cuda.synchronize()
     assert (small.recv.cpu().numpy() == CANARY).all()
     small.run(tuna, 0, 2, 2, "valid again")
+    assert single_launch(tuna)
