@@ -126,60 +126,97 @@ def test_one_context_two_streams_are_ordered(tuna):
         assert a.ok() and b.ok(), it
 
 
-def test_large_calls_with_metadata_on_a_second_stream(tuna):
-    """Calls of 64 MiB and more with several one-kernel phases compute every phase's metadata on a stream of
-    the context's own while the caller's stream moves the payload.  Two such problems back to back on two
-    streams of one context, with a small call between them, with no host synchronisation in between; then the
-    same call profiled (which keeps to one stream), on a context of its own, and on a caller-owned workspace
-    of the size the sizing query names."""
-    big = Prob(wl.counts_normal(320, 21, 1024.0, 256.0, 4), 8, gap=0)          # 100 MiB, the tiled hop
-    zipf = Prob(wl.counts_zipf(384, 22, 1.2, 16384, 4), 9)                    # 120 MiB, gaps: the copy engine's hop
+def _one_long_block(counts, nbytes):
+    c = counts.astype(np.int32).copy()
+    c[3, 41] = nbytes                                       # too long for the kernels that find their blocks themselves
+    return c
+
+
+@pytest.mark.parametrize("pipelined", [False, True])
+def test_large_calls_with_metadata_on_a_second_stream(tuna, pipelined):
+    """Calls of 64 MiB and more with several one-kernel phases.  Where blocks are longer than the kernels take that find
+    their blocks themselves, every phase's metadata is computed on a stream of the context's own while the caller's
+    stream moves the payload; otherwise everything runs on the caller's.  Two such problems back to back on two
+    streams of one context, with a small call between them, with no host synchronisation in between; then the same
+    calls profiled (which keeps to one stream: in two passes where it would be two streams), on a context of its own, and
+    on a caller-owned workspace of the size the sizing query names."""
+    if pipelined:
+        big = Prob(_one_long_block(wl.counts_normal(80, 21, 12288.0, 3072.0, 4), 65540), 8, gap=0)   # the tiled hop
+        other = Prob(_one_long_block(wl.counts_uniform_bytes(96, 22, 20000), 70001), 9)             # gaps, bytes: the engine's
+        kernels = {big: tuna.TUNA_HOP_TILED, other: tuna.TUNA_HOP_ENGINE}
+    else:
+        big = Prob(wl.counts_normal(320, 21, 1024.0, 256.0, 4), 8, gap=0)
+        other = Prob(wl.counts_zipf(384, 22, 1.2, 16384, 4), 9)
+        kernels = {big: tuna.TUNA_HOP_ROWS, other: tuna.TUNA_HOP_ROWS}
     small = Prob(wl.counts_uniform_bytes(50, 10, 900), 6)
-    assert big.lay.payload_bytes > (64 << 20) and zipf.lay.payload_bytes > (64 << 20)
+    assert big.lay.payload_bytes > (64 << 20) and other.lay.payload_bytes > (64 << 20)
+    t_layout = tuna.TUNA_T_EXACT if pipelined else tuna.TUNA_T_AUTO
+    opts = tuna.tuna_opts_init()
+    opts.t_layout = t_layout
     s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
     torch.cuda.synchronize()
     for it, (r1, r2) in enumerate([(2, 4), (8, 20), (18, 2)]):
-        for p in (big, zipf, small):
+        for p in (big, other, small):
             p.recv.fill_(CANARY)
         torch.cuda.synchronize()
-        print("pipelined calls, iteration", it, flush=True)
-        assert big.call(tuna, None, 0, r1, r1, None, s1) == 0
-        assert zipf.call(tuna, None, 16, 4, r2, None, s2) == 0
+        print("large calls, pipelined %s, iteration %d" % (pipelined, it), flush=True)
+        assert big.call(tuna, None, 0, r1, r1, opts, s1) == 0
+        assert other.call(tuna, None, 16, 4, r2, opts, s2) == 0
+        assert tuna.tuna_get_stats().hop_kernels == kernels[other] or it
         assert small.call(tuna, None, 0, 5, 5, None, s1) == 0
-        assert big.call(tuna, None, 0, r2, r2, None, s2) == 0
+        assert big.call(tuna, None, 0, r2, r2, opts, s2) == 0
         torch.cuda.synchronize()
-        assert big.ok() and zipf.ok() and small.ok(), it
+        assert big.ok() and other.ok() and small.ok(), it
         st = tuna.tuna_get_stats()
-        assert st.n_phases >= 2 and sum(st.phase[x].payload_bytes for x in range(st.n_phases)) >= big.lay.payload_bytes
-    o = tuna.tuna_opts_init()
-    o.profile = 1
-    big.recv.fill_(CANARY)
-    assert big.call(tuna, None, 0, 4, 4, o) == 0
-    torch.cuda.synchronize()
-    st = tuna.tuna_get_stats()
-    assert big.ok() and st.hop_kernels == tuna.TUNA_HOP_ROWS
-    assert all(st.phase[x].ms_metadata > 0 and st.phase[x].ms_pack > 0 for x in range(st.n_phases))
+        assert st.n_phases >= 2 and st.hop_kernels == kernels[big]
+        assert sum(st.phase[x].payload_bytes for x in range(st.n_phases)) >= big.lay.payload_bytes
+
+    def check(prob, Q, what, ctx=None):
+        torch.cuda.synchronize()
+        assert prob.ok(), what
+        st = tuna.tuna_ctx_get_stats(ctx)
+        assert st.n_phases >= 2 and st.hop_kernels == kernels[prob], what
+        return st
+
+    profiled = tuna.tuna_opts_init()
+    profiled.t_layout, profiled.profile = t_layout, 1
+
+    def check_times(st):
+        for x in range(st.n_phases):
+            ph = st.phase[x]
+            times = (ph.ms_pack, ph.ms_unpack) if st.hop_kernels != tuna.TUNA_HOP_TILED else (ph.ms_unpack, ph.ms_pack)
+            assert ph.ms_metadata > 0 and times[0] > 0 and times[1] == 0
+
+    for prob, Q in ((big, 0), (other, 16)):
+        prob.recv.fill_(CANARY)
+        assert prob.call(tuna, None, Q, 4, 4, profiled) == 0
+        check_times(check(prob, Q, "profiled"))
     rc, ctx = tuna.tuna_ctx_create()
     assert rc == 0
     try:
-        for r in (3, 7):
-            zipf.recv.fill_(CANARY)
-            assert zipf.call(tuna, ctx, 16, r, r, None, s1) == 0
-            torch.cuda.synchronize()
-            assert zipf.ok(), r
+        for r in (3, 5):
+            for prob, Q in ((other, 16), (big, 0)):
+                prob.recv.fill_(CANARY)
+                assert prob.call(tuna, ctx, Q, r, r, opts, s1) == 0
+                check(prob, Q, "a context of its own", ctx)
     finally:
         assert tuna.tuna_ctx_destroy(ctx) == 0
-    rc, need = tuna.tuna_workspace_bytes(big.meta[0], big.lay.P, 0, 4, 4)
-    assert rc == 0 and need > 0
-    ws = torch.empty(need + 256, dtype=torch.uint8, device="cuda:0")
-    base = (ws.data_ptr() + 255) // 256 * 256
-    assert tuna.tuna_set_workspace(base, need) == 0
+    tuna.tuna_set_option(tuna.TUNA_OPT_DENSE_T, t_layout)   # the sizing query goes by the process-wide options
     try:
-        big.recv.fill_(CANARY)
-        assert big.call(tuna, None, 0, 4, 4) == 0
-        torch.cuda.synchronize()
-        assert big.ok() and tuna.tuna_get_stats().workspace_bytes <= need
+        for prob, Q in ((big, 0), (other, 16)):
+            rc, need = tuna.tuna_workspace_bytes(prob.meta[0], prob.lay.P, Q, 4, 4)
+            assert rc == 0 and need > 0
+            ws = torch.full((need + 512,), CANARY, dtype=torch.uint8, device="cuda:0")
+            base = (ws.data_ptr() + 255) // 256 * 256
+            assert tuna.tuna_set_workspace(base, need) == 0
+            for o in (opts, profiled):
+                prob.recv.fill_(CANARY)
+                assert prob.call(tuna, None, Q, 4, 4, o) == 0
+                assert check(prob, Q, "a caller's workspace").workspace_bytes <= need
+            assert (ws[base - ws.data_ptr() + need:] == CANARY).all() and (ws[:base - ws.data_ptr()] == CANARY).all()
+            assert tuna.tuna_set_workspace(None, 0) == 0
     finally:
+        tuna.tuna_set_option(tuna.TUNA_OPT_DENSE_T, 2)
         assert tuna.tuna_set_workspace(None, 0) == 0
 
 

@@ -85,9 +85,9 @@ def test_config3_full_hierarchical(tuna):
 
 
 def test_config3_caller_workspace_and_phase_times(tuna):
-    """A profiled call of this size is made in two passes (all metadata, a second read-back, then the payload
-    kernels with exact grids).  Here it runs in a caller-owned workspace of tuna_workspace_bytes bytes,
-    with per-kernel timing on: same bytes as the oracle, every stage of every phase timed, and the
+    """A call of this size with three-stage phases is made in two passes (all metadata, a second read-back, then the
+    payload kernels with exact grids), with one-kernel phases in one, whose kernels find their blocks themselves.  Here
+    both run in a caller-owned workspace of tuna_workspace_bytes bytes, with per-kernel timing on: same bytes as the oracle, every stage of every phase timed, and the
     workspace it reports fits the one that was asked for."""
     c = wl.CONFIGS[3]
     P = c.P
@@ -291,15 +291,17 @@ def test_own_blocks_of_64_mebibytes(tuna):
         assert st.ms_self < 10.0
 
 
-def test_byte_granular_two_pass_all_modes(tuna):
-    """P = 512, byte-granular sizes 0..2047 (any alignment), 256 MiB of payload, radix 8 (three digit phases):
-    large enough for the two-pass form of an immediate call (three stages) and for its pipelined form
-    (one-kernel phases), in all four modes (three stages / one-kernel phases x T in slots / in exact size);
-    whole receive buffer against the oracle."""
-    P = 512
-    counts = wl.counts_uniform_bytes(P, 512, 2047)
+@pytest.mark.parametrize("P,longest", [(512, 2047), (160, 70001)])
+def test_byte_granular_two_pass_all_modes(tuna, P, longest):
+    """Byte-granular sizes (any alignment) in three digit phases, in all four modes (three stages / one-kernel phases x T
+    in slots / in exact size), large enough for the two-pass form of a call with three stages: P = 512, sizes 0..2047,
+    256 MiB of payload, where kernels find the blocks of one-kernel phases themselves, and P = 160, sizes 0..8000 and one
+    block of 70001, 100 MiB, where those calls are pipelined (two streams); whole receive buffer against the oracle."""
+    counts = wl.counts_uniform_bytes(P, 512, min(longest, 8000))
+    counts[3, 5] = longest
+    radix = 8 if P == 512 else 6
     lay = wl.make_layout(counts, gap=3)
-    assert lay.payload_bytes > 250 << 20
+    assert lay.payload_bytes > (250 if P == 512 else 90) << 20
     send_host = wl.payload_position_hash(5120, lay.send_bytes)
     want = np.full(lay.recv_bytes, 0x3C, dtype=np.uint8)
     assert oracle.alltoallv(send_host, lay.sendcounts, lay.sdispls, want, lay.recvcounts, lay.rdispls) == 0
@@ -312,13 +314,15 @@ def test_byte_granular_two_pass_all_modes(tuna):
             o = tuna.tuna_opts_init()
             o.mode, o.t_layout = mode, tl
             recv.fill_(0x3C)
-            print("byte-granular two-pass: mode %d, T layout %d" % (mode, tl), flush=True)
-            code = tuna.tuna_alltoallv_ex(None, send, sc, sd, recv, rc, rd, P, 0, 8, 8, o)
+            print("byte-granular: P %d, mode %d, T layout %d" % (P, mode, tl), flush=True)
+            code = tuna.tuna_alltoallv_ex(None, send, sc, sd, recv, rc, rd, P, 0, radix, radix, o)
             assert code == 0, tuna.tuna_strerror(code)
             torch.cuda.synchronize()
             assert torch.equal(recv, want_dev), (mode, tl)
             st = tuna.tuna_get_stats()
             assert (st.granularity, st.n_phases, st.dense_t) == (1, 3, tl)
+            want_kernel = tuna.TUNA_HOP_ROWS if P == 512 else tuna.TUNA_HOP_ENGINE
+            assert st.hop_kernels == (want_kernel if mode == tuna.TUNA_MODE_FUSED else 0)
 
 
 def test_counts_beyond_the_supported_range(tuna):
