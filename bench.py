@@ -7,7 +7,8 @@ and receive buffers are already resident in HBM.  Default workload: the P = 4096
 (block sizes normal(1 KiB, 256 B), ~16 GiB payload), radix sweep {2, 8, 64, 4096}, with the library's
 default options (the mode and the layout of T left to the library).
 
-Prints ONE JSON line:
+Prints ONE JSON line of a few KiB on stdout, and the same with every measured row in full on stderr, behind
+"[bench] detail ":
   value         effective Alltoallv rate (payload bytes / time per call) of the best radix, defaults
   per_radix     every radix of that sweep, with the payload kernels' event-timed rates
   three_stage   the same sweep with pack -> exchange -> unpack as three kernels (the paper's three steps;
@@ -408,7 +409,38 @@ def main():
             "per_radix": three_stage},
         "slots_of_M": slots, "persistent": persistent, "selector": selector, "also_measured": also,
     }
-    print(json.dumps(out))
+    print("[bench] detail " + json.dumps(out), file=sys.stderr, flush=True)
+    print(json.dumps(compact(out)))
+
+
+def compact(x, top=True):
+    """The result with its tables cut to what a reader compares: a row keeps its radix, time and rates; the workloads of
+    also_measured keep the times of their calls and starts."""
+    if isinstance(x, float):
+        return float("%.6g" % x) if not top else x
+    if isinstance(x, list):
+        return [compact(v, False) for v in x]
+    if not isinstance(x, dict):
+        return x
+    if "radix" in x:
+        out = {k: compact(x[k], False) for k in ("radix", "ms_per_step", "ms_per_start", "ms_per_graph_replay", "effective_GBs") if k in x}
+        if "kernels" in x:
+            out["kernel_GBs"] = {k: compact(v["achieved_GBs"], False) for k, v in x["kernels"].items()}
+        return out
+    if top:
+        out = {k: compact(v, k in ("value", "ms_per_step")) for k, v in x.items() if k != "also_measured"}
+        out["also_measured"] = x["also_measured"] and {k: short_times(v) for k, v in x["also_measured"].items()}
+        return out
+    return {k: compact(v, False) for k, v in x.items()}
+
+
+def short_times(w):
+    """{radix: ms} of the calls and of the starts of one further workload."""
+    out = {"calls_ms": {r["radix"]: compact(r["ms_per_step"], False) for r in w["per_radix"]},
+           "starts_ms": {r["radix"]: compact(r["ms_per_start"], False) for r in w["persistent"]}}
+    if w.get("roofline"):
+        out["roofline"] = {k: compact(w["roofline"][k], False) for k in ("kernel", "achieved", "frac")}
+    return out
 
 
 def diagonal_counts(P):
