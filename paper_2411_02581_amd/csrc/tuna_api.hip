@@ -1133,7 +1133,6 @@ int launch_resolve(const Prepared& pr, size_t i, const int32_t* nxt, const HopDe
     return TUNA_OK;
 }
 
-
 // Resolved addresses of a one-kernel phase: row stride and bytes.
 int hop_ld_for(int nseg) { return (nseg + 31) / 32 * 32; }
 size_t hop_bytes_for(int P, int ld) { return 2 * align_up((size_t)P * ld * 8) + align_up((size_t)P * ld * 4); }
@@ -1428,10 +1427,11 @@ int run_one_pass(Prepared& pr, void* mbase, size_t mbytes, void* dbase, hipStrea
     // has checked that it is the transpose of sendcounts): one kernel instead of the rotation and the exchange.
     // Phases that find their blocks themselves need neither.
     pr.sizes_direct = pl.phases.size() == 1 && pr.fused && !pr.debug_sizes;
-    if (direct) (void)0;
-    else if (pr.sizes_direct) hipLaunchKernelGGL(k_rotate_init, grot, dim3(256), 0, s, pr.recvcounts, mb.nxt, P, pr.Q, pr.N, 1);
-    else hipLaunchKernelGGL(k_rotate_init, grot, dim3(256), 0, s, pr.sendcounts, mb.cur, P, pr.Q, pr.N, 0);
-    HIPCHK(hipGetLastError());
+    if (!direct) {
+        if (pr.sizes_direct) hipLaunchKernelGGL(k_rotate_init, grot, dim3(256), 0, s, pr.recvcounts, mb.nxt, P, pr.Q, pr.N, 1);
+        else hipLaunchKernelGGL(k_rotate_init, grot, dim3(256), 0, s, pr.sendcounts, mb.cur, P, pr.Q, pr.N, 0);
+        HIPCHK(hipGetLastError());
+    }
     mark(pr.ctx, s, kCatPrepare, -1);
     rc = launch_self_metadata(pr, s);
     if (rc != TUNA_OK) return rc;
@@ -1443,8 +1443,9 @@ int run_one_pass(Prepared& pr, void* mbase, size_t mbytes, void* dbase, hipStrea
     int32_t* cur = mb.cur;
     int32_t* nxt = mb.nxt;
     if (direct) {
-        // the places in exact-size T, then one kernel per phase that finds and moves its blocks.  The partial sums lie where the hop arrays would (a phase has at most one row per
-        // segment) and are added up when there is no room for the next phase's, at the latest at the end.
+        // the places in exact-size T, then one kernel per phase that finds and moves its blocks.  The partial sums lie where
+        // the hop arrays would (a phase has at most one row per segment) and are added up when there is no room for the
+        // next phase's, at the latest at the end.
         rc = launch_t_places(pr, s);
         if (rc != TUNA_OK) return rc;
         mark(pr.ctx, s, kCatMeta, 0);

@@ -49,8 +49,9 @@ struct Status {
     unsigned long long send_extent;    // max over non-empty blocks of sdispls + count: bytes of sendbuf that hold blocks
     unsigned long long t_chunks;       // exact-size T: chunks stored into T over all phases
     unsigned long long short_blocks;   // blocks of fewer than kShortBlockBytes bytes, empty ones included
-    unsigned long long windows;        // most bytes that one receiver gets from kValTile aligned neighbouring senders (high half)
-                                       // and one sender sends to as many receivers (low half); blocks count up to kWindowBlock
+    unsigned long long windows;        // with blocks of more than kShortBlockBytes: most bytes that one receiver gets from
+                                       // kValTile aligned neighbouring senders (high half) and one sender sends to as many
+                                       // receivers (low half); blocks count up to kWindowBlock
     unsigned long long cls_chunks[kMaxClasses];   // exact-size T: chunks of every class (f, y), summed by the validation pass
     unsigned long long phase_bytes[64];   // payload bytes moved per phase
     unsigned long long phase_chunks[64];  // staged chunks per phase
@@ -228,7 +229,8 @@ __global__ void __launch_bounds__(256) k_build_hops(const PlanScalars pl, int32_
 // them up: no kernel to clear the sums, none to fold the rows, no copy of the result (see run_validate; P = 256, r = 4
 // 138 -> 117 us per call with the above).
 // The first two waves also sum the tile's columns and rows; the largest sums say whether long blocks lie side by side
-// (rows_balanced).
+// (rows_balanced).  Not before a block of more than 256 bytes was seen: shorter ones, which k_hop_direct takes, cannot make
+// a window that counts.
 // ------------------------------------------------------------------------------------------
 constexpr int kValTile = 64;
 constexpr int kValPartial = 8;              // 64-bit words per workgroup in the partial-result array
@@ -251,10 +253,12 @@ __global__ void __launch_bounds__(1024) k_validate(const int32_t* __restrict__ s
                                                    Status* __restrict__ st, int cls_rows, int copies, int clear_totals) {
     __shared__ int tile[kValTile][kValTile + 1];
     __shared__ unsigned long long red[16][8];
+    __shared__ int long_seen;
     extern __shared__ unsigned long long lcls[];          // class_count(nph) sums of this workgroup, `copies` of each (with `mask`)
     const int tx = threadIdx.x, ty = threadIdx.y, ny = blockDim.y;
     const int ncls = mask ? class_count(nph) : 0;
     for (int i = ty * kValTile + tx; i < ncls * copies; i += ny * kValTile) lcls[i] = 0;
+    if (tx == 0 && ty == 0) long_seen = 0;
     __syncthreads();
     unsigned int window = 0;                              // largest sum of a column (first wave) or row (second wave)
     const int tpr = (P + kValTile - 1) / kValTile;       // tiles per row
@@ -324,6 +328,7 @@ __global__ void __launch_bounds__(1024) k_validate(const int32_t* __restrict__ s
                 tile[a][tx] = c;
             }
         }
+        if (mx > kShortBlockBytes) long_seen = 1;
         __syncthreads();
         if (recvcounts) {
             for (int a0 = ty; a0 < kValTile; a0 += 4 * ny) {
@@ -340,7 +345,7 @@ __global__ void __launch_bounds__(1024) k_validate(const int32_t* __restrict__ s
                     // the last lane of a row reads its successor's displacement itself (below)
                     dx[u] = (rdispls && tx == kValTile - 1 && in[u] && i + 1 < P) ? rdispls[idx + 1] : 0;
                 }
-                if (a0 == ty && ty < 2) {                 // under the first loads: bytes of receiver j from the tile's senders, of sender bi + tx
+                if (a0 == ty && ty < 2 && long_seen) {    // under the first loads: bytes of receiver bj + tx, of sender bi + tx
                     const int* entry = ty == 0 ? &tile[0][tx] : &tile[tx][0];
                     const int step = ty == 0 ? kValTile + 1 : 1;
                     unsigned int sum = 0;
