@@ -752,17 +752,11 @@ bool too_large(int P, const Status& hs) {
     return std::min(by_m, by_all) >= (1ull << 31);
 }
 
-// One-kernel phases of problems whose blocks are all short run k_hop_direct (one lane resolves a block, 1, 4 or 16
-// lanes move it) instead of the byte-balanced engine.
-bool small_blocks(const Prepared& pr) { return pr.max_count > 0 && pr.max_count <= kDirectMaxBytes; }
-
 int rows_segs(const Prepared& pr);
 constexpr double kRowsEvenBytes = 24576.0;      // a wave of k_hop_rows with no more is done in three steps
 
-// The other calls and plans whose phases are all one-kernel hops over all rounds at once run k_hop_rows, unless a block
-// can be so long that waves of whole blocks would not balance, long blocks lie side by side (rows_balanced), or the
-// destination-tiled hop can run, or the engine's on whole lines, and its metadata costs less than what its full units
-// gain (rows_mean_limit).
+// The mean block up to which k_hop_rows is taken where the destination-tiled hop can run, or the engine's on whole lines:
+// their metadata costs less than what their full units gain on longer ones.
 // That metadata goes with the blocks and the launches: it is worth saving for short blocks, and up to longer ones where
 // the payload is small.  Normal sizes, per call, tiled against rows: 1 KiB, P = 2048, r = 8 5.39 / 5.23 ms, 1.5 KiB 7.69 /
 // 7.84, 1.8 KiB 9.08 / 9.56; P = 1024 (2.5 to 4 GB), r = 8, 2.4 KiB 2.99 / 3.08, 3.6 KiB 4.31 / 4.62, r = 2 6.99 / 7.39;
@@ -787,6 +781,17 @@ double rows_mean_limit(const Prepared& pr) {
     if (pr.for_plan || pr.total_bytes > (1ull << 30)) return 1536.0;
     return pr.total_bytes > (256ull << 20) ? kRowsBytes / 2 : 4096.0;
 }
+
+// Bytes of the fullest window of blocks (Status.windows), and whether it holds more than `times` the mean one.
+double fullest_window(const Prepared& pr) {
+    const double window = (double)(pr.windows >> 32);
+    return pr.dp->host.phases.size() > 1 ? std::max(window, (double)(pr.windows & 0xffffffffull)) : window;
+}
+bool clustered(const Prepared& pr, double times) {
+    const double mean = (double)pr.total_bytes / ((double)pr.P * (double)pr.P);
+    return fullest_window(pr) > times * mean * (double)std::min(pr.P, kValTile);
+}
+
 // A wave of k_hop_rows takes a number of blocks that the mean gives: where long blocks lie side by side -- a receiver
 // that gets far more than the others, a band of neighbours -- a few waves move most of the payload, 8 KiB at a time
 // (64 KiB from each of 1024 ranks to one, per call and per start: 182 and 46 us with the engine's hop, 1185 and 1105 with
@@ -802,21 +807,43 @@ double rows_mean_limit(const Prepared& pr) {
 // behind it: 64 KiB to one rank 21.1 / 24.8 us, Zipf sizes up to 16 KiB among 96 ranks 10.0 / 13.3, up to 64 KiB among 256
 // (150 MB) 60 / 67 and among 512 (630 MB) 258 / 265, up to 16 KiB among 1024 (870 MB) 359 / 344; byte-granular ones, which
 // cost the engine more, up to 64 KiB among 512 (460 MB) 239 / 212, up to 16 KiB among 256 (39 MB, r = 8) 60 / 70.
-constexpr double kRowsMaxWindow = 6.0;
 bool rows_balanced(const Prepared& pr) {
-    const double total = (double)pr.total_bytes, mean = total / ((double)pr.P * (double)pr.P);
-    double window = (double)(pr.windows >> 32);
-    if (pr.dp->host.phases.size() > 1) window = std::max(window, (double)(pr.windows & 0xffffffffull));
-    const double longest = std::min(window, (double)rows_segs(pr) * (double)pr.max_count);
-    const bool even = window <= kRowsMaxWindow * mean * (double)std::min(pr.P, kValTile);
+    const double total = (double)pr.total_bytes;
+    const double longest = std::min(fullest_window(pr), (double)rows_segs(pr) * (double)pr.max_count);
+    const bool even = !clustered(pr, 6.0);
     if (pr.for_plan) return longest <= kRowsEvenBytes + (even ? total / (pr.gran < 4 ? 1600.0 : 6144.0) : 0.0);
     return longest <= (even ? 196608.0 + total / 512.0 : 81920.0);
 }
-bool row_blocks(const Prepared& pr) {
-    if (pr.max_count <= kDirectMaxBytes || pr.max_count > kRowsMaxBytes || !pr.fused || pr.staggered || pr.block_count > 0) return false;
-    if (!rows_balanced(pr)) return false;
-    return (double)pr.total_bytes <= rows_mean_limit(pr) * (double)pr.P * (double)pr.P;
+
+// The kernel that moves the one-kernel phases of a problem: k_hop_direct (one lane finds a block, 1, 4 or 16 lanes move
+// it) for blocks of up to 256 bytes, k_hop_rows for blocks of up to 64 KiB, all rounds of a phase at once, as long as its
+// waves are balanced (rows_balanced) and the hops with unit lists are not the faster ones (rows_mean_limit); those
+// otherwise (TUNA_HOP_ENGINE stands for both here).
+// Blocks of 65 to 256 bytes: out of the caches the 16-byte accesses of k_hop_direct leave partial lines, so that large
+// payloads run k_hop_rows -- with several phases from 112 MiB on (direct / rows, P = 1024, r = 8 and 32: up to 200 bytes
+// (100 MiB) per start 203 / 201 and 123 / 130 us, up to 256 (128 MiB) 226 / 214 and 139 / 142; P = 1600, up to 100 bytes
+// (122 MiB) per call 541 / 451 and 363 / 339 us; P = 4096, r = 16, normal 128 bytes 4.74 / 3.44 ms, engine 4.34), with one
+// phase, whose stores lie side by side, from 240 MiB on and where blocks share no 16 bytes (P = 2048, 256 MiB, per call 212 /
+// 202 us; P = 1600, 164 MB 137 / 169; word-granular, P = 4096 1.29 / 1.52 ms).  Where rounds are batched or staggered
+// k_hop_rows cannot, and the engine takes word-granular ones over from 256 MiB on (staggered, P = 2048, up to 256 bytes, per
+// start 860 / 699 us, P = 1024, 128 MiB, 195 / 190; in batches of 8 rounds 883 / 831 and 178 / 230).  A plan's k_hop_direct
+// reads 20 bytes of hop arrays per pair whatever there is to move: clustered blocks among empty ones run the engine (256
+// bytes from each of 2048 ranks to one 56 / 10 us per start, to 64 of them 60 / 18; scattered ones, one pair in 64 59 / 93).
+constexpr unsigned long long kMiB = 1ull << 20;
+int block_kernel(const Prepared& pr) {
+    const bool whole = pr.fused && !pr.staggered && pr.block_count == 0, phases = pr.dp->host.phases.size() > 1;
+    if (pr.max_count <= 0) return TUNA_HOP_ENGINE;
+    if (pr.max_count <= kWindowMinBytes) return TUNA_HOP_DIRECT;
+    if (pr.max_count <= kDirectMaxBytes) {
+        if (pr.for_plan && clustered(pr, 8.0)) return TUNA_HOP_ENGINE;
+        if (!whole) return phases && pr.gran >= 4 && pr.total_bytes >= 256 * kMiB ? TUNA_HOP_ENGINE : TUNA_HOP_DIRECT;
+        return pr.total_bytes >= (phases ? 112 : 240) * kMiB && (phases || pr.gran >= 16) ? TUNA_HOP_ROWS : TUNA_HOP_DIRECT;
+    }
+    if (pr.max_count > kRowsMaxBytes || !whole || !rows_balanced(pr)) return TUNA_HOP_ENGINE;
+    return (double)pr.total_bytes <= rows_mean_limit(pr) * (double)pr.P * (double)pr.P ? TUNA_HOP_ROWS : TUNA_HOP_ENGINE;
 }
+bool small_blocks(const Prepared& pr) { return block_kernel(pr) == TUNA_HOP_DIRECT; }
+bool row_blocks(const Prepared& pr) { return block_kernel(pr) == TUNA_HOP_ROWS; }
 constexpr int kTiledMinMeanBytes = 700;    // see prepare_sizes
 constexpr int kTiledMinMeanBytesIntoT = 512;
 
@@ -860,7 +887,7 @@ int prepare_sizes(Prepared& pr, int dense_option, hipStream_t s, Status& hs, boo
     // mean block of 256 bytes, and lose 2 to 8 % below that: a mean block of kTiledMinMeanBytesIntoT.
     const unsigned long long P2 = (unsigned long long)P * (unsigned long long)P;
     pr.tiled = pr.fused && !pr.staggered && pr.block_count == 0 && !(hs.flags & 8u) && (pr.gran == 4 || pr.gran == 16) &&
-               !small_blocks(pr) && !pr.dp->host.phases.empty() &&
+               !pr.dp->host.phases.empty() && hs.max_count > kDirectMaxBytes &&
                hs.total_bytes >= (unsigned long long)kTiledMinMeanBytesIntoT * P2;
     pr.tiled_final = pr.tiled && hs.total_bytes >= (unsigned long long)kTiledMinMeanBytes * P2 && hs.short_blocks * 4 <= P2;
     pr.ds = data_sizes_for(pr.dp->host, hs.max_count, hs.total_chunks, pr.fused, pr.staggered, pr.exact_t, pr.t_chunks,

@@ -49,7 +49,7 @@ struct Status {
     unsigned long long send_extent;    // max over non-empty blocks of sdispls + count: bytes of sendbuf that hold blocks
     unsigned long long t_chunks;       // exact-size T: chunks stored into T over all phases
     unsigned long long short_blocks;   // blocks of fewer than kShortBlockBytes bytes, empty ones included
-    unsigned long long windows;        // with blocks of more than kShortBlockBytes: most bytes that one receiver gets from
+    unsigned long long windows;        // with blocks of more than kWindowMinBytes: most bytes that one receiver gets from
                                        // kValTile aligned neighbouring senders (high half) and one sender sends to as many
                                        // receivers (low half); blocks count up to kWindowBlock
     unsigned long long cls_chunks[kMaxClasses];   // exact-size T: chunks of every class (f, y), summed by the validation pass
@@ -229,14 +229,14 @@ __global__ void __launch_bounds__(256) k_build_hops(const PlanScalars pl, int32_
 // them up: no kernel to clear the sums, none to fold the rows, no copy of the result (see run_validate; P = 256, r = 4
 // 138 -> 117 us per call with the above).
 // The first two waves also sum the tile's columns and rows; the largest sums say whether long blocks lie side by side
-// (rows_balanced).  Not before a block of more than 256 bytes was seen: shorter ones, which k_hop_direct takes, cannot make
-// a window that counts.
+// (clustered).  Not before a block of more than kWindowMinBytes was seen: problems of shorter ones only do not ask.
 // ------------------------------------------------------------------------------------------
 constexpr int kValTile = 64;
 constexpr int kValPartial = 8;              // 64-bit words per workgroup in the partial-result array
 constexpr int kValCopies = 32;
 constexpr int kValFoldRows = 64, kValFoldClasses = 24;      // most workgroups and classes that the host folds
 constexpr int kShortBlockBytes = 256;       // below this a block is mostly edges to the destination-tiled hop
+constexpr int kWindowMinBytes = 64;
 constexpr int kWindowBlock = 1 << 25;       // kValTile of them fit 32 bits
 // the larger ones of two pairs of sums (Status.windows)
 __host__ __device__ inline unsigned long long max_windows(unsigned long long a, unsigned long long b) {
@@ -328,7 +328,7 @@ __global__ void __launch_bounds__(1024) k_validate(const int32_t* __restrict__ s
                 tile[a][tx] = c;
             }
         }
-        if (mx > kShortBlockBytes) long_seen = 1;
+        if (mx > kWindowMinBytes) long_seen = 1;
         __syncthreads();
         if (recvcounts) {
             for (int a0 = ty; a0 < kValTile; a0 += 4 * ny) {

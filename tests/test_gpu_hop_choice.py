@@ -1,6 +1,6 @@
 """Which kernel a one-kernel phase runs (Algorithm "TuNA", lines 15-20 as one hop).  Blocks of up to 256 bytes: the
-direct hop, which finds them itself.  Blocks of up to 64 KiB, all rounds of a phase at once: the row hop, which does
-so too -- except where the destination-tiled hop can run and is the faster one.  That one needs dense receive
+direct hop, which finds them itself, unless the payload is large and they are longer than 64 bytes.  Those and blocks of
+up to 64 KiB, all rounds of a phase at once: the row hop, which finds them too -- except where the destination-tiled hop can run and is the faster one.  That one needs dense receive
 regions and data at least word-granular; for a schedule's last phase, whose blocks all go into R, blocks that are
 mostly interior (mean of 700 bytes or more, at most a quarter of them under 256 bytes); for the phases before it,
 which store whole chunks into T, a mean block of 512 bytes or more.  A plan, which has paid for its metadata, keeps
@@ -197,4 +197,54 @@ def test_hop_of_a_call_by_payload(tuna, P, mean, radix, want):
     assert torch.equal(*results)
     assert st.hop_kernels == {R: tuna.TUNA_HOP_ROWS, T: tuna.TUNA_HOP_TILED}[want], st.hop_kernels
     del results
+    tuna.tuna_release()
+
+
+@pytest.mark.parametrize("P,longest,quantum,radix,opts,call,plan_kernel", [
+    (1024, 200, 1, 16, {}, D, D), (1536, 200, 1, 16, {}, R, R),            # 100 and 225 MiB in three phases
+    (2048, 60, 4, 16, {}, D, D),                                          # blocks of up to 64 bytes, whatever the payload
+    (1536, 128, 16, 1536, {}, D, D), (2048, 144, 16, 2048, {}, R, R),     # one phase: 144 and 288 MiB, chunk-granular
+    (2048, 200, 1, 2048, {}, D, D),                                       # and 400 MiB, byte-granular
+    (2048, 256, 4, 4, {"staggered": 1}, E, E), (2048, 200, 1, 4, {"staggered": 1}, D, D),
+    (1024, 256, 4, 32, {"block_count": 9}, D, D), (1536, 256, 4, 32, {"block_count": 9}, E, E),
+    (512, 256, 4, 512, {"to": 3}, D, E), (512, 256, 4, 16, {"from": 3}, D, E), (512, 256, 4, 512, {"from": 3}, D, D),
+    (512, 256, 4, 16, {"share": 64}, D, D), (512, 64, 4, 512, {"to": 3}, D, D)])
+def test_hop_of_short_blocks(tuna, P, longest, quantum, radix, opts, call, plan_kernel):
+    counts = wl.counts_uniform_elements(P, P + longest, longest // quantum, quantum)
+    i = np.arange(P)
+    if "to" in opts:                                        # one receiver, one sender, one pair in so many
+        counts = np.where(np.broadcast_to(i[None, :] == opts["to"], (P, P)), longest, 0)
+    if "from" in opts:
+        counts = np.where(np.broadcast_to(i[:, None] == opts["from"], (P, P)), longest, 0)
+    if "share" in opts:
+        counts = np.where((i[:, None] * 37 + i[None, :] * 11) % opts["share"] == 0, longest, 0)
+    Q = 16 if "staggered" in opts else 0
+    lay, send, meta, recv = _device_problem(P, counts)
+    args = (send, meta[0], meta[1], recv, meta[2], meta[3], P, Q, radix, radix)
+    print("hop of short blocks", P, longest, quantum, radix, opts, lay.payload_bytes >> 20, "MiB", flush=True)
+    bit = {E: tuna.TUNA_HOP_ENGINE, D: tuna.TUNA_HOP_DIRECT, R: tuna.TUNA_HOP_ROWS}
+
+    def options(mode):
+        o = tuna.tuna_opts_init()
+        o.mode, o.t_layout = mode, tuna.TUNA_T_EXACT
+        if mode == tuna.TUNA_MODE_FUSED:
+            o.staggered, o.block_count = opts.get("staggered", 0), opts.get("block_count", 0)
+        return o
+
+    assert tuna.tuna_alltoallv_ex(None, *args, options(tuna.TUNA_MODE_STAGED)) == 0
+    torch.cuda.synchronize()
+    want = recv.clone()
+    recv.zero_()
+    assert tuna.tuna_alltoallv_ex(None, *args, options(tuna.TUNA_MODE_FUSED)) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(recv, want) and tuna.tuna_get_stats().hop_kernels == bit[call]
+    rc, plan = tuna.tuna_alltoallv_init_ex(None, *args, options(tuna.TUNA_MODE_FUSED))
+    assert rc == 0, tuna.tuna_strerror(rc)
+    try:
+        recv.zero_()
+        assert tuna.tuna_start(plan) == 0
+        torch.cuda.synchronize()
+        assert torch.equal(recv, want) and tuna.tuna_get_stats().hop_kernels == bit[plan_kernel]
+    finally:
+        assert tuna.tuna_plan_free(plan) == 0
     tuna.tuna_release()
