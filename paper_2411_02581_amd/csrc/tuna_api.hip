@@ -1374,8 +1374,8 @@ size_t one_pass_meta_bytes(const Prepared& pr) {
            (hld ? hop_bytes_for(pr.P, hld) : 0) + self_meta_bytes(pr);
 }
 
-// An immediate call whose phases are all one-kernel hops of blocks of up to kRowsMaxBytes, all rounds of a phase at once:
-// done in one pass whatever its payload, k_hop_direct or k_hop_rows finding the blocks themselves.  (What is left of the
+// An immediate call whose phases are all one-kernel hops that k_hop_direct or k_hop_rows moves, all rounds of a phase at
+// once: done in one pass whatever its payload, k_hop_direct or k_hop_rows finding the blocks themselves.  (What is left of the
 // metadata is not worth a second stream: with a size exchange and the scans of T per phase on one, calls were 2 to 7 %
 // slower with phases of 64 MiB to 2 GiB and the same at 14 GiB.)
 bool runs_direct(const Prepared& pr) {

@@ -1163,8 +1163,8 @@ __global__ void __launch_bounds__(256) k_resolve_hop(const ResolveArgs a) {
 // resolved it in two overlapping accesses of 8 or 4 bytes, or byte by byte.  Only bytes of the block are read.
 //   Measured per call against one thread per block (up to 64 bytes) and the engine (above), both from hop arrays:
 // 33 M blocks of 64 bytes and as many empty ones (P = 8192, linear) 6.91 -> 1.57 ms; uniform [0, 16] B, P = 2048, two
-// phases 0.44 -> 0.27 ms; all blocks 256 bytes, P = 2048 as 64 x 32, four phases 1.73 -> 1.40 ms; uniform [0, 248] B,
-// P = 4096, linear 1.64 -> 1.24 ms.
+// phases 0.44 -> 0.27 ms; uniform [0, 248] B, P = 4096, linear 1.64 -> 1.24 ms.  Blocks of more than 64 bytes and payloads
+// beyond the caches are better off in k_hop_rows (block_kernel).
 //   TALL tiles (16 receivers x few segments, LPB = 1 and 4) share the lines of S and sdispls between receivers: that pays
 // when a round has few blocks, as in the linear schedule (64-byte blocks: 1.57 against 2.0 ms).  With many blocks per
 // round neighbouring receivers read other rows, and long rows of one receiver are better (uniform [0, 16] B, two phases:
@@ -1480,7 +1480,8 @@ __device__ __forceinline__ int tiled_pieces(unsigned long long a, int n, bool ha
 }
 
 // ------------------------------------------------------------------------------------------
-// k_hop_rows: a one-kernel phase of blocks of up to 64 KiB, any sizes, alignment and granularity.  One wave takes
+// k_hop_rows: a one-kernel phase of blocks of up to 64 KiB, any alignment and granularity, and any sizes that leave its
+// waves balanced (rows_balanced).  One wave takes
 // `segs` neighbouring segments of one receiver, about 7 KB of payload: lane i finds block s0 + i (source, destination,
 // bytes), a wave scan lays the blocks out as rows of aligned 16-byte pieces of the destination (tiled_pieces), and the
 // wave moves 8 pieces per lane at a time.  What the destination-tiled hop needs a resolve pass, a layout pass and unit
@@ -1496,7 +1497,7 @@ __device__ __forceinline__ int tiled_pieces(unsigned long long a, int n, bool ha
 //   Measured against the destination-tiled hop and the engine's with their metadata kernels: per call, 16 GiB of 1 KiB
 // blocks 6.75 -> 6.35 ms linear and 22.9 -> 22.1 ms at r = 8; 512-byte blocks on average, byte-granular, P = 1000, per
 // start 333 -> 214 us; uniform [0, 512] B, P = 2048, r = 46 1.24 -> 0.99 ms; 512-byte blocks, P = 2048, r = 16
-// 2.57 -> 2.05 ms.  8 pieces per lane against 4: -4 to -9 %.  7000 bytes and not 8192: a wave whose pieces do not fit
+// 2.57 -> 2.05 ms; 256-byte blocks, P = 2048 as 64 x 32, r = 16 1.73 -> 1.25 ms.  8 pieces per lane against 4: -4 to -9 %.  7000 bytes and not 8192: a wave whose pieces do not fit
 // into one step takes a second, nearly empty one.  Streaming stores against cached ones: -8 to -15 %; streaming loads
 // only where blocks are whole lines (512 bytes: -5 %; 1 KiB blocks at 4-byte alignment: up to +6 %).  Four receivers x
 // the same segments per workgroup instead of one receiver: 1 KiB blocks +3 %; rows of workgroups cut so that one XCD sees
