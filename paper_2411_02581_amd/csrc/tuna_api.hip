@@ -799,8 +799,11 @@ bool clustered(const Prepared& pr, double times) {
 // 4 neighbours 0.73 / 2.09 ms).  What can lie side by side in a phase: a receiver's blocks from neighbouring senders,
 // and in a phase before the last also a sender's blocks for others.  Windows of 64 of them hold 1.3 times their mean with
 // uniform sizes, 2 to 3.6 times with Zipf sizes, and 4 times where rows were still as fast (256 ranks, 4 neighbours,
-// 104 / 100 us); everything above was 8 times and more.  (Long blocks of one sender that are as far apart as the radix
-// meet in the first phase without showing in a window: 16 KiB at every 32nd distance, r = 32, 587 / 833 us.)
+// 104 / 100 us); everything above was 8 times and more.  Long blocks of one sender that are as far apart as the radix
+// meet in the first phase without showing in a window (16 KiB at every 32nd distance, P = 1024, r = 32 0.58 / 0.84 ms): in
+// schedules of several phases a wave of longest blocks only has to stay below 160 KiB (Zipf sizes: 131; byte-granular,
+// which cost the engine more, 288, Zipf 196; such blocks of 224 KiB a wave still take 0.73 / 0.97 ms), in a call from 256
+// MiB on.
 // The longest wave alone takes about 1.5 us per 8 KiB, and it can start late.  A call has 40 us and more to spare, what the
 // engine's metadata kernels take: 1 KiB from each of 1024 ranks to one 109 / 74 us, 64 KiB from one to each 109 / 91, Zipf
 // sizes up to 16 KiB among 96 ranks (103 KiB in one wave) 78 / 53, up to 64 KiB among 256 129 / 109.  A plan has those
@@ -809,7 +812,8 @@ bool clustered(const Prepared& pr, double times) {
 // cost the engine more, up to 64 KiB among 512 (460 MB) 239 / 212, up to 16 KiB among 256 (39 MB, r = 8) 60 / 70.
 bool rows_balanced(const Prepared& pr) {
     const double total = (double)pr.total_bytes;
-    const double longest = std::min(fullest_window(pr), (double)rows_segs(pr) * (double)pr.max_count);
+    const double apart = (double)rows_segs(pr) * (double)pr.max_count, longest = std::min(fullest_window(pr), apart);
+    if (pr.dp->host.phases.size() > 1 && apart > (pr.gran < 4 ? 294912.0 : 163840.0) && (pr.for_plan || total > 268435456.0)) return false;
     const bool even = !clustered(pr, 6.0);
     if (pr.for_plan) return longest <= kRowsEvenBytes + (even ? total / (pr.gran < 4 ? 1600.0 : 6144.0) : 0.0);
     return longest <= (even ? 196608.0 + total / 512.0 : 81920.0);

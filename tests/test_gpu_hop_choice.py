@@ -200,6 +200,36 @@ def test_hop_of_a_call_by_payload(tuna, P, mean, radix, want):
     tuna.tuna_release()
 
 
+@pytest.mark.parametrize("P,radix,want,plan_want", [(1024, 32, E, E), (1024, 1024, R, R), (512, 32, R, E)])
+def test_hop_of_long_blocks_a_radix_apart(tuna, P, radix, want, plan_want):
+    """16 KiB at every 32nd distance: evenly spread over a rank's blocks, but one run of the first phase's at radix 32."""
+    i = np.arange(P)
+    lay, send, meta, recv = _device_problem(P, np.where((i[None, :] - i[:, None]) % 32 == 5, 16384, 4), gap=4)
+    print("long blocks a radix apart", P, radix, flush=True)
+    args = (send, meta[0], meta[1], recv, meta[2], meta[3], P, 0, radix, radix)
+    o = tuna.tuna_opts_init()
+    o.mode, o.t_layout = tuna.TUNA_MODE_STAGED, tuna.TUNA_T_EXACT
+    assert tuna.tuna_alltoallv_ex(None, *args, o) == 0
+    torch.cuda.synchronize()
+    reference = recv.clone()
+    recv.zero_()
+    o.mode = tuna.TUNA_MODE_FUSED
+    assert tuna.tuna_alltoallv_ex(None, *args, o) == 0
+    torch.cuda.synchronize()
+    bit = {E: tuna.TUNA_HOP_ENGINE, R: tuna.TUNA_HOP_ROWS}
+    assert torch.equal(recv, reference) and tuna.tuna_get_stats().hop_kernels == bit[want]
+    rc, plan = tuna.tuna_alltoallv_init_ex(None, *args, o)
+    assert rc == 0
+    try:
+        recv.zero_()
+        assert tuna.tuna_start(plan) == 0
+        torch.cuda.synchronize()
+        assert torch.equal(recv, reference) and tuna.tuna_get_stats().hop_kernels == bit[plan_want]
+    finally:
+        assert tuna.tuna_plan_free(plan) == 0
+    tuna.tuna_release()
+
+
 @pytest.mark.parametrize("P,longest,quantum,radix,opts,call,plan_kernel", [
     (1024, 200, 1, 16, {}, D, D), (1536, 200, 1, 16, {}, R, R),            # 100 and 225 MiB in three phases
     (2048, 60, 4, 16, {}, D, D),                                          # blocks of up to 64 bytes, whatever the payload
