@@ -158,11 +158,11 @@ def test_which_hop_runs(tuna, name, radix):
         assert tuna.tuna_plan_free(plan) == 0
 
 
-def _device_problem(P, counts, gap=0):
+def _device_problem(P, counts, gap=0, permute_seed=None):
     """A problem too large for the oracle's test time: its payload is made on the device, its reference is the call with
     three-stage phases (another set of kernels)."""
     dev = "cuda:0"
-    lay = wl.make_layout(np.ascontiguousarray(counts, dtype=np.int32), gap=gap)
+    lay = wl.make_layout(np.ascontiguousarray(counts, dtype=np.int32), gap=gap, permute_seed=permute_seed)
     meta = [torch.from_numpy(a).to(dev) for a in (lay.sendcounts, lay.sdispls, lay.recvcounts, lay.rdispls)]
     gen = torch.Generator(device=dev)
     gen.manual_seed(P)
@@ -235,6 +235,8 @@ def test_hop_of_long_blocks_a_radix_apart(tuna, P, radix, want, plan_want):
     (2048, 60, 4, 16, {}, D, D),                                          # blocks of up to 64 bytes, whatever the payload
     (1536, 128, 16, 1536, {}, D, D), (2048, 144, 16, 2048, {}, R, R),     # one phase: 144 and 288 MiB, chunk-granular
     (2048, 200, 1, 2048, {}, D, D),                                       # and 400 MiB, byte-granular
+    (1536, 200, 1, 4, {"Q": 32, "gap": 3, "permute": 7}, R, R), (1536, 256, 4, 8, {"slots": 1, "gap": 8, "permute": 8}, R, R),
+    (1536, 128, 128, 12, {"Q": 128}, R, R),                               # whole lines
     (2048, 256, 4, 4, {"staggered": 1}, E, E), (2048, 200, 1, 4, {"staggered": 1}, D, D),
     (1024, 256, 4, 32, {"block_count": 9}, D, D), (1536, 256, 4, 32, {"block_count": 9}, E, E),
     (512, 256, 4, 512, {"to": 3}, D, E), (512, 256, 4, 16, {"from": 3}, D, E), (512, 256, 4, 512, {"from": 3}, D, D),
@@ -248,15 +250,15 @@ def test_hop_of_short_blocks(tuna, P, longest, quantum, radix, opts, call, plan_
         counts = np.where(np.broadcast_to(i[:, None] == opts["from"], (P, P)), longest, 0)
     if "share" in opts:
         counts = np.where((i[:, None] * 37 + i[None, :] * 11) % opts["share"] == 0, longest, 0)
-    Q = 16 if "staggered" in opts else 0
-    lay, send, meta, recv = _device_problem(P, counts)
+    Q = 16 if "staggered" in opts else opts.get("Q", 0)
+    lay, send, meta, recv = _device_problem(P, counts, opts.get("gap", 0), opts.get("permute"))
     args = (send, meta[0], meta[1], recv, meta[2], meta[3], P, Q, radix, radix)
     print("hop of short blocks", P, longest, quantum, radix, opts, lay.payload_bytes >> 20, "MiB", flush=True)
     bit = {E: tuna.TUNA_HOP_ENGINE, D: tuna.TUNA_HOP_DIRECT, R: tuna.TUNA_HOP_ROWS}
 
     def options(mode):
         o = tuna.tuna_opts_init()
-        o.mode, o.t_layout = mode, tuna.TUNA_T_EXACT
+        o.mode, o.t_layout = mode, tuna.TUNA_T_SLOTS if "slots" in opts else tuna.TUNA_T_EXACT
         if mode == tuna.TUNA_MODE_FUSED:
             o.staggered, o.block_count = opts.get("staggered", 0), opts.get("block_count", 0)
         return o
