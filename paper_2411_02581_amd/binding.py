@@ -32,7 +32,7 @@ TUNA_MAX_PHASES = 64
 TUNA_RADIX_AUTO = 0
 TUNA_MODE_AUTO, TUNA_MODE_STAGED, TUNA_MODE_FUSED = 0, 1, 2
 TUNA_T_SLOTS, TUNA_T_EXACT, TUNA_T_AUTO = 0, 1, 2
-TUNA_HOP_ENGINE, TUNA_HOP_TILED, TUNA_HOP_DIRECT, TUNA_HOP_ROWS = 1, 2, 4, 8
+TUNA_HOP_ENGINE, TUNA_HOP_TILED, TUNA_HOP_DIRECT, TUNA_HOP_ROWS, TUNA_HOP_LONG = 1, 2, 4, 8, 16
 
 EXPORTS = ("tuna_alltoallv", "tuna_alltoallv_hier", "tuna_alltoallv_noalloc", "tuna_alltoallv_ex", "tuna_alltoallv_init_ex",
            "tuna_opts_init", "tuna_ctx_create", "tuna_ctx_destroy", "tuna_ctx_get_stats", "tuna_build_id", "tuna_debug_phase_sizes", "tuna_workspace_bytes", "tuna_set_workspace",

@@ -422,11 +422,11 @@ void mark(Ctx* c, hipStream_t s, int cat, int phase) {
 // One-shot grid over an upper bound of wave units (4 per workgroup); waves past the device-side
 // unit count exit immediately.
 // Dynamic LDS that leaves room for `resident` workgroups of a copy kernel per compute unit (one wave
-// per SIMD each; 8 is the kernels' own limit).  Nothing uses the memory: it only caps the occupancy.
-// static_lds: the kernel's own LDS bytes.
-size_t occupancy_padding(int resident, size_t static_lds) {
+// per SIMD each; 8 is the kernels' own limit, 32 for workgroups of one wave).  Nothing uses the memory: it only caps the
+// occupancy.  static_lds: the kernel's own LDS bytes.
+size_t occupancy_padding(int resident, size_t static_lds, int limit = 8) {
     constexpr size_t kLdsPerCu = 160 * 1024;
-    if (resident >= 8) return 0;
+    if (resident >= limit) return 0;
     // more than 1 / (resident + 1) of the LDS each, rounded up to 1 KiB: resident + 1 workgroups no longer fit
     const size_t want = (kLdsPerCu / (size_t)(resident + 1) / 1024 + 1) * 1024;
     return want > static_lds ? want - static_lds : 0;
@@ -572,6 +572,7 @@ struct Prepared {
     int max_count = 0;
     unsigned long long total_bytes = 0;
     unsigned long long windows = 0;     // Status.windows
+    unsigned long long short_blocks = 0;
     DataSizes ds{};
     v4u* stage_s = nullptr;
     v4u* stage_r = nullptr;
@@ -848,6 +849,27 @@ int block_kernel(const Prepared& pr) {
 }
 bool small_blocks(const Prepared& pr) { return block_kernel(pr) == TUNA_HOP_DIRECT; }
 bool row_blocks(const Prepared& pr) { return block_kernel(pr) == TUNA_HOP_ROWS; }
+// Room for a phase's units: as much as two lists of the other hops' units take (a call has them side by side and uses
+// neither), and more than there are of these -- a block of n bytes has at most (n + 127) / kLongUnit + 1, the mean of all
+// is 16 KiB and more, and each list has one unit per 4 KiB of payload.
+size_t long_unit_cap(const Prepared& pr) { return 2 * pr.ds.unit_cap; }
+// Phases of long blocks, all rounds at once: k_long_units and k_hop_long.  The line lies at the mean of the blocks that are
+// not short; a unit is a wave however short its block is, so there must be payload for all the pairs as well.  Per call and
+// per start (p), us, the hops that would run otherwise / these:
+//   up to 512 MiB, 16.5 KiB: normal 18 KB, 100 ranks 118 / 101, 40 ranks r = 2 253 / 152, p 17 KB, 100 ranks 57 / 51, r = 2 235 / 212,
+// uniform up to 40 KB, 120 ranks as 10 x 12, r = 4 421 / 387;
+//   above, one phase, 22 KiB: uniform up to 36 KB, 400 ranks p 1031 / 1055, up to 48 KiB p 1435 / 1400, call 1536 / 1492, byte-granular p
+// 1544 / 1464, equal blocks of 32 KiB, 200 ranks 544 / 498, normal 30 KB with gaps 529 / 455, Zipf up to 1.3 MB, 300 ranks 1030 / 805;
+//   several phases, which store whole lines into T with the destination-tiled hop, 32 KiB: normal 24 KiB, 300 ranks, r = 2
+// 3255 / 3340, r = 4 2455 / 2440, 200 ranks r = 2 p 1268 / 1293, 32 KiB r = 2 1892 / 1902, 300 ranks 4270 / 4250, 40 KiB 5330 / 5225.
+bool long_blocks(const Prepared& pr) {
+    if (!pr.fused || pr.staggered || pr.block_count != 0 || pr.debug_sizes || pr.P > kLongMaxRanks) return false;
+    const size_t phases = pr.dp->host.phases.size();
+    if (!phases || phases > kPlaceMaxPhases) return false;
+    const double pairs = (double)pr.P * (double)pr.P, total = (double)pr.total_bytes;
+    const double line = total <= 536870912.0 ? 16896.0 : phases == 1 ? 22528.0 : 32768.0;
+    return total >= 16384.0 * pairs && total > line * (pairs - (double)pr.short_blocks);
+}
 constexpr int kTiledMinMeanBytes = 700;    // see prepare_sizes
 constexpr int kTiledMinMeanBytesIntoT = 512;
 
@@ -878,6 +900,7 @@ int prepare_sizes(Prepared& pr, int dense_option, hipStream_t s, Status& hs, boo
     pr.max_count = hs.max_count;
     pr.total_bytes = hs.total_bytes;
     pr.windows = hs.windows;
+    pr.short_blocks = hs.short_blocks;
     pr.user_limit = (unsigned long long)(uintptr_t)pr.sendbuf + hs.send_extent;
     // The destination-tiled hop: one-kernel phases over all rounds at once, receive regions dense (validation
     // flag), word- or chunk-granular data (whole-line data is as fast in the copy engine, byte-granular data
@@ -946,11 +969,12 @@ bool phase_stores_lines(const Prepared& pr, size_t i) {
 bool phase_is_rows(const Prepared& pr, size_t i) { return row_blocks(pr) && !(pr.for_plan && phase_stores_lines(pr, i)); }
 // The other phases whose stores are mostly whole lines run k_copy_tiled.  (T in slots keeps the copy engine: its slot
 // tails are filled up to the line by a path of their own.)
-bool phase_is_tiled(const Prepared& pr, size_t i) { return phase_stores_lines(pr, i) && !phase_is_rows(pr, i); }
+bool phase_is_tiled(const Prepared& pr, size_t i) { return phase_stores_lines(pr, i) && !phase_is_rows(pr, i) && !long_blocks(pr); }
 
 // The payload kernel of phase i (TUNA_HOP_*; 0: three stages), and those of all phases.
 int phase_kernel(const Prepared& pr, size_t i) {
     if (!phase_is_one_kernel(pr, pr.dp->host.phases[i])) return 0;
+    if (long_blocks(pr)) return TUNA_HOP_LONG;
     if (small_blocks(pr)) return TUNA_HOP_DIRECT;
     if (phase_is_rows(pr, i)) return TUNA_HOP_ROWS;
     return phase_is_tiled(pr, i) ? TUNA_HOP_TILED : TUNA_HOP_ENGINE;
@@ -1146,6 +1170,35 @@ int launch_direct(const Prepared& pr, size_t i, const HopDev& hop, int seg_lo, i
     return TUNA_OK;
 }
 
+// A phase of long blocks: its units into `units` (long_unit_cap of them), their number and the phase's totals into the
+// status block.  The first phase takes the ranks' own blocks along.
+int launch_long_units(const Prepared& pr, size_t i, int4* units, hipStream_t s) {
+    LongArgs a{};
+    a.d.r = resolve_args(pr, i, nullptr, HopDev{});
+    a.d.user_limit = pr.user_limit;
+    a.units = reinterpret_cast<ulonglong2*>(units);
+    a.count = &pr.sb.d_status->phase_units[i][0];
+    a.bytes = &pr.sb.d_status->phase_bytes[i]; a.chunks = &pr.sb.d_status->phase_chunks[i];
+    a.own = i == 0 ? 1 : 0;
+    const dim3 grid((unsigned)std::max(1, std::min(16, kLongMaxRanks / pr.P)), (unsigned)pr.P);
+    if (pr.exact_kernels) hipLaunchKernelGGL(k_long_units<true>, grid, dim3(kScanThreads), 0, s, a);
+    else hipLaunchKernelGGL(k_long_units<false>, grid, dim3(kScanThreads), 0, s, a);
+    HIPCHK(hipGetLastError());
+    return TUNA_OK;
+}
+// and its payload: `known` units, or as many as the status block says, launched for what they will about be
+int launch_hop_long(const Prepared& pr, size_t i, const int4* units, size_t known, hipStream_t s) {
+    const double share = (double)pr.dp->host.phases[i].nseg * (double)pr.P + (i == 0 ? (double)pr.P : 0.0);
+    const double moved = (double)pr.total_bytes / ((double)pr.P * (double)pr.P) * share;
+    const unsigned grid = known ? (unsigned)known : (unsigned)(moved / kLongUnit + share + 1.0);
+    const unsigned int* count = known ? nullptr : &pr.sb.d_status->phase_units[i][0];
+    const ulonglong2* u = reinterpret_cast<const ulonglong2*>(units);
+    if (moved >= kLongStreamBytes) hipLaunchKernelGGL(k_hop_long<true>, dim3(grid), dim3(kWave), occupancy_padding(kLongResident, 0, 32), s, u, count, (unsigned)known, pr.T);
+    else hipLaunchKernelGGL(k_hop_long<false>, dim3(grid), dim3(kWave), occupancy_padding(kLongResident, 0, 32), s, u, count, (unsigned)known, pr.T);
+    HIPCHK(hipGetLastError());
+    return TUNA_OK;
+}
+
 // one-kernel phase: where every block comes from and goes to, once per phase instead of once per wave
 int launch_resolve(const Prepared& pr, size_t i, const int32_t* nxt, const HopDev& hop, hipStream_t s) {
     const PhaseHost& ph = pr.dp->host.phases[i];
@@ -1292,6 +1345,13 @@ int launch_phase_data(const Prepared& pr, size_t i, const LayoutDev& Ls, const L
         }
         int rc;
         const int kernel = phase_kernel(pr, i);
+        if (kernel == TUNA_HOP_LONG) {
+            if (unit_cap) rc = launch_hop_long(pr, i, Lr.units, unit_cap, s);
+            else rc = TUNA_OK;
+            if (rc != TUNA_OK) return rc;
+            mark(pr.ctx, s, kCatPack, (int)i);
+            continue;
+        }
         if (kernel == TUNA_HOP_DIRECT) {
             rc = launch_direct(pr, i, hop, a.seg_lo, a.seg_hi, nullptr, s);
             if (rc != TUNA_OK) return rc;
@@ -1383,7 +1443,7 @@ size_t one_pass_meta_bytes(const Prepared& pr) {
 // metadata is not worth a second stream: with a size exchange and the scans of T per phase on one, calls were 2 to 7 %
 // slower with phases of 64 MiB to 2 GiB and the same at 14 GiB.)
 bool runs_direct(const Prepared& pr) {
-    return pr.fused && !pr.staggered && pr.block_count == 0 && (small_blocks(pr) || row_blocks(pr)) && !pr.dp->host.phases.empty() &&
+    return pr.fused && !pr.staggered && pr.block_count == 0 && (small_blocks(pr) || row_blocks(pr) || long_blocks(pr)) && !pr.dp->host.phases.empty() &&
            pr.dp->host.phases.size() <= kPlaceMaxPhases;
 }
 
@@ -1392,7 +1452,7 @@ bool runs_direct(const Prepared& pr) {
 constexpr int kPairsMinRadix = 16;          // neighbours 64 bytes apart and more
 int launch_t_places(Prepared& pr, hipStream_t s) {
     if (!pr.exact_t) return TUNA_OK;
-    if (pr.dp->host.phases[0].r >= kPairsMinRadix) pr.pairs = reinterpret_cast<uint2*>(pr.hop.dst);
+    if (pr.dp->host.phases[0].r >= kPairsMinRadix && pr.hop.dst) pr.pairs = reinterpret_cast<uint2*>(pr.hop.dst);
     const PlanHost& pl = pr.dp->host;
     PlaceArgs a{};
     a.P = pr.P; a.Q = pr.Q; a.N = pr.N; a.sendcounts = pr.sendcounts; a.recvcounts = pr.recvcounts; a.x = exact_t_of(pr, 0);
@@ -1464,9 +1524,10 @@ int run_one_pass(Prepared& pr, void* mbase, size_t mbytes, void* dbase, hipStrea
         HIPCHK(hipGetLastError());
     }
     mark(pr.ctx, s, kCatPrepare, -1);
-    rc = launch_self_metadata(pr, s);
+    const bool longs = direct && long_blocks(pr);             // the first phase takes the own blocks along
+    rc = longs ? TUNA_OK : launch_self_metadata(pr, s);
     if (rc != TUNA_OK) return rc;
-    rc = launch_self_copy(pr, s);
+    rc = longs ? TUNA_OK : launch_self_copy(pr, s);
     if (rc != TUNA_OK) return rc;
     mark(pr.ctx, s, kCatSelf, -1);
 
@@ -1480,6 +1541,17 @@ int run_one_pass(Prepared& pr, void* mbase, size_t mbytes, void* dbase, hipStrea
         rc = launch_t_places(pr, s);
         if (rc != TUNA_OK) return rc;
         mark(pr.ctx, s, kCatMeta, 0);
+        if (longs) {
+            for (size_t i = 0; i < pl.phases.size(); ++i) {
+                rc = launch_long_units(pr, i, mb.Ls.units, s);
+                if (rc != TUNA_OK) return rc;
+                mark(pr.ctx, s, kCatMeta, (int)i);
+                rc = launch_hop_long(pr, i, mb.Ls.units, 0, s);
+                if (rc != TUNA_OK) return rc;
+                mark(pr.ctx, s, kCatPack, (int)i);
+            }
+            return TUNA_OK;
+        }
         const size_t room = (size_t)pr.hop.ld;
         size_t used = 0;
         PhaseParts parts{};
@@ -1699,6 +1771,8 @@ void carve_full_layout(Carver& cv, int P, size_t unit_cap, LayoutDev& L) {
     L.units = cv.take<int4>(unit_cap);
 }
 
+size_t plan_unit_cap(const Prepared& pr) { return long_blocks(pr) ? long_unit_cap(pr) : pr.ds.unit_cap; }
+
 // Metadata memory of a plan: two size matrices, the per-rank byte sums, per phase two complete layouts.
 size_t plan_meta_bytes(const Prepared& pr) {
     const PlanHost& pl = pr.dp->host;
@@ -1706,7 +1780,7 @@ size_t plan_meta_bytes(const Prepared& pr) {
     size_t hop_bytes = 0;
     for (const auto& ph : pl.phases)
         if (phase_is_one_kernel(pr, ph)) hop_bytes += hop_bytes_for(pr.P, hop_ld_for(ph.nseg));
-    return 2 * align_up(P2 * 4) + align_up((size_t)pr.P * 8) + pl.phases.size() * 2 * layout_bytes_for(pr.P, pr.ds.unit_cap) +
+    return 2 * align_up(P2 * 4) + align_up((size_t)pr.P * 8) + pl.phases.size() * 2 * layout_bytes_for(pr.P, plan_unit_cap(pr)) +
            (pr.exact_t ? exact_t_meta_bytes_for(pl, true) : 0) + hop_bytes + self_meta_bytes(pr);
 }
 
@@ -1726,8 +1800,8 @@ bool plan_carve_meta(Plan* plan, void* meta, size_t mbytes, int32_t** cur, int32
     pr.rank_bytes = cm.take<unsigned long long>(P);
     plan->Ls.resize(nph); plan->Lr.resize(nph); plan->units.assign(nph, 0);
     for (size_t i = 0; i < nph; ++i) {
-        carve_full_layout(cm, P, pr.ds.unit_cap, plan->Ls[i]);
-        carve_full_layout(cm, P, pr.ds.unit_cap, plan->Lr[i]);
+        carve_full_layout(cm, P, plan_unit_cap(pr), plan->Ls[i]);
+        carve_full_layout(cm, P, plan_unit_cap(pr), plan->Lr[i]);
     }
     if (pr.exact_t) carve_exact_t(cm, pl, true, pr);
     plan->hop.assign(nph, HopDev{});
@@ -1749,14 +1823,24 @@ int plan_build_metadata(Plan* plan, void* meta, size_t mbytes, hipStream_t s, bo
     int rc = upload_cbase(pr, s);
     if (rc != TUNA_OK) return rc;
     const dim3 grot((unsigned)((P + 255) / 256), (unsigned)((P + kExchangeRanks - 1) / kExchangeRanks));
-    hipLaunchKernelGGL(k_rotate_init, grot, dim3(256), 0, s, pr.sendcounts, cur, P, pr.Q, pr.N, 0);
-    HIPCHK(hipGetLastError());
-    rc = launch_self_metadata(pr, s);
+    const bool longs = long_blocks(pr);
+    if (longs) {
+        // the totals and unit counts that k_long_units adds to
+        constexpr int kCounters = (int)((offsetof(Status, phase_units) + sizeof(Status::phase_units) - offsetof(Status, phase_bytes)) / 8);
+        hipLaunchKernelGGL(k_zero64, dim3((kCounters + 255) / 256), dim3(256), 0, s, pr.sb.d_status->phase_bytes, kCounters);
+        HIPCHK(hipGetLastError());
+        rc = launch_t_places(pr, s);
+    } else {
+        hipLaunchKernelGGL(k_rotate_init, grot, dim3(256), 0, s, pr.sendcounts, cur, P, pr.Q, pr.N, 0);
+        HIPCHK(hipGetLastError());
+        rc = launch_self_metadata(pr, s);
+    }
     if (rc != TUNA_OK) return rc;
     if (with_marks) mark(pr.ctx, s, kCatPrepare, -1);
     if (pr.debug_sizes) HIPCHK(hipMemcpyAsync(pr.debug_sizes, cur, P2 * 4, hipMemcpyDeviceToHost, s));
     for (size_t i = 0; i < nph; ++i) {
-        rc = launch_phase_metadata(pr, i, cur, nxt, plan->Ls[i], plan->Lr[i], plan->hop[i], s);
+        rc = longs ? launch_long_units(pr, i, plan->Lr[i].units, s)
+                   : launch_phase_metadata(pr, i, cur, nxt, plan->Ls[i], plan->Lr[i], plan->hop[i], s);
         if (rc != TUNA_OK) return rc;
         if (with_marks) mark(pr.ctx, s, kCatMeta, (int)i);
         if (pr.debug_sizes) HIPCHK(hipMemcpyAsync(pr.debug_sizes + (i + 1) * P2, nxt, P2 * 4, hipMemcpyDeviceToHost, s));
@@ -1767,7 +1851,7 @@ int plan_build_metadata(Plan* plan, void* meta, size_t mbytes, hipStream_t s, bo
     HIPCHK(hipMemcpyAsync(pr.sb.h_status, pr.sb.d_status, sizeof(Status), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     unsigned long long max_chunks = 0;
-    if (pr.self_engine) pr.self_units = h_status->self_units;     // exact from now on
+    if (pr.self_engine && !longs) pr.self_units = h_status->self_units;     // exact from now on
     for (size_t i = 0; i < nph; ++i) {
         const bool one = phase_is_one_kernel(pr, pl.phases[i]);
         plan->units[i] = (size_t)std::max(h_status->phase_units[i][0], one ? 0u : h_status->phase_units[i][1]);
@@ -1800,7 +1884,7 @@ void plan_carve_data(Plan* plan, void* data, size_t stage_bytes, size_t dbytes) 
 // The payload kernels of every phase, with exact grids.
 int plan_launch_data(const Plan* plan, hipStream_t s) {
     const Prepared& pr = plan->pr;
-    int rc = launch_self_copy(pr, s);
+    int rc = long_blocks(pr) ? TUNA_OK : launch_self_copy(pr, s);
     if (rc != TUNA_OK) return rc;
     mark(pr.ctx, s, kCatSelf, -1);
     const size_t nph = pr.dp->host.phases.size();

@@ -431,7 +431,7 @@ __global__ void __launch_bounds__(1024) k_validate(const int32_t* __restrict__ s
     }
     // the totals that k_phase_sums adds to (without cls_rows k_validate_finish clears them), not for a sizing query: the
     // totals there belong to the context's last call
-    if (cls_rows && clear_totals && blockIdx.x == 0 && ty == 0) st->phase_bytes[tx] = st->phase_chunks[tx] = 0;
+    if (cls_rows && clear_totals && blockIdx.x == 0 && ty == 0) st->phase_bytes[tx] = st->phase_chunks[tx] = st->phase_units[tx][0] = 0;
 }
 
 // k_zero64: n 64-bit words to zero (the class sums before a validation pass).
@@ -481,7 +481,7 @@ __global__ void __launch_bounds__(256) k_validate_finish(const unsigned long lon
         st->windows = wi;
     }
     // the totals that k_phase_sums adds to; the other paths write them whole
-    if (clear_totals && threadIdx.x < 64) st->phase_bytes[threadIdx.x] = st->phase_chunks[threadIdx.x] = 0;
+    if (clear_totals && threadIdx.x < 64) st->phase_bytes[threadIdx.x] = st->phase_chunks[threadIdx.x] = st->phase_units[threadIdx.x][0] = 0;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1647,6 +1647,149 @@ __global__ void __launch_bounds__(256) k_hop_rows(const DirectArgs a) {
 #pragma unroll
         for (int k = 0; k < CPL; ++k)
             if (act[k]) __builtin_nontemporal_store(v[k], (TUNA_GLOBAL v4u_any*)d[k]);
+    }
+}
+
+// ------------------------------------------------------------------------------------------
+// k_long_units, k_hop_long: a one-kernel phase of long blocks (long_blocks).  k_long_units cuts every block at the 128-byte
+// lines of its destination into units of 4 KiB, each written down as where it is read, where it is stored and how long it
+// is; k_hop_long moves one unit per wave and looks nothing else up before its payload.  The units are in no particular
+// order: a workgroup takes room in the list for its own, so one launch per phase is all the metadata there is.
+//   Bound by memory.  What decides is how compact the part of memory is that is under way at one time: a plain copy of 1.8
+// GiB by workgroups of four waves runs at 6.4 TB/s with 1 KiB per wave, 6.2 with 4 and 5.5 with 8; workgroups of one wave
+// reach 6.35 with 4 KiB and 6.3 with 8 KiB if only 16 and 8 of them are resident, and lose 5 to 10 % with 32 (the units
+// of 8 KiB of k_copy_tiled: 5.4).  Hence one wave per workgroup, 4 KiB, 10 resident (kLongResident, held there by unused
+// LDS; 60 ranks, up to 1 MiB, radix 2 and linear, us per call: 8 resident 1954 / 682, 10 1940 / 683, 12 1980 / 695, 16 2037 /
+// 695, 20 2087 / 698; 8 KiB, 6 resident 1984 / 666, but 200 ranks, 80 KiB 1186 against 1139).  Streaming loads from
+// kLongStreamBytes on (683 / 779; 134 MB 90 / 83, 245 MB 125 / 111).
+//   Against the engine's and the destination-tiled hop with their metadata kernels: 60 ranks, up to 1 MiB, 788 -> 683 us per
+// call (5.3 -> 5.8 TB/s, metadata and validation included), 708 -> 635 per start; 100 ranks, 200 KB, r = 10 1420 -> 1248; 200 ranks, byte-granular up to 150 KB
+// 1374 -> 1060 per start; 20 ranks, up to 200 KB (40 MB) 79-94 -> 56.
+// ------------------------------------------------------------------------------------------
+constexpr int kLongPieces = 4;
+constexpr int kLongUnit = kWave * 16 * kLongPieces;          // bytes
+constexpr int kLongMaxRanks = 512;                           // the workgroups take their room in the list one after the other
+constexpr int kLongResident = 10;                            // workgroups per compute unit
+constexpr double kLongStreamBytes = 268435456.0;
+// in a unit's y: it is not the first of its block; in either: an offset into T, which a plan has not got yet
+constexpr unsigned long long kLongAddress = (1ull << 48) - 1, kLongInside = 1ull << 62, kLongInT = 1ull << 63;
+struct LongArgs {
+    DirectArgs d;
+    ulonglong2* units;      // x: source; y: destination, bytes << 48; kLongInside, kLongInT
+    unsigned int* count;    // starts at zero
+    unsigned long long* bytes;          // of the phase (Status)
+    unsigned long long* chunks;
+    int own;                // 1: the ranks' own blocks too
+};
+template <bool DENSE>
+__global__ void __launch_bounds__(kScanThreads) k_long_units(const LongArgs a) {
+    __shared__ int s_pre[kScanThreads + 1], wsum[kScanThreads / kWave];
+    __shared__ unsigned long long s_src[kScanThreads], s_dst[kScanThreads], w_b[kScanThreads / kWave], w_c[kScanThreads / kWave];
+    __shared__ int s_n[kScanThreads];
+    __shared__ unsigned int s_base;
+    const ResolveArgs& r = a.d.r;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    const int p = blockIdx.y, nseg = r.nseg, all = nseg + a.own;
+    unsigned long long bytes = 0, chunks = 0;
+    for (int base = 0; base < all; base += kScanThreads) {
+        const int s = base + tid;
+        unsigned long long src, dst;
+        int n, exact;
+        bool final;
+        find_block<DENSE, false>(a.d, p, min(s, nseg - 1), src, dst, n, exact, final);
+        unsigned long long in_t = 0;
+        if (s < nseg) {
+            if (r.seg.src[s] >= 0) src |= kLongInT;
+            if (!final) in_t = kLongInT;
+            bytes += (unsigned long long)exact;
+            if (exact > 0) chunks += ((final ? (unsigned int)(dst & 15ull) : 0u) + (unsigned int)exact + 15u) >> 4;
+        } else if (s < all) {
+            const size_t o = (size_t)p * r.P + p;
+            exact = r.sendcounts[o];
+            src = (unsigned long long)r.S + r.sdispls[o];
+            dst = (unsigned long long)r.R + r.rdispls[o];
+        } else {
+            exact = 0;
+        }
+        const int cnt = exact > 0 ? (int)(((unsigned int)(dst & 127ull) + (unsigned int)exact + kLongUnit - 1) / kLongUnit) : 0;
+        const int incl = wave_incl_scan(cnt);
+        if (lane == kWave - 1) wsum[wv] = incl;
+        s_src[tid] = src; s_dst[tid] = dst | in_t; s_n[tid] = exact;
+        __syncthreads();
+        int before = 0, total = 0;
+#pragma unroll
+        for (int w = 0; w < kScanThreads / kWave; ++w) { before += w < wv ? wsum[w] : 0; total += wsum[w]; }
+        s_pre[tid] = before + incl - cnt;
+        // this workgroup's share of the tile's units
+        const int per = (total + gridDim.x - 1) / gridDim.x, lo = min(total, per * (int)blockIdx.x), hi = min(total, lo + per);
+        if (tid == 0) {
+            s_pre[kScanThreads] = total;
+            s_base = hi > lo ? atomicAdd(a.count, (unsigned int)(hi - lo)) : 0u;
+        }
+        __syncthreads();
+        for (int u = lo + tid; u < hi; u += kScanThreads) {
+            int b = 0;
+#pragma unroll
+            for (int step = kScanThreads / 2; step > 0; step >>= 1) b += s_pre[b + step] <= u ? step : 0;
+            const int k = u - s_pre[b], cut = (int)(s_dst[b] & 127ull);
+            const long long from = k ? (long long)k * kLongUnit - cut : 0, to = min((long long)s_n[b], (long long)(k + 1) * kLongUnit - cut);
+            a.units[s_base + (unsigned int)(u - lo)] =
+                make_ulonglong2(s_src[b] + (unsigned long long)from,
+                                (s_dst[b] + (unsigned long long)from) | (unsigned long long)(to - from) << 48 | (k ? kLongInside : 0ull));
+        }
+        __syncthreads();                                     // the next tile overwrites the LDS
+    }
+    if (blockIdx.x) return;
+#pragma unroll
+    for (int d = kWave / 2; d > 0; d >>= 1) { bytes += __shfl_xor(bytes, d, kWave); chunks += __shfl_xor(chunks, d, kWave); }
+    if (lane == 0) { w_b[wv] = bytes; w_c[wv] = chunks; }
+    __syncthreads();
+    if (tid == 0) {
+        for (int w = 1; w < kScanThreads / kWave; ++w) { bytes += w_b[w]; chunks += w_c[w]; }
+        chunks = (chunks + kRankAlignChunks - 1) / kRankAlignChunks * kRankAlignChunks;
+        if (bytes) { atomicAdd(a.bytes, bytes); atomicAdd(a.chunks, chunks); }
+    }
+}
+
+template <bool STREAM>
+__global__ void __launch_bounds__(kWave) k_hop_long(const ulonglong2* __restrict__ units, const unsigned int* __restrict__ count,
+                                                    unsigned int known, unsigned char* T) {
+    const int lane = threadIdx.x;
+    const unsigned int total = count ? *count : known;
+    for (unsigned int u = blockIdx.x; u < total; u += gridDim.x) {
+        const ulonglong2 unit = units[u];
+        const unsigned long long src = (unit.x & ~kLongInT) + (unit.x & kLongInT ? (unsigned long long)T : 0ull);
+        const unsigned long long dst = (unit.y & kLongAddress) + (unit.y & kLongInT ? (unsigned long long)T : 0ull);
+        const int n = (int)(unit.y >> 48) & (2 * kLongUnit - 1), head = (int)((0u - (unsigned int)dst) & 15u);
+        v4u v[kLongPieces];
+        if (n == kLongUnit && head == 0) {
+#pragma unroll
+            for (int k = 0; k < kLongPieces; ++k) {
+                const TUNA_GLOBAL v4u_any* from = (const TUNA_GLOBAL v4u_any*)(src + (unsigned int)((k * kWave + lane) * 16));
+                v[k] = STREAM ? __builtin_nontemporal_load(from) : *from;
+            }
+#pragma unroll
+            for (int k = 0; k < kLongPieces; ++k)
+                __builtin_nontemporal_store(v[k], (TUNA_GLOBAL v4u*)(dst + (unsigned int)((k * kWave + lane) * 16)));
+        } else if (n >= 16 || (unit.y & kLongInside)) {
+            // the ends of a block: 16 bytes that begin or end with it and overlap the pieces beside them; a unit of fewer
+            // than 16 bytes has bytes of its block in front
+            if (head && lane == 0) store_global<v4u_any>(dst, load_global<v4u_any>(src));
+#pragma unroll
+            for (int k = 0; k < kLongPieces; ++k) {
+                const int off = head + (k * kWave + lane) * 16;
+                const long long o = min(off, n - 16);
+                v[k] = load_global<v4u_any>(off < n ? src + (unsigned long long)o : (unsigned long long)units);
+            }
+#pragma unroll
+            for (int k = 0; k < kLongPieces; ++k) {
+                const int off = head + (k * kWave + lane) * 16;
+                const long long o = min(off, n - 16);
+                if (off < n) __builtin_nontemporal_store(v[k], (TUNA_GLOBAL v4u_any*)(dst + (unsigned long long)o));
+            }
+        } else if (lane == 0) {
+            short_store(dst, src, n, short_load(src, n, (unsigned long long)units));
+        }
     }
 }
 
