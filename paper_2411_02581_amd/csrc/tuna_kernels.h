@@ -225,9 +225,9 @@ __global__ void __launch_bounds__(256) k_build_hops(const PlanScalars pl, int32_
 // have 16 waves, so that a tile is one step of four rows per thread for either matrix instead of four steps (P = 256:
 // 19 -> 14 us, P = 1024 23 -> 19 us).  The class sums are LDS atomics on one of kValCopies copies per lane: neighbouring blocks mostly belong
 // to one class, and on one copy a wave's additions queued up behind each other (P = 4096, r = 8: 159 -> 124 us).
-// With `cls_rows` (few workgroups) the partial rows, class sums included, lie in pinned host memory and the host adds
-// them up: no kernel to clear the sums, none to fold the rows, no copy of the result (see run_validate; P = 256, r = 4
-// 138 -> 117 us per call with the above).
+// With a ticket (few workgroups) the partial rows, class sums included, lie in pinned host memory, each ends with the
+// ticket, and the host waits for those and adds the rows up: no kernel to clear the sums, none to fold the rows, no copy of
+// the result (see run_validate; P = 256, r = 4 138 -> 117 us per call with the above).
 // The first two waves also sum the tile's columns and rows; the largest sums say whether long blocks lie side by side
 // (clustered).  Not before a block of more than kWindowMinBytes was seen: problems of shorter ones only do not ask.
 // ------------------------------------------------------------------------------------------
@@ -235,6 +235,13 @@ constexpr int kValTile = 64;
 constexpr int kValPartial = 8;              // 64-bit words per workgroup in the partial-result array
 constexpr int kValCopies = 32;
 constexpr int kValFoldRows = 64, kValFoldClasses = 24;      // most workgroups and classes that the host folds
+constexpr int kValRow = kValPartial + kValFoldClasses + 1;  // words of such a row, the ticket behind the others
+// A wave's stores to pinned host memory, then the number that tells a waiting host that they are there: it need not wait
+// for the kernel's end, its signal and the runtime's look at it.  By a whole wave.
+__device__ __forceinline__ void send_ticket(unsigned long long* word, unsigned long long ticket) {
+    __threadfence_system();
+    if ((threadIdx.x & (kWave - 1)) == 0) __hip_atomic_store(word, ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 constexpr int kShortBlockBytes = 256;       // below this a block is mostly edges to the destination-tiled hop
 constexpr int kWindowMinBytes = 64;
 constexpr int kWindowBlock = 1 << 25;       // kValTile of them fit 32 bits
@@ -250,7 +257,7 @@ __global__ void __launch_bounds__(1024) k_validate(const int32_t* __restrict__ s
                                                    int P, unsigned long long* __restrict__ partial,
                                                    const int32_t* __restrict__ hm1, int Q, int N,
                                                    const unsigned long long* __restrict__ mask, int nph,
-                                                   Status* __restrict__ st, int cls_rows, int copies, int clear_totals) {
+                                                   Status* __restrict__ st, unsigned long long ticket, int copies, int clear_totals) {
     __shared__ int tile[kValTile][kValTile + 1];
     __shared__ unsigned long long red[16][8];
     __shared__ int long_seen;
@@ -401,7 +408,7 @@ __global__ void __launch_bounds__(1024) k_validate(const int32_t* __restrict__ s
         r[1] = (unsigned long long)mx; r[2] = bytes; r[3] = chunks; r[4] = extent; r[5] = tchunks; r[6] = shortb; r[7] = window;
     }
     __syncthreads();
-    unsigned long long* o = partial + (size_t)blockIdx.x * (cls_rows ? kValPartial + kValFoldClasses : kValPartial);
+    unsigned long long* o = partial + (size_t)blockIdx.x * (ticket ? kValRow : kValPartial);
     if (ty == 0) {                                        // one lane per wave's row: sixteen rows one after the other took 1 us more
         const unsigned long long* r = red[min(tx, ny - 1)];
         const bool in = tx < ny;
@@ -426,12 +433,13 @@ __global__ void __launch_bounds__(1024) k_validate(const int32_t* __restrict__ s
     for (int i = ty * kValTile + tx; i < ncls; i += ny * kValTile) {
         unsigned long long v = 0;
         for (int k = 0; k < copies; ++k) v += lcls[i * copies + ((i + k) & (copies - 1))];
-        if (cls_rows) o[kValPartial + i] = v;
+        if (ticket) o[kValPartial + i] = v;                   // (first wave: kValFoldClasses < kWave)
         else if (v) atomicAdd(&st->cls_chunks[i], v);
     }
-    // the totals that k_phase_sums adds to (without cls_rows k_validate_finish clears them), not for a sizing query: the
+    // the totals that k_phase_sums adds to (without a ticket k_validate_finish clears them), not for a sizing query: the
     // totals there belong to the context's last call
-    if (cls_rows && clear_totals && blockIdx.x == 0 && ty == 0) st->phase_bytes[tx] = st->phase_chunks[tx] = st->phase_units[tx][0] = 0;
+    if (ticket && ty == 0) send_ticket(o + kValRow - 1, ticket);
+    if (ticket && clear_totals && blockIdx.x == 0 && ty == 0) st->phase_bytes[tx] = st->phase_chunks[tx] = st->phase_units[tx][0] = 0;
 }
 
 // k_zero64: n 64-bit words to zero (the class sums before a validation pass).
@@ -440,9 +448,12 @@ __global__ void __launch_bounds__(256) k_zero64(unsigned long long* __restrict__
     if (i < n) p[i] = 0;
 }
 
-// k_validate_finish: folds the workgroups' partial results into the status block (one workgroup).
+// k_validate_finish: folds the workgroups' partial results into the status block (one workgroup).  With `mirror` it also
+// writes the block's head and the ncls class sums there, pinned host memory, and sends the ticket, and clears the sums for
+// the next call: in place of a copy command and a launch of k_zero64.
 __global__ void __launch_bounds__(256) k_validate_finish(const unsigned long long* __restrict__ partial, int n,
-                                                         Status* __restrict__ st, int clear_totals) {
+                                                         Status* __restrict__ st, int clear_totals, Status* __restrict__ mirror,
+                                                         int ncls, unsigned long long* __restrict__ word, unsigned long long ticket) {
     __shared__ unsigned long long red[4][8];
     unsigned long long fa = 0, m = 0, by = 0, ch = 0, ex = 0, tc = 0, sb = 0, wi = 0;
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
@@ -479,6 +490,21 @@ __global__ void __launch_bounds__(256) k_validate_finish(const unsigned long lon
         st->t_chunks = tc;
         st->short_blocks = sb;
         st->windows = wi;
+        if (mirror) {
+            mirror->flags = (unsigned int)(fa >> 32);
+            mirror->align_bits = (unsigned int)(fa & 127u);
+            mirror->max_count = (int)m;
+            mirror->total_bytes = by;
+            mirror->total_chunks = ch;
+            mirror->send_extent = ex;
+            mirror->t_chunks = tc;
+            mirror->short_blocks = sb;
+            mirror->windows = wi;
+        }
+    }
+    if (mirror && threadIdx.x < kWave) {
+        for (int i = threadIdx.x; i < ncls; i += kWave) { mirror->cls_chunks[i] = st->cls_chunks[i]; st->cls_chunks[i] = 0; }
+        send_ticket(word, ticket);
     }
     // the totals that k_phase_sums adds to; the other paths write them whole
     if (clear_totals && threadIdx.x < 64) st->phase_bytes[threadIdx.x] = st->phase_chunks[threadIdx.x] = st->phase_units[threadIdx.x][0] = 0;
