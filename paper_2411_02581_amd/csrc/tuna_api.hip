@@ -1491,12 +1491,17 @@ int launch_t_places(Prepared& pr, hipStream_t s) {
     for (size_t i = 0; i < pl.phases.size(); ++i) {
         const int ncls = (int)(pr.dp->tcls[i].size() / 3);
         if (!ncls) continue;
+        for (int k = 0; k < ncls; ++k) a.most = std::max(a.most, (int)pr.dp->tcls[i][3 * k + 2]);
         a.ph[a.nph++] = PlacePhase{pr.dp->d_seg[i].e, pr.dp->d_seg[i].src, pr.dp->d_tord[i], pr.dp->d_tcls[i], (int)i, rows, pl.phases[i].dim,
                                    (int)std::min<int64_t>(pl.phases[i].rx * pl.phases[i].r, INT_MAX)};
         rows += ncls;
     }
     if (!rows) return TUNA_OK;
-    hipLaunchKernelGGL(k_t_places, dim3((unsigned)pr.P, (unsigned)rows), dim3(kScanThreads), 0, s, a);
+    const dim3 grid((unsigned)pr.P, (unsigned)rows);
+    if (pr.P <= kPlaceSlotRanks && pl.phases[0].r >= kPlaceSlotRadix)
+        hipLaunchKernelGGL(k_t_places_slots, grid, dim3(kScanThreads), (size_t)a.most * 4 + (size_t)pr.P * 2, s, a);
+    else
+        hipLaunchKernelGGL(k_t_places, grid, dim3(kScanThreads), 0, s, a);
     HIPCHK(hipGetLastError());
     hipLaunchKernelGGL(k_t_bases, dim3((unsigned)rows), dim3(kScanThreads), 0, s, a);
     HIPCHK(hipGetLastError());

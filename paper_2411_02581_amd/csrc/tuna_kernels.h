@@ -1279,6 +1279,14 @@ __device__ __forceinline__ const int32_t* block_bytes(const int32_t* sendcounts,
 // The neighbours of the first phase's message order are r apart in tpos and in the caller's rows: its offsets and sizes
 // are kept by segment too (pairs) when r is 16 or more: uniform [0, 64] B, P = 4096, r = 64 2.17 -> 1.74 ms per call; at
 // r = 4 and 8 they cost 1 %.
+// k_t_places_slots: the same in the order of the slot indices, for larger radices: consecutive slot indices of one round after
+// the other are consecutive entries of a row of recvcounts and of tpos, where the message order is a radix apart in both.
+// The sizes go through the LDS to be scanned in message order and back.  What bounds k_t_places then is the lines it touches
+// (P = 2048, r = 46: 435 MB missed in the L2s, 73 us for 16 MB of sizes).  Per call, k_t_places / k_t_places_slots: uniform [0, 16]
+// B, P = 2048, r = 46 236 / 184 us; uniform [0, 64] B, P = 4096, r = 64 1.72 / 1.54 ms; uniform [0, 512] B, P = 2048, r = 46 1017 / 972
+// us; uniform [0, 16] B, P = 6000, r = 77 2.62 / 2.22 ms; 64-byte blocks, P = 8192, r = 90 5.19 / 4.67 ms; r = 16 255 / 252 us; r = 8 1767 /
+// 1734 us and 23.38 / 23.34 ms; but r = 4, whose 15 classes each go through all slot indices, P = 1500
+// 586 / 602.  (Neighbouring receivers on one XCD, so that they share those lines in its L2: 195 us at r = 46, but r = 8 +4 %.)
 // k_t_bases: one workgroup per class.  Two launches per call in place of four per phase (rotation and size exchange
 // included): P = 256, r = 4, four phases 174 -> 138 us per call, uniform [0, 100] B, P = 1500, r = 4 682 -> 598 us.
 // ------------------------------------------------------------------------------------------
@@ -1302,6 +1310,7 @@ struct PlaceArgs {
     ExactT x;
     uint2* pairs;           // of the first phase (ResolveArgs)
     int pairs_ld;
+    int most;               // blocks of the largest class
     int by_value;           // the classes' first chunks are here, not in x.cbase: no copy to the device before the kernels
     long long cbase[kPlaceClasses];
 };
@@ -1341,6 +1350,68 @@ __global__ void __launch_bounds__(kScanThreads) k_t_places(const PlaceArgs a) {
                 pos_t[se[k]] = run[k];
                 if (ph.phase == 0 && a.pairs) a.pairs[(size_t)p * a.pairs_ld + sg[k]] = make_uint2((unsigned int)run[k], (unsigned int)sz[k]);
             }
+    }
+    if (threadIdx.x == 0) a.x.csub[(size_t)cid * P + p] = carry;
+}
+constexpr int kPlaceSlotRanks = 8192;       // 48 KiB of LDS
+constexpr int kPlaceSlotRadix = 8;
+// dynamic LDS: the blocks of the largest class (a.most), 4 bytes each, and 2 bytes per slot index
+__global__ void __launch_bounds__(kScanThreads) k_t_places_slots(const PlaceArgs a) {
+    extern __shared__ int s_val[];                       // by index inside the class: bytes, then the chunk offset
+    __shared__ int wsum[kScanThreads / kWave];
+    constexpr int kNone = 0xffff;
+    unsigned short* s_at = reinterpret_cast<unsigned short*>(s_val + a.most);        // by slot index: the index inside the class
+    const int p = blockIdx.x, P = a.P;
+    const int f = place_phase(a, blockIdx.y);
+    const PlacePhase& ph = a.ph[f];
+    const int32_t* cls = ph.tcls + 3 * (blockIdx.y - ph.first);
+    const int cid = cls[0], c0 = cls[1], cn = cls[2];
+    int pn, pg;
+    split_slot_index(p, a.Q, a.N, pn, pg);
+    for (int e = threadIdx.x; e < P; e += kScanThreads) s_at[e] = kNone;
+    __syncthreads();
+    for (int i = threadIdx.x; i < cn; i += kScanThreads) s_at[ph.e[ph.tord[c0 + i]]] = (unsigned short)i;
+    __syncthreads();
+    for (int base = 0; base < P; base += kScanThreads * kScanItems) {
+        int at[kScanItems], sz[kScanItems];
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) {
+            const int e = base + k * kScanThreads + threadIdx.x;
+            at[k] = e < P ? s_at[e] : kNone;
+            int j, l;
+            split_slot_index(min(e, P - 1), a.Q, a.N, j, l);
+            const int32_t* from = block_bytes(a.sendcounts, a.recvcounts, false, pn, pg, j, l, P, a.Q, a.N, ph.dim, ph.rx1);
+            sz[k] = *(at[k] != kNone ? from : a.recvcounts);
+        }
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k)
+            if (at[k] != kNone) s_val[at[k]] = sz[k];
+    }
+    __syncthreads();
+    int carry = 0;
+    for (int base = 0; base < cn; base += kScanThreads * kScanItems) {
+        int ct[kScanItems], sz[kScanItems];
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) {
+            const int i = base + scan_item_index(k);
+            sz[k] = i < cn ? s_val[i] : 0;
+            ct[k] = (sz[k] + 15) >> 4;
+        }
+        int run[kScanItems];
+        block_scan_batch(ct, run, carry, wsum);
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) {
+            const int i = base + scan_item_index(k);
+            if (i >= cn) continue;
+            s_val[i] = run[k];
+            if (ph.phase == 0 && a.pairs) a.pairs[(size_t)p * a.pairs_ld + ph.tord[c0 + i]] = make_uint2((unsigned int)run[k], (unsigned int)sz[k]);
+        }
+    }
+    __syncthreads();
+    int* pos_t = a.x.tpos + ((size_t)ph.phase * P + p) * P;
+    for (int e = threadIdx.x; e < P; e += kScanThreads) {
+        const int at = s_at[e];
+        if (at != kNone) pos_t[e] = s_val[at];
     }
     if (threadIdx.x == 0) a.x.csub[(size_t)cid * P + p] = carry;
 }
