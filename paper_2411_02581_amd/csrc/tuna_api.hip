@@ -1153,10 +1153,46 @@ unsigned direct_columns(const Prepared& pr, const PhaseHost& ph, int nseg, int* 
     *iters = (int)std::max(1LL, std::min(8LL, steps * rows / 8192));
     return (unsigned)((steps + *iters - 1) / *iters);
 }
+// Phases that an immediate call's k_hop_senders moves, and its workgroup columns and steps per workgroup (as direct_columns).
+unsigned sender_columns(const Prepared& pr, const PhaseHost& ph, int* iters) {
+    const int steps = (ph.nseg + 255) / 256;
+    *iters = std::max(1, std::min(steps, (int)((long long)steps * pr.P / sender_sets(direct_lpb(pr)) / kSenderGroups)));
+    return (unsigned)((steps + *iters - 1) / *iters);
+}
+bool sender_phase(const Prepared& pr, const PhaseHost& ph) {
+    int iters = 0;
+    return pr.dp->host.phases.size() > 1 && ph.nz >= kSenderMinRounds && ph.nz <= kSenderMaxRounds &&
+           (long long)sender_columns(pr, ph, &iters) * ph.nz <= ph.nseg;       // (rows of partial sums: no more than segments)
+}
 unsigned direct_rows(const Prepared& pr, const PhaseHost& ph) {
+    if (!row_blocks(pr) && sender_phase(pr, ph)) { int iters = 0; return sender_columns(pr, ph, &iters) * (unsigned)ph.nz; }
     if (row_blocks(pr)) { const int segs = rows_segs(pr); return (unsigned)((ph.nseg + segs - 1) / segs); }
     int iters = 0;
     return direct_columns(pr, ph, ph.nseg, &iters) * (unsigned)(4 / direct_shape(direct_lpb(pr), direct_tall(ph)).waves_r);
+}
+
+template <int LPB, int STREAM>
+void launch_senders_as(const DirectArgs& a, dim3 grid, bool exact, hipStream_t s) {
+    const size_t lds = ((size_t)a.nz + 1) * 8 * sender_sets(LPB);
+    if (exact) hipLaunchKernelGGL((k_hop_senders<LPB, STREAM, true>), grid, dim3(256), lds, s, a);
+    else hipLaunchKernelGGL((k_hop_senders<LPB, STREAM, false>), grid, dim3(256), lds, s, a);
+}
+int launch_senders(const Prepared& pr, size_t i, uint2* part, hipStream_t s) {
+    const PhaseHost& ph = pr.dp->host.phases[i];
+    DirectArgs a{};
+    a.r = resolve_args(pr, i, nullptr, HopDev{});
+    a.T = pr.T; a.part = part; a.nz = ph.nz;
+    const int lpb = direct_lpb(pr), sets = sender_sets(lpb);
+    const dim3 grid(sender_columns(pr, ph, &a.iters), (unsigned)((pr.P + sets - 1) / sets));
+    if (lpb == 1) launch_senders_as<1, 0>(a, grid, pr.exact_kernels, s);
+    else if (lpb == 4) {
+        if (pr.gran >= 16) launch_senders_as<4, 1>(a, grid, pr.exact_kernels, s);
+        else launch_senders_as<4, 0>(a, grid, pr.exact_kernels, s);
+    } else if (pr.gran == 128) launch_senders_as<16, 2>(a, grid, pr.exact_kernels, s);
+    else if (pr.gran == 16) launch_senders_as<16, 1>(a, grid, pr.exact_kernels, s);
+    else launch_senders_as<16, 0>(a, grid, pr.exact_kernels, s);
+    HIPCHK(hipGetLastError());
+    return TUNA_OK;
 }
 
 template <bool LINES>
@@ -1510,8 +1546,10 @@ int launch_t_places(Prepared& pr, hipStream_t s) {
 
 // The payload of such a phase, found and moved in one kernel; partial sums into `part` (direct_rows rows of P entries).
 int launch_direct_payload(const Prepared& pr, size_t i, uint2* part, hipStream_t s) {
-    const int rc = row_blocks(pr) ? launch_rows(pr, i, HopDev{}, part, s)
-                                  : launch_direct(pr, i, HopDev{}, 0, pr.dp->host.phases[i].nseg, part, s);
+    const PhaseHost& ph = pr.dp->host.phases[i];
+    const int rc = row_blocks(pr)         ? launch_rows(pr, i, HopDev{}, part, s)
+                   : sender_phase(pr, ph) ? launch_senders(pr, i, part, s)
+                                          : launch_direct(pr, i, HopDev{}, 0, ph.nseg, part, s);
     if (rc == TUNA_OK) mark(pr.ctx, s, kCatPack, (int)i);
     return rc;
 }

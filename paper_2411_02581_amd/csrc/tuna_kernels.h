@@ -1218,6 +1218,7 @@ struct DirectArgs {
     int segs;                           // segments per wave, at most 64 (k_hop_rows)
     unsigned long long user_limit;      // address one past the last byte of S that holds a block
     uint2* part;                        // [grid.x][P]: payload bytes and chunks of the tile column, per receiver (not when RESOLVED)
+    int nz;                             // rounds of the phase (k_hop_senders)
 };
 
 typedef v4u v4u_any __attribute__((aligned(1)));
@@ -1422,16 +1423,68 @@ __global__ void __launch_bounds__(kScanThreads) k_t_bases(const PlaceArgs a) {
     class_base(a.x, cid, a.by_value ? a.cbase[cid] : a.x.cbase[cid], a.P, wc);
 }
 
+// The blocks that the lanes of a wave have found, SETS each: LPB lanes move one, or its own lane (LPB = 1).  dummy: any 16
+// bytes that can be read.
+template <int LPB> struct ShortLds { unsigned long long src[4][kWave], dst[4][kWave]; int n[4][kWave]; };
+template <> struct ShortLds<1> {};
+template <int LPB, int STREAM, int SETS>
+__device__ __forceinline__ void move_short(const unsigned long long (&src)[SETS], const unsigned long long (&dst)[SETS], const int (&n)[SETS],
+                                           unsigned long long dummy, ShortLds<LPB>& lds) {
+    if constexpr (LPB == 1) {
+        ShortBlock b[SETS];
+#pragma unroll
+        for (int u = 0; u < SETS; ++u) b[u] = short_load(src[u], n[u], dummy);
+#pragma unroll
+        for (int u = 0; u < SETS; ++u) short_store(dst[u], src[u], n[u], b[u]);
+    } else {
+        static_assert(SETS == 1, "a lane finds one block, LPB lanes move it");
+        constexpr int BPS = kWave / LPB;                 // blocks a wave moves per step of its copy loop
+        constexpr int FLIGHT = LPB < 8 ? LPB : 8;        // steps whose loads are in flight together
+        const int lane = threadIdx.x & (kWave - 1);
+        const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+        // the wave's 64 blocks go to its own part of the LDS; no workgroup barrier
+        lds.src[wv][lane] = src[0]; lds.dst[wv][lane] = dst[0]; lds.n[wv][lane] = n[0];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const int c = (lane & (LPB - 1)) * 16;
+#pragma unroll
+        for (int k0 = 0; k0 < LPB; k0 += FLIGHT) {
+            v4u v[FLIGHT];
+            unsigned long long d[FLIGHT];
+            bool act[FLIGHT];
+#pragma unroll
+            for (int k = 0; k < FLIGHT; ++k) {
+                const int b = (k0 + k) * BPS + lane / LPB;
+                const int nb = lds.n[wv][b];
+                act[k] = nb >= 16 && c < nb;
+                const unsigned int o = (unsigned int)min(c, nb - 16);
+                const unsigned long long sa = lds.src[wv][b] + o;
+                d[k] = lds.dst[wv][b] + o;
+                const TUNA_GLOBAL v4u_any* from = (const TUNA_GLOBAL v4u_any*)(act[k] ? sa : dummy);
+                v[k] = STREAM == 2 ? __builtin_nontemporal_load(from) : *from;
+            }
+#pragma unroll
+            for (int k = 0; k < FLIGHT; ++k)
+                if (act[k]) {
+                    if (STREAM) __builtin_nontemporal_store(v[k], (TUNA_GLOBAL v4u_any*)d[k]);
+                    else store_global<v4u_any>(d[k], v[k]);
+                }
+        }
+        // blocks of fewer than 16 bytes: the lane that resolved them
+        const int ns = n[0] < 16 ? n[0] : 0;
+        if (__ballot(ns > 0)) short_store(dst[0], src[0], ns, short_load(src[0], ns, dummy));
+        __builtin_amdgcn_wave_barrier();                 // the next step overwrites the wave's LDS
+    }
+}
+
 template <int LPB, bool TALL, int STREAM, bool DENSE, bool RESOLVED>
 __global__ void __launch_bounds__(256) k_hop_direct(const DirectArgs a) {
     constexpr DirectShape SH = direct_shape(LPB, TALL);
     constexpr int SEGS = kWave / SH.wave_ranks;          // segments per wave and step
     constexpr int SETS = SH.sets;                        // blocks a lane resolves per step
     constexpr int WS = 4 / SH.waves_r;                   // waves side by side along the segments
-    constexpr int BPS = kWave / LPB;                     // blocks a wave moves per step of its copy loop
-    constexpr int FLIGHT = LPB < 8 ? LPB : 8;            // steps whose loads are in flight together
-    __shared__ unsigned long long s_src[LPB > 1 ? 4 : 1][LPB > 1 ? kWave : 1], s_dst[LPB > 1 ? 4 : 1][LPB > 1 ? kWave : 1];
-    __shared__ int s_n[LPB > 1 ? 4 : 1][LPB > 1 ? kWave : 1];
+    __shared__ ShortLds<LPB> lds;
     const ResolveArgs& r = a.r;
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -1512,48 +1565,7 @@ __global__ void __launch_bounds__(256) k_hop_direct(const DirectArgs a) {
             // chunks as the staging layouts count them: cut at the 16-byte boundaries of R
             if (!RESOLVED) sum_c[u] += n[u] > 0 ? ((r.seg.dst[s] < 0 ? (unsigned int)(dst[u] & 15ull) : 0u) + (unsigned int)n[u] + 15u) >> 4 : 0u;
         }
-        const unsigned long long dummy = (unsigned long long)r.seg.e;       // any 16 bytes that can be read
-        if constexpr (LPB == 1) {
-            ShortBlock b[SETS];
-#pragma unroll
-            for (int u = 0; u < SETS; ++u) b[u] = short_load(src[u], n[u], dummy);
-#pragma unroll
-            for (int u = 0; u < SETS; ++u) short_store(dst[u], src[u], n[u], b[u]);
-        } else {
-            // the wave's 64 blocks go to its own part of the LDS; no workgroup barrier
-            s_src[wv][lane] = src[0]; s_dst[wv][lane] = dst[0]; s_n[wv][lane] = n[0];
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            const int c = (lane & (LPB - 1)) * 16;
-#pragma unroll
-            for (int k0 = 0; k0 < LPB; k0 += FLIGHT) {
-                v4u v[FLIGHT];
-                unsigned long long d[FLIGHT];
-                bool act[FLIGHT];
-#pragma unroll
-                for (int k = 0; k < FLIGHT; ++k) {
-                    const int b = (k0 + k) * BPS + lane / LPB;
-                    const int nb = s_n[wv][b];
-                    act[k] = nb >= 16 && c < nb;
-                    const unsigned int o = (unsigned int)min(c, nb - 16);
-                    const unsigned long long sa = s_src[wv][b] + o;
-                    d[k] = s_dst[wv][b] + o;
-                    const TUNA_GLOBAL v4u_any* from = (const TUNA_GLOBAL v4u_any*)(act[k] ? sa : dummy);
-                    v[k] = STREAM == 2 ? __builtin_nontemporal_load(from) : *from;
-                }
-#pragma unroll
-                for (int k = 0; k < FLIGHT; ++k)
-                    if (act[k]) {
-                        if (STREAM) __builtin_nontemporal_store(v[k], (TUNA_GLOBAL v4u_any*)d[k]);
-                        else store_global<v4u_any>(d[k], v[k]);
-                    }
-            }
-            // blocks of fewer than 16 bytes: the lane that resolved them
-            const int ns = n[0] < 16 ? n[0] : 0;
-            if (__ballot(ns > 0)) short_store(dst[0], src[0], ns, short_load(src[0], ns, dummy));
-            __builtin_amdgcn_wave_barrier();             // the next step overwrites the wave's LDS
-        }
+        move_short<LPB, STREAM>(src, dst, n, (unsigned long long)r.seg.e, lds);
     }
     if (!RESOLVED) {
 #pragma unroll
@@ -1562,6 +1574,102 @@ __global__ void __launch_bounds__(256) k_hop_direct(const DirectArgs a) {
             for (int d = SEGS / 2; d > 0; d >>= 1) { sum_b[u] += __shfl_xor(sum_b[u], d, kWave); sum_c[u] += __shfl_xor(sum_c[u], d, kWave); }
             if (sub == 0 && p0 + u < P) a.part[((size_t)blockIdx.x * WS + wv % WS) * P + p0 + u] = make_uint2(sum_b[u], sum_c[u]);
         }
+    }
+}
+
+// ------------------------------------------------------------------------------------------
+// k_hop_senders: k_hop_direct by senders instead of receivers, for phases of many rounds in schedules of several.  The blocks
+// that one rank sends in such a phase -- to nz receivers, in message order -- lie together, in its row of sdispls and of S
+// or in its part of T, and a workgroup takes the blocks of one rank (LPB = 1: of four): all the lines that are read are
+// read by one compute unit, whereas the blocks that one receiver gets are single ones of nz senders, a line each.  The
+// stores go out in runs of a message's blocks either way.
+//   Bound by memory and by the chain of three loads per step, hence a step per workgroup while that makes no more than
+// kSenderGroups of them (uniform [0, 64] B, P = 4096, r = 64: 8 steps 1230 us per call, one 1100).
+//   k_hop_direct / k_hop_senders, us per call: uniform [0, 64] B, P = 4096, r = 64 1480 / 1100 (its phases 750 and 484 / 452 and
+// 371), uniform [0, 16] B, P = 6000, r = 77 2215 / 1945, P = 2048, r = 46 184 / 181, 64-byte blocks, P = 8192, r = 90 4670 / 3960,
+// uniform [0, 40] B, 32 x 32 ranks 123 / 97, uniform [0, 200] B, P = 700, r = 27 108 / 99; r = 13 518 / 508 and 360 / 348; r = 8, P =
+// 2048 401 / 400 and 527 / 603, r = 4 690 / 715: hence kSenderMinRounds.  (In the order of the slot indices, where the loads
+// are the consecutive ones and the stores a receiver each: P = 2048, r = 46 240.)
+//   The sums per receiver that k_phase_sums adds up are one partial row per round and workgroup column here: a message has one
+// sender and one receiver.
+// ------------------------------------------------------------------------------------------
+constexpr int kSenderMinRounds = 12, kSenderMaxRounds = 1024;         // (32 KiB of LDS)
+constexpr int kSenderGroups = 65536;
+constexpr int sender_sets(int lpb) { return lpb == 1 ? 4 : 1; }       // blocks a lane finds per step, of neighbouring senders
+template <int LPB, int STREAM, bool DENSE>
+__global__ void __launch_bounds__(256) k_hop_senders(const DirectArgs a) {
+    constexpr int SETS = sender_sets(LPB);
+    extern __shared__ unsigned long long s_sum[];        // [SETS][nz + 1] by round: payload bytes of the message, and its chunks << 32
+    __shared__ ShortLds<LPB> lds;
+    const ResolveArgs& r = a.r;
+    const int P = r.P, Q = r.Q, N = r.N, q0 = blockIdx.y * SETS, nzs = a.nz + 1;
+    const unsigned long long tb = (unsigned long long)a.T;
+    for (int z = threadIdx.x; z < SETS * nzs; z += 256) s_sum[z] = 0;
+    __syncthreads();
+    for (int it = 0; it < a.iters; ++it) {                // (the bound is the same for the whole workgroup)
+        const int s0 = (blockIdx.x * a.iters + it) * 256;
+        if (s0 >= r.nseg) break;
+        const int s = min(s0 + (int)threadIdx.x, r.nseg - 1);
+        const bool in = s0 + (int)threadIdx.x < r.nseg;
+        const int e = r.seg.e[s], z = r.seg.z[s], ssrc = r.seg.src[s], sdst = r.seg.dst[s], dist = z * r.rx;
+        const int sph = DENSE ? r.seg.srcph[s] : 0, scl = DENSE ? r.seg.scls[s] : 0, dcl = DENSE ? r.seg.dcls[s] : 0;
+        const bool in_s = ssrc < 0, in_r = sdst < 0;
+        int j, l;
+        split_slot_index(e, Q, N, j, l);
+        long long va[SETS], vc[SETS];
+        int vb[SETS], vd[SETS], n[SETS], p[SETS];
+        unsigned long long src[SETS], dst[SETS];
+#pragma unroll
+        for (int u = 0; u < SETS; ++u) {
+            const int q = min(q0 + u, P - 1);
+            int qn, qg;
+            split_slot_index(q, Q, N, qn, qg);
+            int pn = qn, pg = qg;
+            if (r.dim == 0) { pg -= dist; if (pg < 0) pg += Q; }
+            else { pn -= dist; if (pn < 0) pn += N; }
+            p[u] = pn * Q + pg;                              // the receiver
+            int dn = qn - j; if (dn < 0) dn += N;
+            int dg = qg - l; if (dg < 0) dg += Q;
+            int sn = pn + j; if (sn >= N) sn -= N;
+            int sg = pg + l; if (sg >= Q) sg -= Q;
+            const size_t at_s = (size_t)q * P + dn * Q + dg, at_r = (size_t)p[u] * P + sn * Q + sg;
+            const int32_t* pair = reinterpret_cast<const int32_t*>(r.pairs + (size_t)p[u] * r.pairs_ld + s);
+            n[u] = *(in_r ? r.recvcounts + at_r : r.pairs ? pair + 1 : block_bytes(r.sendcounts, r.recvcounts, in_s, pn, pg, j, l, P, Q, N, r.dim, r.rx1));
+            const int64_t* tbase = reinterpret_cast<const int64_t*>(r.x.tbase);
+            va[u] = *(in_s ? r.sdispls + at_s : (DENSE ? tbase + (size_t)scl * P + q : r.sdispls));
+            vc[u] = *(in_r ? r.rdispls + at_r : (DENSE ? tbase + (size_t)dcl * P + p[u] : r.rdispls));
+            if (DENSE) {
+                vb[u] = *(in_s ? r.seg.e : r.x.tpos + ((size_t)sph * P + q) * P + e);
+                vd[u] = *(in_r ? r.seg.e : r.pairs ? pair : r.x.tpos + ((size_t)r.x.phase * P + p[u]) * P + e);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < SETS; ++u) {
+            const int q = min(q0 + u, P - 1);
+            if (DENSE) {
+                src[u] = in_s ? (unsigned long long)r.S + va[u] : tb + ((unsigned long long)(va[u] + vb[u]) << 4);
+                dst[u] = in_r ? (unsigned long long)r.R + vc[u] : tb + ((unsigned long long)(vc[u] + vd[u]) << 4);
+            } else {
+                src[u] = in_s ? (unsigned long long)r.S + va[u] : tb + (unsigned long long)(((long long)q * r.slots + ssrc) * r.slot_bytes);
+                dst[u] = in_r ? (unsigned long long)r.R + vc[u] : tb + (unsigned long long)(((long long)p[u] * r.slots + sdst) * r.slot_bytes);
+            }
+            if (!in || q0 + u >= P) n[u] = 0;
+            n[u] = min(n[u], 16 * LPB);                      // validation has bounded it: nothing is cut here
+            if (n[u] > 0)
+                atomicAdd(&s_sum[u * nzs + z], (unsigned long long)n[u] | (unsigned long long)(((in_r ? (unsigned int)(dst[u] & 15ull) : 0u) + (unsigned int)n[u] + 15u) >> 4) << 32);
+        }
+        move_short<LPB, STREAM>(src, dst, n, (unsigned long long)r.seg.e, lds);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < SETS * a.nz; i += 256) {
+        const int u = i / a.nz, z = 1 + i - u * a.nz, q = q0 + u;
+        if (q >= P) break;
+        int pn, pg;
+        split_slot_index(q, Q, N, pn, pg);
+        if (r.dim == 0) { pg -= z * r.rx; if (pg < 0) pg += Q; }
+        else { pn -= z * r.rx; if (pn < 0) pn += N; }
+        const unsigned long long v = s_sum[u * nzs + z];
+        a.part[((size_t)blockIdx.x * a.nz + z - 1) * P + pn * Q + pg] = make_uint2((unsigned int)v, (unsigned int)(v >> 32));
     }
 }
 
