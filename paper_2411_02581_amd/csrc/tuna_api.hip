@@ -49,29 +49,30 @@ struct DevicePlan {
     bool borrowed = false;               // the device memory belongs to someone else (static scratch)
 };
 
-// The T-bound segments of every phase grouped by the class they are stored into, in message order
-// within a class: tord[phase] lists segment indices, tcls[phase] holds {class id, start, count} triples.
-void build_class_tables(const PlanHost& pl, std::vector<std::vector<int32_t>>& tord, std::vector<std::vector<int32_t>>& tcls) {
+// The classes that every phase stores into: {class id, first entry, blocks} of each that has any, as k_build_classes finds them.
+void class_sizes(const PlanHost& pl, std::vector<std::vector<int32_t>>& tcls) {
     const size_t nph = pl.phases.size();
-    tord.assign(nph, {}); tcls.assign(nph, {});
+    tcls.assign(nph, {});
+    std::vector<int32_t> n(nph);
     for (size_t i = 0; i < nph; ++i) {
-        PhaseScalars ps = phase_scalars(pl.phases[i]);
-        std::vector<std::vector<int32_t>> by_next(nph);       // segment indices by the phase of the next move
+        const PhaseScalars ps = phase_scalars(pl.phases[i]);
+        std::fill(n.begin(), n.end(), 0);
         for (int e = 0; e < pl.P; ++e) {
             SegInfo si{};
             int pos = 0;
-            if (slot_entry(pl.sc, ps, e, &si, &pos) && si.nxt_phase >= 0 && si.nxt_phase < (int)nph)
-                by_next[si.nxt_phase].push_back(pos);
+            if (slot_entry(pl.sc, ps, e, &si, &pos) && si.nxt_phase >= 0 && si.nxt_phase < (int)nph) ++n[si.nxt_phase];
         }
+        int32_t start = 0;
         for (size_t y = i + 1; y < nph; ++y) {
-            if (by_next[y].empty()) continue;
-            std::sort(by_next[y].begin(), by_next[y].end());
-            tcls[i].push_back(class_id((int)i, (int)y, (int)nph));
-            tcls[i].push_back((int32_t)tord[i].size());
-            tcls[i].push_back((int32_t)by_next[y].size());
-            tord[i].insert(tord[i].end(), by_next[y].begin(), by_next[y].end());
+            if (!n[y]) continue;
+            tcls[i].insert(tcls[i].end(), {class_id((int)i, (int)y, (int)nph), start, n[y]});
+            start += n[y];
         }
     }
+}
+// T-bound blocks of a phase
+size_t class_total(const std::vector<int32_t>& tcls) {
+    return tcls.empty() ? 0 : (size_t)tcls[tcls.size() - 2] + (size_t)tcls[tcls.size() - 1];
 }
 
 constexpr int kMailIssued = kValFoldRows * kValRow, kMailReceived = kMailIssued + 1, kMailWords = 2;
@@ -86,6 +87,7 @@ struct StatusBufs {
     unsigned long long* h_part = nullptr;      // the partial results in pinned memory, where few workgroups write them for
     unsigned long long* h_part_dev = nullptr;  // the host to fold (nullptr: none, k_validate_finish folds them); behind them
                                                // kMailWords words: the last ticket handed out, and the last one received
+    bool sums_clear = false;                   // the class sums have been cleared by an earlier kernel of this call
     int num_cus = 256;
 };
 
@@ -327,6 +329,30 @@ void free_device_plan(DevicePlan& dp) {
     dp.d_hm1 = nullptr; dp.d_mask = nullptr;
 }
 
+// Launches the kernels that fill a schedule's device tables (d_seg to d_mask, whose memory is there), and clears n_zero words.
+int launch_tables(const DevicePlan& dp, unsigned long long* zero, int n_zero, hipStream_t s) {
+    const int nph = (int)dp.host.phases.size();
+    for (int f = 0; f < std::max(nph, 1); f += kBuildPhases) {
+        BuildArgs a{};
+        a.pl = dp.host.sc; a.first = f; a.hm1 = dp.d_hm1; a.mask = dp.d_mask; a.zero = zero; a.n_zero = f ? 0 : n_zero;
+        const int n = std::min(kBuildPhases, nph - f);
+        bool classes = false;
+        for (int i = 0; i < n; ++i) {
+            const SegDev& sd = dp.d_seg[f + i];
+            a.ph[i] = BuildPhase{phase_scalars(dp.host.phases[f + i]), const_cast<int32_t*>(sd.e), dp.d_zt[f + i], dp.d_tord[f + i], dp.d_tcls[f + i],
+                                 (int)(sd.z - sd.e)};
+            classes = classes || !dp.tcls[f + i].empty();
+        }
+        if (n <= 0) return TUNA_OK;                       // one rank: nothing moves
+        hipLaunchKernelGGL(k_build_tables, dim3((unsigned)((dp.host.P + 255) / 256), (unsigned)n), dim3(256), 0, s, a);
+        HIPCHK(hipGetLastError());
+        if (!classes) continue;
+        hipLaunchKernelGGL(k_build_classes, dim3((unsigned)(nph - 1 - f), (unsigned)n), dim3(kWave), 0, s, a);
+        HIPCHK(hipGetLastError());
+    }
+    return TUNA_OK;
+}
+
 // Cached schedule of (P, Q, r_l, r_g, fused).  The host keeps scalars only; the per-phase tables are
 // built on the device by k_build_phase_table, on the caller's stream (the kernels that read them
 // are enqueued behind it).
@@ -363,30 +389,20 @@ int get_plan(int P, int Q, int rl, int rg, bool fused, hipStream_t s, DevicePlan
             dp.d_seg_mem.push_back(dm);
             HIPCHK(hipMalloc((void**)&dz, align_up((size_t)P * 4)));
             dp.d_zt.push_back(dz);
-            hipLaunchKernelGGL(k_build_phase_table, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, s, dp.host.sc,
-                               phase_scalars(ph), dm, dm + stride, dm + 2 * stride, dm + 3 * stride, dm + 4 * stride,
-                               dm + 5 * stride, dm + 6 * stride, dm + 7 * stride, dz);
-            HIPCHK(hipGetLastError());
             dp.d_seg.push_back(SegDev{dm, dm + stride, dm + 2 * stride, dm + 3 * stride, dm + 4 * stride, dm + 5 * stride,
                                       dm + 6 * stride, dm + 7 * stride});
         }
         HIPCHK(hipMalloc((void**)&dp.d_hm1, align_up((size_t)P * 4)));
         HIPCHK(hipMalloc((void**)&dp.d_mask, align_up((size_t)P * 8)));
-        hipLaunchKernelGGL(k_build_hops, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, s, dp.host.sc, dp.d_hm1, dp.d_mask);
-        HIPCHK(hipGetLastError());
-        // the class tables of exact-size T come from the host (copied before the call returns: the
-        // vectors are temporaries)
-        std::vector<std::vector<int32_t>> tord;
-        build_class_tables(dp.host, tord, dp.tcls);
+        class_sizes(dp.host, dp.tcls);
         for (size_t i = 0; i < dp.host.phases.size(); ++i) {
             int32_t *d_o = nullptr, *d_c = nullptr;
-            HIPCHK(hipMalloc((void**)&d_o, align_up(tord[i].size() * 4 + 4)));
+            HIPCHK(hipMalloc((void**)&d_o, align_up(class_total(dp.tcls[i]) * 4 + 4)));
             dp.d_tord.push_back(d_o);
             HIPCHK(hipMalloc((void**)&d_c, align_up(dp.tcls[i].size() * 4 + 4)));
             dp.d_tcls.push_back(d_c);
-            if (!tord[i].empty()) HIPCHK(hipMemcpy(d_o, tord[i].data(), tord[i].size() * 4, hipMemcpyHostToDevice));
-            if (!dp.tcls[i].empty()) HIPCHK(hipMemcpy(d_c, dp.tcls[i].data(), dp.tcls[i].size() * 4, hipMemcpyHostToDevice));
         }
+        if (const int rc = launch_tables(dp, nullptr, 0, s)) return rc;
         dp.built_on = s;
         guard.dp = nullptr;
         it = sh.plans.emplace(key, std::move(dp)).first;
@@ -542,7 +558,7 @@ int run_validate(const StatusBufs& sb, const int32_t* sendcounts, const int32_t*
     const bool fold = sb.h_part_dev && vgrid <= (unsigned)kValFoldRows && ncls <= kValFoldClasses;
     const bool mail = sb.h_part_dev && sb.h_status_dev;
     const unsigned long long ticket = sb.h_part ? ++sb.h_part[kMailIssued] : 0;
-    if (ncls > 0 && !fold && !mail) {
+    if (ncls > 0 && !fold && !mail && !sb.sums_clear) {
         hipLaunchKernelGGL(k_zero64, dim3((unsigned)((ncls + 255) / 256)), dim3(256), 0, s, sb.d_status->cls_chunks, ncls);
         HIPCHK(hipGetLastError());
     }
@@ -1513,7 +1529,8 @@ bool runs_direct(const Prepared& pr) {
 // All the metadata of such a call: with exact-size T the places of the blocks that its phases store there.
 // The pairs lie in the hop arrays' destinations, which such a call does not use.
 constexpr int kPairsMinRadix = 16;          // neighbours 64 bytes apart and more
-int launch_t_places(Prepared& pr, hipStream_t s) {
+// own: if given, the ranks' own blocks are moved by the same launch when there is one (*own = true).
+int launch_t_places(Prepared& pr, hipStream_t s, bool* own = nullptr) {
     if (!pr.exact_t) return TUNA_OK;
     if (pr.dp->host.phases[0].r >= kPairsMinRadix && pr.hop.dst) pr.pairs = reinterpret_cast<uint2*>(pr.hop.dst);
     const PlanHost& pl = pr.dp->host;
@@ -1533,7 +1550,12 @@ int launch_t_places(Prepared& pr, hipStream_t s) {
         rows += ncls;
     }
     if (!rows) return TUNA_OK;
-    const dim3 grid((unsigned)pr.P, (unsigned)rows);
+    a.own = -1;
+    if (own) {
+        a.own = rows; *own = true;
+        a.S = (const unsigned char*)pr.sendbuf; a.sdispls = pr.sdispls; a.R = (unsigned char*)pr.recvbuf; a.rdispls = pr.rdispls;
+    }
+    const dim3 grid((unsigned)pr.P, (unsigned)(rows + (own ? 1 : 0)));
     if (pr.P <= kPlaceSlotRanks && pl.phases[0].r >= kPlaceSlotRadix)
         hipLaunchKernelGGL(k_t_places_slots, grid, dim3(kScanThreads), (size_t)a.most * 4 + (size_t)pr.P * 2, s, a);
     else
@@ -1595,22 +1617,26 @@ int run_one_pass(Prepared& pr, void* mbase, size_t mbytes, void* dbase, hipStrea
     }
     mark(pr.ctx, s, kCatPrepare, -1);
     const bool longs = direct && long_blocks(pr);             // the first phase takes the own blocks along
-    rc = longs ? TUNA_OK : launch_self_metadata(pr, s);
-    if (rc != TUNA_OK) return rc;
-    rc = longs ? TUNA_OK : launch_self_copy(pr, s);
-    if (rc != TUNA_OK) return rc;
+    bool own_moved = longs;
+    if (direct) {                                             // the places in exact-size T, and the own blocks with them
+        rc = launch_t_places(pr, s, longs || pr.self_engine ? nullptr : &own_moved);
+        if (rc != TUNA_OK) return rc;
+        mark(pr.ctx, s, kCatMeta, 0);
+    }
+    if (!own_moved) {
+        rc = launch_self_metadata(pr, s);
+        if (rc != TUNA_OK) return rc;
+        rc = launch_self_copy(pr, s);
+        if (rc != TUNA_OK) return rc;
+    }
     mark(pr.ctx, s, kCatSelf, -1);
 
     // ---- digit phases -----------------------------------------------------------------------------
     int32_t* cur = mb.cur;
     int32_t* nxt = mb.nxt;
     if (direct) {
-        // the places in exact-size T, then one kernel per phase that finds and moves its blocks.  The partial sums lie where
-        // the hop arrays would (a phase has at most one row per segment) and are added up when there is no room for the
-        // next phase's, at the latest at the end.
-        rc = launch_t_places(pr, s);
-        if (rc != TUNA_OK) return rc;
-        mark(pr.ctx, s, kCatMeta, 0);
+        // one kernel per phase that finds and moves its blocks.  The partial sums lie where the hop arrays would (a phase has
+        // at most one row per segment) and are added up when there is no room for the next phase's, at the latest at the end.
         if (longs) {
             for (size_t i = 0; i < pl.phases.size(); ++i) {
                 rc = launch_long_units(pr, i, mb.Ls.units, s);
@@ -2210,37 +2236,29 @@ int run_static(const void* sendbuf, const int32_t* sendcounts, const int64_t* sd
     dp.host = make_plan(P, Q, crl, crg, pr.fused, /*with_tables=*/false);
     if ((int)dp.host.phases.size() > TUNA_MAX_PHASES) return TUNA_ERR_TOO_LARGE;
     dp.borrowed = true;                       // nothing of it is freed: it all lies in the static array
-    std::vector<std::vector<int32_t>> tord;
-    build_class_tables(dp.host, tord, dp.tcls);
+    class_sizes(dp.host, dp.tcls);
     size_t table_bytes = align_up((size_t)P * 4) + align_up((size_t)P * 8);
     for (size_t i = 0; i < dp.host.phases.size(); ++i)
         table_bytes += 8 * align_up((size_t)dp.host.phases[i].nseg * 4) + align_up((size_t)P * 4) +
-                       align_up(tord[i].size() * 4 + 4) + align_up(dp.tcls[i].size() * 4 + 4);
+                       align_up(class_total(dp.tcls[i]) * 4 + 4) + align_up(dp.tcls[i].size() * 4 + 4);
     if (cv.off + table_bytes > cv.cap) return TUNA_ERR_NOALLOC_LIMIT;     // before any kernel is launched
     for (size_t i = 0; i < dp.host.phases.size(); ++i) {
         const PhaseHost& ph = dp.host.phases[i];
         const size_t stride = align_up((size_t)ph.nseg * 4) / 4;
         int32_t* dm = cv.take<int32_t>(8 * stride);
         int32_t* dz = cv.take<int32_t>(P);
-        hipLaunchKernelGGL(k_build_phase_table, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, s, dp.host.sc,
-                           phase_scalars(ph), dm, dm + stride, dm + 2 * stride, dm + 3 * stride, dm + 4 * stride,
-                           dm + 5 * stride, dm + 6 * stride, dm + 7 * stride, dz);
-        HIPCHK(hipGetLastError());
         dp.d_zt.push_back(dz);
         dp.d_seg.push_back(SegDev{dm, dm + stride, dm + 2 * stride, dm + 3 * stride, dm + 4 * stride, dm + 5 * stride,
                                   dm + 6 * stride, dm + 7 * stride});
-        int32_t* d_o = cv.take<int32_t>(tord[i].size() + 1);
-        int32_t* d_c = cv.take<int32_t>(dp.tcls[i].size() + 1);
-        // pageable source: the copy has left the host arrays when the call returns
-        if (!tord[i].empty()) HIPCHK(hipMemcpyAsync(d_o, tord[i].data(), tord[i].size() * 4, hipMemcpyHostToDevice, s));
-        if (!dp.tcls[i].empty()) HIPCHK(hipMemcpyAsync(d_c, dp.tcls[i].data(), dp.tcls[i].size() * 4, hipMemcpyHostToDevice, s));
-        dp.d_tord.push_back(d_o);
-        dp.d_tcls.push_back(d_c);
+        dp.d_tord.push_back(cv.take<int32_t>(class_total(dp.tcls[i]) + 1));
+        dp.d_tcls.push_back(cv.take<int32_t>(dp.tcls[i].size() + 1));
     }
     dp.d_hm1 = cv.take<int32_t>(P);
     dp.d_mask = cv.take<unsigned long long>(P);
-    hipLaunchKernelGGL(k_build_hops, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, s, dp.host.sc, dp.d_hm1, dp.d_mask);
-    HIPCHK(hipGetLastError());
+    // the class sums that validation adds to are cleared on the way
+    rc = launch_tables(dp, pr.sb.d_status->cls_chunks, class_count((int)dp.host.phases.size()), s);
+    if (rc != TUNA_OK) return rc;
+    pr.sb.sums_clear = true;
     dp.built_on = s;
     pr.dp = &dp;
 
@@ -2310,13 +2328,17 @@ Features features_of(const PlanHost& pl, double payload_bytes, bool small) {
     const double P = (double)pl.P;
     f.phases = (double)pl.phases.size();
     f.p2 = (f.phases + 1.0) * P * P / 1e6;      // the passes over the P x P size matrix: one per phase, one for validation and rotation
-    double moving = 0.0;
-    for (const auto& ph : pl.phases) moving += (double)ph.nseg * P;
+    double moving = 0.0, by_sender = 0.0;
+    for (const auto& ph : pl.phases) {
+        moving += (double)ph.nseg * P;
+        if (ph.nz >= kSenderMinRounds) by_sender += (double)ph.nseg * P;
+    }
     (small ? f.msmall : f.mblocks) = moving / 1e6;
     // A short block of a schedule of one phase is looked up in the receive counts and the displacements; with several
     // phases its place in T is scanned, stored and looked up twice, and most lookups leave the rows of one rank.  Four
-    // times the constant fits uniform [0, 16] B at P = 2048 within 10 % at r = 2, 8, 46 and P.
-    if (small && f.phases > 1.0) f.msmall *= 4.0;
+    // times the constant fits uniform [0, 16] B at P = 2048 within 10 % at r = 2, 8, 46 and P; three times where
+    // k_hop_senders finds them (r = 46: 0.199 ms, predicted with four times 0.247).
+    if (small && f.phases > 1.0) f.msmall = (4.0 * moving - by_sender) / 1e6;
     // sizes are taken to be independent of the rank distance: every slot index carries payload / P^2
     (small ? f.small_gb : f.hop_gb) = P > 0 ? payload_bytes * (moving / (P * P)) / 1e9 : 0.0;
     // a block of h hops passes through T h - 1 times: it is written there h - 1 times and read h - 1 times,

@@ -146,31 +146,84 @@ __device__ __forceinline__ int partner_up(int n, int g, int Q, int N, int dim, i
 }
 
 // ------------------------------------------------------------------------------------------
-// k_build_phase_table: the rank-independent table of one digit phase, built on the device.  One
+// k_build_tables: the rank-independent tables of the digit phases, built on the device.  One
 // thread per slot index e: its digit value z in this phase (Algorithm "TuNA", lines 8-11: the
 // blocks whose x-th base-r digit equals z), its position in message order, the T slot it is read
 // from / stored to by the map t = o - 1 - dx (r-1) - dz (Section "Estimating temporary buffer
 // size"), or -1 for the send / receive buffer.
 // ------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_build_phase_table(const PlanScalars pl, const PhaseScalars ph,
-                                                           int32_t* __restrict__ seg_e, int32_t* __restrict__ seg_z,
-                                                           int32_t* __restrict__ seg_src, int32_t* __restrict__ seg_dst,
-                                                           int32_t* __restrict__ seg_srcph, int32_t* __restrict__ seg_srcseg,
-                                                           int32_t* __restrict__ seg_scls, int32_t* __restrict__ seg_dcls,
-                                                           int32_t* __restrict__ zt) {
+constexpr int kBuildPhases = 24;
+struct BuildPhase {
+    PhaseScalars ps;
+    int32_t* mem;           // e, z, src, dst, srcph, srcseg, scls, dcls (SegDev), `stride` entries each
+    int32_t* zt;
+    int32_t* tord;          // ExactT
+    int32_t* tcls;
+    int stride;
+};
+struct BuildArgs {
+    PlanScalars pl;
+    BuildPhase ph[kBuildPhases];
+    int first;              // index of ph[0] in the schedule
+    int32_t* hm1;
+    unsigned long long* mask;
+    unsigned long long* zero;           // n_zero words to clear on the way
+    int n_zero;
+};
+// grid (ceil(P / 256), phases); the first row also runs build_hops
+__device__ __forceinline__ void build_hops(const PlanScalars& pl, int e, int32_t* hm1, unsigned long long* mask);
+__global__ void __launch_bounds__(256) k_build_tables(const BuildArgs a) {
+    const PlanScalars& pl = a.pl;
+    const BuildPhase& b = a.ph[blockIdx.y];
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
+    if (blockIdx.x == 0 && blockIdx.y == 0)
+        for (int i = threadIdx.x; i < a.n_zero; i += blockDim.x) a.zero[i] = 0;
     if (e >= pl.P) return;
+    if (blockIdx.y == 0 && a.first == 0) build_hops(pl, e, a.hm1, a.mask);
     SegInfo s;
     int pos = 0;
-    if (slot_entry(pl, ph, e, &s, &pos)) {
-        zt[e] = s.z;
-        seg_e[pos] = s.e; seg_z[pos] = s.z; seg_src[pos] = s.src_slot; seg_dst[pos] = s.dst_slot;
-        seg_srcph[pos] = s.src_phase; seg_srcseg[pos] = s.src_seg;
-        const int cur = ph.dim == 0 ? ph.x : pl.w_l + ph.x;
-        seg_scls[pos] = s.src_phase >= 0 ? class_id(s.src_phase, cur, pl.nph) : -1;
-        seg_dcls[pos] = s.nxt_phase >= 0 ? class_id(cur, s.nxt_phase, pl.nph) : -1;
+    if (slot_entry(pl, b.ps, e, &s, &pos)) {
+        b.zt[e] = s.z;
+        int32_t* m = b.mem + pos;
+        const size_t ld = (size_t)b.stride;
+        m[0] = s.e; m[ld] = s.z; m[2 * ld] = s.src_slot; m[3 * ld] = s.dst_slot; m[4 * ld] = s.src_phase; m[5 * ld] = s.src_seg;
+        const int cur = b.ps.dim == 0 ? b.ps.x : pl.w_l + b.ps.x;
+        m[6 * ld] = s.src_phase >= 0 ? class_id(s.src_phase, cur, pl.nph) : -1;
+        m[7 * ld] = s.nxt_phase >= 0 ? class_id(cur, s.nxt_phase, pl.nph) : -1;
     } else {
-        zt[e] = 0;
+        b.zt[e] = 0;
+    }
+}
+
+// k_build_classes: the T-bound segments of every phase grouped by the class they are stored into, in message order (ExactT,
+// tord and tcls).  Grid (classes a phase can have, phases), one wave per class: it counts the segments of the classes before
+// its own and lists its own.  (On the host, and the lists copied to the device, it cost a call that may keep nothing 15 us.)
+__global__ void __launch_bounds__(kWave) k_build_classes(const BuildArgs a) {
+    const int f = a.first + blockIdx.y, first = class_id(f, f + 1, a.pl.nph), cid = first + blockIdx.x, lane = threadIdx.x;
+    if (f + 1 + (int)blockIdx.x >= a.pl.nph) return;
+    const BuildPhase& b = a.ph[blockIdx.y];
+    const int32_t* dcls = b.mem + 7 * (size_t)b.stride;
+    const int nseg = b.ps.nseg;
+    int before = 0, own = 0;
+    unsigned long long seen = 0;                         // classes before this one that have segments
+    for (int s = lane; s < nseg; s += kWave) {
+        const int c = dcls[s];
+        if (c >= first && c < cid) { ++before; seen |= 1ull << (c - first); }
+        own += c == cid;
+    }
+#pragma unroll
+    for (int d = kWave / 2; d > 0; d >>= 1) {
+        before += __shfl_xor(before, d, kWave);
+        own += __shfl_xor(own, d, kWave);
+        seen |= __shfl_xor(seen, d, kWave);
+    }
+    if (own == 0) return;
+    if (lane < 3) b.tcls[3 * __popcll(seen) + lane] = lane == 0 ? cid : lane == 1 ? before : own;
+    int at = before;
+    for (int s0 = 0; s0 < nseg; s0 += kWave) {
+        const unsigned long long mine = __ballot(s0 + lane < nseg && dcls[min(s0 + lane, nseg - 1)] == cid);
+        if (mine >> lane & 1) b.tord[at + __popcll(mine & ((1ull << lane) - 1))] = s0 + lane;
+        at += __popcll(mine);
     }
 }
 
@@ -197,14 +250,11 @@ __global__ void __launch_bounds__(256) k_fill_uniform(int32_t* __restrict__ send
 }
 
 // ------------------------------------------------------------------------------------------
-// k_build_hops: hm1[e] = (hops of the block with slot index e) - 1, at least 0.  A block makes one
+// build_hops: hm1[e] = (hops of the block with slot index e) - 1, at least 0.  A block makes one
 // hop per non-zero digit of its distance pair (l in base r_l, j in base r_g) and is stored into T
 // after every hop but its last -- hm1[e] times.
 // ------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_build_hops(const PlanScalars pl, int32_t* __restrict__ hm1,
-                                                    unsigned long long* __restrict__ mask) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= pl.P) return;
+__device__ __forceinline__ void build_hops(const PlanScalars& pl, int e, int32_t* hm1, unsigned long long* mask) {
     mask[e] = move_mask(pl, e);
     int j = e / pl.Q, l = e - j * pl.Q, hops = 0;
     for (; l; l /= pl.rl) hops += (l % pl.rl) != 0;
@@ -546,26 +596,28 @@ __global__ void __launch_bounds__(256) k_rotate_init(const int32_t* __restrict__
 // k_self_copy: the block a rank keeps for itself goes straight from S to R (Section "Estimating
 // temporary buffer size": one block is destined for the rank itself).  grid (P, split).
 // ------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_self_copy(const unsigned char* __restrict__ S,
-                                                   const int32_t* __restrict__ sendcounts,
-                                                   const int64_t* __restrict__ sdispls,
-                                                   unsigned char* __restrict__ R,
-                                                   const int64_t* __restrict__ rdispls, int P) {
-    const int p = blockIdx.x;
+__device__ __forceinline__ void own_block(const unsigned char* __restrict__ S, const int32_t* __restrict__ sendcounts,
+                                          const int64_t* __restrict__ sdispls, unsigned char* __restrict__ R,
+                                          const int64_t* __restrict__ rdispls, int P, int p) {
     const size_t d = (size_t)p * P + p;
     const int n = sendcounts[d];
     const unsigned char* src = S + sdispls[d];
     unsigned char* dst = R + rdispls[d];
     const int nchunk = n >> 4;
-    for (int c = blockIdx.y * blockDim.x + threadIdx.x; c < nchunk; c += gridDim.y * blockDim.x) {
+    for (int c = threadIdx.x; c < nchunk; c += 256) {
         uint4 v;
         __builtin_memcpy(&v, src + ((size_t)c << 4), 16);
         __builtin_memcpy(dst + ((size_t)c << 4), &v, 16);
     }
-    if (blockIdx.y == 0) {
-        const int tail = n & 15;
-        if ((int)threadIdx.x < tail) dst[(nchunk << 4) + threadIdx.x] = src[(nchunk << 4) + threadIdx.x];
-    }
+    const int tail = n & 15;
+    if ((int)threadIdx.x < tail) dst[(nchunk << 4) + threadIdx.x] = src[(nchunk << 4) + threadIdx.x];
+}
+__global__ void __launch_bounds__(256) k_self_copy(const unsigned char* __restrict__ S,
+                                                   const int32_t* __restrict__ sendcounts,
+                                                   const int64_t* __restrict__ sdispls,
+                                                   unsigned char* __restrict__ R,
+                                                   const int64_t* __restrict__ rdispls, int P) {
+    own_block(S, sendcounts, sdispls, R, rdispls, P, blockIdx.x);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1312,6 +1364,11 @@ struct PlaceArgs {
     uint2* pairs;           // of the first phase (ResolveArgs)
     int pairs_ld;
     int most;               // blocks of the largest class
+    int own;                // workgroup row that moves the ranks' own blocks (own_block), or -1
+    const unsigned char* S;
+    const int64_t* sdispls;
+    unsigned char* R;
+    const int64_t* rdispls;
     int by_value;           // the classes' first chunks are here, not in x.cbase: no copy to the device before the kernels
     long long cbase[kPlaceClasses];
 };
@@ -1323,6 +1380,7 @@ __device__ __forceinline__ int place_phase(const PlaceArgs& a, int row) {
 __global__ void __launch_bounds__(kScanThreads) k_t_places(const PlaceArgs a) {
     __shared__ int wsum[kScanThreads / kWave];
     const int p = blockIdx.x, P = a.P;
+    if ((int)blockIdx.y == a.own) { own_block(a.S, a.sendcounts, a.sdispls, a.R, a.rdispls, P, p); return; }
     const int f = place_phase(a, blockIdx.y);
     const PlacePhase& ph = a.ph[f];
     const int32_t* cls = ph.tcls + 3 * (blockIdx.y - ph.first);
@@ -1363,6 +1421,7 @@ __global__ void __launch_bounds__(kScanThreads) k_t_places_slots(const PlaceArgs
     constexpr int kNone = 0xffff;
     unsigned short* s_at = reinterpret_cast<unsigned short*>(s_val + a.most);        // by slot index: the index inside the class
     const int p = blockIdx.x, P = a.P;
+    if ((int)blockIdx.y == a.own) { own_block(a.S, a.sendcounts, a.sdispls, a.R, a.rdispls, P, p); return; }
     const int f = place_phase(a, blockIdx.y);
     const PlacePhase& ph = a.ph[f];
     const int32_t* cls = ph.tcls + 3 * (blockIdx.y - ph.first);
