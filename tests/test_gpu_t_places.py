@@ -1,7 +1,8 @@
 """The places of waiting blocks in exact-size T and the phases that find their blocks by them: on both sides of the radix
 and of the rank count where the kernel that lays them out changes, classes of one block and of several batches of a
-workgroup, ranks that no tile divides, hierarchies, gapped and permuted regions, empty blocks.  Reference: the same call
-with three-stage phases and T in slots, which asks for no places."""
+workgroup, ranks that no tile divides, hierarchies, gapped and permuted regions, empty blocks; on both sides of the number
+of rounds from which a workgroup takes the blocks of one sender, with each of its block sizes and kinds of access, and with
+several steps per workgroup.  Reference: the same call with three-stage phases and T in slots, which asks for no places."""
 import numpy as np
 import pytest
 
@@ -28,6 +29,10 @@ CASES = [
     (1024, 0, 1023, 1023, 16, 8, 0.0, {}), (1100, 0, 17, 17, 15, 1, 0.5, {}), (1300, 0, 36, 36, 64, 4, 0.0, {"gap": 4}),
     (1500, 0, 40, 40, 256, 16, 0.0, {"align": 16}), (96, 12, 8, 8, 60, 4, 0.0, {}), (1024, 32, 32, 32, 16, 4, 0.1, {"gap": 2, "permute_seed": 3}),
     (1200, 60, 16, 20, 64, 1, 0.0, {}), (2100, 70, 8, 30, 12, 4, 0.0, {}), (2049, 0, 46, 46, 16, 8, 0.0, {}),
+    # 11, 12 and 13 rounds; the first and the last phase with their own; one block per lane, four and sixteen lanes per block
+    (144, 0, 12, 12, 16, 4, 0.0, {}), (169, 0, 13, 13, 16, 1, 0.1, {"gap": 5, "permute_seed": 4}), (170, 0, 13, 13, 64, 4, 0.0, {}),
+    (183, 0, 14, 14, 64, 16, 0.1, {"align": 16}), (300, 0, 20, 20, 256, 16, 0.1, {"align": 16}), (259, 0, 16, 16, 256, 1, 0.0, {}),
+    (270, 0, 15, 15, 128, 128, 0.3, {"align": 128}), (600, 30, 13, 20, 200, 4, 0.2, {"gap": 1, "permute_seed": 6}), (390, 15, 15, 13, 64, 1, 0.0, {}),
 ]
 
 
@@ -77,8 +82,9 @@ def test_places(tuna, i):
     _run(tuna, P, rpn, rl, rg, counts, lay_args)
 
 
-@pytest.mark.parametrize("P,radix", [(8192, 91), (8193, 91)])
-def test_places_of_many_ranks(tuna, P, radix):
-    """One pair in eight exchanges a word: most classes' blocks are empty."""
+@pytest.mark.parametrize("P,radix,size", [(8192, 91, 4), (8193, 91, 4), (8193, 91, 20)])
+def test_places_of_many_ranks(tuna, P, radix, size):
+    """One pair in eight exchanges a word or five: most classes' blocks are empty.  (20 bytes are moved by four lanes each,
+    several steps of one sender's blocks per workgroup.)"""
     rng = np.random.default_rng(P)
-    _run(tuna, P, 0, radix, radix, (rng.integers(0, 8, (P, P), dtype=np.int32) == 3).astype(np.int32) * 4, {})
+    _run(tuna, P, 0, radix, radix, (rng.integers(0, 8, (P, P), dtype=np.int32) == 3).astype(np.int32) * size, {})
