@@ -372,7 +372,7 @@ int tuna_plan_phase(int P, int ranks_per_node, int local_radix, int global_radix
 int tuna_plan_phase_sources(int P, int ranks_per_node, int local_radix, int global_radix, int phase,
                             int on_device, int32_t* out, int capacity);
 
-/* The same table as the device holds it (the kernels read tables that k_build_phase_table built
+/* The same table as the device holds it (the kernels read tables that k_build_tables built
  * on the GPU with the same index arithmetic): four int32 per moving block in message order,
  * {e, z, source slot, destination slot}.  Needs a GPU; synchronises.  For verification. */
 int tuna_plan_phase_device(int P, int ranks_per_node, int local_radix, int global_radix, int phase,

@@ -354,7 +354,7 @@ int launch_tables(const DevicePlan& dp, unsigned long long* zero, int n_zero, hi
 }
 
 // Cached schedule of (P, Q, r_l, r_g, fused).  The host keeps scalars only; the per-phase tables are
-// built on the device by k_build_phase_table, on the caller's stream (the kernels that read them
+// built on the device by k_build_tables, on the caller's stream (the kernels that read them
 // are enqueued behind it).
 // Radices clamped the way make_plan clamps them.
 void clamp_radices(int Q, int N, int rl, int rg, int* crl, int* crg) {

@@ -207,7 +207,7 @@ def test_fft_count_patterns(tuna, pattern):
 @pytest.mark.parametrize("P,Q,rl,rg", [(16, 0, 2, 2), (30, 0, 3, 3), (64, 0, 64, 64), (24, 4, 2, 3), (60, 5, 5, 2),
                                         (256, 16, 4, 8), (1000, 0, 10, 10)])
 def test_device_built_tables_match_the_host_schedule(tuna, P, Q, rl, rg, mode):
-    """The kernels read tables that k_build_phase_table built on the GPU; they must equal the
+    """The kernels read tables that k_build_tables built on the GPU; they must equal the
     host-side schedule (which tests/test_host_plan.py replays on the CPU) entry for entry."""
     rc, info = tuna.tuna_plan_info(P, Q, rl, rg)
     assert rc == 0
