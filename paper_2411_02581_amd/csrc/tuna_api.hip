@@ -1169,6 +1169,7 @@ unsigned direct_columns(const Prepared& pr, const PhaseHost& ph, int nseg, int* 
     *iters = (int)std::max(1LL, std::min(8LL, steps * rows / 8192));
     return (unsigned)((steps + *iters - 1) / *iters);
 }
+bool runs_direct(const Prepared& pr);
 // Phases that an immediate call's k_hop_senders moves, and its workgroup columns and steps per workgroup (as direct_columns).
 unsigned sender_columns(const Prepared& pr, const PhaseHost& ph, int* iters) {
     const int steps = (ph.nseg + 255) / 256;
@@ -1180,7 +1181,39 @@ bool sender_phase(const Prepared& pr, const PhaseHost& ph) {
     return pr.dp->host.phases.size() > 1 && ph.nz >= kSenderMinRounds && ph.nz <= kSenderMaxRounds &&
            (long long)sender_columns(pr, ph, &iters) * ph.nz <= ph.nseg;       // (rows of partial sums: no more than segments)
 }
+// The only phase of an immediate call's linear schedule, if its blocks are short: k_hop_pairs moves it, and the own blocks; its
+// workgroup columns and steps per workgroup (as direct_columns).
+bool pair_phase(const Prepared& pr) { return pr.dp->host.phases.size() == 1 && runs_direct(pr) && small_blocks(pr) && !long_blocks(pr); }
+PairShape pair_tile(const Prepared& pr) { return pair_shape(direct_lpb(pr), pr.gran >= 16); }
+unsigned pair_columns(const Prepared& pr, int* iters) {
+    const PairShape sh = pair_tile(pr);
+    const long long steps = (pr.P + sh.senders - 1) / sh.senders, rows = (pr.P + pair_ranks(sh) - 1) / pair_ranks(sh);
+    *iters = (int)std::max(1LL, std::min(8LL, steps * rows / 8192));
+    return (unsigned)((steps + *iters - 1) / *iters);
+}
+template <int LPB, int STREAM>
+void launch_pairs_as(const DirectArgs& a, dim3 grid, hipStream_t s) {
+    hipLaunchKernelGGL((k_hop_pairs<LPB, STREAM>), grid, dim3(256), 0, s, a);
+}
+int launch_pairs(const Prepared& pr, uint2* part, hipStream_t s) {
+    DirectArgs a{};
+    a.r = resolve_args(pr, 0, nullptr, HopDev{});
+    a.part = part;
+    const unsigned cols = pair_columns(pr, &a.iters), ranks = (unsigned)pair_ranks(pair_tile(pr));
+    const dim3 grid(cols, ((unsigned)pr.P + ranks - 1) / ranks);
+    const int lpb = direct_lpb(pr);
+    if (lpb == 1) launch_pairs_as<1, 0>(a, grid, s);
+    else if (lpb == 4) {
+        if (pr.gran >= 16) launch_pairs_as<4, 1>(a, grid, s);
+        else launch_pairs_as<4, 0>(a, grid, s);
+    } else if (pr.gran == 128) launch_pairs_as<16, 2>(a, grid, s);
+    else if (pr.gran == 16) launch_pairs_as<16, 1>(a, grid, s);
+    else launch_pairs_as<16, 0>(a, grid, s);
+    HIPCHK(hipGetLastError());
+    return TUNA_OK;
+}
 unsigned direct_rows(const Prepared& pr, const PhaseHost& ph) {
+    if (pair_phase(pr)) { int iters = 0; return pair_columns(pr, &iters); }
     if (!row_blocks(pr) && sender_phase(pr, ph)) { int iters = 0; return sender_columns(pr, ph, &iters) * (unsigned)ph.nz; }
     if (row_blocks(pr)) { const int segs = rows_segs(pr); return (unsigned)((ph.nseg + segs - 1) / segs); }
     int iters = 0;
@@ -1570,6 +1603,7 @@ int launch_t_places(Prepared& pr, hipStream_t s, bool* own = nullptr) {
 int launch_direct_payload(const Prepared& pr, size_t i, uint2* part, hipStream_t s) {
     const PhaseHost& ph = pr.dp->host.phases[i];
     const int rc = row_blocks(pr)         ? launch_rows(pr, i, HopDev{}, part, s)
+                   : pair_phase(pr)       ? launch_pairs(pr, part, s)
                    : sender_phase(pr, ph) ? launch_senders(pr, i, part, s)
                                           : launch_direct(pr, i, HopDev{}, 0, ph.nseg, part, s);
     if (rc == TUNA_OK) mark(pr.ctx, s, kCatPack, (int)i);
@@ -1616,8 +1650,8 @@ int run_one_pass(Prepared& pr, void* mbase, size_t mbytes, void* dbase, hipStrea
         HIPCHK(hipGetLastError());
     }
     mark(pr.ctx, s, kCatPrepare, -1);
-    const bool longs = direct && long_blocks(pr);             // the first phase takes the own blocks along
-    bool own_moved = longs;
+    const bool longs = direct && long_blocks(pr);
+    bool own_moved = longs || (direct && pair_phase(pr));     // the first phase takes the own blocks along
     if (direct) {                                             // the places in exact-size T, and the own blocks with them
         rc = launch_t_places(pr, s, longs || pr.self_engine ? nullptr : &own_moved);
         if (rc != TUNA_OK) return rc;

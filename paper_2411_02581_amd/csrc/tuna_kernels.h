@@ -1732,6 +1732,71 @@ __global__ void __launch_bounds__(256) k_hop_senders(const DirectArgs a) {
     }
 }
 
+// ------------------------------------------------------------------------------------------
+// k_hop_pairs: k_hop_direct for the only phase of a linear schedule, where every block goes from S to R in its only hop: a
+// tile of senders x receivers in the order of the ranks instead of receivers x rounds.  The rows of recvcounts, sdispls and
+// rdispls that a tile needs are whole lines (a tile of rounds is a parallelogram in them: 11 KB of lines for the 5 KB of 256
+// blocks), no table is read, and the ranks' own blocks are on the diagonal: no launch for them.
+//   Bound by memory.  k_hop_direct / k_hop_pairs, us per call: up to 16 bytes, P = 1024 57 / 48, 3000 198 / 163, 8192 1455 / 1124;
+// up to 60, P = 5000 866 / 823, 32-byte blocks, P = 4096 464 / 401, the FFT's 64-byte ones, P = 8192 1574 / 1474; up to
+// 200, P = 1000 82 / 77, 2500 457 / 444, up to 256, P = 1200 159 / 153, 500 55 / 50; P = 100 to 300 42-46 / 38-42.
+//   The tile: up to 16 bytes 32 x 32 (2 x 2 blocks per lane instead of 4: 3000 176; 64 senders 173, 16 178).  Up to 64 bytes 16 x 16,
+// and 8 x 32 where blocks share no 16 bytes and the runs of S that a tile reads count (FFT 1568 with 16 x 16, 1474; P = 5000 823 and
+// 836, Zipf up to 64, P = 6000 803 and 886; 32 x 8 everywhere slower).  Up to 256 bytes 64 x 4, one receiver's stores per wave (16 x 16:
+// P = 1000 86, but 2500 422).  The next step's lookups before this one's payload: no difference.
+// ------------------------------------------------------------------------------------------
+// the tile of one workgroup and step: senders side by side, and blocks a lane finds (of neighbouring receivers)
+struct PairShape { int senders, sets; };
+constexpr PairShape pair_shape(int lpb, bool stream) { return lpb == 1 ? PairShape{32, 4} : PairShape{lpb == 16 ? 64 : stream ? 8 : 16, 1}; }
+constexpr int pair_ranks(PairShape s) { return 4 * (kWave / s.senders) * s.sets; }      // receivers of a tile
+template <int LPB, int STREAM>
+__global__ void __launch_bounds__(256) k_hop_pairs(const DirectArgs a) {
+    constexpr PairShape SH = pair_shape(LPB, STREAM != 0);
+    constexpr int SEND = SH.senders, SETS = SH.sets;
+    __shared__ ShortLds<LPB> lds;
+    const ResolveArgs& r = a.r;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int P = r.P;
+    const int p0 = blockIdx.y * pair_ranks(SH) + (wv * (kWave / SEND) + lane / SEND) * SETS;
+    const int sub = lane & (SEND - 1);
+    unsigned int sum_b[SETS], sum_c[SETS];
+#pragma unroll
+    for (int u = 0; u < SETS; ++u) sum_b[u] = sum_c[u] = 0;
+    const int first = blockIdx.x * a.iters * SEND, last = min(P, first + a.iters * SEND);
+    for (int q0 = first; q0 < last; q0 += SEND) {
+        const int q = min(q0 + sub, P - 1);
+        int n[SETS];
+        long long va[SETS], vc[SETS];
+#pragma unroll
+        for (int u = 0; u < SETS; ++u) {
+            const int p = min(p0 + u, P - 1);
+            n[u] = r.recvcounts[(size_t)p * P + q];
+            va[u] = r.sdispls[(size_t)q * P + p];
+            vc[u] = r.rdispls[(size_t)p * P + q];
+        }
+        unsigned long long src[SETS], dst[SETS];
+#pragma unroll
+        for (int u = 0; u < SETS; ++u) {
+            if (q0 + sub >= last || p0 + u >= P) n[u] = 0;
+            n[u] = min(n[u], 16 * LPB);                  // validation has bounded it: nothing is cut here
+            src[u] = (unsigned long long)r.S + (unsigned long long)va[u];
+            dst[u] = (unsigned long long)r.R + (unsigned long long)vc[u];
+            if (q0 + sub != p0 + u) {                        // (the own block is no part of the phase)
+                sum_b[u] += (unsigned int)n[u];
+                sum_c[u] += n[u] > 0 ? ((unsigned int)(dst[u] & 15ull) + (unsigned int)n[u] + 15u) >> 4 : 0u;
+            }
+        }
+        move_short<LPB, STREAM>(src, dst, n, (unsigned long long)r.recvcounts, lds);
+    }
+#pragma unroll
+    for (int u = 0; u < SETS; ++u) {
+#pragma unroll
+        for (int d = SEND / 2; d > 0; d >>= 1) { sum_b[u] += __shfl_xor(sum_b[u], d, kWave); sum_c[u] += __shfl_xor(sum_c[u], d, kWave); }
+        if (sub == 0 && p0 + u < P) a.part[(size_t)blockIdx.x * P + p0 + u] = make_uint2(sum_b[u], sum_c[u]);
+    }
+}
+
 // pieces segment s owns, and the dead pieces in front of them
 __device__ __forceinline__ int tiled_pieces(unsigned long long a, int n, bool has_prev, unsigned long long e_prev,
                                             int* dead) {
