@@ -796,7 +796,12 @@ bool too_large(int P, const Status& hs) {
     return std::min(by_m, by_all) >= (1ull << 31);
 }
 
-int rows_segs(const Prepared& pr);
+// Segments of kRowsLongBytes of payload by the mean block: what the rules below, which choose between the hops, take a wave
+// of k_hop_rows to have, and were measured with.  (It has no more: rows_segs.)
+double rows_span(const Prepared& pr) {
+    const double mean = std::max(1.0, (double)pr.total_bytes / ((double)pr.P * (double)pr.P));
+    return std::floor(std::max(1.0, std::min(64.0, kRowsLongBytes / mean)));
+}
 constexpr double kRowsEvenBytes = 24576.0;      // a wave of k_hop_rows with no more is done in three steps
 
 // The mean block up to which k_hop_rows is taken where the destination-tiled hop can run, or the engine's on whole lines:
@@ -805,7 +810,7 @@ constexpr double kRowsEvenBytes = 24576.0;      // a wave of k_hop_rows with no 
 // the payload is small.  Normal sizes, per call, tiled against rows: 1 KiB, P = 2048, r = 8 5.39 / 5.23 ms, 1.5 KiB 7.69 /
 // 7.84, 1.8 KiB 9.08 / 9.56; P = 1024 (2.5 to 4 GB), r = 8, 2.4 KiB 2.99 / 3.08, 3.6 KiB 4.31 / 4.62, r = 2 6.99 / 7.39;
 // P = 512 (630 to 940 MB), r = 8, 2.4 KiB 0.74 / 0.68, 3.2 KiB 0.92 / 0.87, r = 2, 3.6 KiB 1.76 / 1.83; P = 256 (240 MB),
-// r = 4, 3.6 KiB 0.40 / 0.34.  Above half of kRowsBytes a wave has one block and half-empty lanes.
+// r = 4, 3.6 KiB 0.40 / 0.34.  Above half of kRowsLongBytes a wave has one block and half-empty lanes.
 // Where some phases could not be tiled (many short blocks in the last one, T in slots) rows are the faster ones throughout
 // up to 4 KiB, in plans too, while waves are even (every other block empty, the others 4092 bytes, P = 1024: per call 936 /
 // 855 us, r = 16 2.27 / 2.15 ms, per start 841 / 786 us), not where a wave can meet several long blocks (Zipf sizes up to
@@ -821,9 +826,9 @@ double rows_mean_limit(const Prepared& pr) {
     if (pr.gran == 128) return !one_layout ? HUGE_VAL : !pr.for_plan ? 16384.0 : pr.max_count <= 12288 ? HUGE_VAL : 0.0;
     if (!pr.tiled) return HUGE_VAL;
     const bool all_tiled = pr.tiled_final && one_layout;
-    if (!all_tiled && (double)rows_segs(pr) * (double)pr.max_count <= kRowsEvenBytes) return 4096.0;
+    if (!all_tiled && rows_span(pr) * (double)pr.max_count <= kRowsEvenBytes) return 4096.0;
     if (pr.for_plan || pr.total_bytes > (1ull << 30)) return 1536.0;
-    return pr.total_bytes > (256ull << 20) ? kRowsBytes / 2 : 4096.0;
+    return pr.total_bytes > (256ull << 20) ? kRowsLongBytes / 2 : 4096.0;
 }
 
 // Bytes of the fullest window of blocks (Status.windows), and whether it holds more than `times` the mean one.
@@ -856,7 +861,7 @@ bool clustered(const Prepared& pr, double times) {
 // cost the engine more, up to 64 KiB among 512 (460 MB) 239 / 212, up to 16 KiB among 256 (39 MB, r = 8) 60 / 70.
 bool rows_balanced(const Prepared& pr) {
     const double total = (double)pr.total_bytes;
-    const double apart = (double)rows_segs(pr) * (double)pr.max_count, longest = std::min(fullest_window(pr), apart);
+    const double apart = rows_span(pr) * (double)pr.max_count, longest = std::min(fullest_window(pr), apart);
     if (pr.dp->host.phases.size() > 1 && apart > (pr.gran < 4 ? 294912.0 : 163840.0) && (pr.for_plan || total > 268435456.0)) return false;
     const bool even = !clustered(pr, 6.0);
     if (pr.for_plan) return longest <= kRowsEvenBytes + (even ? total / (pr.gran < 4 ? 1600.0 : 6144.0) : 0.0);
@@ -1152,10 +1157,15 @@ void launch_direct_shape(int lpb, int gran, const DirectArgs& a, dim3 grid, bool
     else launch_direct_as<16, TALL, 0>(a, grid, exact, s);
 }
 
-// segments a wave of k_hop_rows takes: about kRowsBytes of payload by the mean block
+// Segments a wave of k_hop_rows takes, by the mean block.  Up to 600 bytes kRowsBytes of payload: sizes vary, and a wave whose
+// pieces do not fit into one step of 8 KiB takes a second, nearly empty one (7000 / 5200 bytes: uniform up to 1 KiB, P = 1000
+// 219 / 210 us per start, up to 600 bytes, P = 400, r = 20 48 / 46, 512-byte blocks, P = 1500, r = 2 2252 / 2227 per call).  Longer ones
+// kRowsLongBytes (5200 on 1 KiB blocks, P = 4096 and on Zipf ones of 700 bytes, P = 1024 and 1000: +1 to +4 %).  Small problems 8 and
+// more, pairs / 8192 of them, so that there are waves for all compute units (uniform up to 1 KiB, P = 256, r = 4 104 / 100 us per
+// call, 16 x 16 ranks 102 / 97, up to 1200 bytes, P = 128, r = 2 108 / 98, up to 300, P = 100 68 / 62; 2 to 5 segments: up to 40 % slower).
 int rows_segs(const Prepared& pr) {
-    const double mean = std::max(1.0, (double)pr.total_bytes / ((double)pr.P * (double)pr.P));
-    return (int)std::max(1.0, std::min(64.0, kRowsBytes / mean));
+    const double pairs = (double)pr.P * (double)pr.P, mean = std::max(1.0, (double)pr.total_bytes / pairs);
+    return (int)std::min(std::max(8.0, pairs / 8192.0), mean <= 600.0 ? std::max(1.0, std::min(64.0, kRowsBytes / mean)) : rows_span(pr));
 }
 
 int direct_lpb(const Prepared& pr) { return pr.max_count <= 16 ? 1 : (pr.max_count <= 64 ? 4 : 16); }

@@ -1811,7 +1811,7 @@ __device__ __forceinline__ int tiled_pieces(unsigned long long a, int n, bool ha
 // ------------------------------------------------------------------------------------------
 // k_hop_rows: a one-kernel phase of blocks of up to 64 KiB, any alignment and granularity, and any sizes that leave its
 // waves balanced (rows_balanced).  One wave takes
-// `segs` neighbouring segments of one receiver, about 7 KB of payload: lane i finds block s0 + i (source, destination,
+// `segs` neighbouring segments of one receiver, 5 to 7 KB of payload: lane i finds block s0 + i (source, destination,
 // bytes), a wave scan lays the blocks out as rows of aligned 16-byte pieces of the destination (tiled_pieces), and the
 // wave moves 8 pieces per lane at a time.  What the destination-tiled hop needs a resolve pass, a layout pass and unit
 // lists for -- 40 bytes of hop arrays per block written and read, and four kernels per phase -- lies in one wave's
@@ -1825,15 +1825,16 @@ __device__ __forceinline__ int tiled_pieces(unsigned long long a, int n, bool ha
 // are as fast as aligned ones (16-byte loads 1 byte off: 5.6 TB/s in a copy, like aligned ones).
 //   Measured against the destination-tiled hop and the engine's with their metadata kernels: per call, 16 GiB of 1 KiB
 // blocks 6.75 -> 6.35 ms linear and 22.9 -> 22.1 ms at r = 8; 512-byte blocks on average, byte-granular, P = 1000, per
-// start 333 -> 214 us; uniform [0, 512] B, P = 2048, r = 46 1.24 -> 0.99 ms; 512-byte blocks, P = 2048, r = 16
-// 2.57 -> 2.05 ms; 256-byte blocks, P = 2048 as 64 x 32, r = 16 1.73 -> 1.25 ms.  8 pieces per lane against 4: -4 to -9 %.  7000 bytes and not 8192: a wave whose pieces do not fit
-// into one step takes a second, nearly empty one.  Streaming stores against cached ones: -8 to -15 %; streaming loads
+// start 333 -> 210 us; uniform [0, 512] B, P = 2048, r = 46 1.24 -> 0.99 ms; 512-byte blocks, P = 2048, r = 16
+// 2.57 -> 2.05 ms; 256-byte blocks, P = 2048 as 64 x 32, r = 16 1.73 -> 1.25 ms.  8 pieces per lane against 4: -4 to -9 %.
+// Streaming stores against cached ones: -8 to -15 %; streaming loads
 // only where blocks are whole lines (512 bytes: -5 %; 1 KiB blocks at 4-byte alignment: up to +6 %).  Four receivers x
 // the same segments per workgroup instead of one receiver: 1 KiB blocks +3 %; rows of workgroups cut so that one XCD sees
 // the same senders for all receivers: +1 to +13 %.
 // ------------------------------------------------------------------------------------------
 constexpr int kRowsPieces = 8;              // pieces per lane and step
-constexpr int kRowsBytes = 7000;            // payload of one wave, by the mean block
+constexpr int kRowsBytes = 5200;            // payload of one wave, by the mean block (rows_segs)
+constexpr int kRowsLongBytes = 7000;        // of longer blocks
 constexpr int kRowsMaxBytes = 1 << 16;      // a wave moves whole blocks: longer ones would leave the others waiting
 
 // Where block (segment s, receiver p) is read from and stored to, and its bytes: from the hop arrays, or from the
