@@ -1262,13 +1262,15 @@ void launch_rows_as(const DirectArgs& a, dim3 grid, bool exact, hipStream_t s) {
 }
 
 // The payload of a phase of blocks of up to kRowsMaxBytes; arguments as launch_direct's.
-int launch_rows(const Prepared& pr, size_t i, const HopDev& hop, uint2* part, hipStream_t s) {
+int launch_rows(const Prepared& pr, size_t i, const HopDev& hop, uint2* part, bool own, hipStream_t s) {
     const PhaseHost& ph = pr.dp->host.phases[i];
     DirectArgs a{};
     a.r = resolve_args(pr, i, nullptr, hop);
     a.T = pr.T; a.seg_lo = 0; a.seg_hi = ph.nseg; a.part = part;
     a.segs = rows_segs(pr); a.user_limit = pr.user_limit;
-    const dim3 grid((unsigned)((ph.nseg + 4 * a.segs - 1) / (4 * a.segs)), (unsigned)pr.P);
+    const int cols = (ph.nseg + 4 * a.segs - 1) / (4 * a.segs);
+    a.own = own ? (pr.P + cols - 1) / cols : 0;
+    const dim3 grid((unsigned)cols, (unsigned)(pr.P + a.own));
     if (pr.gran == 128) launch_rows_as<true>(a, grid, pr.exact_kernels, s);
     else launch_rows_as<false>(a, grid, pr.exact_kernels, s);
     HIPCHK(hipGetLastError());
@@ -1277,7 +1279,7 @@ int launch_rows(const Prepared& pr, size_t i, const HopDev& hop, uint2* part, hi
 
 // The payload of a phase of short blocks: from the hop arrays (part null), or found in the same kernel, with partial
 // sums into `part`.
-int launch_direct(const Prepared& pr, size_t i, const HopDev& hop, int seg_lo, int seg_hi, uint2* part, hipStream_t s) {
+int launch_direct(const Prepared& pr, size_t i, const HopDev& hop, int seg_lo, int seg_hi, uint2* part, bool own, hipStream_t s) {
     if (seg_hi <= seg_lo) return TUNA_OK;
     const PhaseHost& ph = pr.dp->host.phases[i];
     DirectArgs a{};
@@ -1285,7 +1287,8 @@ int launch_direct(const Prepared& pr, size_t i, const HopDev& hop, int seg_lo, i
     a.T = pr.T; a.seg_lo = seg_lo; a.seg_hi = seg_hi; a.part = part;
     const unsigned cols = direct_columns(pr, ph, seg_hi - seg_lo, &a.iters);
     const int lpb = direct_lpb(pr), ranks = direct_ranks(direct_shape(lpb, direct_tall(ph)));
-    const dim3 grid(cols, (unsigned)((pr.P + ranks - 1) / ranks));
+    a.own = own ? (int)(((pr.P + kOwnRanks - 1) / kOwnRanks + cols - 1) / cols) : 0;
+    const dim3 grid(cols, (unsigned)((pr.P + ranks - 1) / ranks + a.own));
     if (direct_tall(ph)) launch_direct_shape<true>(lpb, pr.gran, a, grid, pr.exact_kernels, s);
     else launch_direct_shape<false>(lpb, pr.gran, a, grid, pr.exact_kernels, s);
     HIPCHK(hipGetLastError());
@@ -1420,6 +1423,17 @@ int launch_self_copy(const Prepared& pr, hipStream_t s) {
     return TUNA_OK;
 }
 
+// Whether the launch of the first phase takes the ranks' own blocks along, one launch less: all rounds at once, by
+// k_hop_direct or k_hop_rows (a call's k_hop_senders does not).  Us with a launch of their own / without: per start up to 200 bytes, P = 50
+// 9.8 / 7.2, up to 16, P = 400 9.9 / 7.1, up to 1 KiB, P = 100, r = 10 14.0 / 12.3, P = 1000 212 / 208; per call up to 1 KiB, P = 300 60.5 /
+// 56.1, up to 6 KB, P = 128 58.4 / 54.7.  Rows of workgroups in front: one more column shifts which workgroups share an XCD (16
+// GiB linear 6.4 -> 6.6 ms).
+bool own_in_first(const Prepared& pr) {
+    if (pr.self_engine || !pr.fused || pr.staggered || pr.block_count != 0 || pr.dp->host.phases.empty()) return false;
+    const int kernel = phase_kernel(pr, 0);
+    return kernel == TUNA_HOP_ROWS || (kernel == TUNA_HOP_DIRECT && (pr.for_plan || !sender_phase(pr, pr.dp->host.phases[0])));
+}
+
 // The payload kernels of digit phase i: pack, exchange, unpack -- or the one-kernel hop.
 // unit_cap: number of wave units to launch for (an upper bound is fine).
 int launch_phase_data(const Prepared& pr, size_t i, const LayoutDev& Ls, const LayoutDev& Lr, const HopDev& hop,
@@ -1475,13 +1489,13 @@ int launch_phase_data(const Prepared& pr, size_t i, const LayoutDev& Ls, const L
             continue;
         }
         if (kernel == TUNA_HOP_DIRECT) {
-            rc = launch_direct(pr, i, hop, a.seg_lo, a.seg_hi, nullptr, s);
+            rc = launch_direct(pr, i, hop, a.seg_lo, a.seg_hi, nullptr, i == 0 && own_in_first(pr), s);
             if (rc != TUNA_OK) return rc;
             mark(pr.ctx, s, kCatPack, (int)i);
             continue;
         }
         if (kernel == TUNA_HOP_ROWS) {
-            rc = launch_rows(pr, i, hop, nullptr, s);
+            rc = launch_rows(pr, i, hop, nullptr, i == 0 && own_in_first(pr), s);
             if (rc != TUNA_OK) return rc;
             mark(pr.ctx, s, kCatPack, (int)i);
             continue;
@@ -1610,12 +1624,12 @@ int launch_t_places(Prepared& pr, hipStream_t s, bool* own = nullptr) {
 }
 
 // The payload of such a phase, found and moved in one kernel; partial sums into `part` (direct_rows rows of P entries).
-int launch_direct_payload(const Prepared& pr, size_t i, uint2* part, hipStream_t s) {
+int launch_direct_payload(const Prepared& pr, size_t i, uint2* part, bool own, hipStream_t s) {
     const PhaseHost& ph = pr.dp->host.phases[i];
-    const int rc = row_blocks(pr)         ? launch_rows(pr, i, HopDev{}, part, s)
+    const int rc = row_blocks(pr)         ? launch_rows(pr, i, HopDev{}, part, own, s)
                    : pair_phase(pr)       ? launch_pairs(pr, part, s)
                    : sender_phase(pr, ph) ? launch_senders(pr, i, part, s)
-                                          : launch_direct(pr, i, HopDev{}, 0, ph.nseg, part, s);
+                                          : launch_direct(pr, i, HopDev{}, 0, ph.nseg, part, own, s);
     if (rc == TUNA_OK) mark(pr.ctx, s, kCatPack, (int)i);
     return rc;
 }
@@ -1667,7 +1681,8 @@ int run_one_pass(Prepared& pr, void* mbase, size_t mbytes, void* dbase, hipStrea
         if (rc != TUNA_OK) return rc;
         mark(pr.ctx, s, kCatMeta, 0);
     }
-    if (!own_moved) {
+    const bool own_first = direct && !own_moved && own_in_first(pr);
+    if (!own_moved && !own_first) {
         rc = launch_self_metadata(pr, s);
         if (rc != TUNA_OK) return rc;
         rc = launch_self_copy(pr, s);
@@ -1708,7 +1723,7 @@ int run_one_pass(Prepared& pr, void* mbase, size_t mbytes, void* dbase, hipStrea
             parts.part[i] = reinterpret_cast<uint2*>(pr.hop.src) + used * P;
             parts.rows[i] = (int)rows;
             used += rows;
-            rc = launch_direct_payload(pr, i, const_cast<uint2*>(parts.part[i]), s);
+            rc = launch_direct_payload(pr, i, const_cast<uint2*>(parts.part[i]), own_first && i == 0, s);
             if (rc != TUNA_OK) return rc;
         }
         add_up();
@@ -2024,7 +2039,7 @@ void plan_carve_data(Plan* plan, void* data, size_t stage_bytes, size_t dbytes) 
 // The payload kernels of every phase, with exact grids.
 int plan_launch_data(const Plan* plan, hipStream_t s) {
     const Prepared& pr = plan->pr;
-    int rc = long_blocks(pr) ? TUNA_OK : launch_self_copy(pr, s);
+    int rc = long_blocks(pr) || own_in_first(pr) ? TUNA_OK : launch_self_copy(pr, s);
     if (rc != TUNA_OK) return rc;
     mark(pr.ctx, s, kCatSelf, -1);
     const size_t nph = pr.dp->host.phases.size();

@@ -1271,6 +1271,7 @@ struct DirectArgs {
     unsigned long long user_limit;      // address one past the last byte of S that holds a block
     uint2* part;                        // [grid.x][P]: payload bytes and chunks of the tile column, per receiver (not when RESOLVED)
     int nz;                             // rounds of the phase (k_hop_senders)
+    int own;                            // so many rows of workgroups in front move the ranks' own blocks (k_hop_direct, k_hop_rows)
 };
 
 typedef v4u v4u_any __attribute__((aligned(1)));
@@ -1537,6 +1538,24 @@ __device__ __forceinline__ void move_short(const unsigned long long (&src)[SETS]
     }
 }
 
+// The own blocks, of up to kDirectMaxBytes, of the kOwnRanks ranks from p0 on, 16 lanes each.
+constexpr int kOwnRanks = 16;
+__device__ __forceinline__ void own_short(const ResolveArgs& r, int p0) {
+    const int p = p0 + threadIdx.x / 16, lane = threadIdx.x & 15;
+    if (p >= r.P) return;
+    const size_t d = (size_t)p * r.P + p;
+    const int n = r.sendcounts[d];
+    const unsigned long long src = (unsigned long long)r.S + (unsigned long long)r.sdispls[d], dst = (unsigned long long)r.R + (unsigned long long)r.rdispls[d];
+    if (n < 16) {
+        if (lane < n) store_global<unsigned char>(dst + lane, load_global<unsigned char>(src + lane));
+        return;
+    }
+    for (int c = lane * 16; c < n; c += 256) {
+        const unsigned int o = (unsigned int)min(c, n - 16);
+        store_global<v4u_any>(dst + o, load_global<v4u_any>(src + o));
+    }
+}
+
 template <int LPB, bool TALL, int STREAM, bool DENSE, bool RESOLVED>
 __global__ void __launch_bounds__(256) k_hop_direct(const DirectArgs a) {
     constexpr DirectShape SH = direct_shape(LPB, TALL);
@@ -1545,10 +1564,11 @@ __global__ void __launch_bounds__(256) k_hop_direct(const DirectArgs a) {
     constexpr int WS = 4 / SH.waves_r;                   // waves side by side along the segments
     __shared__ ShortLds<LPB> lds;
     const ResolveArgs& r = a.r;
+    if ((int)blockIdx.y < a.own) { own_short(r, (int)(blockIdx.y * gridDim.x + blockIdx.x) * kOwnRanks); return; }
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int P = r.P, Q = r.Q, N = r.N;
-    const int p0 = blockIdx.y * direct_ranks(SH) + (wv / WS) * SH.wave_ranks * SETS + lane / SEGS;
+    const int p0 = (blockIdx.y - a.own) * direct_ranks(SH) + (wv / WS) * SH.wave_ranks * SETS + lane / SEGS;
     const int sub = lane & (SEGS - 1);
     const unsigned long long tb = (unsigned long long)a.T;
     unsigned int sum_b[SETS], sum_c[SETS];
@@ -1903,7 +1923,12 @@ __global__ void __launch_bounds__(256) k_hop_rows(const DirectArgs a) {
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int P = a.r.P;
-    const int p = blockIdx.y;
+    if ((int)blockIdx.y < a.own) {
+        const int own = blockIdx.y * gridDim.x + blockIdx.x;
+        if (own < P) own_block(a.r.S, a.r.sendcounts, a.r.sdispls, a.r.R, a.r.rdispls, P, own);
+        return;
+    }
+    const int p = blockIdx.y - a.own;
     const int grp = blockIdx.x * 4 + wv;
     const int s0 = a.seg_lo + grp * a.segs;
     if (s0 >= a.seg_hi) return;                          // no barrier below: a wave may leave alone

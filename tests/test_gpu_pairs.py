@@ -77,3 +77,40 @@ def test_several_steps(tuna, P, longest, quantum):
     rng = np.random.default_rng(P)
     counts = rng.integers(0, longest // quantum + 1, (P, P), dtype=np.int32) * quantum
     _run(tuna, counts, 0, {})
+
+
+@pytest.mark.parametrize("size", [3, 15, 16, 200, 256, 257, 3001, 65536])
+@pytest.mark.parametrize("P,radix", [(2, 2), (19, 19), (40, 3), (170, 13), (300, 300)])
+def test_own_blocks_only(tuna, P, radix, size):
+    """Nothing but the blocks that ranks keep for themselves, which the launch of the first phase moves: calls and plans, T in
+    either layout."""
+    dev = "cuda:0"
+    counts = np.zeros((P, P), dtype=np.int32)
+    np.fill_diagonal(counts, size)
+    counts[P // 2, P // 2] = 0
+    lay = wl.make_layout(counts, gap=1)
+    host = wl.payload_position_hash(size, lay.send_bytes)
+    want = np.full(lay.recv_bytes, CANARY, dtype=np.uint8)
+    assert oracle.alltoallv(host, lay.sendcounts, lay.sdispls, want, lay.recvcounts, lay.rdispls) == 0
+    send = torch.from_numpy(host).to(dev)
+    recv = torch.full((lay.recv_bytes,), CANARY, dtype=torch.uint8, device=dev)
+    args = [send] + [torch.from_numpy(a).to(dev) for a in (lay.sendcounts, lay.sdispls)] + [recv] + \
+           [torch.from_numpy(a).to(dev) for a in (lay.recvcounts, lay.rdispls)]
+    o = tuna.tuna_opts_init()
+    o.mode = tuna.TUNA_MODE_FUSED
+    for o.t_layout in (tuna.TUNA_T_EXACT, tuna.TUNA_T_SLOTS):
+        print("own blocks", P, radix, size, o.t_layout, flush=True)
+        assert tuna.tuna_alltoallv_ex(None, *args, P, 0, radix, radix, o) == 0
+        torch.cuda.synchronize()
+        assert np.array_equal(recv.cpu().numpy(), want)
+        recv.fill_(CANARY)
+        rc, plan = tuna.tuna_alltoallv_init_ex(None, *args, P, 0, radix, radix, o)
+        assert rc == 0, tuna.tuna_strerror(rc)
+        try:
+            assert tuna.tuna_start(plan) == 0
+            torch.cuda.synchronize()
+            assert np.array_equal(recv.cpu().numpy(), want), "plan"
+        finally:
+            tuna.tuna_plan_free(plan)
+        recv.fill_(CANARY)
+    tuna.tuna_release()
