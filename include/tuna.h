@@ -88,7 +88,7 @@ typedef struct tuna_phase_stats {
 #define TUNA_HOP_TILED 2    /* the destination-tiled hop */
 #define TUNA_HOP_DIRECT 4   /* blocks of up to 256 bytes, found by the kernel that moves them */
 #define TUNA_HOP_ROWS 8     /* blocks of up to 64 KiB, found by the kernel that moves them */
-#define TUNA_HOP_LONG 16    /* blocks longer than that, from a list of 4 KiB units */
+#define TUNA_HOP_LONG 16    /* long blocks (16 KiB and more on average), from a list of 4 KiB units */
 
 typedef struct tuna_stats {
     int32_t P, Q, N;                 /* ranks, ranks per node, nodes (flat: Q = P, N = 1) */
