@@ -87,6 +87,7 @@ struct StatusBufs {
     unsigned long long* h_part = nullptr;      // the partial results in pinned memory, where few workgroups write them for
     unsigned long long* h_part_dev = nullptr;  // the host to fold (nullptr: none, k_validate_finish folds them); behind them
                                                // kMailWords words: the last ticket handed out, and the last one received
+    long long* h_cbase = nullptr;              // kMaxClasses words that upload_cbase sends from (pinned, behind those)
     bool sums_clear = false;                   // the class sums have been cleared by an earlier kernel of this call
     int num_cus = 256;
 };
@@ -191,7 +192,8 @@ int ensure_ctx(Ctx& c) {
     HIPCHK(hipMalloc((void**)&c.sb.d_vpart, align_up(vpart_words(c.sb.num_cus) * 8)));
     HIPCHK(hipMemset(c.sb.d_status, 0, sizeof(Status)));
     HIPCHK(hipStreamSynchronize(nullptr));
-    HIPCHK(hipHostMalloc((void**)&c.sb.h_part, (size_t)(kMailIssued + kMailWords) * 8, hipHostMallocDefault));
+    HIPCHK(hipHostMalloc((void**)&c.sb.h_part, (size_t)(kMailIssued + kMailWords + kMaxClasses) * 8, hipHostMallocDefault));
+    c.sb.h_cbase = reinterpret_cast<long long*>(c.sb.h_part + kMailIssued + kMailWords);
     std::memset(c.sb.h_part, 0, (size_t)(kMailIssued + kMailWords) * 8);
     if (hipHostGetDevicePointer((void**)&c.sb.h_part_dev, c.sb.h_part, 0) != hipSuccess) {
         (void)hipGetLastError();
@@ -657,13 +659,18 @@ void carve_exact_t(Carver& cv, const PlanHost& pl, bool keep_all_phases, Prepare
     pr.x.cbase = pr.d_cbase;
 }
 
-// The classes' places in T go to the device through the pinned mirror of the status block (its class
-// sums have been read by now); the copy is ordered on the stream before the kernels that read it.
+// The classes' places in T go to the device; the copy is ordered on the stream before the kernels that read it.  An immediate
+// call sends them from pinned words that nothing else writes and returns with the copy pending: the next call has been
+// validated behind it, on the same stream or on one that waits for this call, before it writes there.  A plan, which may
+// be made while such a call is in flight, sends its own array, and waits for its stream before it returns.
 int upload_cbase(const Prepared& pr, hipStream_t s) {
     const size_t ncls = pr.cbase.size();
     if (!pr.exact_t || !ncls) return TUNA_OK;
-    long long* stage = reinterpret_cast<long long*>(pr.sb.h_status->cls_chunks);
-    for (size_t k = 0; k < ncls; ++k) stage[k] = pr.cbase[k];
+    const long long* stage = pr.cbase.data();
+    if (!pr.for_plan) {
+        std::copy(pr.cbase.begin(), pr.cbase.end(), pr.sb.h_cbase);
+        stage = pr.sb.h_cbase;
+    }
     HIPCHK(hipMemcpyAsync(pr.d_cbase, stage, ncls * 8, hipMemcpyHostToDevice, s));
     return TUNA_OK;
 }
@@ -2246,6 +2253,7 @@ struct StaticState {
     unsigned char* ptr[kMaxDevices] = {};   // device address of `scratch` on each GPU (every GPU has its own copy)
     int num_cus[kMaxDevices] = {};
     Status h_status;                          // host mirror of the status block (pageable: no pinned allocation)
+    long long h_cbase[kMaxClasses];
 };
 StaticState g_static;
 
@@ -2279,6 +2287,7 @@ int run_static(const void* sendbuf, const int32_t* sendcounts, const int64_t* sd
     pr.sb.d_status = cv.take<Status>(1);
     pr.sb.d_vpart = cv.take<unsigned long long>(vpart_words(pr.sb.num_cus));
     pr.sb.h_status = &g_static.h_status;
+    pr.sb.h_cbase = g_static.h_cbase;
     pr.opt = sh.defaults;
     pr.opt.profile = 0;                       // no events are created here
     pr.fused = mode_is_fused(pr.opt);

@@ -1,0 +1,115 @@
+"""The library's host code on the runtime of fake_hip.cpp.  `python fake_hip.py <runtime> <case> [arguments]` runs one
+case of CASES in a process of its own (the real runtime must not be loaded) and prints its result as JSON; `run` does so."""
+import ctypes
+import json
+import os
+import re
+import subprocess
+import sys
+
+import numpy as np
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+
+def build(folder):
+    """The runtime, under the name that the library asks for."""
+    out, versions = os.path.join(folder, "libamdhip64.so.7"), os.path.join(folder, "versions")
+    with open(versions, "w") as f:
+        f.write("hip_4.2 { hip*; __hip*; fake_*; };\nhip_6.0 { hipGetDevicePropertiesR0600; };\n")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    "-Wl,-soname,libamdhip64.so.7", "-Wl,--version-script=" + versions, "-o", out, os.path.join(HERE, "fake_hip.cpp")],
+                   check=True)
+    return out
+
+
+def run(runtime, case, *args):
+    p = subprocess.run([sys.executable, os.path.abspath(__file__), runtime, case, json.dumps(args)], stdout=subprocess.PIPE,
+                       stderr=subprocess.PIPE, text=True, timeout=300)
+    assert p.returncode == 0, p.stderr[-2000:]
+    return json.loads(p.stdout.splitlines()[-1])
+
+
+class Lib:
+    """The library on that runtime; problems whose payload is never read."""
+
+    def __init__(self, runtime):
+        self.fake = ctypes.CDLL(runtime, mode=ctypes.RTLD_GLOBAL)
+        for name, res, args in (("fake_notes", ctypes.c_int, []), ("fake_name", ctypes.c_char_p, [ctypes.c_int]),
+                                ("fake_stream", ctypes.c_long, [ctypes.c_int]), ("fake_ptr", ctypes.c_size_t, [ctypes.c_int]),
+                                ("fake_before", ctypes.c_long, [ctypes.c_int, ctypes.c_long]),
+                                ("fake_length", ctypes.c_long, [ctypes.c_long]), ("fake_violations", ctypes.c_int, []),
+                                ("fake_allocated", ctypes.c_ulonglong, [])):
+            f = getattr(self.fake, name)
+            f.restype, f.argtypes = res, args
+        sys.path.insert(0, ROOT)
+        import paper_2411_02581_amd.binding as b
+        import workloads
+        self.b, self.wl, self.lib = b, workloads, b.load()
+
+    def problem(self, counts, **layout):
+        lay = self.wl.make_layout(np.ascontiguousarray(counts, dtype=np.int32), **layout)
+        return lay, [0x7000000000] + [a.ctypes.data for a in (lay.sendcounts, lay.sdispls)] + [0x7800000000] + \
+            [a.ctypes.data for a in (lay.recvcounts, lay.rdispls)]
+
+    def options(self, **fields):
+        o = self.b.tuna_opts_t()
+        assert self.lib.tuna_opts_init(ctypes.byref(o)) == 0
+        o.mode = self.b.TUNA_MODE_FUSED                        # not the single launch
+        for k, v in fields.items():
+            setattr(o, k, v)
+        return o
+
+    def call(self, prob, radix, stream, rpn=0, rg=None, ctx=None, **fields):
+        return self.lib.tuna_alltoallv_ex(ctx, *prob[1], prob[0].P, rpn, radix, rg or radix, ctypes.byref(self.options(**fields)), stream)
+
+    def plan(self, prob, radix, stream, rpn=0, rg=None, ctx=None, **fields):
+        plan = ctypes.c_void_p(None)
+        rc = self.lib.tuna_alltoallv_init_ex(ctx, *prob[1], prob[0].P, rpn, radix, rg or radix, ctypes.byref(self.options(**fields)), stream,
+                                             ctypes.byref(plan))
+        assert rc == 0, rc
+        return plan
+
+    def kernels(self, first=0):
+        """[name, stream] of the kernels launched from note `first` on."""
+        out = []
+        for i in range(first, self.fake.fake_notes()):
+            m = re.search(r"\d+(k_[a-z0-9_]+?)(?:I[LN]|E|$)", self.fake.fake_name(i).decode())
+            out.append([m.group(1) if m else "?", self.fake.fake_stream(i)])
+        return out
+
+
+def _engine_counts(P):
+    """Short blocks and a few that are too long for the kernels that find their blocks themselves: the copy engine's hop."""
+    c = np.random.default_rng(P).integers(0, 300, (P, P)).astype(np.int32)
+    c[1, P - 2] = c[P - 1, 3] = 70001
+    return c
+
+
+S1, S2, S3 = 0x1000, 0x2000, 0x3000
+
+
+def case_upload(t, P, radix, then):
+    """A call that sends the places of T's classes to the device, and behind it, before the copy is done, another operation
+    on the context."""
+    prob = t.problem(_engine_counts(P), gap=1)
+    assert t.call(prob, radix, S1, t_layout=t.b.TUNA_T_EXACT) == 0
+    if then == "call":
+        other = t.problem(_engine_counts(P) * 2, gap=1)
+        assert t.call(other, radix, S1, t_layout=t.b.TUNA_T_EXACT) == 0
+    elif then == "call elsewhere":
+        assert t.call(prob, radix, S2, t_layout=t.b.TUNA_T_EXACT) == 0
+    elif then == "query":
+        n = ctypes.c_size_t(0)
+        assert t.lib.tuna_workspace_bytes(prob[1][1], P, 0, radix, radix, ctypes.byref(n)) == 0
+    elif then == "plan":
+        t.plan(t.problem(_engine_counts(P) * 2, gap=1), radix, S2, t_layout=t.b.TUNA_T_EXACT)
+    return {"violations": t.fake.fake_violations()}
+
+
+CASES = {k[5:]: f for k, f in list(globals().items()) if k.startswith("case_")}
+
+if __name__ == "__main__":
+    lib = Lib(sys.argv[1])
+    print(json.dumps(CASES[sys.argv[2]](lib, *json.loads(sys.argv[3]))))

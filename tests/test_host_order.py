@@ -1,0 +1,23 @@
+"""What the host code enqueues, on a runtime that runs it as late as it may (fake_hip.cpp)."""
+import os
+import shutil
+
+import pytest
+
+import fake_hip
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None or not os.path.exists("/opt/rocm/include/hip/hip_runtime_api.h"),
+                                reason="needs g++ and the HIP headers")
+
+
+@pytest.fixture(scope="module")
+def runtime(tmp_path_factory):
+    return fake_hip.build(str(tmp_path_factory.mktemp("fake_hip")))
+
+
+@pytest.mark.parametrize("then", ["call", "call elsewhere", "query", "plan"])
+@pytest.mark.parametrize("P,radix", [(16, 2), (100, 4), (300, 2)])
+def test_places_of_t_are_not_overwritten_on_their_way(runtime, P, radix, then):
+    """The places of T's classes go to the device from pinned memory after a call has returned: nothing may write there
+    until the copy is done.  (300 ranks: more classes than the host adds up itself.)"""
+    assert fake_hip.run(runtime, "upload", P, radix, then) == {"violations": 0}
