@@ -138,7 +138,7 @@ struct Ctx {
     hipStream_t last_stream = nullptr;  // stream of the last immediate call (its end is ev_end when end_recorded)
     unsigned char* tiny_t = nullptr;    // T of the one-kernel call for tiny problems (kTinyTBytes, allocated at its first use)
     const void* tiny_declined = nullptr; // sendcounts of the last problem that kernel declined: it is not asked again for it
-    const void* stats_plan = nullptr;   // the statistics on file belong to this persistent plan (payload bytes known)
+    bool device_totals = false;         // the per-phase totals of the statistics on file are still in *sb.d_status (an immediate call's)
     // pipelined calls (run_pipelined): the stream the metadata kernels run on, the event that lets it start, and one
     // event per phase that lets the phase's payload kernel start; made at the first such call
     hipStream_t meta_stream = nullptr;
@@ -1816,7 +1816,7 @@ int run_tiny(Ctx& c, const void* sendbuf, const int32_t* sendcounts, const int64
     const unsigned int abits = hs.align_bits | (unsigned int)((uintptr_t)sendbuf & 127u) | (unsigned int)((uintptr_t)recvbuf & 127u);
     pr.gran = (abits & 127u) == 0 ? 128 : ((abits & 15u) == 0 ? 16 : ((abits & 3u) == 0 ? 4 : 1));
     c.marks.clear();
-    c.stats_plan = nullptr;
+    c.device_totals = false;
     fill_stats_header(pr, hs, c.stats);
     c.stats.temp_bytes = (int64_t)P * pl.slots * (((int64_t)hs.max_count + 15) / 16 * 16);
     c.stats.workspace_bytes = (int64_t)kTinyTBytes;
@@ -1859,7 +1859,7 @@ int run_once(Ctx& c, const Options& opt, const void* sendbuf, const int32_t* sen
     c.marks.clear();
     c.end_recorded = false;
     c.have_stats = false;
-    c.stats_plan = nullptr;
+    c.device_totals = true;
     c.profile = opt.profile != 0;
     if (c.ready) mark(&c, s, -1, -1);
     Prepared pr;
@@ -1986,11 +1986,13 @@ int plan_build_metadata(Plan* plan, void* meta, size_t mbytes, hipStream_t s, bo
     if (rc != TUNA_OK) return rc;
     const dim3 grot((unsigned)((P + 255) / 256), (unsigned)((P + kExchangeRanks - 1) / kExchangeRanks));
     const bool longs = long_blocks(pr);
-    if (longs) {
-        // the totals and unit counts that k_long_units adds to
+    if (pr.for_plan) {
+        // the totals and unit counts in the plan's own status block: k_long_units adds to them
         constexpr int kCounters = (int)((offsetof(Status, phase_units) + sizeof(Status::phase_units) - offsetof(Status, phase_bytes)) / 8);
         hipLaunchKernelGGL(k_zero64, dim3((kCounters + 255) / 256), dim3(256), 0, s, pr.sb.d_status->phase_bytes, kCounters);
         HIPCHK(hipGetLastError());
+    }
+    if (longs) {
         rc = launch_t_places(pr, s);
     } else {
         hipLaunchKernelGGL(k_rotate_init, grot, dim3(256), 0, s, pr.sendcounts, cur, P, pr.Q, pr.N, 0);
@@ -2073,12 +2075,16 @@ int plan_create(Ctx& c, const Options& opt, const void* sendbuf, const int32_t* 
     fill_stats_header(pr, hs, plan->stats);
     if (plan->empty) { ++sh.live_plans; *out = plan; return TUNA_OK; }
     plan->stats.hop_kernels = hop_kernels_of(pr);
-    const size_t mbytes = plan_meta_bytes(pr);
-    hipError_t e = hipMalloc(&plan->mem_meta, mbytes ? mbytes : kAlign);
+    // The metadata kernels write their totals and unit counts into a status block of the plan's own: in the context's a call that
+    // is in flight on another stream may still be adding up its own, or be counting the units of its long blocks.
+    const size_t mbytes = plan_meta_bytes(pr), sbytes = align_up(sizeof(Status));
+    hipError_t e = hipMalloc(&plan->mem_meta, mbytes + sbytes);
     if (e != hipSuccess) { (void)hipGetLastError(); sh.last_hip_error = (int)e; delete plan; return TUNA_ERR_NOMEM; }
     auto fail = [&](int code) { (void)hipFree(plan->mem_meta); if (plan->mem_data) (void)hipFree(plan->mem_data); delete plan; return code; };
     size_t stage_bytes = 0, dbytes = 0;
+    pr.sb.d_status = reinterpret_cast<Status*>((char*)plan->mem_meta + mbytes);
     rc = plan_build_metadata(plan, plan->mem_meta, mbytes, s, /*with_marks=*/false, &stage_bytes, &dbytes);
+    plan->stats.workspace_bytes += (int64_t)sbytes;
     if (rc != TUNA_OK) return fail(rc == TUNA_ERR_WORKSPACE_TOO_SMALL ? TUNA_ERR_NOMEM : rc);
     if (dbytes) {
         e = hipMalloc(&plan->mem_data, dbytes);
@@ -2097,7 +2103,7 @@ int plan_start(Plan* plan, hipStream_t s) {
     c.marks.clear();
     c.have_stats = false;
     c.stats = plan->stats;
-    c.stats_plan = plan;
+    c.device_totals = false;
     c.profile = plan->pr.opt.profile != 0 || sh.defaults.profile != 0;
     if (plan->empty) { c.end_recorded = false; c.have_stats = true; return TUNA_OK; }
     mark(&c, s, -1, -1);
@@ -2338,7 +2344,7 @@ int run_static(const void* sendbuf, const int32_t* sendcounts, const int64_t* sd
     // the statistics on file (header only: nothing here is timed) are the default context's
     g.marks.clear();
     g.end_recorded = false;
-    g.stats_plan = nullptr;
+    g.device_totals = false;
     fill_stats_header(pr, hs, g.stats);
     g.have_stats = true;
     if (empty) return TUNA_OK;
@@ -2736,7 +2742,6 @@ int tuna_start(tuna_plan_t plan, void* stream) {
 int tuna_plan_free(tuna_plan_t plan) {
     if (!plan) return TUNA_OK;
     Plan* p = reinterpret_cast<Plan*>(plan);
-    if (p->ctx && p->ctx->stats_plan == p) p->ctx->stats_plan = nullptr;
     // the plan goes away whatever the wait for the device says: its memory is released and the count of
     // live plans drops, then the error (if any) is reported
     const hipError_t e = hipDeviceSynchronize();
@@ -2874,7 +2879,7 @@ int tuna_ctx_get_stats(tuna_ctx_t ctx, tuna_stats_t* out) {
     tuna_stats_t& st = g.stats;
     if (g.end_recorded) {
         HIPCHK(hipEventSynchronize(g.ev_end));
-        if (!g.stats_plan) {   // a persistent plan knows its per-phase bytes since it was made
+        if (g.device_totals) {   // a persistent plan knows its per-phase bytes since it was made
             HIPCHK(hipMemcpy(g.sb.h_status, g.sb.d_status, sizeof(Status), hipMemcpyDeviceToHost));
             for (int i = 0; i < st.n_phases; ++i) {
                 st.phase[i].payload_bytes = (int64_t)g.sb.h_status->phase_bytes[i];

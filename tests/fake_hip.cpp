@@ -30,7 +30,7 @@ struct Stream {
     Clock now;
 };
 struct Event { hipStream_t s = nullptr; size_t upto = 0; Clock at; };
-struct Note { std::string name; hipStream_t s; Clock before; const void* ptr; };
+struct Note { std::string name; hipStream_t s; Clock before; const void* ptr; };     // ptr: the status block, or a word of one
 
 struct Launch { dim3 grid, block; size_t lds; hipStream_t s; } launch;
 
@@ -158,6 +158,8 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** a, size_t, hip
         const int m = arg<int>(a, 1);
         ptr = p;
         op = [=] { std::memset(p, 0, (size_t)m * 8); };
+    } else if (is("k_layout_base")) {
+        ptr = arg<const void*>(a, 4);
     }
     enqueue(s, op);
     notes.push_back(Note{n, s, streams[s].now, ptr});

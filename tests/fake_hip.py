@@ -108,6 +108,19 @@ def case_upload(t, P, radix, then):
     return {"violations": t.fake.fake_violations()}
 
 
+def case_plan_status(t, counts, P, radix, plan_counts, plan_P, plan_radix):
+    """A plan is made on one stream while a call of the same context is in flight on another: do its kernels write into the
+    status block that the call uses?"""
+    sizes = {"long": lambda P: np.full((P, P), 40000), "engine": _engine_counts}
+    assert t.call(t.problem(sizes[counts](P)), radix, S1) == 0
+    status = [t.fake.fake_ptr(i) for i, k in enumerate(t.kernels()) if k[0] == "k_validate"][0]
+    first = t.fake.fake_notes()
+    t.plan(t.problem(sizes[plan_counts](plan_P)), plan_radix, S2)
+    words = [(k[0], t.fake.fake_ptr(first + i)) for i, k in enumerate(t.kernels(first)) if k[0] in ("k_zero64", "k_layout_base")]
+    # (sums of classes, which the plan's validation leaves as it finds them, are the first 16 KiB and 64 bytes)
+    return {"seen": len(words), "shared": [n for n, p in words if status <= p < status + 32768]}
+
+
 CASES = {k[5:]: f for k, f in list(globals().items()) if k.startswith("case_")}
 
 if __name__ == "__main__":

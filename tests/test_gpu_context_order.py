@@ -1,0 +1,112 @@
+"""Operations of one context that follow each other without a host synchronisation, on one stream and on several: each
+result is that of the same call made alone, with three-stage phases."""
+import numpy as np
+import pytest
+
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+CANARY = 0x5A
+
+
+@pytest.fixture(scope="module")
+def tuna():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2411_02581_amd as t
+    t.load()
+    return t
+
+
+class Prob:
+    def __init__(self, tuna, counts, seed, gap=0):
+        dev = "cuda:0"
+        self.tuna, self.lay = tuna, wl.make_layout(np.ascontiguousarray(counts, dtype=np.int32), gap=gap)
+        lay, gen = self.lay, torch.Generator(device=dev)
+        gen.manual_seed(seed)
+        self.send = torch.empty(lay.send_bytes // 8 + 1, dtype=torch.int64, device=dev).random_(generator=gen)
+        self.meta = [torch.from_numpy(a).to(dev) for a in (lay.sendcounts, lay.sdispls, lay.recvcounts, lay.rdispls)]
+        self.recv = torch.full((lay.recv_bytes,), CANARY, dtype=torch.uint8, device=dev)
+        assert self.call(4, mode=tuna.TUNA_MODE_STAGED) == 0
+        torch.cuda.synchronize()
+        self.want = self.recv.clone()
+
+    def args(self):
+        sc, sd, rc_, rd = self.meta
+        return (self.send, sc, sd, self.recv, rc_, rd, self.lay.P, 0)
+
+    def options(self, **fields):
+        o = self.tuna.tuna_opts_init()
+        o.mode = self.tuna.TUNA_MODE_FUSED                   # small problems too take the general path
+        for k, v in fields.items():
+            setattr(o, k, v)
+        return o
+
+    def call(self, radix, stream=None, **fields):
+        return self.tuna.tuna_alltoallv_ex(None, *self.args(), radix, radix, self.options(**fields), stream)
+
+    def clear(self):
+        self.recv.fill_(CANARY)
+        torch.cuda.synchronize()
+
+    def ok(self):
+        return torch.equal(self.recv, self.want)
+
+
+def _uniform(P, longest, seed):
+    return np.random.default_rng(seed).integers(0, longest // 4 + 1, (P, P)) * 4
+
+
+@pytest.mark.parametrize("radix", [2, 48])
+def test_a_plan_is_made_while_a_call_of_long_blocks_is_in_flight(tuna, radix):
+    """Both count the units of their blocks on the device."""
+    big, other = Prob(tuna, _uniform(48, 900000, 1), 1), Prob(tuna, _uniform(24, 120000, 2), 2)
+    side = torch.cuda.Stream()
+    for it in range(6):
+        big.clear()
+        other.clear()
+        print("plan beside a call", radix, it, flush=True)
+        assert big.call(radix, side) == 0
+        rc, plan = tuna.tuna_alltoallv_init_ex(None, *other.args(), 3, 3, other.options(), None)
+        assert rc == 0, tuna.tuna_strerror(rc)
+        try:
+            st = tuna.tuna_get_stats()                       # the call's
+            assert st.hop_kernels == tuna.TUNA_HOP_LONG and st.P == 48
+            own = int(np.trace(big.lay.sendcounts))
+            assert radix == 2 or st.phase[0].payload_bytes == big.lay.payload_bytes - own
+            assert tuna.tuna_start(plan) == 0
+            torch.cuda.synchronize()
+            assert big.ok() and other.ok(), it
+            assert tuna.tuna_get_stats().hop_kernels == tuna.TUNA_HOP_LONG
+        finally:
+            assert tuna.tuna_plan_free(plan) == 0
+    tuna.tuna_release()
+
+
+@pytest.mark.parametrize("P,radix", [(16, 2), (100, 4), (300, 2)])
+def test_calls_that_send_the_places_of_t_to_the_device(tuna, P, radix):
+    """Back to back on one stream and with a plan and a sizing query between them, whose validation reads other sums of classes."""
+    def counts(k):
+        c = _uniform(P, 300, k)
+        c[1, P - 2] = c[P - 1, 3] = 70004                    # too long for the kernels that find their blocks themselves
+        return c
+    a, b = Prob(tuna, counts(1), 1, gap=1), Prob(tuna, 2 * counts(2), 2, gap=1)
+    exact = {"t_layout": tuna.TUNA_T_EXACT}
+    side = torch.cuda.Stream()
+    for it in range(8):
+        a.clear()
+        b.clear()
+        print("places on their way", P, radix, it, flush=True)
+        assert a.call(radix, side, **exact) == 0
+        if it % 4 == 1:
+            assert tuna.tuna_workspace_bytes(b.meta[0], P, 0, radix, radix)[0] == 0
+        if it % 4 == 2:
+            rc, plan = tuna.tuna_alltoallv_init_ex(None, *b.args(), radix, radix, b.options(**exact), None)
+            assert rc == 0 and tuna.tuna_plan_free(plan) == 0
+        assert b.call(radix, None if it % 4 == 3 else side, **exact) == 0
+        assert tuna.tuna_get_stats().hop_kernels & tuna.TUNA_HOP_ENGINE
+        torch.cuda.synchronize()
+        assert a.ok() and b.ok(), it
+    tuna.tuna_release()

@@ -21,3 +21,12 @@ def test_places_of_t_are_not_overwritten_on_their_way(runtime, P, radix, then):
     """The places of T's classes go to the device from pinned memory after a call has returned: nothing may write there
     until the copy is done.  (300 ranks: more classes than the host adds up itself.)"""
     assert fake_hip.run(runtime, "upload", P, radix, then) == {"violations": 0}
+
+
+@pytest.mark.parametrize("plan", [("long", 70, 3), ("long", 20, 20), ("engine", 90, 4)])
+@pytest.mark.parametrize("call", [("long", 60, 60), ("long", 64, 2), ("engine", 100, 4)])
+def test_a_plan_counts_in_a_status_block_of_its_own(runtime, call, plan):
+    """Making a plan does not wait for a call in flight on another stream of the context, whose kernels count in the context's
+    status block: k_hop_long moves as many units as stand there."""
+    r = fake_hip.run(runtime, "plan_status", *call, *plan)
+    assert r["seen"] > 0 and r["shared"] == []
