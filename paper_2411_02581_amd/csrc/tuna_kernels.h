@@ -287,7 +287,8 @@ constexpr int kValCopies = 32;
 constexpr int kValFoldRows = 64, kValFoldClasses = 24;      // most workgroups and classes that the host folds
 constexpr int kValRow = kValPartial + kValFoldClasses + 1;  // words of such a row, the ticket behind the others
 // A wave's stores to pinned host memory, then the number that tells a waiting host that they are there: it need not wait
-// for the kernel's end, its signal and the runtime's look at it.  By a whole wave.
+// for the kernel's end, its signal and the runtime's look at it.  By a whole wave, as its last stores: a call that is refused
+// returns on the ticket, and the context's next one, on whatever stream, is ordered behind nothing else.
 __device__ __forceinline__ void send_ticket(unsigned long long* word, unsigned long long ticket) {
     __threadfence_system();
     if ((threadIdx.x & (kWave - 1)) == 0) __hip_atomic_store(word, ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -486,10 +487,10 @@ __global__ void __launch_bounds__(1024) k_validate(const int32_t* __restrict__ s
         if (ticket) o[kValPartial + i] = v;                   // (first wave: kValFoldClasses < kWave)
         else if (v) atomicAdd(&st->cls_chunks[i], v);
     }
-    // the totals that k_phase_sums adds to (without a ticket k_validate_finish clears them), not for a sizing query: the
-    // totals there belong to the context's last call
-    if (ticket && ty == 0) send_ticket(o + kValRow - 1, ticket);
+    // the totals that k_phase_sums adds to, and the units that k_long_units counts (without a ticket k_validate_finish clears
+    // them), not for a sizing query: the totals there belong to the context's last call
     if (ticket && clear_totals && blockIdx.x == 0 && ty == 0) st->phase_bytes[tx] = st->phase_chunks[tx] = st->phase_units[tx][0] = 0;
+    if (ticket && ty == 0) send_ticket(o + kValRow - 1, ticket);
 }
 
 // k_zero64: n 64-bit words to zero (the class sums before a validation pass).
@@ -552,12 +553,12 @@ __global__ void __launch_bounds__(256) k_validate_finish(const unsigned long lon
             mirror->windows = wi;
         }
     }
+    // the totals that k_phase_sums adds to, and the units that k_long_units counts; the other paths write them whole
+    if (clear_totals && threadIdx.x < 64) st->phase_bytes[threadIdx.x] = st->phase_chunks[threadIdx.x] = st->phase_units[threadIdx.x][0] = 0;
     if (mirror && threadIdx.x < kWave) {
         for (int i = threadIdx.x; i < ncls; i += kWave) { mirror->cls_chunks[i] = st->cls_chunks[i]; st->cls_chunks[i] = 0; }
         send_ticket(word, ticket);
     }
-    // the totals that k_phase_sums adds to; the other paths write them whole
-    if (clear_totals && threadIdx.x < 64) st->phase_bytes[threadIdx.x] = st->phase_chunks[threadIdx.x] = st->phase_units[threadIdx.x][0] = 0;
 }
 
 // ------------------------------------------------------------------------------------------

@@ -110,3 +110,29 @@ def test_calls_that_send_the_places_of_t_to_the_device(tuna, P, radix):
         torch.cuda.synchronize()
         assert a.ok() and b.ok(), it
     tuna.tuna_release()
+
+
+@pytest.mark.parametrize("P,radix", [(48, 2), (48, 48), (300, 2), (300, 300)])
+def test_a_call_behind_a_refused_one_on_another_stream(tuna, P, radix):
+    """A refused call returns as soon as the host knows that it is: what its validation clears is cleared by then.  The call
+    behind it counts its units and bytes there."""
+    prob = Prob(tuna, _uniform(P, 900000 if P < 100 else 60000, 3), 3)
+    bad = prob.meta[0].clone()
+    bad[1, 2] += 4                                           # not the transpose of the receive counts
+    sides = [torch.cuda.Stream(), torch.cuda.Stream()]
+    totals = None
+    for it in range(12):
+        prob.clear()
+        print("behind a refused call", P, radix, it, flush=True)
+        a = list(prob.args())
+        a[1] = bad
+        assert tuna.tuna_alltoallv_ex(None, *a, radix, radix, prob.options(), sides[it % 2]) == tuna.TUNA_ERR_COUNT_MISMATCH
+        assert prob.call(radix, sides[1 - it % 2]) == 0
+        st = tuna.tuna_get_stats()
+        assert (st.hop_kernels == tuna.TUNA_HOP_LONG) == (P < 100 or radix == 300)
+        now = [(st.phase[x].payload_bytes, st.phase[x].staged_bytes) for x in range(st.n_phases)]
+        totals = totals or now
+        assert now == totals and all(b > 0 for b, _ in now)
+        torch.cuda.synchronize()
+        assert prob.ok(), it
+    tuna.tuna_release()
