@@ -133,9 +133,13 @@ struct Ctx {
     bool profile = false;               // the call being issued records events
     std::vector<hipEvent_t> ev_pool;
     std::vector<Mark> marks;
+    // The last immediate call that has put work on a stream: its stream, and with end_recorded its end in ev_end.  A call on
+    // another stream waits for it, whatever was refused, found empty or started from a plan in between.
     hipEvent_t ev_end = nullptr;
     bool end_recorded = false;
-    hipStream_t last_stream = nullptr;  // stream of the last immediate call (its end is ev_end when end_recorded)
+    hipStream_t last_stream = nullptr;
+    hipEvent_t ev_start = nullptr;      // end of the last profiled start of a plan
+    hipEvent_t stats_end = nullptr;     // the event that the statistics on file are complete with (ev_end, ev_start; nullptr: they are)
     unsigned char* tiny_t = nullptr;    // T of the one-kernel call for tiny problems (kTinyTBytes, allocated at its first use)
     const void* tiny_declined = nullptr; // sendcounts of the last problem that kernel declined: it is not asked again for it
     bool device_totals = false;         // the per-phase totals of the statistics on file are still in *sb.d_status (an immediate call's)
@@ -214,6 +218,7 @@ void free_ctx(Ctx& c) {
     if (c.data) (void)hipFree(c.data);
     if (c.tiny_t) (void)hipFree(c.tiny_t);
     if (c.ev_end) (void)hipEventDestroy(c.ev_end);
+    if (c.ev_start) (void)hipEventDestroy(c.ev_start);
     for (hipEvent_t e : c.ev_pool) (void)hipEventDestroy(e);
     for (hipEvent_t e : c.ev_phase) (void)hipEventDestroy(e);
     if (c.ev_fork) (void)hipEventDestroy(c.ev_fork);
@@ -1820,7 +1825,8 @@ int run_tiny(Ctx& c, const void* sendbuf, const int32_t* sendcounts, const int64
     fill_stats_header(pr, hs, c.stats);
     c.stats.temp_bytes = (int64_t)P * pl.slots * (((int64_t)hs.max_count + 15) / 16 * 16);
     c.stats.workspace_bytes = (int64_t)kTinyTBytes;
-    c.end_recorded = false;
+    c.end_recorded = false;                                   // (it has ended, and what it waited for)
+    c.stats_end = nullptr;
     c.last_stream = s;
     c.have_stats = true;
     *done = true;
@@ -1857,7 +1863,7 @@ int run_once(Ctx& c, const Options& opt, const void* sendbuf, const int32_t* sen
     hipStream_t s = (hipStream_t)stream;
     if (c.ready && c.end_recorded && c.last_stream != s) HIPCHK(hipStreamWaitEvent(s, c.ev_end, 0));
     c.marks.clear();
-    c.end_recorded = false;
+    c.stats_end = nullptr;
     c.have_stats = false;
     c.device_totals = true;
     c.profile = opt.profile != 0;
@@ -1897,10 +1903,12 @@ int run_once(Ctx& c, const Options& opt, const void* sendbuf, const int32_t* sen
         }
         rc = run_one_pass(pr, mbase, mbytes, dbase, s, st);
     }
+    // (also behind what a call that failed half-way has enqueued)
+    const hipError_t e = hipEventRecord(c.ev_end, s);
+    if (e == hipSuccess) { c.end_recorded = true; c.last_stream = s; }
     if (rc != TUNA_OK) return rc;
-    HIPCHK(hipEventRecord(c.ev_end, s));
-    c.end_recorded = true;
-    c.last_stream = s;
+    HIPCHK(e);
+    c.stats_end = c.ev_end;
     c.have_stats = true;
     return TUNA_OK;
 }
@@ -2105,15 +2113,16 @@ int plan_start(Plan* plan, hipStream_t s) {
     c.stats = plan->stats;
     c.device_totals = false;
     c.profile = plan->pr.opt.profile != 0 || sh.defaults.profile != 0;
-    if (plan->empty) { c.end_recorded = false; c.have_stats = true; return TUNA_OK; }
+    c.stats_end = nullptr;
+    if (plan->empty) { c.have_stats = true; return TUNA_OK; }
     mark(&c, s, -1, -1);
     mark(&c, s, kCatPrepare, -1);
     int rc = plan_launch_data(plan, s);
     if (rc != TUNA_OK) return rc;
     if (c.profile) {
-        HIPCHK(hipEventRecord(c.ev_end, s));
-        c.end_recorded = true;
-        c.last_stream = s;
+        if (!c.ev_start) HIPCHK(hipEventCreate(&c.ev_start));
+        HIPCHK(hipEventRecord(c.ev_start, s));
+        c.stats_end = c.ev_start;
     }
     c.have_stats = true;
     return TUNA_OK;
@@ -2343,7 +2352,7 @@ int run_static(const void* sendbuf, const int32_t* sendcounts, const int64_t* sd
     if (rc != TUNA_OK) return rc;
     // the statistics on file (header only: nothing here is timed) are the default context's
     g.marks.clear();
-    g.end_recorded = false;
+    g.stats_end = nullptr;
     g.device_totals = false;
     fill_stats_header(pr, hs, g.stats);
     g.have_stats = true;
@@ -2877,8 +2886,8 @@ int tuna_ctx_get_stats(tuna_ctx_t ctx, tuna_stats_t* out) {
     if (!out) return TUNA_ERR_ARG;
     if (!g.have_stats) { std::memset(out, 0, sizeof(*out)); out->last_hip_error = sh.last_hip_error; return TUNA_OK; }
     tuna_stats_t& st = g.stats;
-    if (g.end_recorded) {
-        HIPCHK(hipEventSynchronize(g.ev_end));
+    if (g.stats_end) {
+        HIPCHK(hipEventSynchronize(g.stats_end));
         if (g.device_totals) {   // a persistent plan knows its per-phase bytes since it was made
             HIPCHK(hipMemcpy(g.sb.h_status, g.sb.d_status, sizeof(Status), hipMemcpyDeviceToHost));
             for (int i = 0; i < st.n_phases; ++i) {

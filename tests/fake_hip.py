@@ -121,6 +121,41 @@ def case_plan_status(t, counts, P, radix, plan_counts, plan_P, plan_radix):
     return {"seen": len(words), "shared": [n for n, p in words if status <= p < status + 32768]}
 
 
+def case_order(t, between, P, radix):
+    """A call, something else that leaves it in flight, and a call on another stream: is that one's first kernel behind the
+    first call?"""
+    prob = t.problem(np.full((P, P), 300), gap=1)
+    nothing = t.problem(np.zeros((P, P)), gap=1)
+    plans = [t.plan(nothing, 2, S3), t.plan(prob, radix, S3, profile=1)]
+    assert t.call(prob, radix, S1) == 0
+    length = t.fake.fake_length(S1)
+    if between == "ranks per node":
+        assert t.call(prob, radix, S2, rpn=7) == t.b.TUNA_ERR_ARG
+    elif between == "no counts":
+        assert t.call((prob[0], [None] * 6), radix, S3) == t.b.TUNA_ERR_ARG
+    elif between == "refused":
+        wrong = t.problem(np.full((P, P), 300), gap=1)
+        wrong[0].sendcounts[1, 2] += 4
+        assert t.call(wrong, radix, S3) == t.b.TUNA_ERR_COUNT_MISMATCH
+    elif between == "empty":
+        assert t.call(nothing, radix, S3) == 0
+    elif between == "empty start":
+        assert t.lib.tuna_start(plans[0], S3) == 0
+    elif between == "profiled start":
+        assert t.lib.tuna_start(plans[1], S3) == 0
+    elif between == "profiled start there":
+        assert t.lib.tuna_start(plans[1], S2) == 0
+    elif between == "noalloc":
+        assert t.lib.tuna_alltoallv_noalloc(*prob[1], P, 0, radix, radix, S3) == 0
+    elif between == "query":
+        n = ctypes.c_size_t(0)
+        assert t.lib.tuna_workspace_bytes(prob[1][1], P, 0, radix, radix, ctypes.byref(n)) == 0
+    first = t.fake.fake_notes()
+    assert t.call(prob, radix, S2) == 0
+    assert t.fake.fake_stream(first) == S2
+    return {"behind": t.fake.fake_before(first, S1) >= length > 0}
+
+
 CASES = {k[5:]: f for k, f in list(globals().items()) if k.startswith("case_")}
 
 if __name__ == "__main__":

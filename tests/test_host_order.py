@@ -30,3 +30,11 @@ def test_a_plan_counts_in_a_status_block_of_its_own(runtime, call, plan):
     status block: k_hop_long moves as many units as stand there."""
     r = fake_hip.run(runtime, "plan_status", *call, *plan)
     assert r["seen"] > 0 and r["shared"] == []
+
+
+@pytest.mark.parametrize("P,radix", [(16, 16), (100, 4)])
+@pytest.mark.parametrize("between", ["nothing", "ranks per node", "no counts", "refused", "empty", "empty start", "profiled start",
+                                     "profiled start there", "noalloc", "query"])
+def test_a_call_on_another_stream_is_behind_the_one_in_flight(runtime, between, P, radix):
+    """They share the context's workspace, whatever was called between them."""
+    assert fake_hip.run(runtime, "order", between, P, radix) == {"behind": True}
