@@ -909,10 +909,9 @@ int block_kernel(const Prepared& pr) {
 }
 bool small_blocks(const Prepared& pr) { return block_kernel(pr) == TUNA_HOP_DIRECT; }
 bool row_blocks(const Prepared& pr) { return block_kernel(pr) == TUNA_HOP_ROWS; }
-// Room for a phase's units: as much as two lists of the other hops' units take (a call has them side by side and uses
-// neither), and more than there are of these -- a block of n bytes has at most (n + 127) / kLongUnit + 1, the mean of all
-// is 16 KiB and more, and each list has one unit per 4 KiB of payload.
-size_t long_unit_cap(const Prepared& pr) { return 2 * pr.ds.unit_cap; }
+// Room for a phase's units, of which a block of n bytes has at most (n + 127) / kLongUnit + 1.  A call has it where the two lists
+// of the other hops' units lie side by side: each has one unit per 4 KiB of payload, and the mean block is 16 KiB and more.
+size_t long_unit_cap(const Prepared& pr) { return (size_t)(pr.total_bytes / kLongUnit) + 2 * (size_t)pr.P * (size_t)pr.P; }
 // Phases of long blocks, all rounds at once: k_long_units and k_hop_long.  The line lies at the mean of the blocks that are
 // not short; a unit is a wave however short its block is, so there must be payload for all the pairs as well.  Per call and
 // per start (p), us, the hops that would run otherwise / these:
@@ -1941,16 +1940,17 @@ void carve_full_layout(Carver& cv, int P, size_t unit_cap, LayoutDev& L) {
     L.units = cv.take<int4>(unit_cap);
 }
 
-size_t plan_unit_cap(const Prepared& pr) { return long_blocks(pr) ? long_unit_cap(pr) : pr.ds.unit_cap; }
-
-// Metadata memory of a plan: two size matrices, the per-rank byte sums, per phase two complete layouts.
+// Metadata memory of a plan: two size matrices, the per-rank byte sums, per phase two complete layouts and the hop arrays.  Long
+// blocks: per phase the list of units, and the places in T while they are made.
 size_t plan_meta_bytes(const Prepared& pr) {
     const PlanHost& pl = pr.dp->host;
+    if (long_blocks(pr))
+        return pl.phases.size() * align_up(long_unit_cap(pr) * sizeof(int4)) + (pr.exact_t ? exact_t_meta_bytes_for(pl, false) : 0);
     const size_t P2 = (size_t)pr.P * pr.P;
     size_t hop_bytes = 0;
     for (const auto& ph : pl.phases)
         if (phase_is_one_kernel(pr, ph)) hop_bytes += hop_bytes_for(pr.P, hop_ld_for(ph.nseg));
-    return 2 * align_up(P2 * 4) + align_up((size_t)pr.P * 8) + pl.phases.size() * 2 * layout_bytes_for(pr.P, plan_unit_cap(pr)) +
+    return 2 * align_up(P2 * 4) + align_up((size_t)pr.P * 8) + pl.phases.size() * 2 * layout_bytes_for(pr.P, pr.ds.unit_cap) +
            (pr.exact_t ? exact_t_meta_bytes_for(pl, true) : 0) + hop_bytes + self_meta_bytes(pr);
 }
 
@@ -1965,16 +1965,21 @@ bool plan_carve_meta(Plan* plan, void* meta, size_t mbytes, int32_t** cur, int32
     const int P = pr.P;
     const size_t P2 = (size_t)P * P;
     Carver cm(meta, mbytes);
+    plan->Ls.assign(nph, LayoutDev{}); plan->Lr.assign(nph, LayoutDev{}); plan->units.assign(nph, 0);
+    plan->hop.assign(nph, HopDev{});
+    if (long_blocks(pr)) {
+        for (size_t i = 0; i < nph; ++i) plan->Lr[i].units = cm.take<int4>(long_unit_cap(pr));
+        if (pr.exact_t) carve_exact_t(cm, pl, false, pr);
+        return cm.ok;
+    }
     *cur = cm.take<int32_t>(P2);
     *nxt = cm.take<int32_t>(P2);
     pr.rank_bytes = cm.take<unsigned long long>(P);
-    plan->Ls.resize(nph); plan->Lr.resize(nph); plan->units.assign(nph, 0);
     for (size_t i = 0; i < nph; ++i) {
-        carve_full_layout(cm, P, plan_unit_cap(pr), plan->Ls[i]);
-        carve_full_layout(cm, P, plan_unit_cap(pr), plan->Lr[i]);
+        carve_full_layout(cm, P, pr.ds.unit_cap, plan->Ls[i]);
+        carve_full_layout(cm, P, pr.ds.unit_cap, plan->Lr[i]);
     }
     if (pr.exact_t) carve_exact_t(cm, pl, true, pr);
-    plan->hop.assign(nph, HopDev{});
     for (size_t i = 0; i < nph; ++i)
         if (phase_is_one_kernel(pr, pl.phases[i])) carve_hop(cm, P, hop_ld_for(pl.phases[i].nseg), plan->hop[i]);
     carve_self(cm, pr);

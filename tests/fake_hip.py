@@ -156,6 +156,19 @@ def case_order(t, between, P, radix):
     return {"behind": t.fake.fake_before(first, S1) >= length > 0}
 
 
+def case_plan_bytes(t, P, size, radix, t_layout):
+    prob = t.problem(np.full((P, P), size), gap=1)
+    plan = t.plan(t.problem(np.full((P, P), 0)), radix, S1)     # (the context, and the schedule's tables)
+    assert t.lib.tuna_plan_free(plan) == 0
+    before = t.fake.fake_allocated()
+    plan = t.plan(prob, radix, S1, t_layout=t_layout)
+    took = t.fake.fake_allocated() - before
+    st = t.b.tuna_stats_t()
+    assert t.lib.tuna_start(plan, S1) == 0 and t.lib.tuna_get_stats(ctypes.byref(st)) == 0
+    assert st.hop_kernels == t.b.TUNA_HOP_LONG
+    return {"phases": st.n_phases, "meta": took - st.temp_bytes, "said": st.workspace_bytes - took}
+
+
 CASES = {k[5:]: f for k, f in list(globals().items()) if k.startswith("case_")}
 
 if __name__ == "__main__":

@@ -38,3 +38,13 @@ def test_a_plan_counts_in_a_status_block_of_its_own(runtime, call, plan):
 def test_a_call_on_another_stream_is_behind_the_one_in_flight(runtime, between, P, radix):
     """They share the context's workspace, whatever was called between them."""
     assert fake_hip.run(runtime, "order", between, P, radix) == {"behind": True}
+
+
+@pytest.mark.parametrize("t_layout", [0, 1])
+@pytest.mark.parametrize("P,size,radix", [(16, 4 << 20, 16), (16, 4 << 20, 2), (64, 300001, 8), (200, 40000, 200)])
+def test_a_plan_of_long_blocks_holds_one_list_of_units_per_phase(runtime, P, size, radix, t_layout):
+    """16 bytes per 4 KiB of payload and two per block, and with several phases the places in T: 20 bytes per block and phase."""
+    r = fake_hip.run(runtime, "plan_bytes", P, size, radix, t_layout)
+    phases = r["phases"]
+    assert r["meta"] <= phases * (16 * (P * P * size // 4096 + 2 * P * P) + 20 * P * P) + 65536
+    assert 0 <= r["said"] + 4096 <= 8192
