@@ -379,6 +379,10 @@ int get_plan(int P, int Q, int rl, int rg, bool fused, hipStream_t s, DevicePlan
     auto key = std::make_tuple(P, Q, crl, crg, fused ? 1 : 0);
     auto it = sh.plans.find(key);
     if (it == sh.plans.end()) {
+        // kernels that a stream only records would leave a cached schedule without tables
+        hipStreamCaptureStatus recording = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &recording) != hipSuccess) (void)hipGetLastError();
+        if (recording != hipStreamCaptureStatusNone) { sh.last_hip_error = (int)hipErrorStreamCaptureUnsupported; return TUNA_ERR_HIP; }
         DevicePlan dp;
         dp.host = make_plan(P, Q, crl, crg, fused, /*with_tables=*/false);
         if ((int)dp.host.phases.size() > TUNA_MAX_PHASES) return TUNA_ERR_TOO_LARGE;

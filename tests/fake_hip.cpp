@@ -25,6 +25,7 @@ using Clock = std::map<hipStream_t, long>;
 void merge(Clock& a, const Clock& b) { for (auto& x : b) a[x.first] = std::max(a[x.first], x.second); }
 
 struct Stream {
+    bool recording = false;             // what it is given is dropped, and waiting for it fails
     std::vector<std::function<void()>> ops;
     size_t done = 0;
     Clock now;
@@ -53,6 +54,7 @@ void wait_all() { for (auto& x : streams) wait(x.first); }
 void enqueue(hipStream_t s, std::function<void()> f) {
     Stream& st = streams[s];
     merge(st.now, host);
+    if (st.recording) f = [] {};
     st.ops.push_back(std::move(f));
     st.now[s] = (long)st.ops.size();
 }
@@ -185,7 +187,15 @@ hipError_t hipMemcpyAsync(void* d, const void* src, size_t n, hipMemcpyKind kind
     });
     return hipSuccess;
 }
-hipError_t hipStreamSynchronize(hipStream_t s) { wait(s); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t s) {
+    if (streams[s].recording) return hipErrorStreamCaptureUnsupported;
+    wait(s);
+    return hipSuccess;
+}
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* st) {
+    *st = streams[s].recording ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
 hipError_t hipDeviceSynchronize() { wait_all(); return hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = (hipStream_t)(next_stream += 16); return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t s) { wait(s); return hipSuccess; }
@@ -212,6 +222,7 @@ hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; 
 hipError_t hipFuncGetAttributes(hipFuncAttributes* f, const void*) { std::memset(f, 0, sizeof *f); return hipSuccess; }
 hipError_t hipMemGetInfo(size_t* f, size_t* t) { *f = *t = (size_t)288 << 30; return hipSuccess; }
 
+void fake_record(long s, int on) { streams[(hipStream_t)s].recording = on != 0; }
 int fake_notes() { return (int)notes.size(); }
 const char* fake_name(int i) { return notes[i].name.c_str(); }
 long fake_stream(int i) { return (long)notes[i].s; }

@@ -48,3 +48,10 @@ def test_a_plan_of_long_blocks_holds_one_list_of_units_per_phase(runtime, P, siz
     phases = r["phases"]
     assert r["meta"] <= phases * (16 * (P * P * size // 4096 + 2 * P * P) + 20 * P * P) + 65536
     assert 0 <= r["said"] + 4096 <= 8192
+
+
+@pytest.mark.parametrize("plan", [False, True])
+@pytest.mark.parametrize("P,radix", [(16, 4), (100, 3)])
+def test_no_schedule_is_kept_whose_tables_were_only_recorded(runtime, P, radix, plan):
+    """In a capture that allows allocations the kernels that fill a new schedule's tables would not have run."""
+    assert fake_hip.run(runtime, "recording", P, radix, plan) == {"refused": True, "tables": 1}
