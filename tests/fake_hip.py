@@ -69,11 +69,14 @@ class Lib:
         return plan
 
     def kernels(self, first=0):
-        """[name, stream] of the kernels launched from note `first` on."""
+        """[name, stream, template arguments] of the kernels launched from note `first` on."""
         out = []
         for i in range(first, self.fake.fake_notes()):
-            m = re.search(r"\d+(k_[a-z0-9_]+?)(?:I[LN]|E|$)", self.fake.fake_name(i).decode())
-            out.append([m.group(1) if m else "?", self.fake.fake_stream(i)])
+            name = self.fake.fake_name(i).decode()
+            n, at = re.search(r"(\d+)k_", name).group(1), name.index("k_")
+            n = next(int(n[j:]) for j in range(len(n)) if n[j] != "0" and at + int(n[j:]) <= len(name))
+            args = re.match(r"I((?:L[a-z]+\d+E)+)E", name[at + n:])
+            out.append([name[at:at + n], self.fake.fake_stream(i), [int(v) for v in re.findall(r"L[a-z]+(\d+)E", args.group(1))] if args else []])
         return out
 
 
@@ -177,6 +180,25 @@ def case_recording(t, P, radix, plan):
     first = t.fake.fake_notes()
     assert t.call(prob, radix, S1) == 0
     return {"refused": rc == t.b.TUNA_ERR_HIP, "tables": [k[0] for k in t.kernels(first)].count("k_build_tables")}
+
+
+def case_routes(t, problems, plan):
+    """The payload kernels of each of `problems` and the kernels of their places in T."""
+    out = []
+    for P, rpn, rl, rg, longest, q, t_layout, layout in problems:
+        counts = np.random.default_rng(P).integers(0, longest // q + 1, (P, P)) * q
+        counts[0, P - 1] = longest
+        prob = t.problem(counts, **layout)
+        first = t.fake.fake_notes()
+        if plan:
+            p = t.plan(prob, rl, S1, rpn=rpn, rg=rg, t_layout=t_layout)
+            first = t.fake.fake_notes()
+            assert t.lib.tuna_start(p, S1) == 0
+        else:
+            assert t.call(prob, rl, S1, rpn=rpn, rg=rg, t_layout=t_layout) == 0
+        out.append([[k[0], k[2]] for k in t.kernels(first) if k[0].startswith(("k_hop", "k_copy", "k_t_", "k_self_copy"))])
+        assert t.lib.tuna_release() == 0 or plan
+    return out
 
 
 CASES = {k[5:]: f for k, f in list(globals().items()) if k.startswith("case_")}

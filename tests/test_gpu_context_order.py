@@ -136,3 +136,52 @@ def test_a_call_behind_a_refused_one_on_another_stream(tuna, P, radix):
         torch.cuda.synchronize()
         assert prob.ok(), it
     tuna.tuna_release()
+
+
+@pytest.mark.parametrize("P,radix,longest", [(12, 12, 200000), (12, 2, 100000), (9, 3, 300001), (40, 40, 36000), (2, 2, 3000000)])
+def test_long_blocks_without_allocations(tuna, P, radix, longest):
+    """Two calls in a row: the units of the second are counted from zero again, in memory that still holds the first one's."""
+    counts = np.random.default_rng(P).integers(longest // 4, longest + 1, (P, P))
+    counts[P - 1, 0], counts[0, 1] = 0, 5
+    a, b = Prob(tuna, counts, 1, gap=3), Prob(tuna, counts[::-1].copy(), 2)
+    for it in range(3):
+        a.clear()
+        b.clear()
+        print("long blocks, noalloc", P, radix, it, flush=True)
+        for p in (a, b):
+            rc = tuna.tuna_alltoallv_noalloc(*p.args(), radix, radix)
+            assert rc == 0, tuna.tuna_strerror(rc)
+            assert tuna.tuna_get_stats().hop_kernels == tuna.TUNA_HOP_LONG
+        torch.cuda.synchronize()
+        assert a.ok() and b.ok(), it
+    tuna.tuna_release()
+
+
+@pytest.mark.parametrize("radix", [3, 64])
+def test_calls_of_long_blocks_back_to_back(tuna, radix):
+    """One behind the other on one stream and on two, no host synchronisation between them, behind a call of another hop."""
+    a, b, c = Prob(tuna, _uniform(64, 200000, 4), 4), Prob(tuna, _uniform(50, 300000, 5), 5, gap=2), Prob(tuna, _uniform(80, 30, 6), 6)
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    for it in range(4):
+        for p in (a, b, c):
+            p.clear()
+        print("long blocks back to back", radix, it, flush=True)
+        assert c.call(radix, s1) == 0
+        assert a.call(radix, s1) == 0
+        assert tuna.tuna_get_stats().hop_kernels == tuna.TUNA_HOP_LONG if it % 2 else True
+        assert b.call(radix, s2 if it % 2 else s1) == 0
+        torch.cuda.synchronize()
+        assert a.ok() and b.ok() and c.ok(), it
+    tuna.tuna_release()
+
+
+def test_statistics_of_a_plan_outlive_it(tuna):
+    prob, other = Prob(tuna, _uniform(30, 3000, 7), 7), Prob(tuna, _uniform(30, 900, 8), 8)
+    assert other.call(3) == 0
+    rc, plan = tuna.tuna_alltoallv_init_ex(None, *prob.args(), 3, 3, prob.options(profile=1), None)
+    assert rc == 0
+    assert tuna.tuna_start(plan) == 0
+    before = [(ph.payload_bytes, ph.staged_bytes) for ph in tuna.tuna_get_stats().phase]
+    assert tuna.tuna_plan_free(plan) == 0
+    assert [(ph.payload_bytes, ph.staged_bytes) for ph in tuna.tuna_get_stats().phase] == before and before[0][0] > 0
+    tuna.tuna_release()
