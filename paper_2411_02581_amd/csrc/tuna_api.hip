@@ -1183,7 +1183,8 @@ int rows_segs(const Prepared& pr) {
     return (int)std::min(std::max(8.0, pairs / 8192.0), mean <= 600.0 ? std::max(1.0, std::min(64.0, kRowsBytes / mean)) : rows_span(pr));
 }
 
-int direct_lpb(const Prepared& pr) { return pr.max_count <= 16 ? 1 : (pr.max_count <= 64 ? 4 : 16); }
+int lanes_per_block(int64_t max_block) { return max_block <= 16 ? 1 : (max_block <= 64 ? 4 : 16); }
+int direct_lpb(const Prepared& pr) { return lanes_per_block(pr.max_count); }
 bool direct_tall(const PhaseHost& ph) { return (long long)ph.nz * 16 > ph.nseg; }
 // Workgroup columns and steps per workgroup over `nseg` segments of a phase: one step each while that gives no more than 8192 workgroups (four
 // per resident slot of the device), then up to 8 steps; and the rows of partial sums that such a launch stores.
@@ -1195,17 +1196,19 @@ unsigned direct_columns(const Prepared& pr, const PhaseHost& ph, int nseg, int* 
     return (unsigned)((steps + *iters - 1) / *iters);
 }
 bool runs_direct(const Prepared& pr);
-// Phases that an immediate call's k_hop_senders moves, and its workgroup columns and steps per workgroup (as direct_columns).
-unsigned sender_columns(const Prepared& pr, const PhaseHost& ph, int* iters) {
+// Phases of a schedule of several that an immediate call's k_hop_senders moves, and its workgroup columns and steps per workgroup
+// (as direct_columns); lpb: lanes per block.
+unsigned sender_columns(int P, const PhaseHost& ph, int lpb, int* iters) {
     const int steps = (ph.nseg + 255) / 256;
-    *iters = std::max(1, std::min(steps, (int)((long long)steps * pr.P / sender_sets(direct_lpb(pr)) / kSenderGroups)));
+    *iters = std::max(1, std::min(steps, (int)((long long)steps * P / sender_sets(lpb) / kSenderGroups)));
     return (unsigned)((steps + *iters - 1) / *iters);
 }
-bool sender_phase(const Prepared& pr, const PhaseHost& ph) {
+bool by_senders(int P, const PhaseHost& ph, int lpb) {
     int iters = 0;
-    return pr.dp->host.phases.size() > 1 && ph.nz >= kSenderMinRounds && ph.nz <= kSenderMaxRounds &&
-           (long long)sender_columns(pr, ph, &iters) * ph.nz <= ph.nseg;       // (rows of partial sums: no more than segments)
+    return ph.nz >= kSenderMinRounds && ph.nz <= kSenderMaxRounds &&
+           (long long)sender_columns(P, ph, lpb, &iters) * ph.nz <= ph.nseg;       // (rows of partial sums: no more than segments)
 }
+bool sender_phase(const Prepared& pr, const PhaseHost& ph) { return pr.dp->host.phases.size() > 1 && by_senders(pr.P, ph, direct_lpb(pr)); }
 // The only phase of an immediate call's linear schedule, if its blocks are short: k_hop_pairs moves it, and the own blocks; its
 // workgroup columns and steps per workgroup (as direct_columns).
 bool pair_phase(const Prepared& pr) { return pr.dp->host.phases.size() == 1 && runs_direct(pr) && small_blocks(pr) && !long_blocks(pr); }
@@ -1239,7 +1242,7 @@ int launch_pairs(const Prepared& pr, uint2* part, hipStream_t s) {
 }
 unsigned direct_rows(const Prepared& pr, const PhaseHost& ph) {
     if (pair_phase(pr)) { int iters = 0; return pair_columns(pr, &iters); }
-    if (!row_blocks(pr) && sender_phase(pr, ph)) { int iters = 0; return sender_columns(pr, ph, &iters) * (unsigned)ph.nz; }
+    if (!row_blocks(pr) && sender_phase(pr, ph)) { int iters = 0; return sender_columns(pr.P, ph, direct_lpb(pr), &iters) * (unsigned)ph.nz; }
     if (row_blocks(pr)) { const int segs = rows_segs(pr); return (unsigned)((ph.nseg + segs - 1) / segs); }
     int iters = 0;
     return direct_columns(pr, ph, ph.nseg, &iters) * (unsigned)(4 / direct_shape(direct_lpb(pr), direct_tall(ph)).waves_r);
@@ -1257,7 +1260,7 @@ int launch_senders(const Prepared& pr, size_t i, uint2* part, hipStream_t s) {
     a.r = resolve_args(pr, i, nullptr, HopDev{});
     a.T = pr.T; a.part = part; a.nz = ph.nz;
     const int lpb = direct_lpb(pr), sets = sender_sets(lpb);
-    const dim3 grid(sender_columns(pr, ph, &a.iters), (unsigned)((pr.P + sets - 1) / sets));
+    const dim3 grid(sender_columns(pr.P, ph, lpb, &a.iters), (unsigned)((pr.P + sets - 1) / sets));
     if (lpb == 1) launch_senders_as<1, 0>(a, grid, pr.exact_kernels, s);
     else if (lpb == 4) {
         if (pr.gran >= 16) launch_senders_as<4, 1>(a, grid, pr.exact_kernels, s);
@@ -2414,8 +2417,12 @@ struct Features {
     double phases, p2, hop_gb, mblocks, msmall, small_gb, t_share;    // t_share: share of the hop bytes that is written to or read from T
 };
 
-// small: the problem's one-kernel phases run k_hop_direct (one-kernel mode and no block above 64 bytes)
-Features features_of(const PlanHost& pl, double payload_bytes, bool small) {
+// Problems whose one-kernel phases find their short blocks themselves (one-kernel mode and no block above 64 bytes).
+constexpr int kModelSmallBytes = 64;
+bool small_block_path(bool fused, int64_t max_block) { return fused && max_block > 0 && max_block <= kModelSmallBytes; }
+
+Features features_of(const PlanHost& pl, double payload_bytes, bool fused, int64_t max_block) {
+    const bool small = small_block_path(fused, max_block);
     Features f{};
     const double P = (double)pl.P;
     f.phases = (double)pl.phases.size();
@@ -2423,7 +2430,7 @@ Features features_of(const PlanHost& pl, double payload_bytes, bool small) {
     double moving = 0.0, by_sender = 0.0;
     for (const auto& ph : pl.phases) {
         moving += (double)ph.nseg * P;
-        if (ph.nz >= kSenderMinRounds) by_sender += (double)ph.nseg * P;
+        if (by_senders(pl.P, ph, lanes_per_block(max_block))) by_sender += (double)ph.nseg * P;
     }
     (small ? f.msmall : f.mblocks) = moving / 1e6;
     // A short block of a schedule of one phase is looked up in the receive counts and the displacements; with several
@@ -2452,13 +2459,10 @@ double bytes_ms(const Model& m, const Features& f) { return m.c[3] * f.hop_gb + 
 // the model's byte and block terms: what depends on the payload
 double data_ms(const Model& m, const Features& f) { return bytes_ms(m, f) + m.c[4] * f.mblocks + m.c[5] * f.msmall; }
 
-constexpr int kModelSmallBytes = 64;
-bool small_block_path(bool fused, int64_t max_block) { return fused && max_block > 0 && max_block <= kModelSmallBytes; }
-
 double predict_ms(int P, int Q, int rl, int rg, bool fused, int t_layout, int64_t payload_bytes, int64_t max_block,
                   int granularity) {
     const PlanHost pl = make_plan(P, Q, rl, rg, false, /*with_tables=*/false);
-    Features f = features_of(pl, (double)payload_bytes, small_block_path(fused, max_block));
+    Features f = features_of(pl, (double)payload_bytes, fused, max_block);
     const Model& m = g_model.m[fused ? 1 : 0];
     double ms = model_ms(m, f);
     if (granularity > 0 && granularity < 4) ms += bytes_ms(m, f) * (g_model.byte_granular[fused ? 1 : 0] - 1.0);
@@ -2607,7 +2611,7 @@ int calibrate(hipStream_t s) {
                 }
                 std::sort(t + 1, t + kReps);
                 const PlanHost pl = make_plan(pb.P, pb.P, r, r, false, false);
-                (is_odd ? Xo : is_lines ? Xl : X)[fused].push_back(features_of(pl, (double)entries * pb.S, small_block_path(fused != 0, pb.S)));
+                (is_odd ? Xo : is_lines ? Xl : X)[fused].push_back(features_of(pl, (double)entries * pb.S, fused != 0, pb.S));
                 (is_odd ? yo : is_lines ? yl : y)[fused].push_back(t[1 + (kReps - 1) / 2]);      // median of the timed calls
             }
         }

@@ -7,6 +7,7 @@ import shutil
 import pytest
 
 import fake_hip
+import paper_2411_02581_amd as tuna
 import test_gpu_pairs
 import test_gpu_t_places
 
@@ -112,3 +113,17 @@ def test_own_blocks_go_with_the_first_launch(runtime, own_first):
         problems = [(170, 0, 13, 13, 60, 4, SLOTS, {})]
     for prob, kernels in zip(problems, fake_hip.run(runtime, "routes", problems, False)):
         assert ("k_self_copy" in [k for k, _ in kernels]) == (not own_first), prob
+
+
+@pytest.mark.parametrize("longest", [8, 60])
+@pytest.mark.parametrize("P,radix", [(1024, 32), (1024, 1023), (1024, 12), (1024, 13), (2048, 46), (2048, 600), (3000, 1500), (1024, 4)])
+def test_the_cost_model_prices_blocks_by_the_kernel_that_finds_them(P, radix, longest):
+    """Short blocks of several phases cost four times the constant, three times where k_hop_senders finds them."""
+    rc, c = tuna.tuna_model_constants(tuna.TUNA_MODE_FUSED)
+    assert rc == 0
+    phases, payload = _phases(P, 0, radix, 0), P * P * longest // 2
+    blocks = sum(n * P for _, n in phases)
+    priced = sum(n * P * (3 if _by_senders(z, n) else 4) for z, n in phases)
+    want = c[0] + c[1] * len(phases) + c[2] * (len(phases) + 1) * P * P / 1e6 + c[5] * priced / 1e6 + c[6] * payload * blocks / (P * P) / 1e9
+    rc, ms = tuna.tuna_predict_ms(P, 0, radix, radix, tuna.TUNA_MODE_FUSED, tuna.TUNA_T_EXACT, payload, longest, 4)
+    assert rc == 0 and ms == pytest.approx(want, rel=1e-9)
