@@ -33,7 +33,8 @@
  *     workspace, a small status block and the statistics of its last call.  The entry points without a
  *     context argument use the process's default context.  Calls on one context share its workspace:
  *     a call issued on another stream than the context's previous call makes its stream wait for that
- *     call first, so they do not race (and do not overlap).  Calls on different contexts share nothing
+ *     call first, so they do not race (and do not overlap).  Making plans, starting them and sizing queries
+ *     write nothing that a call in flight uses, and do not wait for it.  Calls on different contexts share nothing
  *     but the read-only cached schedules and may overlap.  A context is not thread-safe: one host
  *     thread at a time per context; the process-wide defaults (tuna_set_option) are plain variables.
  *   - There is no CPU fallback: without a HIP device every compute entry point returns
@@ -82,11 +83,11 @@ typedef struct tuna_phase_stats {
     float ms_unpack;        /* every other one as ms_pack (tuna_stats_t.hop_kernels says which they were) */
 } tuna_phase_stats_t;
 
-/* Payload kernels of one-kernel phases.  One call or plan runs the destination-tiled hop in some of its phases and one
- * of the other three in the rest. */
+/* Payload kernels of one-kernel phases.  One call or plan runs one of them throughout, or the destination-tiled hop in some
+ * of its phases and the engine's hop or that of blocks of up to 64 KiB in the rest. */
 #define TUNA_HOP_ENGINE 1   /* the copy engine's hop */
 #define TUNA_HOP_TILED 2    /* the destination-tiled hop */
-#define TUNA_HOP_DIRECT 4   /* blocks of up to 256 bytes, found by the kernel that moves them */
+#define TUNA_HOP_DIRECT 4   /* blocks of up to 256 bytes, found by the kernel that moves them (one of three, by rounds and phases) */
 #define TUNA_HOP_ROWS 8     /* blocks of up to 64 KiB, found by the kernel that moves them */
 #define TUNA_HOP_LONG 16    /* long blocks (16 KiB and more on average), from a list of 4 KiB units */
 
@@ -138,8 +139,8 @@ typedef struct tuna_plan_info {
  *   ranks_per_node  Q.  0, 1 or P: flat TuNA over all P ranks.  Otherwise Q must divide P, rank
  *                   p lives on node p / Q with local id p % Q, and the hierarchical variant runs
  *                   with local radix min(radix, Q) and global radix min(radix, N), N = P / Q.
- * The call validates the counts on the device, reads a few integers back (one stream
- * synchronisation), sizes or grows the workspace, then enqueues all phases on `stream` and
+ * The call validates the counts on the device, waits until the result has arrived on the host (everything
+ * enqueued on `stream` before is done by then), sizes or grows the workspace, then enqueues all phases on `stream` and
  * returns without waiting for them.  Payloads of 64 MiB and more with at least two digit phases whose
  * blocks are not found by the kernels that move them (TUNA_HOP_ENGINE, TUNA_HOP_TILED): with one-kernel hops (the default) the block-size exchanges and scans of all phases run on a
  * second stream owned by the context while `stream` moves the payload, each phase's payload kernel
@@ -235,7 +236,7 @@ int tuna_alltoallv_ex(tuna_ctx_t ctx, const void* sendbuf, const int32_t* sendco
  * matrices, scans, work lists, staging buffers, T -- carved from one static device array of
  * TUNA_NOALLOC_SCRATCH_BYTES bytes that each GPU the library runs on holds until the process ends.
  * The call itself calls no hipMalloc, hipFree, hipHostMalloc or hipEventCreate (it still reads a
- * few integers back and synchronises `stream` once, like tuna_alltoallv).  A problem that needs
+ * few integers back and synchronises `stream` once).  A problem that needs
  * more than the array returns TUNA_ERR_NOALLOC_LIMIT before any payload byte has moved: the need
  * is about 26 P^2 bytes of tables and scans per phase-independent part, 24 bytes per moving block
  * and phase of schedule tables, twice the payload for the staging buffers of three-stage phases
@@ -404,7 +405,8 @@ int tuna_debug_phase_sizes(const void* sendbuf, const int32_t* sendcounts, const
  * hops; T in the paper's slots adds to the byte term by how empty the slots are (mean block / M).  When no
  * block exceeds 64 bytes the one-kernel hops run a kernel of their own (1 or 4 lanes per block), whose
  * blocks and bytes are priced by constants of their own, c5 and c6, in place of c4 and c3; such a block counts
- * four times in a schedule of several phases, where its size has to be exchanged and its place in T scanned.
+ * four times in a schedule of several phases, where its place in T has to be scanned and looked up, three times in phases of 12
+ * to 1024 rounds.
  *   tuna_calibrate   times about sixty immediate calls of dense synthetic problems on the current
  *                    device (a few hundred milliseconds; allocates up to about 8 GiB and frees it;
  *                    synchronises) and fits the constants to them.  Without it the constants are the

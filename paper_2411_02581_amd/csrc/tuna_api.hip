@@ -38,7 +38,7 @@ struct DevicePlan {
     std::vector<SegDev> d_seg;
     std::vector<int32_t*> d_seg_mem;
     hipStream_t built_on = nullptr;      // stream the table kernels were enqueued on
-    bool complete = false;               // known to have finished (a later call synchronised)
+    bool complete = false;               // known to be there (a later call has waited for kernels behind them)
     std::vector<int32_t*> d_zt;
     int32_t* d_hm1 = nullptr;            // [P]: hops - 1 of every slot index (how often the block is stored into T)
     unsigned long long* d_mask = nullptr; // [P]: phases in which the block with a slot index moves (move_mask)
@@ -552,7 +552,9 @@ int wait_ticket(const unsigned long long* word, unsigned long long ticket, hipSt
     return TUNA_OK;
 }
 
-// Validation + sizing pass shared by tuna_alltoallv* and tuna_workspace_bytes: fills *sb.h_status.
+// Validation + sizing pass shared by tuna_alltoallv* and tuna_workspace_bytes: fills *sb.h_status.  When it returns everything that
+// the stream held before is done, and all that validation stores but not, with a ticket, its last kernel's end: the stream
+// need not be idle.
 // clear_totals: the per-phase totals in *sb.d_status start at zero (an immediate call, whose kernels may add to them).  A
 // sizing query and a plan leave them alone: until the next call they are the last one's statistics, or still being summed.
 int run_validate(const StatusBufs& sb, const int32_t* sendcounts, const int32_t* recvcounts, const int64_t* sdispls,
@@ -945,7 +947,7 @@ int prepare_sizes(Prepared& pr, int dense_option, hipStream_t s, Status& hs, boo
                           (dense_option != 0 && has_t) ? pr.dp : nullptr, !pr.for_plan);
     if (rc != TUNA_OK) return rc;
     hs = *pr.sb.h_status;
-    if (pr.dp->built_on == s) pr.dp->complete = true;      // run_validate synchronised this stream
+    if (pr.dp->built_on == s) pr.dp->complete = true;      // run_validate has waited for kernels of this stream behind the tables'
     if (hs.flags & 1u) return TUNA_ERR_NEGATIVE_COUNT;
     if (hs.flags & 2u) return TUNA_ERR_COUNT_MISMATCH;
     if (hs.flags & 4u) return TUNA_ERR_ARG;                 // a non-empty block at a negative displacement
@@ -2830,7 +2832,7 @@ int tuna_workspace_bytes(const int32_t* sendcounts, int P, int ranks_per_node, i
     const unsigned long long t_chunks = (o.t_layout != 0 && pl.slots > 0)
         ? colour_classes(pl, fused, staggered, o.block_count > 0, h_status->cls_chunks, cbase) : 0;
     const bool exact_t = choose_exact_t(o.t_layout, pl, *h_status, t_chunks) && pl.slots > 0;
-    dp->complete = true;                                  // run_validate synchronised the stream the tables were built on
+    dp->complete = true;                                  // run_validate has waited for kernels behind the tables' (get_plan for another stream's)
     if (h_status->flags & 1u) return TUNA_ERR_NEGATIVE_COUNT;
     if (too_large(P, *h_status)) return TUNA_ERR_TOO_LARGE;
     const DataSizes ds = data_sizes_for(pl, h_status->max_count, h_status->total_chunks, fused, staggered,

@@ -595,7 +595,8 @@ __global__ void __launch_bounds__(256) k_rotate_init(const int32_t* __restrict__
 
 // ------------------------------------------------------------------------------------------
 // k_self_copy: the block a rank keeps for itself goes straight from S to R (Section "Estimating
-// temporary buffer size": one block is destined for the rank itself).  grid (P, split).
+// temporary buffer size": one block is destined for the rank itself).  One workgroup per rank; own_block is what other launches
+// that take the own blocks along run for a rank.
 // ------------------------------------------------------------------------------------------
 __device__ __forceinline__ void own_block(const unsigned char* __restrict__ S, const int32_t* __restrict__ sendcounts,
                                           const int64_t* __restrict__ sdispls, unsigned char* __restrict__ R,
@@ -2018,7 +2019,7 @@ __global__ void __launch_bounds__(256) k_hop_rows(const DirectArgs a) {
 // LDS; 60 ranks, up to 1 MiB, radix 2 and linear, us per call: 8 resident 1954 / 682, 10 1940 / 683, 12 1980 / 695, 16 2037 /
 // 695, 20 2087 / 698; 8 KiB, 6 resident 1984 / 666, but 200 ranks, 80 KiB 1186 against 1139).  Streaming loads from
 // kLongStreamBytes on (683 / 779; 134 MB 90 / 83, 245 MB 125 / 111).
-//   Against the engine's and the destination-tiled hop with their metadata kernels: 60 ranks, up to 1 MiB, 788 -> 683 us per
+//   Against the engine's and the destination-tiled hop with their metadata kernels: 60 ranks, up to 1 MiB, 786 -> 681 us per
 // call (5.3 -> 5.8 TB/s, metadata and validation included), 708 -> 635 per start; 100 ranks, 200 KB, r = 10 1420 -> 1248; 200 ranks, byte-granular up to 150 KB
 // 1374 -> 1060 per start; 20 ranks, up to 200 KB (40 MB) 79-94 -> 56.
 // ------------------------------------------------------------------------------------------
