@@ -2390,7 +2390,8 @@ int run_static(const void* sendbuf, const int32_t* sendcounts, const int64_t* sd
 // 64 bytes run another kernel (k_hop_direct, 1 or 4 lanes per block), whose blocks and bytes are priced by
 // constants of their own, c5 and c6, in place of c4 and c3.  The built-in constants were fitted to
 // immediate calls on MI355X by tuna_calibrate; calling it replaces them by a fit to calls timed on the
-// device at hand.
+// device at hand.  Over 59 one-kernel calls of 60 to 6000 ranks, up to 16 bytes to 1 MiB, radix 2 to linear, the built-in ones are
+// off by 8 % on average (long blocks, whose hop they do not know, +5 to +11 %), at most by -32 % (64 bytes, P = 4096, linear).
 constexpr int kModelTerms = 7;
 static_assert(kModelTerms + 3 == TUNA_MODEL_CONSTANTS, "tuna_model_constants reports the terms and the three factors");
 struct Model {
@@ -2437,8 +2438,9 @@ Features features_of(const PlanHost& pl, double payload_bytes, bool fused, int64
     (small ? f.msmall : f.mblocks) = moving / 1e6;
     // A short block of a schedule of one phase is looked up in the receive counts and the displacements; with several
     // phases its place in T is scanned, stored and looked up twice, and most lookups leave the rows of one rank.  Four
-    // times the constant fits uniform [0, 16] B at P = 2048 within 10 % at r = 2, 8, 46 and P; three times where
-    // k_hop_senders finds them (r = 46: 0.199 ms, predicted with four times 0.247).
+    // times the constant fits uniform [0, 16] B at P = 2048 within 10 % at r = 2, 8 and P; three times where
+    // k_hop_senders finds them (predicted / measured: r = 13 0.87, r = 32 1.14; up to 60 bytes 0.79 and 0.98; P = 1000 1.07 and
+    // 1.06; P = 4096, r = 64 0.90, P = 6000, r = 77 0.84).
     if (small && f.phases > 1.0) f.msmall = (4.0 * moving - by_sender) / 1e6;
     // sizes are taken to be independent of the rank distance: every slot index carries payload / P^2
     (small ? f.small_gb : f.hop_gb) = P > 0 ? payload_bytes * (moving / (P * P)) / 1e9 : 0.0;

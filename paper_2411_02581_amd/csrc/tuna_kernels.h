@@ -317,6 +317,10 @@ __global__ void __launch_bounds__(1024) k_validate(const int32_t* __restrict__ s
     const int ncls = mask ? class_count(nph) : 0;
     for (int i = ty * kValTile + tx; i < ncls * copies; i += ny * kValTile) lcls[i] = 0;
     if (tx == 0 && ty == 0) long_seen = 0;
+    // the totals that k_phase_sums adds to, and the units that k_long_units counts (without a ticket k_validate_finish clears
+    // them), not for a sizing query: the totals there belong to the context's last call.  First of all: right in front of the
+    // ticket these stores cost a call 2 us
+    if (ticket && clear_totals && blockIdx.x == 0 && ty == 0) st->phase_bytes[tx] = st->phase_chunks[tx] = st->phase_units[tx][0] = 0;
     __syncthreads();
     unsigned int window = 0;                              // largest sum of a column (first wave) or row (second wave)
     const int tpr = (P + kValTile - 1) / kValTile;       // tiles per row
@@ -487,9 +491,6 @@ __global__ void __launch_bounds__(1024) k_validate(const int32_t* __restrict__ s
         if (ticket) o[kValPartial + i] = v;                   // (first wave: kValFoldClasses < kWave)
         else if (v) atomicAdd(&st->cls_chunks[i], v);
     }
-    // the totals that k_phase_sums adds to, and the units that k_long_units counts (without a ticket k_validate_finish clears
-    // them), not for a sizing query: the totals there belong to the context's last call
-    if (ticket && clear_totals && blockIdx.x == 0 && ty == 0) st->phase_bytes[tx] = st->phase_chunks[tx] = st->phase_units[tx][0] = 0;
     if (ticket && ty == 0) send_ticket(o + kValRow - 1, ticket);
 }
 
@@ -506,6 +507,8 @@ __global__ void __launch_bounds__(256) k_validate_finish(const unsigned long lon
                                                          Status* __restrict__ st, int clear_totals, Status* __restrict__ mirror,
                                                          int ncls, unsigned long long* __restrict__ word, unsigned long long ticket) {
     __shared__ unsigned long long red[4][8];
+    // the totals that k_phase_sums adds to, and the units that k_long_units counts; the other paths write them whole
+    if (clear_totals && threadIdx.x < 64) st->phase_bytes[threadIdx.x] = st->phase_chunks[threadIdx.x] = st->phase_units[threadIdx.x][0] = 0;
     unsigned long long fa = 0, m = 0, by = 0, ch = 0, ex = 0, tc = 0, sb = 0, wi = 0;
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
         const unsigned long long* o = partial + (size_t)i * kValPartial;
@@ -553,8 +556,6 @@ __global__ void __launch_bounds__(256) k_validate_finish(const unsigned long lon
             mirror->windows = wi;
         }
     }
-    // the totals that k_phase_sums adds to, and the units that k_long_units counts; the other paths write them whole
-    if (clear_totals && threadIdx.x < 64) st->phase_bytes[threadIdx.x] = st->phase_chunks[threadIdx.x] = st->phase_units[threadIdx.x][0] = 0;
     if (mirror && threadIdx.x < kWave) {
         for (int i = threadIdx.x; i < ncls; i += kWave) { mirror->cls_chunks[i] = st->cls_chunks[i]; st->cls_chunks[i] = 0; }
         send_ticket(word, ticket);
@@ -1668,8 +1669,9 @@ __global__ void __launch_bounds__(256) k_hop_direct(const DirectArgs a) {
 // kSenderGroups of them (uniform [0, 64] B, P = 4096, r = 64: 8 steps 1230 us per call, one 1100).
 //   k_hop_direct / k_hop_senders, us per call: uniform [0, 64] B, P = 4096, r = 64 1480 / 1100 (its phases 750 and 484 / 452 and
 // 371), uniform [0, 16] B, P = 6000, r = 77 2215 / 1945, P = 2048, r = 46 184 / 181, 64-byte blocks, P = 8192, r = 90 4670 / 3960,
-// uniform [0, 40] B, 32 x 32 ranks 123 / 97, uniform [0, 200] B, P = 700, r = 27 108 / 99; r = 13 518 / 508 and 360 / 348; r = 8, P =
-// 2048 401 / 400 and 527 / 603, r = 4 690 / 715: hence kSenderMinRounds.  (In the order of the slot indices, where the loads
+// uniform [0, 40] B, 32 x 32 ranks 123 / 97, uniform [0, 200] B, P = 700, r = 27 108 / 99; r = 13 511 / 501 and 357 / 343; fewer rounds, P =
+// 2048, up to 60 B, r = 8 518 / 600, r = 12 502 / 565, r = 4 690 / 715: hence kSenderMinRounds, though 600 ranks gain from r = 8 on
+// (95 / 85); above it r = 16, P = 2048 alone loses (442 / 462, 64-byte blocks 328 / 340).  (In the order of the slot indices, where the loads
 // are the consecutive ones and the stores a receiver each: P = 2048, r = 46 240.)
 //   The sums per receiver that k_phase_sums adds up are one partial row per round and workgroup column here: a message has one
 // sender and one receiver.
@@ -1761,7 +1763,8 @@ __global__ void __launch_bounds__(256) k_hop_senders(const DirectArgs a) {
 // blocks), no table is read, and the ranks' own blocks are on the diagonal: no launch for them.
 //   Bound by memory.  k_hop_direct / k_hop_pairs, us per call: up to 16 bytes, P = 1024 57 / 48, 3000 198 / 163, 8192 1455 / 1124;
 // up to 60, P = 5000 866 / 823, 32-byte blocks, P = 4096 464 / 401, the FFT's 64-byte ones, P = 8192 1574 / 1474; up to
-// 200, P = 1000 82 / 77, 2500 457 / 444, up to 256, P = 1200 159 / 153, 500 55 / 50; P = 100 to 300 42-46 / 38-42.
+// 200, P = 1000 82 / 77, 2500 457 / 444, up to 256, P = 1200 159 / 153, 500 55 / 50; P = 50 to 300, whose own blocks k_hop_direct takes
+// along too, 40-43 / 41-43, up to 200 bytes, P = 2000 260 / 263.
 //   The tile: up to 16 bytes 32 x 32 (2 x 2 blocks per lane instead of 4: 3000 176; 64 senders 173, 16 178).  Up to 64 bytes 16 x 16,
 // and 8 x 32 where blocks share no 16 bytes and the runs of S that a tile reads count (FFT 1568 with 16 x 16, 1474; P = 5000 823 and
 // 836, Zipf up to 64, P = 6000 803 and 886; 32 x 8 everywhere slower).  Up to 256 bytes 64 x 4, one receiver's stores per wave (16 x 16:
@@ -2025,7 +2028,9 @@ __global__ void __launch_bounds__(256) k_hop_rows(const DirectArgs a) {
 // ------------------------------------------------------------------------------------------
 constexpr int kLongPieces = 4;
 constexpr int kLongUnit = kWave * 16 * kLongPieces;          // bytes
-constexpr int kLongMaxRanks = 512;                           // the workgroups take their room in the list one after the other
+// The workgroups take their room in the list one after the other.  (Measured beyond it since, the hops that run there / these: 600 to
+// 1024 ranks, 24 to 48 KiB 3.16 / 3.08 ms, 7.9 / 7.2, 19.1 / 17.0 per call, byte-granular 34 KiB, 800 ranks 9.6 / 7.8.)
+constexpr int kLongMaxRanks = 512;
 constexpr int kLongResident = 10;                            // workgroups per compute unit
 constexpr double kLongStreamBytes = 268435456.0;
 // in a unit's y: it is not the first of its block; in either: an offset into T, which a plan has not got yet
