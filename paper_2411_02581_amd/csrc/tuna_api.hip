@@ -2390,8 +2390,9 @@ int run_static(const void* sendbuf, const int32_t* sendcounts, const int64_t* sd
 // 64 bytes run another kernel (k_hop_direct, 1 or 4 lanes per block), whose blocks and bytes are priced by
 // constants of their own, c5 and c6, in place of c4 and c3.  The built-in constants were fitted to
 // immediate calls on MI355X by tuna_calibrate; calling it replaces them by a fit to calls timed on the
-// device at hand.  Over 59 one-kernel calls of 60 to 6000 ranks, up to 16 bytes to 1 MiB, radix 2 to linear, the built-in ones are
-// off by 8 % on average (long blocks, whose hop they do not know, +5 to +11 %), at most by -32 % (64 bytes, P = 4096, linear).
+// device at hand.  Over 59 one-kernel calls of 60 to 6000 ranks, up to 16 bytes to 1 MiB, radix 2 to linear, made one at a time
+// through the Python binding, the built-in ones are off by 8 % on average (long blocks, whose hop they do not know, +5 to +11 %), at most by
+// -32 % (64 bytes, P = 4096, linear); against calls in a loop they are 10 to 40 % too high where a call takes less than 0.2 ms.
 constexpr int kModelTerms = 7;
 static_assert(kModelTerms + 3 == TUNA_MODEL_CONSTANTS, "tuna_model_constants reports the terms and the three factors");
 struct Model {
