@@ -201,6 +201,57 @@ def case_routes(t, problems, plan):
     return out
 
 
+def case_sequence(t, seed, steps):
+    """Random operations on two contexts and three streams; kernels of immediate calls that are not behind every earlier call of
+    their context, and copies whose source was overwritten."""
+    rng = np.random.default_rng(seed)
+    big = _engine_counts(100)
+    big[big > 0] += 8000                                       # 64 MiB and more: metadata on a second stream, or two passes
+    kinds = {"short": (np.full((90, 90), 40), {}), "rows": (np.full((50, 50), 900), {"gap": 1}), "engine": (_engine_counts(64), {"gap": 1}),
+             "many phases": (_engine_counts(300), {}), "long": (np.full((24, 24), 50000), {}), "pipelined": (big, {"gap": 1})}
+    probs = {k: t.problem(c, **lay) for k, (c, lay) in kinds.items()}
+    nothing = t.problem(np.zeros((50, 50)))
+    wrong = t.problem(np.full((50, 50), 900))
+    wrong[0].sendcounts[1, 2] += 4
+    rc, other = t.b.tuna_ctx_create()
+    assert rc == 0
+    ends, plans, late, calls = {None: [], other: []}, [], [], 0
+    names = list(probs)
+    for step in range(steps):
+        ctx, s = (None, other)[rng.integers(2)], int(rng.choice([S1, S2, S3]))
+        what = rng.choice(["call"] * 4 + ["refused", "empty", "bad", "plan", "start", "start", "free", "query", "noalloc", "stats"])
+        kind, radix = names[rng.integers(len(names))], int(rng.choice([2, 3, 8, 14, 400]))
+        first = t.fake.fake_notes()
+        if what == "call":
+            calls += 1
+            mode = t.b.TUNA_MODE_STAGED if rng.random() < 0.2 else t.b.TUNA_MODE_FUSED
+            assert t.call(probs[kind], radix, s, ctx=ctx, mode=mode, t_layout=int(rng.integers(3)), profile=int(rng.random() < 0.2)) == 0
+            for i, k in enumerate(t.kernels(first)):
+                if not k[0].startswith("k_build"):             # (a new schedule's tables)
+                    late += [[step, kind, k[0]] for stream, upto in ends[ctx] if stream != k[1] and t.fake.fake_before(first + i, stream) < upto]
+            ends[ctx].append((s, t.fake.fake_length(s)))
+        elif what == "refused":
+            assert t.call(wrong, radix, s, ctx=ctx) == t.b.TUNA_ERR_COUNT_MISMATCH
+        elif what == "empty":
+            assert t.call(nothing, radix, s, ctx=ctx) == 0
+        elif what == "bad":
+            assert t.call((nothing[0], [None] * 6), radix, s, ctx=ctx) == t.b.TUNA_ERR_ARG
+        elif what == "plan":
+            prob = nothing if rng.random() < 0.2 else probs[kind]
+            plans.append(t.plan(prob, radix, s, ctx=ctx, t_layout=int(rng.integers(3)), profile=int(rng.random() < 0.5)))
+        elif what == "start" and plans:
+            assert t.lib.tuna_start(plans[rng.integers(len(plans))], s) == 0
+        elif what == "free" and plans and rng.random() < 0.3:  # (waits for the device)
+            assert t.lib.tuna_plan_free(plans.pop()) == 0
+        elif what == "query":
+            assert t.lib.tuna_workspace_bytes(probs[kind][1][1], probs[kind][0].P, 0, radix, radix, ctypes.byref(ctypes.c_size_t(0))) == 0
+        elif what == "noalloc":
+            assert t.lib.tuna_alltoallv_noalloc(*probs["short"][1], probs["short"][0].P, 0, radix, radix, s) == 0
+        elif what == "stats" and rng.random() < 0.2:           # (waits for the call)
+            assert t.lib.tuna_ctx_get_stats(ctx, ctypes.byref(t.b.tuna_stats_t())) == 0
+    return {"calls": calls, "late": late[:5], "violations": t.fake.fake_violations()}
+
+
 CASES = {k[5:]: f for k, f in list(globals().items()) if k.startswith("case_")}
 
 if __name__ == "__main__":

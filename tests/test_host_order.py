@@ -55,3 +55,10 @@ def test_a_plan_of_long_blocks_holds_one_list_of_units_per_phase(runtime, P, siz
 def test_no_schedule_is_kept_whose_tables_were_only_recorded(runtime, P, radix, plan):
     """In a capture that allows allocations the kernels that fill a new schedule's tables would not have run."""
     assert fake_hip.run(runtime, "recording", P, radix, plan) == {"refused": True, "tables": 1}
+
+
+@pytest.mark.parametrize("seed", range(12))
+def test_sequences_of_operations(runtime, seed):
+    """Every kernel of an immediate call, on whatever stream, is behind all earlier calls of its context."""
+    r = fake_hip.run(runtime, "sequence", seed, 120)
+    assert r["calls"] > 20 and r["late"] == [] and r["violations"] == 0
