@@ -36,7 +36,7 @@ constexpr size_t kTailSlack = 256;
 struct DevicePlan {
     PlanHost host;
     std::vector<SegDev> d_seg;
-    std::vector<int32_t*> d_seg_mem;
+    void* mem = nullptr;                 // the memory of everything below (nullptr: it lies in the static scratch)
     hipStream_t built_on = nullptr;      // stream the table kernels were enqueued on
     bool complete = false;               // known to be there (a later call has waited for kernels behind them)
     std::vector<int32_t*> d_zt;
@@ -46,7 +46,6 @@ struct DevicePlan {
     // for the launch shapes, the classes on the host
     std::vector<int32_t*> d_tord, d_tcls;
     std::vector<std::vector<int32_t>> tcls;   // per phase: {class id, first entry of tord, entries} per class
-    bool borrowed = false;               // the device memory belongs to someone else (static scratch)
 };
 
 // The classes that every phase stores into: {class id, first entry, blocks} of each that has any, as k_build_classes finds them.
@@ -110,7 +109,7 @@ struct Shared {
     bool ready = false;
     int device = -1;
     int num_cus = 256;
-    std::map<std::tuple<int, int, int, int, int>, DevicePlan> plans;
+    std::map<std::tuple<int, int, int, int, int, int>, DevicePlan> plans;
     int live_plans = 0;                 // persistent plans not yet freed (they point into `plans`)
     int live_contexts = 0;              // contexts made by tuna_ctx_create and not yet destroyed
     int last_hip_error = 0;
@@ -324,16 +323,33 @@ DataSizes data_sizes_for(const PlanHost& pl, long long M, unsigned long long tot
 }
 
 void free_device_plan(DevicePlan& dp) {
-    if (!dp.borrowed) {
-        for (auto* p : dp.d_seg_mem) (void)hipFree(p);
-        for (auto* p : dp.d_zt) (void)hipFree(p);
-        for (auto* p : dp.d_tord) (void)hipFree(p);
-        for (auto* p : dp.d_tcls) (void)hipFree(p);
-        if (dp.d_hm1) (void)hipFree(dp.d_hm1);
-        if (dp.d_mask) (void)hipFree(dp.d_mask);
+    if (dp.mem) (void)hipFree(dp.mem);
+    dp = DevicePlan{};
+}
+
+// Memory of a schedule's device tables (whose host part, tcls included, is there), and its carving.
+size_t table_bytes(const DevicePlan& dp) {
+    const size_t P = (size_t)dp.host.P;
+    size_t b = align_up(P * 4) + align_up(P * 8);
+    for (size_t i = 0; i < dp.host.phases.size(); ++i)
+        b += 8 * align_up((size_t)dp.host.phases[i].nseg * 4) + align_up(P * 4) + align_up(class_total(dp.tcls[i]) * 4 + 4) +
+             align_up(dp.tcls[i].size() * 4 + 4);
+    return b;
+}
+void carve_tables(Carver& cv, DevicePlan& dp) {
+    const size_t P = (size_t)dp.host.P;
+    for (size_t i = 0; i < dp.host.phases.size(); ++i) {
+        // field-major table: e[], z[], src[], dst[], srcph[], srcseg[], scls[], dcls[]
+        const size_t stride = align_up((size_t)dp.host.phases[i].nseg * 4) / 4;
+        int32_t* dm = cv.take<int32_t>(8 * stride);
+        dp.d_zt.push_back(cv.take<int32_t>(P));
+        dp.d_seg.push_back(SegDev{dm, dm + stride, dm + 2 * stride, dm + 3 * stride, dm + 4 * stride, dm + 5 * stride,
+                                  dm + 6 * stride, dm + 7 * stride});
+        dp.d_tord.push_back(cv.take<int32_t>(class_total(dp.tcls[i]) + 1));
+        dp.d_tcls.push_back(cv.take<int32_t>(dp.tcls[i].size() + 1));
     }
-    dp.d_seg_mem.clear(); dp.d_zt.clear(); dp.d_seg.clear(); dp.d_tord.clear(); dp.d_tcls.clear();
-    dp.d_hm1 = nullptr; dp.d_mask = nullptr;
+    dp.d_hm1 = cv.take<int32_t>(P);
+    dp.d_mask = cv.take<unsigned long long>(P);
 }
 
 // Launches the kernels that fill a schedule's device tables (d_seg to d_mask, whose memory is there), and clears n_zero words.
@@ -360,7 +376,7 @@ int launch_tables(const DevicePlan& dp, unsigned long long* zero, int n_zero, hi
     return TUNA_OK;
 }
 
-// Cached schedule of (P, Q, r_l, r_g, fused).  The host keeps scalars only; the per-phase tables are
+// Cached schedule of (P, Q, r_l, r_g, fused, by_index).  The host keeps scalars only; the per-phase tables are
 // built on the device by k_build_tables, on the caller's stream (the kernels that read them
 // are enqueued behind it).
 // Radices clamped the way make_plan clamps them.
@@ -372,11 +388,11 @@ void clamp_radices(int Q, int N, int rl, int rg, int* crl, int* crg) {
     if (N < 2) *crg = 2;
 }
 
-int get_plan(int P, int Q, int rl, int rg, bool fused, hipStream_t s, DevicePlan** out) {
+int get_plan(int P, int Q, int rl, int rg, bool fused, bool by_index, hipStream_t s, DevicePlan** out) {
     const int N = P / Q;
     int crl, crg;
     clamp_radices(Q, N, rl, rg, &crl, &crg);
-    auto key = std::make_tuple(P, Q, crl, crg, fused ? 1 : 0);
+    auto key = std::make_tuple(P, Q, crl, crg, fused ? 1 : 0, by_index ? 1 : 0);
     auto it = sh.plans.find(key);
     if (it == sh.plans.end()) {
         // kernels that a stream only records would leave a cached schedule without tables
@@ -384,35 +400,18 @@ int get_plan(int P, int Q, int rl, int rg, bool fused, hipStream_t s, DevicePlan
         if (hipStreamIsCapturing(s, &recording) != hipSuccess) (void)hipGetLastError();
         if (recording != hipStreamCaptureStatusNone) { sh.last_hip_error = (int)hipErrorStreamCaptureUnsupported; return TUNA_ERR_HIP; }
         DevicePlan dp;
-        dp.host = make_plan(P, Q, crl, crg, fused, /*with_tables=*/false);
+        dp.host = make_plan(P, Q, crl, crg, fused, /*with_tables=*/false, by_index);
         if ((int)dp.host.phases.size() > TUNA_MAX_PHASES) return TUNA_ERR_TOO_LARGE;
         // a schedule that cannot be completed leaves nothing behind (its kernels may be in flight: wait)
         struct Guard {
             DevicePlan* dp; hipStream_t s;
             ~Guard() { if (dp) { (void)hipStreamSynchronize(s); free_device_plan(*dp); } }
         } guard{&dp, s};
-        for (auto& ph : dp.host.phases) {
-            // field-major table: e[], z[], src[], dst[], srcph[], srcseg[]
-            const size_t stride = align_up((size_t)ph.nseg * 4) / 4;
-            int32_t* dm = nullptr;
-            int32_t* dz = nullptr;
-            HIPCHK(hipMalloc((void**)&dm, 8 * stride * 4 + kAlign));
-            dp.d_seg_mem.push_back(dm);
-            HIPCHK(hipMalloc((void**)&dz, align_up((size_t)P * 4)));
-            dp.d_zt.push_back(dz);
-            dp.d_seg.push_back(SegDev{dm, dm + stride, dm + 2 * stride, dm + 3 * stride, dm + 4 * stride, dm + 5 * stride,
-                                      dm + 6 * stride, dm + 7 * stride});
-        }
-        HIPCHK(hipMalloc((void**)&dp.d_hm1, align_up((size_t)P * 4)));
-        HIPCHK(hipMalloc((void**)&dp.d_mask, align_up((size_t)P * 8)));
         class_sizes(dp.host, dp.tcls);
-        for (size_t i = 0; i < dp.host.phases.size(); ++i) {
-            int32_t *d_o = nullptr, *d_c = nullptr;
-            HIPCHK(hipMalloc((void**)&d_o, align_up(class_total(dp.tcls[i]) * 4 + 4)));
-            dp.d_tord.push_back(d_o);
-            HIPCHK(hipMalloc((void**)&d_c, align_up(dp.tcls[i].size() * 4 + 4)));
-            dp.d_tcls.push_back(d_c);
-        }
+        const size_t bytes = table_bytes(dp);
+        HIPCHK(hipMalloc(&dp.mem, bytes));
+        Carver cv(dp.mem, bytes);
+        carve_tables(cv, dp);
         if (const int rc = launch_tables(dp, nullptr, 0, s)) return rc;
         dp.built_on = s;
         guard.dp = nullptr;
@@ -647,7 +646,6 @@ struct Prepared {
     long long* d_cbase = nullptr;       // [classes]: where the host placed every class in T
     std::vector<long long> cbase;       // the same on the host
     unsigned long long t_chunks = 0;    // chunks of exact-size T as laid out
-    uint2* pairs = nullptr;             // first phase's T-bound blocks by segment (launch_t_places)
     HopDev hop{};                       // one-kernel phases of a one-pass call: the resolved addresses of the phase being run
     // the ranks' own blocks: moved by the copy engine when blocks can be large (see launch_self_copy)
     bool self_engine = false;
@@ -994,6 +992,18 @@ int prepare_sizes(Prepared& pr, int dense_option, hipStream_t s, Status& hs, boo
 // (measured on every workload of the benchmark: 2.0 to 2.6 times faster per call, less memory).
 bool mode_is_fused(const Options& o) { return o.mode != TUNA_MODE_STAGED; }
 
+// Segments in the order of their slot indices, where nothing needs a message's blocks together (batches of rounds, the three
+// stages) and T is in exact size.  Blocks that travel together then lie together in T whatever their digit was -- in message
+// order a phase's neighbours are the radix apart in T -- and so do their entries of the matrices and of the places in T.
+// Message order / this, per call: uniform [0, 16] B, P = 2048, r = 46 179 / 163 us, P = 1000, r = 4 146 / 135; up to 40 B, P = 2048, r = 8
+// 396 / 370; up to 250, P = 600, r = 4 153 / 145; up to 1 KiB, P = 2048, r = 45 1736 / 1703, P = 256, r = 4 99.2 / 97.1; 1 KiB, P = 1024, r = 8
+// 1340 / 1329; r = 2, the same order, 1.00; uniform [0, 64] B, P = 4096, r = 64 1176 / 1181; per start: up to 32 B, P = 1000, r = 10
+// 63.7 / 46.4, up to 80, r = 8 108.7 / 104.7.  Message order where it is the faster one: T in slots, whose places do not follow one
+// another (256-byte blocks, P = 2048 as 64 x 32, r = 16 1297 / 1316), and the copy engine's hop (Zipf sizes, per start, P = 200, r = 8
+// 48.7 / 51.4, P = 100, r = 10 20.5 / 22.0); their schedule is made when validation has told (not by the call that allocates nothing).
+int hop_kernels_of(const Prepared& pr);
+bool slot_order(bool fused, bool staggered, int block_count) { return fused && !staggered && block_count == 0; }
+
 int prepare_call(Ctx& c, const Options& opt, const void* sendbuf, const int32_t* sendcounts, const int64_t* sdispls,
                  void* recvbuf, const int32_t* recvcounts, const int64_t* rdispls, int P, int ranks_per_node, int rl,
                  int rg, hipStream_t s, Prepared& pr, Status& hs, bool* empty) {
@@ -1013,12 +1023,16 @@ int prepare_call(Ctx& c, const Options& opt, const void* sendbuf, const int32_t*
     // staggered inter-node schedule: one block per message, N - 1 node distances, straight from T
     pr.staggered = opt.staggered != 0 && N > 1;
     if (pr.staggered) rg = N;
-    rc = get_plan(P, Q, rl, rg, pr.fused, s, &pr.dp);
+    const bool by_index = slot_order(pr.fused, pr.staggered, opt.block_count);
+    rc = get_plan(P, Q, rl, rg, pr.fused, by_index, s, &pr.dp);
     if (rc != TUNA_OK) return rc;
     pr.sendbuf = sendbuf; pr.recvbuf = recvbuf; pr.sendcounts = sendcounts; pr.recvcounts = recvcounts;
     pr.sdispls = sdispls; pr.rdispls = rdispls;
     pr.block_count = opt.block_count;
-    return prepare_sizes(pr, opt.t_layout, s, hs, empty);
+    rc = prepare_sizes(pr, opt.t_layout, s, hs, empty);
+    if (rc != TUNA_OK || *empty || !by_index || pr.dp->host.slots == 0 || long_blocks(pr)) return rc;
+    if (pr.exact_t && !(hop_kernels_of(pr) & TUNA_HOP_ENGINE)) return rc;
+    return get_plan(P, Q, rl, rg, pr.fused, /*by_index=*/false, s, &pr.dp);
 }
 
 // Phases whose stores are mostly whole lines: the last one (all its blocks are final) when the blocks are mostly
@@ -1147,13 +1161,13 @@ ResolveArgs resolve_args(const Prepared& pr, size_t i, const int32_t* nxt, const
     ra.sendcounts = pr.sendcounts; ra.recvcounts = pr.recvcounts;
     ra.P = pr.P; ra.Q = pr.Q; ra.N = pr.N; ra.dim = ph.dim; ra.rx = (int)ph.rx;
     ra.rx1 = (int)std::min<int64_t>(ph.rx * ph.r, INT_MAX);
+    ra.near_s = ra.rx1 < kNearSendRadix ? 1 : 0;
     ra.S = (const unsigned char*)pr.sendbuf; ra.sdispls = pr.sdispls;
     ra.R = (unsigned char*)pr.recvbuf; ra.rdispls = pr.rdispls;
     ra.slots = pr.ds.slots; ra.slot_bytes = pr.ds.slot_bytes;
     ra.x = exact_t_of(pr, i);
     ra.hop = hop;
     ra.exact_sizes = small_blocks(pr) ? 1 : 0;
-    if (i == 0 && pr.pairs) { ra.pairs = pr.pairs; ra.pairs_ld = pr.hop.ld; }
     return ra;
 }
 
@@ -1604,16 +1618,12 @@ bool runs_direct(const Prepared& pr) {
 }
 
 // All the metadata of such a call: with exact-size T the places of the blocks that its phases store there.
-// The pairs lie in the hop arrays' destinations, which such a call does not use.
-constexpr int kPairsMinRadix = 16;          // neighbours 64 bytes apart and more
 // own: if given, the ranks' own blocks are moved by the same launch when there is one (*own = true).
 int launch_t_places(Prepared& pr, hipStream_t s, bool* own = nullptr) {
     if (!pr.exact_t) return TUNA_OK;
-    if (pr.dp->host.phases[0].r >= kPairsMinRadix && pr.hop.dst) pr.pairs = reinterpret_cast<uint2*>(pr.hop.dst);
     const PlanHost& pl = pr.dp->host;
     PlaceArgs a{};
     a.P = pr.P; a.Q = pr.Q; a.N = pr.N; a.sendcounts = pr.sendcounts; a.recvcounts = pr.recvcounts; a.x = exact_t_of(pr, 0);
-    a.pairs = pr.pairs; a.pairs_ld = pr.hop.ld;
     a.by_value = pr.cbase.size() <= kPlaceClasses ? 1 : 0;
     if (a.by_value) std::copy(pr.cbase.begin(), pr.cbase.end(), a.cbase);
     else if (const int rc = upload_cbase(pr, s)) return rc;
@@ -1782,7 +1792,7 @@ int run_tiny(Ctx& c, const void* sendbuf, const int32_t* sendcounts, const int64
     int rc = ensure_ctx(c);
     if (rc != TUNA_OK) return rc;
     DevicePlan* dp = nullptr;
-    rc = get_plan(P, Q, rl, rg, /*fused=*/true, s, &dp);
+    rc = get_plan(P, Q, rl, rg, /*fused=*/true, /*by_index=*/true, s, &dp);
     if (rc != TUNA_OK) return rc;
     const PlanHost& pl = dp->host;
     if ((int)pl.phases.size() > kTinyMaxPhases) return TUNA_OK;
@@ -2330,28 +2340,11 @@ int run_static(const void* sendbuf, const int32_t* sendcounts, const int64_t* sd
     int crl, crg;
     clamp_radices(Q, N, rl, rg, &crl, &crg);
     DevicePlan dp;
-    dp.host = make_plan(P, Q, crl, crg, pr.fused, /*with_tables=*/false);
+    dp.host = make_plan(P, Q, crl, crg, pr.fused, /*with_tables=*/false, slot_order(pr.fused, pr.staggered, pr.block_count));
     if ((int)dp.host.phases.size() > TUNA_MAX_PHASES) return TUNA_ERR_TOO_LARGE;
-    dp.borrowed = true;                       // nothing of it is freed: it all lies in the static array
     class_sizes(dp.host, dp.tcls);
-    size_t table_bytes = align_up((size_t)P * 4) + align_up((size_t)P * 8);
-    for (size_t i = 0; i < dp.host.phases.size(); ++i)
-        table_bytes += 8 * align_up((size_t)dp.host.phases[i].nseg * 4) + align_up((size_t)P * 4) +
-                       align_up(class_total(dp.tcls[i]) * 4 + 4) + align_up(dp.tcls[i].size() * 4 + 4);
-    if (cv.off + table_bytes > cv.cap) return TUNA_ERR_NOALLOC_LIMIT;     // before any kernel is launched
-    for (size_t i = 0; i < dp.host.phases.size(); ++i) {
-        const PhaseHost& ph = dp.host.phases[i];
-        const size_t stride = align_up((size_t)ph.nseg * 4) / 4;
-        int32_t* dm = cv.take<int32_t>(8 * stride);
-        int32_t* dz = cv.take<int32_t>(P);
-        dp.d_zt.push_back(dz);
-        dp.d_seg.push_back(SegDev{dm, dm + stride, dm + 2 * stride, dm + 3 * stride, dm + 4 * stride, dm + 5 * stride,
-                                  dm + 6 * stride, dm + 7 * stride});
-        dp.d_tord.push_back(cv.take<int32_t>(class_total(dp.tcls[i]) + 1));
-        dp.d_tcls.push_back(cv.take<int32_t>(dp.tcls[i].size() + 1));
-    }
-    dp.d_hm1 = cv.take<int32_t>(P);
-    dp.d_mask = cv.take<unsigned long long>(P);
+    if (cv.off + table_bytes(dp) > cv.cap) return TUNA_ERR_NOALLOC_LIMIT;     // before any kernel is launched
+    carve_tables(cv, dp);
     // the class sums that validation adds to are cleared on the way
     rc = launch_tables(dp, pr.sb.d_status->cls_chunks, class_count((int)dp.host.phases.size()), s);
     if (rc != TUNA_OK) return rc;
@@ -2558,9 +2551,11 @@ int calibrate(hipStream_t s) {
     const Problem lines = {2048, 256, {8, 2048, 0}};
     // tiny (fixed costs), many tiny blocks (per-block and per-entry costs), large blocks beyond the caches
     // (bytes), and a mix; S is 4 bytes off a multiple of 16, the usual alignment of float payloads
-    const Problem problems[] = {{32, 300, {2, 6, 32}}, {256, 516, {2, 16, 256}}, {1024, 20, {2, 32, 1024}}, {2048, 36, {8, 2048, 0}},
-                                {2048, 4, {2, 2048, 0}}, {1024, 60, {4, 1024, 0}},
-                                {512, 4100, {2, 23, 512}}, {2048, 260, {8, 2048, 0}}};
+    // (short blocks over many radices: what a phase of them costs goes with P^2 more than with the blocks that move, which the two
+    // constants have to share; radix 8 of blocks of up to 16 bytes came out 39 % too high with few of them, within 16 % now)
+    const Problem problems[] = {{32, 300, {2, 6, 32}}, {256, 516, {2, 16, 256}}, {1024, 20, {2, 32, 1024}}, {2048, 36, {46, 2048, 0}},
+                                {2048, 4, {2, 2048, 0}}, {2048, 8, {3, 8, 2048}}, {2048, 12, {2, 8, 46}}, {1024, 12, {4, 10, 32}},
+                                {1024, 60, {4, 1024, 0}}, {512, 4100, {2, 23, 512}}, {2048, 260, {8, 2048, 0}}};
     size_t max_entries = 0, max_bytes = 0;
     for (const Problem& pb : problems) {
         max_entries = std::max(max_entries, (size_t)pb.P * pb.P);
@@ -2824,7 +2819,7 @@ int tuna_workspace_bytes(const int32_t* sendcounts, int P, int ranks_per_node, i
     const bool fused = mode_is_fused(o);
     const bool staggered = o.staggered != 0 && N > 1;
     DevicePlan* dp = nullptr;
-    rc = get_plan(P, Q, local_radix, staggered ? N : global_radix, fused, nullptr, &dp);
+    rc = get_plan(P, Q, local_radix, staggered ? N : global_radix, fused, slot_order(fused, staggered, o.block_count), nullptr, &dp);
     if (rc != TUNA_OK) return rc;
     const PlanHost& pl = dp->host;
     rc = run_validate(g.sb, sendcounts, nullptr, nullptr, nullptr, P, nullptr, (o.t_layout != 0 && pl.slots > 0) ? dp : nullptr,
@@ -2991,7 +2986,7 @@ int tuna_plan_phase_device(int P, int ranks_per_node, int local_radix, int globa
     if (rc != TUNA_OK) return rc;
     if (sh.defaults.staggered && P / Q > 1) global_radix = P / Q;
     DevicePlan* dp = nullptr;
-    rc = get_plan(P, Q, local_radix, global_radix, query_fused(), nullptr, &dp);
+    rc = get_plan(P, Q, local_radix, global_radix, query_fused(), /*by_index=*/false, nullptr, &dp);
     if (rc != TUNA_OK) return rc;
     if (phase >= (int)dp->host.phases.size()) return TUNA_ERR_ARG;
     HIPCHK(hipDeviceSynchronize());
@@ -3025,7 +3020,7 @@ int tuna_plan_phase_sources(int P, int ranks_per_node, int local_radix, int glob
     if (rc != TUNA_OK) return rc;
     if (sh.defaults.staggered && P / Q > 1) global_radix = P / Q;
     DevicePlan* dp = nullptr;
-    rc = get_plan(P, Q, local_radix, global_radix, query_fused(), nullptr, &dp);
+    rc = get_plan(P, Q, local_radix, global_radix, query_fused(), /*by_index=*/false, nullptr, &dp);
     if (rc != TUNA_OK) return rc;
     if (phase >= (int)dp->host.phases.size()) return TUNA_ERR_ARG;
     HIPCHK(hipDeviceSynchronize());

@@ -82,7 +82,8 @@ struct ExactT {
     const long long* cbase;  // [classes]: first chunk of each class in T (from the host)
     long long* tbase;        // [classes][P]: first chunk in T of rank p's part of a class
     int* csub;               // [classes][P]: chunks of rank p's part of a class
-    int* tpos;               // [phases][P][P]: chunk offset, inside its rank's part of its class, of the block with slot index e that the phase stored
+    int* tpos;               // [phases][P][P]: chunk offset, inside its rank's part of its class, of every block that the phase stored: by segment
+                             // where phases find their blocks themselves (k_t_places), else by slot index
     int* tpre;               // [P][ld]: the same offsets for the phase being run, in message order
     int ld;
     int phase;               // index of the phase being run
@@ -1156,8 +1157,7 @@ struct ResolveArgs {
     const int32_t* sendcounts;          // block sizes for the kernels that find their blocks themselves (block_bytes)
     const int32_t* recvcounts;
     int rx1;                            // r^(x+1) of the phase
-    const uint2* pairs;                 // first phase of a schedule with exact-size T: [P][pairs_ld] by segment, the T-bound blocks' chunk offset and bytes
-    int pairs_ld;
+    int near_s;                         // 1: the bytes of a block that never moved lie nearer in sendcounts (kNearSendRadix)
     SegDev seg;
     int nseg;
     int P, Q, N, dim, rx;
@@ -1314,7 +1314,11 @@ __device__ __forceinline__ void short_store(unsigned long long dst, unsigned lon
 // covered the digits up to x of its distance, so it comes from O = (n, g) + that part and is bound for D = O - (j, l)
 // (Algorithm "TuNA", line 14, without the exchange: in one memory every size can be looked up where the caller wrote
 // it).  The entry of recvcounts is the nearer one where neighbouring blocks have one destination (final blocks, and
-// all later phases: runs of r^(x+1) blocks), that of sendcounts where they have one origin (never moved before).
+// all later phases: runs of r^(x+1) blocks), that of sendcounts where they have one origin: blocks that never moved before, to
+// one sender's k_hop_senders, and to one receiver's kernels while r^(x+1) is below kNearSendRadix (runs of r^(x+1) in P / r^(x+1) rows of
+// recvcounts against r^x - 1 strided rows of sendcounts; sendcounts / recvcounts, us per call: up to 16 B, P = 2048, r = 8 283 / 275,
+// P = 1000, r = 4 131.5 / 129, up to 40, P = 2048, r = 8 386 / 380, normal 128 B, P = 4096, r = 16 3137 / 3089; k_hop_senders, P = 2048, r = 46 162 / 173).
+constexpr int kNearSendRadix = 8;
 __device__ __forceinline__ const int32_t* block_bytes(const int32_t* sendcounts, const int32_t* recvcounts, bool in_s, int n, int g, int j,
                                                       int l, int P, int Q, int N, int dim, int rx1) {
     int on = n, og = g + l;
@@ -1333,12 +1337,11 @@ __device__ __forceinline__ const int32_t* block_bytes(const int32_t* sendcounts,
 // phase stores into T, of all phases at once -- block sizes come from the caller's matrices (block_bytes), so no phase
 // waits for another's size exchange.  k_t_places: one workgroup per receiver and class scans the chunks of the class's
 // blocks in message order; the offsets inside the receiver's part go to tpos by slot index, the part's size to csub.
-// The neighbours of the first phase's message order are r apart in tpos and in the caller's rows: its offsets and sizes
-// are kept by segment too (pairs) when r is 16 or more: uniform [0, 64] B, P = 4096, r = 64 2.17 -> 1.74 ms per call; at
-// r = 4 and 8 they cost 1 %.
-// k_t_places_slots: the same in the order of the slot indices, for larger radices: consecutive slot indices of one round after
-// the other are consecutive entries of a row of recvcounts and of tpos, where the message order is a radix apart in both.
-// The sizes go through the LDS to be scanned in message order and back.  What bounds k_t_places then is the lines it touches
+// In the order of the segments, that is of the slot indices (slot_order).  A copy of the first phase's offsets and sizes by segment, which
+// paid in message order, costs now: P = 2048, r = 46 161 -> 182 us per call, uniform [0, 64] B, P = 4096, r = 64 1181 -> 1240.
+// k_t_places_slots: the same for larger radices, the sizes read for all slot indices in turn: consecutive ones of one round after
+// the other are consecutive entries of a row of recvcounts and of tpos.  They go through the LDS to be scanned
+// in the order of the segments and back.  What bounds k_t_places then is the lines it touches
 // (P = 2048, r = 46: 435 MB missed in the L2s, 73 us for 16 MB of sizes).  Per call, k_t_places / k_t_places_slots: uniform [0, 16]
 // B, P = 2048, r = 46 236 / 184 us; uniform [0, 64] B, P = 4096, r = 64 1.72 / 1.54 ms; uniform [0, 512] B, P = 2048, r = 46 1017 / 972
 // us; uniform [0, 16] B, P = 6000, r = 77 2.62 / 2.22 ms; 64-byte blocks, P = 8192, r = 90 5.19 / 4.67 ms; r = 16 255 / 252 us; r = 8 1767 /
@@ -1365,8 +1368,6 @@ struct PlaceArgs {
     const int32_t* sendcounts;
     const int32_t* recvcounts;
     ExactT x;
-    uint2* pairs;           // of the first phase (ResolveArgs)
-    int pairs_ld;
     int most;               // blocks of the largest class
     int own;                // workgroup row that moves the ranks' own blocks (own_block), or -1
     const unsigned char* S;
@@ -1394,25 +1395,21 @@ __global__ void __launch_bounds__(kScanThreads) k_t_places(const PlaceArgs a) {
     int* pos_t = a.x.tpos + ((size_t)ph.phase * P + p) * P;
     int carry = 0;
     for (int base = 0; base < cn; base += kScanThreads * kScanItems) {
-        int ct[kScanItems], se[kScanItems], sg[kScanItems], sz[kScanItems];
+        int ct[kScanItems], sg[kScanItems];
 #pragma unroll
         for (int k = 0; k < kScanItems; ++k) {
             const int i = base + scan_item_index(k);
             sg[k] = ph.tord[c0 + min(i, cn - 1)];
-            se[k] = ph.e[sg[k]];
             int j, l;
-            split_slot_index(se[k], a.Q, a.N, j, l);
-            sz[k] = *block_bytes(a.sendcounts, a.recvcounts, ph.src[sg[k]] < 0, pn, pg, j, l, P, a.Q, a.N, ph.dim, ph.rx1);
-            ct[k] = i < cn ? (sz[k] + 15) >> 4 : 0;
+            split_slot_index(ph.e[sg[k]], a.Q, a.N, j, l);
+            const int n = *block_bytes(a.sendcounts, a.recvcounts, ph.src[sg[k]] < 0, pn, pg, j, l, P, a.Q, a.N, ph.dim, ph.rx1);
+            ct[k] = i < cn ? (n + 15) >> 4 : 0;
         }
         int run[kScanItems];
         block_scan_batch(ct, run, carry, wsum);
 #pragma unroll
         for (int k = 0; k < kScanItems; ++k)
-            if (base + scan_item_index(k) < cn) {
-                pos_t[se[k]] = run[k];
-                if (ph.phase == 0 && a.pairs) a.pairs[(size_t)p * a.pairs_ld + sg[k]] = make_uint2((unsigned int)run[k], (unsigned int)sz[k]);
-            }
+            if (base + scan_item_index(k) < cn) pos_t[sg[k]] = run[k];
     }
     if (threadIdx.x == 0) a.x.csub[(size_t)cid * P + p] = carry;
 }
@@ -1420,7 +1417,7 @@ constexpr int kPlaceSlotRanks = 8192;       // 48 KiB of LDS
 constexpr int kPlaceSlotRadix = 8;
 // dynamic LDS: the blocks of the largest class (a.most), 4 bytes each, and 2 bytes per slot index
 __global__ void __launch_bounds__(kScanThreads) k_t_places_slots(const PlaceArgs a) {
-    extern __shared__ int s_val[];                       // by index inside the class: bytes, then the chunk offset
+    extern __shared__ int s_val[];                       // bytes by index inside the class
     __shared__ int wsum[kScanThreads / kWave];
     constexpr int kNone = 0xffff;
     unsigned short* s_at = reinterpret_cast<unsigned short*>(s_val + a.most);        // by slot index: the index inside the class
@@ -1452,30 +1449,23 @@ __global__ void __launch_bounds__(kScanThreads) k_t_places_slots(const PlaceArgs
             if (at[k] != kNone) s_val[at[k]] = sz[k];
     }
     __syncthreads();
+    int* pos_t = a.x.tpos + ((size_t)ph.phase * P + p) * P;
     int carry = 0;
     for (int base = 0; base < cn; base += kScanThreads * kScanItems) {
-        int ct[kScanItems], sz[kScanItems];
+        int ct[kScanItems], sg[kScanItems];
 #pragma unroll
         for (int k = 0; k < kScanItems; ++k) {
             const int i = base + scan_item_index(k);
-            sz[k] = i < cn ? s_val[i] : 0;
-            ct[k] = (sz[k] + 15) >> 4;
+            ct[k] = i < cn ? (s_val[i] + 15) >> 4 : 0;
+            sg[k] = ph.tord[c0 + min(i, cn - 1)];
         }
         int run[kScanItems];
         block_scan_batch(ct, run, carry, wsum);
 #pragma unroll
         for (int k = 0; k < kScanItems; ++k) {
             const int i = base + scan_item_index(k);
-            if (i >= cn) continue;
-            s_val[i] = run[k];
-            if (ph.phase == 0 && a.pairs) a.pairs[(size_t)p * a.pairs_ld + ph.tord[c0 + i]] = make_uint2((unsigned int)run[k], (unsigned int)sz[k]);
+            if (i < cn) pos_t[sg[k]] = run[k];
         }
-    }
-    __syncthreads();
-    int* pos_t = a.x.tpos + ((size_t)ph.phase * P + p) * P;
-    for (int e = threadIdx.x; e < P; e += kScanThreads) {
-        const int at = s_at[e];
-        if (at != kNone) pos_t[e] = s_val[at];
     }
     if (threadIdx.x == 0) a.x.csub[(size_t)cid * P + p] = carry;
 }
@@ -1598,7 +1588,7 @@ __global__ void __launch_bounds__(256) k_hop_direct(const DirectArgs a) {
             }
         } else {
             const int e = r.seg.e[s], dist = r.seg.z[s] * r.rx, ssrc = r.seg.src[s], sdst = r.seg.dst[s];
-            const int sph = DENSE ? r.seg.srcph[s] : 0, scl = DENSE ? r.seg.scls[s] : 0, dcl = DENSE ? r.seg.dcls[s] : 0;
+            const int sph = DENSE ? r.seg.srcph[s] : 0, sseg = DENSE ? r.seg.srcseg[s] : 0, scl = DENSE ? r.seg.scls[s] : 0, dcl = DENSE ? r.seg.dcls[s] : 0;
             const bool in_s = ssrc < 0, in_r = sdst < 0;  // read from S (never moved), stored into R (final)
             int j, l;
             split_slot_index(e, Q, N, j, l);
@@ -1617,14 +1607,13 @@ __global__ void __launch_bounds__(256) k_hop_direct(const DirectArgs a) {
                 int sn = pn + j; if (sn >= N) sn -= N;
                 int sg = pg + l; if (sg >= Q) sg -= Q;
                 const size_t at_s = (size_t)q[u] * P + dn * Q + dg, at_r = (size_t)p * P + sn * Q + sg;
-                const int32_t* pair = reinterpret_cast<const int32_t*>(r.pairs + (size_t)p * r.pairs_ld + s);
-                n[u] = *(in_r ? r.recvcounts + at_r : r.pairs ? pair + 1 : block_bytes(r.sendcounts, r.recvcounts, in_s, pn, pg, j, l, P, Q, N, r.dim, r.rx1));
+                n[u] = *(in_r ? r.recvcounts + at_r : block_bytes(r.sendcounts, r.recvcounts, in_s && r.near_s, pn, pg, j, l, P, Q, N, r.dim, r.rx1));
                 const int64_t* tbase = reinterpret_cast<const int64_t*>(r.x.tbase);
                 va[u] = *(in_s ? r.sdispls + at_s : (DENSE ? tbase + (size_t)scl * P + q[u] : r.sdispls));
                 vc[u] = *(in_r ? r.rdispls + at_r : (DENSE ? tbase + (size_t)dcl * P + p : r.rdispls));
                 if (DENSE) {
-                    vb[u] = *(in_s ? r.seg.e : r.x.tpos + ((size_t)sph * P + q[u]) * P + e);
-                    vd[u] = *(in_r ? r.seg.e : r.pairs ? pair : r.x.tpos + ((size_t)r.x.phase * P + p) * P + e);
+                    vb[u] = *(in_s ? r.seg.e : r.x.tpos + ((size_t)sph * P + q[u]) * P + sseg);
+                    vd[u] = *(in_r ? r.seg.e : r.x.tpos + ((size_t)r.x.phase * P + p) * P + s);
                 }
             }
 #pragma unroll
@@ -1695,7 +1684,7 @@ __global__ void __launch_bounds__(256) k_hop_senders(const DirectArgs a) {
         const int s = min(s0 + (int)threadIdx.x, r.nseg - 1);
         const bool in = s0 + (int)threadIdx.x < r.nseg;
         const int e = r.seg.e[s], z = r.seg.z[s], ssrc = r.seg.src[s], sdst = r.seg.dst[s], dist = z * r.rx;
-        const int sph = DENSE ? r.seg.srcph[s] : 0, scl = DENSE ? r.seg.scls[s] : 0, dcl = DENSE ? r.seg.dcls[s] : 0;
+        const int sph = DENSE ? r.seg.srcph[s] : 0, sseg = DENSE ? r.seg.srcseg[s] : 0, scl = DENSE ? r.seg.scls[s] : 0, dcl = DENSE ? r.seg.dcls[s] : 0;
         const bool in_s = ssrc < 0, in_r = sdst < 0;
         int j, l;
         split_slot_index(e, Q, N, j, l);
@@ -1716,14 +1705,13 @@ __global__ void __launch_bounds__(256) k_hop_senders(const DirectArgs a) {
             int sn = pn + j; if (sn >= N) sn -= N;
             int sg = pg + l; if (sg >= Q) sg -= Q;
             const size_t at_s = (size_t)q * P + dn * Q + dg, at_r = (size_t)p[u] * P + sn * Q + sg;
-            const int32_t* pair = reinterpret_cast<const int32_t*>(r.pairs + (size_t)p[u] * r.pairs_ld + s);
-            n[u] = *(in_r ? r.recvcounts + at_r : r.pairs ? pair + 1 : block_bytes(r.sendcounts, r.recvcounts, in_s, pn, pg, j, l, P, Q, N, r.dim, r.rx1));
+            n[u] = *(in_r ? r.recvcounts + at_r : block_bytes(r.sendcounts, r.recvcounts, in_s, pn, pg, j, l, P, Q, N, r.dim, r.rx1));
             const int64_t* tbase = reinterpret_cast<const int64_t*>(r.x.tbase);
             va[u] = *(in_s ? r.sdispls + at_s : (DENSE ? tbase + (size_t)scl * P + q : r.sdispls));
             vc[u] = *(in_r ? r.rdispls + at_r : (DENSE ? tbase + (size_t)dcl * P + p[u] : r.rdispls));
             if (DENSE) {
-                vb[u] = *(in_s ? r.seg.e : r.x.tpos + ((size_t)sph * P + q) * P + e);
-                vd[u] = *(in_r ? r.seg.e : r.pairs ? pair : r.x.tpos + ((size_t)r.x.phase * P + p[u]) * P + e);
+                vb[u] = *(in_s ? r.seg.e : r.x.tpos + ((size_t)sph * P + q) * P + sseg);
+                vd[u] = *(in_r ? r.seg.e : r.x.tpos + ((size_t)r.x.phase * P + p[u]) * P + s);
             }
         }
 #pragma unroll
@@ -1883,7 +1871,7 @@ __device__ __forceinline__ void find_block(const DirectArgs& a, int p, int s, un
     } else {
         const int P = r.P, Q = r.Q, N = r.N;
         const int e = r.seg.e[s], dist = r.seg.z[s] * r.rx, ssrc = r.seg.src[s], sdst = r.seg.dst[s];
-        const int sph = DENSE ? r.seg.srcph[s] : 0, scl = DENSE ? r.seg.scls[s] : 0, dcl = DENSE ? r.seg.dcls[s] : 0;
+        const int sph = DENSE ? r.seg.srcph[s] : 0, sseg = DENSE ? r.seg.srcseg[s] : 0, scl = DENSE ? r.seg.scls[s] : 0, dcl = DENSE ? r.seg.dcls[s] : 0;
         in_s = ssrc < 0;
         final = sdst < 0;
         int j, l, pn, pg, qn, qg;
@@ -1896,16 +1884,15 @@ __device__ __forceinline__ void find_block(const DirectArgs& a, int p, int s, un
         int sn = pn + j; if (sn >= N) sn -= N;
         int sg = pg + l; if (sg >= Q) sg -= Q;
         const size_t at_s = (size_t)q * P + dn * Q + dg, at_r = (size_t)p * P + sn * Q + sg;
-        const int32_t* pair = reinterpret_cast<const int32_t*>(r.pairs + (size_t)p * r.pairs_ld + s);
-        n = *(final ? r.recvcounts + at_r : r.pairs ? pair + 1 : block_bytes(r.sendcounts, r.recvcounts, in_s, pn, pg, j, l, P, Q, N, r.dim, r.rx1));
+        n = *(final ? r.recvcounts + at_r : block_bytes(r.sendcounts, r.recvcounts, in_s && r.near_s, pn, pg, j, l, P, Q, N, r.dim, r.rx1));
         exact = n;
         if (!final) n = (n + 15) & ~15;
         if (DENSE) {
             const int64_t* tbase = reinterpret_cast<const int64_t*>(r.x.tbase);
             const long long va = *(in_s ? r.sdispls + at_s : tbase + (size_t)scl * P + q);
             const long long vc = *(final ? r.rdispls + at_r : tbase + (size_t)dcl * P + p);
-            const int vb = *(in_s ? r.seg.e : r.x.tpos + ((size_t)sph * P + q) * P + e);
-            const int vd = *(final ? r.seg.e : r.pairs ? pair : r.x.tpos + ((size_t)r.x.phase * P + p) * P + e);
+            const int vb = *(in_s ? r.seg.e : r.x.tpos + ((size_t)sph * P + q) * P + sseg);
+            const int vd = *(final ? r.seg.e : r.x.tpos + ((size_t)r.x.phase * P + p) * P + s);
             src = in_s ? (unsigned long long)r.S + va : tb + ((unsigned long long)(va + vb) << 4);
             dst = final ? (unsigned long long)r.R + vc : tb + ((unsigned long long)(vc + vd) << 4);
         } else {

@@ -53,6 +53,7 @@ struct PlanScalars {
     long long global0;    // first T slot of the global phase
     long long slots1;     // slots of one copy of T
     int fused;
+    int by_index;         // 1: the segments of a phase lie in the order of their slot indices, not in message order
     int w_l;              // number of local phases (they come first in the phase list)
     int nph;              // number of phases
 };
@@ -142,6 +143,18 @@ TUNA_HD inline long long count_below_digit(const PhaseScalars& ph, int z) {
     return (long long)(z - 1) * full * ph.rx + whole * ph.rx + ((a >= 1 && a <= z - 1) ? b : 0);
 }
 
+// Number of slot indices below e whose blocks move in the phase: the position of slot index e among its segments in the order
+// of the slot indices.
+TUNA_HD inline int moving_below(const PlanScalars& pl, const PhaseScalars& ph, int e) {
+    const int j = e / pl.Q, l = e - j * pl.Q;
+    auto below = [&](long long c) -> long long {                      // coordinates below c whose digit is not zero
+        const long long part = c % ph.rx1;
+        return c - ((c / ph.rx1) * ph.rx + (part < ph.rx ? part : ph.rx));
+    };
+    if (ph.dim == 0) return (int)((long long)j * below(pl.Q) + below(l));
+    return (int)(below(j) * pl.Q + ((j / ph.rx) % ph.r ? l : 0));
+}
+
 // Hops a block with distance pair (j, l) has made before phase (dim, x): non-zero digits of l
 // below x (all of l's digits once the global phases run) plus non-zero digits of j below x.
 TUNA_HD inline int hops_before(const PlanScalars& pl, const PhaseScalars& ph, int j, int l) {
@@ -162,8 +175,8 @@ TUNA_HD inline int hops_before(const PlanScalars& pl, const PhaseScalars& ph, in
 //   otherwise a T slot: [0, B_l) own-node blocks by the paper's map t over l; then (N-1)(Q-1)
 //   slots for blocks of the other nodes' groups that moved locally (they wait for the global
 //   phase); then B_g super-slots of Q blocks for the global phase (map t over j).
-// Position of slot index e in a phase's message order and its digit value there (0 and -1 when the
-// block does not move in that phase).  Only dim, r, size, rx and rx1 of `ph` are used.
+// Position of slot index e in a phase's message order (by_index: in the order of the slot indices) and its digit value there
+// (0 and -1 when the block does not move in that phase).  Only dim, r, size, rx and rx1 of `ph` are used.
 TUNA_HD inline int slot_position(const PlanScalars& pl, const PhaseScalars& ph, int e, int* z_out) {
     const int Q = pl.Q;
     const int j = e / Q, l = e - j * Q;
@@ -171,6 +184,7 @@ TUNA_HD inline int slot_position(const PlanScalars& pl, const PhaseScalars& ph, 
     const int z = (int)((c / ph.rx) % ph.r);
     *z_out = z;
     if (z == 0) return -1;
+    if (pl.by_index) return moving_below(pl, ph, e);
     const long long rc = (c / ph.rx1) * ph.rx + (c % ph.rx);          // rank of c among those with digit z
     const long long mult = ph.dim == 0 ? pl.N : Q;
     const long long start = count_below_digit(ph, z) * mult;
@@ -254,7 +268,8 @@ inline PhaseScalars phase_scalars(const PhaseHost& ph) {
 // copy a block sits in is the parity of the number of hops it has made, which depends on its
 // index only -- it is folded into the slot numbers of the tables.
 // with_tables = false computes the scalars only (the device builds its own tables).
-inline PlanHost make_plan(int P, int Q, int rl, int rg, bool fused = false, bool with_tables = true) {
+// by_index = true: PlanScalars.
+inline PlanHost make_plan(int P, int Q, int rl, int rg, bool fused = false, bool with_tables = true, bool by_index = false) {
     PlanHost pl;
     pl.P = P; pl.Q = Q; pl.N = P / Q;
     const int N = pl.N;
@@ -273,6 +288,7 @@ inline PlanHost make_plan(int P, int Q, int rl, int rg, bool fused = false, bool
     sc.global0 = sc.foreign0 + (long long)(N - 1) * (Q - 1);
     sc.slots1 = sc.global0 + (long long)pl.B_g * Q;
     sc.fused = fused ? 1 : 0;
+    sc.by_index = by_index ? 1 : 0;
     sc.w_l = pl.w_l;
     sc.nph = pl.w_l + pl.w_g;
     pl.slots = fused ? 2 * sc.slots1 : sc.slots1;
