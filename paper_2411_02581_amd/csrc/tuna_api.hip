@@ -1172,20 +1172,22 @@ ResolveArgs resolve_args(const Prepared& pr, size_t i, const int32_t* nxt, const
 }
 
 template <int LPB, bool TALL, int STREAM>
-void launch_direct_as(const DirectArgs& a, dim3 grid, bool exact, hipStream_t s) {
+void launch_direct_as(const DirectArgs& a, dim3 grid, bool exact, bool senders, hipStream_t s) {
     if (!a.part) hipLaunchKernelGGL((k_hop_direct<LPB, TALL, STREAM, false, true>), grid, dim3(256), 0, s, a);
+    else if (senders && exact) hipLaunchKernelGGL((k_hop_senders<LPB, STREAM, true, TALL>), grid, dim3(256), 0, s, a);
+    else if (senders) hipLaunchKernelGGL((k_hop_senders<LPB, STREAM, false, TALL>), grid, dim3(256), 0, s, a);
     else if (exact) hipLaunchKernelGGL((k_hop_direct<LPB, TALL, STREAM, true, false>), grid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL((k_hop_direct<LPB, TALL, STREAM, false, false>), grid, dim3(256), 0, s, a);
 }
 template <bool TALL>
-void launch_direct_shape(int lpb, int gran, const DirectArgs& a, dim3 grid, bool exact, hipStream_t s) {
-    if (lpb == 1) launch_direct_as<1, TALL, 0>(a, grid, exact, s);
+void launch_direct_shape(int lpb, int gran, const DirectArgs& a, dim3 grid, bool exact, bool senders, hipStream_t s) {
+    if (lpb == 1) launch_direct_as<1, TALL, 0>(a, grid, exact, senders, s);
     else if (lpb == 4) {
-        if (gran >= 16) launch_direct_as<4, TALL, 1>(a, grid, exact, s);
-        else launch_direct_as<4, TALL, 0>(a, grid, exact, s);
-    } else if (gran == 128) launch_direct_as<16, TALL, 2>(a, grid, exact, s);
-    else if (gran == 16) launch_direct_as<16, TALL, 1>(a, grid, exact, s);
-    else launch_direct_as<16, TALL, 0>(a, grid, exact, s);
+        if (gran >= 16) launch_direct_as<4, TALL, 1>(a, grid, exact, senders, s);
+        else launch_direct_as<4, TALL, 0>(a, grid, exact, senders, s);
+    } else if (gran == 128) launch_direct_as<16, TALL, 2>(a, grid, exact, senders, s);
+    else if (gran == 16) launch_direct_as<16, TALL, 1>(a, grid, exact, senders, s);
+    else launch_direct_as<16, TALL, 0>(a, grid, exact, senders, s);
 }
 
 // Segments a wave of k_hop_rows takes, by the mean block.  Up to 600 bytes kRowsBytes of payload: sizes vary, and a wave whose
@@ -1199,9 +1201,12 @@ int rows_segs(const Prepared& pr) {
     return (int)std::min(std::max(8.0, pairs / 8192.0), mean <= 600.0 ? std::max(1.0, std::min(64.0, kRowsBytes / mean)) : rows_span(pr));
 }
 
+constexpr int kTallMinRounds = 7;
 int lanes_per_block(int64_t max_block) { return max_block <= 16 ? 1 : (max_block <= 64 ? 4 : 16); }
 int direct_lpb(const Prepared& pr) { return lanes_per_block(pr.max_count); }
-bool direct_tall(const PhaseHost& ph) { return (long long)ph.nz * 16 > ph.nseg; }
+// Tall tiles where a round has few blocks, and in the first phase of more than a few rounds (k_hop_senders; k_hop_direct, up to 16 B, P =
+// 2048, r = 8 274 / 267 us per call, up to 40 380 / 382, r = 4 664 / 664).
+bool direct_tall(const PhaseHost& ph) { return (long long)ph.nz * 16 > ph.nseg || (ph.dim == 0 && ph.rx == 1 && ph.nz >= kTallMinRounds); }
 // Workgroup columns and steps per workgroup over `nseg` segments of a phase: one step each while that gives no more than 8192 workgroups (four
 // per resident slot of the device), then up to 8 steps; and the rows of partial sums that such a launch stores.
 unsigned direct_columns(const Prepared& pr, const PhaseHost& ph, int nseg, int* iters) {
@@ -1212,19 +1217,11 @@ unsigned direct_columns(const Prepared& pr, const PhaseHost& ph, int nseg, int* 
     return (unsigned)((steps + *iters - 1) / *iters);
 }
 bool runs_direct(const Prepared& pr);
-// Phases of a schedule of several that an immediate call's k_hop_senders moves, and its workgroup columns and steps per workgroup
-// (as direct_columns); lpb: lanes per block.
-unsigned sender_columns(int P, const PhaseHost& ph, int lpb, int* iters) {
-    const int steps = (ph.nseg + 255) / 256;
-    *iters = std::max(1, std::min(steps, (int)((long long)steps * P / sender_sets(lpb) / kSenderGroups)));
-    return (unsigned)((steps + *iters - 1) / *iters);
+// Phases of a schedule of several that an immediate call's k_hop_senders moves: many rounds, and 256 blocks of a rank to each.
+bool by_senders(const PhaseHost& ph) {
+    return ph.nz >= kSenderMinRounds && ph.nz <= kSenderMaxRounds && (long long)((ph.nseg + 255) / 256) * ph.nz <= ph.nseg;
 }
-bool by_senders(int P, const PhaseHost& ph, int lpb) {
-    int iters = 0;
-    return ph.nz >= kSenderMinRounds && ph.nz <= kSenderMaxRounds &&
-           (long long)sender_columns(P, ph, lpb, &iters) * ph.nz <= ph.nseg;       // (rows of partial sums: no more than segments)
-}
-bool sender_phase(const Prepared& pr, const PhaseHost& ph) { return pr.dp->host.phases.size() > 1 && by_senders(pr.P, ph, direct_lpb(pr)); }
+bool sender_phase(const Prepared& pr, const PhaseHost& ph) { return pr.dp->host.phases.size() > 1 && by_senders(ph); }
 // The only phase of an immediate call's linear schedule, if its blocks are short: k_hop_pairs moves it, and the own blocks; its
 // workgroup columns and steps per workgroup (as direct_columns).
 bool pair_phase(const Prepared& pr) { return pr.dp->host.phases.size() == 1 && runs_direct(pr) && small_blocks(pr) && !long_blocks(pr); }
@@ -1258,34 +1255,9 @@ int launch_pairs(const Prepared& pr, uint2* part, hipStream_t s) {
 }
 unsigned direct_rows(const Prepared& pr, const PhaseHost& ph) {
     if (pair_phase(pr)) { int iters = 0; return pair_columns(pr, &iters); }
-    if (!row_blocks(pr) && sender_phase(pr, ph)) { int iters = 0; return sender_columns(pr.P, ph, direct_lpb(pr), &iters) * (unsigned)ph.nz; }
     if (row_blocks(pr)) { const int segs = rows_segs(pr); return (unsigned)((ph.nseg + segs - 1) / segs); }
     int iters = 0;
     return direct_columns(pr, ph, ph.nseg, &iters) * (unsigned)(4 / direct_shape(direct_lpb(pr), direct_tall(ph)).waves_r);
-}
-
-template <int LPB, int STREAM>
-void launch_senders_as(const DirectArgs& a, dim3 grid, bool exact, hipStream_t s) {
-    const size_t lds = ((size_t)a.nz + 1) * 8 * sender_sets(LPB);
-    if (exact) hipLaunchKernelGGL((k_hop_senders<LPB, STREAM, true>), grid, dim3(256), lds, s, a);
-    else hipLaunchKernelGGL((k_hop_senders<LPB, STREAM, false>), grid, dim3(256), lds, s, a);
-}
-int launch_senders(const Prepared& pr, size_t i, uint2* part, hipStream_t s) {
-    const PhaseHost& ph = pr.dp->host.phases[i];
-    DirectArgs a{};
-    a.r = resolve_args(pr, i, nullptr, HopDev{});
-    a.T = pr.T; a.part = part; a.nz = ph.nz;
-    const int lpb = direct_lpb(pr), sets = sender_sets(lpb);
-    const dim3 grid(sender_columns(pr.P, ph, lpb, &a.iters), (unsigned)((pr.P + sets - 1) / sets));
-    if (lpb == 1) launch_senders_as<1, 0>(a, grid, pr.exact_kernels, s);
-    else if (lpb == 4) {
-        if (pr.gran >= 16) launch_senders_as<4, 1>(a, grid, pr.exact_kernels, s);
-        else launch_senders_as<4, 0>(a, grid, pr.exact_kernels, s);
-    } else if (pr.gran == 128) launch_senders_as<16, 2>(a, grid, pr.exact_kernels, s);
-    else if (pr.gran == 16) launch_senders_as<16, 1>(a, grid, pr.exact_kernels, s);
-    else launch_senders_as<16, 0>(a, grid, pr.exact_kernels, s);
-    HIPCHK(hipGetLastError());
-    return TUNA_OK;
 }
 
 template <bool LINES>
@@ -1323,8 +1295,9 @@ int launch_direct(const Prepared& pr, size_t i, const HopDev& hop, int seg_lo, i
     const int lpb = direct_lpb(pr), ranks = direct_ranks(direct_shape(lpb, direct_tall(ph)));
     a.own = own ? (int)(((pr.P + kOwnRanks - 1) / kOwnRanks + cols - 1) / cols) : 0;
     const dim3 grid(cols, (unsigned)((pr.P + ranks - 1) / ranks + a.own));
-    if (direct_tall(ph)) launch_direct_shape<true>(lpb, pr.gran, a, grid, pr.exact_kernels, s);
-    else launch_direct_shape<false>(lpb, pr.gran, a, grid, pr.exact_kernels, s);
+    const bool senders = sender_phase(pr, ph);
+    if (direct_tall(ph)) launch_direct_shape<true>(lpb, pr.gran, a, grid, pr.exact_kernels, senders, s);
+    else launch_direct_shape<false>(lpb, pr.gran, a, grid, pr.exact_kernels, senders, s);
     HIPCHK(hipGetLastError());
     return TUNA_OK;
 }
@@ -1658,7 +1631,6 @@ int launch_direct_payload(const Prepared& pr, size_t i, uint2* part, bool own, h
     const PhaseHost& ph = pr.dp->host.phases[i];
     const int rc = row_blocks(pr)         ? launch_rows(pr, i, HopDev{}, part, own, s)
                    : pair_phase(pr)       ? launch_pairs(pr, part, s)
-                   : sender_phase(pr, ph) ? launch_senders(pr, i, part, s)
                                           : launch_direct(pr, i, HopDev{}, 0, ph.nseg, part, own, s);
     if (rc == TUNA_OK) mark(pr.ctx, s, kCatPack, (int)i);
     return rc;
@@ -2427,7 +2399,7 @@ Features features_of(const PlanHost& pl, double payload_bytes, bool fused, int64
     double moving = 0.0, by_sender = 0.0;
     for (const auto& ph : pl.phases) {
         moving += (double)ph.nseg * P;
-        if (by_senders(pl.P, ph, lanes_per_block(max_block))) by_sender += (double)ph.nseg * P;
+        if (by_senders(ph)) by_sender += (double)ph.nseg * P;
     }
     (small ? f.msmall : f.mblocks) = moving / 1e6;
     // A short block of a schedule of one phase is looked up in the receive counts and the displacements; with several

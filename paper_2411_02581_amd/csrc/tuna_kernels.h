@@ -1273,7 +1273,6 @@ struct DirectArgs {
     int segs;                           // segments per wave, at most 64 (k_hop_rows)
     unsigned long long user_limit;      // address one past the last byte of S that holds a block
     uint2* part;                        // [grid.x][P]: payload bytes and chunks of the tile column, per receiver (not when RESOLVED)
-    int nz;                             // rounds of the phase (k_hop_senders)
     int own;                            // so many rows of workgroups in front move the ranks' own blocks (k_hop_direct, k_hop_rows)
 };
 
@@ -1550,7 +1549,7 @@ __device__ __forceinline__ void own_short(const ResolveArgs& r, int p0) {
 }
 
 template <int LPB, bool TALL, int STREAM, bool DENSE, bool RESOLVED>
-__global__ void __launch_bounds__(256) k_hop_direct(const DirectArgs a) {
+__device__ __forceinline__ void hop_direct(const DirectArgs& a) {
     constexpr DirectShape SH = direct_shape(LPB, TALL);
     constexpr int SEGS = kWave / SH.wave_ranks;          // segments per wave and step
     constexpr int SETS = SH.sets;                        // blocks a lane resolves per step
@@ -1648,101 +1647,23 @@ __global__ void __launch_bounds__(256) k_hop_direct(const DirectArgs a) {
     }
 }
 
+template <int LPB, bool TALL, int STREAM, bool DENSE, bool RESOLVED>
+__global__ void __launch_bounds__(256) k_hop_direct(const DirectArgs a) { hop_direct<LPB, TALL, STREAM, DENSE, RESOLVED>(a); }
+
 // ------------------------------------------------------------------------------------------
-// k_hop_senders: k_hop_direct by senders instead of receivers, for phases of many rounds in schedules of several.  The blocks
-// that one rank sends in such a phase -- to nz receivers, in message order -- lie together, in its row of sdispls and of S
-// or in its part of T, and a workgroup takes the blocks of one rank (LPB = 1: of four): all the lines that are read are
-// read by one compute unit, whereas the blocks that one receiver gets are single ones of nz senders, a line each.  The
-// stores go out in runs of a message's blocks either way.
-//   Bound by memory and by the chain of three loads per step, hence a step per workgroup while that makes no more than
-// kSenderGroups of them (uniform [0, 64] B, P = 4096, r = 64: 8 steps 1230 us per call, one 1100).
-//   k_hop_direct / k_hop_senders, us per call: uniform [0, 64] B, P = 4096, r = 64 1480 / 1100 (its phases 750 and 484 / 452 and
-// 371), uniform [0, 16] B, P = 6000, r = 77 2215 / 1945, P = 2048, r = 46 184 / 181, 64-byte blocks, P = 8192, r = 90 4670 / 3960,
-// uniform [0, 40] B, 32 x 32 ranks 123 / 97, uniform [0, 200] B, P = 700, r = 27 108 / 99; r = 13 511 / 501 and 357 / 343; fewer rounds, P =
-// 2048, up to 60 B, r = 8 518 / 600, r = 12 502 / 565, r = 4 690 / 715: hence kSenderMinRounds, though 600 ranks gain from r = 8 on
-// (95 / 85); above it r = 16, P = 2048 alone loses (442 / 462, 64-byte blocks 328 / 340).  (In the order of the slot indices, where the loads
-// are the consecutive ones and the stores a receiver each: P = 2048, r = 46 240.)
-//   The sums per receiver that k_phase_sums adds up are one partial row per round and workgroup column here: a message has one
-// sender and one receiver.
+// k_hop_senders: k_hop_direct's work in phases of many rounds of schedules of several phases, in tiles whose blocks of one sender lie side
+// by side.  Many rounds have many senders, and with the segments in the order of the slot indices (slot_order) a phase's senders
+// change either from segment to segment -- the first phase, r^x = 1: neighbouring receivers then get neighbouring blocks of a sender, so
+// tiles are TALL, 16 receivers x 16 rounds = 31 senders with up to 16 blocks each, stored as 16 runs of T -- or after r^x
+// segments, and a row of one receiver's segments is a run of a sender's part of T and of R (direct_tall).
+//   Bound by memory, the lines of the matrices and of T's places above all.  Against workgroups that take the blocks that one rank sends
+// (its loads together, its stores a receiver each), us per call: uniform [0, 16] B, P = 2048, r = 46 162 / 148, P = 6000, r = 77 1796 / 1509,
+// P = 1024, r = 32 76.5 / 73; up to 64 B, P = 4096, r = 64 1203 / 1135, up to 60, P = 2048, r = 16 409 / 391, P = 1024, r = 32 93 / 95; up to 40, r = 13
+// 346 / 335; T in slots, 64-byte blocks, P = 4096, r = 64 1393 / 1198, r = 16 445 / 404, 16-byte ones, P = 2048, r = 46 220 / 187.
 // ------------------------------------------------------------------------------------------
-constexpr int kSenderMinRounds = 12, kSenderMaxRounds = 1024;         // (32 KiB of LDS)
-constexpr int kSenderGroups = 65536;
-constexpr int sender_sets(int lpb) { return lpb == 1 ? 4 : 1; }       // blocks a lane finds per step, of neighbouring senders
-template <int LPB, int STREAM, bool DENSE>
-__global__ void __launch_bounds__(256) k_hop_senders(const DirectArgs a) {
-    constexpr int SETS = sender_sets(LPB);
-    extern __shared__ unsigned long long s_sum[];        // [SETS][nz + 1] by round: payload bytes of the message, and its chunks << 32
-    __shared__ ShortLds<LPB> lds;
-    const ResolveArgs& r = a.r;
-    const int P = r.P, Q = r.Q, N = r.N, q0 = blockIdx.y * SETS, nzs = a.nz + 1;
-    const unsigned long long tb = (unsigned long long)a.T;
-    for (int z = threadIdx.x; z < SETS * nzs; z += 256) s_sum[z] = 0;
-    __syncthreads();
-    for (int it = 0; it < a.iters; ++it) {                // (the bound is the same for the whole workgroup)
-        const int s0 = (blockIdx.x * a.iters + it) * 256;
-        if (s0 >= r.nseg) break;
-        const int s = min(s0 + (int)threadIdx.x, r.nseg - 1);
-        const bool in = s0 + (int)threadIdx.x < r.nseg;
-        const int e = r.seg.e[s], z = r.seg.z[s], ssrc = r.seg.src[s], sdst = r.seg.dst[s], dist = z * r.rx;
-        const int sph = DENSE ? r.seg.srcph[s] : 0, sseg = DENSE ? r.seg.srcseg[s] : 0, scl = DENSE ? r.seg.scls[s] : 0, dcl = DENSE ? r.seg.dcls[s] : 0;
-        const bool in_s = ssrc < 0, in_r = sdst < 0;
-        int j, l;
-        split_slot_index(e, Q, N, j, l);
-        long long va[SETS], vc[SETS];
-        int vb[SETS], vd[SETS], n[SETS], p[SETS];
-        unsigned long long src[SETS], dst[SETS];
-#pragma unroll
-        for (int u = 0; u < SETS; ++u) {
-            const int q = min(q0 + u, P - 1);
-            int qn, qg;
-            split_slot_index(q, Q, N, qn, qg);
-            int pn = qn, pg = qg;
-            if (r.dim == 0) { pg -= dist; if (pg < 0) pg += Q; }
-            else { pn -= dist; if (pn < 0) pn += N; }
-            p[u] = pn * Q + pg;                              // the receiver
-            int dn = qn - j; if (dn < 0) dn += N;
-            int dg = qg - l; if (dg < 0) dg += Q;
-            int sn = pn + j; if (sn >= N) sn -= N;
-            int sg = pg + l; if (sg >= Q) sg -= Q;
-            const size_t at_s = (size_t)q * P + dn * Q + dg, at_r = (size_t)p[u] * P + sn * Q + sg;
-            n[u] = *(in_r ? r.recvcounts + at_r : block_bytes(r.sendcounts, r.recvcounts, in_s, pn, pg, j, l, P, Q, N, r.dim, r.rx1));
-            const int64_t* tbase = reinterpret_cast<const int64_t*>(r.x.tbase);
-            va[u] = *(in_s ? r.sdispls + at_s : (DENSE ? tbase + (size_t)scl * P + q : r.sdispls));
-            vc[u] = *(in_r ? r.rdispls + at_r : (DENSE ? tbase + (size_t)dcl * P + p[u] : r.rdispls));
-            if (DENSE) {
-                vb[u] = *(in_s ? r.seg.e : r.x.tpos + ((size_t)sph * P + q) * P + sseg);
-                vd[u] = *(in_r ? r.seg.e : r.x.tpos + ((size_t)r.x.phase * P + p[u]) * P + s);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < SETS; ++u) {
-            const int q = min(q0 + u, P - 1);
-            if (DENSE) {
-                src[u] = in_s ? (unsigned long long)r.S + va[u] : tb + ((unsigned long long)(va[u] + vb[u]) << 4);
-                dst[u] = in_r ? (unsigned long long)r.R + vc[u] : tb + ((unsigned long long)(vc[u] + vd[u]) << 4);
-            } else {
-                src[u] = in_s ? (unsigned long long)r.S + va[u] : tb + (unsigned long long)(((long long)q * r.slots + ssrc) * r.slot_bytes);
-                dst[u] = in_r ? (unsigned long long)r.R + vc[u] : tb + (unsigned long long)(((long long)p[u] * r.slots + sdst) * r.slot_bytes);
-            }
-            if (!in || q0 + u >= P) n[u] = 0;
-            n[u] = min(n[u], 16 * LPB);                      // validation has bounded it: nothing is cut here
-            if (n[u] > 0)
-                atomicAdd(&s_sum[u * nzs + z], (unsigned long long)n[u] | (unsigned long long)(((in_r ? (unsigned int)(dst[u] & 15ull) : 0u) + (unsigned int)n[u] + 15u) >> 4) << 32);
-        }
-        move_short<LPB, STREAM>(src, dst, n, (unsigned long long)r.seg.e, lds);
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < SETS * a.nz; i += 256) {
-        const int u = i / a.nz, z = 1 + i - u * a.nz, q = q0 + u;
-        if (q >= P) break;
-        int pn, pg;
-        split_slot_index(q, Q, N, pn, pg);
-        if (r.dim == 0) { pg -= z * r.rx; if (pg < 0) pg += Q; }
-        else { pn -= z * r.rx; if (pn < 0) pn += N; }
-        const unsigned long long v = s_sum[u * nzs + z];
-        a.part[((size_t)blockIdx.x * a.nz + z - 1) * P + pn * Q + pg] = make_uint2((unsigned int)v, (unsigned int)(v >> 32));
-    }
-}
+constexpr int kSenderMinRounds = 12, kSenderMaxRounds = 1024;
+template <int LPB, int STREAM, bool DENSE, bool TALL>
+__global__ void __launch_bounds__(256) k_hop_senders(const DirectArgs a) { hop_direct<LPB, TALL, STREAM, DENSE, false>(a); }
 
 // ------------------------------------------------------------------------------------------
 // k_hop_pairs: k_hop_direct for the only phase of a linear schedule, where every block goes from S to R in its only hop: a
