@@ -40,7 +40,6 @@ struct DevicePlan {
     hipStream_t built_on = nullptr;      // stream the table kernels were enqueued on
     bool complete = false;               // known to be there (a later call has waited for kernels behind them)
     std::vector<int32_t*> d_zt;
-    int32_t* d_hm1 = nullptr;            // [P]: hops - 1 of every slot index (how often the block is stored into T)
     unsigned long long* d_mask = nullptr; // [P]: phases in which the block with a slot index moves (move_mask)
     // exact-size T: per phase the T-bound segments grouped by class (see ExactT), on the device and,
     // for the launch shapes, the classes on the host
@@ -330,7 +329,7 @@ void free_device_plan(DevicePlan& dp) {
 // Memory of a schedule's device tables (whose host part, tcls included, is there), and its carving.
 size_t table_bytes(const DevicePlan& dp) {
     const size_t P = (size_t)dp.host.P;
-    size_t b = align_up(P * 4) + align_up(P * 8);
+    size_t b = align_up(P * 8);
     for (size_t i = 0; i < dp.host.phases.size(); ++i)
         b += 8 * align_up((size_t)dp.host.phases[i].nseg * 4) + align_up(P * 4) + align_up(class_total(dp.tcls[i]) * 4 + 4) +
              align_up(dp.tcls[i].size() * 4 + 4);
@@ -348,7 +347,6 @@ void carve_tables(Carver& cv, DevicePlan& dp) {
         dp.d_tord.push_back(cv.take<int32_t>(class_total(dp.tcls[i]) + 1));
         dp.d_tcls.push_back(cv.take<int32_t>(dp.tcls[i].size() + 1));
     }
-    dp.d_hm1 = cv.take<int32_t>(P);
     dp.d_mask = cv.take<unsigned long long>(P);
 }
 
@@ -357,7 +355,7 @@ int launch_tables(const DevicePlan& dp, unsigned long long* zero, int n_zero, hi
     const int nph = (int)dp.host.phases.size();
     for (int f = 0; f < std::max(nph, 1); f += kBuildPhases) {
         BuildArgs a{};
-        a.pl = dp.host.sc; a.first = f; a.hm1 = dp.d_hm1; a.mask = dp.d_mask; a.zero = zero; a.n_zero = f ? 0 : n_zero;
+        a.pl = dp.host.sc; a.first = f; a.mask = dp.d_mask; a.zero = zero; a.n_zero = f ? 0 : n_zero;
         const int n = std::min(kBuildPhases, nph - f);
         bool classes = false;
         for (int i = 0; i < n; ++i) {
@@ -561,7 +559,7 @@ int run_validate(const StatusBufs& sb, const int32_t* sendcounts, const int32_t*
     // every field of the status block a call reads is written by the call's own kernels: no clearing (the class sums, which
     // kernels add to, start at zero and are cleared as they are read)
     const size_t t = (size_t)((P + kValTile - 1) / kValTile);
-    const unsigned vgrid = (unsigned)(t * t < (size_t)sb.num_cus * 8 ? t * t : (size_t)sb.num_cus * 8);
+    const unsigned vgrid = (unsigned)(t * t < (size_t)sb.num_cus * 2 ? t * t : (size_t)sb.num_cus * 2);
     // with a schedule that has T: also the size of every class of exact-size T (summed into the status block)
     const int nph = exact_t_for ? (int)exact_t_for->host.phases.size() : 0;
     const int ncls = class_count(nph);
@@ -574,24 +572,24 @@ int run_validate(const StatusBufs& sb, const int32_t* sendcounts, const int32_t*
         hipLaunchKernelGGL(k_zero64, dim3((unsigned)((ncls + 255) / 256)), dim3(256), 0, s, sb.d_status->cls_chunks, ncls);
         HIPCHK(hipGetLastError());
     }
-    const unsigned ny = t * t < (size_t)sb.num_cus * 2 ? 16 : 4;
-    const int copies = ncls <= 160 ? kValCopies : 1;         // 40 KiB of LDS; no schedule has more than 136
-    hipLaunchKernelGGL(k_validate, dim3(vgrid), dim3(kValTile, ny), (size_t)ncls * copies * 8, s, sendcounts, recvcounts, sdispls,
-                       rdispls, P, fold ? sb.h_part_dev : sb.d_vpart, exact_t_for ? exact_t_for->d_hm1 : nullptr,
-                       exact_t_for ? exact_t_for->host.Q : 1, exact_t_for ? exact_t_for->host.N : 1,
-                       exact_t_for ? exact_t_for->d_mask : nullptr, nph, sb.d_status, fold ? ticket : 0ull, copies, clear_totals ? 1 : 0);
+    const int copies = ncls <= 104 ? kValCopies : ncls <= 208 ? kValCopies / 2 : 1;         // at most 26 KiB of LDS beside the tiles'; no schedule has more than 136
+    const bool whole = recvcounts != nullptr;
+    hipLaunchKernelGGL(whole ? k_validate<true> : k_validate<false>, dim3(vgrid), dim3(kValTile, kValRows), (size_t)ncls * copies * 8, s, sendcounts,
+                       recvcounts, sdispls, rdispls, P, fold ? sb.h_part_dev : sb.d_vpart, copies, exact_t_for ? exact_t_for->host.Q : 1,
+                       exact_t_for ? exact_t_for->host.N : 1, exact_t_for ? exact_t_for->d_mask : nullptr, nph, sb.d_status, fold ? ticket : 0ull,
+                       clear_totals ? 1 : 0);
     HIPCHK(hipGetLastError());
     if (fold) {
         Status& h = *sb.h_status;
         unsigned long long fa = 0, m = 0;
-        h.total_bytes = h.total_chunks = h.send_extent = h.t_chunks = h.short_blocks = h.windows = 0;
+        h.total_bytes = h.total_chunks = h.send_extent = h.short_blocks = h.windows = 0;
         for (int i = 0; i < ncls; ++i) h.cls_chunks[i] = 0;
         for (unsigned r = 0; r < vgrid; ++r) {
             const unsigned long long* o = sb.h_part + (size_t)r * kValRow;
             if (const int rc = wait_ticket(o + kValRow - 1, ticket, s)) return rc;
             fa |= o[0]; m = std::max(m, o[1]);
             h.total_bytes += o[2]; h.total_chunks += o[3]; h.send_extent = std::max(h.send_extent, o[4]);
-            h.t_chunks += o[5]; h.short_blocks += o[6]; h.windows = max_windows(h.windows, o[7]);
+            h.short_blocks += o[6]; h.windows = max_windows(h.windows, o[7]);
             for (int i = 0; i < ncls; ++i) h.cls_chunks[i] += o[kValPartial + i];
         }
         h.flags = (unsigned int)(fa >> 32); h.align_bits = (unsigned int)(fa & 127u); h.max_count = (int)m;

@@ -47,7 +47,7 @@ struct Status {
     unsigned long long total_bytes;    // sum of sendcounts
     unsigned long long total_chunks;   // sum of ceil(count / 16)
     unsigned long long send_extent;    // max over non-empty blocks of sdispls + count: bytes of sendbuf that hold blocks
-    unsigned long long t_chunks;       // exact-size T: chunks stored into T over all phases
+    unsigned long long reserved1;
     unsigned long long short_blocks;   // blocks of fewer than kShortBlockBytes bytes, empty ones included
     unsigned long long windows;        // with blocks of more than kWindowMinBytes: most bytes that one receiver gets from
                                        // kValTile aligned neighbouring senders (high half) and one sender sends to as many
@@ -139,6 +139,33 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
     return v;
 }
 
+// op over the values of a wave (LANES = 64), or of each row of 16 lanes (16), in its last lane: by lane moves of the vector unit,
+// no LDS.  The other lanes hold parts.
+template <int CTRL, int ROWS, class T> __device__ __forceinline__ T lane_move(T v, T none) {
+    static_assert(sizeof(T) == 4 || sizeof(T) == 8, "one or two registers");
+    if constexpr (sizeof(T) == 4) {
+        return (T)__builtin_amdgcn_update_dpp((int)none, (int)v, CTRL, ROWS, 0xf, false);
+    } else {
+        const unsigned int lo = (unsigned int)__builtin_amdgcn_update_dpp((int)(unsigned int)none, (int)(unsigned int)v, CTRL, ROWS, 0xf, false);
+        const unsigned int hi = (unsigned int)__builtin_amdgcn_update_dpp((int)(none >> 32), (int)(v >> 32), CTRL, ROWS, 0xf, false);
+        return (T)hi << 32 | lo;
+    }
+}
+template <int LANES, class T, class Op> __device__ __forceinline__ T last_lane(T v, T none, Op op) {
+    v = op(v, lane_move<0x111, 0xf>(v, none));            // from 1, 2, 4, 8 lanes below in the row
+    v = op(v, lane_move<0x112, 0xf>(v, none));
+    v = op(v, lane_move<0x114, 0xf>(v, none));
+    v = op(v, lane_move<0x118, 0xf>(v, none));
+    if (LANES == kWave) {
+        v = op(v, lane_move<0x142, 0xa>(v, none));        // the last lane of the row before to rows 1 and 3,
+        v = op(v, lane_move<0x143, 0xc>(v, none));        // of the first half to the second
+    }
+    return v;
+}
+struct AddOp { template <class T> __device__ T operator()(T a, T b) const { return a + b; } };
+struct MaxOp { template <class T> __device__ T operator()(T a, T b) const { return a > b ? a : b; } };
+struct OrOp { template <class T> __device__ T operator()(T a, T b) const { return a | b; } };
+
 // Sender of the message with digit value z that rank (n, g) receives in a phase: the rank at
 // distance +z*r^x in the phase's dimension (Algorithm "TuNA": recvrank = p + z r^x).
 __device__ __forceinline__ int partner_up(int n, int g, int Q, int N, int dim, int dist) {
@@ -166,13 +193,11 @@ struct BuildArgs {
     PlanScalars pl;
     BuildPhase ph[kBuildPhases];
     int first;              // index of ph[0] in the schedule
-    int32_t* hm1;
-    unsigned long long* mask;
+    unsigned long long* mask;           // move_mask of every slot index
     unsigned long long* zero;           // n_zero words to clear on the way
     int n_zero;
 };
-// grid (ceil(P / 256), phases); the first row also runs build_hops
-__device__ __forceinline__ void build_hops(const PlanScalars& pl, int e, int32_t* hm1, unsigned long long* mask);
+// grid (ceil(P / 256), phases); the first row also fills `mask`
 __global__ void __launch_bounds__(256) k_build_tables(const BuildArgs a) {
     const PlanScalars& pl = a.pl;
     const BuildPhase& b = a.ph[blockIdx.y];
@@ -180,7 +205,7 @@ __global__ void __launch_bounds__(256) k_build_tables(const BuildArgs a) {
     if (blockIdx.x == 0 && blockIdx.y == 0)
         for (int i = threadIdx.x; i < a.n_zero; i += blockDim.x) a.zero[i] = 0;
     if (e >= pl.P) return;
-    if (blockIdx.y == 0 && a.first == 0) build_hops(pl, e, a.hm1, a.mask);
+    if (blockIdx.y == 0 && a.first == 0) a.mask[e] = move_mask(pl, e);
     SegInfo s;
     int pos = 0;
     if (slot_entry(pl, b.ps, e, &s, &pos)) {
@@ -251,38 +276,27 @@ __global__ void __launch_bounds__(256) k_fill_uniform(int32_t* __restrict__ send
 }
 
 // ------------------------------------------------------------------------------------------
-// build_hops: hm1[e] = (hops of the block with slot index e) - 1, at least 0.  A block makes one
-// hop per non-zero digit of its distance pair (l in base r_l, j in base r_g) and is stored into T
-// after every hop but its last -- hm1[e] times.
-// ------------------------------------------------------------------------------------------
-__device__ __forceinline__ void build_hops(const PlanScalars& pl, int e, int32_t* hm1, unsigned long long* mask) {
-    mask[e] = move_mask(pl, e);
-    int j = e / pl.Q, l = e - j * pl.Q, hops = 0;
-    for (; l; l /= pl.rl) hops += (l % pl.rl) != 0;
-    for (; j; j /= pl.rg) hops += (j % pl.rg) != 0;
-    hm1[e] = hops > 1 ? hops - 1 : 0;
-}
-
-// ------------------------------------------------------------------------------------------
 // k_validate: one pass over the P x P matrices in 64 x 64 tiles.  Finds M (Algorithm "TuNA",
 // line 1: the maximum block size over all ranks, here one device reduction instead of an
 // allreduce), the totals the workspace is sized from, checks counts >= 0 and
 // recvcounts == transpose(sendcounts) through an LDS tile so both matrices are read row-wise
-// (a wave reads 64 consecutive entries of one row).  With `hm1` it also sums the exact size of T:
-// ceil(count / 16) * hm1[slot index of the block] chunks over all blocks.
-// A non-empty block with a negative displacement is flagged too.  Workgroups of (64, 4) threads
-// stride over the tiles and write one row of partial results each.
-// Bound by its reads (24 bytes per pair) at P = 4096 and by the chain of loads per tile below P = 1024: there workgroups
-// have 16 waves, so that a tile is one step of four rows per thread for either matrix instead of four steps (P = 256:
-// 19 -> 14 us, P = 1024 23 -> 19 us).  The class sums are LDS atomics on one of kValCopies copies per lane: neighbouring blocks mostly belong
+// (a wave reads 64 consecutive entries of one row).  With `mask` it also sums the chunks of every class of exact-size T.
+// A non-empty block with a negative displacement is flagged too.  Workgroups of (64, 16) threads, two per compute unit,
+// stride over the tiles and write one row of partial results each.  WHOLE: all four matrices; else sendcounts alone (a sizing query).
+// Bound by its reads (24 bytes per pair) from P = 4096 on and by latency below, so a tile is one step: a thread has its four rows of all four
+// matrices and of the masks in flight at once, and there is one barrier per tile (two buffers).  Against two steps with a barrier
+// behind each, and from 23 x 23 tiles on eight of four waves (us of the kernel): P = 256, r = 4 15.4 / 10.6, P = 1024 20.1 / 14.1, P =
+// 2048, r = 46 35.2 / 23.5, P = 4096 98 / 79 (5.1 TB/s), P = 8192 315 / 288; 4 us of the first for sums by lane moves instead of the LDS.
+// The class sums are LDS atomics on one of `copies` copies per lane: neighbouring blocks mostly belong
 // to one class, and on one copy a wave's additions queued up behind each other (P = 4096, r = 8: 159 -> 124 us).
 // With a ticket (few workgroups) the partial rows, class sums included, lie in pinned host memory, each ends with the
 // ticket, and the host waits for those and adds the rows up: no kernel to clear the sums, none to fold the rows, no copy of
 // the result (see run_validate; P = 256, r = 4 138 -> 117 us per call with the above).
-// The first two waves also sum the tile's columns and rows; the largest sums say whether long blocks lie side by side
+// The tile's columns and rows are summed too; the largest sums say whether long blocks lie side by side
 // (clustered).  Not before a block of more than kWindowMinBytes was seen: problems of shorter ones only do not ask.
 // ------------------------------------------------------------------------------------------
 constexpr int kValTile = 64;
+constexpr int kValRows = 16;                // waves of a workgroup
 constexpr int kValPartial = 8;              // 64-bit words per workgroup in the partial-result array
 constexpr int kValCopies = 32;
 constexpr int kValFoldRows = 64, kValFoldClasses = 24;      // most workgroups and classes that the host folds
@@ -302,192 +316,167 @@ __host__ __device__ inline unsigned long long max_windows(unsigned long long a, 
     const unsigned long long low = 0xffffffffull, ar = a >> 32, br = b >> 32, as = a & low, bs = b & low;
     return (ar > br ? ar : br) << 32 | (as > bs ? as : bs);
 }
-__global__ void __launch_bounds__(1024) k_validate(const int32_t* __restrict__ sendcounts,
-                                                   const int32_t* __restrict__ recvcounts,
-                                                   const int64_t* __restrict__ sdispls,
-                                                   const int64_t* __restrict__ rdispls,
-                                                   int P, unsigned long long* __restrict__ partial,
-                                                   const int32_t* __restrict__ hm1, int Q, int N,
-                                                   const unsigned long long* __restrict__ mask, int nph,
-                                                   Status* __restrict__ st, unsigned long long ticket, int copies, int clear_totals) {
-    __shared__ int tile[kValTile][kValTile + 1];
-    __shared__ unsigned long long red[16][8];
+template <bool WHOLE>
+__global__ void __launch_bounds__(kValTile * kValRows, 8) k_validate(const int32_t* __restrict__ sendcounts,
+                                                                     const int32_t* __restrict__ recvcounts,
+                                                                     const int64_t* __restrict__ sdispls,
+                                                                     const int64_t* __restrict__ rdispls,
+                                                                     int P, unsigned long long* __restrict__ partial, int copies,
+                                                                     int Q, int N, const unsigned long long* __restrict__ mask, int nph,
+                                                                     Status* __restrict__ st, unsigned long long ticket, int clear_totals) {
+    constexpr int kRows = kValTile / kValRows;            // rows of a tile per thread
+    __shared__ int tile[2][kValTile][kValTile + 1];
+    __shared__ unsigned int sums[2][2][kValTile];         // bytes per receiver, per sender of a tile
+    __shared__ unsigned long long red[kValRows][8];
     __shared__ int long_seen;
     extern __shared__ unsigned long long lcls[];          // class_count(nph) sums of this workgroup, `copies` of each (with `mask`)
-    const int tx = threadIdx.x, ty = threadIdx.y, ny = blockDim.y;
+    const int tx = threadIdx.x, ty = __builtin_amdgcn_readfirstlane(threadIdx.y);
     const int ncls = mask ? class_count(nph) : 0;
-    for (int i = ty * kValTile + tx; i < ncls * copies; i += ny * kValTile) lcls[i] = 0;
+    for (int i = ty * kValTile + tx; i < ncls * copies; i += kValRows * kValTile) lcls[i] = 0;
+    if (ty < 4) sums[ty >> 1][ty & 1][tx] = 0;
     if (tx == 0 && ty == 0) long_seen = 0;
     // the totals that k_phase_sums adds to, and the units that k_long_units counts (without a ticket k_validate_finish clears
     // them), not for a sizing query: the totals there belong to the context's last call.  First of all: right in front of the
     // ticket these stores cost a call 2 us
     if (ticket && clear_totals && blockIdx.x == 0 && ty == 0) st->phase_bytes[tx] = st->phase_chunks[tx] = st->phase_units[tx][0] = 0;
     __syncthreads();
-    unsigned int window = 0;                              // largest sum of a column (first wave) or row (second wave)
+    unsigned int window = 0;                              // largest sum of a receiver (first wave) or a sender (second wave)
     const int tpr = (P + kValTile - 1) / kValTile;       // tiles per row
     const int ntile = tpr * tpr;
     unsigned int flags = 0, abits = 0;
-    int mx = 0;
-    unsigned long long bytes = 0, chunks = 0, extent = 0, tchunks = 0, shortb = 0;
-    for (int t = blockIdx.x; t < ntile; t += gridDim.x) {        // a workgroup strides over tiles
+    int mx = 0, buf = 0;
+    unsigned long long bytes = 0, chunks = 0, extent = 0;
+    unsigned int shortb = 0;
+    for (int t = blockIdx.x; t < ntile; t += gridDim.x, buf ^= 1) {        // a workgroup strides over tiles
         const int bi = (t / tpr) * kValTile, bj = (t % tpr) * kValTile;
-        const int j = bj + tx;
-        const int jn = hm1 ? j / Q : 0, jg = hm1 ? j - jn * Q : 0;   // the destination's node and local id
-        // four rows per step, their loads issued together from clamped indices: with one row per step the pass
-        // was a chain of 32 dependent memory round trips per tile (48 us for 1024 ranks)
-        for (int a0 = ty; a0 < kValTile; a0 += 4 * ny) {
-            int cv[4];
-            long long dv[4];
-            bool ok[4];
+        const int j = bj + tx, i2 = bi + tx;              // the receiver of a row's entry of sendcounts, the sender of one of recvcounts
+        // every load of the tile, from clamped indices
+        int cv[kRows], rv[kRows];
+        long long dv[kRows], rd[kRows], rx = 0;
+        unsigned int mv[kRows];                           // (no more than 32 phases: fewer than 2^30 ranks)
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int i = bi + a0 + ny * u;
-                ok[u] = i < P && j < P;
-                const size_t idx = ok[u] ? (size_t)i * P + j : 0;
-                cv[u] = sendcounts[idx];
-                dv[u] = sdispls ? sdispls[idx] : 0;
-            }
+        for (int u = 0; u < kRows; ++u) {
+            const size_t at = (size_t)min(bi + ty + kValRows * u, P - 1) * P + min(j, P - 1);
+            cv[u] = sendcounts[at];
+            if (WHOLE) dv[u] = sdispls[at];
+        }
+        if (mask) {
+            const int jn = min(j, P - 1) / Q, jg = min(j, P - 1) - jn * Q;    // the destination's node and local id
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int a = a0 + ny * u;
-                const int i = bi + a;
-                int c = 0;
-                if (ok[u]) {
-                    c = cv[u];
-                    if (c < 0) { flags |= 1u; c = 0; }
-                    abits |= (unsigned int)c;
-                    if (sdispls) {
-                        const int64_t d = dv[u];
-                        abits |= (unsigned int)d & 127u;
-                        if (c > 0) {
-                            if (d >= 0) extent = max(extent, (unsigned long long)d + (unsigned long long)c);
-                            else flags |= 4u;
-                        }
-                    }
-                    mx = max(mx, c);
-                    bytes += (unsigned long long)c;
-                    shortb += c < kShortBlockBytes ? 1u : 0u;
-                    const unsigned long long ch = (unsigned long long)((c + 15) >> 4);
-                    chunks += ch;
-                    if (hm1 && c > 0) {
-                        const int in = i / Q, ig = i - in * Q;
-                        int dn = in - jn; if (dn < 0) dn += N;
-                        int dg = ig - jg; if (dg < 0) dg += Q;
-                        tchunks += ch * (unsigned long long)hm1[dn * Q + dg];
-                        if (mask) {
-                            // the block waits in T between every two consecutive phases in which it moves
-                            unsigned long long m = mask[dn * Q + dg];
-                            int f = __ffsll((long long)m) - 1;
-                            m &= m - 1;
-                            while (m) {
-                                const int y = __ffsll((long long)m) - 1;
-                                m &= m - 1;
-                                atomicAdd(&lcls[class_id(f, y, nph) * copies + (tx & (copies - 1))], ch);
-                                f = y;
-                            }
-                        }
-                    }
-                }
-                tile[a][tx] = c;
+            for (int u = 0; u < kRows; ++u) {
+                const int i = min(bi + ty + kValRows * u, P - 1), in = i / Q;
+                int dn = in - jn; if (dn < 0) dn += N;
+                int dg = i - in * Q - jg; if (dg < 0) dg += Q;
+                mv[u] = (unsigned int)mask[dn * Q + dg];
             }
         }
+        if (WHOLE) {
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) {
+                const size_t at = (size_t)min(bj + ty + kValRows * u, P - 1) * P + min(i2, P - 1);
+                rv[u] = recvcounts[at];
+                rd[u] = rdispls[at];
+            }
+            // what the last lane of row u has behind it, in the lanes u, u + kRows, ...
+            rx = rdispls[(size_t)min(bj + ty + kValRows * (tx & (kRows - 1)), P - 1) * P + min(bi + kValTile, P - 1)];
+        }
+        unsigned int to = 0;                              // bytes that this thread's senders have for receiver j
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) {
+            const int a = ty + kValRows * u;
+            int c = 0;
+            if (bi + a < P && j < P) {
+                c = cv[u];
+                if (c < 0) { flags |= 1u; c = 0; }
+                abits |= (unsigned int)c;
+                if (WHOLE) {
+                    abits |= (unsigned int)dv[u] & 127u;
+                    if (c > 0) {
+                        if (dv[u] >= 0) extent = max(extent, (unsigned long long)dv[u] + (unsigned long long)c);
+                        else flags |= 4u;
+                    }
+                }
+                mx = max(mx, c);
+                bytes += (unsigned long long)c;
+                shortb += c < kShortBlockBytes ? 1u : 0u;
+                const unsigned long long ch = (unsigned long long)((c + 15) >> 4);
+                chunks += ch;
+                if (mask && c > 0) {
+                    // the block waits in T between every two consecutive phases in which it moves
+                    unsigned int m = mv[u];
+                    int f = __ffs((int)m) - 1;
+                    m &= m - 1;
+                    while (m) {
+                        const int y = __ffs((int)m) - 1;
+                        m &= m - 1;
+                        atomicAdd(&lcls[class_id(f, y, nph) * copies + (tx & (copies - 1))], ch);
+                        f = y;
+                    }
+                }
+            }
+            to += (unsigned int)min(c, kWindowBlock);
+            tile[buf][a][tx] = c;
+        }
+        if (!WHOLE) continue;
         if (mx > kWindowMinBytes) long_seen = 1;
-        __syncthreads();
-        if (recvcounts) {
-            for (int a0 = ty; a0 < kValTile; a0 += 4 * ny) {
-                int rv[4];
-                long long dv[4], dx[4];
-                bool in[4];
+        __syncthreads();                                  // the only one per tile: the next one's entries go to the other buffer
+        unsigned int from = 0;                            // bytes that sender i2 has for this thread's receivers
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int jr = bj + a0 + ny * u, i = bi + tx;     // recvcounts[jr][i] must equal sendcounts[i][jr]
-                    in[u] = i < P && jr < P;
-                    const size_t idx = in[u] ? (size_t)jr * P + i : 0;
-                    rv[u] = recvcounts[idx];
-                    dv[u] = rdispls ? rdispls[idx] : 0;
-                    // the last lane of a row reads its successor's displacement itself (below)
-                    dx[u] = (rdispls && tx == kValTile - 1 && in[u] && i + 1 < P) ? rdispls[idx + 1] : 0;
-                }
-                if (a0 == ty && ty < 2 && long_seen) {    // under the first loads: bytes of receiver bj + tx, of sender bi + tx
-                    const int* entry = ty == 0 ? &tile[0][tx] : &tile[tx][0];
-                    const int step = ty == 0 ? kValTile + 1 : 1;
-                    unsigned int sum = 0;
-#pragma unroll 16
-                    for (int a = 0; a < kValTile; ++a) sum += (unsigned int)min(entry[a * step], kWindowBlock);
-                    window = max(window, sum);
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int a = a0 + ny * u;
-                    const int i = bi + tx;
-                    int rc = 0;
-                    long long d = 0;
-                    if (in[u]) {
-                        rc = rv[u];
-                        if (rc < 0) flags |= 1u;
-                        else if (rc != tile[tx][a]) flags |= 2u;
-                        if (rdispls) {
-                            d = dv[u];
-                            abits |= (unsigned int)d & 127u;
-                            if (rc > 0 && d < 0) flags |= 4u;
-                        }
-                    }
-                    if (rdispls) {
-                        // dense receive regions: every block starts where its predecessor in source order ends
-                        // (flag 8 when not; the destination-tiled hop needs it).  A wave holds 64
-                        // neighbours of one row.
-                        long long dn = __shfl_down(d, 1, kWave);
-                        if (tx == kValTile - 1) dn = dx[u];
-                        if (in[u] && i + 1 < P && dn != d + (long long)max(rc, 0)) flags |= 8u;
-                    }
-                }
+        for (int u = 0; u < kRows; ++u) {
+            const int a = ty + kValRows * u;
+            const int c = tile[buf][tx][a];
+            from += (unsigned int)min(c, kWindowBlock);
+            const bool in = bj + a < P && i2 < P;
+            if (in) {
+                if (rv[u] < 0) flags |= 1u;
+                else if (rv[u] != c) flags |= 2u;         // recvcounts[jr][i] must equal sendcounts[i][jr]
+                abits |= (unsigned int)rd[u] & 127u;
+                if (rv[u] > 0 && rd[u] < 0) flags |= 4u;
             }
+            // dense receive regions: every block starts where its predecessor in source order ends (flag 8 when not; the
+            // destination-tiled hop needs it).  A wave holds 64 neighbours of one row.
+            long long dn = __shfl_down(rd[u], 1, kWave);
+            const long long behind = __shfl(rx, u, kWave);
+            if (tx == kValTile - 1) dn = behind;
+            if (in && i2 + 1 < P && dn != rd[u] + (long long)max(rv[u], 0)) flags |= 8u;
         }
-        __syncthreads();
+        if (long_seen) {                                  // windows of neighbouring blocks
+            atomicAdd(&sums[buf][0][tx], to);
+            atomicAdd(&sums[buf][1][tx], from);
+        }
+        // the sums of the tile before, which every wave added to in front of the barrier above
+        if (ty < 2) { window = max(window, sums[buf ^ 1][ty][tx]); sums[buf ^ 1][ty][tx] = 0; }
     }
+    __syncthreads();
+    if (ty < 2) window = max(window, sums[buf ^ 1][ty][tx]);
     // wave reduction, workgroup reduction through LDS, then one row of partial results per workgroup
-#pragma unroll
-    for (int d = kWave / 2; d > 0; d >>= 1) {
-        flags |= __shfl_xor(flags, d, kWave);
-        abits |= __shfl_xor(abits, d, kWave);
-        mx = max(mx, __shfl_xor(mx, d, kWave));
-        bytes += __shfl_xor(bytes, d, kWave);
-        chunks += __shfl_xor(chunks, d, kWave);
-        tchunks += __shfl_xor(tchunks, d, kWave);
-        shortb += __shfl_xor(shortb, d, kWave);
-        extent = max(extent, (unsigned long long)__shfl_xor(extent, d, kWave));
-        window = max(window, __shfl_xor(window, d, kWave));
-    }
-    if (tx == 0) {                                       // one wave per value of ty
+    unsigned long long fa = last_lane<kWave>(flags << 8 | (abits & 127u), 0u, OrOp());
+    fa = fa >> 8 << 32 | (fa & 127u);
+    unsigned long long m = last_lane<kWave>((unsigned int)mx, 0u, MaxOp()), sb = last_lane<kWave>(shortb, 0u, AddOp());
+    unsigned long long by = last_lane<kWave>(bytes, 0ull, AddOp()), ch = last_lane<kWave>(chunks, 0ull, AddOp());
+    unsigned long long ex = last_lane<kWave>(extent, 0ull, MaxOp());
+    window = last_lane<kWave>(window, 0u, MaxOp());
+    if (tx == kWave - 1) {                               // one wave per value of ty
         unsigned long long* r = red[ty];
-        r[0] = ((unsigned long long)flags << 32) | (abits & 127u);
-        r[1] = (unsigned long long)mx; r[2] = bytes; r[3] = chunks; r[4] = extent; r[5] = tchunks; r[6] = shortb; r[7] = window;
+        r[0] = fa; r[1] = m; r[2] = by; r[3] = ch; r[4] = ex; r[6] = sb; r[7] = window;
     }
     __syncthreads();
     unsigned long long* o = partial + (size_t)blockIdx.x * (ticket ? kValRow : kValPartial);
-    if (ty == 0) {                                        // one lane per wave's row: sixteen rows one after the other took 1 us more
-        const unsigned long long* r = red[min(tx, ny - 1)];
-        const bool in = tx < ny;
-        unsigned long long fa = in ? r[0] : 0, m = in ? r[1] : 0, by = in ? r[2] : 0, ch = in ? r[3] : 0, ex = in ? r[4] : 0;
-        unsigned long long tc = in ? r[5] : 0, sb = in ? r[6] : 0;
+    if (ty == 0) {                                        // one lane per wave's row
+        static_assert(kValRows == 16, "a row of lanes");
+        const unsigned long long* r = red[tx & (kValRows - 1)];
         const unsigned long long wi = red[0][7] << 32 | red[1][7];
-#pragma unroll
-        for (int d = 8; d > 0; d >>= 1) {
-            fa |= __shfl_xor(fa, d, kWave);
-            m = max(m, (unsigned long long)__shfl_xor(m, d, kWave));
-            by += __shfl_xor(by, d, kWave);
-            ch += __shfl_xor(ch, d, kWave);
-            ex = max(ex, (unsigned long long)__shfl_xor(ex, d, kWave));
-            tc += __shfl_xor(tc, d, kWave);
-            sb += __shfl_xor(sb, d, kWave);
-        }
+        fa = last_lane<kValRows>(r[0], 0ull, OrOp()); m = last_lane<kValRows>(r[1], 0ull, MaxOp());
+        by = last_lane<kValRows>(r[2], 0ull, AddOp()); ch = last_lane<kValRows>(r[3], 0ull, AddOp());
+        ex = last_lane<kValRows>(r[4], 0ull, MaxOp()); sb = last_lane<kValRows>(r[6], 0ull, AddOp());
         // one row of partial results per workgroup, folded by k_validate_finish or the host: thousands of atomics
         // on the same few addresses would take longer than reading the matrices
-        if (tx == 0) { o[0] = fa; o[1] = m; o[2] = by; o[3] = ch; o[4] = ex; o[5] = tc; o[6] = sb; o[7] = wi; }
+        if (tx == kValRows - 1) { o[0] = fa; o[1] = m; o[2] = by; o[3] = ch; o[4] = ex; o[5] = 0; o[6] = sb; o[7] = wi; }
     }
     // the class sums: in the row, or one atomic per class and workgroup that holds any of it (cls_chunks starts at zero)
-    for (int i = ty * kValTile + tx; i < ncls; i += ny * kValTile) {
+    for (int i = ty * kValTile + tx; i < ncls; i += kValRows * kValTile) {
         unsigned long long v = 0;
+#pragma unroll 8
         for (int k = 0; k < copies; ++k) v += lcls[i * copies + ((i + k) & (copies - 1))];
         if (ticket) o[kValPartial + i] = v;                   // (first wave: kValFoldClasses < kWave)
         else if (v) atomicAdd(&st->cls_chunks[i], v);
@@ -510,10 +499,10 @@ __global__ void __launch_bounds__(256) k_validate_finish(const unsigned long lon
     __shared__ unsigned long long red[4][8];
     // the totals that k_phase_sums adds to, and the units that k_long_units counts; the other paths write them whole
     if (clear_totals && threadIdx.x < 64) st->phase_bytes[threadIdx.x] = st->phase_chunks[threadIdx.x] = st->phase_units[threadIdx.x][0] = 0;
-    unsigned long long fa = 0, m = 0, by = 0, ch = 0, ex = 0, tc = 0, sb = 0, wi = 0;
+    unsigned long long fa = 0, m = 0, by = 0, ch = 0, ex = 0, sb = 0, wi = 0;
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
         const unsigned long long* o = partial + (size_t)i * kValPartial;
-        fa |= o[0]; m = max(m, o[1]); by += o[2]; ch += o[3]; ex = max(ex, o[4]); tc += o[5]; sb += o[6];
+        fa |= o[0]; m = max(m, o[1]); by += o[2]; ch += o[3]; ex = max(ex, o[4]); sb += o[6];
         wi = max_windows(wi, o[7]);
     }
 #pragma unroll
@@ -523,18 +512,17 @@ __global__ void __launch_bounds__(256) k_validate_finish(const unsigned long lon
         by += __shfl_xor(by, d, kWave);
         ch += __shfl_xor(ch, d, kWave);
         ex = max(ex, (unsigned long long)__shfl_xor(ex, d, kWave));
-        tc += __shfl_xor(tc, d, kWave);
         sb += __shfl_xor(sb, d, kWave);
         wi = max_windows(wi, __shfl_xor(wi, d, kWave));
     }
     const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-    if (lane == 0) { red[wv][0] = fa; red[wv][1] = m; red[wv][2] = by; red[wv][3] = ch; red[wv][4] = ex; red[wv][5] = tc; red[wv][6] = sb; red[wv][7] = wi; }
+    if (lane == 0) { red[wv][0] = fa; red[wv][1] = m; red[wv][2] = by; red[wv][3] = ch; red[wv][4] = ex; red[wv][6] = sb; red[wv][7] = wi; }
     __syncthreads();
     if (threadIdx.x == 0) {
-        fa = m = by = ch = ex = tc = sb = wi = 0;
+        fa = m = by = ch = ex = sb = wi = 0;
         for (int w = 0; w < 4; ++w) {
             fa |= red[w][0]; m = max(m, red[w][1]); by += red[w][2]; ch += red[w][3]; ex = max(ex, red[w][4]);
-            tc += red[w][5]; sb += red[w][6]; wi = max_windows(wi, red[w][7]);
+            sb += red[w][6]; wi = max_windows(wi, red[w][7]);
         }
         st->flags = (unsigned int)(fa >> 32);
         st->align_bits = (unsigned int)(fa & 127u);
@@ -542,7 +530,6 @@ __global__ void __launch_bounds__(256) k_validate_finish(const unsigned long lon
         st->total_bytes = by;
         st->total_chunks = ch;
         st->send_extent = ex;
-        st->t_chunks = tc;
         st->short_blocks = sb;
         st->windows = wi;
         if (mirror) {
@@ -552,7 +539,6 @@ __global__ void __launch_bounds__(256) k_validate_finish(const unsigned long lon
             mirror->total_bytes = by;
             mirror->total_chunks = ch;
             mirror->send_extent = ex;
-            mirror->t_chunks = tc;
             mirror->short_blocks = sb;
             mirror->windows = wi;
         }
@@ -2862,7 +2848,7 @@ __global__ void __launch_bounds__(kTinyThreads) k_tiny_call(const TinyArgs a) {
         const unsigned long long t_need = (unsigned long long)P * (unsigned long long)a.slots * (unsigned long long)slot_bytes;
         const bool ok = fl == 0 && by <= kTinyMaxPayload && t_need <= a.t_capacity;
         a.st->flags = fl & 7u; a.st->align_bits = ab; a.st->max_count = m; a.st->total_bytes = by; a.st->total_chunks = ch;
-        a.st->send_extent = ex; a.st->t_chunks = 0; a.st->tiny_done = ok ? 1 : 0;
+        a.st->send_extent = ex; a.st->tiny_done = ok ? 1 : 0;
         verdict = ok ? m : -1;
     }
     __syncthreads();
