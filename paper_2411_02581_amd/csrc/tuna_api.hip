@@ -532,79 +532,6 @@ int resolve_hierarchy(int P, int ranks_per_node, int* Q) {
     return TUNA_OK;
 }
 
-// Waits until the device has written `ticket` to a word of pinned memory: by looking at it for a short while, which sees it a
-// few microseconds after it was written, then by the stream's synchronisation (work of the caller's may be in front of it).
-// Per call, against the kernel's end, a copy of the result and the synchronisation: P = 256, r = 4 120 -> 109 us, uniform [0, 16]
-// B, P = 2048, r = 46 249 -> 235, P = 128, linear 50 -> 46.  (The single-launch call, which has to end before it returns, gains
-// nothing: 34.2 / 34.0.)
-int wait_ticket(const unsigned long long* word, unsigned long long ticket, hipStream_t s) {
-    const auto start = std::chrono::steady_clock::now();
-    for (unsigned int i = 1; __atomic_load_n(word, __ATOMIC_ACQUIRE) != ticket; ++i) {
-        if (i % 64 || std::chrono::steady_clock::now() - start < std::chrono::microseconds(500)) continue;
-        HIPCHK(hipStreamSynchronize(s));
-        if (__atomic_load_n(word, __ATOMIC_ACQUIRE) == ticket) break;
-        sh.last_hip_error = (int)hipErrorUnknown;
-        return TUNA_ERR_HIP;
-    }
-    return TUNA_OK;
-}
-
-// Validation + sizing pass shared by tuna_alltoallv* and tuna_workspace_bytes: fills *sb.h_status.  When it returns everything that
-// the stream held before is done, and all that validation stores but not, with a ticket, its last kernel's end: the stream
-// need not be idle.
-// clear_totals: the per-phase totals in *sb.d_status start at zero (an immediate call, whose kernels may add to them).  A
-// sizing query and a plan leave them alone: until the next call they are the last one's statistics, or still being summed.
-int run_validate(const StatusBufs& sb, const int32_t* sendcounts, const int32_t* recvcounts, const int64_t* sdispls,
-                 const int64_t* rdispls, int P, hipStream_t s, const DevicePlan* exact_t_for, bool clear_totals) {
-    // every field of the status block a call reads is written by the call's own kernels: no clearing (the class sums, which
-    // kernels add to, start at zero and are cleared as they are read)
-    const size_t t = (size_t)((P + kValTile - 1) / kValTile);
-    const unsigned vgrid = (unsigned)(t * t < (size_t)sb.num_cus * 2 ? t * t : (size_t)sb.num_cus * 2);
-    // with a schedule that has T: also the size of every class of exact-size T (summed into the status block)
-    const int nph = exact_t_for ? (int)exact_t_for->host.phases.size() : 0;
-    const int ncls = class_count(nph);
-    // Few workgroups: their rows go straight to pinned memory and the host adds them up.  More rows would take longer to
-    // cross the bus and to add up than the two kernels and the copy they save (about 20 us).
-    const bool fold = sb.h_part_dev && vgrid <= (unsigned)kValFoldRows && ncls <= kValFoldClasses;
-    const bool mail = sb.h_part_dev && sb.h_status_dev;
-    const unsigned long long ticket = sb.h_part ? ++sb.h_part[kMailIssued] : 0;
-    if (ncls > 0 && !fold && !mail && !sb.sums_clear) {
-        hipLaunchKernelGGL(k_zero64, dim3((unsigned)((ncls + 255) / 256)), dim3(256), 0, s, sb.d_status->cls_chunks, ncls);
-        HIPCHK(hipGetLastError());
-    }
-    const int copies = ncls <= 104 ? kValCopies : ncls <= 208 ? kValCopies / 2 : 1;         // at most 26 KiB of LDS beside the tiles'; no schedule has more than 136
-    const bool whole = recvcounts != nullptr;
-    hipLaunchKernelGGL(whole ? k_validate<true> : k_validate<false>, dim3(vgrid), dim3(kValTile, kValRows), (size_t)ncls * copies * 8, s, sendcounts,
-                       recvcounts, sdispls, rdispls, P, fold ? sb.h_part_dev : sb.d_vpart, copies, exact_t_for ? exact_t_for->host.Q : 1,
-                       exact_t_for ? exact_t_for->host.N : 1, exact_t_for ? exact_t_for->d_mask : nullptr, nph, sb.d_status, fold ? ticket : 0ull,
-                       clear_totals ? 1 : 0);
-    HIPCHK(hipGetLastError());
-    if (fold) {
-        Status& h = *sb.h_status;
-        unsigned long long fa = 0, m = 0;
-        h.total_bytes = h.total_chunks = h.send_extent = h.short_blocks = h.windows = 0;
-        for (int i = 0; i < ncls; ++i) h.cls_chunks[i] = 0;
-        for (unsigned r = 0; r < vgrid; ++r) {
-            const unsigned long long* o = sb.h_part + (size_t)r * kValRow;
-            if (const int rc = wait_ticket(o + kValRow - 1, ticket, s)) return rc;
-            fa |= o[0]; m = std::max(m, o[1]);
-            h.total_bytes += o[2]; h.total_chunks += o[3]; h.send_extent = std::max(h.send_extent, o[4]);
-            h.short_blocks += o[6]; h.windows = max_windows(h.windows, o[7]);
-            for (int i = 0; i < ncls; ++i) h.cls_chunks[i] += o[kValPartial + i];
-        }
-        h.flags = (unsigned int)(fa >> 32); h.align_bits = (unsigned int)(fa & 127u); h.max_count = (int)m;
-        return TUNA_OK;
-    }
-    hipLaunchKernelGGL(k_validate_finish, dim3(1), dim3(256), 0, s, sb.d_vpart, (int)vgrid, sb.d_status, clear_totals ? 1 : 0,
-                       mail ? sb.h_status_dev : nullptr, ncls, mail ? sb.h_part_dev + kMailReceived : nullptr, ticket);
-    HIPCHK(hipGetLastError());
-    if (mail) return wait_ticket(sb.h_part + kMailReceived, ticket, s);
-    // the head and the class sums behind it in one copy
-    HIPCHK(hipMemcpyAsync(sb.h_status, sb.d_status, offsetof(Status, cls_chunks) + (size_t)ncls * 8, hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    return TUNA_OK;
-}
-
 // What the data kernels of a call need, fixed once the counts have been validated and sized.
 struct Prepared {
     int P = 0, Q = 0, N = 0;
@@ -652,7 +579,91 @@ struct Prepared {
     size_t self_units = 0;              // wave units to launch for: an upper bound, or the exact count of a plan
     int block_count = 0;                // rounds per batch of launches (0: all rounds of a phase at once)
     unsigned long long* rank_bytes = nullptr;   // [P] scratch of the metadata kernels
+    // Metadata memory that is there before the sizes are known (nullptr: none, or not to be used), and whether the kernels of
+    // launch_early ran in it; early_totals: ... and the phases' totals come from them
+    void* early_mem = nullptr;
+    size_t early_bytes = 0;
+    bool early = false, early_totals = false;
 };
+int launch_early(Prepared& pr, bool verdict, hipStream_t s);
+
+// Waits until the device has written `ticket` to a word of pinned memory: by looking at it for a short while, which sees it a
+// few microseconds after it was written, then by the stream's synchronisation (work of the caller's may be in front of it).
+// Per call, against the kernel's end, a copy of the result and the synchronisation: P = 256, r = 4 120 -> 109 us, uniform [0, 16]
+// B, P = 2048, r = 46 249 -> 235, P = 128, linear 50 -> 46.  (The single-launch call, which has to end before it returns, gains
+// nothing: 34.2 / 34.0.)
+int wait_ticket(const unsigned long long* word, unsigned long long ticket, hipStream_t s) {
+    const auto start = std::chrono::steady_clock::now();
+    for (unsigned int i = 1; __atomic_load_n(word, __ATOMIC_ACQUIRE) != ticket; ++i) {
+        if (i % 64 || std::chrono::steady_clock::now() - start < std::chrono::microseconds(500)) continue;
+        HIPCHK(hipStreamSynchronize(s));
+        if (__atomic_load_n(word, __ATOMIC_ACQUIRE) == ticket) break;
+        sh.last_hip_error = (int)hipErrorUnknown;
+        return TUNA_ERR_HIP;
+    }
+    return TUNA_OK;
+}
+
+// Validation + sizing pass shared by tuna_alltoallv* and tuna_workspace_bytes: fills *sb.h_status.  When it returns everything that
+// the stream held before is done, and all that validation stores but not, with a ticket, its last kernel's end: the stream
+// need not be idle.
+// clear_totals: the per-phase totals in *sb.d_status start at zero (an immediate call, whose kernels may add to them).  A
+// sizing query and a plan leave them alone: until the next call they are the last one's statistics, or still being summed.
+// early: a call whose kernels may start before the host knows the result (launch_early).
+int run_validate(const StatusBufs& sb, const int32_t* sendcounts, const int32_t* recvcounts, const int64_t* sdispls,
+                 const int64_t* rdispls, int P, hipStream_t s, const DevicePlan* exact_t_for, bool clear_totals, Prepared* early = nullptr) {
+    // every field of the status block a call reads is written by the call's own kernels: no clearing (the class sums, which
+    // kernels add to, start at zero and are cleared as they are read)
+    const size_t t = (size_t)((P + kValTile - 1) / kValTile);
+    const unsigned vgrid = (unsigned)(t * t < (size_t)sb.num_cus * 2 ? t * t : (size_t)sb.num_cus * 2);
+    // with a schedule that has T: also the size of every class of exact-size T (summed into the status block)
+    const int nph = exact_t_for ? (int)exact_t_for->host.phases.size() : 0;
+    const int ncls = class_count(nph);
+    // Few workgroups: their rows go straight to pinned memory and the host adds them up.  More rows would take longer to
+    // cross the bus and to add up than the two kernels and the copy they save (about 20 us).
+    const bool fold = sb.h_part_dev && vgrid <= (unsigned)kValFoldRows && ncls <= kValFoldClasses;
+    const bool mail = sb.h_part_dev && sb.h_status_dev;
+    const unsigned long long ticket = sb.h_part ? ++sb.h_part[kMailIssued] : 0;
+    if (ncls > 0 && !fold && !mail && !sb.sums_clear) {
+        hipLaunchKernelGGL(k_zero64, dim3((unsigned)((ncls + 255) / 256)), dim3(256), 0, s, sb.d_status->cls_chunks, ncls);
+        HIPCHK(hipGetLastError());
+    }
+    const int copies = ncls <= 104 ? kValCopies : ncls <= 208 ? kValCopies / 2 : 1;         // at most 26 KiB of LDS beside the tiles'; no schedule has more than 136
+    const bool whole = recvcounts != nullptr;
+    hipLaunchKernelGGL(whole ? k_validate<true> : k_validate<false>, dim3(vgrid), dim3(kValTile, kValRows), (size_t)ncls * copies * 8, s, sendcounts,
+                       recvcounts, sdispls, rdispls, P, fold ? sb.h_part_dev : sb.d_vpart, copies, exact_t_for ? exact_t_for->host.Q : 1,
+                       exact_t_for ? exact_t_for->host.N : 1, exact_t_for ? exact_t_for->d_mask : nullptr, nph, sb.d_status, fold ? ticket : 0ull,
+                       clear_totals ? 1 : 0);
+    HIPCHK(hipGetLastError());
+    if (fold) {
+        if (early)
+            if (const int rc = launch_early(*early, /*verdict=*/false, s)) return rc;
+        Status& h = *sb.h_status;
+        unsigned long long fa = 0, m = 0;
+        h.total_bytes = h.total_chunks = h.send_extent = h.short_blocks = h.windows = 0;
+        for (int i = 0; i < ncls; ++i) h.cls_chunks[i] = 0;
+        for (unsigned r = 0; r < vgrid; ++r) {
+            const unsigned long long* o = sb.h_part + (size_t)r * kValRow;
+            if (const int rc = wait_ticket(o + kValRow - 1, ticket, s)) return rc;
+            fa |= o[0]; m = std::max(m, o[1]);
+            h.total_bytes += o[2]; h.total_chunks += o[3]; h.send_extent = std::max(h.send_extent, o[4]);
+            h.short_blocks += o[6]; h.windows = max_windows(h.windows, o[7]);
+            for (int i = 0; i < ncls; ++i) h.cls_chunks[i] += o[kValPartial + i];
+        }
+        h.flags = (unsigned int)(fa >> 32); h.align_bits = (unsigned int)(fa & 127u); h.max_count = (int)m;
+        return TUNA_OK;
+    }
+    hipLaunchKernelGGL(k_validate_finish, dim3(1), dim3(256), 0, s, sb.d_vpart, (int)vgrid, sb.d_status, clear_totals ? 1 : 0,
+                       mail ? sb.h_status_dev : nullptr, ncls, mail ? sb.h_part_dev + kMailReceived : nullptr, ticket);
+    HIPCHK(hipGetLastError());
+    if (early)
+        if (const int rc = launch_early(*early, /*verdict=*/true, s)) return rc;
+    if (mail) return wait_ticket(sb.h_part + kMailReceived, ticket, s);
+    // the head and the class sums behind it in one copy
+    HIPCHK(hipMemcpyAsync(sb.h_status, sb.d_status, offsetof(Status, cls_chunks) + (size_t)ncls * 8, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    return TUNA_OK;
+}
 
 void carve_exact_t(Carver& cv, const PlanHost& pl, bool keep_all_phases, Prepared& pr) {
     const size_t nph = pl.phases.size(), P = (size_t)pl.P, ncls = (size_t)class_count((int)nph);
@@ -722,9 +733,13 @@ unsigned long long colour_classes(const PlanHost& pl, bool fused, bool staggered
     // are tried (by first use, by size, by length of life, by size times length of life) and the
     // tightest result is kept (at most 12 % above the bytes alive at one time on the schedules measured).
     cbase.assign((size_t)class_count(nph), 0);
+    // (This runs between validation's result and a call's first launch: 28 classes 33 -> 10 us, 45 92 -> 25, against a sorted list
+    // of the busy ranges for every class.)
     unsigned long long best_extent = ~0ull;
+    std::vector<Item> it;
+    std::vector<const Item*> placed;                         // by their places
     for (int order = 0; order < 4; ++order) {
-        std::vector<Item> it = items;
+        it = items;
         std::stable_sort(it.begin(), it.end(), [order](const Item& a, const Item& b) {
             const long long la = a.end - a.start + 1, lb = b.end - b.start + 1;
             switch (order) {
@@ -738,19 +753,20 @@ unsigned long long colour_classes(const PlanHost& pl, bool fused, bool staggered
             }
         });
         unsigned long long extent = 0;
-        for (size_t k = 0; k < it.size(); ++k) {
-            std::vector<std::pair<long long, long long>> busy;   // ranges of the classes alive together with this one
-            for (size_t m = 0; m < k; ++m)
-                if (it[m].end >= it[k].start && it[m].start <= it[k].end)
-                    busy.emplace_back(it[m].off, it[m].off + (long long)it[m].cap);
-            std::sort(busy.begin(), busy.end());
+        placed.clear();
+        for (size_t k = 0; k < it.size() && extent < best_extent; ++k) {
+            Item& x = it[k];
             long long off = 0;
-            for (const auto& b : busy) {
-                if (off + (long long)it[k].cap <= b.first) break;
-                off = std::max(off, b.second);
+            for (const Item* p : placed) {
+                if (off + (long long)x.cap <= p->off) break;
+                if (p->end >= x.start && p->start <= x.end) off = std::max(off, p->off + (long long)p->cap);
             }
-            it[k].off = off;
-            extent = std::max(extent, (unsigned long long)off + it[k].cap);
+            x.off = off;
+            extent = std::max(extent, (unsigned long long)off + x.cap);
+            size_t at = placed.size();
+            placed.push_back(&x);
+            for (; at > 0 && placed[at - 1]->off > off; --at) placed[at] = placed[at - 1];
+            placed[at] = &x;
         }
         if (extent < best_extent) {
             best_extent = extent;
@@ -769,7 +785,7 @@ unsigned long long colour_classes(const PlanHost& pl, bool fused, bool staggered
 bool choose_exact_t(int option, const PlanHost& pl, const Status& hs, unsigned long long exact_t_chunks) {
     if (option != 2) return option != 0;
     const double slot_bytes = (double)((hs.max_count + 127) / 128 * 128);
-    if ((double)hs.total_bytes >= 0.9 * (double)pl.P * (double)pl.P * slot_bytes) return false;
+    if (slots_are_full(hs.total_bytes, pl.P, hs.max_count)) return false;
     const double slots_t = (double)pl.P * (double)pl.slots * slot_bytes;
     const double exact_t = (double)exact_t_chunks * 16.0 + (double)pl.phases.size() * (double)pl.P * (double)pl.P * 4.0;
     if (exact_t <= slots_t) return true;
@@ -940,9 +956,11 @@ int prepare_sizes(Prepared& pr, int dense_option, hipStream_t s, Status& hs, boo
     const int P = pr.P;
     const bool has_t = pr.dp->host.slots > 0;              // a schedule without T (r >= P - 1) has nothing to size
     int rc = run_validate(pr.sb, pr.sendcounts, pr.recvcounts, pr.sdispls, pr.rdispls, P, s,
-                          (dense_option != 0 && has_t) ? pr.dp : nullptr, !pr.for_plan);
+                          (dense_option != 0 && has_t) ? pr.dp : nullptr, !pr.for_plan, pr.early_mem ? &pr : nullptr);
     if (rc != TUNA_OK) return rc;
     hs = *pr.sb.h_status;
+    // A refused call is done when it returns.
+    if (pr.early && ((hs.flags & 7u) || too_large(P, hs) || (hs.total_bytes && (!pr.sendbuf || !pr.recvbuf)))) HIPCHK(hipStreamSynchronize(s));
     if (pr.dp->built_on == s) pr.dp->complete = true;      // run_validate has waited for kernels of this stream behind the tables'
     if (hs.flags & 1u) return TUNA_ERR_NEGATIVE_COUNT;
     if (hs.flags & 2u) return TUNA_ERR_COUNT_MISMATCH;
@@ -1171,7 +1189,7 @@ ResolveArgs resolve_args(const Prepared& pr, size_t i, const int32_t* nxt, const
 
 template <int LPB, bool TALL, int STREAM>
 void launch_direct_as(const DirectArgs& a, dim3 grid, bool exact, bool senders, hipStream_t s) {
-    if (!a.part) hipLaunchKernelGGL((k_hop_direct<LPB, TALL, STREAM, false, true>), grid, dim3(256), 0, s, a);
+    if (a.r.hop.src) hipLaunchKernelGGL((k_hop_direct<LPB, TALL, STREAM, false, true>), grid, dim3(256), 0, s, a);
     else if (senders && exact) hipLaunchKernelGGL((k_hop_senders<LPB, STREAM, true, TALL>), grid, dim3(256), 0, s, a);
     else if (senders) hipLaunchKernelGGL((k_hop_senders<LPB, STREAM, false, TALL>), grid, dim3(256), 0, s, a);
     else if (exact) hipLaunchKernelGGL((k_hop_direct<LPB, TALL, STREAM, true, false>), grid, dim3(256), 0, s, a);
@@ -1260,7 +1278,7 @@ unsigned direct_rows(const Prepared& pr, const PhaseHost& ph) {
 
 template <bool LINES>
 void launch_rows_as(const DirectArgs& a, dim3 grid, bool exact, hipStream_t s) {
-    if (!a.part) hipLaunchKernelGGL((k_hop_rows<LINES, false, true>), grid, dim3(256), 0, s, a);
+    if (a.r.hop.src) hipLaunchKernelGGL((k_hop_rows<LINES, false, true>), grid, dim3(256), 0, s, a);
     else if (exact) hipLaunchKernelGGL((k_hop_rows<LINES, true, false>), grid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL((k_hop_rows<LINES, false, false>), grid, dim3(256), 0, s, a);
 }
@@ -1281,8 +1299,8 @@ int launch_rows(const Prepared& pr, size_t i, const HopDev& hop, uint2* part, bo
     return TUNA_OK;
 }
 
-// The payload of a phase of short blocks: from the hop arrays (part null), or found in the same kernel, with partial
-// sums into `part`.
+// The payload of a phase of short blocks: from the hop arrays, if there are any, or found in the same kernel, with partial
+// sums into `part`, if there is one.
 int launch_direct(const Prepared& pr, size_t i, const HopDev& hop, int seg_lo, int seg_hi, uint2* part, bool own, hipStream_t s) {
     if (seg_hi <= seg_lo) return TUNA_OK;
     const PhaseHost& ph = pr.dp->host.phases[i];
@@ -1308,7 +1326,7 @@ int launch_long_units(const Prepared& pr, size_t i, int4* units, hipStream_t s) 
     a.d.user_limit = pr.user_limit;
     a.units = reinterpret_cast<ulonglong2*>(units);
     a.count = &pr.sb.d_status->phase_units[i][0];
-    a.bytes = &pr.sb.d_status->phase_bytes[i]; a.chunks = &pr.sb.d_status->phase_chunks[i];
+    if (!pr.early_totals) { a.bytes = &pr.sb.d_status->phase_bytes[i]; a.chunks = &pr.sb.d_status->phase_chunks[i]; }
     a.own = i == 0 ? 1 : 0;
     const dim3 grid((unsigned)std::max(1, std::min(16, kLongMaxRanks / pr.P)), (unsigned)pr.P);
     if (pr.exact_kernels) hipLaunchKernelGGL(k_long_units<true>, grid, dim3(kScanThreads), 0, s, a);
@@ -1429,14 +1447,14 @@ int launch_self_copy(const Prepared& pr, hipStream_t s) {
 }
 
 // Whether the launch of the first phase takes the ranks' own blocks along, one launch less: all rounds at once, by
-// k_hop_direct or k_hop_rows (a call's k_hop_senders does not).  Us with a launch of their own / without: per start up to 200 bytes, P = 50
+// k_hop_direct or k_hop_rows (a call's k_hop_senders only where k_t_places ran too early to do it).  Us with a launch of their own / without: per start up to 200 bytes, P = 50
 // 9.8 / 7.2, up to 16, P = 400 9.9 / 7.1, up to 1 KiB, P = 100, r = 10 14.0 / 12.3, P = 1000 212 / 208; per call up to 1 KiB, P = 300 60.5 /
 // 56.1, up to 6 KB, P = 128 58.4 / 54.7.  Rows of workgroups in front: one more column shifts which workgroups share an XCD (16
 // GiB linear 6.4 -> 6.6 ms).
 bool own_in_first(const Prepared& pr) {
     if (pr.self_engine || !pr.fused || pr.staggered || pr.block_count != 0 || pr.dp->host.phases.empty()) return false;
     const int kernel = phase_kernel(pr, 0);
-    return kernel == TUNA_HOP_ROWS || (kernel == TUNA_HOP_DIRECT && (pr.for_plan || !sender_phase(pr, pr.dp->host.phases[0])));
+    return kernel == TUNA_HOP_ROWS || (kernel == TUNA_HOP_DIRECT && (pr.for_plan || pr.early || !sender_phase(pr, pr.dp->host.phases[0])));
 }
 
 // The payload kernels of digit phase i: pack, exchange, unpack -- or the one-kernel hop.
@@ -1588,43 +1606,111 @@ bool runs_direct(const Prepared& pr) {
            pr.dp->host.phases.size() <= kPlaceMaxPhases;
 }
 
-// All the metadata of such a call: with exact-size T the places of the blocks that its phases store there.
-// own: if given, the ranks' own blocks are moved by the same launch when there is one (*own = true).
-int launch_t_places(Prepared& pr, hipStream_t s, bool* own = nullptr) {
-    if (!pr.exact_t) return TUNA_OK;
+// All the metadata of such a call: with exact-size T the places of the blocks that its phases store there (k_t_places, k_t_bases).
+//
+// The places follow from the counts alone; only where the classes lie waits for the host.  So k_t_places runs under the host's
+// wait for validation's result, in memory that an earlier call has left (launch_early), for up to kEarlyEntries entries of the
+// matrices (8 to 30 us, of which the wait hides 12; where T is in slots or a hop has metadata kernels it was for nothing).  Up to kEarlyTotalsRanks
+// ranks it finds the phases' totals on the way, which follow from the counts and rdispls: a pass over the receivers' rows that
+// the wait hides too, in place of the hops' partial sums and k_phase_sums, the call's last kernel (2048 ranks 10 us, which it does not
+// hide).  A linear schedule has no places, its totals are found there all the same (k_row_totals).
+constexpr double kEarlyEntries = 9e6;
+constexpr int kEarlyTotalsRanks = 512;
+
+// (rows: one per class)
+void place_args(const Prepared& pr, PlaceArgs& a) {
     const PlanHost& pl = pr.dp->host;
-    PlaceArgs a{};
-    a.P = pr.P; a.Q = pr.Q; a.N = pr.N; a.sendcounts = pr.sendcounts; a.recvcounts = pr.recvcounts; a.x = exact_t_of(pr, 0);
-    a.by_value = pr.cbase.size() <= kPlaceClasses ? 1 : 0;
-    if (a.by_value) std::copy(pr.cbase.begin(), pr.cbase.end(), a.cbase);
-    else if (const int rc = upload_cbase(pr, s)) return rc;
-    int rows = 0;
+    a.P = pr.P; a.Q = pr.Q; a.N = pr.N; a.sendcounts = pr.sendcounts; a.recvcounts = pr.recvcounts; a.x = pr.x;
+    a.R = (unsigned char*)pr.recvbuf; a.rdispls = pr.rdispls;
+    a.st = pr.sb.d_status;
+    a.own = -1;
     for (size_t i = 0; i < pl.phases.size(); ++i) {
         const int ncls = (int)(pr.dp->tcls[i].size() / 3);
         if (!ncls) continue;
         for (int k = 0; k < ncls; ++k) a.most = std::max(a.most, (int)pr.dp->tcls[i][3 * k + 2]);
-        a.ph[a.nph++] = PlacePhase{pr.dp->d_seg[i].e, pr.dp->d_seg[i].src, pr.dp->d_tord[i], pr.dp->d_tcls[i], (int)i, rows, pl.phases[i].dim,
+        a.ph[a.nph++] = PlacePhase{pr.dp->d_seg[i].e, pr.dp->d_seg[i].src, pr.dp->d_tord[i], pr.dp->d_tcls[i], (int)i, a.rows, pl.phases[i].dim,
                                    (int)std::min<int64_t>(pl.phases[i].rx * pl.phases[i].r, INT_MAX)};
-        rows += ncls;
+        a.rows += ncls;
     }
-    if (!rows) return TUNA_OK;
-    a.own = -1;
-    if (own) {
-        a.own = rows; *own = true;
-        a.S = (const unsigned char*)pr.sendbuf; a.sdispls = pr.sdispls; a.R = (unsigned char*)pr.recvbuf; a.rdispls = pr.rdispls;
+}
+// The totals of the phases too: their parts lie where the hop arrays would.
+void want_totals(const Prepared& pr, PlaceArgs& a) {
+    const PlanHost& pl = pr.dp->host;
+    a.part = reinterpret_cast<ulonglong2*>(pr.hop.src);
+    a.nfin = (int)pl.phases.size();
+    for (int i = 0; i < a.nfin; ++i) {
+        const PhaseHost& ph = pl.phases[i];
+        const int64_t hi = std::min<int64_t>(ph.rx * ph.r, ph.dim == 0 ? pr.Q : pr.N);
+        if (i == 0) a.fin[0] = ph.dim == 0 ? 1 : pr.Q;
+        a.fin[i + 1] = (int)(ph.dim == 0 ? hi : hi * pr.Q);
     }
-    const dim3 grid((unsigned)pr.P, (unsigned)(rows + (own ? 1 : 0)));
-    if (pr.P <= kPlaceSlotRanks && pl.phases[0].r >= kPlaceSlotRadix)
+}
+int launch_places(const Prepared& pr, const PlaceArgs& a, int more, hipStream_t s) {
+    const dim3 grid((unsigned)pr.P, (unsigned)(a.rows + more));
+    if (pr.P <= kPlaceSlotRanks && pr.dp->host.phases[0].r >= kPlaceSlotRadix)
         hipLaunchKernelGGL(k_t_places_slots, grid, dim3(kScanThreads), (size_t)a.most * 4 + (size_t)pr.P * 2, s, a);
     else
         hipLaunchKernelGGL(k_t_places, grid, dim3(kScanThreads), 0, s, a);
     HIPCHK(hipGetLastError());
-    hipLaunchKernelGGL(k_t_bases, dim3((unsigned)rows), dim3(kScanThreads), 0, s, a);
+    return TUNA_OK;
+}
+int launch_bases(const PlaceArgs& a, hipStream_t s) {
+    hipLaunchKernelGGL(k_t_bases, dim3((unsigned)(a.rows + a.nfin)), dim3(kScanThreads), 0, s, a);
     HIPCHK(hipGetLastError());
     return TUNA_OK;
 }
 
-// The payload of such a phase, found and moved in one kernel; partial sums into `part` (direct_rows rows of P entries).
+// verdict: the status block holds what validation found when these kernels run.
+int launch_early(Prepared& pr, bool verdict, hipStream_t s) {
+    const PlanHost& pl = pr.dp->host;
+    const size_t phases = pl.phases.size();
+    double entries = (double)pr.P * (double)pr.P;
+    for (size_t i = 0; i < phases; ++i) entries += (double)class_total(pr.dp->tcls[i]) * (double)pr.P;
+    if (!pr.fused || pr.staggered || pr.block_count != 0 || !phases || phases > kPlaceMaxPhases || entries > kEarlyEntries || (phases > 1 && pr.opt.t_layout == TUNA_T_SLOTS)) return TUNA_OK;
+    Carver cm(pr.early_mem, pr.early_bytes);
+    carve_meta(cm, pr.P);
+    if (phases > 1) carve_exact_t(cm, pl, false, pr);
+    const int hld = max_hop_ld(pr);
+    carve_hop(cm, pr.P, hld, pr.hop);
+    PlaceArgs a{};
+    place_args(pr, a);
+    const bool totals = pr.P <= kEarlyTotalsRanks;
+    if (totals) want_totals(pr, a);
+    if (!cm.ok || (phases == 1 && !totals) || (size_t)(a.rows + a.nfin) * (size_t)pr.P * sizeof(ulonglong2) > hop_bytes_for(pr.P, hld)) return TUNA_OK;
+    a.verdict = verdict ? 1 : 0;
+    a.slots_rule = phases > 1 && pr.opt.t_layout == TUNA_T_AUTO ? 1 : 0;
+    a.max_block = pr.P > kLongMaxRanks ? kRowsMaxBytes : INT_MAX;
+    pr.early = true;
+    pr.early_totals = totals;
+    if (phases > 1) return launch_places(pr, a, a.nfin, s);
+    hipLaunchKernelGGL(k_row_totals, dim3((unsigned)((pr.P + kScanThreads / kWave - 1) / (kScanThreads / kWave))), dim3(kScanThreads), 0, s, a);
+    HIPCHK(hipGetLastError());
+    return TUNA_OK;
+}
+
+// own: if given, the ranks' own blocks are moved by the same launch when there is one (*own = true).
+int launch_t_places(Prepared& pr, hipStream_t s, bool* own = nullptr) {
+    if (!pr.exact_t) return TUNA_OK;
+    PlaceArgs a{};
+    place_args(pr, a);
+    if (!a.rows) return TUNA_OK;
+    a.by_value = pr.cbase.size() <= kPlaceClasses ? 1 : 0;
+    if (a.by_value) std::copy(pr.cbase.begin(), pr.cbase.end(), a.cbase);
+    else if (const int rc = upload_cbase(pr, s)) return rc;
+    if (pr.early) {
+        if (pr.early_totals) want_totals(pr, a);
+        return launch_bases(a, s);
+    }
+    if (own) {
+        a.own = a.rows; *own = true;
+        a.S = (const unsigned char*)pr.sendbuf; a.sdispls = pr.sdispls;
+    }
+    // (a row behind the classes' is the own blocks')
+    if (const int rc = launch_places(pr, a, own ? 1 : 0, s)) return rc;
+    return launch_bases(a, s);
+}
+
+// The payload of such a phase, found and moved in one kernel; partial sums into `part`, if there is one (direct_rows rows of P entries).
 int launch_direct_payload(const Prepared& pr, size_t i, uint2* part, bool own, hipStream_t s) {
     const PhaseHost& ph = pr.dp->host.phases[i];
     const int rc = row_blocks(pr)         ? launch_rows(pr, i, HopDev{}, part, own, s)
@@ -1644,6 +1730,11 @@ int run_one_pass(Prepared& pr, void* mbase, size_t mbytes, void* dbase, hipStrea
     Carver cm(mbase, mbytes);
     MetaBuffers mb = carve_meta(cm, P);
     pr.rank_bytes = mb.rank_bytes;
+    const bool direct = runs_direct(pr);
+    // what ran early is good for a call whose phases find their blocks themselves, T being in exact size; the totals of a linear
+    // schedule are in the status block by now, those of others come with k_t_bases
+    pr.early = pr.early && direct && pr.exact_t;
+    pr.early_totals = pr.early_totals && direct && (pr.early || pl.phases.size() == 1);
     if (pr.exact_t) carve_exact_t(cm, pl, false, pr);
     if (const int hld = max_hop_ld(pr)) carve_hop(cm, P, hld, pr.hop);
     carve_self(cm, pr);
@@ -1654,7 +1745,6 @@ int run_one_pass(Prepared& pr, void* mbase, size_t mbytes, void* dbase, hipStrea
     pr.stage_r = cd.take<v4u>(pr.fused ? 0 : ds.stage_chunks);
     pr.T = cd.take<unsigned char>(ds.t_bytes + kTailSlack);
     if (!cm.ok || !cd.ok) return TUNA_ERR_WORKSPACE_TOO_SMALL;
-    const bool direct = runs_direct(pr);
     int rc = direct ? TUNA_OK : upload_cbase(pr, s);         // launch_t_places passes them on
     if (rc != TUNA_OK) return rc;
     st.temp_bytes = (int64_t)ds.t_bytes;
@@ -1717,6 +1807,11 @@ int run_one_pass(Prepared& pr, void* mbase, size_t mbytes, void* dbase, hipStrea
             used = 0;
         };
         for (size_t i = 0; i < pl.phases.size(); ++i) {
+            if (pr.early_totals) {
+                rc = launch_direct_payload(pr, i, nullptr, own_first && i == 0, s);
+                if (rc != TUNA_OK) return rc;
+                continue;
+            }
             const size_t rows = direct_rows(pr, pl.phases[i]);
             if (used + rows > room) add_up();
             if (i) mark(pr.ctx, s, kCatMeta, (int)i);        // all phases' places were found before the first: next to nothing
@@ -1726,7 +1821,7 @@ int run_one_pass(Prepared& pr, void* mbase, size_t mbytes, void* dbase, hipStrea
             rc = launch_direct_payload(pr, i, const_cast<uint2*>(parts.part[i]), own_first && i == 0, s);
             if (rc != TUNA_OK) return rc;
         }
-        add_up();
+        if (!pr.early_totals) add_up();
         HIPCHK(hipGetLastError());
         return TUNA_OK;
     }
@@ -1859,15 +1954,28 @@ int run_once(Ctx& c, const Options& opt, const void* sendbuf, const int32_t* sen
     Prepared pr;
     Status hs{};
     bool empty = false;
+    if (c.ready && !c.profile) {                              // a context's first call has no memory yet
+        pr.early_mem = c.user_ws ? c.user_ws : c.meta;
+        pr.early_bytes = c.user_ws ? c.user_ws_bytes : c.meta_bytes;
+    }
     int rc = prepare_call(c, opt, sendbuf, sendcounts, sdispls, recvbuf, recvcounts, rdispls, P, ranks_per_node, rl, rg,
                           s, pr, hs, &empty);
     if (rc != TUNA_OK) return rc;
     tuna_stats_t& st = c.stats;
     fill_stats_header(pr, hs, st);
-    if (empty) { c.have_stats = true; return TUNA_OK; }
+    if (empty) {
+        if (pr.early) {
+            HIPCHK(hipEventRecord(c.ev_end, s));
+            c.end_recorded = true; c.last_stream = s;
+        }
+        c.have_stats = true;
+        return TUNA_OK;
+    }
     st.hop_kernels = hop_kernels_of(pr);
     const PlanHost& pl = pr.dp->host;
     const bool direct = runs_direct(pr);
+    const bool early = pr.early;
+    if (!direct) pr.early = pr.early_totals = false;
     if (use_two_pass(pl, hs) && pr.fused && !c.profile && !pr.debug_sizes && !direct) {
         rc = run_pipelined(c, pr, s);
     } else if (use_two_pass(pl, hs) && !direct) {
@@ -1878,16 +1986,22 @@ int run_once(Ctx& c, const Options& opt, const void* sendbuf, const int32_t* sen
         const DataSizes& ds = pr.ds;
         void *mbase, *dbase;
         if (c.user_ws) {
-            if (mbytes + ds.total > c.user_ws_bytes) return TUNA_ERR_WORKSPACE_TOO_SMALL;
+            if (mbytes + ds.total > c.user_ws_bytes) {
+                if (early) HIPCHK(hipStreamSynchronize(s));
+                return TUNA_ERR_WORKSPACE_TOO_SMALL;
+            }
             mbase = c.user_ws;
             dbase = (char*)c.user_ws + mbytes;
         } else {
-            rc = grow(&c.meta, &c.meta_bytes, mbytes);
-            if (rc != TUNA_OK) return rc;
-            rc = grow(&c.data, &c.data_bytes, ds.total);
-            if (rc != TUNA_OK) return rc;
+            const int rc_meta = grow(&c.meta, &c.meta_bytes, mbytes);
+            rc = rc_meta == TUNA_OK ? grow(&c.data, &c.data_bytes, ds.total) : rc_meta;
+            if (rc != TUNA_OK) {
+                if (early) HIPCHK(hipStreamSynchronize(s));
+                return rc;
+            }
             mbase = c.meta;
             dbase = c.data;
+            if (c.meta_bytes != pr.early_bytes) pr.early = false;     // new memory, perhaps where the old was
         }
         rc = run_one_pass(pr, mbase, mbytes, dbase, s, st);
     }
@@ -2323,6 +2437,8 @@ int run_static(const void* sendbuf, const int32_t* sendcounts, const int64_t* sd
     pr.dp = &dp;
 
     // ---- validation and sizing (one read-back), then the one-pass call ---------------------------------
+    pr.early_mem = cv.base + cv.off;
+    pr.early_bytes = cv.cap - cv.off;
     Status hs{};
     bool empty = false;
     rc = prepare_sizes(pr, pr.opt.t_layout, s, hs, &empty);
@@ -2336,7 +2452,10 @@ int run_static(const void* sendbuf, const int32_t* sendcounts, const int64_t* sd
     if (empty) return TUNA_OK;
     g.stats.hop_kernels = hop_kernels_of(pr);
     const size_t mbytes = one_pass_meta_bytes(pr);
-    if (cv.off + mbytes + pr.ds.total > cv.cap) return TUNA_ERR_NOALLOC_LIMIT;
+    if (cv.off + mbytes + pr.ds.total > cv.cap) {
+        if (pr.early) HIPCHK(hipStreamSynchronize(s));
+        return TUNA_ERR_NOALLOC_LIMIT;
+    }
     char* mbase = cv.base + cv.off;
     return run_one_pass(pr, mbase, mbytes, mbase + mbytes, s, g.stats);
 }

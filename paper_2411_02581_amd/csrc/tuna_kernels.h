@@ -1258,7 +1258,7 @@ struct DirectArgs {
     int iters;                          // steps of segments per workgroup (k_hop_direct)
     int segs;                           // segments per wave, at most 64 (k_hop_rows)
     unsigned long long user_limit;      // address one past the last byte of S that holds a block
-    uint2* part;                        // [grid.x][P]: payload bytes and chunks of the tile column, per receiver (not when RESOLVED)
+    uint2* part;                        // [grid.x][P]: payload bytes and chunks of the tile column, per receiver (null: not wanted)
     int own;                            // so many rows of workgroups in front move the ranks' own blocks (k_hop_direct, k_hop_rows)
 };
 
@@ -1361,7 +1361,101 @@ struct PlaceArgs {
     const int64_t* rdispls;
     int by_value;           // the classes' first chunks are here, not in x.cbase: no copy to the device before the kernels
     long long cbase[kPlaceClasses];
+    // the phases' totals, if wanted: payload bytes and chunks of every class row and, behind those, of the final blocks of each of
+    // nfin phases, per receiver
+    ulonglong2* part;       // [rows + nfin][P]
+    int rows, nfin;
+    int fin[kPlaceMaxPhases + 1];       // the final blocks of phase x are the slot indices fin[x] .. fin[x + 1] - 1
+    Status* st;
+    // kernels that run before the host has seen what validation found: nothing is to be done where they say so
+    int verdict;            // 1: *st holds it
+    int slots_rule;         // full slots are taken (slots_are_full)
+    int max_block;
 };
+// T in the paper's slots of M bytes is at least 90 % full: see choose_exact_t
+__host__ __device__ inline bool slots_are_full(unsigned long long total_bytes, int P, int max_count) {
+    const double slot_bytes = (double)((max_count + 127) / 128 * 128);
+    return (double)total_bytes >= 0.9 * (double)P * (double)P * slot_bytes;
+}
+__device__ __forceinline__ bool no_places(const PlaceArgs& a) {
+    if (!a.verdict) return false;
+    const Status& st = *a.st;
+    return (st.flags & 7u) || st.total_bytes == 0 || st.max_count > a.max_block || (a.slots_rule && slots_are_full(st.total_bytes, a.P, st.max_count));
+}
+// Sum over a workgroup of kScanThreads, in its thread 0.
+__device__ __forceinline__ unsigned long long block_sum(unsigned long long v, unsigned long long* wsum) {
+    v = last_lane<kWave>(v, 0ull, AddOp());
+    __syncthreads();                                      // wsum of the sum before is consumed
+    if ((threadIdx.x & (kWave - 1)) == kWave - 1) wsum[threadIdx.x / kWave] = v;
+    __syncthreads();
+    v = 0;
+#pragma unroll
+    for (int k = 0; k < kScanThreads / kWave; ++k) v += wsum[k];
+    return v;
+}
+// Payload bytes and chunks, cut at the 16-byte boundaries of R, of the blocks that receiver p gets for good in phase x: this
+// thread's share, one in `threads`.
+__device__ __forceinline__ void final_shares(const PlaceArgs& a, int p, int x, int thread, int threads, unsigned long long& bytes,
+                                             unsigned long long& chunks) {
+    const int P = a.P, hi = a.fin[x + 1];
+    int pn, pg;
+    split_slot_index(p, a.Q, a.N, pn, pg);
+    bytes = chunks = 0;
+#pragma unroll 4
+    for (int e = a.fin[x] + thread; e < hi; e += threads) {
+        int j, l;
+        split_slot_index(e, a.Q, a.N, j, l);
+        int sn = pn + j; if (sn >= a.N) sn -= a.N;
+        int sg = pg + l; if (sg >= a.Q) sg -= a.Q;
+        const size_t at = (size_t)p * P + sn * a.Q + sg;
+        const int n = a.recvcounts[at];
+        const unsigned int head = (unsigned int)((unsigned long long)a.R + (unsigned long long)a.rdispls[at]) & 15u;
+        bytes += (unsigned long long)(unsigned int)n;
+        chunks += n > 0 ? (head + (unsigned int)n + 15u) >> 4 : 0u;
+    }
+}
+__device__ __forceinline__ void final_totals(const PlaceArgs& a, int p, int x) {
+    __shared__ unsigned long long s_sum[kScanThreads / kWave];
+    unsigned long long bytes, chunks;
+    final_shares(a, p, x, threadIdx.x, kScanThreads, bytes, chunks);
+    bytes = block_sum(bytes, s_sum);
+    chunks = block_sum(chunks, s_sum);
+    if (threadIdx.x == 0) a.part[(size_t)(a.rows + x) * a.P + p] = make_ulonglong2(bytes, chunks);
+}
+// k_row_totals: the totals of a linear schedule's only phase, a wave per receiver.  Validation has cleared them.
+__global__ void __launch_bounds__(kScanThreads) k_row_totals(const PlaceArgs a) {
+    __shared__ unsigned long long s_sum[kScanThreads / kWave];
+    if (no_places(a)) return;
+    const int lane = threadIdx.x & (kWave - 1), p = blockIdx.x * (kScanThreads / kWave) + threadIdx.x / kWave;
+    unsigned long long bytes = 0, chunks = 0;
+    if (p < a.P) {
+        final_shares(a, p, 0, lane, kWave, bytes, chunks);
+        chunks = last_lane<kWave>(chunks, 0ull, AddOp());
+        chunks = lane == kWave - 1 ? (chunks + kRankAlignChunks - 1) / kRankAlignChunks * kRankAlignChunks : 0;
+    }
+    bytes = block_sum(bytes, s_sum);
+    chunks = block_sum(chunks, s_sum);
+    if (threadIdx.x == 0) { atomicAdd(&a.st->phase_bytes[0], bytes); atomicAdd(&a.st->phase_chunks[0], chunks); }
+}
+// The totals of phase x from those, every receiver's chunks rounded up to a line as the staging layouts round them.
+__device__ __forceinline__ void phase_totals(const PlaceArgs& a, int x) {
+    __shared__ unsigned long long s_sum[kScanThreads / kWave];
+    int lo = 0, hi = 0;                                   // its class rows
+    for (int f = 0; f < a.nph; ++f)
+        if (a.ph[f].phase == x) { lo = a.ph[f].first; hi = f + 1 < a.nph ? a.ph[f + 1].first : a.rows; }
+    unsigned long long bytes = 0, chunks = 0;
+    for (int p = threadIdx.x; p < a.P; p += kScanThreads) {
+        ulonglong2 v = a.part[(size_t)(a.rows + x) * a.P + p];
+        unsigned long long c = v.y;
+        bytes += v.x;
+#pragma unroll 4
+        for (int k = lo; k < hi; ++k) { v = a.part[(size_t)k * a.P + p]; bytes += v.x; c += v.y; }
+        chunks += (c + kRankAlignChunks - 1) / kRankAlignChunks * kRankAlignChunks;
+    }
+    bytes = block_sum(bytes, s_sum);
+    chunks = block_sum(chunks, s_sum);
+    if (threadIdx.x == 0) { a.st->phase_bytes[x] = bytes; a.st->phase_chunks[x] = chunks; }
+}
 __device__ __forceinline__ int place_phase(const PlaceArgs& a, int row) {
     int f = 0;
     while (f + 1 < a.nph && a.ph[f + 1].first <= row) ++f;
@@ -1369,8 +1463,11 @@ __device__ __forceinline__ int place_phase(const PlaceArgs& a, int row) {
 }
 __global__ void __launch_bounds__(kScanThreads) k_t_places(const PlaceArgs a) {
     __shared__ int wsum[kScanThreads / kWave];
+    __shared__ unsigned long long s_sum[kScanThreads / kWave];
     const int p = blockIdx.x, P = a.P;
     if ((int)blockIdx.y == a.own) { own_block(a.S, a.sendcounts, a.sdispls, a.R, a.rdispls, P, p); return; }
+    if (no_places(a)) return;
+    if ((int)blockIdx.y >= a.rows) { final_totals(a, p, blockIdx.y - a.rows); return; }
     const int f = place_phase(a, blockIdx.y);
     const PlacePhase& ph = a.ph[f];
     const int32_t* cls = ph.tcls + 3 * (blockIdx.y - ph.first);
@@ -1379,6 +1476,7 @@ __global__ void __launch_bounds__(kScanThreads) k_t_places(const PlaceArgs a) {
     split_slot_index(p, a.Q, a.N, pn, pg);
     int* pos_t = a.x.tpos + ((size_t)ph.phase * P + p) * P;
     int carry = 0;
+    unsigned long long bytes = 0;
     for (int base = 0; base < cn; base += kScanThreads * kScanItems) {
         int ct[kScanItems], sg[kScanItems];
 #pragma unroll
@@ -1389,6 +1487,7 @@ __global__ void __launch_bounds__(kScanThreads) k_t_places(const PlaceArgs a) {
             split_slot_index(ph.e[sg[k]], a.Q, a.N, j, l);
             const int n = *block_bytes(a.sendcounts, a.recvcounts, ph.src[sg[k]] < 0, pn, pg, j, l, P, a.Q, a.N, ph.dim, ph.rx1);
             ct[k] = i < cn ? (n + 15) >> 4 : 0;
+            bytes += i < cn ? (unsigned long long)(unsigned int)n : 0ull;
         }
         int run[kScanItems];
         block_scan_batch(ct, run, carry, wsum);
@@ -1396,7 +1495,10 @@ __global__ void __launch_bounds__(kScanThreads) k_t_places(const PlaceArgs a) {
         for (int k = 0; k < kScanItems; ++k)
             if (base + scan_item_index(k) < cn) pos_t[sg[k]] = run[k];
     }
-    if (threadIdx.x == 0) a.x.csub[(size_t)cid * P + p] = carry;
+    if (a.part) bytes = block_sum(bytes, s_sum);
+    if (threadIdx.x != 0) return;
+    a.x.csub[(size_t)cid * P + p] = carry;
+    if (a.part) a.part[(size_t)blockIdx.y * P + p] = make_ulonglong2(bytes, (unsigned long long)carry);
 }
 constexpr int kPlaceSlotRanks = 8192;       // 48 KiB of LDS
 constexpr int kPlaceSlotRadix = 8;
@@ -1404,10 +1506,13 @@ constexpr int kPlaceSlotRadix = 8;
 __global__ void __launch_bounds__(kScanThreads) k_t_places_slots(const PlaceArgs a) {
     extern __shared__ int s_val[];                       // bytes by index inside the class
     __shared__ int wsum[kScanThreads / kWave];
+    __shared__ unsigned long long s_sum[kScanThreads / kWave];
     constexpr int kNone = 0xffff;
     unsigned short* s_at = reinterpret_cast<unsigned short*>(s_val + a.most);        // by slot index: the index inside the class
     const int p = blockIdx.x, P = a.P;
     if ((int)blockIdx.y == a.own) { own_block(a.S, a.sendcounts, a.sdispls, a.R, a.rdispls, P, p); return; }
+    if (no_places(a)) return;
+    if ((int)blockIdx.y >= a.rows) { final_totals(a, p, blockIdx.y - a.rows); return; }
     const int f = place_phase(a, blockIdx.y);
     const PlacePhase& ph = a.ph[f];
     const int32_t* cls = ph.tcls + 3 * (blockIdx.y - ph.first);
@@ -1436,12 +1541,14 @@ __global__ void __launch_bounds__(kScanThreads) k_t_places_slots(const PlaceArgs
     __syncthreads();
     int* pos_t = a.x.tpos + ((size_t)ph.phase * P + p) * P;
     int carry = 0;
+    unsigned long long bytes = 0;
     for (int base = 0; base < cn; base += kScanThreads * kScanItems) {
         int ct[kScanItems], sg[kScanItems];
 #pragma unroll
         for (int k = 0; k < kScanItems; ++k) {
             const int i = base + scan_item_index(k);
             ct[k] = i < cn ? (s_val[i] + 15) >> 4 : 0;
+            bytes += i < cn ? (unsigned long long)(unsigned int)s_val[i] : 0ull;
             sg[k] = ph.tord[c0 + min(i, cn - 1)];
         }
         int run[kScanItems];
@@ -1452,10 +1559,15 @@ __global__ void __launch_bounds__(kScanThreads) k_t_places_slots(const PlaceArgs
             if (i < cn) pos_t[sg[k]] = run[k];
         }
     }
-    if (threadIdx.x == 0) a.x.csub[(size_t)cid * P + p] = carry;
+    if (a.part) bytes = block_sum(bytes, s_sum);
+    if (threadIdx.x != 0) return;
+    a.x.csub[(size_t)cid * P + p] = carry;
+    if (a.part) a.part[(size_t)blockIdx.y * P + p] = make_ulonglong2(bytes, (unsigned long long)carry);
 }
 __global__ void __launch_bounds__(kScanThreads) k_t_bases(const PlaceArgs a) {
     __shared__ long long wc[kScanThreads / kWave];
+    if (no_places(a)) return;
+    if ((int)blockIdx.x >= a.rows) { phase_totals(a, blockIdx.x - a.rows); return; }
     const PlacePhase& ph = a.ph[place_phase(a, blockIdx.x)];
     const int cid = ph.tcls[3 * (blockIdx.x - ph.first)];
     class_base(a.x, cid, a.by_value ? a.cbase[cid] : a.x.cbase[cid], a.P, wc);
@@ -1623,7 +1735,7 @@ __device__ __forceinline__ void hop_direct(const DirectArgs& a) {
         }
         move_short<LPB, STREAM>(src, dst, n, (unsigned long long)r.seg.e, lds);
     }
-    if (!RESOLVED) {
+    if (!RESOLVED && a.part) {
 #pragma unroll
         for (int u = 0; u < SETS; ++u) {
 #pragma unroll
@@ -1709,6 +1821,7 @@ __global__ void __launch_bounds__(256) k_hop_pairs(const DirectArgs a) {
         }
         move_short<LPB, STREAM>(src, dst, n, (unsigned long long)r.recvcounts, lds);
     }
+    if (!a.part) return;
 #pragma unroll
     for (int u = 0; u < SETS; ++u) {
 #pragma unroll
@@ -1837,7 +1950,7 @@ __global__ void __launch_bounds__(256) k_hop_rows(const DirectArgs a) {
     bool final;
     find_block<DENSE, RESOLVED>(a, p, min(s0 + min(lane, a.segs - 1), a.seg_hi - 1), src, dst, n, exact, final);
     if (!in || n < 0) n = exact = 0;
-    if (!RESOLVED) {
+    if (!RESOLVED && a.part) {
         unsigned int b = (unsigned int)exact, c = n > 0 ? ((final ? (unsigned int)(dst & 15ull) : 0u) + (unsigned int)exact + 15u) >> 4 : 0u;
 #pragma unroll
         for (int d = kWave / 2; d > 0; d >>= 1) { b += __shfl_xor(b, d, kWave); c += __shfl_xor(c, d, kWave); }
@@ -1933,7 +2046,7 @@ struct LongArgs {
     DirectArgs d;
     ulonglong2* units;      // x: source; y: destination, bytes << 48; kLongInside, kLongInT
     unsigned int* count;    // starts at zero
-    unsigned long long* bytes;          // of the phase (Status)
+    unsigned long long* bytes;          // of the phase (Status; null: not wanted)
     unsigned long long* chunks;
     int own;                // 1: the ranks' own blocks too
 };
@@ -2003,7 +2116,7 @@ __global__ void __launch_bounds__(kScanThreads) k_long_units(const LongArgs a) {
     if (tid == 0) {
         for (int w = 1; w < kScanThreads / kWave; ++w) { bytes += w_b[w]; chunks += w_c[w]; }
         chunks = (chunks + kRankAlignChunks - 1) / kRankAlignChunks * kRankAlignChunks;
-        if (bytes) { atomicAdd(a.bytes, bytes); atomicAdd(a.chunks, chunks); }
+        if (bytes && a.bytes) { atomicAdd(a.bytes, bytes); atomicAdd(a.chunks, chunks); }
     }
 }
 

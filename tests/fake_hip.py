@@ -252,6 +252,28 @@ def case_sequence(t, seed, steps):
     return {"calls": calls, "late": late[:5], "violations": t.fake.fake_violations()}
 
 
+def case_early(t, calls):
+    """The kernels of each of `calls` in turn, [P, radix, longest block, mode], without those of new schedules; and whether the host has
+    waited for them all when the call returns."""
+    out = []
+    for P, radix, longest, staged, wrong in calls:
+        counts = np.random.default_rng(P).integers(0, longest + 1, (P, P))
+        counts[0, P - 1] = longest
+        prob = t.problem(counts, gap=1)
+        if wrong:
+            prob[0].sendcounts[1, 2] += 4
+        first = t.fake.fake_notes()
+        rc = t.call(prob, radix, S1, mode=t.b.TUNA_MODE_STAGED if staged else t.b.TUNA_MODE_FUSED, t_layout=t.b.TUNA_T_EXACT)
+        assert rc == (t.b.TUNA_ERR_COUNT_MISMATCH if wrong else 0)
+        done = t.fake.fake_length(S1)
+        out.append([[k[0] for k in t.kernels(first) if not k[0].startswith("k_build")], None])
+        nothing = t.problem(np.zeros((4, 4)))
+        at = t.fake.fake_notes()
+        assert t.call(nothing, 2, S2) == 0                     # (its first kernel is behind what the host has waited for)
+        out[-1][1] = t.fake.fake_before(at, S1) >= done
+    return out
+
+
 CASES = {k[5:]: f for k, f in list(globals().items()) if k.startswith("case_")}
 
 if __name__ == "__main__":

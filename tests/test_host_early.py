@@ -1,0 +1,44 @@
+"""Kernels of a call that run while the host waits for what validation found, on a runtime that runs none (fake_hip.cpp)."""
+import os
+import shutil
+
+import pytest
+
+import fake_hip
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None or not os.path.exists("/opt/rocm/include/hip/hip_runtime_api.h"),
+                                reason="needs g++ and the HIP headers")
+
+
+@pytest.fixture(scope="module")
+def runtime(tmp_path_factory):
+    return fake_hip.build(str(tmp_path_factory.mktemp("fake_hip")))
+
+
+def _hops(kernels):
+    return [k for k in kernels if k.startswith("k_hop")]
+
+
+@pytest.mark.parametrize("P,radix,longest", [(100, 4, 300), (100, 100, 300), (100, 4, 60), (200, 14, 200), (100, 100, 60), (300, 2, 60), (600, 25, 60)])
+def test_a_call_finds_its_places_early_once_there_is_memory(runtime, P, radix, longest):
+    """And, of up to 512 ranks, the totals of its phases: no partial sums to add up at its end.  (300 ranks, radix 2: more classes than
+    the host adds up itself.)"""
+    (first, _), (second, _) = fake_hip.run(runtime, "early", [[P, radix, longest, 0, 0]] * 2)
+    assert first[-1] == "k_phase_sums" and (second[-1] == "k_phase_sums") == (P > 512)
+    assert _hops(first) == _hops(second) and "k_self_copy" not in second
+    early = [k for k in second if k.startswith("k_t_places") or k == "k_row_totals"]
+    assert len(early) == 1 and (early[0] == "k_row_totals") == (radix == P) == ("k_t_bases" not in second)
+    assert second.index(early[0]) == (2 if "k_validate_finish" in second else 1)
+
+
+def test_places_found_in_memory_that_is_replaced_are_found_again(runtime):
+    """The own blocks' layout makes the metadata of long blocks larger than what was there when validation began."""
+    (_, _), (kernels, _), (again, _) = fake_hip.run(runtime, "early", [[48, 2, 300, 0, 0], [48, 2, 900000, 0, 0], [48, 2, 900000, 0, 0]])
+    assert kernels.count("k_t_places") == 2 and again.count("k_t_places") == 1
+    assert _hops(kernels) == _hops(again) == ["k_hop_long"] * 6
+
+
+@pytest.mark.parametrize("P,radix", [(100, 4), (100, 100), (600, 25)])
+def test_a_refused_call_has_ended(runtime, P, radix):
+    (_, _), (kernels, done) = fake_hip.run(runtime, "early", [[P, radix, 60, 0, 0], [P, radix, 60, 0, 1]])
+    assert any(k.startswith("k_t_places") or k == "k_row_totals" for k in kernels) and not _hops(kernels) and done
