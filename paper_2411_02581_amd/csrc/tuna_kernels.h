@@ -1775,7 +1775,9 @@ __global__ void __launch_bounds__(256) k_hop_senders(const DirectArgs a) { hop_d
 //   The tile: up to 16 bytes 32 x 32 (2 x 2 blocks per lane instead of 4: 3000 176; 64 senders 173, 16 178).  Up to 64 bytes 16 x 16,
 // and 8 x 32 where blocks share no 16 bytes and the runs of S that a tile reads count (FFT 1568 with 16 x 16, 1474; P = 5000 823 and
 // 836, Zipf up to 64, P = 6000 803 and 886; 32 x 8 everywhere slower).  Up to 256 bytes 64 x 4, one receiver's stores per wave (16 x 16:
-// P = 1000 86, but 2500 422).  The next step's lookups before this one's payload: no difference.
+// P = 1000 86, but 2500 422).  The next step's lookups before this one's payload: no difference; but its sizes alone (AHEAD) let a wave
+// pass over a step in which nothing is sent without its displacements, 16 bytes a pair: FFT, P = 8192 1461 / 1382, P = 3000 221 / 215, others
+// the same, up to 16 bytes, P = 3000, where registers count, 170 / 175.
 // ------------------------------------------------------------------------------------------
 // the tile of one workgroup and step: senders side by side, and blocks a lane finds (of neighbouring receivers)
 struct PairShape { int senders, sets; };
@@ -1796,14 +1798,29 @@ __global__ void __launch_bounds__(256) k_hop_pairs(const DirectArgs a) {
 #pragma unroll
     for (int u = 0; u < SETS; ++u) sum_b[u] = sum_c[u] = 0;
     const int first = blockIdx.x * a.iters * SEND, last = min(P, first + a.iters * SEND);
+    constexpr bool AHEAD = LPB > 1;
+    int next[SETS];                                      // AHEAD: the bytes of the next step's blocks
+#pragma unroll
+    for (int u = 0; u < SETS; ++u)
+        if (AHEAD) next[u] = r.recvcounts[(size_t)min(p0 + u, P - 1) * P + min(first + sub, P - 1)];
     for (int q0 = first; q0 < last; q0 += SEND) {
         const int q = min(q0 + sub, P - 1);
         int n[SETS];
         long long va[SETS], vc[SETS];
+        if (AHEAD) {
+            bool some = q0 == first;                     // (the first step does not wait for its sizes)
+#pragma unroll
+            for (int u = 0; u < SETS; ++u) {
+                n[u] = next[u];
+                next[u] = r.recvcounts[(size_t)min(p0 + u, P - 1) * P + min(q0 + SEND + sub, last - 1)];
+                if (q0 != first) some = some || n[u] > 0;
+            }
+            if (!__ballot(some)) continue;
+        }
 #pragma unroll
         for (int u = 0; u < SETS; ++u) {
             const int p = min(p0 + u, P - 1);
-            n[u] = r.recvcounts[(size_t)p * P + q];
+            if (!AHEAD) n[u] = r.recvcounts[(size_t)p * P + q];
             va[u] = r.sdispls[(size_t)q * P + p];
             vc[u] = r.rdispls[(size_t)p * P + q];
         }
