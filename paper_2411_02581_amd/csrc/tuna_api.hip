@@ -108,6 +108,7 @@ struct Shared {
     bool ready = false;
     int device = -1;
     int num_cus = 256;
+    size_t max_lds = 0;                 // of one workgroup
     std::map<std::tuple<int, int, int, int, int, int>, DevicePlan> plans;
     int live_plans = 0;                 // persistent plans not yet freed (they point into `plans`)
     int live_contexts = 0;              // contexts made by tuna_ctx_create and not yet destroyed
@@ -177,6 +178,7 @@ int ensure_device() {
     hipDeviceProp_t prop;
     HIPCHK(hipGetDeviceProperties(&prop, sh.device));
     sh.num_cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
+    sh.max_lds = prop.sharedMemPerBlock / 16 * 16;
     sh.ready = true;
     return TUNA_OK;
 }
@@ -1889,8 +1891,12 @@ int run_tiny(Ctx& c, const void* sendbuf, const int32_t* sendcounts, const int64
     // the kernel keeps the size and displacement matrices and every phase's tables in LDS
     int table_entries = 0;
     for (int i = 0; i < a.nph; ++i) table_entries += pl.phases[i].nseg;
-    const size_t lds = tiny_lds_bytes(P, table_entries);
-    static_assert(tiny_lds_bytes(kTinyMaxRanks, kTinyMaxPhases * kTinyMaxRanks) <= 48 * 1024, "what a kernel may use without asking");
+    const size_t fixed = tiny_lds_bytes(P, table_entries);
+    static_assert(((size_t)3 * kTinyMaxRanks * kTinyMaxRanks + 4 * kTinyMaxPhases * kTinyMaxRanks + 3 * (kTinyMaxMoving + kTinyMovingPerPhase * kTinyMaxPhases)) * 4 < 60 * 1024,
+                  "what a kernel may use without asking");
+    static const size_t own = static_lds_of(k_tiny_call);
+    const size_t lds = pl.slots > 0 && sh.max_lds > fixed + own ? sh.max_lds - own : fixed;
+    a.entries = table_entries; a.moving = table_entries * P; a.t_lds = (int)(lds - fixed);
     hipLaunchKernelGGL(k_tiny_call, dim3(1), dim3(kTinyThreads), lds, s, a);
     HIPCHK(hipGetLastError());
     if (!c.sb.h_status_dev) HIPCHK(hipMemcpyAsync(c.sb.h_status, c.sb.d_status, 64, hipMemcpyDeviceToHost, s));

@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 #include <climits>
 #include <cstdint>
+#include <type_traits>
 
 #include "tuna_plan.h"
 
@@ -2843,20 +2844,24 @@ __global__ void __launch_bounds__(kCopyThreads) k_copy_tiled(const TiledCopyArgs
 // What a phase needs besides the payload is read from global memory once, at the start, all loads in
 // flight together, and kept in LDS: the rotated sizes, the low 32 bits of both displacement
 // matrices and the tables of every phase.  A block's size is looked up where the rotation left it (no
-// exchange between the phases).  A phase then costs one round trip to memory -- the
-// payload's -- instead of four dependent ones (tables, sizes, displacements, payload).
+// exchange between the phases).  Where every block of every phase is read from and stored to is then worked out at once, a thread per
+// block, and kept in LDS too; T lies there as well where it fits (the device has 160 KB a workgroup), as the 16-byte registers that
+// move a block, else in global memory.
 // The kernel declines -- writes tiny_done = 0 and moves nothing -- when the counts are invalid, when
 // the problem is not tiny after all (payload above kTinyMaxPayload, T above its capacity) or when a
 // displacement of a non-empty block does not fit into 32 bits; the host then takes the general path,
 // which reports the error or does the work.
-// Bound by latency: one workgroup, and per phase a round trip of the payload and a barrier behind its stores.  Without the
-// exchange and with 16 bytes per lane in place of 4 or 1: 16 ranks, r = 2 38 -> 34 us per call, 24 ranks byte-granular
-// 163 -> 61 us, 64 ranks linear byte-granular 250 -> 118 us.
+// Bound by the instructions of one workgroup and by latency: a call has 15 us of launch and wait, the kernel a round trip for the matrices, one
+// for S and R each, and 1 to 2 us per phase.  With 16 lanes that each worked out their block's place, phase by phase, that arithmetic
+// was most of the kernel (T in the LDS alone changed nothing).  Us per call, before / now: 16 ranks, up to 256 bytes, r = 2 34.0 /
+// 27.7, r = 4 30.9 / 25.8, linear 26.5 / 22.7; 24 ranks, r = 2, up to 60 bytes 50.9 / 40.7; 30 ranks, linear, up to 16 bytes 39.2 / 30.2; 4 x 4
+// ranks, up to 100 bytes 37.1 / 28.8.
 // Dynamic LDS: tiny_lds_bytes(P, total table entries).
 // ------------------------------------------------------------------------------------------
 constexpr int kTinyMaxRanks = 40;           // above it every schedule moves more blocks than run_tiny sends here
 constexpr int kTinyMaxPhases = 8;
 constexpr int kTinyThreads = 1024;
+constexpr int kTinyGroups = kTinyThreads / 16;
 constexpr unsigned long long kTinyMaxPayload = 1ull << 20;      // bytes
 struct TinyPhase {
     const int32_t* e;
@@ -2877,23 +2882,39 @@ struct TinyArgs {
     unsigned char* T;               // capacity t_capacity bytes
     long long slots;                // T slots per rank (both copies)
     unsigned long long t_capacity;
+    int entries;                    // table entries of all phases
+    int moving;                     // and blocks, P per entry
+    int t_lds;                      // bytes of LDS behind matrices and tables, for T if it fits
     Status* st;                     // the first 64 bytes are written; in pinned host memory, so that the host reads
                                     // them after the stream's synchronisation without a copy of its own
 };
 
-// three P x P arrays of 4 bytes (the sizes and two displacement matrices) and four ints per table entry
+// three P x P arrays of 4 bytes (the sizes and two displacement matrices), four ints per table entry and three per block that
+// moves, in whole chunks
 constexpr size_t tiny_lds_bytes(int P, int table_entries) {
-    return ((size_t)3 * P * P + (size_t)4 * table_entries) * 4;
+    return (((size_t)3 * P * P + (size_t)4 * table_entries + (size_t)3 * P * table_entries) * 4 + 15) / 16 * 16;
 }
 
-// one wave copies `n` bytes; dword granular when everything is 4-byte aligned, else byte by byte
-__device__ __forceinline__ void tiny_copy(unsigned char* dst, const unsigned char* src, int n, int lane) {
-    if ((((unsigned long long)dst | (unsigned long long)src | (unsigned long long)n) & 3ull) == 0) {
-        const uint32_t* s4 = reinterpret_cast<const uint32_t*>(src);
-        uint32_t* d4 = reinterpret_cast<uint32_t*>(dst);
-        for (int i = lane; i < (n >> 2); i += kWave) d4[i] = s4[i];
-    } else {
-        for (int i = lane; i < n; i += kWave) dst[i] = src[i];
+// A block of fewer than 16 bytes as one register of 16: the overlapping parts that short_load and short_store work with.
+__device__ __forceinline__ v4u short_pack(unsigned long long src, int n, unsigned long long dummy) {
+    const ShortBlock b = short_load(src, n, dummy);
+    v4u v = {b.x0, b.x1, 0u, 0u};
+    if (n >= 8) { v.x = (unsigned int)b.w0; v.y = (unsigned int)(b.w0 >> 32); v.z = (unsigned int)b.w1; v.w = (unsigned int)(b.w1 >> 32); }
+    else if (n > 0 && n < 4)
+        v.x = load_global<unsigned char>(src) | load_global<unsigned char>(src + (n >> 1)) << 8 | load_global<unsigned char>(src + n - 1) << 16;
+    return v;
+}
+__device__ __forceinline__ void short_unpack(unsigned long long dst, int n, v4u v) {
+    if (n >= 8) {
+        store_global<u64_any>(dst, (unsigned long long)v.y << 32 | v.x);
+        if (n > 8) store_global<u64_any>(dst + n - 8, (unsigned long long)v.w << 32 | v.z);
+    } else if (n >= 4) {
+        store_global<u32_any>(dst, v.x);
+        if (n > 4) store_global<u32_any>(dst + n - 4, v.y);
+    } else if (n > 0) {
+        store_global<unsigned char>(dst, (unsigned char)v.x);
+        store_global<unsigned char>(dst + (n >> 1), (unsigned char)(v.x >> 8));
+        store_global<unsigned char>(dst + n - 1, (unsigned char)(v.x >> 16));
     }
 }
 
@@ -2908,19 +2929,19 @@ __global__ void __launch_bounds__(kTinyThreads) k_tiny_call(const TinyArgs a) {
     int* tab = reinterpret_cast<int*>(rd32 + P2);                   // per phase: e[nseg], z[nseg], src[nseg], dst[nseg]
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     constexpr int kWaves = kTinyThreads / kWave;
-    // ---- the tables of every phase: requested first, so that they travel together with the matrices ------
-    {
-        int off = 0;
+    // ---- the tables of every phase, four ints per entry: requested first, so that they travel together with the matrices ----
+    auto table_entry = [&](int k) {
         for (int x = 0; x < a.nph; ++x) {
             const TinyPhase& ph = a.ph[x];
-            for (int k = tid; k < 4 * ph.nseg; k += kTinyThreads) {
+            if (k < 4 * ph.nseg) {
                 const int f = k / ph.nseg, s_ = k - f * ph.nseg;
-                const int32_t* srcp = f == 0 ? ph.e : (f == 1 ? ph.z : (f == 2 ? ph.src : ph.dst));
-                tab[off + k] = srcp[s_];
+                return (f == 0 ? ph.e : (f == 1 ? ph.z : (f == 2 ? ph.src : ph.dst))) + s_;
             }
-            off += 4 * ph.nseg;
+            k -= 4 * ph.nseg;
         }
-    }
+        return a.sendcounts;                                        // any int that can be read
+    };
+    const int entry = *table_entry(tid);
     // ---- validation, and the initial rotation (index only) on the way ---------------------------------------
     unsigned int flags = 0, abits = 0;
     int mx = 0;
@@ -2950,120 +2971,153 @@ __global__ void __launch_bounds__(kTinyThreads) k_tiny_call(const TinyArgs a) {
         sd32[k] = (unsigned int)sd;
         rd32[j * P + i] = (unsigned int)rd;
     }
-#pragma unroll
-    for (int d = kWave / 2; d > 0; d >>= 1) {
-        flags |= __shfl_xor(flags, d, kWave);
-        abits |= __shfl_xor(abits, d, kWave);
-        mx = max(mx, __shfl_xor(mx, d, kWave));
-        bytes += __shfl_xor(bytes, d, kWave);
-        chunks += __shfl_xor(chunks, d, kWave);
-        extent = max(extent, (unsigned long long)__shfl_xor(extent, d, kWave));
-    }
-    if (lane == 0) {
-        red[wv][0] = ((unsigned long long)flags << 40) | ((unsigned long long)(abits & 127u) << 32) | (unsigned int)mx;
+    if (tid < 4 * a.entries) tab[tid] = entry;
+    for (int k = tid + kTinyThreads; k < 4 * a.entries; k += kTinyThreads) tab[k] = *table_entry(k);
+    flags = last_lane<kWave>(flags << 8 | (abits & 127u), 0u, OrOp());
+    mx = (int)last_lane<kWave>((unsigned int)mx, 0u, MaxOp());
+    bytes = last_lane<kWave>(bytes, 0ull, AddOp());
+    chunks = last_lane<kWave>(chunks, 0ull, AddOp());
+    extent = last_lane<kWave>(extent, 0ull, MaxOp());
+    if (lane == kWave - 1) {
+        red[wv][0] = (unsigned long long)flags << 32 | (unsigned int)mx;
         red[wv][1] = bytes; red[wv][2] = chunks; red[wv][3] = extent;
     }
     __syncthreads();
-    long long slot_bytes = 0;
-    if (tid == 0) {
-        unsigned int fl = 0, ab = 0;
-        int m = 0;
-        unsigned long long by = 0, ch = 0, ex = 0;
-        for (int w = 0; w < kWaves; ++w) {
-            fl |= (unsigned int)(red[w][0] >> 40); ab |= (unsigned int)(red[w][0] >> 32) & 127u;
-            m = max(m, (int)(unsigned int)(red[w][0] & 0xffffffffull));
-            by += red[w][1]; ch += red[w][2]; ex = max(ex, red[w][3]);
+    if (wv == 0) {
+        static_assert(kWaves == 16, "a row of lanes");
+        const unsigned long long* r = red[lane & (kWaves - 1)];
+        const unsigned int fl = last_lane<kWaves>((unsigned int)(r[0] >> 32), 0u, OrOp()), m = last_lane<kWaves>((unsigned int)r[0], 0u, MaxOp());
+        const unsigned long long by = last_lane<kWaves>(r[1], 0ull, AddOp()), ch = last_lane<kWaves>(r[2], 0ull, AddOp());
+        const unsigned long long ex = last_lane<kWaves>(r[3], 0ull, MaxOp());
+        if (lane == kWaves - 1) {
+            const long long slot_bytes = ((long long)m + 15) / 16 * 16;
+            const unsigned long long t_need = (unsigned long long)P * (unsigned long long)a.slots * (unsigned long long)slot_bytes;
+            const bool ok = fl >> 8 == 0 && by <= kTinyMaxPayload && t_need <= a.t_capacity;
+            a.st->flags = fl >> 8 & 7u; a.st->align_bits = fl & 127u; a.st->max_count = (int)m; a.st->total_bytes = by; a.st->total_chunks = ch;
+            a.st->send_extent = ex; a.st->tiny_done = ok ? 1 : 0;
+            verdict = ok ? (int)m : -1;
         }
-        slot_bytes = ((long long)m + 15) / 16 * 16;
-        const unsigned long long t_need = (unsigned long long)P * (unsigned long long)a.slots * (unsigned long long)slot_bytes;
-        const bool ok = fl == 0 && by <= kTinyMaxPayload && t_need <= a.t_capacity;
-        a.st->flags = fl & 7u; a.st->align_bits = ab; a.st->max_count = m; a.st->total_bytes = by; a.st->total_chunks = ch;
-        a.st->send_extent = ex; a.st->tiny_done = ok ? 1 : 0;
-        verdict = ok ? m : -1;
     }
     __syncthreads();
     if (verdict < 0) return;                             // uniform: declined, nothing has moved
-    slot_bytes = ((long long)verdict + 15) / 16 * 16;
-    // ---- the ranks' own blocks ---------------------------------------------------------------------------------
-    for (int p = wv; p < P; p += kWaves) {
-        const int n = cur[p * P];                        // slot index 0: the block a rank keeps
-        if (n > 0) tiny_copy(a.R + rd32[p * P + p], a.S + sd32[p * P + p], n, lane);
-    }
-    // ---- digit phases ----------------------------------------------------------------------------------------
-    int off = 0;
-    const unsigned long long dummy = (unsigned long long)a.T;       // any 16 bytes that can be read
-    for (int x = 0; x < a.nph; ++x) {
+    const long long slot_bytes = ((long long)verdict + 15) / 16 * 16;
+    // ---- where every block of every phase is read from, stored to, and its bytes: a thread per block, all phases at once ----
+    unsigned int* d_src = reinterpret_cast<unsigned int*>(tab + 4 * a.entries);     // offset into S, or T
+    unsigned int* d_dst = d_src + a.moving;                                         // into R, or T
+    unsigned int* d_n = d_dst + a.moving;
+    constexpr unsigned int kSrcT = 1u << 30, kDstT = 1u << 31;                      // (blocks have no more than kTinyMaxPayload bytes)
+    for (int k0 = tid; k0 < a.moving; k0 += kTinyThreads) {
+        int x = 0, k = k0, off = 0;
+        while (k >= P * a.ph[x].nseg) { k -= P * a.ph[x].nseg; off += 4 * a.ph[x].nseg; ++x; }
         const int nseg = a.ph[x].nseg, dim = a.ph[x].dim, rx = a.ph[x].rx, rx1 = a.ph[x].rx1;
-        const int* te = tab + off;
-        const int* tz = te + nseg;
-        const int* ts = tz + nseg;
-        const int* td = ts + nseg;
-        off += 4 * nseg;
-        // the hops.  Sixteen lanes move one block; the 64 groups of the workgroup take the blocks 64 apart, two
-        // per step, so that the whole workgroup has loads in flight at once (with one thread per block and the
-        // copies done wave by wave, a phase of 128 blocks kept two waves busy and fourteen idle).  Every lane of
-        // a group resolves the block itself: source, destination and size come from LDS.
-        const int nb = P * nseg;
-        const int grp = tid >> 4, sub = tid & 15;
-        auto resolve = [&](int k, unsigned long long& src, unsigned long long& dst) -> int {
-            if (k >= nb) return 0;
-            const int q = k / nseg, s = k - q * nseg;
-            const int e = te[s];
-            int qn, qg, j, l;
-            split_slot_index(q, Q, N, qn, qg);
-            split_slot_index(e, Q, N, j, l);
-            // the block's size: in the rotated sizes of the rank it comes from, the digits up to this phase's away (see
-            // block_bytes); no exchange from phase to phase
-            int on0 = qn, og0 = qg + l;
-            if (dim == 0) og0 = qg + l % rx1;
-            else on0 = qn + j % rx1;
-            if (og0 >= Q) og0 -= Q;
-            if (on0 >= N) on0 -= N;
-            const int size = cur[(on0 * Q + og0) * P + e];
-            if (size <= 0) return 0;
-            const int sender = partner_up(qn, qg, Q, N, dim, tz[s] * rx);
-            const int ssrc = ts[s], sdst = td[s];
-            if (ssrc < 0) {
-                int sn, sg;
-                split_slot_index(sender, Q, N, sn, sg);
-                int dn = sn - j; if (dn < 0) dn += N;
-                int dg = sg - l; if (dg < 0) dg += Q;
-                src = (unsigned long long)(a.S + sd32[sender * P + dn * Q + dg]);
-            } else {
-                src = (unsigned long long)(a.T + ((long long)sender * a.slots + ssrc) * slot_bytes);
-            }
-            if (sdst < 0) {
-                int on = qn + j; if (on >= N) on -= N;
-                int og = qg + l; if (og >= Q) og -= Q;
-                dst = (unsigned long long)(a.R + rd32[q * P + on * Q + og]);
-            } else {
-                dst = (unsigned long long)(a.T + ((long long)q * a.slots + sdst) * slot_bytes);
-            }
-            return size;
-        };
-        for (int b0 = 0; b0 < nb; b0 += 2 * (kTinyThreads / 16)) {
-            unsigned long long sa = 0, da = 0, sb = 0, db = 0;
-            const int na = resolve(b0 + grp, sa, da);
-            const int nbb = resolve(b0 + kTinyThreads / 16 + grp, sb, db);
-            // 16 bytes per lane at the blocks' own alignment, the last ones ending with the block (as in k_hop_direct): a
-            // block of up to 256 bytes is one round trip
-            for (int o = sub * 16; o < max(na, nbb); o += 256) {
-                const bool wa = na >= 16 && o < na, wb = nbb >= 16 && o < nbb;
-                const int oa = min(o, na - 16), ob = min(o, nbb - 16);
-                const v4u va = load_global<v4u_any>(wa ? sa + oa : dummy);
-                const v4u vb = load_global<v4u_any>(wb ? sb + ob : dummy);
-                if (wa) store_global<v4u_any>(da + oa, va);
-                if (wb) store_global<v4u_any>(db + ob, vb);
-            }
-            if (sub == 0) {
-                const int sha = na < 16 ? na : 0, shb = nbb < 16 ? nbb : 0;
-                const ShortBlock ba = short_load(sa, sha, dummy), bb = short_load(sb, shb, dummy);
-                short_store(da, sa, sha, ba);
-                short_store(db, sb, shb, bb);
-            }
-        }
-        __syncthreads();                                  // the blocks stored into T are read in a later phase
+        const int q = k / nseg, s = k - q * nseg;
+        const int* t = tab + off + s;
+        const int e = t[0], ssrc = t[2 * nseg], sdst = t[3 * nseg];
+        int qn, qg, j, l;
+        split_slot_index(q, Q, N, qn, qg);
+        split_slot_index(e, Q, N, j, l);
+        // the block's size: in the rotated sizes of the rank it comes from, the digits up to this phase's away (see
+        // block_bytes); no exchange from phase to phase
+        int on0 = qn, og0 = qg + l;
+        if (dim == 0) og0 = qg + l % rx1;
+        else on0 = qn + j % rx1;
+        if (og0 >= Q) og0 -= Q;
+        if (on0 >= N) on0 -= N;
+        const int size = cur[(on0 * Q + og0) * P + e];
+        const int sender = partner_up(qn, qg, Q, N, dim, t[nseg] * rx);
+        int sn, sg;
+        split_slot_index(sender, Q, N, sn, sg);
+        int dn = sn - j; if (dn < 0) dn += N;
+        int dg = sg - l; if (dg < 0) dg += Q;
+        int on = qn + j; if (on >= N) on -= N;
+        int og = qg + l; if (og >= Q) og -= Q;
+        d_src[k0] = ssrc < 0 ? sd32[sender * P + dn * Q + dg] : (unsigned int)((sender * (int)a.slots + ssrc) * (int)slot_bytes);
+        d_dst[k0] = sdst < 0 ? rd32[q * P + on * Q + og] : (unsigned int)((q * (int)a.slots + sdst) * (int)slot_bytes);
+        d_n[k0] = (unsigned int)size | (ssrc < 0 ? 0u : kSrcT) | (sdst < 0 ? 0u : kDstT);
     }
+    __syncthreads();
+    // ---- digit phases; the ranks' own blocks go with the first ----------------------------------------------
+    const unsigned long long dummy = (unsigned long long)a.T;       // any 16 bytes that can be read
+    v4u* const t_lds = reinterpret_cast<v4u*>(tiny_lds + ((3 * P2 + 4 * a.entries + 3 * a.moving + 3) & ~3));
+    auto run_phases = [&](auto t_in_lds) {
+        constexpr bool LDS = decltype(t_in_lds)::value;
+        int first = 0;
+        for (int x = 0; x == 0 || x < a.nph; ++x) {
+            // the hops.  Sixteen lanes move one block; the 64 groups of the workgroup take the blocks 64 apart, two
+            // per step, so that the whole workgroup has loads in flight at once (with one thread per block and the
+            // copies done wave by wave, a phase of 128 blocks kept two waves busy and fourteen idle).
+            const int nb = a.nph ? P * a.ph[x].nseg : 0;
+            const int grp = tid >> 4, sub = tid & 15;
+            // COUNT blocks per group: the first two of the phase, the third, in the first step, the one that a rank keeps
+            auto step = [&](auto count, int b0) {
+                constexpr int COUNT = decltype(count)::value;
+                unsigned long long src[COUNT], dst[COUNT];       // addresses, or with LDS offsets into the T there
+                bool src_t[COUNT], dst_t[COUNT];
+                int n[COUNT], most = 0;
+#pragma unroll
+                for (int u = 0; u < COUNT; ++u) {
+                    src_t[u] = dst_t[u] = false;
+                    if (u < 2) {
+                        const int b = b0 + u * kTinyGroups + grp, k = b < nb ? first + b : 0;
+                        const unsigned int w = b < nb ? d_n[k] : 0u;
+                        n[u] = (int)(w & (kSrcT - 1));
+                        src_t[u] = LDS && (w & kSrcT); dst_t[u] = LDS && (w & kDstT);
+                        src[u] = d_src[k] + (w & kSrcT ? LDS ? 0ull : (unsigned long long)a.T : (unsigned long long)a.S);
+                        dst[u] = d_dst[k] + (w & kDstT ? LDS ? 0ull : (unsigned long long)a.T : (unsigned long long)a.R);
+                    } else {
+                        const int p = min(grp, P - 1), d = p * P + p;
+                        src[u] = (unsigned long long)(a.S + sd32[d]);
+                        dst[u] = (unsigned long long)(a.R + rd32[d]);
+                        n[u] = grp < P ? cur[p * P] : 0;             // slot index 0
+                    }
+                    most = max(most, n[u]);
+                }
+                // 16 bytes per lane at the blocks' own alignment, the last ones ending with the block (as in k_hop_direct): a
+                // block of up to 256 bytes is one round trip.  T in the LDS holds these registers one after the other.
+                for (int o = sub * 16; o < most; o += 256) {
+                    v4u v[COUNT];
+#pragma unroll
+                    for (int u = 0; u < COUNT; ++u) {
+                        const bool w = n[u] >= 16 && o < n[u];
+                        v[u] = load_global<v4u_any>(w && !src_t[u] ? src[u] + (unsigned int)min(o, n[u] - 16) : dummy);
+                        if (LDS && u < 2) {
+                            const v4u from_t = t_lds[w && src_t[u] ? (int)(src[u] + o) >> 4 : 0];
+                            v[u] = src_t[u] ? from_t : v[u];
+                        }
+                    }
+#pragma unroll
+                    for (int u = 0; u < COUNT; ++u) {
+                        if (n[u] < 16 || o >= n[u]) continue;
+                        if (dst_t[u]) t_lds[(int)(dst[u] + o) >> 4] = v[u];
+                        else store_global<v4u_any>(dst[u] + (unsigned int)min(o, n[u] - 16), v[u]);
+                    }
+                }
+                bool shorts = false;
+#pragma unroll
+                for (int u = 0; u < COUNT; ++u) { if (n[u] >= 16 || sub != 0) n[u] = 0; shorts = shorts || n[u] > 0; }
+                if (__ballot(shorts)) {
+                    v4u v[COUNT];
+#pragma unroll
+                    for (int u = 0; u < COUNT; ++u) {
+                        v[u] = short_pack(src[u], src_t[u] ? 0 : n[u], dummy);
+                        if (src_t[u] && n[u] > 0) v[u] = t_lds[(int)src[u] >> 4];
+                    }
+#pragma unroll
+                    for (int u = 0; u < COUNT; ++u) {
+                        if (dst_t[u]) { if (n[u] > 0) t_lds[(int)dst[u] >> 4] = v[u]; }
+                        else short_unpack(dst[u], n[u], v[u]);
+                    }
+                }
+            };
+            static_assert(kTinyMaxRanks <= kTinyGroups, "a group per rank");
+            if (x == 0) step(std::integral_constant<int, 3>(), 0);
+            for (int b0 = x == 0 ? 2 * kTinyGroups : 0; b0 < nb; b0 += 2 * kTinyGroups) step(std::integral_constant<int, 2>(), b0);
+            first += nb;
+            __syncthreads();                                  // the blocks stored into T are read in a later phase
+        }
+    };
+    if (a.slots > 0 && a.t_lds >= 16 && (long long)P * a.slots * slot_bytes <= (long long)a.t_lds) run_phases(std::true_type());
+    else run_phases(std::false_type());
 }
 
 }  // namespace tuna
