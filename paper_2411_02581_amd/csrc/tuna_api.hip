@@ -85,6 +85,7 @@ struct StatusBufs {
     unsigned long long* h_part = nullptr;      // the partial results in pinned memory, where few workgroups write them for
     unsigned long long* h_part_dev = nullptr;  // the host to fold (nullptr: none, k_validate_finish folds them); behind them
                                                // kMailWords words: the last ticket handed out, and the last one received
+    unsigned long long* h_rows = nullptr;      // without pinned memory: where the few workgroups' results are copied to
     long long* h_cbase = nullptr;              // kMaxClasses words that upload_cbase sends from (pinned, behind those)
     bool sums_clear = false;                   // the class sums have been cleared by an earlier kernel of this call
     int num_cus = 256;
@@ -353,11 +354,13 @@ void carve_tables(Carver& cv, DevicePlan& dp) {
 }
 
 // Launches the kernels that fill a schedule's device tables (d_seg to d_mask, whose memory is there), and clears n_zero words.
-int launch_tables(const DevicePlan& dp, unsigned long long* zero, int n_zero, hipStream_t s) {
+// (A workgroup goes through all slot indices twice for the list of a class: not beyond kListRanks of them.)
+constexpr int kListRanks = 1024;
+int launch_tables(const DevicePlan& dp, bool by_index, unsigned long long* zero, int n_zero, hipStream_t s) {
     const int nph = (int)dp.host.phases.size();
     for (int f = 0; f < std::max(nph, 1); f += kBuildPhases) {
         BuildArgs a{};
-        a.pl = dp.host.sc; a.first = f; a.mask = dp.d_mask; a.zero = zero; a.n_zero = f ? 0 : n_zero;
+        a.pl = dp.host.sc; a.first = f; a.rows = std::min(kBuildPhases, nph - f); a.mask = dp.d_mask; a.zero = zero; a.n_zero = f ? 0 : n_zero;
         const int n = std::min(kBuildPhases, nph - f);
         bool classes = false;
         for (int i = 0; i < n; ++i) {
@@ -367,9 +370,10 @@ int launch_tables(const DevicePlan& dp, unsigned long long* zero, int n_zero, hi
             classes = classes || !dp.tcls[f + i].empty();
         }
         if (n <= 0) return TUNA_OK;                       // one rank: nothing moves
-        hipLaunchKernelGGL(k_build_tables, dim3((unsigned)((dp.host.P + 255) / 256), (unsigned)n), dim3(256), 0, s, a);
+        const bool lists = classes && by_index && n == nph && dp.host.P <= kListRanks;
+        hipLaunchKernelGGL(k_build_tables, dim3((unsigned)((dp.host.P + 255) / 256), (unsigned)(n + (lists ? class_count(nph) : 0))), dim3(256), 0, s, a);
         HIPCHK(hipGetLastError());
-        if (!classes) continue;
+        if (!classes || lists) continue;
         hipLaunchKernelGGL(k_build_classes, dim3((unsigned)(nph - 1 - f), (unsigned)n), dim3(kWave), 0, s, a);
         HIPCHK(hipGetLastError());
     }
@@ -412,7 +416,7 @@ int get_plan(int P, int Q, int rl, int rg, bool fused, bool by_index, hipStream_
         HIPCHK(hipMalloc(&dp.mem, bytes));
         Carver cv(dp.mem, bytes);
         carve_tables(cv, dp);
-        if (const int rc = launch_tables(dp, nullptr, 0, s)) return rc;
+        if (const int rc = launch_tables(dp, by_index, nullptr, 0, s)) return rc;
         dp.built_on = s;
         guard.dp = nullptr;
         it = sh.plans.emplace(key, std::move(dp)).first;
@@ -622,10 +626,11 @@ int run_validate(const StatusBufs& sb, const int32_t* sendcounts, const int32_t*
     const int nph = exact_t_for ? (int)exact_t_for->host.phases.size() : 0;
     const int ncls = class_count(nph);
     // Few workgroups: their rows go straight to pinned memory and the host adds them up.  More rows would take longer to
-    // cross the bus and to add up than the two kernels and the copy they save (about 20 us).
-    const bool fold = sb.h_part_dev && vgrid <= (unsigned)kValFoldRows && ncls <= kValFoldClasses;
+    // cross the bus and to add up than the two kernels and the copy they save (about 20 us).  The call that allocates nothing has no
+    // pinned memory and copies the rows: a kernel less between it and the host (up to 792 bytes, P = 61, linear 54 -> 51.5 us).
+    const bool fold = (sb.h_part_dev || sb.h_rows) && vgrid <= (unsigned)kValFoldRows && ncls <= kValFoldClasses;
     const bool mail = sb.h_part_dev && sb.h_status_dev;
-    const unsigned long long ticket = sb.h_part ? ++sb.h_part[kMailIssued] : 0;
+    const unsigned long long ticket = sb.h_part ? ++sb.h_part[kMailIssued] : 1;
     if (ncls > 0 && !fold && !mail && !sb.sums_clear) {
         hipLaunchKernelGGL(k_zero64, dim3((unsigned)((ncls + 255) / 256)), dim3(256), 0, s, sb.d_status->cls_chunks, ncls);
         HIPCHK(hipGetLastError());
@@ -633,7 +638,7 @@ int run_validate(const StatusBufs& sb, const int32_t* sendcounts, const int32_t*
     const int copies = ncls <= 104 ? kValCopies : ncls <= 208 ? kValCopies / 2 : 1;         // at most 26 KiB of LDS beside the tiles'; no schedule has more than 136
     const bool whole = recvcounts != nullptr;
     hipLaunchKernelGGL(whole ? k_validate<true> : k_validate<false>, dim3(vgrid), dim3(kValTile, kValRows), (size_t)ncls * copies * 8, s, sendcounts,
-                       recvcounts, sdispls, rdispls, P, fold ? sb.h_part_dev : sb.d_vpart, copies, exact_t_for ? exact_t_for->host.Q : 1,
+                       recvcounts, sdispls, rdispls, P, fold && sb.h_part_dev ? sb.h_part_dev : sb.d_vpart, copies, exact_t_for ? exact_t_for->host.Q : 1,
                        exact_t_for ? exact_t_for->host.N : 1, exact_t_for ? exact_t_for->d_mask : nullptr, nph, sb.d_status, fold ? ticket : 0ull,
                        clear_totals ? 1 : 0);
     HIPCHK(hipGetLastError());
@@ -644,9 +649,14 @@ int run_validate(const StatusBufs& sb, const int32_t* sendcounts, const int32_t*
         unsigned long long fa = 0, m = 0;
         h.total_bytes = h.total_chunks = h.send_extent = h.short_blocks = h.windows = 0;
         for (int i = 0; i < ncls; ++i) h.cls_chunks[i] = 0;
+        if (!sb.h_part_dev) {
+            HIPCHK(hipMemcpyAsync(sb.h_rows, sb.d_vpart, (size_t)vgrid * kValRow * 8, hipMemcpyDeviceToHost, s));
+            HIPCHK(hipStreamSynchronize(s));
+        }
         for (unsigned r = 0; r < vgrid; ++r) {
-            const unsigned long long* o = sb.h_part + (size_t)r * kValRow;
-            if (const int rc = wait_ticket(o + kValRow - 1, ticket, s)) return rc;
+            const unsigned long long* o = (sb.h_part_dev ? sb.h_part : sb.h_rows) + (size_t)r * kValRow;
+            if (sb.h_part_dev)
+                if (const int rc = wait_ticket(o + kValRow - 1, ticket, s)) return rc;
             fa |= o[0]; m = std::max(m, o[1]);
             h.total_bytes += o[2]; h.total_chunks += o[3]; h.send_extent = std::max(h.send_extent, o[4]);
             h.short_blocks += o[6]; h.windows = max_windows(h.windows, o[7]);
@@ -2383,6 +2393,7 @@ struct StaticState {
     int num_cus[kMaxDevices] = {};
     Status h_status;                          // host mirror of the status block (pageable: no pinned allocation)
     long long h_cbase[kMaxClasses];
+    unsigned long long h_rows[kValFoldRows * kValRow];
 };
 StaticState g_static;
 
@@ -2417,6 +2428,7 @@ int run_static(const void* sendbuf, const int32_t* sendcounts, const int64_t* sd
     pr.sb.d_vpart = cv.take<unsigned long long>(vpart_words(pr.sb.num_cus));
     pr.sb.h_status = &g_static.h_status;
     pr.sb.h_cbase = g_static.h_cbase;
+    pr.sb.h_rows = g_static.h_rows;
     pr.opt = sh.defaults;
     pr.opt.profile = 0;                       // no events are created here
     pr.fused = mode_is_fused(pr.opt);
@@ -2430,13 +2442,14 @@ int run_static(const void* sendbuf, const int32_t* sendcounts, const int64_t* sd
     int crl, crg;
     clamp_radices(Q, N, rl, rg, &crl, &crg);
     DevicePlan dp;
-    dp.host = make_plan(P, Q, crl, crg, pr.fused, /*with_tables=*/false, slot_order(pr.fused, pr.staggered, pr.block_count));
+    const bool by_index = slot_order(pr.fused, pr.staggered, pr.block_count);
+    dp.host = make_plan(P, Q, crl, crg, pr.fused, /*with_tables=*/false, by_index);
     if ((int)dp.host.phases.size() > TUNA_MAX_PHASES) return TUNA_ERR_TOO_LARGE;
     class_sizes(dp.host, dp.tcls);
     if (cv.off + table_bytes(dp) > cv.cap) return TUNA_ERR_NOALLOC_LIMIT;     // before any kernel is launched
     carve_tables(cv, dp);
     // the class sums that validation adds to are cleared on the way
-    rc = launch_tables(dp, pr.sb.d_status->cls_chunks, class_count((int)dp.host.phases.size()), s);
+    rc = launch_tables(dp, by_index, pr.sb.d_status->cls_chunks, class_count((int)dp.host.phases.size()), s);
     if (rc != TUNA_OK) return rc;
     pr.sb.sums_clear = true;
     dp.built_on = s;

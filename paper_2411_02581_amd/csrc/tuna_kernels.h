@@ -194,13 +194,63 @@ struct BuildArgs {
     PlanScalars pl;
     BuildPhase ph[kBuildPhases];
     int first;              // index of ph[0] in the schedule
+    int rows;               // phases here
     unsigned long long* mask;           // move_mask of every slot index
     unsigned long long* zero;           // n_zero words to clear on the way
     int n_zero;
 };
-// grid (ceil(P / 256), phases); the first row also fills `mask`
+// The lists of k_build_classes, by a workgroup of k_build_tables: where segments lie in the order of the slot indices the list of a
+// class needs no finished table.  f: the phase, y: the one that forwards the class.
+__device__ __forceinline__ void class_list(const BuildArgs& a, const BuildPhase& b, int f, int y) {
+    __shared__ int s_n[2][4];
+    __shared__ unsigned long long s_seen;
+    const PlanScalars& pl = a.pl;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    int before = 0, own = 0;
+    unsigned long long seen = 0;                         // classes before this one that have segments
+    if (tid == 0) s_seen = 0;
+    __syncthreads();
+    for (int e = tid; e < pl.P; e += 256) {
+        SegInfo s;
+        int pos;
+        if (!slot_entry(pl, b.ps, e, &s, &pos)) continue;
+        if (s.nxt_phase > f && s.nxt_phase < y) { ++before; seen |= 1ull << (s.nxt_phase - f - 1); }
+        own += s.nxt_phase == y;
+    }
+    before = last_lane<kWave>(before, 0, AddOp()); own = last_lane<kWave>(own, 0, AddOp());
+    if (lane == kWave - 1) { s_n[0][wv] = before; s_n[1][wv] = own; }
+    if (seen) atomicOr(&s_seen, seen);
+    __syncthreads();
+    before = s_n[0][0] + s_n[0][1] + s_n[0][2] + s_n[0][3];
+    own = s_n[1][0] + s_n[1][1] + s_n[1][2] + s_n[1][3];
+    seen = s_seen;
+    if (own == 0) return;
+    if (tid < 3) b.tcls[3 * __popcll(seen) + tid] = tid == 0 ? class_id(f, y, pl.nph) : tid == 1 ? before : own;
+    int at = before;
+    for (int e0 = 0; e0 < pl.P; e0 += 256) {
+        SegInfo s;
+        int pos = 0;
+        const bool in = e0 + tid < pl.P && slot_entry(pl, b.ps, min(e0 + tid, pl.P - 1), &s, &pos) && s.nxt_phase == y;
+        const unsigned long long mine = __ballot(in);
+        __syncthreads();                                 // s_n of the step before is consumed
+        if (lane == 0) s_n[0][wv] = __popcll(mine);
+        __syncthreads();
+        int here = at;
+        for (int w = 0; w < 4; ++w) { here += w < wv ? s_n[0][w] : 0; at += s_n[0][w]; }
+        if (in) b.tord[here + __popcll(mine & ((1ull << lane) - 1))] = pos;
+    }
+}
+// grid (ceil(P / 256), rows); the first row also fills `mask`.  More rows, one per class of the schedule behind those, stand in for k_build_classes: a
+// launch less for a call that may keep no schedule (with validation's results copied instead of folded by a kernel 87 -> 60 us, P = 200, r = 16).
 __global__ void __launch_bounds__(256) k_build_tables(const BuildArgs a) {
     const PlanScalars& pl = a.pl;
+    if ((int)blockIdx.y >= a.rows) {
+        if (blockIdx.x) return;
+        int f = 0, k = blockIdx.y - a.rows;
+        while (k >= pl.nph - 1 - f) { k -= pl.nph - 1 - f; ++f; }
+        class_list(a, a.ph[f], f, f + 1 + k);
+        return;
+    }
     const BuildPhase& b = a.ph[blockIdx.y];
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
     if (blockIdx.x == 0 && blockIdx.y == 0)
