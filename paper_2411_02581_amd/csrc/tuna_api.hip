@@ -142,6 +142,9 @@ struct Ctx {
     hipEvent_t stats_end = nullptr;     // the event that the statistics on file are complete with (ev_end, ev_start; nullptr: they are)
     unsigned char* tiny_t = nullptr;    // T of the one-kernel call for tiny problems (kTinyTBytes, allocated at its first use)
     const void* tiny_declined = nullptr; // sendcounts of the last problem that kernel declined: it is not asked again for it
+    std::tuple<int, int, int, int> tiny_asked{};     // the schedule (P, Q, radices) it was asked for last, its slots of T,
+    long long tiny_slots = 0;
+    int tiny_vain = 0;                   // and how often in vain since it took one
     bool device_totals = false;         // the per-phase totals of the statistics on file are still in *sb.d_status (an immediate call's)
     // pipelined calls (run_pipelined): the stream the metadata kernels run on, the event that lets it start, and one
     // event per phase that lets the phase's payload kernel start; made at the first such call
@@ -1857,7 +1860,13 @@ int run_once(Ctx& c, const Options& opt, const void* sendbuf, const int32_t* sen
 // launch and a synchronisation.  Only when everything was left to the library (mode, no batches, no
 // staggering, no profiling).  *done = false: the kernel declined (invalid counts, or not that small) and
 // nothing has moved; the caller goes on with the general path.
+// A program whose problems are of one kind asks in vain every time if they are not that small: after kTinyVain times the kernel is not asked
+// for that schedule until a problem comes that it would have taken (other inputs in each call: P = 10, 21 KB, r = 3 77 -> 51 us, P = 21, up to 12 KB, linear 79 -> 57).
 constexpr size_t kTinyTBytes = 4u << 20;
+constexpr int kTinyVain = 4;
+bool tiny_would_fit(int P, long long slots, const Status& hs) {
+    return hs.total_bytes <= kTinyMaxPayload && (unsigned long long)P * (unsigned long long)slots * (((unsigned long long)hs.max_count + 15) / 16 * 16) <= kTinyTBytes;
+}
 constexpr long long kTinyMaxMoving = 1200, kTinyMovingPerPhase = 200;       // blocks moved, over all ranks and phases
 int run_tiny(Ctx& c, const void* sendbuf, const int32_t* sendcounts, const int64_t* sdispls, void* recvbuf,
              const int32_t* recvcounts, const int64_t* rdispls, int P, int ranks_per_node, int rl, int rg,
@@ -1879,6 +1888,9 @@ int run_tiny(Ctx& c, const void* sendbuf, const int32_t* sendcounts, const int64
     long long moving = 0;
     for (const auto& ph : pl.phases) moving += (long long)ph.nseg * P;
     if (moving > kTinyMaxMoving + kTinyMovingPerPhase * (long long)pl.phases.size()) return TUNA_OK;
+    const auto schedule = std::make_tuple(P, Q, pl.rl, pl.rg);
+    if (c.tiny_asked != schedule) { c.tiny_asked = schedule; c.tiny_slots = pl.slots; c.tiny_vain = 0; }
+    if (c.tiny_vain >= kTinyVain) return TUNA_OK;
     *asked = true;
     if (!c.tiny_t) {
         const hipError_t e = hipMalloc((void**)&c.tiny_t, kTinyTBytes);
@@ -1913,7 +1925,8 @@ int run_tiny(Ctx& c, const void* sendbuf, const int32_t* sendcounts, const int64
     HIPCHK(hipStreamSynchronize(s));
     if (dp->built_on == s) dp->complete = true;
     const Status& hs = *c.sb.h_status;
-    if (!hs.tiny_done) return TUNA_OK;
+    if (!hs.tiny_done) { ++c.tiny_vain; return TUNA_OK; }
+    c.tiny_vain = 0;
     // statistics: the schedule's numbers; nothing is timed
     Prepared pr;
     pr.P = P; pr.Q = Q; pr.N = P / Q; pr.dp = dp; pr.fused = true;
@@ -1977,6 +1990,7 @@ int run_once(Ctx& c, const Options& opt, const void* sendbuf, const int32_t* sen
     int rc = prepare_call(c, opt, sendbuf, sendcounts, sdispls, recvbuf, recvcounts, rdispls, P, ranks_per_node, rl, rg,
                           s, pr, hs, &empty);
     if (rc != TUNA_OK) return rc;
+    if (c.tiny_vain >= kTinyVain && std::get<0>(c.tiny_asked) == P && tiny_would_fit(P, c.tiny_slots, hs)) c.tiny_vain = 0;
     tuna_stats_t& st = c.stats;
     fill_stats_header(pr, hs, st);
     if (empty) {
