@@ -974,8 +974,6 @@ int prepare_sizes(Prepared& pr, int dense_option, hipStream_t s, Status& hs, boo
                           (dense_option != 0 && has_t) ? pr.dp : nullptr, !pr.for_plan, pr.early_mem ? &pr : nullptr);
     if (rc != TUNA_OK) return rc;
     hs = *pr.sb.h_status;
-    // A refused call is done when it returns.
-    if (pr.early && ((hs.flags & 7u) || too_large(P, hs) || (hs.total_bytes && (!pr.sendbuf || !pr.recvbuf)))) HIPCHK(hipStreamSynchronize(s));
     if (pr.dp->built_on == s) pr.dp->complete = true;      // run_validate has waited for kernels of this stream behind the tables'
     if (hs.flags & 1u) return TUNA_ERR_NEGATIVE_COUNT;
     if (hs.flags & 2u) return TUNA_ERR_COUNT_MISMATCH;
@@ -1989,7 +1987,10 @@ int run_once(Ctx& c, const Options& opt, const void* sendbuf, const int32_t* sen
     }
     int rc = prepare_call(c, opt, sendbuf, sendcounts, sdispls, recvbuf, recvcounts, rdispls, P, ranks_per_node, rl, rg,
                           s, pr, hs, &empty);
-    if (rc != TUNA_OK) return rc;
+    if (rc != TUNA_OK) {
+        if (pr.early) HIPCHK(hipStreamSynchronize(s));        // a refused call is done when it returns
+        return rc;
+    }
     if (c.tiny_vain >= kTinyVain && std::get<0>(c.tiny_asked) == P && tiny_would_fit(P, c.tiny_slots, hs)) c.tiny_vain = 0;
     tuna_stats_t& st = c.stats;
     fill_stats_header(pr, hs, st);
@@ -2475,7 +2476,10 @@ int run_static(const void* sendbuf, const int32_t* sendcounts, const int64_t* sd
     Status hs{};
     bool empty = false;
     rc = prepare_sizes(pr, pr.opt.t_layout, s, hs, &empty);
-    if (rc != TUNA_OK) return rc;
+    if (rc != TUNA_OK) {
+        if (pr.early) HIPCHK(hipStreamSynchronize(s));
+        return rc;
+    }
     // the statistics on file (header only: nothing here is timed) are the default context's
     g.marks.clear();
     g.stats_end = nullptr;
