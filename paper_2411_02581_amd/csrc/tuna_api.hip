@@ -1880,9 +1880,11 @@ int run_tiny(Ctx& c, const void* sendbuf, const int32_t* sendcounts, const int64
     if (rc != TUNA_OK) return rc;
     const PlanHost& pl = dp->host;
     if ((int)pl.phases.size() > kTinyMaxPhases) return TUNA_OK;
-    // One workgroup moves 128 blocks at a time, about 20 ns a block; the general path costs a launch or two per phase but
-    // has the whole device.  Per call, one launch against the general path: 16 ranks r = 2 34 / 60 us, linear 16 26 / 46,
-    // 24 33 / 46, 32 42 / 46, 48 66 / 46, 64 118 / 49; r = 2 24 ranks 49 / 64, 32 ranks 73 / 66, 64 ranks 277 / 93.
+    // One workgroup takes about 14 ns a short block and moves 45 GB/s; the general path costs a launch or two per phase but
+    // has the whole device.  Per call, one launch against the general path, blocks of up to 16 / up to 250 bytes, us: linear, 240 blocks moved (16 ranks)
+    // 23 and 33 / 22 and 31, 552 (24) 27 and 27 to 32 / 25 and 28, 992 (32) 32 and 27 to 32 / 28 and 29, 1560 (40) 39 and 33 / 33 and 34; three phases, 1008 35
+    // and 36 / 31 and 34; five, 1248 40 and 46 / 35 and 43, 1792 46 and 48 / 39 and 44, 2560 55 and 47 / 44 and 45.  1 MiB of payload is the most it
+    // takes: at 16 ranks, r = 2, blocks of up to 2000 bytes 39 and 45, 8000 82 and 41.
     long long moving = 0;
     for (const auto& ph : pl.phases) moving += (long long)ph.nseg * P;
     if (moving > kTinyMaxMoving + kTinyMovingPerPhase * (long long)pl.phases.size()) return TUNA_OK;

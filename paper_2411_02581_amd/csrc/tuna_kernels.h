@@ -2233,7 +2233,7 @@ __global__ void __launch_bounds__(kWave) k_hop_long(const ulonglong2* __restrict
 // k_phase_sums: the partial sums of the phases that ran as k_hop_direct or k_hop_rows, rows[x] rows of P entries for
 // phase x, into the status block: payload bytes, and staged chunks with every receiver's share rounded up to a line
 // as the staging layouts round it.  Four threads per receiver, grid (ceil(P / 64), phases); k_validate_finish cleared
-// the totals.
+// the totals.  (Up to 512 ranks they mostly come from the counts instead, before the phases run: launch_early.)
 struct PhaseParts { const uint2* part[64]; int rows[64]; };
 __global__ void __launch_bounds__(256) k_phase_sums(PhaseParts parts, int P, Status* __restrict__ st) {
     __shared__ unsigned long long s_b[4][kWave], s_c[4][kWave];
