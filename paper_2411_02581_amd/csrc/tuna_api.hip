@@ -1687,6 +1687,7 @@ int launch_early(Prepared& pr, bool verdict, hipStream_t s) {
     carve_hop(cm, pr.P, hld, pr.hop);
     PlaceArgs a{};
     place_args(pr, a);
+    if (phases > 1 && !a.rows) return TUNA_OK;               // radix P - 1: nothing waits in T
     const bool totals = pr.P <= kEarlyTotalsRanks;
     if (totals) want_totals(pr, a);
     if (!cm.ok || (phases == 1 && !totals) || (size_t)(a.rows + a.nfin) * (size_t)pr.P * sizeof(ulonglong2) > hop_bytes_for(pr.P, hld)) return TUNA_OK;

@@ -5,6 +5,7 @@
 //     and host waits);
 //   - every pending copy whose pinned source the host or a kernel writes before it is done ("violations");
 //   - the bytes of device memory allocated.
+// A launch without a workgroup fails, as it does on a device.
 #include <hip/hip_runtime_api.h>
 #include <sys/mman.h>
 
@@ -43,6 +44,7 @@ Clock host;
 int violations = 0;
 u64 allocated = 0;
 long next_stream = 0x51000;
+hipError_t last_error = hipSuccess;
 u64 head[8];                            // flags << 32 | alignment, longest, bytes, chunks, extent, chunks in T, short blocks, windows
 
 void run(hipStream_t s, size_t upto) {
@@ -134,6 +136,7 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
 hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** a, size_t, hipStream_t s) {
     const std::string& n = names[f];
     const void* ptr = nullptr;
+    if (!grid.x || !grid.y || !grid.z) return last_error = hipErrorInvalidConfiguration;
     std::function<void()> op = [] {};
     auto is = [&](const char* k) { return n.find(std::to_string(std::strlen(k)) + k) != std::string::npos; };
     if (is("k_validate")) {
@@ -214,7 +217,7 @@ hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
     enqueue(s, [=] { run(ev.s, ev.upto); });
     return hipSuccess;
 }
-hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipGetLastError() { const hipError_t e = last_error; last_error = hipSuccess; return e; }
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipGetDeviceCount(int* n) { *n = 1; return hipSuccess; }
 hipError_t hipGetDeviceProperties(hipDeviceProp_t* p, int) { std::memset(p, 0, sizeof *p); p->multiProcessorCount = 256; return hipSuccess; }

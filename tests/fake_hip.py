@@ -274,6 +274,17 @@ def case_early(t, calls):
     return out
 
 
+def case_no_places(t, P, radix, before):
+    """The return code and kernels of a call whose blocks never wait in T: behind one of `before`, [ranks, radix], that leaves memory; with none,
+    as the call that allocates nothing."""
+    prob = t.problem(np.full((P, P), 40))
+    if before:
+        assert t.call(t.problem(np.full((before[0], before[0]), 40)), before[1], S1) == 0
+    first = t.fake.fake_notes()
+    rc = t.call(prob, radix, S1) if before else t.lib.tuna_alltoallv_noalloc(*prob[1], P, 0, radix, radix, S1)
+    return [rc, [k[0] for k in t.kernels(first) if not k[0].startswith("k_build")]]
+
+
 CASES = {k[5:]: f for k, f in list(globals().items()) if k.startswith("case_")}
 
 if __name__ == "__main__":

@@ -42,3 +42,10 @@ def test_places_found_in_memory_that_is_replaced_are_found_again(runtime):
 def test_a_refused_call_has_ended(runtime, P, radix):
     (_, _), (kernels, done) = fake_hip.run(runtime, "early", [[P, radix, 60, 0, 0], [P, radix, 60, 0, 1]])
     assert any(k.startswith("k_t_places") or k == "k_row_totals" for k in kernels) and not _hops(kernels) and done
+
+
+@pytest.mark.parametrize("P,radix,before", [(513, 512, [513, 2]), (600, 599, [700, 26]), (100, 99, [100, 4]), (513, 512, None), (400, 399, None)])
+def test_a_schedule_of_two_phases_without_t_has_no_places(runtime, P, radix, before):
+    """Radix P - 1: every block moves once, so there is nothing to find early."""
+    rc, kernels = fake_hip.run(runtime, "no_places", P, radix, before)
+    assert rc == 0 and len(_hops(kernels)) == 2 and not [k for k in kernels if k.startswith("k_t_")]

@@ -13,7 +13,7 @@ torch = pytest.importorskip("torch")
 CANARY = 0xA5
 
 
-@pytest.mark.parametrize("P,rpn,rl,rg", [(2, 0, 2, 2), (65, 0, 8, 8), (128, 0, 2, 2), (129, 0, 2, 2), (512, 0, 23, 23), (513, 0, 23, 23), (512, 0, 512, 512),
+@pytest.mark.parametrize("P,rpn,rl,rg", [(2, 0, 2, 2), (65, 0, 8, 8), (128, 0, 2, 2), (129, 0, 2, 2), (512, 0, 23, 23), (513, 0, 23, 23), (512, 0, 512, 512), (513, 0, 512, 512),
                                          (192, 12, 4, 4)])
 def test_sizes(P, rpn, rl, rg):
     if not torch.cuda.is_available():
