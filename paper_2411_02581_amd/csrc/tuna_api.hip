@@ -2020,25 +2020,19 @@ int run_once(Ctx& c, const Options& opt, const void* sendbuf, const int32_t* sen
         const DataSizes& ds = pr.ds;
         void *mbase, *dbase;
         if (c.user_ws) {
-            if (mbytes + ds.total > c.user_ws_bytes) {
-                if (early) HIPCHK(hipStreamSynchronize(s));
-                return TUNA_ERR_WORKSPACE_TOO_SMALL;
-            }
+            if (mbytes + ds.total > c.user_ws_bytes) rc = TUNA_ERR_WORKSPACE_TOO_SMALL;
             mbase = c.user_ws;
             dbase = (char*)c.user_ws + mbytes;
         } else {
-            const int rc_meta = grow(&c.meta, &c.meta_bytes, mbytes);
-            rc = rc_meta == TUNA_OK ? grow(&c.data, &c.data_bytes, ds.total) : rc_meta;
-            if (rc != TUNA_OK) {
-                if (early) HIPCHK(hipStreamSynchronize(s));
-                return rc;
-            }
+            rc = grow(&c.meta, &c.meta_bytes, mbytes);
+            if (rc == TUNA_OK) rc = grow(&c.data, &c.data_bytes, ds.total);
             mbase = c.meta;
             dbase = c.data;
             if (c.meta_bytes != pr.early_bytes) pr.early = false;     // new memory, perhaps where the old was
         }
-        rc = run_one_pass(pr, mbase, mbytes, dbase, s, st);
+        if (rc == TUNA_OK) rc = run_one_pass(pr, mbase, mbytes, dbase, s, st);
     }
+    if (rc != TUNA_OK && early) HIPCHK(hipStreamSynchronize(s));
     // (also behind what a call that failed half-way has enqueued)
     const hipError_t e = hipEventRecord(c.ev_end, s);
     if (e == hipSuccess) { c.end_recorded = true; c.last_stream = s; }

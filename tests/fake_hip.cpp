@@ -45,6 +45,7 @@ int violations = 0;
 u64 allocated = 0;
 long next_stream = 0x51000;
 hipError_t last_error = hipSuccess;
+bool no_streams = false;
 u64 head[8];                            // flags << 32 | alignment, longest, bytes, chunks, extent, chunks in T, short blocks, windows
 
 void run(hipStream_t s, size_t upto) {
@@ -200,7 +201,11 @@ hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* st) {
     return hipSuccess;
 }
 hipError_t hipDeviceSynchronize() { wait_all(); return hipSuccess; }
-hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = (hipStream_t)(next_stream += 16); return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
+    if (no_streams) return hipErrorOutOfMemory;
+    *s = (hipStream_t)(next_stream += 16);
+    return hipSuccess;
+}
 hipError_t hipStreamDestroy(hipStream_t s) { wait(s); return hipSuccess; }
 hipError_t hipEventCreate(hipEvent_t* e) { *e = (hipEvent_t) new Event(); return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
@@ -226,12 +231,14 @@ hipError_t hipFuncGetAttributes(hipFuncAttributes* f, const void*) { std::memset
 hipError_t hipMemGetInfo(size_t* f, size_t* t) { *f = *t = (size_t)288 << 30; return hipSuccess; }
 
 void fake_record(long s, int on) { streams[(hipStream_t)s].recording = on != 0; }
+void fake_no_streams() { no_streams = true; }
 int fake_notes() { return (int)notes.size(); }
 const char* fake_name(int i) { return notes[i].name.c_str(); }
 long fake_stream(int i) { return (long)notes[i].s; }
 const void* fake_ptr(int i) { return notes[i].ptr; }
 long fake_before(int i, long s) { return notes[i].before[(hipStream_t)s]; }      // so many operations of s are complete before kernel i
 long fake_length(long s) { return (long)streams[(hipStream_t)s].ops.size(); }
+long fake_waited(long s) { return host[(hipStream_t)s]; }                        // so many operations of s the host has waited for
 int fake_violations() { wait_all(); return violations; }
 u64 fake_allocated() { return allocated; }
 }

@@ -36,7 +36,7 @@ class Lib:
         for name, res, args in (("fake_notes", ctypes.c_int, []), ("fake_name", ctypes.c_char_p, [ctypes.c_int]),
                                 ("fake_stream", ctypes.c_long, [ctypes.c_int]), ("fake_ptr", ctypes.c_size_t, [ctypes.c_int]),
                                 ("fake_before", ctypes.c_long, [ctypes.c_int, ctypes.c_long]),
-                                ("fake_length", ctypes.c_long, [ctypes.c_long]), ("fake_violations", ctypes.c_int, []),
+                                ("fake_waited", ctypes.c_long, [ctypes.c_long]), ("fake_length", ctypes.c_long, [ctypes.c_long]), ("fake_violations", ctypes.c_int, []),
                                 ("fake_allocated", ctypes.c_ulonglong, [])):
             f = getattr(self.fake, name)
             f.restype, f.argtypes = res, args
@@ -283,6 +283,20 @@ def case_no_places(t, P, radix, before):
     first = t.fake.fake_notes()
     rc = t.call(prob, radix, S1) if before else t.lib.tuna_alltoallv_noalloc(*prob[1], P, 0, radix, radix, S1)
     return [rc, [k[0] for k in t.kernels(first) if not k[0].startswith("k_build")]]
+
+
+def case_small_workspace(t, kind, P, radix):
+    """A call on a caller's workspace of 4 MiB, which holds its metadata and not T: its kernels, and whether the host has waited for them."""
+    counts = {"one pass": np.full((P, P), 300), "pipelined": _engine_counts(P) + 8000, "two passes": _engine_counts(P) + 8000}[kind]
+    prob = t.problem(counts, gap=1)
+    assert t.call(t.problem(np.full((4, 4), 40)), 2, S1) == 0                  # (a context's first call has no early kernels)
+    room = np.zeros((4 << 20) + 256, np.uint8)
+    assert t.lib.tuna_set_workspace(room.ctypes.data + -room.ctypes.data % 256, 4 << 20) == 0
+    first = t.fake.fake_notes()
+    if kind == "two passes":
+        t.fake.fake_no_streams()
+    assert t.call(prob, radix, S1, t_layout=t.b.TUNA_T_EXACT) == t.b.TUNA_ERR_WORKSPACE_TOO_SMALL
+    return [[k[0] for k in t.kernels(first)], t.fake.fake_waited(S1) >= t.fake.fake_length(S1)]
 
 
 CASES = {k[5:]: f for k, f in list(globals().items()) if k.startswith("case_")}

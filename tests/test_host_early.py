@@ -49,3 +49,9 @@ def test_a_schedule_of_two_phases_without_t_has_no_places(runtime, P, radix, bef
     """Radix P - 1: every block moves once, so there is nothing to find early."""
     rc, kernels = fake_hip.run(runtime, "no_places", P, radix, before)
     assert rc == 0 and len(_hops(kernels)) == 2 and not [k for k in kernels if k.startswith("k_t_")]
+
+
+@pytest.mark.parametrize("kind,P,radix", [("one pass", 200, 4), ("pipelined", 100, 4), ("two passes", 100, 4)])
+def test_a_call_whose_workspace_is_too_small_has_ended(runtime, kind, P, radix):
+    kernels, done = fake_hip.run(runtime, "small_workspace", kind, P, radix)
+    assert any(k.startswith("k_t_places") for k in kernels) and not _hops(kernels) and done
