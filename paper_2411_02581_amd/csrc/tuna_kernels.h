@@ -379,13 +379,13 @@ __global__ void __launch_bounds__(kValTile * kValRows, 8) k_validate(const int32
     __shared__ int tile[2][kValTile][kValTile + 1];
     __shared__ unsigned int sums[2][2][kValTile];         // bytes per receiver, per sender of a tile
     __shared__ unsigned long long red[kValRows][8];
-    __shared__ int long_seen;
+    __shared__ int long_seen[2];                          // (per buffer: a wave may be a tile ahead of one that still asks)
     extern __shared__ unsigned long long lcls[];          // class_count(nph) sums of this workgroup, `copies` of each (with `mask`)
     const int tx = threadIdx.x, ty = __builtin_amdgcn_readfirstlane(threadIdx.y);
     const int ncls = mask ? class_count(nph) : 0;
     for (int i = ty * kValTile + tx; i < ncls * copies; i += kValRows * kValTile) lcls[i] = 0;
     if (ty < 4) sums[ty >> 1][ty & 1][tx] = 0;
-    if (tx == 0 && ty == 0) long_seen = 0;
+    if (tx < 2 && ty == 0) long_seen[tx] = 0;
     // the totals that k_phase_sums adds to, and the units that k_long_units counts (without a ticket k_validate_finish clears
     // them), not for a sizing query: the totals there belong to the context's last call.  First of all: right in front of the
     // ticket these stores cost a call 2 us
@@ -469,7 +469,7 @@ __global__ void __launch_bounds__(kValTile * kValRows, 8) k_validate(const int32
             tile[buf][a][tx] = c;
         }
         if (!WHOLE) continue;
-        if (mx > kWindowMinBytes) long_seen = 1;
+        if (mx > kWindowMinBytes) long_seen[buf] = 1;     // (in every tile from the first long block on)
         __syncthreads();                                  // the only one per tile: the next one's entries go to the other buffer
         unsigned int from = 0;                            // bytes that sender i2 has for this thread's receivers
 #pragma unroll
@@ -491,7 +491,7 @@ __global__ void __launch_bounds__(kValTile * kValRows, 8) k_validate(const int32
             if (tx == kValTile - 1) dn = behind;
             if (in && i2 + 1 < P && dn != rd[u] + (long long)max(rv[u], 0)) flags |= 8u;
         }
-        if (long_seen) {                                  // windows of neighbouring blocks
+        if (long_seen[buf]) {                              // windows of neighbouring blocks
             atomicAdd(&sums[buf][0][tx], to);
             atomicAdd(&sums[buf][1][tx], from);
         }

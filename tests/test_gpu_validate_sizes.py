@@ -61,3 +61,30 @@ def test_validation(tuna, P, radix):
     assert np.array_equal(recv.cpu().numpy(), want)
     st = tuna.tuna_get_stats()
     assert st.total_payload_bytes == lay.payload_bytes and st.max_block_bytes == counts.max() and st.granularity == 4
+
+
+def test_windows_count_from_the_first_long_block_on(tuna):
+    """1536 ranks are 24 x 24 tiles, of which some workgroups take two, one behind the other: blocks of 64 bytes in the first, one of 65 in
+    the second.  What a tile holds before its workgroup has seen a block of more than 64 bytes is in no window, whichever of its waves are
+    ahead, so the blocks do not cluster and a plan's phase runs the direct hop; every time."""
+    P = 1536
+    counts = np.zeros((P, P), dtype=np.int32)
+    counts[:64, :384] = 64                                   # tiles 0 to 5
+    counts[64 * 21 + 5, 64 * 8 + 3:64 * 14:64] = 65          # one block in each of the tiles 512 to 517
+    mean = counts.sum() / P**2
+    assert 65 < 8 * 64 * mean < 64 * 64 / 4                  # clustered with a part of a first tile's window, not without
+    lay = wl.make_layout(counts)
+    host = wl.payload_position_hash(9, lay.send_bytes)
+    want = np.full(lay.recv_bytes, CANARY, dtype=np.uint8)
+    assert oracle.alltoallv(host, lay.sendcounts, lay.sdispls, want, lay.recvcounts, lay.rdispls) == 0
+    dev = "cuda:0"
+    send = torch.from_numpy(host).to(dev)
+    d = [torch.from_numpy(np.ascontiguousarray(a)).to(dev) for a in (lay.sendcounts, lay.sdispls, lay.recvcounts, lay.rdispls)]
+    for _ in range(8):
+        recv = torch.full((lay.recv_bytes,), CANARY, dtype=torch.uint8, device=dev)
+        rc, plan = tuna.tuna_alltoallv_init(send, d[0], d[1], recv, d[2], d[3], P, 0, P, P)
+        assert rc == 0 and tuna.tuna_start(plan) == 0
+        torch.cuda.synchronize()
+        assert tuna.tuna_get_stats().hop_kernels == tuna.TUNA_HOP_DIRECT
+        assert np.array_equal(recv.cpu().numpy(), want)
+        assert tuna.tuna_plan_free(plan) == 0
