@@ -145,6 +145,7 @@ struct Ctx {
     std::tuple<int, int, int, int> tiny_asked{};     // the schedule (P, Q, radices) it was asked for last, its slots of T,
     long long tiny_slots = 0;
     int tiny_vain = 0;                   // and how often in vain since it took one
+    bool tiny_skipped = false;           // the call being made would have asked it but for that
     bool device_totals = false;         // the per-phase totals of the statistics on file are still in *sb.d_status (an immediate call's)
     // pipelined calls (run_pipelined): the stream the metadata kernels run on, the event that lets it start, and one
     // event per phase that lets the phase's payload kernel start; made at the first such call
@@ -1864,6 +1865,7 @@ int run_once(Ctx& c, const Options& opt, const void* sendbuf, const int32_t* sen
 constexpr size_t kTinyTBytes = 4u << 20;
 constexpr int kTinyVain = 4;
 bool tiny_would_fit(int P, long long slots, const Status& hs) {
+    if (hs.send_extent > 1ull << 32 || (hs.flags & 16u)) return false;
     return hs.total_bytes <= kTinyMaxPayload && (unsigned long long)P * (unsigned long long)slots * (((unsigned long long)hs.max_count + 15) / 16 * 16) <= kTinyTBytes;
 }
 constexpr long long kTinyMaxMoving = 1200, kTinyMovingPerPhase = 200;       // blocks moved, over all ranks and phases
@@ -1891,7 +1893,8 @@ int run_tiny(Ctx& c, const void* sendbuf, const int32_t* sendcounts, const int64
     if (moving > kTinyMaxMoving + kTinyMovingPerPhase * (long long)pl.phases.size()) return TUNA_OK;
     const auto schedule = std::make_tuple(P, Q, pl.rl, pl.rg);
     if (c.tiny_asked != schedule) { c.tiny_asked = schedule; c.tiny_slots = pl.slots; c.tiny_vain = 0; }
-    if (c.tiny_vain >= kTinyVain) return TUNA_OK;
+    c.tiny_skipped = c.tiny_vain >= kTinyVain;
+    if (c.tiny_skipped) return TUNA_OK;
     *asked = true;
     if (!c.tiny_t) {
         const hipError_t e = hipMalloc((void**)&c.tiny_t, kTinyTBytes);
@@ -1951,6 +1954,7 @@ int run_tiny(Ctx& c, const void* sendbuf, const int32_t* sendcounts, const int64
 int run(Ctx& c, const Options& opt, const void* sendbuf, const int32_t* sendcounts, const int64_t* sdispls,
         void* recvbuf, const int32_t* recvcounts, const int64_t* rdispls, int P, int ranks_per_node, int rl, int rg,
         void* stream) {
+    c.tiny_skipped = false;
     if (P <= kTinyMaxRanks && opt.mode == TUNA_MODE_AUTO && opt.t_layout == TUNA_T_AUTO && !opt.staggered &&
         !opt.block_count && !opt.profile && !c.user_ws && c.tiny_declined != (const void*)sendcounts) {
         bool done = false, asked = false;
@@ -1994,7 +1998,7 @@ int run_once(Ctx& c, const Options& opt, const void* sendbuf, const int32_t* sen
         if (pr.early) HIPCHK(hipStreamSynchronize(s));        // a refused call is done when it returns
         return rc;
     }
-    if (c.tiny_vain >= kTinyVain && std::get<0>(c.tiny_asked) == P && tiny_would_fit(P, c.tiny_slots, hs)) c.tiny_vain = 0;
+    if (c.tiny_skipped && tiny_would_fit(P, c.tiny_slots, hs)) c.tiny_vain = 0;
     tuna_stats_t& st = c.stats;
     fill_stats_header(pr, hs, st);
     if (empty) {

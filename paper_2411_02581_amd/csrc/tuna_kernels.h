@@ -41,7 +41,7 @@ constexpr int kMaxClasses = 64 * 63 / 2;     // class_count(TUNA_MAX_PHASES)
 // other arrays; head and class sums are read back after validation, in one copy.
 struct Status {
     unsigned int flags;            // bit 0: negative count, bit 1: recvcounts != transpose(sendcounts), (bit 3: receive regions not dense)
-                                   // bit 2: negative displacement of a non-empty block
+                                   // bit 2: negative displacement of a non-empty block, (bit 4: one into R of 4 GiB and more)
     unsigned int align_bits;       // OR of all counts and displacements, low 7 bits (they decide the granularity)
     int max_count;                 // M
     int tiny_done;                 // k_tiny_call: 1 = the whole call was done by that one kernel, 0 = it declined (nothing moved)
@@ -482,7 +482,8 @@ __global__ void __launch_bounds__(kValTile * kValRows, 8) k_validate(const int32
                 if (rv[u] < 0) flags |= 1u;
                 else if (rv[u] != c) flags |= 2u;         // recvcounts[jr][i] must equal sendcounts[i][jr]
                 abits |= (unsigned int)rd[u] & 127u;
-                if (rv[u] > 0 && rd[u] < 0) flags |= 4u;
+                const int high = (int)(rd[u] >> 32);
+                if (rv[u] > 0 && high) flags |= high < 0 ? 4u : 16u;
             }
             // dense receive regions: every block starts where its predecessor in source order ends (flag 8 when not; the
             // destination-tiled hop needs it).  A wave holds 64 neighbours of one row.

@@ -106,6 +106,7 @@ void validate(const int32_t* sc, const int32_t* rc, const int64_t* sd, const int
             if (sd && n) { bits |= (unsigned int)sd[k]; head[4] = std::max(head[4], (u64)(sd[k] + n)); }
             if (rd && rc && rc[k] > 0) {
                 bits |= (unsigned int)rd[k];
+                if (rd[k] >> 32) flags |= 16;
                 if (j + 1 < P && rc[k + 1] > 0 && rd[k + 1] != rd[k] + rc[k]) flags |= 8;
             }
         }

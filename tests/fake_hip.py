@@ -299,6 +299,20 @@ def case_small_workspace(t, kind, P, radix):
     return [[k[0] for k in t.kernels(first)], t.fake.fake_waited(S1) >= t.fake.fake_length(S1)]
 
 
+def case_single_launch(t, calls):
+    """Whether each of `calls`, [kind, radix], all of 12 ranks and with inputs of their own, asked k_tiny_call (which declines everything here)."""
+    out, keep = [], []
+    for kind, radix in calls:
+        keep.append(t.problem(np.full((12, 12), 9000 if kind == "large" else 40)))
+        lay = keep[-1][0]
+        if kind in ("far in S", "far in R"):
+            (lay.sdispls if kind == "far in S" else lay.rdispls)[3:] += 1 << 32
+        first = t.fake.fake_notes()
+        assert t.call(keep[-1], radix, S1, mode=t.b.TUNA_MODE_FUSED if kind == "own options" else t.b.TUNA_MODE_AUTO) == 0
+        out.append("k_tiny_call" in [k[0] for k in t.kernels(first)])
+    return out
+
+
 CASES = {k[5:]: f for k, f in list(globals().items()) if k.startswith("case_")}
 
 if __name__ == "__main__":

@@ -62,3 +62,15 @@ def test_sequences_of_operations(runtime, seed):
     """Every kernel of an immediate call, on whatever stream, is behind all earlier calls of its context."""
     r = fake_hip.run(runtime, "sequence", seed, 120)
     assert r["calls"] > 20 and r["late"] == [] and r["violations"] == 0
+
+
+@pytest.mark.parametrize("kind", ["large", "far in S", "far in R"])
+def test_the_single_launch_is_not_asked_in_vain_for_long(runtime, kind):
+    """Problems that it declines, other inputs each time: four times, then not again, until one comes that it would have taken.  Neither a
+    call that would not ask it nor one of another schedule is such a one."""
+    asked = fake_hip.run(runtime, "single_launch", [[kind, 3]] * 12)
+    assert asked == [True] * 4 + [False] * 8
+    asked = fake_hip.run(runtime, "single_launch", [[kind, 3]] * 5 + [["own options", 3], ["own options", 2]] + [[kind, 3]] * 2 + [["small", 3]] + [[kind, 3]] * 5)
+    assert asked == [True] * 4 + [False] * 6 + [True] * 4 + [False]
+    asked = fake_hip.run(runtime, "single_launch", [[kind, 3]] * 5 + [["small", 2]] + [[kind, 3]] * 5)
+    assert asked == [True] * 4 + [False] + [True] + [True] * 4 + [False]
