@@ -119,6 +119,22 @@ struct Shared {
 
 Shared sh;
 
+// Whether a schedule's early kernels (launch_early) are worth launching: not after kEarlyVain calls in a row whose phases had no use
+// for them, until one comes that has.  (Per call with them / without, us: 64 KiB from each of 512 ranks to one, r = 4 244 / 234, linear 94 / 91,
+// 16 KiB, P = 1024, r = 8 221 / 205, normal 4300 bytes, P = 512, r = 4 1507 / 1491; the call that allocates nothing, short blocks and two of 70 KB, P = 500, r =
+// 8 238 / 228, r = 23 189 / 180.)
+constexpr int kEarlyVain = 2;
+struct EarlyUse {
+    std::tuple<int, int, int, int, int> asked{};        // P, ranks per node, radices, layout of T
+    int vain = 0;
+    bool worth(int P, int ranks_per_node, int rl, int rg, int t_layout) {
+        const auto key = std::make_tuple(P, ranks_per_node, rl, rg, t_layout);
+        if (key != asked) { asked = key; vain = 0; }
+        return vain < kEarlyVain;
+    }
+    void found(bool used) { vain = used ? 0 : std::min(vain + 1, kEarlyVain); }
+};
+
 // Everything one immediate call writes besides the caller's receive buffer: the workspace, the status
 // block, the statistics and the profiling events.  Calls that share a context share these; calls on
 // different contexts share nothing and may overlap in time.
@@ -146,6 +162,7 @@ struct Ctx {
     long long tiny_slots = 0;
     int tiny_vain = 0;                   // and how often in vain since it took one
     bool tiny_skipped = false;           // the call being made would have asked it but for that
+    EarlyUse early;
     bool device_totals = false;         // the per-phase totals of the statistics on file are still in *sb.d_status (an immediate call's)
     // pipelined calls (run_pipelined): the stream the metadata kernels run on, the event that lets it start, and one
     // event per phase that lets the phase's payload kernel start; made at the first such call
@@ -1624,10 +1641,12 @@ bool runs_direct(const Prepared& pr) {
 //
 // The places follow from the counts alone; only where the classes lie waits for the host.  So k_t_places runs under the host's
 // wait for validation's result, in memory that an earlier call has left (launch_early), for up to kEarlyEntries entries of the
-// matrices (8 to 30 us, of which the wait hides 12; where T is in slots or a hop has metadata kernels it was for nothing).  Up to kEarlyTotalsRanks
+// matrices: 8 to 30 us, of which the wait hides 12; where T is in slots or a hop has metadata kernels it is for nothing, and left out after two
+// such calls (EarlyUse).  Up to kEarlyTotalsRanks
 // ranks it finds the phases' totals on the way, which follow from the counts and rdispls: a pass over the receivers' rows that
 // the wait hides too, in place of the hops' partial sums and k_phase_sums, the call's last kernel (2048 ranks 10 us, which it does not
-// hide).  A linear schedule has no places, its totals are found there all the same (k_row_totals).
+// hide).  A linear schedule has no places, its totals are found there all the same (k_row_totals).  The call that allocates nothing waits for
+// a copy behind these kernels: it hides nothing of them and has them for that last launch alone, so not above kEarlyTotalsRanks.
 constexpr double kEarlyEntries = 9e6;
 constexpr int kEarlyTotalsRanks = 512;
 
@@ -1988,7 +2007,8 @@ int run_once(Ctx& c, const Options& opt, const void* sendbuf, const int32_t* sen
     Prepared pr;
     Status hs{};
     bool empty = false;
-    if (c.ready && !c.profile) {                              // a context's first call has no memory yet
+    const bool worth = c.early.worth(P, ranks_per_node, rl, rg, opt.t_layout);
+    if (c.ready && !c.profile && worth) {                     // (a context's first call has no memory yet)
         pr.early_mem = c.user_ws ? c.user_ws : c.meta;
         pr.early_bytes = c.user_ws ? c.user_ws_bytes : c.meta_bytes;
     }
@@ -2013,6 +2033,7 @@ int run_once(Ctx& c, const Options& opt, const void* sendbuf, const int32_t* sen
     const PlanHost& pl = pr.dp->host;
     const bool direct = runs_direct(pr);
     const bool early = pr.early;
+    if (early || !worth) c.early.found(direct && (pr.exact_t || pl.phases.size() == 1));
     if (!direct) pr.early = pr.early_totals = false;
     if (use_two_pass(pl, hs) && pr.fused && !c.profile && !pr.debug_sizes && !direct) {
         rc = run_pipelined(c, pr, s);
@@ -2410,6 +2431,7 @@ struct StaticState {
     Status h_status;                          // host mirror of the status block (pageable: no pinned allocation)
     long long h_cbase[kMaxClasses];
     unsigned long long h_rows[kValFoldRows * kValRow];
+    EarlyUse early;
 };
 StaticState g_static;
 
@@ -2472,8 +2494,12 @@ int run_static(const void* sendbuf, const int32_t* sendcounts, const int64_t* sd
     pr.dp = &dp;
 
     // ---- validation and sizing (one read-back), then the one-pass call ---------------------------------
-    pr.early_mem = cv.base + cv.off;
-    pr.early_bytes = cv.cap - cv.off;
+    // (The copy of its result is behind the early kernels here, so the wait hides nothing of them: only where they save a launch.)
+    const bool worth = g_static.early.worth(P, ranks_per_node, rl, rg, pr.opt.t_layout);
+    if (P <= kEarlyTotalsRanks && worth) {
+        pr.early_mem = cv.base + cv.off;
+        pr.early_bytes = cv.cap - cv.off;
+    }
     Status hs{};
     bool empty = false;
     rc = prepare_sizes(pr, pr.opt.t_layout, s, hs, &empty);
@@ -2489,6 +2515,7 @@ int run_static(const void* sendbuf, const int32_t* sendcounts, const int64_t* sd
     g.have_stats = true;
     if (empty) return TUNA_OK;
     g.stats.hop_kernels = hop_kernels_of(pr);
+    if (pr.early || !worth) g_static.early.found(runs_direct(pr) && (pr.exact_t || dp.host.phases.size() == 1));
     const size_t mbytes = one_pass_meta_bytes(pr);
     if (cv.off + mbytes + pr.ds.total > cv.cap) {
         if (pr.early) HIPCHK(hipStreamSynchronize(s));

@@ -313,6 +313,26 @@ def case_single_launch(t, calls):
     return out
 
 
+def case_early_use(t, P, radix, calls, noalloc):
+    """Whether each of `calls` on one schedule -- "direct", "engine", "staged", "slots" -- launched early kernels: behind validation and ahead of
+    what needs its result."""
+    short, engine = t.problem(np.full((P, P), 300), gap=1), t.problem(_engine_counts(P), gap=1)
+    out = []
+    for kind in ["direct"] + calls:
+        prob = engine if kind == "engine" else short
+        first = t.fake.fake_notes()
+        if noalloc:
+            assert t.lib.tuna_alltoallv_noalloc(*prob[1], P, 0, radix, radix, S1) == 0
+        else:
+            assert t.call(prob, radix, S1, mode=t.b.TUNA_MODE_STAGED if kind == "staged" else t.b.TUNA_MODE_FUSED,
+                          t_layout=t.b.TUNA_T_SLOTS if kind == "slots" else t.b.TUNA_T_EXACT) == 0
+        kernels = [k[0] for k in t.kernels(first)]
+        validated = max(i for i, k in enumerate(kernels) if k.startswith("k_validate"))
+        # (k_t_bases and the hops' partial sums tell a direct call that found its places early from one that did not)
+        out.append(kernels[validated + 1].startswith(("k_t_places", "k_row_totals")) and "k_phase_sums" not in kernels)
+    return out[1:]
+
+
 CASES = {k[5:]: f for k, f in list(globals().items()) if k.startswith("case_")}
 
 if __name__ == "__main__":

@@ -55,3 +55,18 @@ def test_a_schedule_of_two_phases_without_t_has_no_places(runtime, P, radix, bef
 def test_a_call_whose_workspace_is_too_small_has_ended(runtime, kind, P, radix):
     kernels, done = fake_hip.run(runtime, "small_workspace", kind, P, radix)
     assert any(k.startswith("k_t_places") for k in kernels) and not _hops(kernels) and done
+
+
+@pytest.mark.parametrize("P,radix", [(100, 4), (100, 100)])
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_early_kernels_that_were_for_nothing_are_left_out(runtime, P, radix, noalloc):
+    """After two calls in a row whose phases had no use for them, until one comes that has."""
+    calls = ["direct"] + ["engine"] * 4 + ["direct"] * 2 + ["engine", "direct"] * 2 + ["engine"] * 3 + ["direct"] * 2
+    want = [True] + [True] * 2 + [False] * 2 + [False, True] + [True] * 4 + [True] * 2 + [False] + [False, True]
+    assert fake_hip.run(runtime, "early_use", P, radix, calls, noalloc) == want
+
+
+def test_calls_that_launch_none_do_not_count(runtime):
+    calls = ["engine", "staged", "staged", "slots", "slots", "direct", "engine", "staged", "engine", "staged", "engine"]
+    want = [True] + [False] * 4 + [True] * 2 + [False] + [True] + [False] * 2
+    assert fake_hip.run(runtime, "early_use", 100, 4, calls, False) == want
