@@ -1251,24 +1251,32 @@ int rows_segs(const Prepared& pr) {
 constexpr int kTallMinRounds = 7;
 int lanes_per_block(int64_t max_block) { return max_block <= 16 ? 1 : (max_block <= 64 ? 4 : 16); }
 int direct_lpb(const Prepared& pr) { return lanes_per_block(pr.max_count); }
-// Tall tiles where a round has few blocks, and in the first phase of more than a few rounds (k_hop_senders; k_hop_direct, up to 16 B, P =
-// 2048, r = 8 274 / 267 us per call, up to 40 380 / 382, r = 4 664 / 664).
-bool direct_tall(const PhaseHost& ph) { return (long long)ph.nz * 16 > ph.nseg || (ph.dim == 0 && ph.rx == 1 && ph.nz >= kTallMinRounds); }
-// Workgroup columns and steps per workgroup over `nseg` segments of a phase: one step each while that gives no more than 8192 workgroups (four
-// per resident slot of the device), then up to 8 steps; and the rows of partial sums that such a launch stores.
-unsigned direct_columns(const Prepared& pr, const PhaseHost& ph, int nseg, int* iters) {
-    const DirectShape sh = direct_shape(direct_lpb(pr), direct_tall(ph));
-    const int segs = direct_segs(sh);
-    const long long steps = (nseg + segs - 1) / segs, rows = (pr.P + direct_ranks(sh) - 1) / direct_ranks(sh);
-    *iters = (int)std::max(1LL, std::min(8LL, steps * rows / 8192));
-    return (unsigned)((steps + *iters - 1) / *iters);
-}
 bool runs_direct(const Prepared& pr);
 // Phases of a schedule of several that an immediate call's k_hop_senders moves: many rounds, and 256 blocks of a rank to each.
 bool by_senders(const PhaseHost& ph) {
     return ph.nz >= kSenderMinRounds && ph.nz <= kSenderMaxRounds && (long long)((ph.nseg + 255) / 256) * ph.nz <= ph.nseg;
 }
 bool sender_phase(const Prepared& pr, const PhaseHost& ph) { return pr.dp->host.phases.size() > 1 && by_senders(ph); }
+// Tall tiles where a round has few blocks, and in the first phase of seven rounds and more with the segments in the order of the slot
+// indices.  Wide / tall, us: up to 16 B, per start P = 4000, r = 16 496 / 466, r = 8 612 / 603, P = 2048, r = 46 79.1 / 75.8, per call 854 / 810, 1033 /
+// 1019 and 142 / 139; up to 200, P = 1000, r = 24 119 / 112 and 169 / 166, r = 8 170 / 166 and 235 / 229; up to 60 B the wide ones are up to 1 % ahead (P = 4000, r = 16
+// 1286 / 1300 and 1549 / 1556); five rounds gain 1 to 2 %, three and fewer nothing.  In message order a round's segments lie together: tall only
+// where a call finds the blocks of many rounds itself (k_hop_senders: T in slots), since with hop arrays it is as often the slower one: batches of 16
+// rounds, per start, up to 16 B, P = 2048, r = 46 143 / 154, r = 12 171 / 163, up to 60, r = 8 358 / 363, r = 46 272 / 268; T in slots, P = 600, r = 9 27.5 / 28.5.
+bool direct_tall(const Prepared& pr, const PhaseHost& ph) {
+    if ((long long)ph.nz * 16 > ph.nseg) return true;
+    if (ph.dim != 0 || ph.rx != 1) return false;
+    return pr.dp->host.sc.by_index ? ph.nz >= kTallMinRounds : !pr.for_plan && runs_direct(pr) && sender_phase(pr, ph);
+}
+// Workgroup columns and steps per workgroup over `nseg` segments of a phase: one step each while that gives no more than 8192 workgroups (four
+// per resident slot of the device), then up to 8 steps; and the rows of partial sums that such a launch stores.
+unsigned direct_columns(const Prepared& pr, const PhaseHost& ph, int nseg, int* iters) {
+    const DirectShape sh = direct_shape(direct_lpb(pr), direct_tall(pr, ph));
+    const int segs = direct_segs(sh);
+    const long long steps = (nseg + segs - 1) / segs, rows = (pr.P + direct_ranks(sh) - 1) / direct_ranks(sh);
+    *iters = (int)std::max(1LL, std::min(8LL, steps * rows / 8192));
+    return (unsigned)((steps + *iters - 1) / *iters);
+}
 // The only phase of an immediate call's linear schedule, if its blocks are short: k_hop_pairs moves it, and the own blocks; its
 // workgroup columns and steps per workgroup (as direct_columns).
 bool pair_phase(const Prepared& pr) { return pr.dp->host.phases.size() == 1 && runs_direct(pr) && small_blocks(pr) && !long_blocks(pr); }
@@ -1304,7 +1312,7 @@ unsigned direct_rows(const Prepared& pr, const PhaseHost& ph) {
     if (pair_phase(pr)) { int iters = 0; return pair_columns(pr, &iters); }
     if (row_blocks(pr)) { const int segs = rows_segs(pr); return (unsigned)((ph.nseg + segs - 1) / segs); }
     int iters = 0;
-    return direct_columns(pr, ph, ph.nseg, &iters) * (unsigned)(4 / direct_shape(direct_lpb(pr), direct_tall(ph)).waves_r);
+    return direct_columns(pr, ph, ph.nseg, &iters) * (unsigned)(4 / direct_shape(direct_lpb(pr), direct_tall(pr, ph)).waves_r);
 }
 
 template <bool LINES>
@@ -1339,11 +1347,11 @@ int launch_direct(const Prepared& pr, size_t i, const HopDev& hop, int seg_lo, i
     a.r = resolve_args(pr, i, nullptr, hop);
     a.T = pr.T; a.seg_lo = seg_lo; a.seg_hi = seg_hi; a.part = part;
     const unsigned cols = direct_columns(pr, ph, seg_hi - seg_lo, &a.iters);
-    const int lpb = direct_lpb(pr), ranks = direct_ranks(direct_shape(lpb, direct_tall(ph)));
+    const int lpb = direct_lpb(pr), ranks = direct_ranks(direct_shape(lpb, direct_tall(pr, ph)));
     a.own = own ? (int)(((pr.P + kOwnRanks - 1) / kOwnRanks + cols - 1) / cols) : 0;
     const dim3 grid(cols, (unsigned)((pr.P + ranks - 1) / ranks + a.own));
     const bool senders = sender_phase(pr, ph);
-    if (direct_tall(ph)) launch_direct_shape<true>(lpb, pr.gran, a, grid, pr.exact_kernels, senders, s);
+    if (direct_tall(pr, ph)) launch_direct_shape<true>(lpb, pr.gran, a, grid, pr.exact_kernels, senders, s);
     else launch_direct_shape<false>(lpb, pr.gran, a, grid, pr.exact_kernels, senders, s);
     HIPCHK(hipGetLastError());
     return TUNA_OK;

@@ -127,3 +127,18 @@ def test_the_cost_model_prices_blocks_by_the_kernel_that_finds_them(P, radix, lo
     want = c[0] + c[1] * len(phases) + c[2] * (len(phases) + 1) * P * P / 1e6 + c[5] * priced / 1e6 + c[6] * payload * blocks / (P * P) / 1e9
     rc, ms = tuna.tuna_predict_ms(P, 0, radix, radix, tuna.TUNA_MODE_FUSED, tuna.TUNA_T_EXACT, payload, longest, 4)
     assert rc == 0 and ms == pytest.approx(want, rel=1e-9)
+
+
+@pytest.mark.parametrize("plan,t_layout", [(False, EXACT), (True, EXACT), (False, SLOTS), (True, SLOTS)])
+def test_tall_tiles_where_neighbouring_segments_have_one_sender_each(runtime, plan, t_layout):
+    """With T in exact size segments lie in the order of the slot indices: the first phase runs tall tiles from seven rounds on.  With T in slots
+    they lie in message order: only a call's kernel that finds the blocks of twelve rounds and more itself."""
+    problems = [(600, 0, r, r, n, 4, t_layout, {}) for r in (7, 8, 9, 12, 13, 25) for n in (16, 60, 200)]
+    for prob, kernels in zip(problems, fake_hip.run(runtime, "routes", problems, plan)):
+        hops = [(k, a) for k, a in kernels if k.startswith("k_hop")]
+        assert len(hops) > 1, prob
+        name, args = hops[0]
+        rounds = prob[2] - 1
+        tall = args[3] if name == "k_hop_senders" else args[1]
+        assert name == ("k_hop_direct" if plan or rounds < 12 else "k_hop_senders"), prob
+        assert tall == (rounds >= 7 if t_layout == EXACT else not plan and rounds >= 12), prob
