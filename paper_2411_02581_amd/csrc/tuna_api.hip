@@ -181,8 +181,9 @@ Ctx g;                                  // the default context
 
 inline size_t align_up(size_t v, size_t a = kAlign) { return (v + a - 1) / a * a; }
 
-// 64-bit words of the validation pass's partial results: at most 8 workgroups per compute unit
-inline size_t vpart_words(int num_cus) { return (size_t)num_cus * 8 * kValPartial; }
+// 64-bit words of the validation pass's partial results: room for 8 workgroups per compute unit (there are two), and for the longer rows
+// that the call which allocates nothing copies: up to 64, however few compute units a part of a device has.
+inline size_t vpart_words(int num_cus) { return std::max((size_t)num_cus * 8 * kValPartial, (size_t)kValFoldRows * kValRow); }
 
 // The library runs on the HIP device that is current at its first call.
 int ensure_device() {

@@ -9,6 +9,8 @@
 #include <hip/hip_runtime_api.h>
 #include <sys/mman.h>
 
+#include "../paper_2411_02581_amd/csrc/tuna_plan.h"
+
 #include <algorithm>
 #include <climits>
 #include <cstdint>
@@ -32,7 +34,7 @@ struct Stream {
     Clock now;
 };
 struct Event { hipStream_t s = nullptr; size_t upto = 0; Clock at; };
-struct Note { std::string name; hipStream_t s; Clock before; const void* ptr; };     // ptr: the status block, or a word of one
+struct Note { std::string name; hipStream_t s; Clock before; const void* ptr; const void* end; };     // ptr: the status block, or a word of one, or a schedule's tables; end: of the rows that k_validate writes
 
 struct Launch { dim3 grid, block; size_t lds; hipStream_t s; } launch;
 
@@ -46,6 +48,7 @@ u64 allocated = 0;
 long next_stream = 0x51000;
 hipError_t last_error = hipSuccess;
 bool no_streams = false;
+int units = 256;
 u64 head[8];                            // flags << 32 | alignment, longest, bytes, chunks, extent, chunks in T, short blocks, windows
 
 void run(hipStream_t s, size_t upto) {
@@ -137,7 +140,7 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
 
 hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** a, size_t, hipStream_t s) {
     const std::string& n = names[f];
-    const void* ptr = nullptr;
+    const void *ptr = nullptr, *end = nullptr;
     if (!grid.x || !grid.y || !grid.z) return last_error = hipErrorInvalidConfiguration;
     std::function<void()> op = [] {};
     auto is = [&](const char* k) { return n.find(std::to_string(std::strlen(k)) + k) != std::string::npos; };
@@ -149,6 +152,7 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** a, size_t, hip
         const u64 ticket = arg<u64>(a, 12);
         const unsigned g = grid.x;
         ptr = arg<const void*>(a, 11);
+        end = rows + (size_t)g * (ticket ? kRow : 8);
         op = [=] { validate(sc, rc, sd, rd, P, rows, nph * (nph - 1) / 2, ticket, g); };
     } else if (is("k_validate_finish")) {
         char *st = arg<char*>(a, 2), *mirror = arg<char*>(a, 4);
@@ -167,9 +171,12 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** a, size_t, hip
         op = [=] { std::memset(p, 0, (size_t)m * 8); };
     } else if (is("k_layout_base")) {
         ptr = arg<const void*>(a, 4);
+    } else if (is("k_build_tables")) {
+        struct Args { tuna::PlanScalars pl; tuna::PhaseScalars ps; const void* mem; };
+        ptr = static_cast<const Args*>(a[0])->mem;
     }
     enqueue(s, op);
-    notes.push_back(Note{n, s, streams[s].now, ptr});
+    notes.push_back(Note{n, s, streams[s].now, ptr, end});
     return hipSuccess;
 }
 
@@ -226,8 +233,8 @@ hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
 hipError_t hipGetLastError() { const hipError_t e = last_error; last_error = hipSuccess; return e; }
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipGetDeviceCount(int* n) { *n = 1; return hipSuccess; }
-hipError_t hipGetDeviceProperties(hipDeviceProp_t* p, int) { std::memset(p, 0, sizeof *p); p->multiProcessorCount = 256; return hipSuccess; }
-hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
+hipError_t hipGetDeviceProperties(hipDeviceProp_t* p, int) { std::memset(p, 0, sizeof *p); p->multiProcessorCount = units; return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = units; return hipSuccess; }
 hipError_t hipFuncGetAttributes(hipFuncAttributes* f, const void*) { std::memset(f, 0, sizeof *f); return hipSuccess; }
 hipError_t hipMemGetInfo(size_t* f, size_t* t) { *f = *t = (size_t)288 << 30; return hipSuccess; }
 
@@ -237,6 +244,8 @@ int fake_notes() { return (int)notes.size(); }
 const char* fake_name(int i) { return notes[i].name.c_str(); }
 long fake_stream(int i) { return (long)notes[i].s; }
 const void* fake_ptr(int i) { return notes[i].ptr; }
+const void* fake_end(int i) { return notes[i].end; }
+void fake_units(int n) { units = n; }
 long fake_before(int i, long s) { return notes[i].before[(hipStream_t)s]; }      // so many operations of s are complete before kernel i
 long fake_length(long s) { return (long)streams[(hipStream_t)s].ops.size(); }
 long fake_waited(long s) { return host[(hipStream_t)s]; }                        // so many operations of s the host has waited for

@@ -35,6 +35,7 @@ class Lib:
         self.fake = ctypes.CDLL(runtime, mode=ctypes.RTLD_GLOBAL)
         for name, res, args in (("fake_notes", ctypes.c_int, []), ("fake_name", ctypes.c_char_p, [ctypes.c_int]),
                                 ("fake_stream", ctypes.c_long, [ctypes.c_int]), ("fake_ptr", ctypes.c_size_t, [ctypes.c_int]),
+                                ("fake_end", ctypes.c_size_t, [ctypes.c_int]),
                                 ("fake_before", ctypes.c_long, [ctypes.c_int, ctypes.c_long]),
                                 ("fake_waited", ctypes.c_long, [ctypes.c_long]), ("fake_length", ctypes.c_long, [ctypes.c_long]), ("fake_violations", ctypes.c_int, []),
                                 ("fake_allocated", ctypes.c_ulonglong, [])):
@@ -331,6 +332,16 @@ def case_early_use(t, P, radix, calls, noalloc):
         # (k_t_bases and the hops' partial sums tell a direct call that found its places early from one that did not)
         out.append(kernels[validated + 1].startswith(("k_t_places", "k_row_totals")) and "k_phase_sums" not in kernels)
     return out[1:]
+
+
+def case_rows_of_validation(t, units, P, radix):
+    """The call that allocates nothing on a device of so many compute units: where the rows that validation writes end, and where the schedule's
+    tables begin."""
+    t.fake.fake_units(units)
+    prob, first = t.problem(np.full((P, P), 4)), t.fake.fake_notes()
+    assert t.lib.tuna_alltoallv_noalloc(*prob[1], P, 0, radix, radix, S1) == 0
+    names = [k[0] for k in t.kernels(first)]
+    return [t.fake.fake_end(first + names.index("k_validate")), t.fake.fake_ptr(first + names.index("k_build_tables"))]
 
 
 CASES = {k[5:]: f for k, f in list(globals().items()) if k.startswith("case_")}

@@ -74,3 +74,11 @@ def test_the_single_launch_is_not_asked_in_vain_for_long(runtime, kind):
     assert asked == [True] * 4 + [False] * 6 + [True] * 4 + [False]
     asked = fake_hip.run(runtime, "single_launch", [[kind, 3]] * 5 + [["small", 2]] + [[kind, 3]] * 5)
     assert asked == [True] * 4 + [False] + [True] + [True] * 4 + [False]
+
+
+@pytest.mark.parametrize("units", [256, 64, 32, 16, 8])
+@pytest.mark.parametrize("P,radix", [(512, 23), (300, 2), (65, 8)])
+def test_rows_of_validation_lie_in_front_of_the_tables(runtime, units, P, radix):
+    """Also where a device shows as few compute units as one of its parts has: what one workgroup writes does not get less."""
+    end, tables = fake_hip.run(runtime, "rows_of_validation", units, P, radix)
+    assert 0 < end <= tables
