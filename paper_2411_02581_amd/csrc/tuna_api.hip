@@ -376,8 +376,10 @@ void carve_tables(Carver& cv, DevicePlan& dp) {
 }
 
 // Launches the kernels that fill a schedule's device tables (d_seg to d_mask, whose memory is there), and clears n_zero words.
-// (A workgroup goes through all slot indices twice for the list of a class: not beyond kListRanks of them.)
-constexpr int kListRanks = 1024;
+// A workgroup goes through all slot indices twice for the list of a class, so not beyond kListRanks of them (a launch of their own / with the
+// tables, us per call that allocates nothing, blocks of up to 16 bytes: 30 ranks, r = 6 75 / 54, 60, r = 3 96 / 93, r = 8 79 / 56, 200, r = 24 87 / 62, r = 4 112 / 110,
+// 400, r = 3 165 / 161, r = 8 122 / 113, 500, r = 8 140 / 135, r = 2 242 / 248; 600, r = 8 152 / 149, r = 2 275 / 286, 800, r = 12 154 / 151, r = 4 209 / 214, r = 2 338 / 351).
+constexpr int kListRanks = 512;
 int launch_tables(const DevicePlan& dp, bool by_index, unsigned long long* zero, int n_zero, hipStream_t s) {
     const int nph = (int)dp.host.phases.size();
     for (int f = 0; f < std::max(nph, 1); f += kBuildPhases) {
@@ -1654,8 +1656,8 @@ bool runs_direct(const Prepared& pr) {
 // such calls (EarlyUse).  Up to kEarlyTotalsRanks
 // ranks it finds the phases' totals on the way, which follow from the counts and rdispls: a pass over the receivers' rows that
 // the wait hides too, in place of the hops' partial sums and k_phase_sums, the call's last kernel (2048 ranks 10 us, which it does not
-// hide).  A linear schedule has no places, its totals are found there all the same (k_row_totals).  The call that allocates nothing waits for
-// a copy behind these kernels: it hides nothing of them and has them for that last launch alone, so not above kEarlyTotalsRanks.
+// hide).  A linear schedule has no places, its totals are found there all the same (k_row_totals).  The call that allocates nothing has
+// them in schedules of two phases (run_static).
 constexpr double kEarlyEntries = 9e6;
 constexpr int kEarlyTotalsRanks = 512;
 
@@ -2503,9 +2505,12 @@ int run_static(const void* sendbuf, const int32_t* sendcounts, const int64_t* sd
     pr.dp = &dp;
 
     // ---- validation and sizing (one read-back), then the one-pass call ---------------------------------
-    // (The copy of its result is behind the early kernels here, so the wait hides nothing of them: only where they save a launch.)
+    // The copy of its result is behind the early kernels here, so the wait hides nothing of them and gets longer.  Schedules of two phases,
+    // which wait the shortest, gain a third, those of more and the linear one nothing or less (without / with them, us, blocks of up to 16
+    // bytes: two phases, 30 ranks 79 / 53, 200 84 / 61, 500 113 / 81; more, 200, r = 8 99 / 98, r = 2 151 / 163, 300, r = 2 188 / 210, 500, r = 8 135 / 139, r
+    // = 3 193 / 209, r = 2 248 / 296, 600, r = 2 286 / 348; linear, 60 51.5 / 51.3, 200 54.2 / 55.3, 500 58.4 / 60.4).
     const bool worth = g_static.early.worth(P, ranks_per_node, rl, rg, pr.opt.t_layout);
-    if (P <= kEarlyTotalsRanks && worth) {
+    if (P <= kEarlyTotalsRanks && dp.host.phases.size() == 2 && worth) {
         pr.early_mem = cv.base + cv.off;
         pr.early_bytes = cv.cap - cv.off;
     }

@@ -317,7 +317,7 @@ def case_single_launch(t, calls):
 def case_early_use(t, P, radix, calls, noalloc):
     """Whether each of `calls` on one schedule -- "direct", "engine", "staged", "slots" -- launched early kernels: behind validation and ahead of
     what needs its result."""
-    short, engine = t.problem(np.full((P, P), 300), gap=1), t.problem(_engine_counts(P), gap=1)
+    short, engine = t.problem(np.full((P, P), 40), gap=1), t.problem(_engine_counts(P), gap=1)
     out = []
     for kind in ["direct"] + calls:
         prob = engine if kind == "engine" else short

@@ -57,8 +57,7 @@ def test_a_call_whose_workspace_is_too_small_has_ended(runtime, kind, P, radix):
     assert any(k.startswith("k_t_places") for k in kernels) and not _hops(kernels) and done
 
 
-@pytest.mark.parametrize("P,radix", [(100, 4), (100, 100)])
-@pytest.mark.parametrize("noalloc", [False, True])
+@pytest.mark.parametrize("P,radix,noalloc", [(100, 4, False), (100, 100, False), (100, 10, False), (100, 10, True)])
 def test_early_kernels_that_were_for_nothing_are_left_out(runtime, P, radix, noalloc):
     """After two calls in a row whose phases had no use for them, until one comes that has."""
     calls = ["direct"] + ["engine"] * 4 + ["direct"] * 2 + ["engine", "direct"] * 2 + ["engine"] * 3 + ["direct"] * 2
@@ -70,3 +69,9 @@ def test_calls_that_launch_none_do_not_count(runtime):
     calls = ["engine", "staged", "staged", "slots", "slots", "direct", "engine", "staged", "engine", "staged", "engine"]
     want = [True] + [False] * 4 + [True] * 2 + [False] + [True] + [False] * 2
     assert fake_hip.run(runtime, "early_use", 100, 4, calls, False) == want
+
+
+@pytest.mark.parametrize("P,radix,early", [(100, 10, True), (512, 23, True), (512, 500, True), (513, 23, False), (100, 9, False), (100, 2, False), (100, 100, False)])
+def test_the_call_that_allocates_nothing_has_them_in_two_phases(runtime, P, radix, early):
+    """Up to 512 ranks: it waits for a copy behind them."""
+    assert fake_hip.run(runtime, "early_use", P, radix, ["direct"] * 2, True) == [early] * 2
