@@ -7,6 +7,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <climits>
+#include <cstddef>
 #include <cstdint>
 #include <type_traits>
 
@@ -1191,6 +1192,7 @@ __device__ __forceinline__ unsigned long long exact_t_src(unsigned char* T, cons
 // persistent plan resolves them before its T is allocated.
 // ------------------------------------------------------------------------------------------
 struct ResolveArgs {
+    HopDev hop;                         // (first: DirectArgs)
     const int32_t* nxt;                 // [P][P] block sizes after the phase's size exchange (the receiver's view); k_resolve_hop only
     const int32_t* sendcounts;          // block sizes for the kernels that find their blocks themselves (block_bytes)
     const int32_t* recvcounts;
@@ -1206,7 +1208,6 @@ struct ResolveArgs {
     long long slots;                    // T in slots: slot s of rank p at offset (p * slots + s) * slot_bytes
     long long slot_bytes;
     ExactT x;                           // T in exact size
-    HopDev hop;
     int exact_sizes;                    // 1: every size is the block's byte count (k_hop_direct copies exactly that), also into T
 };
 
@@ -1303,16 +1304,22 @@ constexpr DirectShape direct_shape(int lpb, bool tall) {
 }
 constexpr int direct_segs(DirectShape s) { return kWave / s.wave_ranks * (4 / s.waves_r); }
 constexpr int direct_ranks(DirectShape s) { return s.wave_ranks * s.sets * s.waves_r; }
+// What a kernel with hop arrays reads comes first, in one 64-byte line: a wave that is launched waits for its arguments line after line.  Three
+// lines / two / one, us per start, up to 1 KiB: 60 ranks, r = 2 30.2 / 29.0 / 27.9, 150, r = 16 15.9 / - / 15.0, 256, r = 2 83.1 / 81.3 / 79.4, 400, r = 3
+// 134.7 / - / 132.0; up to 200 bytes, 500, r = 4 49.6 / - / 48.9.
 struct DirectArgs {
-    ResolveArgs r;                      // hop: only when RESOLVED
     unsigned char* T;
-    int seg_lo, seg_hi;
-    int iters;                          // steps of segments per workgroup (k_hop_direct)
-    int segs;                           // segments per wave, at most 64 (k_hop_rows)
     unsigned long long user_limit;      // address one past the last byte of S that holds a block
-    uint2* part;                        // [grid.x][P]: payload bytes and chunks of the tile column, per receiver (null: not wanted)
+    int seg_lo, seg_hi;
+    union {
+        int iters;                      // steps of segments per workgroup (k_hop_direct)
+        int segs;                       // segments per wave, at most 64 (k_hop_rows)
+    };
     int own;                            // so many rows of workgroups in front move the ranks' own blocks (k_hop_direct, k_hop_rows)
+    ResolveArgs r;                      // hop: only when RESOLVED
+    uint2* part;                        // [grid.x][P]: payload bytes and chunks of the tile column, per receiver (null: not wanted)
 };
+static_assert(offsetof(DirectArgs, r) + offsetof(ResolveArgs, nxt) == 64, "one line");
 
 typedef v4u v4u_any __attribute__((aligned(1)));
 typedef unsigned long long u64_any __attribute__((aligned(1)));
