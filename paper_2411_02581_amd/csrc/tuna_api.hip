@@ -2560,20 +2560,19 @@ struct Model {
     double c[kModelTerms];
 };
 struct ModelSet {
-    Model m[2] = {{{0.0405, 0.0378, 0.0068, 1.0048, 0.0414, 0.0, 0.0}},            // [0] three stages
-                  // [1] one-kernel hops; a gigabyte of short blocks is not priced under one of long blocks, though
-                  // the fit, whose short-block problems are mostly cache resident, says 0.30
-                  {{0.0366, 0.0133, 0.0016, 0.3783, 0.0193, 0.0053, 0.3800}}};
+    Model m[2] = {{{0.0382, 0.0352, 0.0145, 1.0116, 0.0244, 0.0, 0.0}},            // [0] three stages
+                  // [1] one-kernel hops; a gigabyte of short blocks is not priced under one of long blocks (the fit: 0.373)
+                  {{0.0166, 0.0102, 0.0033, 0.3783, 0.0124, 0.0027, 0.3800}}};
     // T in the paper's slots of M bytes: the bytes that pass through T cost more the emptier the slots are
     // (sparse writes and reads): their share of the byte term is scaled by 1 + k * (1 - mean / M)
     double slot_penalty[2] = {0.25, 0.45};
     // byte-granular problems (some count, displacement or buffer address is not a multiple of 4) run the
     // kernel variants that load and store single bytes at block edges: their byte term is scaled by this
-    double byte_granular[2] = {1.15, 1.05};
+    double byte_granular[2] = {1.15, 1.044};
     // line-granular problems (every count, displacement and buffer address is a multiple of 128) run the kernel
     // variants that read their sources with streaming loads, and no block shares a line with its neighbour:
     // their byte and block terms are scaled by this
-    double line_granular[2] = {0.90, 0.83};
+    double line_granular[2] = {0.908, 0.855};
     bool calibrated = false;
 };
 ModelSet g_model;
@@ -2599,10 +2598,10 @@ Features features_of(const PlanHost& pl, double payload_bytes, bool fused, int64
     }
     (small ? f.msmall : f.mblocks) = moving / 1e6;
     // A short block of a schedule of one phase is looked up in the receive counts and the displacements; with several
-    // phases its place in T is scanned, stored and looked up twice, and most lookups leave the rows of one rank.  Four
-    // times the constant fits uniform [0, 16] B at P = 2048 within 10 % at r = 2, 8 and P; three times where
-    // k_hop_senders finds them (predicted / measured: r = 13 0.87, r = 32 1.14; up to 60 bytes 0.79 and 0.98; P = 1000 1.07 and
-    // 1.06; P = 4096, r = 64 0.90, P = 6000, r = 77 0.84).
+    // phases its place in T is scanned, stored and looked up twice, and most lookups leave the rows of one rank: four times the
+    // constant, and three times in phases of many rounds (by_senders), whose tiles have a sender's blocks side by side.  Predicted / measured, blocks
+    // of up to 16 bytes and of up to 60: P = 1000, r = 2 0.94 and 0.89, r = 8 1.14 and 1.06, r = 16 1.07 and 1.01; P = 2048, r = 8 1.14 and 0.91, r = 13 1.05 and
+    // 0.84, r = 46 1.20 and 0.91; P = 4000, r = 8 1.08 and 0.77, r = 46 0.96 and 0.77.
     if (small && f.phases > 1.0) f.msmall = (4.0 * moving - by_sender) / 1e6;
     // sizes are taken to be independent of the rank distance: every slot index carries payload / P^2
     (small ? f.small_gb : f.hop_gb) = P > 0 ? payload_bytes * (moving / (P * P)) / 1e9 : 0.0;
