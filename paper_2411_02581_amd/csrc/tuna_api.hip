@@ -1255,7 +1255,7 @@ constexpr int kTallMinRounds = 7;
 int lanes_per_block(int64_t max_block) { return max_block <= 16 ? 1 : (max_block <= 64 ? 4 : 16); }
 int direct_lpb(const Prepared& pr) { return lanes_per_block(pr.max_count); }
 bool runs_direct(const Prepared& pr);
-// Phases of a schedule of several that an immediate call's k_hop_senders moves: many rounds, and 256 blocks of a rank to each.
+// Phases of a schedule of several that an immediate call's k_hop_senders moves: many rounds, up to about 256.
 bool by_senders(const PhaseHost& ph) {
     return ph.nz >= kSenderMinRounds && ph.nz <= kSenderMaxRounds && (long long)((ph.nseg + 255) / 256) * ph.nz <= ph.nseg;
 }
@@ -1658,6 +1658,10 @@ bool runs_direct(const Prepared& pr) {
 // the wait hides too, in place of the hops' partial sums and k_phase_sums, the call's last kernel (2048 ranks 10 us, which it does not
 // hide).  A linear schedule has no places, its totals are found there all the same (k_row_totals).  The call that allocates nothing has
 // them in schedules of two phases (run_static).
+// Without them / below the limit, us per call: up to 16 B, P = 700, r = 24 69.9 / 61.7, P = 1500, r = 4 229 / 225, P = 2048, r = 46 144 / 139; above it, without /
+// with: P = 2048, r = 8 273 / 269, r = 2 640 / 641, P = 2600, r = 2 1054 / 1068, P = 3200, r = 8 669 / 667, up to 200 3885 / 3905 (r = 2).
+// Totals by the hops / early: up to 16 B, P = 128, r = 4 51.2 / 44.9, P = 512, r = 2 138 / 132, linear 39.7 / 34.2, up to 1000, P = 512, r = 16 166 / 160; above 512: P =
+// 768, r = 4 99.2 / 95.1, r = 2 193 / 191, up to 200 278 / 282, P = 1500, r = 4 224 / 226, linear 65.6 / 58.8 (a side that would gain and is not taken).
 constexpr double kEarlyEntries = 9e6;
 constexpr int kEarlyTotalsRanks = 512;
 

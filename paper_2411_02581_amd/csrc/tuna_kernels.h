@@ -62,21 +62,22 @@ struct Status {
     unsigned int reserved2;
 };
 
-// The per-phase table of moving blocks on the device, one array per field (message order).
+// The per-phase table of moving blocks (segments) on the device, one array per field: in message order or in that of the slot indices
+// (PlanScalars.by_index).
 struct SegDev {
     const int32_t* e;      // slot index j*Q + l
     const int32_t* z;      // digit value: which message, partner distance z*r^x
     const int32_t* src;    // source T slot or -1 (send buffer)
     const int32_t* dst;    // destination T slot or -1 (receive buffer)
     const int32_t* srcph;  // phase in which the block arrived in T, or -1 (send buffer)
-    const int32_t* srcseg; // its position in that phase's message order
+    const int32_t* srcseg; // its position in that phase's table
     const int32_t* scls;   // exact-size T: class (arrival phase, this phase) the block is read from, or -1
     const int32_t* dcls;   // exact-size T: class (this phase, next move) the block is stored into, or -1
 };
 
 // Exact-size T.  A block that arrives in phase f and moves again in phase y waits in T from f to y: the
 // blocks of one such class (f, y) lie together, rank after rank, each rank's part back to back in
-// message order (padded to 16 bytes per block, to a 128-byte line per rank).  Where a class lies in T
+// the order of the segments (padded to 16 bytes per block, to a 128-byte line per rank).  Where a class lies in T
 // is decided on the host from the classes' sizes (the validation pass sums them) and lifetimes: classes
 // whose lifetimes do not overlap share memory, so T holds what waits in it at one time, not what ever
 // passed through it.  All offsets are in 16-byte chunks.
@@ -86,11 +87,11 @@ struct ExactT {
     int* csub;               // [classes][P]: chunks of rank p's part of a class
     int* tpos;               // [phases][P][P]: chunk offset, inside its rank's part of its class, of every block that the phase stored: by segment
                              // where phases find their blocks themselves (k_t_places), else by slot index
-    int* tpre;               // [P][ld]: the same offsets for the phase being run, in message order
+    int* tpre;               // [P][ld]: the same offsets for the phase being run, by segment
     int ld;
     int phase;               // index of the phase being run
     // the T-bound blocks of the phase being run, grouped by class: tord[tcls[3k+1] .. +tcls[3k+2]) are the
-    // segment indices of class tcls[3k], in message order
+    // segment indices of class tcls[3k], ascending
     const int32_t* tord;
     const int32_t* tcls;
     int ncls;                // classes the phase being run stores into
@@ -1286,9 +1287,9 @@ __global__ void __launch_bounds__(256) k_resolve_hop(const ResolveArgs a) {
 // phases 0.44 -> 0.27 ms; uniform [0, 248] B, P = 4096, linear 1.64 -> 1.24 ms.  Blocks of more than 64 bytes and payloads
 // beyond the caches are better off in k_hop_rows (block_kernel).
 //   TALL tiles (16 receivers x few segments, LPB = 1 and 4) share the lines of S and sdispls between receivers: that pays
-// when a round has few blocks, as in the linear schedule (64-byte blocks: 1.57 against 2.0 ms).  With many blocks per
-// round neighbouring receivers read other rows, and long rows of one receiver are better (uniform [0, 16] B, two phases:
-// 0.26 against 0.33 ms).
+// when a round has few blocks, as in the linear schedule (64-byte blocks: 1.57 against 2.0 ms), or neighbouring segments are of other rounds,
+// as in the first phase in the order of the slot indices (direct_tall).  With many blocks of one round side by side neighbouring receivers read
+// other rows, and long rows of one receiver are better (uniform [0, 16] B, two phases in message order: 0.26 against 0.33 ms).
 //   STREAM: 1 = streaming stores (chunk-granular data; -4 %, but +5 % and more where blocks share 16-byte chunks),
 // 2 = streaming loads too (whole lines; another -4 %).
 //   Payload bytes and 16-byte chunks are summed per receiver and stored as one partial result per tile column
@@ -1358,10 +1359,11 @@ __device__ __forceinline__ void short_store(unsigned long long dst, unsigned lon
 // covered the digits up to x of its distance, so it comes from O = (n, g) + that part and is bound for D = O - (j, l)
 // (Algorithm "TuNA", line 14, without the exchange: in one memory every size can be looked up where the caller wrote
 // it).  The entry of recvcounts is the nearer one where neighbouring blocks have one destination (final blocks, and
-// all later phases: runs of r^(x+1) blocks), that of sendcounts where they have one origin: blocks that never moved before, to
-// one sender's k_hop_senders, and to one receiver's kernels while r^(x+1) is below kNearSendRadix (runs of r^(x+1) in P / r^(x+1) rows of
-// recvcounts against r^x - 1 strided rows of sendcounts; sendcounts / recvcounts, us per call: up to 16 B, P = 2048, r = 8 283 / 275,
-// P = 1000, r = 4 131.5 / 129, up to 40, P = 2048, r = 8 386 / 380, normal 128 B, P = 4096, r = 16 3137 / 3089; k_hop_senders, P = 2048, r = 46 162 / 173).
+// all later phases: runs of r^(x+1) blocks), that of sendcounts where they have one origin: blocks that never moved before, while
+// r^(x+1) is below kNearSendRadix (near_s; runs of r^(x+1) in P / r^(x+1) rows of recvcounts against r^x - 1 strided rows of sendcounts).
+// Never / below 8 / always, us per call: up to 16 B, P = 2048, r = 3 440 / 430 / 442, r = 4 370 / 366 / 375, r = 8 275 / 274 / 286, r = 46 139 / 138 / 150, P =
+// 4000, r = 2 2281 / 2244 / 2301, r = 16 810 / 810 / 853; up to 60, P = 2048, r = 4 631 / 630 / 644, P = 1000, r = 6 140 / 137 / 140; up to 200, P = 1000, r = 46
+// 133 / 133 / 139; 500 ranks the same.
 constexpr int kNearSendRadix = 8;
 __device__ __forceinline__ const int32_t* block_bytes(const int32_t* sendcounts, const int32_t* recvcounts, bool in_s, int n, int g, int j,
                                                       int l, int P, int Q, int N, int dim, int rx1) {
@@ -1380,8 +1382,8 @@ __device__ __forceinline__ const int32_t* block_bytes(const int32_t* sendcounts,
 // k_t_places, k_t_bases: exact-size T for phases that find their blocks themselves: the places of the blocks that every
 // phase stores into T, of all phases at once -- block sizes come from the caller's matrices (block_bytes), so no phase
 // waits for another's size exchange.  k_t_places: one workgroup per receiver and class scans the chunks of the class's
-// blocks in message order; the offsets inside the receiver's part go to tpos by slot index, the part's size to csub.
-// In the order of the segments, that is of the slot indices (slot_order).  A copy of the first phase's offsets and sizes by segment, which
+// blocks in the order of the segments, that is of the slot indices (slot_order); the offsets inside the receiver's part go to tpos by segment,
+// the part's size to csub.  A copy of the first phase's offsets and sizes by segment, which
 // paid in message order, costs now: P = 2048, r = 46 161 -> 182 us per call, uniform [0, 64] B, P = 4096, r = 64 1181 -> 1240.
 // k_t_places_slots: the same for larger radices, the sizes read for all slot indices in turn: consecutive ones of one round after
 // the other are consecutive entries of a row of recvcounts and of tpos.  They go through the LDS to be scanned
@@ -1808,11 +1810,12 @@ template <int LPB, bool TALL, int STREAM, bool DENSE, bool RESOLVED>
 __global__ void __launch_bounds__(256) k_hop_direct(const DirectArgs a) { hop_direct<LPB, TALL, STREAM, DENSE, RESOLVED>(a); }
 
 // ------------------------------------------------------------------------------------------
-// k_hop_senders: k_hop_direct's work in phases of many rounds of schedules of several phases, in tiles whose blocks of one sender lie side
-// by side.  Many rounds have many senders, and with the segments in the order of the slot indices (slot_order) a phase's senders
-// change either from segment to segment -- the first phase, r^x = 1: neighbouring receivers then get neighbouring blocks of a sender, so
+// k_hop_senders: k_hop_direct under a name of its own in phases of many rounds of schedules of several phases (by_senders), whose tiles have a
+// sender's blocks side by side.  Many rounds have many senders, and with the segments in the order of the slot indices (slot_order) a phase's
+// senders change either from segment to segment -- the first phase, r^x = 1: neighbouring receivers then get neighbouring blocks of a sender, so
 // tiles are TALL, 16 receivers x 16 rounds = 31 senders with up to 16 blocks each, stored as 16 runs of T -- or after r^x
-// segments, and a row of one receiver's segments is a run of a sender's part of T and of R (direct_tall).
+// segments, and a row of one receiver's segments is a run of a sender's part of T and of R (direct_tall).  The code is k_hop_direct's; what the
+// rule decides is the tile in message order, who moves the own blocks (own_in_first) and what the cost model asks, and traces keep these phases apart.
 //   Bound by memory, the lines of the matrices and of T's places above all.  Against workgroups that take the blocks that one rank sends
 // (its loads together, its stores a receiver each), us per call: uniform [0, 16] B, P = 2048, r = 46 162 / 148, P = 6000, r = 77 1796 / 1509,
 // P = 1024, r = 32 76.5 / 73; up to 64 B, P = 4096, r = 64 1203 / 1135, up to 60, P = 2048, r = 16 409 / 391, P = 1024, r = 32 93 / 95; up to 40, r = 13
