@@ -37,7 +37,8 @@ struct DevicePlan {
     PlanHost host;
     std::vector<SegDev> d_seg;
     void* mem = nullptr;                 // the memory of everything below (nullptr: it lies in the static scratch)
-    hipStream_t built_on = nullptr;      // stream the table kernels were enqueued on
+    hipStream_t built_on = nullptr;      // stream the table kernels were enqueued on (it may be gone by now)
+    hipEvent_t made = nullptr;           // their end (a cached schedule's)
     bool complete = false;               // known to be there (a later call has waited for kernels behind them)
     std::vector<int32_t*> d_zt;
     unsigned long long* d_mask = nullptr; // [P]: phases in which the block with a slot index moves (move_mask)
@@ -348,6 +349,7 @@ DataSizes data_sizes_for(const PlanHost& pl, long long M, unsigned long long tot
 
 void free_device_plan(DevicePlan& dp) {
     if (dp.mem) (void)hipFree(dp.mem);
+    if (dp.made) (void)hipEventDestroy(dp.made);
     dp = DevicePlan{};
 }
 
@@ -440,14 +442,16 @@ int get_plan(int P, int Q, int rl, int rg, bool fused, bool by_index, hipStream_
         HIPCHK(hipMalloc(&dp.mem, bytes));
         Carver cv(dp.mem, bytes);
         carve_tables(cv, dp);
+        HIPCHK(hipEventCreateWithFlags(&dp.made, hipEventDisableTiming));
         if (const int rc = launch_tables(dp, by_index, nullptr, 0, s)) return rc;
+        HIPCHK(hipEventRecord(dp.made, s));
         dp.built_on = s;
         guard.dp = nullptr;
         it = sh.plans.emplace(key, std::move(dp)).first;
     }
     // a cached schedule built on another stream: make sure its tables are complete
     if (it->second.built_on != s && !it->second.complete) {
-        HIPCHK(hipStreamSynchronize(it->second.built_on));
+        HIPCHK(hipEventSynchronize(it->second.made));
         it->second.complete = true;
     }
     *out = &it->second;

@@ -29,6 +29,7 @@ void merge(Clock& a, const Clock& b) { for (auto& x : b) a[x.first] = std::max(a
 
 struct Stream {
     bool recording = false;             // what it is given is dropped, and waiting for it fails
+    bool gone = false;                  // destroyed: waiting for it fails
     std::vector<std::function<void()>> ops;
     size_t done = 0;
     Clock now;
@@ -201,6 +202,7 @@ hipError_t hipMemcpyAsync(void* d, const void* src, size_t n, hipMemcpyKind kind
 }
 hipError_t hipStreamSynchronize(hipStream_t s) {
     if (streams[s].recording) return hipErrorStreamCaptureUnsupported;
+    if (streams[s].gone) return hipErrorContextIsDestroyed;
     wait(s);
     return hipSuccess;
 }
@@ -239,6 +241,7 @@ hipError_t hipFuncGetAttributes(hipFuncAttributes* f, const void*) { std::memset
 hipError_t hipMemGetInfo(size_t* f, size_t* t) { *f = *t = (size_t)288 << 30; return hipSuccess; }
 
 void fake_record(long s, int on) { streams[(hipStream_t)s].recording = on != 0; }
+void fake_destroy(long s) { wait((hipStream_t)s); streams[(hipStream_t)s].gone = true; }
 void fake_no_streams() { no_streams = true; }
 int fake_notes() { return (int)notes.size(); }
 const char* fake_name(int i) { return notes[i].name.c_str(); }

@@ -344,6 +344,22 @@ def case_rows_of_validation(t, units, P, radix):
     return [t.fake.fake_end(first + names.index("k_validate")), t.fake.fake_ptr(first + names.index("k_build_tables"))]
 
 
+def case_stream_gone(t, kind, P, radix, plan, first):
+    """The return code of a call, or of the making of a plan, on a stream after the one that the schedule was first used on has been destroyed, or
+    is being recorded."""
+    prob = t.problem(_engine_counts(P) if kind == "engine" else np.full((P, P), 300), gap=1)
+    fields = {"mode": t.b.TUNA_MODE_STAGED if kind == "staged" else t.b.TUNA_MODE_FUSED, "t_layout": t.b.TUNA_T_SLOTS if kind == "slots" else t.b.TUNA_T_EXACT}
+    assert t.call(prob, radix, S1, **fields) == 0
+    if first == "destroyed":
+        t.fake.fake_destroy(S1)
+    else:
+        t.fake.fake_record(S1, 1)
+    if plan:
+        handle = ctypes.c_void_p(None)
+        return t.lib.tuna_alltoallv_init_ex(None, *prob[1], P, 0, radix, radix, ctypes.byref(t.options(**fields)), S2, ctypes.byref(handle))
+    return t.call(prob, radix, S2, **fields)
+
+
 CASES = {k[5:]: f for k, f in list(globals().items()) if k.startswith("case_")}
 
 if __name__ == "__main__":

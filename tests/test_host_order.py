@@ -82,3 +82,11 @@ def test_rows_of_validation_lie_in_front_of_the_tables(runtime, units, P, radix)
     """Also where a device shows as few compute units as one of its parts has: what one workgroup writes does not get less."""
     end, tables = fake_hip.run(runtime, "rows_of_validation", units, P, radix)
     assert 0 < end <= tables
+
+
+@pytest.mark.parametrize("first", ["destroyed", "recorded"])
+@pytest.mark.parametrize("plan", [False, True])
+@pytest.mark.parametrize("kind", ["direct", "engine", "slots", "staged"])
+def test_a_schedule_outlives_the_stream_it_was_made_on(runtime, kind, plan, first):
+    """Its tables are in memory of the library's: who uses it next on another stream does not ask for the first one."""
+    assert fake_hip.run(runtime, "stream_gone", kind, 100, 4, plan, first) == 0
