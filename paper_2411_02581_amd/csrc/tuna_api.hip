@@ -1697,12 +1697,12 @@ void want_totals(const Prepared& pr, PlaceArgs& a) {
         a.fin[i + 1] = (int)(ph.dim == 0 ? hi : hi * pr.Q);
     }
 }
-int launch_places(const Prepared& pr, const PlaceArgs& a, int more, hipStream_t s) {
+int launch_places(const Prepared& pr, const PlaceArgs& a, int more, const Status::Verdict* verdict, hipStream_t s) {
     const dim3 grid((unsigned)pr.P, (unsigned)(a.rows + more));
     if (pr.P <= kPlaceSlotRanks && pr.dp->host.phases[0].r >= kPlaceSlotRadix)
-        hipLaunchKernelGGL(k_t_places_slots, grid, dim3(kScanThreads), (size_t)a.most * 4 + (size_t)pr.P * 2, s, a);
+        hipLaunchKernelGGL(k_t_places_slots, grid, dim3(kScanThreads), (size_t)a.most * 4 + (size_t)pr.P * 2, s, a, verdict);
     else
-        hipLaunchKernelGGL(k_t_places, grid, dim3(kScanThreads), 0, s, a);
+        hipLaunchKernelGGL(k_t_places, grid, dim3(kScanThreads), 0, s, a, verdict);
     HIPCHK(hipGetLastError());
     return TUNA_OK;
 }
@@ -1712,7 +1712,7 @@ int launch_bases(const PlaceArgs& a, hipStream_t s) {
     return TUNA_OK;
 }
 
-// verdict: the status block holds what validation found when these kernels run.
+// verdict: the status block holds what validation found when these kernels run (k_validate_finish has run).
 int launch_early(Prepared& pr, bool verdict, hipStream_t s) {
     const PlanHost& pl = pr.dp->host;
     const size_t phases = pl.phases.size();
@@ -1730,13 +1730,13 @@ int launch_early(Prepared& pr, bool verdict, hipStream_t s) {
     const bool totals = pr.P <= kEarlyTotalsRanks;
     if (totals) want_totals(pr, a);
     if (!cm.ok || (phases == 1 && !totals) || (size_t)(a.rows + a.nfin) * (size_t)pr.P * sizeof(ulonglong2) > hop_bytes_for(pr.P, hld)) return TUNA_OK;
-    a.verdict = verdict ? 1 : 0;
     a.slots_rule = phases > 1 && pr.opt.t_layout == TUNA_T_AUTO ? 1 : 0;
     a.max_block = pr.P > kLongMaxRanks ? kRowsMaxBytes : INT_MAX;
     pr.early = true;
     pr.early_totals = totals;
-    if (phases > 1) return launch_places(pr, a, a.nfin, s);
-    hipLaunchKernelGGL(k_row_totals, dim3((unsigned)((pr.P + kScanThreads / kWave - 1) / (kScanThreads / kWave))), dim3(kScanThreads), 0, s, a);
+    const Status::Verdict* found = verdict ? &pr.sb.d_status->verdict : nullptr;
+    if (phases > 1) return launch_places(pr, a, a.nfin, found, s);
+    hipLaunchKernelGGL(k_row_totals, dim3((unsigned)((pr.P + kScanThreads / kWave - 1) / (kScanThreads / kWave))), dim3(kScanThreads), 0, s, a, found);
     HIPCHK(hipGetLastError());
     return TUNA_OK;
 }
@@ -1759,7 +1759,7 @@ int launch_t_places(Prepared& pr, hipStream_t s, bool* own = nullptr) {
         a.S = (const unsigned char*)pr.sendbuf; a.sdispls = pr.sdispls;
     }
     // (a row behind the classes' is the own blocks')
-    if (const int rc = launch_places(pr, a, own ? 1 : 0, s)) return rc;
+    if (const int rc = launch_places(pr, a, own ? 1 : 0, nullptr, s)) return rc;
     return launch_bases(a, s);
 }
 

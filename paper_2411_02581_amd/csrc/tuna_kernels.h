@@ -60,6 +60,13 @@ struct Status {
     unsigned int phase_units[64][2];      // wave units per phase: [0] receive-side layout, [1] send-side layout
     unsigned int self_units;              // wave units of the ranks' own blocks when the copy engine moves them
     unsigned int reserved2;
+    // What an immediate call's validation found, once more, for kernels of the call that run ahead of the host (no_places): unlike the
+    // head it is left alone by plans and sizing queries, which do not wait for a call in flight.
+    struct Verdict {
+        unsigned int flags;
+        int max_count;
+        unsigned long long total_bytes;
+    } verdict;
 };
 
 // The per-phase table of moving blocks (segments) on the device, one array per field: in message order or in that of the slot indices
@@ -578,6 +585,7 @@ __global__ void __launch_bounds__(256) k_validate_finish(const unsigned long lon
             fa |= red[w][0]; m = max(m, red[w][1]); by += red[w][2]; ch += red[w][3]; ex = max(ex, red[w][4]);
             sb += red[w][6]; wi = max_windows(wi, red[w][7]);
         }
+        if (clear_totals) st->verdict = Status::Verdict{(unsigned int)(fa >> 32), (int)m, by};
         st->flags = (unsigned int)(fa >> 32);
         st->align_bits = (unsigned int)(fa & 127u);
         st->max_count = (int)m;
@@ -1428,8 +1436,7 @@ struct PlaceArgs {
     int rows, nfin;
     int fin[kPlaceMaxPhases + 1];       // the final blocks of phase x are the slot indices fin[x] .. fin[x + 1] - 1
     Status* st;
-    // kernels that run before the host has seen what validation found: nothing is to be done where they say so
-    int verdict;            // 1: *st holds it
+    // kernels that run before the host has seen what validation found: nothing is to be done where it says so (no_places)
     int slots_rule;         // full slots are taken (slots_are_full)
     int max_block;
 };
@@ -1438,9 +1445,10 @@ __host__ __device__ inline bool slots_are_full(unsigned long long total_bytes, i
     const double slot_bytes = (double)((max_count + 127) / 128 * 128);
     return (double)total_bytes >= 0.9 * (double)P * (double)P * slot_bytes;
 }
-__device__ __forceinline__ bool no_places(const PlaceArgs& a) {
-    if (!a.verdict) return false;
-    const Status& st = *a.st;
+// verdict: null where it is not known when the kernels run
+__device__ __forceinline__ bool no_places(const PlaceArgs& a, const Status::Verdict* verdict) {
+    if (!verdict) return false;
+    const Status::Verdict st = *verdict;
     return (st.flags & 7u) || st.total_bytes == 0 || st.max_count > a.max_block || (a.slots_rule && slots_are_full(st.total_bytes, a.P, st.max_count));
 }
 // Sum over a workgroup of kScanThreads, in its thread 0.
@@ -1484,9 +1492,9 @@ __device__ __forceinline__ void final_totals(const PlaceArgs& a, int p, int x) {
     if (threadIdx.x == 0) a.part[(size_t)(a.rows + x) * a.P + p] = make_ulonglong2(bytes, chunks);
 }
 // k_row_totals: the totals of a linear schedule's only phase, a wave per receiver.  Validation has cleared them.
-__global__ void __launch_bounds__(kScanThreads) k_row_totals(const PlaceArgs a) {
+__global__ void __launch_bounds__(kScanThreads) k_row_totals(const PlaceArgs a, const Status::Verdict* verdict) {
     __shared__ unsigned long long s_sum[kScanThreads / kWave];
-    if (no_places(a)) return;
+    if (no_places(a, verdict)) return;
     const int lane = threadIdx.x & (kWave - 1), p = blockIdx.x * (kScanThreads / kWave) + threadIdx.x / kWave;
     unsigned long long bytes = 0, chunks = 0;
     if (p < a.P) {
@@ -1522,12 +1530,12 @@ __device__ __forceinline__ int place_phase(const PlaceArgs& a, int row) {
     while (f + 1 < a.nph && a.ph[f + 1].first <= row) ++f;
     return f;
 }
-__global__ void __launch_bounds__(kScanThreads) k_t_places(const PlaceArgs a) {
+__global__ void __launch_bounds__(kScanThreads) k_t_places(const PlaceArgs a, const Status::Verdict* verdict) {
     __shared__ int wsum[kScanThreads / kWave];
     __shared__ unsigned long long s_sum[kScanThreads / kWave];
     const int p = blockIdx.x, P = a.P;
     if ((int)blockIdx.y == a.own) { own_block(a.S, a.sendcounts, a.sdispls, a.R, a.rdispls, P, p); return; }
-    if (no_places(a)) return;
+    if (no_places(a, verdict)) return;
     if ((int)blockIdx.y >= a.rows) { final_totals(a, p, blockIdx.y - a.rows); return; }
     const int f = place_phase(a, blockIdx.y);
     const PlacePhase& ph = a.ph[f];
@@ -1564,7 +1572,7 @@ __global__ void __launch_bounds__(kScanThreads) k_t_places(const PlaceArgs a) {
 constexpr int kPlaceSlotRanks = 8192;       // 48 KiB of LDS
 constexpr int kPlaceSlotRadix = 8;
 // dynamic LDS: the blocks of the largest class (a.most), 4 bytes each, and 2 bytes per slot index
-__global__ void __launch_bounds__(kScanThreads) k_t_places_slots(const PlaceArgs a) {
+__global__ void __launch_bounds__(kScanThreads) k_t_places_slots(const PlaceArgs a, const Status::Verdict* verdict) {
     extern __shared__ int s_val[];                       // bytes by index inside the class
     __shared__ int wsum[kScanThreads / kWave];
     __shared__ unsigned long long s_sum[kScanThreads / kWave];
@@ -1572,7 +1580,7 @@ __global__ void __launch_bounds__(kScanThreads) k_t_places_slots(const PlaceArgs
     unsigned short* s_at = reinterpret_cast<unsigned short*>(s_val + a.most);        // by slot index: the index inside the class
     const int p = blockIdx.x, P = a.P;
     if ((int)blockIdx.y == a.own) { own_block(a.S, a.sendcounts, a.sdispls, a.R, a.rdispls, P, p); return; }
-    if (no_places(a)) return;
+    if (no_places(a, verdict)) return;
     if ((int)blockIdx.y >= a.rows) { final_totals(a, p, blockIdx.y - a.rows); return; }
     const int f = place_phase(a, blockIdx.y);
     const PlacePhase& ph = a.ph[f];
@@ -1627,7 +1635,6 @@ __global__ void __launch_bounds__(kScanThreads) k_t_places_slots(const PlaceArgs
 }
 __global__ void __launch_bounds__(kScanThreads) k_t_bases(const PlaceArgs a) {
     __shared__ long long wc[kScanThreads / kWave];
-    if (no_places(a)) return;
     if ((int)blockIdx.x >= a.rows) { phase_totals(a, blockIdx.x - a.rows); return; }
     const PlacePhase& ph = a.ph[place_phase(a, blockIdx.x)];
     const int cid = ph.tcls[3 * (blockIdx.x - ph.first)];

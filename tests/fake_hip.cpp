@@ -35,7 +35,7 @@ struct Stream {
     Clock now;
 };
 struct Event { hipStream_t s = nullptr; size_t upto = 0; Clock at; };
-struct Note { std::string name; hipStream_t s; Clock before; const void* ptr; const void* end; };     // ptr: the status block, or a word of one, or a schedule's tables; end: of the rows that k_validate writes
+struct Note { std::string name; hipStream_t s; Clock before; const void* ptr; const void* end; };     // ptr: the status block, or a word of one (what a kernel ahead of the host reads of it), or a schedule's tables; end: of the rows that k_validate writes
 
 struct Launch { dim3 grid, block; size_t lds; hipStream_t s; } launch;
 
@@ -170,6 +170,8 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** a, size_t, hip
         const int m = arg<int>(a, 1);
         ptr = p;
         op = [=] { std::memset(p, 0, (size_t)m * 8); };
+    } else if (is("k_t_places") || is("k_t_places_slots") || is("k_row_totals")) {
+        ptr = arg<const void*>(a, 1);
     } else if (is("k_layout_base")) {
         ptr = arg<const void*>(a, 4);
     } else if (is("k_build_tables")) {

@@ -360,6 +360,20 @@ def case_stream_gone(t, kind, P, radix, plan, first):
     return t.call(prob, radix, S2, **fields)
 
 
+def case_verdict(t, P, radix):
+    """Where the kernels that a call launches ahead of the host look up what validation found, from the status block on."""
+    prob = t.problem(np.random.default_rng(P).integers(0, 60, (P, P)))
+    assert t.call(prob, radix, S1) == 0
+    first = t.fake.fake_notes()
+    assert t.call(prob, radix, S1) == 0
+    names = [k[0] for k in t.kernels(first)]
+    status = t.fake.fake_ptr(first + names.index("k_validate"))
+    early = [i for i, k in enumerate(names) if k.startswith("k_t_places") or k == "k_row_totals"]
+    assert len(early) == 1
+    ptr = t.fake.fake_ptr(first + early[0])
+    return ["k_validate_finish" in names, ptr - status if ptr else None]
+
+
 CASES = {k[5:]: f for k, f in list(globals().items()) if k.startswith("case_")}
 
 if __name__ == "__main__":

@@ -75,3 +75,12 @@ def test_calls_that_launch_none_do_not_count(runtime):
 def test_the_call_that_allocates_nothing_has_them_in_two_phases(runtime, P, radix, early):
     """Up to 512 ranks: it waits for a copy behind them."""
     assert fake_hip.run(runtime, "early_use", P, radix, ["direct"] * 2, True) == [early] * 2
+
+
+@pytest.mark.parametrize("P,radix", [(600, 25), (600, 2), (300, 2), (100, 4), (512, 512)])
+def test_what_early_kernels_look_up_is_the_calls_own(runtime, P, radix):
+    """Plans and sizing queries do not wait for a call in flight, and their validation writes the head of the context's status block and the sums
+    of the classes behind it: 64 bytes, and 8 for each of 2016.  A kernel ahead of the host may not have run by then."""
+    by_kernel, at = fake_hip.run(runtime, "verdict", P, radix)
+    assert (at is not None) == by_kernel
+    assert at is None or at >= 64 + 8 * 2016
