@@ -1047,13 +1047,15 @@ int prepare_sizes(Prepared& pr, int dense_option, hipStream_t s, Status& hs, boo
 bool mode_is_fused(const Options& o) { return o.mode != TUNA_MODE_STAGED; }
 
 // Segments in the order of their slot indices, where nothing needs a message's blocks together (batches of rounds, the three
-// stages) and T is in exact size.  Blocks that travel together then lie together in T whatever their digit was -- in message
+// stages).  Blocks that travel together then lie together in T whatever their digit was -- in message
 // order a phase's neighbours are the radix apart in T -- and so do their entries of the matrices and of the places in T.
 // Message order / this, per call: uniform [0, 16] B, P = 2048, r = 46 179 / 163 us, P = 1000, r = 4 146 / 135; up to 40 B, P = 2048, r = 8
 // 396 / 370; up to 250, P = 600, r = 4 153 / 145; up to 1 KiB, P = 2048, r = 45 1736 / 1703, P = 256, r = 4 99.2 / 97.1; 1 KiB, P = 1024, r = 8
 // 1340 / 1329; r = 2, the same order, 1.00; uniform [0, 64] B, P = 4096, r = 64 1176 / 1181; per start: up to 32 B, P = 1000, r = 10
-// 63.7 / 46.4, up to 80, r = 8 108.7 / 104.7.  Message order where it is the faster one: T in slots, whose places do not follow one
-// another (256-byte blocks, P = 2048 as 64 x 32, r = 16 1297 / 1316), and the copy engine's hop (Zipf sizes, per start, P = 200, r = 8
+// 63.7 / 46.4, up to 80, r = 8 108.7 / 104.7.  T in slots, short blocks: per call up to 16 B, P = 1000, r = 32 88 / 70 (message order in wide tiles
+// 79), r = 13 119 / 103, P = 4096, r = 64 1251 / 1151, up to 60, P = 1000, r = 64 108.6 / 90, P = 4096, r = 64 1810 / 1627, r = 16 2794 / 2665, up to 200, P = 600,
+// r = 13 88 / 82; per start up to 60, P = 1000, r = 64 64.5 / 57.3, 128-byte blocks the same.  Message order where it is the faster one: longer blocks with T
+// in slots, whose places do not follow one another (256-byte blocks, P = 2048 as 64 x 32, r = 16 1297 / 1316), and the copy engine's hop (Zipf sizes, per start, P = 200, r = 8
 // 48.7 / 51.4, P = 100, r = 10 20.5 / 22.0); their schedule is made when validation has told (not by the call that allocates nothing).
 int hop_kernels_of(const Prepared& pr);
 bool slot_order(bool fused, bool staggered, int block_count) { return fused && !staggered && block_count == 0; }
@@ -1085,7 +1087,7 @@ int prepare_call(Ctx& c, const Options& opt, const void* sendbuf, const int32_t*
     pr.block_count = opt.block_count;
     rc = prepare_sizes(pr, opt.t_layout, s, hs, empty);
     if (rc != TUNA_OK || *empty || !by_index || pr.dp->host.slots == 0 || long_blocks(pr)) return rc;
-    if (pr.exact_t && !(hop_kernels_of(pr) & TUNA_HOP_ENGINE)) return rc;
+    if ((pr.exact_t || small_blocks(pr)) && !(hop_kernels_of(pr) & TUNA_HOP_ENGINE)) return rc;
     return get_plan(P, Q, rl, rg, pr.fused, /*by_index=*/false, s, &pr.dp);
 }
 
@@ -1267,13 +1269,11 @@ bool sender_phase(const Prepared& pr, const PhaseHost& ph) { return pr.dp->host.
 // Tall tiles where a round has few blocks, and in the first phase of seven rounds and more with the segments in the order of the slot
 // indices.  Wide / tall, us: up to 16 B, per start P = 4000, r = 16 496 / 466, r = 8 612 / 603, P = 2048, r = 46 79.1 / 75.8, per call 854 / 810, 1033 /
 // 1019 and 142 / 139; up to 200, P = 1000, r = 24 119 / 112 and 169 / 166, r = 8 170 / 166 and 235 / 229; up to 60 B the wide ones are up to 1 % ahead (P = 4000, r = 16
-// 1286 / 1300 and 1549 / 1556); five rounds gain 1 to 2 %, three and fewer nothing.  In message order a round's segments lie together: tall only
-// where a call finds the blocks of many rounds itself (k_hop_senders: T in slots), since with hop arrays it is as often the slower one: batches of 16
-// rounds, per start, up to 16 B, P = 2048, r = 46 143 / 154, r = 12 171 / 163, up to 60, r = 8 358 / 363, r = 46 272 / 268; T in slots, P = 600, r = 9 27.5 / 28.5.
+// 1286 / 1300 and 1549 / 1556); five rounds gain 1 to 2 %, three and fewer nothing.  In message order (batches of rounds, staggered schedules) a
+// round's segments lie together, and tall tiles are as often the slower ones: batches of 16 rounds, per start, up to 16 B, P = 2048, r = 46 143 / 154, r = 12 171 /
+// 163, up to 60, r = 8 358 / 363, r = 46 272 / 268.
 bool direct_tall(const Prepared& pr, const PhaseHost& ph) {
-    if ((long long)ph.nz * 16 > ph.nseg) return true;
-    if (ph.dim != 0 || ph.rx != 1) return false;
-    return pr.dp->host.sc.by_index ? ph.nz >= kTallMinRounds : !pr.for_plan && runs_direct(pr) && sender_phase(pr, ph);
+    return (long long)ph.nz * 16 > ph.nseg || (pr.dp->host.sc.by_index && ph.dim == 0 && ph.rx == 1 && ph.nz >= kTallMinRounds);
 }
 // Workgroup columns and steps per workgroup over `nseg` segments of a phase: one step each while that gives no more than 8192 workgroups (four
 // per resident slot of the device), then up to 8 steps; and the rows of partial sums that such a launch stores.

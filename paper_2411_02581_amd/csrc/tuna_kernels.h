@@ -1822,11 +1822,11 @@ __global__ void __launch_bounds__(256) k_hop_direct(const DirectArgs a) { hop_di
 // senders change either from segment to segment -- the first phase, r^x = 1: neighbouring receivers then get neighbouring blocks of a sender, so
 // tiles are TALL, 16 receivers x 16 rounds = 31 senders with up to 16 blocks each, stored as 16 runs of T -- or after r^x
 // segments, and a row of one receiver's segments is a run of a sender's part of T and of R (direct_tall).  The code is k_hop_direct's; what the
-// rule decides is the tile in message order, who moves the own blocks (own_in_first) and what the cost model asks, and traces keep these phases apart.
+// rule decides is who moves the own blocks (own_in_first) and what the cost model asks, and traces keep these phases apart.
 //   Bound by memory, the lines of the matrices and of T's places above all.  Against workgroups that take the blocks that one rank sends
 // (its loads together, its stores a receiver each), us per call: uniform [0, 16] B, P = 2048, r = 46 162 / 148, P = 6000, r = 77 1796 / 1509,
 // P = 1024, r = 32 76.5 / 73; up to 64 B, P = 4096, r = 64 1203 / 1135, up to 60, P = 2048, r = 16 409 / 391, P = 1024, r = 32 93 / 95; up to 40, r = 13
-// 346 / 335; T in slots, 64-byte blocks, P = 4096, r = 64 1393 / 1198, r = 16 445 / 404, 16-byte ones, P = 2048, r = 46 220 / 187.
+// 346 / 335; T in slots, up to 16 B, P = 1000, r = 32 77 / 70, up to 60, r = 64 97 / 90, P = 4096, r = 64 1605 / 1627, r = 16 2586 / 2665.
 // ------------------------------------------------------------------------------------------
 constexpr int kSenderMinRounds = 12, kSenderMaxRounds = 1024;
 template <int LPB, int STREAM, bool DENSE, bool TALL>

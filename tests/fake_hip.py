@@ -186,17 +186,18 @@ def case_recording(t, P, radix, plan):
 def case_routes(t, problems, plan):
     """The payload kernels of each of `problems` and the kernels of their places in T."""
     out = []
-    for P, rpn, rl, rg, longest, q, t_layout, layout in problems:
+    for P, rpn, rl, rg, longest, q, t_layout, layout, *more in problems:
+        options = dict(more[0] if more else {}, t_layout=t_layout)
         counts = np.random.default_rng(P).integers(0, longest // q + 1, (P, P)) * q
         counts[0, P - 1] = longest
         prob = t.problem(counts, **layout)
         first = t.fake.fake_notes()
         if plan:
-            p = t.plan(prob, rl, S1, rpn=rpn, rg=rg, t_layout=t_layout)
+            p = t.plan(prob, rl, S1, rpn=rpn, rg=rg, **options)
             first = t.fake.fake_notes()
             assert t.lib.tuna_start(p, S1) == 0
         else:
-            assert t.call(prob, rl, S1, rpn=rpn, rg=rg, t_layout=t_layout) == 0
+            assert t.call(prob, rl, S1, rpn=rpn, rg=rg, **options) == 0
         out.append([[k[0], k[2]] for k in t.kernels(first) if k[0].startswith(("k_hop", "k_copy", "k_t_", "k_self_copy"))])
         assert t.lib.tuna_release() == 0 or plan
     return out
@@ -372,6 +373,21 @@ def case_verdict(t, P, radix):
     assert len(early) == 1
     ptr = t.fake.fake_ptr(first + early[0])
     return ["k_validate_finish" in names, ptr - status if ptr else None]
+
+
+def case_schedules(t, problems, plan):
+    """How many schedules each of `problems` (as in case_routes) makes."""
+    out = []
+    for P, rpn, rl, rg, longest, q, t_layout, layout in problems:
+        prob = t.problem(np.random.default_rng(P).integers(0, longest // q + 1, (P, P)) * q, **layout)
+        first = t.fake.fake_notes()
+        if plan:
+            assert t.lib.tuna_plan_free(t.plan(prob, rl, S1, rpn=rpn, rg=rg, t_layout=t_layout)) == 0
+        else:
+            assert t.call(prob, rl, S1, rpn=rpn, rg=rg, t_layout=t_layout) == 0
+        out.append([k[0] for k in t.kernels(first)].count("k_build_tables"))
+        assert t.lib.tuna_release() == 0
+    return out
 
 
 CASES = {k[5:]: f for k, f in list(globals().items()) if k.startswith("case_")}

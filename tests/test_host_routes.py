@@ -129,16 +129,23 @@ def test_the_cost_model_prices_blocks_by_the_kernel_that_finds_them(P, radix, lo
     assert rc == 0 and ms == pytest.approx(want, rel=1e-9)
 
 
-@pytest.mark.parametrize("plan,t_layout", [(False, EXACT), (True, EXACT), (False, SLOTS), (True, SLOTS)])
-def test_tall_tiles_where_neighbouring_segments_have_one_sender_each(runtime, plan, t_layout):
-    """With T in exact size segments lie in the order of the slot indices: the first phase runs tall tiles from seven rounds on.  With T in slots
-    they lie in message order: only a call's kernel that finds the blocks of twelve rounds and more itself."""
-    problems = [(600, 0, r, r, n, 4, t_layout, {}) for r in (7, 8, 9, 12, 13, 25) for n in (16, 60, 200)]
+@pytest.mark.parametrize("plan", [False, True])
+def test_tall_tiles_where_neighbouring_segments_have_one_sender_each(runtime, plan):
+    """In the order of the slot indices, with T in exact size and in slots, the first phase runs tall tiles from seven rounds on; in message
+    order, which batches of rounds need, it does not."""
+    problems = [(600, 0, r, r, n, 4, t, {}, o) for r in (7, 8, 9, 12, 13, 25) for n in (16, 60, 200) for t in (EXACT, SLOTS) for o in ({}, {"block_count": 30})]
     for prob, kernels in zip(problems, fake_hip.run(runtime, "routes", problems, plan)):
         hops = [(k, a) for k, a in kernels if k.startswith("k_hop")]
         assert len(hops) > 1, prob
         name, args = hops[0]
-        rounds = prob[2] - 1
-        tall = args[3] if name == "k_hop_senders" else args[1]
-        assert name == ("k_hop_direct" if plan or rounds < 12 else "k_hop_senders"), prob
-        assert tall == (rounds >= 7 if t_layout == EXACT else not plan and rounds >= 12), prob
+        rounds, batches = prob[2] - 1, bool(prob[8])
+        assert name == ("k_hop_direct" if plan or batches or rounds < 12 else "k_hop_senders"), prob
+        assert (args[3] if name == "k_hop_senders" else args[1]) == (rounds >= 7 and not batches), prob
+
+
+@pytest.mark.parametrize("plan", [False, True])
+def test_short_blocks_keep_the_order_of_the_slot_indices(runtime, plan):
+    """Whatever T's layout is: no second schedule is made when validation has told.  Longer blocks with T in slots have one."""
+    problems = [(300, 0, r, r, n, 4, t, {"gap": 4}) for r in (4, 20) for n in (16, 200, 1000) for t in (EXACT, SLOTS)]
+    for prob, tables in zip(problems, fake_hip.run(runtime, "schedules", problems, plan)):
+        assert tables == (2 if prob[6] == SLOTS and prob[4] == 1000 else 1), prob
