@@ -1,5 +1,5 @@
-"""The validation pass at the sizes where its shape changes: one and several 64 x 64 tiles, workgroups of 16 and of 4
-waves (22 x 22 and 23 x 23 tiles), rows added up by the host (at most 64 workgroups and 24 classes of waiting blocks)
+"""The validation pass at the sizes where its shape changes: one and several 64 x 64 tiles, workgroups that take one and
+two of them (22 x 22 and 23 x 23 tiles), rows added up by the host (at most 64 workgroups and 24 classes of waiting blocks)
 and by a kernel.  A valid problem arrives byte for byte, and a wrong entry anywhere -- also in the last row and column
 -- is reported with its code before anything moves."""
 import numpy as np

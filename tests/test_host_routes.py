@@ -38,8 +38,7 @@ def _phases(P, rpn, rl, rg):
 
 
 def _by_senders(rounds, blocks):
-    """Up to 2100 ranks a workgroup takes 256 blocks of a rank; it leaves a row of partial sums per round, for which there is
-    room if there are no more than blocks."""
+    """Many rounds, up to about 256."""
     return 12 <= rounds <= 1024 and (blocks + 255) // 256 * rounds <= blocks
 
 
